@@ -11,6 +11,45 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 namespace pl {
 
+// ---- wavefront reductions: 16 lanes by data-parallel primitives (a few cycles a step instead of an LDS
+// round trip), the four rows of 16 by shuffles; fixed order, every lane ends with the result -------------
+#ifdef __HIP_DEVICE_COMPILE__
+template <int CTRL>
+__device__ inline int dpp_i(int v) { return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false); }
+template <int CTRL>
+__device__ inline float dpp_f(float v) { return __builtin_bit_cast(float, dpp_i<CTRL>(__builtin_bit_cast(int, v))); }
+#else
+template <int CTRL>
+__device__ inline int dpp_i(int v) { return v; }
+template <int CTRL>
+__device__ inline float dpp_f(float v) { return v; }
+#endif
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
+__device__ inline float wave_sum(float v) {
+  v += dpp_f<DPP_XOR1>(v);
+  v += dpp_f<DPP_XOR2>(v);
+  v += dpp_f<DPP_HALF_MIRROR>(v);
+  v += dpp_f<DPP_MIRROR>(v);
+  v += __shfl_xor(v, 16, 64);
+  return v + __shfl_xor(v, 32, 64);
+}
+__device__ inline float wave_max(float v) {
+  v = fmaxf(v, dpp_f<DPP_XOR1>(v));
+  v = fmaxf(v, dpp_f<DPP_XOR2>(v));
+  v = fmaxf(v, dpp_f<DPP_HALF_MIRROR>(v));
+  v = fmaxf(v, dpp_f<DPP_MIRROR>(v));
+  v = fmaxf(v, __shfl_xor(v, 16, 64));
+  return fmaxf(v, __shfl_xor(v, 32, 64));
+}
+__device__ inline int wave_min(int v) {
+  v = min(v, dpp_i<DPP_XOR1>(v));
+  v = min(v, dpp_i<DPP_XOR2>(v));
+  v = min(v, dpp_i<DPP_HALF_MIRROR>(v));
+  v = min(v, dpp_i<DPP_MIRROR>(v));
+  v = min(v, __shfl_xor(v, 16, 64));
+  return min(v, __shfl_xor(v, 32, 64));
+}
+
 // ---- KV page geometry (one layer, one page, one kv head: K block then V block) ---------------
 // Tokens of a page are grouped in runs of 32 (t = 32 r + u).  Both blocks are laid out so that the
 // 64 lanes of a wavefront read one MFMA operand with a single fully contiguous 1 KiB load.

@@ -352,6 +352,29 @@ def test_sampler_tokens_bit_exact_and_logprobs_close(n, V):
         assert abs(lp[r] - lp_ref) <= 1e-4 * max(1.0, abs(lp_ref))
 
 
+@pytest.mark.parametrize("n,V", [(1, 4), (2, 8188), (2, 8192), (3, 8196), (26, 152064), (27, 152064), (512, 4096)])
+def test_sampler_at_slice_and_launch_boundaries_with_masked_entries(n, V):
+    """One slice and a little more or less, both sides of the choice of threads per slice (512 workgroups), and rows
+    with masked entries: -inf, the lowest float, a whole masked slice, equal logits."""
+    rng = np.random.default_rng(V * 5 + n)
+    logits = (rng.standard_normal((n, V)) * 3).astype(np.float32)
+    logits[0, : V // 2] = -np.inf
+    if n > 1:
+        logits[1] = np.float32(-1.25)
+    if n > 2:
+        logits[2, ::3] = np.finfo(np.float32).min
+        logits[2, : min(8192, V // 2)] = -np.inf
+    seq_id = rng.integers(0, 2**63, size=n, dtype=np.uint64)
+    pos = rng.integers(0, 16384, size=n).astype(np.int32)
+    temps = rng.choice([1.0, 0.7, 1.5], n).astype(np.float32)
+    tok, lp = _gpu_sample(logits, seq_id, pos, temps, np.full(n, -1, np.int32), 77)
+    for r in list(range(min(n, 6))) + [n - 1]:
+        with np.errstate(over="ignore"):             # the lowest float at T < 1 becomes -inf
+            t_ref, lp_ref = sampler.sample_row(logits[r], float(temps[r]), 77, int(seq_id[r]), int(pos[r]))
+        assert tok[r] == t_ref, (r, tok[r], t_ref)
+        assert abs(lp[r] - lp_ref) <= 1e-4 * max(1.0, abs(lp_ref))
+
+
 def test_sampler_ties_resolve_to_the_lowest_index_like_the_oracle():
     """Constant logits: the winner is decided by the noise alone, and with 2^23 distinct uniforms over
     152064 entries equal maxima do occur; both sides must pick the lowest index."""
