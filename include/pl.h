@@ -201,7 +201,7 @@ int pl_swap_poll(pl_engine *e, int32_t *staged_ready, uint32_t *active_version);
 int pl_add_sequence(pl_engine *e, uint64_t seq_id, const int32_t *prompt, int32_t n_prompt,
                     int32_t max_new, float temperature, int32_t *out_slot);
 /* Batched prompt reading on refill ("add prompts", Alg. 2): reads the positions of the slot's prompt
- * that have not been read yet, except the last one, in passes of up to 256 positions
+ * that have not been read yet, except the last one, in passes of up to 1024 positions
  * through the same kernels as a decode step (rows = consecutive positions of one sequence, causal
  * because row i attends to positions <= its own), under the active weights.  It leaves exactly the
  * keys and values that reading those tokens one per step would leave (up to bf16 rounding of
@@ -295,6 +295,14 @@ int pl_debug_gemm_plan(int32_t M_max, int32_t N, int32_t K, int32_t mode, int32_
  * are bit-identical for every M <= M_max.  PL_E_INVAL (nothing launched) for unsupported shapes. */
 int pl_debug_gemm_planned(const void *x, const void *w, void *y, void *ws, int32_t M_max, int32_t M, int32_t N, int32_t K,
                           int32_t mode, void *stream);
+
+/* The product of up to 1024 rows as the prompt passes of such an engine launch it when they hold more than
+ * 256 rows: the K slices of an output element are added up, in slice order, by the workgroup that owns it.
+ * y is one slice (mode 0: device fp32 [M, N]; mode 1: device bf16 [M, N / 2]), bit-identical to adding
+ * pl_debug_gemm_planned's slices in order (mode 1: to its result).  PL_E_INVAL (nothing launched) for
+ * unsupported shapes. */
+int pl_debug_gemm_folded(const void *x, const void *w, void *y, int32_t M_max, int32_t M, int32_t N, int32_t K, int32_t mode,
+                         void *stream);
 
 /* Launch a kernel that only reads the device buffer (contiguous 16-byte loads, 8 in flight per lane;
  * ordinary loads, or non-temporal ones if `nontemporal` is non-zero) on `stream`; returns the number of bytes it reads (a multiple of 256 MiB, <= nbytes) or a negative

@@ -27,7 +27,9 @@ constexpr int LDS_ROW = 72;     // padded row length (elements) of the x tile in
 //
 // gemm_tile computes one tile (column tile at n_tile0, rows from m0, K slice `split`) with the whole
 // workgroup; the kernels below are thin wrappers that pick the tile(s) of a workgroup.
-template <int WM, int WN, int AT, int BT, int MODE>
+// FOLD: all K slices of `ksteps` k-steps in one go: every slice's sum starts from zero and is added to the
+// running total in slice order, so the one result equals the sum a consumer makes of separate slices bit for bit.
+template <int WM, int WN, int AT, int BT, int MODE, bool FOLD = false>
 __device__ __forceinline__ void gemm_tile(bf16_t (*xs)[WM * AT * 32 * LDS_ROW], const bf16_t *__restrict__ X,
                                           const bf16_t *__restrict__ W, void *__restrict__ Yv, int M, int N, int K,
                                           int ksteps, int n_tile0, int m0, int split, int n_end, int ldy, int y_col0) {
@@ -39,7 +41,7 @@ __device__ __forceinline__ void gemm_tile(bf16_t (*xs)[WM * AT * 32 * LDS_ROW], 
   const int wm = wave / WN, wn = wave % WN;
   const int n0 = n_tile0 + wn * BT * 32;
   const int kbeg = split * ksteps * BK;
-  const int nks = min(ksteps, K / BK - split * ksteps);
+  const int nks = FOLD ? K / BK : min(ksteps, K / BK - split * ksteps);
   const int lrow = l & 31, half = l >> 5;
 
   // Buffer addressing: one resource per operand, a per-lane byte offset in a VGPR, everything that
@@ -164,16 +166,46 @@ __device__ __forceinline__ void gemm_tile(bf16_t (*xs)[WM * AT * 32 * LDS_ROW], 
   using I2 = std::integral_constant<int, 2>; using I3 = std::integral_constant<int, 3>;
   using Y = std::true_type; using No = std::false_type;
   int ks = 0;
+  f32x16 tot[FOLD ? AT : 1][FOLD ? BT : 1];
+  int slice_end = ksteps;
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int a = 0; a < AT; ++a)
+#pragma unroll
+      for (int b = 0; b < BT; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) tot[a][b][i] = 0.f;
+  }
+  auto fold = [&]() {
+    if constexpr (FOLD) {
+#pragma unroll
+      for (int a = 0; a < AT; ++a)
+#pragma unroll
+        for (int b = 0; b < BT; ++b)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) { tot[a][b][i] += acc[a][b][i]; acc[a][b][i] = 0.f; }
+    }
+  };
   for (; ks < nks - 4; ks += 4) {
+    if (FOLD && ks == slice_end) { fold(); slice_end += ksteps; }
     kstep(I0{}, Y{}, Y{}, Y{}, ks);
     kstep(I1{}, Y{}, Y{}, Y{}, ks + 1);
     kstep(I2{}, Y{}, Y{}, Y{}, ks + 2);
     kstep(I3{}, Y{}, Y{}, Y{}, ks + 3);
   }
+  if (FOLD && ks == slice_end) fold();
   kstep(I0{}, Y{}, Y{}, Y{}, ks);
   kstep(I1{}, Y{}, No{}, Y{}, ks + 1);
   kstep(I2{}, No{}, No{}, Y{}, ks + 2);
   kstep(I3{}, No{}, No{}, No{}, ks + 3);
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int a = 0; a < AT; ++a)
+#pragma unroll
+      for (int b = 0; b < BT; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[a][b][i] += tot[a][b][i];
+  }
 
   // epilogue: accumulator register i of lane l is row (i/4)*8 + (l/32)*4 + i%4, column l%32
 #pragma unroll
@@ -421,6 +453,19 @@ __global__ __launch_bounds__(256) void gemm_kernel(const bf16_t *__restrict__ X,
   gemm_tile<WM, WN, AT, BT, MODE>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, blockIdx.y, n_end, ldy, y_col0);
 }
 
+// Many rows (prompt passes): flat grid in XCD-local groups of row tiles as above, all K slices of a tile in
+// one workgroup.
+template <int WM, int WN, int AT, int BT, int MODE>
+__global__ __launch_bounds__(256) void gemm_fold_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
+                                                        void *__restrict__ Yv, int M, int N, int K, int ksteps,
+                                                        int n_base, int n_end, int nrow) {
+  constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
+  __shared__ __attribute__((aligned(16))) bf16_t xs[2][BM * LDS_ROW];
+  const int rtile = (blockIdx.x >> 3) % nrow, ctile = (blockIdx.x / (8 * nrow)) * 8 + (blockIdx.x & 7);
+  if (n_base + ctile * BN >= n_end) return;   // padding of the flat grid (uniform for the workgroup)
+  gemm_tile<WM, WN, AT, BT, MODE, true>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, 0, n_end, N, 0);
+}
+
 // The SwiGLU product of a 129..256-row batch in ONE launch of one workgroup per compute unit.  Workgroup i
 // computes main tile i (128 x 256, row tiles paired on an XCD as above) with the SwiGLU epilogue.  The
 // columns left over beyond the last full round of tiles, [n_main, N), are cut into 128 x 256 tiles and
@@ -520,6 +565,30 @@ int launch_by_id(int cfg, const Launch &L) {
     case GEMM_256x64P: return launch_cfg<4, 1, 2, 2>(L);
     default: return -1;
   }
+}
+
+// Columns [n_begin, n_end) of a product of many rows, K in `splits` slices added up in the workgroup (one slice:
+// the plain kernel, which needs no second set of accumulators).
+template <int WM, int WN, int AT, int BT>
+int launch_fold_cfg(Launch L) {
+  constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
+  if (BT == 1 && L.mode == 1) return -1;
+  if (L.n_end <= L.n_begin) return 0;
+  const int splits = L.splits;
+  L.splits = 1;
+  L.paired = true;
+  if (splits == 1) return launch_cfg<WM, WN, AT, BT>(L);
+  const int nrow = (L.M + BM - 1) / BM, grid = ((L.n_end - L.n_begin + BN - 1) / BN + 7) / 8 * 8 * nrow;
+  const int ksteps = 4 * ((L.K / (4 * BK) + splits - 1) / splits);
+  if (L.mode == 0)
+    hipLaunchKernelGGL((gemm_fold_kernel<WM, WN, AT, BT, 0>), dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps,
+                       L.n_begin, L.n_end, nrow);
+  else if constexpr (BT == 2 && AT <= 2)
+    hipLaunchKernelGGL((gemm_fold_kernel<WM, WN, AT, BT, 1>), dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps,
+                       L.n_begin, L.n_end, nrow);
+  else
+    return -1;
+  return hipGetLastError() == hipSuccess ? 0 : -7;
 }
 
 bool splits_valid(int K, int splits) {
@@ -670,6 +739,42 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
   if (rc || n_main == N) return rc;
   return launch_gemm_cfg(GEMM_64x128, x, w, y, ws, M, N, K, mode, mode == 1 ? ks.rem_splits : ks.splits, n_main, N,
                          false, s);
+}
+
+// A product of up to GEMM_MAX_ROWS rows with all K slices of an element added up in the workgroup, in slice
+// order: y is ONE slice (mode 0: [M][N]; mode 1: the SwiGLU result), equal bit for bit to what a consumer of
+// launch_gemm's slices gets by adding them in order.  From 257 rows on the tiles alone fill the chip, and the
+// partial sums that a K split writes and its consumer reads (33 MB per 256 rows of the 7B down projection)
+// are saved.  Measured at 1024 rows against four 256-row launches, consumers' reads not counted: QKV / O / gate-up
+// / down of the 1.5B shape 14 / 13 / 73 / 52 against 50 / 43 / 116 / 100 us, of the 7B shape 53 / 37 / 288 / 189
+// against 82 / 71 / 350 / 200 us.
+int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, int K, int mode, const GemmSplit &ks, hipStream_t s) {
+  if (M < 1 || M > GEMM_MAX_ROWS || K % (4 * BK) || N % 32 || !splits_valid(K, ks.splits)) return -1;
+  if (mode != 0 && mode != 1) return -1;
+  if (mode == 1 && (N % 64 || ks.n_main % 64 || !splits_valid(K, ks.rem_splits))) return -1;
+  if (mode == 0 && ks.n_main != N) return -1;
+  if (ks.n_main < 0 || ks.n_main > N) return -1;
+  if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
+  Launch L{x, w, y, M, N, K, mode, ks.splits, 0, ks.n_main, N, 0, true, s};
+  if (mode == 1) {
+    // 7B shape, 1024 rows: 288 us with 128 x 256 tiles, 302 with 256 x 128, 349 with 128 x 128; 1.5B shape (a third of
+    // the tiles): 78, 85, 73
+    const int rc = ks.splits == 1 && ks.n_main >= 128 * 256 ? launch_fold_cfg<1, 4, 4, 2>(L) : launch_fold_cfg<2, 2, 2, 2>(L);
+    if (rc || ks.n_main == N) return rc;
+    L.n_begin = ks.n_main; L.n_end = N; L.splits = ks.rem_splits;
+    return launch_fold_cfg<2, 2, 2, 2>(L);
+  }
+  // The shape with the least time of its fullest compute unit: a k-step of 64 takes 0.26 / 0.38 / 0.65 / 1.05 us per
+  // resident 64 x 64 / 128 x 64 / 128 x 128 / 128 x 256 tile (fits of a sweep over the products of the 1.5B, 7B
+  // and 32B shapes at 511 and 1024 rows; the choice is the measured best in all 18).
+  auto cost = [&](int bm, int bn, double t) { return (((M + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256 * t; };
+  const double c[4] = {cost(64, 64, 0.26), cost(128, 64, 0.38), cost(128, 128, 0.65), cost(128, 256, 1.05)};
+  switch (std::min_element(c, c + 4) - c) {
+    case 0: return launch_fold_cfg<2, 2, 1, 1>(L);
+    case 1: return launch_fold_cfg<2, 2, 2, 1>(L);
+    case 2: return launch_fold_cfg<2, 2, 2, 2>(L);
+    default: return launch_fold_cfg<1, 4, 4, 2>(L);
+  }
 }
 
 }  // namespace pl

@@ -52,7 +52,8 @@ __device__ inline float block_sum(float v) {
   return t;
 }
 
-// h[row] += sum_s parts[s][row]; a[row] = rmsnorm(h[row]) * g.  Partials are added in slice order.
+// h[row] += sum_s parts[s][row]; a[row] = rmsnorm(h[row]) * g.  The slices are added up in slice order, their
+// sum to h (a product that comes as one slice, added up the same way before, gives the same bits).
 // One workgroup of NT threads per row, NV 16-byte pieces per thread (NT * NV * 4 >= d); the row stays in
 // registers between the two passes.
 template <int NT, int NV>
@@ -66,7 +67,7 @@ __global__ __launch_bounds__(NT) void resid_rmsnorm_kernel(float *h, const float
   for (int it = 0; it < NV; ++it) {
     const int idx = threadIdx.x + it * NT;
     if (idx < d4) {
-      float4 x = h4[idx];
+      float4 x = h4[idx], y = make_float4(0.f, 0.f, 0.f, 0.f);
       // loads of up to 8 slices are issued together, the adds stay in slice order
       for (int s0 = 0; s0 < splits; s0 += 8) {
         float4 p[8];
@@ -75,8 +76,9 @@ __global__ __launch_bounds__(NT) void resid_rmsnorm_kernel(float *h, const float
           if (s0 + u < splits) p[u] = ((const float4 *)(parts + ((int64_t)(s0 + u) * n + row) * d))[idx];
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-          if (s0 + u < splits) { x.x += p[u].x; x.y += p[u].y; x.z += p[u].z; x.w += p[u].w; }
+          if (s0 + u < splits) { y.x += p[u].x; y.y += p[u].y; y.z += p[u].z; y.w += p[u].w; }
       }
+      x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
       h4[idx] = x;
       v[it] = x;
       ss += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;

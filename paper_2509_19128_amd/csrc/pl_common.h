@@ -101,6 +101,9 @@ int64_t gemm_workspace_elems(int M_max, int N, const GemmSplit &ks);
 // ws: fp32 workspace of gemm_workspace_elems (mode 1 with split K), else may be null
 int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int N, int K, int mode,
                 const GemmSplit &ks, hipStream_t s);
+constexpr int GEMM_MAX_ROWS = 1024;   // of launch_gemm_folded
+int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, int K, int mode, const GemmSplit &ks,
+                       hipStream_t s);
 int launch_gemm_cfg(int cfg, const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int N, int K, int mode,
                     int splits, int n_begin, int n_end, bool paired, hipStream_t s);
 int gemm_tile_rows(int cfg);

@@ -75,7 +75,8 @@ struct pl_engine {
   pl_model_cfg cfg{};
   bool dry = false;
   int G = 1, page_tokens = 64, pages_per_seq = 0;
-  int rows_cap = 0;   // rows the work buffers hold: max(max_batch, 256), so cache-only passes can take 256 rows
+  int rows_cap = 0;    // rows the decode step's work buffers hold: max(max_batch, 256)
+  int pass_rows = 0;   // rows a cache-only pass takes, and its work buffers hold
   int64_t n_pages = 0, layer_stride = 0, page_stride = 0;   // elements
   // weights
   std::vector<Tensor> layout;
@@ -117,9 +118,9 @@ struct pl_engine {
     int32_t *m_input(bool dev) { return m_pos(dev) + rows_cap; }
     int32_t *m_forced(bool dev) { return m_input(dev) + rows_cap; }
     float *m_inv_t(bool dev) { return (float *)(m_forced(dev) + rows_cap); }
+    int64_t meta_bytes() const { return (int64_t)rows_cap * (4 * 5 + 8); }
   };
   Work wk[2];
-  int64_t meta_bytes = 0;
   // Host images of the cache-only passes in flight: a pass's image must stay intact until its copy to
   // the device has run, so the passes take images from a ring; each entry carries the events that
   // time its pass.
@@ -252,7 +253,7 @@ int alloc_work(pl_engine *e, pl_engine::Work &w, int64_t R, int64_t parts_elems,
   const int64_t wide = e->esz / 2;   // the activation buffers are declared bf16; the fp32 build needs twice the bytes
   int rc;
   w.rows_cap = (int)R;
-  if ((rc = dev_alloc(&w.meta_d, e->meta_bytes))) return rc;
+  if ((rc = dev_alloc(&w.meta_d, w.meta_bytes()))) return rc;
   if ((rc = dev_alloc(&w.h, R * d))) return rc;
   if ((rc = dev_alloc(&w.a, R * d * wide))) return rc;
   if ((rc = dev_alloc(&w.parts, parts_elems))) return rc;
@@ -266,7 +267,7 @@ int alloc_work(pl_engine *e, pl_engine::Work &w, int64_t R, int64_t parts_elems,
   if ((rc = dev_alloc(&w.attn_po, np * c.head_dim))) return rc;
   if ((rc = dev_alloc(&w.attn_pml, np * 2))) return rc;
   if ((rc = dev_alloc(&w.attn_work, pl::attention_worklist_ints((int)R, e->attn_max_chunks)))) return rc;
-  if (pinned_image) HIP_TRY(hipHostMalloc((void **)&w.meta_h, (size_t)e->meta_bytes, hipHostMallocDefault));
+  if (pinned_image) HIP_TRY(hipHostMalloc((void **)&w.meta_h, (size_t)w.meta_bytes(), hipHostMallocDefault));
   return PL_OK;
 }
 
@@ -277,6 +278,8 @@ void free_work(pl_engine::Work &w) {
   w = pl_engine::Work{};
 }
 
+// Passes of more rows than this add up a product's K slices inside the GEMM (launch_gemm_folded).
+constexpr int SLICED_ROWS = 256;
 constexpr int PASS_RING = 8;   // host metadata images of cache-only passes that may wait on the device at once
 
 int alloc_device(pl_engine *e) {
@@ -305,19 +308,34 @@ int alloc_device(pl_engine *e) {
   e->ks_gu = pl::gemm_pick_split(B, 2 * c.d_ffn, (int)d, 1);
   e->ks_d = pl::gemm_pick_split(B, (int)d, c.d_ffn, 0);
   e->ks_lm = pl::GemmSplit{1, c.vocab, 1};
-  const int64_t R = e->rows_cap;   // rows of the activation buffers (cache-only passes take up to 256 rows)
-  int64_t parts = std::max(std::max(std::max(e->ks_qkv.splits * wq, e->ks_o.splits * d), e->ks_d.splits * d) * R,
-                           pl::gemm_workspace_elems((int)R, 2 * c.d_ffn, e->ks_gu));
-  if (e->f32) parts = R * std::max(wq, 2 * (int64_t)c.d_ffn);   // the fp32 build keeps whole products there
+  // fp32 partial sums of a work set: K slices for passes of up to SLICED_ROWS rows, one folded slice beyond
+  auto parts_elems = [&](int64_t R) {
+    if (e->f32) return R * std::max(wq, 2 * (int64_t)c.d_ffn);   // the fp32 build keeps whole products there
+    const int64_t sliced = std::min<int64_t>(R, std::max(B, SLICED_ROWS));
+    const int64_t slices = std::max(std::max(std::max(e->ks_qkv.splits * wq, e->ks_o.splits * d), e->ks_d.splits * d) * sliced,
+                                    pl::gemm_workspace_elems((int)sliced, 2 * c.d_ffn, e->ks_gu));
+    return std::max(slices, std::max(wq, d) * R);
+  };
   // the chunk length is fixed by max_batch alone, so a sequence's attention result never depends on
   // how many rows a pass holds
   e->attn_chunk = pl::attention_chunk_tokens(B, c.n_kv_heads, c.max_context);
   e->attn_max_chunks = (c.max_context + e->attn_chunk - 1) / e->attn_chunk;
-  if ((rc = alloc_work(e, e->wk[0], R, parts, true))) return rc;
-  if ((rc = alloc_work(e, e->wk[1], R, parts, false))) return rc;
+  if ((rc = alloc_work(e, e->wk[0], e->rows_cap, parts_elems(e->rows_cap), true))) return rc;
+  // The passes' buffers give way where memory is tight: passes of rows_cap rows do the same, more slowly.
+  auto alloc_pass_work = [&](int rows) {
+    hipStream_t s = e->wk[1].stream;
+    free_work(e->wk[1]);
+    (void)hipGetLastError();
+    e->wk[1].stream = s;
+    e->pass_rows = rows;
+    return alloc_work(e, e->wk[1], rows, parts_elems(rows), false);
+  };
+  rc = alloc_pass_work(e->pass_rows);
+  if (rc == PL_E_NOMEM && e->pass_rows > e->rows_cap) rc = alloc_pass_work(e->rows_cap);
+  if (rc) return rc;
   e->ring.resize(PASS_RING);
   for (auto &im : e->ring) {
-    HIP_TRY(hipHostMalloc((void **)&im.meta_h, (size_t)e->meta_bytes, hipHostMallocDefault));
+    HIP_TRY(hipHostMalloc((void **)&im.meta_h, (size_t)e->wk[1].meta_bytes(), hipHostMallocDefault));
     HIP_TRY(hipEventCreate(&im.ev_begin));
     HIP_TRY(hipEventCreate(&im.ev_end));
   }
@@ -342,7 +360,9 @@ int alloc_device(pl_engine *e) {
     set_pool_pages(e, e->n_pages);
   }
   const int64_t pool_elems = e->layer_stride * c.n_layers;
-  if ((rc = dev_alloc(&e->kv_pool, pool_elems * e->esz))) return rc;
+  rc = dev_alloc(&e->kv_pool, pool_elems * e->esz);
+  if (rc == PL_E_NOMEM && e->pass_rows > e->rows_cap && !(rc = alloc_pass_work(e->rows_cap))) rc = dev_alloc(&e->kv_pool, pool_elems * e->esz);
+  if (rc) return rc;
   // Every position a kernel may touch must hold a finite value: masked soft-max weights are
   // exactly 0, and 0 * finite stays 0.
   HIP_TRY(hipMemsetAsync(e->kv_pool, 0, (size_t)pool_elems * e->esz, e->s_dec));
@@ -433,6 +453,11 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   const bf16_t *gf = base + e->layout[e->layout.size() - 2].offset;
   const bf16_t *lm = base + e->layout.back().offset;
   int rc = 0;
+  const bool fold = prefill && n > std::max(c.max_batch, SLICED_ROWS);   // many rows: the products come as one slice each
+  auto gemm = [&](const bf16_t *x, const bf16_t *wt, void *y, float *ws, int N, int K, int mode, const pl::GemmSplit &ks) {
+    return fold ? pl::launch_gemm_folded(x, wt, y, n, N, K, mode, ks, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, s);
+  };
+  auto slices = [&](const pl::GemmSplit &ks) { return fold ? 1 : ks.splits; };
   rc |= pl::launch_rope_tables(w.m_pos(true), w.cs, w.ctx_len, n, c.head_dim, c.rope_theta, s);
   rc |= pl::launch_attention_worklist(w.ctx_len, w.m_row_slot(true), w.pt, w.attn_work, n, e->attn_max_chunks,
                                       e->attn_chunk, e->page_tokens, e->pages_per_seq, s);
@@ -443,9 +468,9 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
     const LayerW lw = layer_weights(e, l);
     bf16_t *kv_layer = (bf16_t *)e->kv_pool + (int64_t)l * e->layer_stride;
     if (timed) mark(e, CAT_OTHER);
-    rc |= pl::launch_gemm(w.a, lw.w_qkv, w.parts, nullptr, n, wq, d, 0, e->ks_qkv, s);
+    rc |= gemm(w.a, lw.w_qkv, w.parts, nullptr, wq, d, 0, e->ks_qkv);
     if (timed) mark(e, CAT_GEMM);
-    rc |= pl::launch_rope_append(w.parts, e->ks_qkv.splits, w.cs, w.m_pos(true), w.m_row_slot(true), w.pt,
+    rc |= pl::launch_rope_append(w.parts, slices(e->ks_qkv), w.cs, w.m_pos(true), w.m_row_slot(true), w.pt,
                                  w.q_rot, kv_layer, n, c.n_q_heads, c.n_kv_heads, c.head_dim, e->page_tokens,
                                  e->pages_per_seq, s);
     pl::AttnParams ap{};
@@ -466,15 +491,15 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
     } else {
       rc |= pl::launch_attention(ap, s);
     }
-    rc |= pl::launch_gemm(w.attn_out, lw.w_o, w.parts, nullptr, n, d, qd, 0, e->ks_o, s);
+    rc |= gemm(w.attn_out, lw.w_o, w.parts, nullptr, d, qd, 0, e->ks_o);
     if (timed) mark(e, CAT_GEMM);
-    rc |= pl::launch_resid_rmsnorm(w.h, w.parts, e->ks_o.splits, lw.g2, w.a, n, d, c.rms_eps, s);
+    rc |= pl::launch_resid_rmsnorm(w.h, w.parts, slices(e->ks_o), lw.g2, w.a, n, d, c.rms_eps, s);
     if (timed) mark(e, CAT_OTHER);
-    rc |= pl::launch_gemm(w.a, lw.w_gu, w.mid, w.parts, n, 2 * c.d_ffn, d, 1, e->ks_gu, s);
-    rc |= pl::launch_gemm(w.mid, lw.w_d, w.parts, nullptr, n, d, c.d_ffn, 0, e->ks_d, s);
+    rc |= gemm(w.a, lw.w_gu, w.mid, w.parts, 2 * c.d_ffn, d, 1, e->ks_gu);
+    rc |= gemm(w.mid, lw.w_d, w.parts, nullptr, d, c.d_ffn, 0, e->ks_d);
     if (timed) mark(e, CAT_GEMM);
     const bf16_t *g_next = (l + 1 < c.n_layers) ? layer_weights(e, l + 1).g1 : gf;
-    rc |= pl::launch_resid_rmsnorm(w.h, w.parts, e->ks_d.splits, g_next, w.a, n, d, c.rms_eps, s);
+    rc |= pl::launch_resid_rmsnorm(w.h, w.parts, slices(e->ks_d), g_next, w.a, n, d, c.rms_eps, s);
   }
   if (prefill) return rc ? fail(PL_E_HIP, "kernel launch failed: %s", hipGetErrorString(hipGetLastError())) : PL_OK;
   mark(e, CAT_OTHER);
@@ -635,13 +660,13 @@ int drain_passes(pl_engine *e) {
 }
 
 // Cache-only passes: rows (slot, position, token) go through the decode kernels in prefill mode, in
-// groups of up to 256, on the second work set's stream; the rows of one slot must come in position
+// groups of up to pass_rows, on the second work set's stream; the rows of one slot must come in position
 // order, because a row attends to the keys and values that earlier rows of its slot (in this or an
 // earlier group) leave.  Returns once everything is enqueued; the caller waits (or records an event).
 int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::vector<int32_t> &positions,
                   const std::vector<int32_t> &tokens, double *ms_total, uint64_t *passes) {
   const pl_model_cfg &c = e->cfg;
-  const int rows_max = 256;
+  const int rows_max = e->pass_rows;
   pl_engine::Work &w = e->wk[1];
   if (!e->dry) HIP_TRY(hipSetDevice(c.device));
   const size_t total = slots.size();
@@ -679,7 +704,7 @@ int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::ve
       // The dirty flag stays: the decode stream sends the table to its own copy.
       if (r0 == 0)
         HIP_TRY(hipMemcpyAsync(w.pt, e->pt_h, (size_t)c.max_batch * e->pages_per_seq * 4, hipMemcpyHostToDevice, s));
-      HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)e->meta_bytes, hipMemcpyHostToDevice, s));
+      HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)w.meta_bytes(), hipMemcpyHostToDevice, s));
       HIP_TRY(hipEventRecord(im.ev_begin, s));
       int rc = run_step(e, w, n, true);
       if (rc) return rc;
@@ -758,10 +783,11 @@ int pl_create(const pl_model_cfg *cfg, pl_engine **out) {
   e->seqs.resize(cfg->max_batch);
   set_pool_pages(e, n_pages);
   e->rows_cap = std::max(cfg->max_batch, 256);
-  e->meta_bytes = (int64_t)e->rows_cap * (4 * 5 + 8);
-  e->wk[0].rows_cap = e->wk[1].rows_cap = e->rows_cap;
+  e->pass_rows = e->f32 ? e->rows_cap : pl::GEMM_MAX_ROWS;   // the fp32 test build keeps whole products: fewer rows
+  e->wk[0].rows_cap = e->rows_cap;
+  e->wk[1].rows_cap = e->pass_rows;
   if (e->dry) {
-    e->wk[0].meta_h = (char *)calloc(1, (size_t)e->meta_bytes);
+    e->wk[0].meta_h = (char *)calloc(1, (size_t)e->wk[0].meta_bytes());
     if (!e->wk[0].meta_h) { delete e; return fail(PL_E_NOMEM, "out of host memory"); }
   } else {
     if (cfg->device < 0) { delete e; return fail(PL_E_INVAL, "bad device"); }
@@ -1155,7 +1181,7 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
       HIP_TRY(hipMemcpyAsync(w.pt, e->pt_h, (size_t)c.max_batch * e->pages_per_seq * 4, hipMemcpyHostToDevice, s));
       e->pt_dirty = false;
     }
-    HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)e->meta_bytes, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)w.meta_bytes(), hipMemcpyHostToDevice, s));
     HIP_TRY(hipEventRecord(e->ev_a, s));
     e->prof_n = 0;   // a replayed graph records no per-kernel events: nothing of an earlier step may be counted again
     int rc = run_step(e, w, n);
@@ -1486,6 +1512,18 @@ int pl_debug_gemm_planned(const void *x, const void *w, void *y, void *ws, int32
   const pl::GemmSplit ks = pl::gemm_pick_split(M_max, N, K, mode);
   if (!ws && mode == 1 && pl::gemm_workspace_elems(M_max, N, ks) > 0) return fail(PL_E_INVAL, "this plan needs a workspace");
   int rc = pl::launch_gemm((const bf16_t *)x, (const bf16_t *)w, y, (float *)ws, M, N, K, mode, ks, (hipStream_t)stream);
+  if (rc == -1) return fail(PL_E_INVAL, "unsupported GEMM shape M=%d N=%d K=%d mode=%d", M, N, K, mode);
+  if (rc) return fail(PL_E_HIP, "GEMM launch failed");
+  return PL_OK;
+}
+
+int pl_debug_gemm_folded(const void *x, const void *w, void *y, int32_t M_max, int32_t M, int32_t N, int32_t K, int32_t mode,
+                         void *stream) {
+  if (!x || !w || !y) return fail(PL_E_INVAL, "NULL argument");
+  if (M_max < 1 || M_max > 512 || M < 1 || M > pl::GEMM_MAX_ROWS || N < 32 || K < 256 || (mode != 0 && mode != 1))
+    return fail(PL_E_INVAL, "unsupported GEMM shape");
+  int rc = pl::launch_gemm_folded((const bf16_t *)x, (const bf16_t *)w, y, M, N, K, mode, pl::gemm_pick_split(M_max, N, K, mode),
+                                  (hipStream_t)stream);
   if (rc == -1) return fail(PL_E_INVAL, "unsupported GEMM shape M=%d N=%d K=%d mode=%d", M, N, K, mode);
   if (rc) return fail(PL_E_HIP, "GEMM launch failed");
   return PL_OK;

@@ -310,6 +310,40 @@ def test_plain_products_of_an_engine_are_the_same_for_every_row_count(M_max, N, 
             assert np.array_equal(got, widest[:, :M]), M
 
 
+@pytest.mark.parametrize("M_max,N,K,mode", [(64, 2048, 1536, 0), (64, 1536, 8960, 0), (256, 4608, 3584, 0), (128, 7168, 5120, 0),
+                                            (2, 96, 256, 0), (64, 2 * 8960, 256, 1), (256, 2 * 18944, 768, 1), (256, 2 * 18976, 768, 1)])
+def test_products_of_many_rows_equal_the_slices_of_few_added_in_order(M_max, N, K, mode):
+    """The products of a prompt pass of more than 256 rows add up the K slices in the workgroup: bit-equal to the
+    slices a narrow pass of the same engine gives its consumer, added in slice order, at the row counts where a tile or
+    the choice of a tile shape ends.  (Row counts and shapes between them reach every tile shape of the choice.)"""
+    splits, n_main, _, ws_elems = pl.pl_debug_gemm_plan(M_max, N, K, mode)
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    x = torch.empty(1024, K, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
+    w = torch.empty(N * K, device="cuda", dtype=torch.bfloat16).normal_(0, 0.05, generator=g)
+    want = torch.empty(1024, N if mode == 0 else N // 2, device="cuda", dtype=torch.float32)
+    ws = torch.empty(max(ws_elems, 1), device="cuda", dtype=torch.float32)
+    for r in range(0, 1024, M_max):
+        rows = min(M_max, 1024 - r)
+        y = torch.empty(splits, rows, N, device="cuda") if mode == 0 else torch.empty(rows, N // 2, device="cuda", dtype=torch.bfloat16)
+        pl.pl_debug_gemm_planned(x[r:].data_ptr(), w.data_ptr(), y.data_ptr(), ws.data_ptr(), M_max, rows, N, K, mode, 0)
+        if mode == 0:
+            for s in range(1, splits):
+                y[0] += y[s]
+            want[r:r + rows] = y[0]
+        else:
+            want[r:r + rows] = y.float()
+        torch.cuda.synchronize()
+    for M in (257, 300, 384, 511, 512, 513, 1023, 1024):
+        y = torch.full((M + 1, want.shape[1]), float("nan"), device="cuda", dtype=torch.float32 if mode == 0 else torch.bfloat16)
+        pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), M_max, M, N, K, mode, 0)
+        torch.cuda.synchronize()
+        assert torch.equal(y[:M].float(), want[:M]), M
+        assert bool(y[M].isnan().all()), M             # nothing written beyond the rows
+    for bad in [(1025, N, K), (0, N, K), (300, N, K + 64), (300, N + 16, K)]:
+        with pytest.raises(pl.PlError):
+            pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), M_max, *bad, mode, 0)
+
+
 def test_gemm_rejects_bad_shapes():
     t = torch.zeros(600 * 512, device="cuda", dtype=torch.bfloat16)
     for args in [(4, 64, 192, 0, 1), (0, 64, 256, 0, 1), (4, 64, 512, 0, 3), (4, 96, 256, 1, 1), (4, 64, 512, 1, 2),
