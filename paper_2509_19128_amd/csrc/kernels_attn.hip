@@ -6,8 +6,13 @@
 // wavefront fetches one contiguous KiB that is already in MFMA operand order (the page layout is
 // chosen for that), the query heads that share a kv head ride along as the 16 columns of one
 // 16x16x32 MFMA so each K/V byte is read once for the whole group, and soft-max statistics are
-// reduced with cross-lane shuffles.  Work is split over (sequence, kv head, chunk of tokens);
-// chunks of one sequence are merged by a second kernel in a fixed order.
+// reduced with cross-lane shuffles.  Work is split over (sequence, kv head, item of tokens).
+//
+// The order of a result's additions is fixed by the chunk length alone, whatever is launched: a chunk is
+// cut into subs of ATTN_SUB tokens; wavefront w takes the 32-token runs w, w + 4, ... of a sub with an
+// online soft-max, folds its subs in order, the four wavefronts are merged, and the chunks of a sequence
+// are folded in order.  An item is a chunk, or one sub where few sequences would leave the chip idle
+// (the wavefronts' partial results then go to a merge kernel that does the same folds).
 #include "pl_common.h"
 
 #ifndef PL_ATTN_NS
@@ -20,10 +25,56 @@
 namespace pl {
 namespace {
 
+constexpr int SUB_RUNS = ATTN_SUB / 32;
+
 __device__ inline float shfl_xor(float v, int mask) { return __shfl_xor(v, mask, 64); }
 
+// (m, l, o) <- (m, l, o) folded with a later part (mi, li, oi); m is in log2 units.  A part without tokens
+// has mi = -inf and changes nothing; the first part is taken over as it is.
+template <typename V>
+__device__ inline void fold_part(float &m, float &l, V &o, float mi, float li, V oi) {
+  const float M = fmaxf(m, mi);
+  const float e0 = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M), e1 = mi == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mi - M);
+  o = o * e0 + oi * e1;
+  l = l * e0 + li * e1;
+  m = M;
+}
+
+// Values that another workgroup of the same launch reads: written through to the memory all XCDs share and
+// read from there (agent scope), so that no L2 has to be written back or invalidated.
+__device__ inline void store_shared(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline float load_shared(const float *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The chunks of one (sequence, kv head), written by store_shared, folded in order into the output row.  256 threads.
+template <int HD>
+__device__ inline void merge_chunks(const AttnParams &p, int b, int g, int nchunk) {
+  const int G = p.Hq / p.Hkv;
+  const int64_t base = ((int64_t)b * p.Hkv + g) * p.max_chunks;
+  for (int idx = threadIdx.x; idx < G * HD; idx += 256) {
+    const int h = idx / HD, d = idx % HD;
+    const float *ml = p.part_ml + base * ATTN_ML + h * 2, *po = p.part_o + base * G * HD + idx;
+    float M = -INFINITY, L = 0.f, O = 0.f;
+    for (int c0 = 0; c0 < nchunk; c0 += 8) {   // the loads of eight chunks are issued together
+      float m8[8], l8[8], o8[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int c = min(c0 + u, nchunk - 1);
+        m8[u] = load_shared(ml + (int64_t)c * ATTN_ML);
+        l8[u] = load_shared(ml + (int64_t)c * ATTN_ML + 1);
+        o8[u] = load_shared(po + (int64_t)c * G * HD);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (c0 + u < nchunk) fold_part(M, L, O, m8[u], l8[u], o8[u]);
+    }
+    p.out[((int64_t)b * p.Hq + g * G + h) * HD + d] = (__bf16)(O / L);
+  }
+}
+
 template <int HD, int NS>
-__global__ __launch_bounds__(256) void attn_decode_kernel(AttnParams p) {
+__global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
   constexpr int NJ = HD / 32;   // QK MFMAs per 16-token tile
   constexpr int NV = HD / 16;   // PV MFMAs per 32-token run
   // Work items come from a compact list built on the device for this step: every launched workgroup
@@ -34,19 +85,35 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(AttnParams p) {
   // a workgroup are one dependent scalar load away (its record; records beyond the list's end say so
   // themselves) instead of five: with the memory system saturated each such load takes about a
   // microsecond during which the workgroup has nothing in flight.
+  // Calls whose items all run at once whatever their order need no list (work null): item i is chunk
+  // i % max_chunks of sequence i / max_chunks.
   const int item = blockIdx.x / p.Hkv, g = blockIdx.x % p.Hkv;
-  const int4 *rec = (const int4 *)(p.work + 8 + 8 * (int64_t)item);
-  const int4 r0 = rec[0], r1 = rec[1];
-  const int b = r0.x, c = r0.y, ctx = r0.z, slot = r0.w;
-  if (ctx <= 0) return;   // beyond the end of the list (the list kernel clears the records up to the buffer's end)
-  const int t0 = c * p.chunk;
-  const int t1 = min(ctx, t0 + p.chunk);
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+  int b, c, ctx, slot;
+  int4 r1;   // page ids
+  if (p.work) {
+    const int4 *rec = (const int4 *)(p.work + 8 + 8 * (int64_t)item);
+    const int4 r0 = rec[0];
+    r1 = rec[1];
+    b = r0.x; c = r0.y; ctx = r0.z; slot = r0.w;
+    if (ctx <= 0) return;   // beyond the end of the list (the list kernel clears the records up to the grid's end)
+  } else {
+    b = slot = item / p.max_chunks;
+    c = item % p.max_chunks;
+    ctx = p.ctx_len[b];
+    const int32_t *row = p.page_table + (int64_t)slot * p.pages_per_seq;
+    const int p0 = (int)((int64_t)c * p.item_tokens / p.page_tokens), last = p.pages_per_seq - 1;
+    r1 = make_int4(row[min(p0, last)], row[min(p0 + 1, last)], row[min(p0 + 2, last)], row[min(p0 + 3, last)]);
+    if (c * p.item_tokens >= ctx) return;
+  }
+  const int t0 = c * p.item_tokens;
+  const int t1 = min(ctx, t0 + p.item_tokens);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;   // uniform: page ids by scalar loads
   const int head = l & 15, qg = l >> 4;
   const int G = p.Hq / p.Hkv;
   const int32_t *pt = p.page_table + (int64_t)slot * p.pages_per_seq;
   const int page_first = t0 / p.page_tokens;   // r1 holds the ids of pages page_first .. page_first + 3
   const float scale = 1.4426950408889634f / sqrtf((float)HD);   // log2(e) / sqrt(hd)
+  const int64_t page_elems = (int64_t)2 * p.page_tokens * HD;   // K block + V block of one kv head
 
   // Query operand: column = head of the group (zero for the padding columns), k = head-dim slice.
   bf16x8 qf[NJ];
@@ -66,7 +133,6 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(AttnParams p) {
   float m = -INFINITY, lsum = 0.f;
 
   const int nblk = (t1 - t0 + 31) >> 5;
-  const int64_t page_elems = (int64_t)2 * p.page_tokens * HD;   // K block + V block of one kv head
   // page id of a run, and the address of its K fragments given that id: the id of the run a stage will
   // hold next is fetched one refill ahead, so that no K/V load waits for a page-table load
   auto page_of = [&](int blk) -> int {
@@ -100,10 +166,41 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(AttnParams p) {
   int page_next[NS];   // page of the run stage st takes after the one it holds
 #pragma unroll
   for (int st = 0; st < NS; ++st) {
-    const int b0 = wave + 4 * st;
-    if (b0 < nblk) { const bf16_t *kb = run_base(b0, page_of(b0)); load_k(st, kb); load_v(st, kb); }
+    // without a condition (a wavefront without a run loads the last one), so that the wait counts that follow stay exact
+    const int b0 = wave + 4 * st, bl = min(b0, nblk - 1);
+    const bf16_t *kb = run_base(bl, page_of(bl));
+    load_k(st, kb);
+    load_v(st, kb);
     page_next[st] = b0 + 4 * NS < nblk ? page_of(b0 + 4 * NS) : 0;
   }
+  // Results of this wavefront's finished subs, folded in order; o is kept in the wavefront's own part of sm_o.
+  __shared__ float sm_o[4][16][HD];
+  __shared__ float sm_m[4][16], sm_l[4][16];
+  float m_all = -INFINITY, l_all = 0.f;
+  bool folded = false;
+  auto fold_sub = [&](bool first) {
+    lsum += shfl_xor(lsum, 16);
+    lsum += shfl_xor(lsum, 32);
+    float *mine = &sm_o[wave][head][qg * 4];
+    if (first) {
+      if (head < G) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) *(f32x4 *)(mine + i * 16) = o[i];
+      }
+      m_all = m; l_all = lsum;
+      return;
+    }
+    const float M = fmaxf(m_all, m), e0 = __builtin_amdgcn_exp2f(m_all - M), e1 = __builtin_amdgcn_exp2f(m - M);
+    if (head < G) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const f32x4 was = *(const f32x4 *)(mine + i * 16);
+        *(f32x4 *)(mine + i * 16) = was * e0 + o[i] * e1;
+      }
+    }
+    l_all = l_all * e0 + lsum * e1;
+    m_all = M;
+  };
   for (int base = wave; base < nblk; base += 4 * NS) {
 #pragma unroll
     for (int st = 0; st < NS; ++st) {
@@ -157,22 +254,33 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(AttnParams p) {
         if (nb) load_v(st, nb);
       }
     }
+    // end of a sub: SUB_RUNS runs, of which this wavefront took every fourth
+    if ((base & (SUB_RUNS - 1)) + 4 * NS >= SUB_RUNS && base + 4 * NS < nblk) {
+      fold_sub(!folded);
+      folded = true;
+      m = -INFINITY;
+      lsum = 0.f;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
   }
-  lsum += shfl_xor(lsum, 16);
-  lsum += shfl_xor(lsum, 32);
 
-  // merge the four wavefronts of the workgroup
-  __shared__ float sm_o[4][16][HD];
-  __shared__ float sm_m[4][16], sm_l[4][16];
-  if (head < G) {
+  if (p.item_tokens < p.chunk && ctx > p.item_tokens) {   // an item is one sub: the wavefronts' results, for the merge kernel
+    lsum += shfl_xor(lsum, 16);
+    lsum += shfl_xor(lsum, 32);
+    const int64_t part = ((int64_t)item * p.Hkv + g) * 4 + wave;
+    if (head < G) {
 #pragma unroll
-    for (int i = 0; i < NV; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) sm_o[wave][head][i * 16 + qg * 4 + e] = o[i][e];
-    if (qg == 0) { sm_m[wave][head] = m; sm_l[wave][head] = lsum; }
+      for (int i = 0; i < NV; ++i) *(f32x4 *)(p.part_o + (part * G + head) * HD + i * 16 + qg * 4) = o[i];
+      if (qg == 0) *(float2 *)(p.part_ml + (part * 16 + head) * 2) = make_float2(m, lsum);
+    }
+    return;
   }
+  fold_sub(!folded);   // (the loop leaves the last sub of a wavefront open)
+  if (head < G && qg == 0) { sm_m[wave][head] = m_all; sm_l[wave][head] = l_all; }
   __syncthreads();
-  const bool single = ctx <= p.chunk;
+  // merge the four wavefronts of the workgroup
+  const int nchunk = (ctx + p.chunk - 1) / p.chunk;
   const int64_t pidx = ((int64_t)b * p.Hkv + g) * p.max_chunks + c;
   for (int idx = threadIdx.x; idx < G * HD; idx += 256) {
     int h = idx / HD, d = idx % HD;
@@ -184,13 +292,97 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(AttnParams p) {
       L += sm_l[w][h] * f;
       O += sm_o[w][h][d] * f;
     }
-    if (single) {
+    if (nchunk == 1) {
       p.out[((int64_t)b * p.Hq + g * G + h) * HD + d] = (__bf16)(O / L);
     } else {
-      p.part_o[(pidx * G + h) * HD + d] = O;
-      if (d == 0) { p.part_ml[(pidx * G + h) * 2] = M; p.part_ml[(pidx * G + h) * 2 + 1] = L; }
+      store_shared(p.part_o + pidx * G * HD + idx, O);
+      if (d == 0) {
+        store_shared(p.part_ml + pidx * ATTN_ML + h * 2, M);
+        store_shared(p.part_ml + pidx * ATTN_ML + h * 2 + 1, L);
+      }
     }
   }
+  if (nchunk == 1 || !p.tickets) return;
+  // The workgroup that finishes a (sequence, kv head) last folds its chunks: no merge launch (a 5 us kernel and
+  // a launch gap per layer).  Every store above has reached the shared memory (the wait) before the
+  // ticket is taken; partial results of different workgroups share no cache line (128 bytes), so the last one
+  // cannot have an old copy.  Release and acquire fences in their place would write back and invalidate the XCD's L2
+  // in every workgroup (2.5 times the launch's time).
+  __shared__ int s_last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t *ticket = p.tickets + (int64_t)b * p.Hkv + g;
+    const int before = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_last = before == nchunk - 1;
+    if (before == nchunk - 1) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+  }
+  __syncthreads();
+  if (s_last) merge_chunks<HD>(p, b, g, nchunk);
+}
+
+// Merge of rows that span several items, where the decode kernel does not do it itself: one workgroup of HD
+// threads per (row, query head), four output elements each; thread group w folds wavefront w's subs, thread
+// group 0 whole chunks.  Latency bound (a few KiB per thread group): the loads of 16 parts are issued together.
+template <int HD>
+__global__ __launch_bounds__(HD) void attn_merge_kernel(AttnParams p) {
+  constexpr int QUADS = HD / 4;
+  const int b = blockIdx.y, hq = blockIdx.x, w = threadIdx.x / QUADS, d = threadIdx.x % QUADS * 4;
+  const int G = p.Hq / p.Hkv, g = hq / G, h = hq % G;
+  const bool subs = p.item_tokens < p.chunk;
+  const int ctx = p.ctx_len[b], first = subs ? p.first_item[b] : 0;   // (list index of the row's first item)
+  if (ctx <= p.item_tokens) return;   // the decode kernel wrote the row
+  const int nchunk = (ctx + p.chunk - 1) / p.chunk;
+  __shared__ f32x4 so[4][QUADS];
+  __shared__ float sml[4][2];
+  float M = -INFINITY, L = 0.f;
+  f32x4 O = {0.f, 0.f, 0.f, 0.f};
+  // fold of n parts, part i at index at(i)
+  auto fold_parts = [&](float &m, float &l, f32x4 &o, int n, int ml_floats, auto at) {
+    for (int j0 = 0; j0 < n; j0 += 16) {
+      float2 ml[16];
+      f32x4 o16[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int64_t part = at(min(j0 + u, n - 1));
+        ml[u] = *(const float2 *)(p.part_ml + part * ml_floats + h * 2);
+        o16[u] = *(const f32x4 *)(p.part_o + (part * G + h) * HD + d);
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (j0 + u < n) fold_part(m, l, o, ml[u].x, ml[u].y, o16[u]);
+    }
+  };
+  if (!subs) {
+    const int64_t base = ((int64_t)b * p.Hkv + g) * p.max_chunks;
+    if (w == 0) fold_parts(M, L, O, nchunk, ATTN_ML, [&](int c) { return base + c; });
+  }
+  for (int c = 0; subs && c < nchunk; ++c) {
+    const int per = p.chunk / p.item_tokens, n = min(per, (ctx - c * p.chunk + p.item_tokens - 1) / p.item_tokens);
+    float mw = -INFINITY, lw = 0.f;
+    f32x4 ow = {0.f, 0.f, 0.f, 0.f};
+    fold_parts(mw, lw, ow, n, 32, [&](int j) { return ((int64_t)(first + c * per + j) * p.Hkv + g) * 4 + w; });
+    __syncthreads();
+    so[w][threadIdx.x % QUADS] = ow;
+    if (d == 0) { sml[w][0] = mw; sml[w][1] = lw; }
+    __syncthreads();
+    // the merge of the four wavefronts as the decode kernel does it
+    const float Mc = fmaxf(fmaxf(sml[0][0], sml[1][0]), fmaxf(sml[2][0], sml[3][0]));
+    float Lc = 0.f;
+    f32x4 Oc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float f = __builtin_amdgcn_exp2f(sml[v][0] - Mc);
+      Lc += sml[v][1] * f;
+      Oc += so[v][threadIdx.x % QUADS] * f;
+    }
+    fold_part(M, L, O, Mc, Lc, Oc);
+  }
+  if (w != 0) return;
+  bf16x4 out;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) out[e] = (__bf16)(O[e] / L);
+  *(bf16x4 *)(p.out + ((int64_t)b * p.Hq + hq) * HD + d) = out;
 }
 
 // Inclusive prefix sum over the 1024 threads of the workgroup (wave shuffles, then the 16 wave totals).
@@ -215,38 +407,50 @@ __device__ inline int block_scan_1024(int v, int *wsum, int *total) {
   return v + before;
 }
 
-// work[0] = number of items, work[1] = number of sequences longer than one chunk (listed in `multi` as
-// row | chunks << 12, the rest of the list -1);
-// the items are 8-int records from work[8] on: {sequence, chunk, context length, slot, ids of the
-// chunk's first four pages}.  All full chunks come first, then each
-// sequence's last (partial or full) chunk, longest first, so that the workgroups still running when
-// the grid drains are the short ones.  One workgroup; n_seq <= 1024.
+// The list's items are 8-int records from work[8] on: {sequence, chunk, context length, slot, ids of the
+// chunk's first four pages}.  All full chunks come first, then each sequence's last (partial or full) chunk,
+// longest first, so that the workgroups still running when the grid drains are the short ones.  With
+// `contiguous` a sequence's items follow one another instead, from first_item[sequence] on (what the merge
+// kernel of single subs needs; those launches run all items at once).  Records up to index `cap` beyond the
+// list's end say "no item".  One workgroup; n_seq <= 1024.  Each record has a thread of its own that finds its
+// sequence in the prefix sums: a thread per sequence that walks its chunks takes 10 us where sequences have 15.
 __global__ __launch_bounds__(1024) void attn_worklist_kernel(const int32_t *ctx_len, const int32_t *row_slot,
-                                                             const int32_t *page_table, int32_t *work, int32_t *multi,
-                                                             int n_seq, int chunk, int page_tokens, int pages_per_seq) {
+                                                             const int32_t *page_table, int32_t *work, int32_t *tickets,
+                                                             int32_t *first_item, int n_seq, int Hkv, int item_tokens,
+                                                             int page_tokens, int pages_per_seq, int cap, bool contiguous) {
   __shared__ int wsum[16];
   __shared__ __attribute__((aligned(16))) int tail[1024];
+  __shared__ int pre[1024], s_ctx[1024], s_slot[1024];
   const int b = threadIdx.x;
   const int ctx = b < n_seq ? ctx_len[b] : 0;
   const int slot = b < n_seq ? (row_slot ? row_slot[b] : b) : 0;
-  const int n = (ctx + chunk - 1) / chunk;
-  const int full = n > 0 ? n - 1 : 0;
-  const int32_t *pt = page_table + (int64_t)slot * pages_per_seq;
-  const int last_page = ctx > 0 ? (ctx - 1) / page_tokens : 0;
-  auto put = [&](int i, int c) {
+  const int n = (ctx + item_tokens - 1) / item_tokens;
+  const int listed = contiguous ? n : n > 0 ? n - 1 : 0;   // items of this sequence in the first part of the list
+  auto put = [&](int i, int bb, int c, int cx, int sl) {
+    if (i >= cap) return;
+    const int32_t *pt = page_table + (int64_t)sl * pages_per_seq;
+    const int last_page = (cx - 1) / page_tokens, p0 = (int)((int64_t)c * item_tokens / page_tokens);
     int4 *rec = (int4 *)(work + 8 + 8 * (int64_t)i);
-    const int p0 = c * chunk / page_tokens;
-    rec[0] = make_int4(b, c, ctx, slot);
-    rec[1] = make_int4(pt[min(p0, last_page)], pt[min(p0 + 1, last_page)], pt[min(p0 + 2, last_page)],
-                       pt[min(p0 + 3, last_page)]);
+    rec[0] = make_int4(bb, c, cx, sl);
+    rec[1] = make_int4(pt[min(p0, last_page)], pt[min(p0 + 1, last_page)], pt[min(p0 + 2, last_page)], pt[min(p0 + 3, last_page)]);
   };
-  int total_full, n_last;
-  const int at = block_scan_1024(full, wsum, &total_full) - full;
-  for (int c = 0; c < full; ++c) put(at + c, c);
-  const int rem = n > 0 ? ctx - (n - 1) * chunk : 0;
+  int total, n_last = 0;
+  pre[b] = block_scan_1024(listed, wsum, &total) - listed;
+  s_ctx[b] = ctx;
+  s_slot[b] = slot;
+  const int rem = n > 0 ? ctx - (n - 1) * item_tokens : 0;
   tail[b] = rem;   // 0 for empty rows and for threads at or beyond n_seq
-  (void)block_scan_1024(n > 0, wsum, &n_last);   // also orders the writes to tail before the reads below
-  if (n > 0) {   // rank among the last chunks: longer first, lower sequence index first among equals
+  if (!contiguous) (void)block_scan_1024(n > 0, wsum, &n_last);
+  __syncthreads();
+  if (contiguous && b < n_seq) first_item[b] = pre[b];
+  for (int i = b; i < total; i += 1024) {   // last sequence whose items start at or before i
+    int lo = 0;
+#pragma unroll
+    for (int step = 512; step > 0; step >>= 1)
+      if (pre[lo + step] <= i) lo += step;   // lo + step <= 1023
+    put(i, lo, i - pre[lo], s_ctx[lo], s_slot[lo]);
+  }
+  if (!contiguous && n > 0) {   // rank among the last chunks: longer first, lower sequence index first among equals
     int rank = 0;
     const int4 *t4 = (const int4 *)tail;
     for (int o4 = 0; o4 < (n_seq + 3) / 4; ++o4) {
@@ -257,82 +461,10 @@ __global__ __launch_bounds__(1024) void attn_worklist_kernel(const int32_t *ctx_
       rank += (t.z > rem) || (t.z == rem && o + 2 < b);
       rank += (t.w > rem) || (t.w == rem && o + 3 < b);
     }
-    put(total_full + rank, n - 1);
+    put(total + rank, b, n - 1, ctx, slot);
   }
-  // rows that span several chunks, in row order: what the merge kernel walks
-  int n_multi;
-  const int mi = block_scan_1024(n > 1, wsum, &n_multi) - (n > 1);
-  if (n > 1) multi[mi] = b | (n << 12);   // row and its number of chunks in one word (n_seq <= 1024)
-  for (int i = n_multi + b; i < n_seq; i += 1024) multi[i] = -1;   // beyond the list's end
-  if (b == 0) { work[0] = total_full + n_last; work[1] = n_multi; }
-  // records beyond the list's end, up to the end of the record area (the multi list starts there), say
-  // "no item": a workgroup of the decode kernel learns that from its own record, without a second
-  // dependent load of the list's length
-  const int cap = (int)((multi - (work + 8)) / 8);
-  for (int i = total_full + n_last + b; i < cap; i += 1024) ((int4 *)(work + 8 + 8 * (int64_t)i))[0] = make_int4(0, 0, 0, 0);
-}
-
-// Merge of the chunks of multi-chunk sequences, in chunk order.  One workgroup of HD threads per
-// (listed sequence, query head); the list is the work-list kernel's, the grid is sized by the
-// caller's bound on its length.  The kernel is latency bound (a few KiB per workgroup), so every load
-// that does not depend on another is issued at once: thread c fetches the statistics of chunk c, the
-// weights go through LDS, and each thread then sums its output element over the chunks, eight loads
-// at a time, in chunk order.
-template <int HD>
-__global__ __launch_bounds__(HD < 64 ? 64 : HD) void attn_combine_kernel(AttnParams p) {
-  constexpr int NT = HD < 64 ? 64 : HD;   // threads: whole wavefronts; thread d < HD owns output element d
-  // one list entry = row | number of chunks << 12, negative beyond the list's end: the chunk statistics
-  // are one dependent load away
-  const int entry = p.multi[blockIdx.y];
-  if (entry < 0) return;
-  const int b = entry & 0xFFF, nchunk = entry >> 12, hq = blockIdx.x;
-  const int G = p.Hq / p.Hkv, g = hq / G, h = hq % G;
-  const int64_t base = ((int64_t)b * p.Hkv + g) * p.max_chunks;
-  const float *ml = p.part_ml + (base * G + h) * 2;                   // chunk c at ml[c * G * 2]
-  const float *po = p.part_o + (base * G + h) * HD + (threadIdx.x < HD ? threadIdx.x : 0);   // chunk c at po[c * G * HD]
-  __shared__ float sw[NT];      // weight of chunk c (NT chunks at a time)
-  __shared__ float red[2][NT / 64];
-  const int d = threadIdx.x, lane = d & 63, wave = d >> 6;
-  float O = 0.f, L = 0.f;
-  // the running maximum over all chunks first (chunks beyond HD are walked in rounds of HD)
-  float M = -INFINITY;
-  for (int c0 = 0; c0 < nchunk; c0 += NT) {
-    float m = c0 + d < nchunk ? ml[(int64_t)(c0 + d) * G * 2] : -INFINITY;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-    if (lane == 0) red[0][wave] = m;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) M = fmaxf(M, red[0][w]);
-    __syncthreads();
-  }
-  for (int c0 = 0; c0 < nchunk; c0 += NT) {
-    const int nc = min(NT, nchunk - c0);
-    float wgt = 0.f, lw = 0.f;
-    if (d < nc) {
-      const float2 v = *(const float2 *)(ml + (int64_t)(c0 + d) * G * 2);
-      wgt = __builtin_amdgcn_exp2f(v.x - M);
-      lw = v.y * wgt;
-    }
-    sw[d] = wgt;
-    // L: sum of l_c w_c in a fixed order (lanes by shuffle tree, then the waves in order)
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) lw += __shfl_xor(lw, o, 64);
-    if (lane == 0) red[1][wave] = lw;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) L += red[1][w];
-    for (int c = 0; c < nc; c += 8) {
-      float o8[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) o8[u] = c + u < nc ? po[(int64_t)(c0 + c + u) * G * HD] : 0.f;
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (c + u < nc) O += o8[u] * sw[c + u];
-    }
-    __syncthreads();
-  }
-  if (d < HD) p.out[((int64_t)b * p.Hq + hq) * HD + d] = (__bf16)(O / L);
+  for (int i = b; i < n_seq * Hkv; i += 1024) tickets[i] = 0;
+  for (int i = total + n_last + b; i < cap; i += 1024) ((int4 *)(work + 8 + 8 * (int64_t)i))[0] = make_int4(0, 0, 0, 0);
 }
 
 }  // namespace
@@ -346,44 +478,45 @@ int attention_chunk_tokens(int n_seq, int Hkv, int max_ctx) {
   return chunk;
 }
 
-// ints of the work buffer (which must be 32-byte aligned): a header of 8, one 8-int record per item,
-// then the list of multi-chunk sequences
-int64_t attention_worklist_ints(int n_seq, int max_chunks) { return 8 + 8 * (int64_t)n_seq * max_chunks + n_seq; }
-const int32_t *attention_multi_list(const int32_t *work, int n_seq, int max_chunks) {
-  return work + 8 + 8 * (int64_t)n_seq * max_chunks;
+// A step in which one item would outlast the rest: an item is then one sub.  A compute unit alone streams about
+// 1/128 of what the chip does, so a launch lasts at least longest_item x 128 of total bytes; cutting pays from
+// about three subs on (the merge launch takes 5 us, a sub 5).  7B shape, 19 sequences of 7000 tokens in an engine of
+// 256 slots (8192-token chunks): 82 + 5 (merge) -> 34 + 8 us per layer.  The result's bits do not depend on the choice.
+bool attention_split(int chunk, int64_t total_tokens, int64_t longest_item, int64_t n_subs, int Hkv) {
+  return chunk > ATTN_SUB && longest_item >= 3 * ATTN_SUB && n_subs * Hkv <= ATTN_SPLIT_PARTS && longest_item * 128 > total_tokens * Hkv;
 }
 
-int launch_attention_worklist(const int32_t *ctx_len, const int32_t *row_slot, const int32_t *page_table, int32_t *work,
-                              int n_seq, int max_chunks, int chunk, int page_tokens, int pages_per_seq, hipStream_t s) {
-  if (n_seq <= 0 || n_seq > 1024 || ((uintptr_t)work & 31)) return -1;
-  hipLaunchKernelGGL(attn_worklist_kernel, dim3(1), dim3(1024), 0, s, ctx_len, row_slot, page_table, work,
-                     (int32_t *)attention_multi_list(work, n_seq, max_chunks), n_seq, chunk, page_tokens, pages_per_seq);
+// ints of the work buffer (which must be 32-byte aligned): a header of 8, one 8-int record per item
+int64_t attention_worklist_ints(int64_t max_items) { return 8 + 8 * max_items; }
+
+int launch_attention_worklist(const AttnParams &p, int cap, hipStream_t s) {
+  if (p.n_seq <= 0 || p.n_seq > 1024 || ((uintptr_t)p.work & 31)) return -1;
+  const bool contiguous = p.item_tokens < p.chunk;
+  hipLaunchKernelGGL(attn_worklist_kernel, dim3(1), dim3(1024), 0, s, p.ctx_len, p.row_slot, p.page_table, p.work, p.tickets,
+                     p.first_item, p.n_seq, p.Hkv, p.item_tokens, p.page_tokens, p.pages_per_seq, cap, contiguous);
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }
 
-// part: 0 = the decode kernel and, where a row spans several chunks, the merge kernel; 1 = the decode
-// kernel alone; 2 = the merge kernel alone (so that a caller can time the two separately)
+template <int HD>
+static void launch_attention_hd(const AttnParams &p, hipStream_t s, int part) {
+  if (part != 2) {
+    const dim3 grid((unsigned)(p.max_items * p.Hkv));
+    hipLaunchKernelGGL((attn_decode_kernel<HD, PL_ATTN_NS>), grid, dim3(256), 0, s, p);
+  }
+  // items are subs, or there is no list (whose kernel clears the tickets) and a row can span several chunks
+  if (part != 1 && (p.item_tokens < p.chunk || (!p.tickets && p.max_chunks > 1)))
+    hipLaunchKernelGGL(attn_merge_kernel<HD>, dim3(p.Hq, p.n_seq), dim3(HD), 0, s, p);
+}
+
+// part: 0 = the decode kernel and, where it does not merge the items of a row itself, the merge kernel; 1 = the
+// decode kernel alone; 2 = the merge kernel alone (so that a caller can time the two separately)
 int launch_attention(const AttnParams &p, hipStream_t s, int part) {
   if (p.n_seq <= 0) return 0;
-  // max_items and max_multi bound the two lists (a host that knows the step's contexts passes the
-  // exact lengths; otherwise n_seq * max_chunks and n_seq)
-  dim3 grid(p.max_items * p.Hkv), cgrid(p.Hq, p.max_multi > 0 ? p.max_multi : 1);
-  const bool decode = part != 2, merge = p.max_multi > 0 && part != 1;
   switch (p.hd) {
-    case 128:
-      if (decode) hipLaunchKernelGGL((attn_decode_kernel<128, PL_ATTN_NS>), grid, dim3(256), 0, s, p);
-      if (merge) hipLaunchKernelGGL(attn_combine_kernel<128>, cgrid, dim3(128), 0, s, p);
-      break;
-    case 64:
-      if (decode) hipLaunchKernelGGL((attn_decode_kernel<64, PL_ATTN_NS>), grid, dim3(256), 0, s, p);
-      if (merge) hipLaunchKernelGGL(attn_combine_kernel<64>, cgrid, dim3(64), 0, s, p);
-      break;
-    case 32:
-      if (decode) hipLaunchKernelGGL((attn_decode_kernel<32, PL_ATTN_NS>), grid, dim3(256), 0, s, p);
-      if (merge) hipLaunchKernelGGL(attn_combine_kernel<32>, cgrid, dim3(64), 0, s, p);
-      break;
-    default:
-      return -1;
+    case 128: launch_attention_hd<128>(p, s, part); break;
+    case 64: launch_attention_hd<64>(p, s, part); break;
+    case 32: launch_attention_hd<32>(p, s, part); break;
+    default: return -1;
   }
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }

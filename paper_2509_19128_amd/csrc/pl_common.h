@@ -63,26 +63,30 @@ __host__ __device__ inline int64_t v_elem_offset(int t, int d, int hd) {
   return ((int64_t)((r * (hd / 16) + d / 16) * 4 + (u >> 3))) * 128 + (d & 15) * 8 + (u & 7);
 }
 
+constexpr int ATTN_SUB = 512;            // tokens of a sub of an attention chunk (chunks are powers of two)
+constexpr int ATTN_ML = 32;              // floats of the soft-max statistics of one part: (m, l) of up to 16 heads, one cache line
+constexpr int ATTN_SPLIT_PARTS = 2048;   // most (sub, kv head) pairs of a launch whose items are subs
 struct AttnParams {
   const bf16_t *q;          // [n_seq, Hq, hd]
   const bf16_t *kv;         // page pool of one layer
   const int32_t *page_table;// [n_slots, pages_per_seq], row = slot_of_row[row] (or row if null)
   const int32_t *ctx_len;   // [n_seq]
   const int32_t *row_slot;  // [n_seq] or null
-  const int32_t *work;      // work list built by launch_attention_worklist for these ctx_len, row_slot and page_table
-  const int32_t *multi;     // attention_multi_list(work, ...): rows longer than one chunk
+  int32_t *work;            // work list built by launch_attention_worklist for these ctx_len, row_slot and page_table;
+                            // null: none (row_slot null; max_items = n_seq * max_chunks)
+  int32_t *tickets;         // [n_seq, Hkv], zero between launches (the work-list kernel clears them); null without a list
+  int32_t *first_item;      // [n_seq] list index of a row's first item (item_tokens < chunk)
   int32_t max_items;        // upper bound on the list length (sizes the grid)
-  int32_t max_multi;        // upper bound on the number of rows longer than one chunk; 0 = none, no merge launch
   bf16_t *out;              // [n_seq, Hq, hd]
-  float *part_o;            // [n_seq, Hkv, max_chunks, G, hd]
-  float *part_ml;           // [n_seq, Hkv, max_chunks, G, 2]
+  float *part_o;            // [n_seq, Hkv, max_chunks, G, hd]; item_tokens < chunk: [item, Hkv, 4, G, hd]
+  float *part_ml;           // [n_seq, Hkv, max_chunks, ATTN_ML]; item_tokens < chunk: [item, Hkv, 4, 16, 2]
   int32_t n_seq, Hq, Hkv, hd, page_tokens, pages_per_seq, chunk, max_chunks;
+  int32_t item_tokens;      // tokens of a work item: chunk, or ATTN_SUB where attention_split says so
 };
 int launch_attention(const AttnParams &p, hipStream_t s, int part = 0);
-int64_t attention_worklist_ints(int n_seq, int max_chunks);
-const int32_t *attention_multi_list(const int32_t *work, int n_seq, int max_chunks);
-int launch_attention_worklist(const int32_t *ctx_len, const int32_t *row_slot, const int32_t *page_table, int32_t *work,
-                              int n_seq, int max_chunks, int chunk, int page_tokens, int pages_per_seq, hipStream_t s);
+int64_t attention_worklist_ints(int64_t max_items);
+bool attention_split(int chunk, int64_t total_tokens, int64_t longest_item, int64_t n_subs, int Hkv);
+int launch_attention_worklist(const AttnParams &p, int cap, hipStream_t s);
 int attention_chunk_tokens(int n_seq, int Hkv, int max_ctx);
 
 // x and W are each addressed through one buffer descriptor with 32-bit byte offsets kept in signed

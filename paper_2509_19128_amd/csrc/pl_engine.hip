@@ -107,10 +107,11 @@ struct pl_engine {
     char *meta_h = nullptr, *meta_d = nullptr;   // per-pass metadata: host (pinned) and device images, same layout
     float *h = nullptr, *parts = nullptr, *cs = nullptr, *attn_po = nullptr, *attn_pml = nullptr;
     bf16_t *a = nullptr, *q_rot = nullptr, *attn_out = nullptr, *mid = nullptr;
-    int32_t *ctx_len = nullptr, *attn_work = nullptr;
+    int32_t *ctx_len = nullptr, *attn_work = nullptr, *attn_tickets = nullptr, *attn_first = nullptr;
     int32_t *pt = nullptr;   // device copy of the page table, written on this set's stream only
+    int64_t items_cap = 0;   // records the attention work list holds
     int attn_items = 0;   // bound on this pass's attention work items
-    int attn_multi = 0;   // rows of this pass that span more than one attention chunk
+    bool attn_split = false;   // this step's attention items are single subs
     // the 8-byte ids come first, so every array is aligned for its type whatever rows_cap is
     uint64_t *m_seq_id(bool dev) { return (uint64_t *)(dev ? meta_d : meta_h); }
     int32_t *m_row_slot(bool dev) { return (int32_t *)(m_seq_id(dev) + rows_cap); }
@@ -153,7 +154,8 @@ struct pl_engine {
   // shape is the number of rows, the weight buffer, and the (rounded-up) grid bounds of the two
   // attention kernels; everything that changes from step to step is read from device buffers.
   struct StepGraph {
-    int n = 0, buf = 0, items = 0, multi = 0, set = 0;   // set: 0 decode step, 1 cache-only pass
+    int n = 0, buf = 0, items = 0, set = 0;   // set: 0 decode step, 1 cache-only pass
+    bool split = false;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     uint64_t last_use = 0;
@@ -263,16 +265,20 @@ int alloc_work(pl_engine *e, pl_engine::Work &w, int64_t R, int64_t parts_elems,
   if ((rc = dev_alloc(&w.cs, R * c.head_dim))) return rc;
   if ((rc = dev_alloc(&w.ctx_len, R))) return rc;
   if ((rc = dev_alloc(&w.pt, (int64_t)c.max_batch * e->pages_per_seq))) return rc;
-  const int64_t np = R * c.n_kv_heads * e->attn_max_chunks * e->G;
-  if ((rc = dev_alloc(&w.attn_po, np * c.head_dim))) return rc;
-  if ((rc = dev_alloc(&w.attn_pml, np * 2))) return rc;
-  if ((rc = dev_alloc(&w.attn_work, pl::attention_worklist_ints((int)R, e->attn_max_chunks)))) return rc;
+  const int64_t split = e->attn_chunk > pl::ATTN_SUB ? pl::ATTN_SPLIT_PARTS : 0;   // (sub, kv head) pairs
+  const int64_t np = std::max<int64_t>(R * c.n_kv_heads * e->attn_max_chunks, 4 * split);
+  if ((rc = dev_alloc(&w.attn_po, np * e->G * c.head_dim))) return rc;
+  if ((rc = dev_alloc(&w.attn_pml, np * pl::ATTN_ML))) return rc;
+  w.items_cap = std::max<int64_t>(R * e->attn_max_chunks, split);
+  if ((rc = dev_alloc(&w.attn_work, pl::attention_worklist_ints(w.items_cap)))) return rc;
+  if ((rc = dev_alloc(&w.attn_tickets, R * c.n_kv_heads))) return rc;
+  if ((rc = dev_alloc(&w.attn_first, R))) return rc;
   if (pinned_image) HIP_TRY(hipHostMalloc((void **)&w.meta_h, (size_t)w.meta_bytes(), hipHostMallocDefault));
   return PL_OK;
 }
 
 void free_work(pl_engine::Work &w) {
-  void *dev[] = {w.meta_d, w.h, w.a, w.parts, w.q_rot, w.attn_out, w.mid, w.cs, w.ctx_len, w.pt, w.attn_po, w.attn_pml, w.attn_work};
+  void *dev[] = {w.meta_d, w.h, w.a, w.parts, w.q_rot, w.attn_out, w.mid, w.cs, w.ctx_len, w.pt, w.attn_po, w.attn_pml, w.attn_work, w.attn_tickets, w.attn_first};
   for (void *p : dev)
     if (p) (void)hipFree(p);
   w = pl_engine::Work{};
@@ -459,8 +465,14 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   };
   auto slices = [&](const pl::GemmSplit &ks) { return fold ? 1 : ks.splits; };
   rc |= pl::launch_rope_tables(w.m_pos(true), w.cs, w.ctx_len, n, c.head_dim, c.rope_theta, s);
-  rc |= pl::launch_attention_worklist(w.ctx_len, w.m_row_slot(true), w.pt, w.attn_work, n, e->attn_max_chunks,
-                                      e->attn_chunk, e->page_tokens, e->pages_per_seq, s);
+  pl::AttnParams ap{};
+  ap.page_table = w.pt; ap.ctx_len = w.ctx_len; ap.row_slot = w.m_row_slot(true);
+  ap.out = w.attn_out; ap.part_o = w.attn_po; ap.part_ml = w.attn_pml;
+  ap.n_seq = n; ap.Hq = c.n_q_heads; ap.Hkv = c.n_kv_heads; ap.hd = c.head_dim;
+  ap.page_tokens = e->page_tokens; ap.pages_per_seq = e->pages_per_seq; ap.chunk = e->attn_chunk;
+  ap.max_chunks = e->attn_max_chunks; ap.item_tokens = w.attn_split ? pl::ATTN_SUB : e->attn_chunk;
+  ap.work = w.attn_work; ap.tickets = w.attn_tickets; ap.first_item = w.attn_first; ap.max_items = w.attn_items;
+  rc |= pl::launch_attention_worklist(ap, w.attn_items, s);
   const bf16_t *g_first = c.n_layers ? layer_weights(e, 0).g1 : gf;
   rc |= pl::launch_embed_rmsnorm(embed, g_first, w.m_input(true), nullptr, w.m_row_slot(true), w.h, w.a, n,
                                  d, c.vocab, c.rms_eps, s);
@@ -470,17 +482,9 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
     if (timed) mark(e, CAT_OTHER);
     rc |= gemm(w.a, lw.w_qkv, w.parts, nullptr, wq, d, 0, e->ks_qkv);
     if (timed) mark(e, CAT_GEMM);
-    rc |= pl::launch_rope_append(w.parts, slices(e->ks_qkv), w.cs, w.m_pos(true), w.m_row_slot(true), w.pt,
-                                 w.q_rot, kv_layer, n, c.n_q_heads, c.n_kv_heads, c.head_dim, e->page_tokens,
-                                 e->pages_per_seq, s);
-    pl::AttnParams ap{};
-    ap.q = w.q_rot; ap.kv = kv_layer; ap.page_table = w.pt; ap.ctx_len = w.ctx_len;
-    ap.row_slot = w.m_row_slot(true); ap.out = w.attn_out; ap.part_o = w.attn_po; ap.part_ml = w.attn_pml;
-    ap.n_seq = n; ap.Hq = c.n_q_heads; ap.Hkv = c.n_kv_heads; ap.hd = c.head_dim;
-    ap.page_tokens = e->page_tokens; ap.pages_per_seq = e->pages_per_seq; ap.chunk = e->attn_chunk;
-    ap.max_chunks = e->attn_max_chunks;
-    ap.work = w.attn_work; ap.max_items = w.attn_items;
-    ap.multi = pl::attention_multi_list(w.attn_work, n, e->attn_max_chunks); ap.max_multi = w.attn_multi;
+    rc |= pl::launch_rope_append(w.parts, slices(e->ks_qkv), w.cs, w.m_pos(true), w.m_row_slot(true), w.pt, w.q_rot, kv_layer, n,
+                                 c.n_q_heads, c.n_kv_heads, c.head_dim, e->page_tokens, e->pages_per_seq, s);
+    ap.q = w.q_rot; ap.kv = kv_layer;
     if (prefill && l + 1 == c.n_layers) break;
     if (timed && e->profile) {   // the timers bracket the decode kernel alone; the merge kernel counts as "other"
       mark(e, CAT_OTHER, true);
@@ -529,13 +533,12 @@ void drop_graph(pl_engine::StepGraph &g) {
 int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) {
   if (!e->use_graphs || (!prefill && e->profile != 0)) return enqueue_step(e, w, n, prefill);
   const int set = prefill ? 1 : 0;
-  // grid bounds of the attention kernels in coarse steps, so that few shapes occur; workgroups beyond
+  // grid bound of the attention kernel in coarse steps, so that few shapes occur; workgroups beyond
   // the lists' real lengths (which the kernels read from device memory) leave at once
-  w.attn_items = std::min((w.attn_items + 63) / 64 * 64, n * e->attn_max_chunks);
-  if (w.attn_multi) w.attn_multi = std::min((w.attn_multi + 15) / 16 * 16, n);
+  w.attn_items = (int)std::min<int64_t>((w.attn_items + 63) / 64 * 64, w.items_cap);
   pl_engine::StepGraph *g = nullptr;
   for (auto &x : e->graphs)
-    if (x.n == n && x.buf == e->active_buf && x.items == w.attn_items && x.multi == w.attn_multi && x.set == set) { g = &x; break; }
+    if (x.n == n && x.buf == e->active_buf && x.items == w.attn_items && x.split == w.attn_split && x.set == set) { g = &x; break; }
   if (!g) {
     if (e->graphs.size() >= MAX_STEP_GRAPHS) {   // evict the least recently used
       size_t lru = 0;
@@ -545,7 +548,7 @@ int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) {
       e->graphs.erase(e->graphs.begin() + lru);
     }
     pl_engine::StepGraph ng;
-    ng.n = n; ng.buf = e->active_buf; ng.items = w.attn_items; ng.multi = w.attn_multi; ng.set = set;
+    ng.n = n; ng.buf = e->active_buf; ng.items = w.attn_items; ng.split = w.attn_split; ng.set = set;
     HIP_TRY(hipStreamBeginCapture(w.stream, hipStreamCaptureModeThreadLocal));
     const int rc = enqueue_step(e, w, n, prefill);
     const hipError_t ce = hipStreamEndCapture(w.stream, &ng.graph);
@@ -681,7 +684,7 @@ int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::ve
         harvest_passes(e);
       }
       w.meta_h = im.meta_h;
-      int items = 0, multi = 0;
+      int items = 0;
       int32_t *row_slot = w.m_row_slot(false), *pos = w.m_pos(false), *inp = w.m_input(false), *frc = w.m_forced(false);
       float *inv_t = w.m_inv_t(false);
       uint64_t *sid = w.m_seq_id(false);
@@ -694,10 +697,8 @@ int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::ve
         inv_t[r] = q.inv_t;
         sid[r] = q.seq_id;
         items += (pos[r] + 1 + e->attn_chunk - 1) / e->attn_chunk;
-        multi += pos[r] + 1 > e->attn_chunk;
       }
       w.attn_items = items;
-      w.attn_multi = multi;
       hipStream_t s = w.stream;
       // The page table goes up on this stream into this set's own device copy (no device buffer is ever
       // written from two streams); the rows of the slots being read do not change while they are read.
@@ -783,7 +784,8 @@ int pl_create(const pl_model_cfg *cfg, pl_engine **out) {
   e->seqs.resize(cfg->max_batch);
   set_pool_pages(e, n_pages);
   e->rows_cap = std::max(cfg->max_batch, 256);
-  e->pass_rows = e->f32 ? e->rows_cap : pl::GEMM_MAX_ROWS;   // the fp32 test build keeps whole products: fewer rows
+  // no more than all slots can hold; the fp32 test build keeps whole products: fewer rows
+  e->pass_rows = e->f32 ? e->rows_cap : (int)std::min<int64_t>(std::max<int64_t>((int64_t)cfg->max_batch * cfg->max_context, e->rows_cap), pl::GEMM_MAX_ROWS);
   e->wk[0].rows_cap = e->rows_cap;
   e->wk[1].rows_cap = e->pass_rows;
   if (e->dry) {
@@ -1147,7 +1149,7 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
   uint64_t *sid = w.m_seq_id(false);
   int r = 0;
   double kv_tokens = 0;
-  int items = 0, multi = 0;
+  int items = 0, subs = 0, longest = 0;
   for (int s = 0; s < c.max_batch; ++s) {
     Seq &q = e->seqs[s];
     if (!q.active || q.reading) continue;
@@ -1166,12 +1168,13 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
     sid[r] = q.seq_id;
     kv_tokens += q.pos;
     items += (q.pos + 1 + e->attn_chunk - 1) / e->attn_chunk;
-    multi += q.pos + 1 > e->attn_chunk;
+    subs += q.pos / pl::ATTN_SUB + 1;
+    longest = std::max(longest, std::min(q.pos + 1, e->attn_chunk));
     ++r;
   }
 
-  w.attn_items = items;
-  w.attn_multi = multi;
+  w.attn_split = pl::attention_split(e->attn_chunk, (int64_t)kv_tokens + r, longest, subs, c.n_kv_heads);
+  w.attn_items = w.attn_split ? subs : items;
 
   // 4. run
   if (!e->dry) {
@@ -1406,11 +1409,14 @@ int pl_debug_kv_pool(pl_engine *e, void **device_ptr, int64_t *nbytes) {
 
 // ---- kernel-level entry points ---------------------------------------------------------------------
 
+// Calls with at most this many workgroups need no work list: all of them run at once, or nearly, in any order.
+static bool attention_direct(int32_t n_seq, int32_t n_kv_heads, int64_t max_chunks) { return n_seq * max_chunks * n_kv_heads <= 2048; }
+
 int64_t pl_attention_workspace_bytes(int32_t n_seq, int32_t n_q_heads, int32_t n_kv_heads, int32_t hd, int32_t max_ctx) {
   if (n_seq < 1 || n_q_heads < 1 || n_kv_heads < 1 || hd < 1 || max_ctx < 1) return 0;
   const int chunk = pl::attention_chunk_tokens(n_seq, n_kv_heads, max_ctx);
-  const int64_t max_chunks = (max_ctx + chunk - 1) / chunk;
-  return (int64_t)n_seq * n_q_heads * max_chunks * (hd + 2) * 4 + pl::attention_worklist_ints(n_seq, (int)max_chunks) * 4 + 32;
+  const int64_t max_chunks = (max_ctx + chunk - 1) / chunk, np = (int64_t)n_seq * max_chunks;
+  return np * n_q_heads * hd * 4 + np * n_kv_heads * pl::ATTN_ML * 4 + (pl::attention_worklist_ints(np) + (int64_t)n_seq * n_kv_heads) * 4 + 128;
 }
 
 int pl_attention_decode(const void *q, const void *kv_pages, const int32_t *page_table, const int32_t *ctx_len,
@@ -1426,18 +1432,18 @@ int pl_attention_decode(const void *q, const void *kv_pages, const int32_t *page
   p.row_slot = nullptr; p.out = (bf16_t *)out;
   p.n_seq = n_seq; p.Hq = n_q_heads; p.Hkv = n_kv_heads; p.hd = hd; p.page_tokens = page_tokens;
   p.pages_per_seq = pages_per_seq;
-  p.chunk = pl::attention_chunk_tokens(n_seq, n_kv_heads, max_ctx);
+  p.chunk = p.item_tokens = pl::attention_chunk_tokens(n_seq, n_kv_heads, max_ctx);
   p.max_chunks = (max_ctx + p.chunk - 1) / p.chunk;
-  const int64_t np = (int64_t)n_seq * n_q_heads * p.max_chunks;
-  p.part_o = (float *)workspace;
-  p.part_ml = p.part_o + np * hd;
-  int32_t *work = (int32_t *)(((uintptr_t)(p.part_ml + np * 2) + 31) & ~(uintptr_t)31);   // records are read 16 bytes at a time
-  p.work = work;
-  p.multi = pl::attention_multi_list(work, n_seq, p.max_chunks);
-  p.max_items = n_seq * p.max_chunks;
-  p.max_multi = p.max_chunks > 1 ? n_seq : 0;
+  const int64_t np = (int64_t)n_seq * p.max_chunks;
+  p.part_o = (float *)(((uintptr_t)workspace + 127) & ~(uintptr_t)127);   // parts start on cache lines of their own
+  p.part_ml = p.part_o + np * n_q_heads * hd;
+  p.max_items = (int32_t)np;
   if (n_seq > 1024) return fail(PL_E_INVAL, "at most 1024 sequences per launch");
-  if (pl::launch_attention_worklist(ctx_len, nullptr, page_table, work, n_seq, p.max_chunks, p.chunk, page_tokens, pages_per_seq, (hipStream_t)stream)) return fail(PL_E_HIP, "attention launch failed");
+  if (!attention_direct(n_seq, n_kv_heads, p.max_chunks)) {
+    p.work = (int32_t *)(p.part_ml + np * n_kv_heads * pl::ATTN_ML);
+    p.tickets = p.work + pl::attention_worklist_ints(np);
+    if (pl::launch_attention_worklist(p, p.max_items, (hipStream_t)stream)) return fail(PL_E_HIP, "attention launch failed");
+  }
   if (pl::launch_attention(p, (hipStream_t)stream)) return fail(PL_E_HIP, "attention launch failed");
   return PL_OK;
 }

@@ -5,6 +5,7 @@ are compared bit-exactly given identical logits: the engine's own draw must equa
 run on the engine's logits."""
 import numpy as np
 import pytest
+import torch
 
 import paper_2509_19128_amd as pl
 import synth
@@ -434,6 +435,71 @@ def test_prompt_passes_of_many_rows_leave_the_cache_of_reading_token_by_token(we
         assert np.array_equal(logits[0], logits[1]) and outs[0]["logprob"][0] == outs[1]["logprob"][0]
     for e in engines:
         e.close()
+
+
+@pytest.mark.parametrize("Hq,Hkv,hd,d", [(16, 1, 128, 256), (4, 4, 64, 256), (8, 1, 32, 256), (12, 2, 64, 2560)])
+def test_decode_steps_rotate_and_append_like_the_passes(Hq, Hkv, hd, d):
+    """A decode step's attention adds up the QKV slices, rotates and appends by itself, a pass in a kernel of its
+    own: caches and logits of a prompt read one token per step and in a pass are bit-identical for every head
+    dimension, groups of one head and of 16 (more rotated quads than threads), one slice and more than eight."""
+    m = synth.ModelCfg(2, d, Hq, Hkv, hd, 256, 512)
+    eng = [pl.Engine.from_model(m, max_batch=2, max_context=256, kv_pool_tokens=512, kv_page_tokens=64, seed=3, device=0) for _ in range(2)]
+    blob = eng[0].pack_weights(synth.make_weights(m, seed=9), synth.f32_to_bf16_bits)
+    prompts = synth.random_prompts(np.random.default_rng(4), 2, 140, m.vocab)
+    for e in eng:
+        e.load_weights(blob)
+        for i in range(2):
+            e.add_sequence(i, prompts[i], 4)
+    for i in range(2):
+        eng[0].prefill(i)
+    for _ in range(139):
+        eng[1].decode_step()
+    for i in range(2):
+        kv = [[e.debug_read_kv(i, l, 139) for l in range(m.n_layers)] for e in eng]
+        for l in range(m.n_layers):
+            for part in range(2):
+                assert np.array_equal(kv[0][l][part], kv[1][l][part]), (i, l, part)
+    for _ in range(3):
+        for e in eng:
+            e.decode_step(np.array([5, 6], np.int32))
+        logits = [e.debug_get_logits(2) for e in eng]
+        assert np.isfinite(logits[0]).all() and np.array_equal(logits[0], logits[1])
+    for e in eng:
+        e.close()
+
+
+def test_a_sequence_alone_equals_the_same_among_many(weights):
+    """An engine of 512 slots has attention chunks of 2048 tokens here.  A step of few sequences cuts them into
+    smaller work items, a step of many does not: the same sequences' logits are bit-identical, at contexts around
+    the ends of an item, of a chunk and of a wavefront's share."""
+    master, _ = weights
+    contexts = [2500, 2048, 2049, 1536, 1537, 513, 3600, 2080]
+    seen = []
+    for n in (len(contexts), 60):
+        eng = pl.Engine.from_model(M, max_batch=512, max_context=4096, kv_pool_tokens=62 * 4096, kv_page_tokens=128, seed=SEED, device=0)
+        eng.load_weights(eng.pack_weights(master, synth.f32_to_bf16_bits))
+        ptr, nbytes = eng.debug_kv_pool()
+        pool = torch.as_tensor(_Device(ptr, nbytes // 2), device="cuda").view(torch.bfloat16)
+        pool.normal_(0, 1, generator=torch.Generator(device="cuda").manual_seed(3))
+        torch.cuda.synchronize()
+        for i in range(n):      # the first ones get the same pages in both engines
+            c = contexts[i] if i < len(contexts) else 3000 + 7 * i
+            assert eng.debug_add_sequence_at(i, None, 16, 4096 - 16, 1.0, c - 1, c - 16, 5 + i % 50) == i
+        for _ in range(3):
+            out = eng.decode_step(np.full(512, 9, np.int32))
+            assert out["n"] == n
+            seen.append((n, eng.debug_get_logits(n)[:len(contexts)], out["logprob"][:len(contexts)].copy()))
+        eng.close()
+    for few, many in zip(seen[:3], seen[3:]):
+        assert few[0] != many[0] and np.isfinite(few[1]).all()
+        assert np.array_equal(few[1], many[1]) and np.array_equal(few[2], many[2])
+
+
+class _Device:
+    """A device buffer that the library owns, for torch.as_tensor."""
+
+    def __init__(self, ptr, n):
+        self.__cuda_array_interface__ = dict(shape=(n,), typestr="<i2", data=(ptr, False), version=2)
 
 
 def test_batched_prefill_under_the_weights_active_at_admission_then_a_swap(weights):
