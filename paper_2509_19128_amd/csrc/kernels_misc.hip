@@ -1,42 +1,10 @@
-// Small row-wise kernels of the decode step: token select + embedding gather + RMSNorm, residual
-// add (summing split-K partials) + RMSNorm, rotary tables, rotary + KV-cache append.
+// Small row-wise kernels of the decode step: the kernel that begins a step (metadata, work list, rotary tables,
+// embedding gather + RMSNorm), residual add (summing split-K partials) + RMSNorm, rotary + KV-cache append.
+#include "attn_worklist.h"
 #include "pl_common.h"
 
 namespace pl {
 namespace {
-
-__device__ inline float block_sum_256(float v) {
-  __shared__ float red[4];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return red[0] + red[1] + red[2] + red[3];
-}
-
-// h[row] = E[token]; a[row] = rmsnorm(h[row]) * g.  token = input_tok[row] if >= 0, else the token
-// the previous step produced for this row's slot.
-__global__ __launch_bounds__(256) void embed_rmsnorm_kernel(const bf16_t *embed, const bf16_t *g,
-                                                            const int32_t *input_tok, const int32_t *last_tok,
-                                                            const int32_t *row_slot, float *h, bf16_t *a,
-                                                            int d, int vocab, float eps) {
-  const int row = blockIdx.x;
-  int tok = input_tok[row];
-  if (tok < 0 && last_tok) tok = last_tok[row_slot[row]];
-  tok = min(max(tok, 0), vocab - 1);
-  const bf16_t *e = embed + (int64_t)tok * d;
-  float ss = 0.f;
-  for (int i = threadIdx.x; i < d; i += 256) {
-    float v = (float)e[i];
-    h[(int64_t)row * d + i] = v;
-    ss += v * v;
-  }
-  ss = block_sum_256(ss);
-  const float r = 1.0f / sqrtf(ss / (float)d + eps);
-  for (int i = threadIdx.x; i < d; i += 256)
-    a[(int64_t)row * d + i] = (__bf16)(h[(int64_t)row * d + i] * r * (float)g[i]);
-}
 
 template <int NW>
 __device__ inline float block_sum(float v) {
@@ -50,6 +18,64 @@ __device__ inline float block_sum(float v) {
 #pragma unroll
   for (int w = 0; w < NW; ++w) t += red[w];
   return t;
+}
+
+// cos/sin of pos * theta^(-2i/hd), evaluated in double so long positions lose nothing
+__device__ inline void rope_angle(float *cs, int pos, int i, int hd, float theta) {
+  const double inv_freq = pow((double)theta, -2.0 * (double)i / (double)hd);
+  const double ang = (double)pos * inv_freq;
+  cs[i] = (float)cos(ang);
+  cs[hd / 2 + i] = (float)sin(ang);
+}
+
+// The beginning of a step or pass, one launch: everything the layers need that depends on the metadata alone.
+// Workgroup 0 applies the step's page-table changes and builds the attention work list; workgroup r + 1 brings
+// row r: its metadata (read from the host's pinned image in a decode step, where a copy would be a launch of its
+// own ahead of this one), cos/sin of its position, h = E[token], a = rmsnorm(h) * g.
+// As separate launches: metadata copy 4 us, tables 4, work list 13, embedding 13 (7B shape, 256 rows), each with its
+// launch gap; now 14 us.
+__global__ __launch_bounds__(1024) void step_begin_kernel(StepBegin q, AttnParams p, int cap) {
+  if (blockIdx.x == 0) {
+    const int n_upd = q.updates ? q.updates[0] : 0;
+    for (int i = threadIdx.x; i < n_upd; i += 1024) q.page_table[q.updates[2 + 2 * i]] = q.updates[3 + 2 * i];
+    __syncthreads();   // the list is built from the table
+    const int b = threadIdx.x;
+    const bool has = b < p.n_seq;
+    build_worklist(has ? q.src.pos[b] + 1 : 0, has ? q.src.row_slot[b] : 0, q.page_table, p.work, p.tickets, p.first_item, p.n_seq, p.Hkv,
+                   p.item_tokens, p.page_tokens, p.pages_per_seq, cap, p.item_tokens < p.chunk);
+    return;
+  }
+  const int row = blockIdx.x - 1, pos = q.src.pos[row], d8 = q.d >> 3;
+  const int tok = min(max(q.src.input_tok[row], 0), q.vocab - 1);
+  const bool mine = (int)threadIdx.x < d8;   // d <= 8192: one piece of eight elements per thread
+  bf16x8 e = {};
+  if (mine) e = ((const bf16x8 *)(q.embed + (int64_t)tok * q.d))[threadIdx.x];
+  const int i = 1023 - (int)threadIdx.x;   // the last wavefronts, which have least of the row, take the angles
+  if (i < p.hd / 2) rope_angle(q.cs + (int64_t)row * p.hd, pos, i, p.hd, q.theta);
+  if (threadIdx.x == 0) {
+    q.ctx_len[row] = pos + 1;
+    if (q.dst.pos) {
+      q.dst.row_slot[row] = q.src.row_slot[row];
+      q.dst.pos[row] = pos;
+      q.dst.forced[row] = q.src.forced[row];
+      q.dst.inv_t[row] = q.src.inv_t[row];
+      q.dst.seq_id[row] = q.src.seq_id[row];
+    }
+  }
+  float v[8], ss = 0.f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) { v[k] = (float)e[k]; ss += v[k] * v[k]; }
+  ss = block_sum<16>(ss);
+  if (!mine) return;
+  const float r = 1.0f / sqrtf(ss / (float)q.d + q.eps);
+  const bf16x8 g = ((const bf16x8 *)q.g)[threadIdx.x];
+  bf16x8 o;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) o[k] = (__bf16)(v[k] * r * (float)g[k]);
+  f32x4 *h = (f32x4 *)(q.h + (int64_t)row * q.d) + 2 * threadIdx.x;
+  h[0] = f32x4{v[0], v[1], v[2], v[3]};
+  h[1] = f32x4{v[4], v[5], v[6], v[7]};
+  ((bf16x8 *)(q.a + (int64_t)row * q.d))[threadIdx.x] = o;
 }
 
 // h[row] += sum_s parts[s][row]; a[row] = rmsnorm(h[row]) * g.  The slices are added up in slice order, their
@@ -101,17 +127,13 @@ __global__ __launch_bounds__(NT) void resid_rmsnorm_kernel(float *h, const float
   }
 }
 
-// cos/sin of pos * theta^(-2i/hd), evaluated in double so long positions lose nothing; also the
-// attention length of the step (pos + 1).
+// The rotary tables alone, and the attention length of the step (pos + 1): fp32 test build.
 __global__ void rope_tables_kernel(const int32_t *pos, float *cs, int32_t *ctx_len, int n, int hd, float theta) {
   const int half = hd / 2;
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n * half) return;
   const int row = idx / half, i = idx % half;
-  const double inv_freq = pow((double)theta, -2.0 * (double)i / (double)hd);
-  const double ang = (double)pos[row] * inv_freq;
-  cs[(int64_t)row * hd + i] = (float)cos(ang);
-  cs[(int64_t)row * hd + half + i] = (float)sin(ang);
+  rope_angle(cs + (int64_t)row * hd, pos[row], i, hd, theta);
   if (i == 0) ctx_len[row] = pos[row] + 1;
 }
 
@@ -217,12 +239,10 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int64_t n) {
 
 static inline int ok() { return hipGetLastError() == hipSuccess ? 0 : -7; }
 
-int launch_embed_rmsnorm(const bf16_t *embed, const bf16_t *g, const int32_t *input_tok,
-                         const int32_t *last_tok, const int32_t *row_slot, float *h, bf16_t *a, int n,
-                         int d, int vocab, float eps, hipStream_t s) {
-  if (n <= 0) return 0;
-  hipLaunchKernelGGL(embed_rmsnorm_kernel, dim3(n), dim3(256), 0, s, embed, g, input_tok, last_tok, row_slot,
-                     h, a, d, vocab, eps);
+int launch_step_begin(const StepBegin &q, const AttnParams &p, int cap, hipStream_t s) {
+  if (p.n_seq <= 0) return 0;
+  if (p.n_seq > 1024 || q.d > 8192 || ((uintptr_t)p.work & 31)) return -1;
+  hipLaunchKernelGGL(step_begin_kernel, dim3(p.n_seq + 1), dim3(1024), 0, s, q, p, cap);
   return ok();
 }
 

@@ -124,14 +124,25 @@ int launch_sample(const SampleParams &p, hipStream_t s);
 int sample_static_workspace(int n, int vocab, void **ptr);
 void sample_static_limits(int *max_rows, int *max_vocab);
 
-// per-step metadata, one row per occupied slot (device copies of host arrays)
+// per-step metadata, one row per occupied slot
 struct StepMeta {
-  const int32_t *row_slot, *pos, *input_tok, *forced;
-  const float *inv_t; const uint64_t *seq_id;
+  int32_t *row_slot, *pos, *input_tok, *forced;
+  float *inv_t;
+  uint64_t *seq_id;
 };
-int launch_embed_rmsnorm(const bf16_t *embed, const bf16_t *g, const int32_t *input_tok,
-                         const int32_t *last_tok, const int32_t *row_slot, float *h, bf16_t *a,
-                         int n, int d, int vocab, float eps, hipStream_t s);
+struct StepBegin {
+  StepMeta src;             // where the rows' metadata is read: the host's pinned image, or the device's
+  StepMeta dst;             // device copies for the kernels that follow (pos null: src is the device's)
+  const int32_t *updates;   // null, or {count, -, (element of the page table, page id) ...}
+  int32_t *page_table;
+  const bf16_t *embed, *g;
+  float *h, *cs;
+  bf16_t *a;
+  int32_t *ctx_len;
+  int32_t d, vocab;
+  float eps, theta;
+};
+int launch_step_begin(const StepBegin &q, const AttnParams &p, int cap, hipStream_t s);
 int launch_resid_rmsnorm(float *h, const float *parts, int splits, const bf16_t *g, bf16_t *a, int n,
                          int d, float eps, hipStream_t s);
 int launch_rope_tables(const int32_t *pos, float *cs, int32_t *ctx_len, int n, int hd, float theta,

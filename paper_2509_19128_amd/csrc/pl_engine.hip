@@ -119,7 +119,13 @@ struct pl_engine {
     int32_t *m_input(bool dev) { return m_pos(dev) + rows_cap; }
     int32_t *m_forced(bool dev) { return m_input(dev) + rows_cap; }
     float *m_inv_t(bool dev) { return (float *)(m_forced(dev) + rows_cap); }
+    // page-table changes of a decode step (host image only): count, unused, then (element, page id) pairs
+    int32_t *m_updates() { return (int32_t *)(m_inv_t(false) + rows_cap); }
     int64_t meta_bytes() const { return (int64_t)rows_cap * (4 * 5 + 8); }
+    int64_t image_bytes() const { return meta_bytes() + ((int64_t)rows_cap * 2 + 2) * 4; }
+    pl::StepMeta meta(bool dev) {
+      return pl::StepMeta{m_row_slot(dev), m_pos(dev), m_input(dev), m_forced(dev), m_inv_t(dev), m_seq_id(dev)};
+    }
   };
   Work wk[2];
   // Host images of the cache-only passes in flight: a pass's image must stay intact until its copy to
@@ -141,10 +147,8 @@ struct pl_engine {
   hipEvent_t ev_pre_buf[2] = {nullptr, nullptr};
   bool pre_buf_pending[2] = {false, false};
   float *logits = nullptr;
-  int32_t *tok_d = nullptr;
-  float *lp_d = nullptr;
   void *samp_ws = nullptr;
-  int32_t *tok_h = nullptr;
+  int32_t *tok_h = nullptr;   // pinned: the sampler writes the step's tokens and log-probs there itself
   float *lp_h = nullptr;
   int attn_chunk = 1024, attn_max_chunks = 1;
   pl::GemmSplit ks_qkv{1, 0, 1}, ks_o{1, 0, 1}, ks_gu{1, 0, 1}, ks_d{1, 0, 1}, ks_lm{1, 0, 1};
@@ -267,18 +271,20 @@ int alloc_work(pl_engine *e, pl_engine::Work &w, int64_t R, int64_t parts_elems,
   if ((rc = dev_alloc(&w.pt, (int64_t)c.max_batch * e->pages_per_seq))) return rc;
   const int64_t split = e->attn_chunk > pl::ATTN_SUB ? pl::ATTN_SPLIT_PARTS : 0;   // (sub, kv head) pairs
   const int64_t np = std::max<int64_t>(R * c.n_kv_heads * e->attn_max_chunks, 4 * split);
-  if ((rc = dev_alloc(&w.attn_po, np * e->G * c.head_dim))) return rc;
-  if ((rc = dev_alloc(&w.attn_pml, np * pl::ATTN_ML))) return rc;
+  const int64_t po = np * e->G * c.head_dim;   // a multiple of a cache line (32 floats)
+  if ((rc = dev_alloc(&w.attn_po, po + np * pl::ATTN_ML))) return rc;
+  w.attn_pml = w.attn_po + po;
   w.items_cap = std::max<int64_t>(R * e->attn_max_chunks, split);
-  if ((rc = dev_alloc(&w.attn_work, pl::attention_worklist_ints(w.items_cap)))) return rc;
-  if ((rc = dev_alloc(&w.attn_tickets, R * c.n_kv_heads))) return rc;
-  if ((rc = dev_alloc(&w.attn_first, R))) return rc;
-  if (pinned_image) HIP_TRY(hipHostMalloc((void **)&w.meta_h, (size_t)w.meta_bytes(), hipHostMallocDefault));
+  const int64_t work = pl::attention_worklist_ints(w.items_cap);
+  if ((rc = dev_alloc(&w.attn_work, work + R * c.n_kv_heads + R))) return rc;
+  w.attn_tickets = w.attn_work + work;
+  w.attn_first = w.attn_tickets + R * c.n_kv_heads;
+  if (pinned_image) HIP_TRY(hipHostMalloc((void **)&w.meta_h, (size_t)w.image_bytes(), hipHostMallocDefault));
   return PL_OK;
 }
 
 void free_work(pl_engine::Work &w) {
-  void *dev[] = {w.meta_d, w.h, w.a, w.parts, w.q_rot, w.attn_out, w.mid, w.cs, w.ctx_len, w.pt, w.attn_po, w.attn_pml, w.attn_work, w.attn_tickets, w.attn_first};
+  void *dev[] = {w.meta_d, w.h, w.a, w.parts, w.q_rot, w.attn_out, w.mid, w.cs, w.ctx_len, w.pt, w.attn_po, w.attn_work};
   for (void *p : dev)
     if (p) (void)hipFree(p);
   w = pl_engine::Work{};
@@ -348,8 +354,6 @@ int alloc_device(pl_engine *e) {
   e->ev_slot.resize(B);
   for (auto &ev : e->ev_slot) HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
   if ((rc = dev_alloc(&e->logits, (int64_t)B * c.vocab))) return rc;
-  if ((rc = dev_alloc(&e->tok_d, B))) return rc;
-  if ((rc = dev_alloc(&e->lp_d, B))) return rc;
   char *ws = nullptr;
   if ((rc = dev_alloc(&ws, pl::sample_workspace_bytes(B, c.vocab)))) return rc;
   e->samp_ws = ws;
@@ -440,7 +444,7 @@ int enqueue_step_f32(pl_engine *e, pl_engine::Work &w, int n, bool prefill) {
   pl::SampleParams sp{};
   sp.logits = e->logits; sp.n = n; sp.vocab = c.vocab; sp.seq_id = w.m_seq_id(true);
   sp.position = w.m_pos(true); sp.inv_t = w.m_inv_t(true); sp.forced = w.m_forced(true);
-  sp.seed = c.seed; sp.token = e->tok_d; sp.logprob = e->lp_d; sp.workspace = e->samp_ws;
+  sp.seed = c.seed; sp.token = e->tok_h; sp.logprob = e->lp_h; sp.workspace = e->samp_ws;
   rc |= pl::launch_sample(sp, s);
   return rc ? fail(PL_E_HIP, "kernel launch failed: %s", hipGetErrorString(hipGetLastError())) : PL_OK;
 }
@@ -464,7 +468,6 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
     return fold ? pl::launch_gemm_folded(x, wt, y, n, N, K, mode, ks, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, s);
   };
   auto slices = [&](const pl::GemmSplit &ks) { return fold ? 1 : ks.splits; };
-  rc |= pl::launch_rope_tables(w.m_pos(true), w.cs, w.ctx_len, n, c.head_dim, c.rope_theta, s);
   pl::AttnParams ap{};
   ap.page_table = w.pt; ap.ctx_len = w.ctx_len; ap.row_slot = w.m_row_slot(true);
   ap.out = w.attn_out; ap.part_o = w.attn_po; ap.part_ml = w.attn_pml;
@@ -472,10 +475,13 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   ap.page_tokens = e->page_tokens; ap.pages_per_seq = e->pages_per_seq; ap.chunk = e->attn_chunk;
   ap.max_chunks = e->attn_max_chunks; ap.item_tokens = w.attn_split ? pl::ATTN_SUB : e->attn_chunk;
   ap.work = w.attn_work; ap.tickets = w.attn_tickets; ap.first_item = w.attn_first; ap.max_items = w.attn_items;
-  rc |= pl::launch_attention_worklist(ap, w.attn_items, s);
-  const bf16_t *g_first = c.n_layers ? layer_weights(e, 0).g1 : gf;
-  rc |= pl::launch_embed_rmsnorm(embed, g_first, w.m_input(true), nullptr, w.m_row_slot(true), w.h, w.a, n,
-                                 d, c.vocab, c.rms_eps, s);
+  pl::StepBegin sb{};
+  sb.src = w.meta(prefill);   // a pass's metadata is on the device already, a decode step's is fetched from the host's image
+  if (!prefill) { sb.dst = w.meta(true); sb.updates = w.m_updates(); }
+  sb.page_table = w.pt; sb.embed = embed; sb.g = c.n_layers ? layer_weights(e, 0).g1 : gf;
+  sb.h = w.h; sb.cs = w.cs; sb.a = w.a; sb.ctx_len = w.ctx_len;
+  sb.d = d; sb.vocab = c.vocab; sb.eps = c.rms_eps; sb.theta = c.rope_theta;
+  rc |= pl::launch_step_begin(sb, ap, w.attn_items, s);
   for (int l = 0; l < c.n_layers && !rc; ++l) {
     const LayerW lw = layer_weights(e, l);
     bf16_t *kv_layer = (bf16_t *)e->kv_pool + (int64_t)l * e->layer_stride;
@@ -512,7 +518,7 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   pl::SampleParams sp{};
   sp.logits = e->logits; sp.n = n; sp.vocab = c.vocab; sp.seq_id = w.m_seq_id(true);
   sp.position = w.m_pos(true); sp.inv_t = w.m_inv_t(true); sp.forced = w.m_forced(true);
-  sp.seed = c.seed; sp.token = e->tok_d; sp.logprob = e->lp_d; sp.workspace = e->samp_ws;
+  sp.seed = c.seed; sp.token = e->tok_h; sp.logprob = e->lp_h; sp.workspace = e->samp_ws;
   sp.last_tok = nullptr; sp.row_slot = nullptr;
   rc |= pl::launch_sample(sp, s);
   mark(e, CAT_SAMPLE);
@@ -789,7 +795,7 @@ int pl_create(const pl_model_cfg *cfg, pl_engine **out) {
   e->wk[0].rows_cap = e->rows_cap;
   e->wk[1].rows_cap = e->pass_rows;
   if (e->dry) {
-    e->wk[0].meta_h = (char *)calloc(1, (size_t)e->wk[0].meta_bytes());
+    e->wk[0].meta_h = (char *)calloc(1, (size_t)e->wk[0].image_bytes());
     if (!e->wk[0].meta_h) { delete e; return fail(PL_E_NOMEM, "out of host memory"); }
   } else {
     if (cfg->device < 0) { delete e; return fail(PL_E_INVAL, "bad device"); }
@@ -809,7 +815,7 @@ void pl_destroy(pl_engine *e) {
     if (e->s_dec) (void)hipStreamSynchronize(e->s_dec);
     if (e->s_copy) (void)hipStreamSynchronize(e->s_copy);
     if (e->wk[1].stream) (void)hipStreamSynchronize(e->wk[1].stream);
-    void *dev[] = {e->wbuf[0], e->wbuf[1], e->kv_pool, e->logits, e->tok_d, e->lp_d, e->samp_ws};
+    void *dev[] = {e->wbuf[0], e->wbuf[1], e->kv_pool, e->logits, e->samp_ws};
     for (void *p : dev)
       if (p) (void)hipFree(p);
     void *hst[] = {e->pt_h, e->wk[0].meta_h, e->tok_h, e->lp_h};
@@ -1149,15 +1155,20 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
   uint64_t *sid = w.m_seq_id(false);
   int r = 0;
   double kv_tokens = 0;
-  int items = 0, subs = 0, longest = 0;
+  int items = 0, subs = 0, longest = 0, n_upd = 0;
+  int32_t *upd = w.m_updates();
   for (int s = 0; s < c.max_batch; ++s) {
     Seq &q = e->seqs[s];
     if (!q.active || q.reading) continue;
     if (q.pos / e->page_tokens >= (int)q.pages.size()) {
       q.pages.push_back(e->free_pages.back());
       e->free_pages.pop_back();
-      if (e->pt_h) e->pt_h[(int64_t)s * e->pages_per_seq + q.pages.size() - 1] = q.pages.back();
-      e->pt_dirty = true;
+      if (e->pt_h) {   // one element per slot and step at most
+        const int64_t at = (int64_t)s * e->pages_per_seq + q.pages.size() - 1;
+        e->pt_h[at] = q.pages.back();
+        upd[2 + 2 * n_upd] = (int32_t)at;
+        upd[3 + 2 * n_upd++] = q.pages.back();
+      }
     }
     row_slot[r] = s;
     pos[r] = q.pos;
@@ -1180,18 +1191,22 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
   if (!e->dry) {
     HIP_TRY(hipSetDevice(c.device));
     hipStream_t s = e->s_dec;
-    if (e->pt_dirty) {
+    // admissions change many elements of the page table: the whole table goes up; pages added by this step are
+    // applied by its first kernel, which also fetches the metadata from the host's image
+    if (e->pt_dirty || (e->f32 && n_upd)) {
       HIP_TRY(hipMemcpyAsync(w.pt, e->pt_h, (size_t)c.max_batch * e->pages_per_seq * 4, hipMemcpyHostToDevice, s));
       e->pt_dirty = false;
     }
-    HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)w.meta_bytes(), hipMemcpyHostToDevice, s));
+    upd[0] = n_upd;
+    if (e->f32) HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)w.meta_bytes(), hipMemcpyHostToDevice, s));
     HIP_TRY(hipEventRecord(e->ev_a, s));
     e->prof_n = 0;   // a replayed graph records no per-kernel events: nothing of an earlier step may be counted again
     int rc = run_step(e, w, n);
-    if (rc) return rc;
+    if (rc) {
+      e->pt_dirty = true;   // this step's page-table changes may not have been applied
+      return rc;
+    }
     HIP_TRY(hipEventRecord(e->ev_b, s));
-    HIP_TRY(hipMemcpyAsync(e->tok_h, e->tok_d, (size_t)n * 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(e->lp_h, e->lp_d, (size_t)n * 4, hipMemcpyDeviceToHost, s));
     const double t_enq = now_ms();
     HIP_TRY(hipStreamSynchronize(s));
     e->st.host_enqueue_ms += t_enq - t_enter;
