@@ -32,12 +32,31 @@ __device__ inline float shfl_xor(float v, int mask) { return __shfl_xor(v, mask,
 
 // (m, l, o) <- (m, l, o) folded with a later part (mi, li, oi); m is in log2 units.  A part without tokens
 // has mi = -inf and changes nothing; the first part is taken over as it is.
+// The operations are spelled out so that every kernel rounds them alike.
+__device__ inline float fold_value(float o, float e0, float oi, float e1) { return __builtin_fmaf(o, e0, __fmul_rn(oi, e1)); }
+__device__ inline f32x4 fold_value(f32x4 o, float e0, f32x4 oi, float e1) {
+  f32x4 r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = fold_value(o[i], e0, oi[i], e1);
+  return r;
+}
+__device__ inline f32x4 fma4(f32x4 a, float b, f32x4 c) {
+  f32x4 r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = __builtin_fmaf(a[i], b, c[i]);
+  return r;
+}
+__device__ inline void fold_factors(float m, float mi, float &M, float &e0, float &e1) {
+  M = fmaxf(m, mi);
+  e0 = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
+  e1 = mi == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mi - M);
+}
 template <typename V>
 __device__ inline void fold_part(float &m, float &l, V &o, float mi, float li, V oi) {
-  const float M = fmaxf(m, mi);
-  const float e0 = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M), e1 = mi == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mi - M);
-  o = o * e0 + oi * e1;
-  l = l * e0 + li * e1;
+  float M, e0, e1;
+  fold_factors(m, mi, M, e0, e1);
+  o = fold_value(o, e0, oi, e1);
+  l = fold_value(l, e0, li, e1);
   m = M;
 }
 
@@ -191,15 +210,13 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
       m_all = m; l_all = lsum;
       return;
     }
-    const float M = fmaxf(m_all, m), e0 = __builtin_amdgcn_exp2f(m_all - M), e1 = __builtin_amdgcn_exp2f(m - M);
+    float M, e0, e1;
+    fold_factors(m_all, m, M, e0, e1);
     if (head < G) {
 #pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const f32x4 was = *(const f32x4 *)(mine + i * 16);
-        *(f32x4 *)(mine + i * 16) = was * e0 + o[i] * e1;
-      }
+      for (int i = 0; i < NV; ++i) *(f32x4 *)(mine + i * 16) = fold_value(*(const f32x4 *)(mine + i * 16), e0, o[i], e1);
     }
-    l_all = l_all * e0 + lsum * e1;
+    l_all = fold_value(l_all, e0, lsum, e1);
     m_all = M;
   };
   for (int base = wave; base < nblk; base += 4 * NS) {
@@ -245,7 +262,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
           psum += pe;
           pf[e] = (__bf16)pe;
         }
-        lsum = lsum * alpha + psum;
+        lsum = __builtin_fmaf(lsum, alpha, psum);
         m = m_new;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
@@ -290,8 +307,8 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       float f = __builtin_amdgcn_exp2f(sm_m[w][h] - M);
-      L += sm_l[w][h] * f;
-      O += sm_o[w][h][d] * f;
+      L = __builtin_fmaf(sm_l[w][h], f, L);
+      O = __builtin_fmaf(sm_o[w][h][d], f, O);
     }
     if (nchunk == 1) {
       p.out[((int64_t)b * p.Hq + g * G + h) * HD + d] = (__bf16)(O / L);
@@ -374,8 +391,8 @@ __global__ __launch_bounds__(HD) void attn_merge_kernel(AttnParams p) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const float f = __builtin_amdgcn_exp2f(sml[v][0] - Mc);
-      Lc += sml[v][1] * f;
-      Oc += so[v][threadIdx.x % QUADS] * f;
+      Lc = __builtin_fmaf(sml[v][1], f, Lc);
+      Oc = fma4(so[v][threadIdx.x % QUADS], f, Oc);
     }
     fold_part(M, L, O, Mc, Lc, Oc);
   }
@@ -384,6 +401,215 @@ __global__ __launch_bounds__(HD) void attn_merge_kernel(AttnParams p) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) out[e] = (__bf16)(O[e] / L);
   *(bf16x4 *)(p.out + ((int64_t)b * p.Hq + hq) * HD + d) = out;
+}
+
+// Attention of the rows of a cache-only pass: consecutive positions of one sequence, each over the positions up to its
+// own.  One workgroup per (group of rows, kv head) walks all keys of the group's longest row; the columns of an MFMA
+// are the heads of 16 / G rows, and every K/V operand serves CB such column blocks, where one row per workgroup
+// (as in a decode step) reads the sequence once per row.  Operation by operation the same sums as the decode kernel
+// for every row: runs, subs, wavefronts and chunks in the same order; a run that lies beyond a row's positions
+// leaves its column as it was (weights 0, factor 1).
+// Bound by vector arithmetic (about 100 operations per run and column block), then by L2.  3001-token prompt, 1.5B
+// shape: 960 -> 375 us over the twelve launches of its passes; 512-token prompt, 7B shape: 79 -> 57 us.
+template <int HD, int CB>
+__global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnParams p) {
+  constexpr int NJ = HD / 32, NV = HD / 16, COLS = CB * 16, PER = COLS * HD / 1024;
+  const int g = blockIdx.x % p.Hkv, n_groups = p.groups[0], index = n_groups - 1 - (int)(blockIdx.x / p.Hkv);   // longest rows first
+  if (index < 0) return;
+  const int row0 = p.groups[2 + 2 * index], nrows = p.groups[3 + 2 * index];
+  const int G = p.Hq / p.Hkv, rpb = 16 / G;   // rows of a column block
+  const int32_t *pt = p.page_table + (int64_t)p.row_slot[row0] * p.pages_per_seq;
+  const int ctx0 = p.ctx_len[row0], ctx_max = ctx0 + nrows - 1;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, col = l & 15, qg = l >> 4;
+  const float scale = 1.4426950408889634f / sqrtf((float)HD);   // log2(e) / sqrt(hd)
+  const int64_t page_elems = (int64_t)2 * p.page_tokens * HD;
+
+  // queries in operand order: element (column block, slice j, lane); in LDS, as the registers are taken by the results
+  __shared__ __attribute__((aligned(16))) bf16x8 sq[CB * NJ * 64];
+  for (int i = threadIdx.x; i < CB * NJ * 64; i += 256) {
+    const int ln = i & 63, j = i / 64 % NJ, cb = i / (64 * NJ), c = ln & 15, r = cb * rpb + c / G;
+    bf16x8 v = {};
+    if (c / G < rpb && r < nrows) v = *(const bf16x8 *)(p.q + ((int64_t)(row0 + r) * p.Hq + g * G + c % G) * HD + j * 32 + (ln >> 4) * 8);
+    sq[i] = v;
+  }
+  __shared__ int s_ctx[COLS];   // context of a column; columns without a row see no position
+  if (threadIdx.x < COLS) {
+    const int in = threadIdx.x % 16 / G, r = threadIdx.x / 16 * rpb + in;
+    s_ctx[threadIdx.x] = in < rpb && r < nrows ? ctx0 + r : 0;
+  }
+
+  __shared__ __attribute__((aligned(16))) float sm_o[4][COLS][HD];
+  __shared__ float sm_m[4][COLS], sm_l[4][COLS];
+  // Result of the chunks so far: a thread owns the quads threadIdx.x + 256 k of [COLS][HD].
+  f32x4 run_o[PER];
+  __shared__ float run_m[COLS], run_l[COLS], s_f[4][COLS], s_e[2][COLS];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) run_o[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (threadIdx.x < COLS) { run_m[threadIdx.x] = -INFINITY; run_l[threadIdx.x] = 0.f; }
+
+  __syncthreads();
+  int ctx[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) ctx[cb] = s_ctx[cb * 16 + col];
+  bf16x8 kf[2][NJ], vf[NV];
+  auto run_at = [&](int tok) {   // the run that starts at token tok, or the sequence's last one
+    tok = min(tok, (ctx_max - 1) & ~31);
+    return p.kv + ((int64_t)pt[tok / p.page_tokens] * p.Hkv + g) * page_elems + (int64_t)(tok % p.page_tokens) * HD + l * 8;
+  };
+  auto load_k = [&](const bf16_t *kb) {
+#pragma unroll
+    for (int T = 0; T < 2; ++T)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) kf[T][j] = *(const bf16x8 *)(kb + (T * NJ + j) * 512);
+  };
+  auto load_v = [&](const bf16_t *kb) {
+    const bf16_t *vb = kb + (int64_t)p.page_tokens * HD;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) vf[i] = *(const bf16x8 *)(vb + i * 512);
+  };
+  load_k(run_at(wave * 32));
+  load_v(run_at(wave * 32));
+  for (int t0 = 0; t0 < ctx_max; t0 += p.chunk) {
+    const int t1 = min(ctx_max, t0 + p.chunk), nblk = (t1 - t0 + 31) >> 5;
+    f32x4 o[CB][NV];
+    float m[CB], lsum[CB], m_all[CB], l_all[CB];
+    auto reset = [&]() {
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) {
+        m[cb] = -INFINITY;
+        lsum[cb] = 0.f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) o[cb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    };
+    reset();
+    bool folded = false;
+    auto fold_sub = [&]() {
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) {
+        lsum[cb] += shfl_xor(lsum[cb], 16);
+        lsum[cb] += shfl_xor(lsum[cb], 32);
+        float *mine = &sm_o[wave][cb * 16 + col][qg * 4];
+        if (!folded) {
+#pragma unroll
+          for (int i = 0; i < NV; ++i) *(f32x4 *)(mine + i * 16) = o[cb][i];
+          m_all[cb] = m[cb];
+          l_all[cb] = lsum[cb];
+          continue;
+        }
+        float Mx, e0, e1;
+        fold_factors(m_all[cb], m[cb], Mx, e0, e1);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) *(f32x4 *)(mine + i * 16) = fold_value(*(const f32x4 *)(mine + i * 16), e0, o[cb][i], e1);
+        l_all[cb] = fold_value(l_all[cb], e0, lsum[cb], e1);
+        m_all[cb] = Mx;
+      }
+    };
+    for (int blk = wave; blk < nblk; blk += 4) {
+      asm volatile("" ::: "memory");   // the queries stay in LDS: read anew for every run
+      f32x4 s4[CB][2];
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) {
+        bf16x8 qf[NJ];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) qf[j] = sq[(cb * NJ + j) * 64 + l];
+#pragma unroll
+        for (int T = 0; T < 2; ++T) {
+          s4[cb][T] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) s4[cb][T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[T][j], qf[j], s4[cb][T], 0, 0, 0);
+        }
+      }
+      const bf16_t *nb = run_at(blk + 4 < nblk ? t0 + (blk + 4) * 32 : t0 + p.chunk + wave * 32);   // (of the next chunk)
+      load_k(nb);
+      const int tbase = t0 + blk * 32 + qg * 8;
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) {
+        float s[8], mb = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          float v = s4[cb][e >> 2][e & 3] * scale;
+          v = (tbase + e < ctx[cb]) ? v : -INFINITY;
+          s[e] = v;
+          mb = fmaxf(mb, v);
+        }
+        mb = fmaxf(mb, shfl_xor(mb, 16));
+        mb = fmaxf(mb, shfl_xor(mb, 32));
+        const float m_new = fmaxf(m[cb], mb), m_ref = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f(m[cb] - m_ref);
+        float psum = 0.f;
+        bf16x8 pf;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float pe = __builtin_amdgcn_exp2f(s[e] - m_ref);
+          psum += pe;
+          pf[e] = (__bf16)pe;
+        }
+        lsum[cb] = __builtin_fmaf(lsum[cb], alpha, psum);
+        m[cb] = m_new;
+        if (__builtin_amdgcn_ballot_w64(!(alpha == 1.f))) {   // a maximum has moved (a factor of 1 changes nothing)
+#pragma unroll
+          for (int i = 0; i < NV; ++i) o[cb][i] *= alpha;
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) o[cb][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i], pf, o[cb][i], 0, 0, 0);
+      }
+      load_v(nb);
+      if ((blk & (SUB_RUNS - 1)) + 4 >= SUB_RUNS && blk + 4 < nblk) {   // end of a sub
+        fold_sub();
+        folded = true;
+        reset();
+      }
+    }
+    fold_sub();
+    if (qg == 0) {
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) { sm_m[wave][cb * 16 + col] = m_all[cb]; sm_l[wave][cb * 16 + col] = l_all[cb]; }
+    }
+    __syncthreads();
+    // merge of the four wavefronts and fold of the chunk: the factors of a column once, then its elements; a
+    // column that ends before this chunk keeps what it has (factors 1 and 0)
+    if (threadIdx.x < COLS) {
+      const int cc = threadIdx.x;
+      const bool here = s_ctx[cc] > t0;
+      const float Mc = fmaxf(fmaxf(sm_m[0][cc], sm_m[1][cc]), fmaxf(sm_m[2][cc], sm_m[3][cc]));
+      float Lc = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const float f = here ? __builtin_amdgcn_exp2f(sm_m[w][cc] - Mc) : 0.f;
+        Lc = __builtin_fmaf(sm_l[w][cc], f, Lc);
+        s_f[w][cc] = f;
+      }
+      float M = run_m[cc], e0 = 1.f, e1 = 0.f;
+      if (here) {
+        fold_factors(run_m[cc], Mc, M, e0, e1);
+        run_l[cc] = fold_value(run_l[cc], e0, Lc, e1);
+        run_m[cc] = M;
+      }
+      s_e[0][cc] = e0;
+      s_e[1][cc] = e1;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int at = threadIdx.x + 256 * k, cc = at / (HD / 4), d = at % (HD / 4) * 4;
+      f32x4 Oc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < 4; ++w) Oc = fma4(*(const f32x4 *)&sm_o[w][cc][d], s_f[w][cc], Oc);
+      run_o[k] = fold_value(run_o[k], s_e[0][cc], Oc, s_e[1][cc]);
+    }
+    __syncthreads();   // the next chunk's results go to the same place
+  }
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int at = threadIdx.x + 256 * k, cc = at / (HD / 4), d = at % (HD / 4) * 4;
+    const int in = cc % 16 / G, r = cc / 16 * rpb + in, h = cc % 16 % G;
+    if (in >= rpb || r >= nrows) continue;
+    bf16x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = (__bf16)(run_o[k][e] / run_l[cc]);
+    *(bf16x4 *)(p.out + ((int64_t)(row0 + r) * p.Hq + g * G + h) * HD + d) = o;
+  }
 }
 
 __global__ __launch_bounds__(1024) void attn_worklist_kernel(AttnParams p, int cap) {
@@ -439,6 +665,22 @@ int launch_attention(const AttnParams &p, hipStream_t s, int part) {
     case 128: launch_attention_hd<128>(p, s, part); break;
     case 64: launch_attention_hd<64>(p, s, part); break;
     case 32: launch_attention_hd<32>(p, s, part); break;
+    default: return -1;
+  }
+  return hipGetLastError() == hipSuccess ? 0 : -7;
+}
+
+// Rows of a group of attn_rows_kernel: CB column blocks of 16 / G rows.
+constexpr int ATTN_ROWS_CB = 2;
+int attention_rows_per_group(int Hq, int Hkv) { return ATTN_ROWS_CB * (16 / (Hq / Hkv)); }
+
+int launch_attention_rows(const AttnParams &p, hipStream_t s) {
+  if (p.n_seq <= 0) return 0;
+  const dim3 grid((unsigned)(p.max_items * p.Hkv));
+  switch (p.hd) {
+    case 128: hipLaunchKernelGGL((attn_rows_kernel<128, ATTN_ROWS_CB>), grid, dim3(256), 0, s, p); break;
+    case 64: hipLaunchKernelGGL((attn_rows_kernel<64, ATTN_ROWS_CB>), grid, dim3(256), 0, s, p); break;
+    case 32: hipLaunchKernelGGL((attn_rows_kernel<32, ATTN_ROWS_CB>), grid, dim3(256), 0, s, p); break;
     default: return -1;
   }
   return hipGetLastError() == hipSuccess ? 0 : -7;

@@ -29,7 +29,7 @@ __device__ inline void rope_angle(float *cs, int pos, int i, int hd, float theta
 }
 
 // The beginning of a step or pass, one launch: everything the layers need that depends on the metadata alone.
-// Workgroup 0 applies the step's page-table changes and builds the attention work list; workgroup r + 1 brings
+// Workgroup 0 applies a decode step's page-table changes and builds the attention work list; workgroup r + 1 brings
 // row r: its metadata (read from the host's pinned image in a decode step, where a copy would be a launch of its
 // own ahead of this one), cos/sin of its position, h = E[token], a = rmsnorm(h) * g.
 // As separate launches: metadata copy 4 us, tables 4, work list 13, embedding 13 (7B shape, 256 rows), each with its
@@ -37,6 +37,7 @@ __device__ inline void rope_angle(float *cs, int pos, int i, int hd, float theta
 __global__ __launch_bounds__(1024) void step_begin_kernel(StepBegin q, AttnParams p, int cap) {
   if (blockIdx.x == 0) {
     const int n_upd = q.updates ? q.updates[0] : 0;
+    if (!p.work) return;   // a pass
     for (int i = threadIdx.x; i < n_upd; i += 1024) q.page_table[q.updates[2 + 2 * i]] = q.updates[3 + 2 * i];
     __syncthreads();   // the list is built from the table
     const int b = threadIdx.x;

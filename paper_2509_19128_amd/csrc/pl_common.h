@@ -76,7 +76,8 @@ struct AttnParams {
                             // null: none (row_slot null; max_items = n_seq * max_chunks)
   int32_t *tickets;         // [n_seq, Hkv], zero between launches (the work-list kernel clears them); null without a list
   int32_t *first_item;      // [n_seq] list index of a row's first item (item_tokens < chunk)
-  int32_t max_items;        // upper bound on the list length (sizes the grid)
+  const int32_t *groups;    // rows of a pass: {count, -, (first row, rows) ...}, each group consecutive positions of one slot
+  int32_t max_items;        // upper bound on the list length, or on the number of groups (sizes the grid)
   bf16_t *out;              // [n_seq, Hq, hd]
   float *part_o;            // [n_seq, Hkv, max_chunks, G, hd]; item_tokens < chunk: [item, Hkv, 4, G, hd]
   float *part_ml;           // [n_seq, Hkv, max_chunks, ATTN_ML]; item_tokens < chunk: [item, Hkv, 4, 16, 2]
@@ -84,6 +85,8 @@ struct AttnParams {
   int32_t item_tokens;      // tokens of a work item: chunk, or ATTN_SUB where attention_split says so
 };
 int launch_attention(const AttnParams &p, hipStream_t s, int part = 0);
+int launch_attention_rows(const AttnParams &p, hipStream_t s);
+int attention_rows_per_group(int Hq, int Hkv);
 int64_t attention_worklist_ints(int64_t max_items);
 bool attention_split(int chunk, int64_t total_tokens, int64_t longest_item, int64_t n_subs, int Hkv);
 int launch_attention_worklist(const AttnParams &p, int cap, hipStream_t s);

@@ -119,8 +119,9 @@ struct pl_engine {
     int32_t *m_input(bool dev) { return m_pos(dev) + rows_cap; }
     int32_t *m_forced(bool dev) { return m_input(dev) + rows_cap; }
     float *m_inv_t(bool dev) { return (float *)(m_forced(dev) + rows_cap); }
-    // page-table changes of a decode step (host image only): count, unused, then (element, page id) pairs
-    int32_t *m_updates() { return (int32_t *)(m_inv_t(false) + rows_cap); }
+    // behind the rows, {count, -, pairs}: a decode step's page-table changes (element, page id; fetched from the host
+    // image), a pass's groups of rows (first row, rows)
+    int32_t *m_pairs(bool dev) { return (int32_t *)(m_inv_t(dev) + rows_cap); }
     int64_t meta_bytes() const { return (int64_t)rows_cap * (4 * 5 + 8); }
     int64_t image_bytes() const { return meta_bytes() + ((int64_t)rows_cap * 2 + 2) * 4; }
     pl::StepMeta meta(bool dev) {
@@ -253,13 +254,13 @@ int dev_alloc(T **p, int64_t n_elems) {
   return PL_OK;
 }
 
-int alloc_work(pl_engine *e, pl_engine::Work &w, int64_t R, int64_t parts_elems, bool pinned_image) {
+int alloc_work(pl_engine *e, pl_engine::Work &w, int64_t R, int64_t parts_elems, bool decode) {
   const pl_model_cfg &c = e->cfg;
   const int64_t d = c.d_model, qd = (int64_t)c.n_q_heads * c.head_dim;
   const int64_t wide = e->esz / 2;   // the activation buffers are declared bf16; the fp32 build needs twice the bytes
   int rc;
   w.rows_cap = (int)R;
-  if ((rc = dev_alloc(&w.meta_d, w.meta_bytes()))) return rc;
+  if ((rc = dev_alloc(&w.meta_d, w.image_bytes()))) return rc;
   if ((rc = dev_alloc(&w.h, R * d))) return rc;
   if ((rc = dev_alloc(&w.a, R * d * wide))) return rc;
   if ((rc = dev_alloc(&w.parts, parts_elems))) return rc;
@@ -269,17 +270,21 @@ int alloc_work(pl_engine *e, pl_engine::Work &w, int64_t R, int64_t parts_elems,
   if ((rc = dev_alloc(&w.cs, R * c.head_dim))) return rc;
   if ((rc = dev_alloc(&w.ctx_len, R))) return rc;
   if ((rc = dev_alloc(&w.pt, (int64_t)c.max_batch * e->pages_per_seq))) return rc;
-  const int64_t split = e->attn_chunk > pl::ATTN_SUB ? pl::ATTN_SPLIT_PARTS : 0;   // (sub, kv head) pairs
-  const int64_t np = std::max<int64_t>(R * c.n_kv_heads * e->attn_max_chunks, 4 * split);
-  const int64_t po = np * e->G * c.head_dim;   // a multiple of a cache line (32 floats)
-  if ((rc = dev_alloc(&w.attn_po, po + np * pl::ATTN_ML))) return rc;
-  w.attn_pml = w.attn_po + po;
-  w.items_cap = std::max<int64_t>(R * e->attn_max_chunks, split);
-  const int64_t work = pl::attention_worklist_ints(w.items_cap);
-  if ((rc = dev_alloc(&w.attn_work, work + R * c.n_kv_heads + R))) return rc;
-  w.attn_tickets = w.attn_work + work;
-  w.attn_first = w.attn_tickets + R * c.n_kv_heads;
-  if (pinned_image) HIP_TRY(hipHostMalloc((void **)&w.meta_h, (size_t)w.image_bytes(), hipHostMallocDefault));
+  if (decode) {   // a pass's attention needs no list and no partial results
+    const int64_t split = e->attn_chunk > pl::ATTN_SUB ? pl::ATTN_SPLIT_PARTS : 0;   // (sub, kv head) pairs
+    const int64_t np = std::max<int64_t>(R * c.n_kv_heads * e->attn_max_chunks, 4 * split);
+    const int64_t po = np * e->G * c.head_dim;   // a multiple of a cache line (32 floats)
+    if ((rc = dev_alloc(&w.attn_po, po + np * pl::ATTN_ML))) return rc;
+    w.attn_pml = w.attn_po + po;
+    w.items_cap = std::max<int64_t>(R * e->attn_max_chunks, split);
+    const int64_t work = pl::attention_worklist_ints(w.items_cap);
+    if ((rc = dev_alloc(&w.attn_work, work + R * c.n_kv_heads + R))) return rc;
+    w.attn_tickets = w.attn_work + work;
+    w.attn_first = w.attn_tickets + R * c.n_kv_heads;
+  } else {
+    w.items_cap = R;
+  }
+  if (decode) HIP_TRY(hipHostMalloc((void **)&w.meta_h, (size_t)w.image_bytes(), hipHostMallocDefault));
   return PL_OK;
 }
 
@@ -347,7 +352,7 @@ int alloc_device(pl_engine *e) {
   if (rc) return rc;
   e->ring.resize(PASS_RING);
   for (auto &im : e->ring) {
-    HIP_TRY(hipHostMalloc((void **)&im.meta_h, (size_t)e->wk[1].meta_bytes(), hipHostMallocDefault));
+    HIP_TRY(hipHostMalloc((void **)&im.meta_h, (size_t)e->wk[1].image_bytes(), hipHostMallocDefault));
     HIP_TRY(hipEventCreate(&im.ev_begin));
     HIP_TRY(hipEventCreate(&im.ev_end));
   }
@@ -475,9 +480,10 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   ap.page_tokens = e->page_tokens; ap.pages_per_seq = e->pages_per_seq; ap.chunk = e->attn_chunk;
   ap.max_chunks = e->attn_max_chunks; ap.item_tokens = w.attn_split ? pl::ATTN_SUB : e->attn_chunk;
   ap.work = w.attn_work; ap.tickets = w.attn_tickets; ap.first_item = w.attn_first; ap.max_items = w.attn_items;
+  if (prefill) ap.groups = w.m_pairs(true);
   pl::StepBegin sb{};
   sb.src = w.meta(prefill);   // a pass's metadata is on the device already, a decode step's is fetched from the host's image
-  if (!prefill) { sb.dst = w.meta(true); sb.updates = w.m_updates(); }
+  if (!prefill) { sb.dst = w.meta(true); sb.updates = w.m_pairs(false); }
   sb.page_table = w.pt; sb.embed = embed; sb.g = c.n_layers ? layer_weights(e, 0).g1 : gf;
   sb.h = w.h; sb.cs = w.cs; sb.a = w.a; sb.ctx_len = w.ctx_len;
   sb.d = d; sb.vocab = c.vocab; sb.eps = c.rms_eps; sb.theta = c.rope_theta;
@@ -492,7 +498,9 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
                                  c.n_q_heads, c.n_kv_heads, c.head_dim, e->page_tokens, e->pages_per_seq, s);
     ap.q = w.q_rot; ap.kv = kv_layer;
     if (prefill && l + 1 == c.n_layers) break;
-    if (timed && e->profile) {   // the timers bracket the decode kernel alone; the merge kernel counts as "other"
+    if (prefill) {
+      rc |= pl::launch_attention_rows(ap, s);
+    } else if (timed && e->profile) {   // the timers bracket the decode kernel alone; the merge kernel counts as "other"
       mark(e, CAT_OTHER, true);
       rc |= pl::launch_attention(ap, s, 1);
       mark(e, CAT_ATTN, true);
@@ -691,7 +699,9 @@ int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::ve
       }
       w.meta_h = im.meta_h;
       int items = 0;
+      const int per_group = pl::attention_rows_per_group(c.n_q_heads, c.n_kv_heads);
       int32_t *row_slot = w.m_row_slot(false), *pos = w.m_pos(false), *inp = w.m_input(false), *frc = w.m_forced(false);
+      int32_t *groups = w.m_pairs(false);
       float *inv_t = w.m_inv_t(false);
       uint64_t *sid = w.m_seq_id(false);
       for (int r = 0; r < n; ++r) {
@@ -702,8 +712,14 @@ int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::ve
         frc[r] = -1;
         inv_t[r] = q.inv_t;
         sid[r] = q.seq_id;
-        items += (pos[r] + 1 + e->attn_chunk - 1) / e->attn_chunk;
+        // groups of rows that one attention workgroup takes: consecutive positions of one slot
+        if (r == 0 || row_slot[r] != row_slot[r - 1] || pos[r] != pos[r - 1] + 1 || groups[1 + 2 * items] == per_group) {
+          groups[2 + 2 * items] = r;
+          groups[3 + 2 * items++] = 0;
+        }
+        ++groups[1 + 2 * items];
       }
+      groups[0] = items;
       w.attn_items = items;
       hipStream_t s = w.stream;
       // The page table goes up on this stream into this set's own device copy (no device buffer is ever
@@ -711,7 +727,7 @@ int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::ve
       // The dirty flag stays: the decode stream sends the table to its own copy.
       if (r0 == 0)
         HIP_TRY(hipMemcpyAsync(w.pt, e->pt_h, (size_t)c.max_batch * e->pages_per_seq * 4, hipMemcpyHostToDevice, s));
-      HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)w.meta_bytes(), hipMemcpyHostToDevice, s));
+      HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)w.image_bytes(), hipMemcpyHostToDevice, s));
       HIP_TRY(hipEventRecord(im.ev_begin, s));
       int rc = run_step(e, w, n, true);
       if (rc) return rc;
@@ -1156,7 +1172,7 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
   int r = 0;
   double kv_tokens = 0;
   int items = 0, subs = 0, longest = 0, n_upd = 0;
-  int32_t *upd = w.m_updates();
+  int32_t *upd = w.m_pairs(false);
   for (int s = 0; s < c.max_batch; ++s) {
     Seq &q = e->seqs[s];
     if (!q.active || q.reading) continue;

@@ -412,13 +412,15 @@ def test_batched_prefill_leaves_the_cache_of_reading_the_prompt_token_by_token(w
     eng_b.close(); eng_s.close()
 
 
-@pytest.mark.parametrize("n_prompt", [258, 1026, 1300])
-def test_prompt_passes_of_many_rows_leave_the_cache_of_reading_token_by_token(weights, n_prompt):
+@pytest.mark.parametrize("n_prompt,max_batch", [(258, 4), (1026, 4), (1300, 4), (2120, 512)])
+def test_prompt_passes_of_many_rows_leave_the_cache_of_reading_token_by_token(weights, n_prompt, max_batch):
     """Passes of more than 256 rows, one full pass of 1024, a full one and a remainder: bit-identical caches and
-    logits to the engine's own token-by-token path (a row's result depends on its own sequence only)."""
+    logits to the engine's own token-by-token path (a row's result depends on its own sequence only).  The engine of
+    512 slots has attention chunks of 2048 tokens (four subs each), the others of 128."""
     master, _ = weights
     prompt = synth.random_prompts(np.random.default_rng(n_prompt), 1, n_prompt, M.vocab)[0]
-    engines = [_engine(max_context=1408, kv_pool_tokens=2 * 1408) for _ in range(2)]
+    context = 1408 if max_batch == 4 else 4096
+    engines = [_engine(max_batch, max_context=context, kv_pool_tokens=2 * context) for _ in range(2)]
     for e in engines:
         e.load_weights(e.pack_weights(master, synth.f32_to_bf16_bits))
         assert e.add_sequence(7, prompt, 6) == 0
@@ -430,7 +432,7 @@ def test_prompt_passes_of_many_rows_leave_the_cache_of_reading_token_by_token(we
         for part in range(2):
             assert np.array_equal(caches[0][l][part], caches[1][l][part]), (l, part)
     for step in range(3):
-        outs = [e.decode_step(np.full(4, 3 + step, np.int32)) for e in engines]
+        outs = [e.decode_step(np.full(max_batch, 3 + step, np.int32)) for e in engines]
         logits = [e.debug_get_logits(1) for e in engines]
         assert np.array_equal(logits[0], logits[1]) and outs[0]["logprob"][0] == outs[1]["logprob"][0]
     for e in engines:
