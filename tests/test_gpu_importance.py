@@ -55,6 +55,37 @@ def test_weights_and_ess_match_the_oracle(lens, spread, c):
     assert np.isclose(tot[0], w_ref.sum(), rtol=1e-11) and np.isclose(tot[1], (w_ref * w_ref).sum(), rtol=1e-11)
 
 
+@pytest.mark.parametrize("shift_pi,shift_mu,shift_w", [(0, 0, 0), (1, 1, 1), (3, 3, 3), (2, 2, 1), (0, 1, 0)])
+def test_weights_at_every_alignment_of_the_arrays_and_of_the_sequences(shift_pi, shift_mu, shift_w):
+    """Arrays that start on the same and on different positions of a 16-byte line, sequences that begin and end
+    anywhere in one, lengths around one round of the workgroup; masked (-inf), infinite and NaN differences as
+    fmin(c, exp(.)) has them."""
+    rng = np.random.default_rng(5)
+    lens = [1, 2, 3, 4, 5, 7, 0, 4095, 4096, 4097, 8191, 4 * 4096 + 3, 6]
+    pi, mu, off = _case(rng, lens, 1.5)
+    pi[20:26] = [-np.inf, np.inf, np.nan, 800.0, -800.0, 3.0]
+    mu[20:26] = [0.0, 0.0, 0.0, 0.0, 0.0, np.nan]
+
+    def shifted(x, k):
+        t = torch.zeros(len(x) + 4, device="cuda", dtype=torch.float32)
+        t[k:k + len(x)] = torch.from_numpy(x)
+        return t
+    a, b, w = shifted(pi, shift_pi), shifted(mu, shift_mu), shifted(np.full(len(pi), -7, np.float32), shift_w)
+    o = torch.from_numpy(off.astype(np.int64)).cuda()
+    sums, ess, tot = (torch.empty(k, device="cuda", dtype=torch.float64) for k in (2 * len(lens), len(lens), 3))
+    pl.pl_is_ess(a[shift_pi:].data_ptr(), b[shift_mu:].data_ptr(), o.data_ptr(), len(lens), 5.0, w[shift_w:].data_ptr(), sums.data_ptr(),
+                 ess.data_ptr(), tot.data_ptr(), 0)
+    torch.cuda.synchronize()
+    with np.errstate(over="ignore", invalid="ignore"):
+        ref = np.fmin(5.0, np.exp(pi.astype(np.float64) - mu.astype(np.float64)))
+    got = w.cpu().numpy()
+    assert np.allclose(got[shift_w:shift_w + len(pi)], ref, rtol=1e-6, atol=0)
+    assert (got[:shift_w] == 0).all() and (got[shift_w + len(pi):] == 0).all()
+    for s in range(len(lens)):
+        seg = ref[off[s]:off[s + 1]]
+        assert np.isclose(sums[2 * s].item(), seg.sum(), rtol=1e-11) and np.isclose(sums[2 * s + 1].item(), (seg * seg).sum(), rtol=1e-11)
+
+
 def test_on_policy_batch_is_exactly_one_and_weights_are_optional():
     rng = np.random.default_rng(8)
     lp = (-rng.random(5000) * 9).astype(np.float32)
