@@ -497,6 +497,23 @@ __global__ __launch_bounds__(256) void gemm_gu_fused_kernel(const bf16_t *__rest
     gemm_tile<WM, WN, AT, BT, 0>(xs, X, W, ws, M, N, K, rem_ksteps, n_main + ctileB * BN, rtileB * BM, split, N, N - n_main, n_main);
 }
 
+// The same product for calls of at most one row tile (a decayed batch in an engine sized for more rows): workgroups
+// below n_tiles take the main tiles, the others the K slices of the remainder, in one launch.  The two launches
+// in a row each left part of the chip idle: 7B shape, 19 rows, 43 + 11 us and a gap; joined 50.
+template <int WM, int WN, int AT, int BT>
+__global__ __launch_bounds__(256) void gemm_gu_joint_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
+                                                            bf16_t *__restrict__ mid, float *__restrict__ ws, int M, int N,
+                                                            int K, int n_main, int n_tiles, int rem_splits, int rem_ksteps) {
+  constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
+  __shared__ __attribute__((aligned(16))) bf16_t xs[2][BM * LDS_ROW];
+  const int item = (int)blockIdx.x - n_tiles;
+  if (item < 0)   // uniform for the workgroup
+    gemm_tile<WM, WN, AT, BT, 1>(xs, X, W, mid, M, N, K, K / BK, (int)blockIdx.x * BN, 0, 0, n_main, 0, 0);
+  else
+    gemm_tile<WM, WN, AT, BT, 0>(xs, X, W, ws, M, N, K, rem_ksteps, n_main + item / rem_splits * BN, 0, item % rem_splits, N,
+                                 N - n_main, n_main);
+}
+
 // SwiGLU over K-split partial sums: parts [splits][M][ld] holds columns [col0, col0 + ld) of the
 // interleaved gate/up product (blocks of 64 columns: 32 gate, then the 32 matching up columns);
 // mid[m][(col0 + c) / 2 ...] = silu(sum_s gate) * (sum_s up), slices added in order.
@@ -732,6 +749,20 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
     const int rem_ksteps = 4 * ((K / (4 * BK) + ks.rem_splits - 1) / ks.rem_splits);
     hipLaunchKernelGGL((gemm_gu_fused_kernel<1, 4, 4, 2>), dim3(wgs), dim3(256), 0, s, x, w, (bf16_t *)y, ws, M, N, K, n_main,
                        ks.rem_splits, rem_ksteps);
+    if (hipGetLastError() != hipSuccess) return -7;
+    return swiglu_reduce(ws, ks.rem_splits, M, N - n_main, n_main, (bf16_t *)y, N / 2, s);
+  }
+  if (mode == 1 && M <= 128 && n_main < N && ks.rem_splits > 1 && ks.splits == 1 && ws) {
+    if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
+    const int bn = cfg == GEMM_64x128 ? 128 : 256, n_tiles = (n_main + bn - 1) / bn;
+    const dim3 grid(n_tiles + (N - n_main + bn - 1) / bn * ks.rem_splits);
+    const int rem_ksteps = 4 * ((K / (4 * BK) + ks.rem_splits - 1) / ks.rem_splits);
+    if (cfg == GEMM_32x256)
+      hipLaunchKernelGGL((gemm_gu_joint_kernel<1, 4, 1, 2>), grid, dim3(256), 0, s, x, w, (bf16_t *)y, ws, M, N, K, n_main, n_tiles, ks.rem_splits, rem_ksteps);
+    else if (cfg == GEMM_64x128)
+      hipLaunchKernelGGL((gemm_gu_joint_kernel<2, 2, 1, 2>), grid, dim3(256), 0, s, x, w, (bf16_t *)y, ws, M, N, K, n_main, n_tiles, ks.rem_splits, rem_ksteps);
+    else
+      hipLaunchKernelGGL((gemm_gu_joint_kernel<1, 4, 4, 2>), grid, dim3(256), 0, s, x, w, (bf16_t *)y, ws, M, N, K, n_main, n_tiles, ks.rem_splits, rem_ksteps);
     if (hipGetLastError() != hipSuccess) return -7;
     return swiglu_reduce(ws, ks.rem_splits, M, N - n_main, n_main, (bf16_t *)y, N / 2, s);
   }
