@@ -93,7 +93,11 @@ __device__ inline void merge_chunks(const AttnParams &p, int b, int g, int nchun
   }
 }
 
-template <int HD, int NS>
+// ROTATE: q, k and v of the step come as the QKV product's slices of partial sums; the workgroup adds them up and
+// rotates its group's heads, and the item that holds the step's own position also appends k and v to the cache
+// and patches them into the run it has loaded.  Saves a launch per layer, but the rotation is a dependent round
+// trip ahead of the first scores: worth it while all workgroups run at once (attention_rotates).
+template <int HD, int NS, bool ROTATE>
 __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
   constexpr int NJ = HD / 32;   // QK MFMAs per 16-token tile
   constexpr int NV = HD / 16;   // PV MFMAs per 32-token run
@@ -135,17 +139,44 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
   const float scale = 1.4426950408889634f / sqrtf((float)HD);   // log2(e) / sqrt(hd)
   const int64_t page_elems = (int64_t)2 * p.page_tokens * HD;   // K block + V block of one kv head
 
+  __shared__ __attribute__((aligned(16))) bf16_t s_qkv[ROTATE ? 18 * HD : 8];   // rotated q of the group's heads (16), k, v
+  const bool appends = ROTATE && t1 == ctx;   // this item holds the step's own position, ctx - 1
+  // ROTATE: one thread per four rotated pairs of a head of the group, of k or of v
+  constexpr int QUADS = HD / 8;
+  const int n_rot = ROTATE ? (G + (appends ? 2 : 0)) * QUADS : 0, hh = threadIdx.x / QUADS, pair = threadIdx.x % QUADS * 4;
+  const bool rotates = (int)threadIdx.x < n_rot;
+  f32x4 f1[8], f2[8], rc = {}, rs = {};
+  int own_page = 0;
+  if (ROTATE && rotates) {
+    // everything the rotation reads is requested before the first K/V loads: loads return in order
+    const int width = (p.Hq + 2 * p.Hkv) * HD;
+    const float *src = p.qkv + (int64_t)b * width + (hh < G ? g * G + hh : hh == G ? p.Hq + g : p.Hq + p.Hkv + g) * HD + pair;
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (u < p.splits) {
+        f1[u] = *(const f32x4 *)(src + (int64_t)u * p.n_seq * width);
+        f2[u] = *(const f32x4 *)(src + (int64_t)u * p.n_seq * width + HD / 2);
+      }
+    rc = *(const f32x4 *)(p.cs + (int64_t)b * HD + pair);
+    rs = *(const f32x4 *)(p.cs + (int64_t)b * HD + HD / 2 + pair);
+    if (appends) own_page = pt[(ctx - 1) / p.page_tokens];
+  }
+  if constexpr (ROTATE) __builtin_amdgcn_sched_barrier(0);
+
   // Query operand: column = head of the group (zero for the padding columns), k = head-dim slice.
   bf16x8 qf[NJ];
+  auto read_q = [&](const bf16_t *q) {
 #pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    if (head < G) {
-      qf[j] = *(const bf16x8 *)(p.q + ((int64_t)b * p.Hq + g * G + head) * HD + j * 32 + qg * 8);
-    } else {
+    for (int j = 0; j < NJ; ++j) {
+      if (head < G) {
+        qf[j] = *(const bf16x8 *)(q + head * HD + j * 32 + qg * 8);
+      } else {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) qf[j][e] = (__bf16)0.0f;
+        for (int e = 0; e < 8; ++e) qf[j][e] = (__bf16)0.0f;
+      }
     }
-  }
+  };
+  if constexpr (!ROTATE) read_q(p.q + ((int64_t)b * p.Hq + g * G) * HD);
 
   f32x4 o[NV];
 #pragma unroll
@@ -183,16 +214,80 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) vf[st][i] = __builtin_nontemporal_load((const bf16x8 *)(vb + i * 512));
   };
+  // The first loads carry no condition (a wavefront without a run loads the last one), so that the wait counts that
+  // follow stay exact.  ROTATE: stage 0 is requested right behind the rotation's input, the others when that has
+  // arrived and freed its registers.
   int page_next[NS];   // page of the run stage st takes after the one it holds
-#pragma unroll
-  for (int st = 0; st < NS; ++st) {
-    // without a condition (a wavefront without a run loads the last one), so that the wait counts that follow stay exact
+  auto load_first = [&](int st) {
     const int b0 = wave + 4 * st, bl = min(b0, nblk - 1);
     const bf16_t *kb = run_base(bl, page_of(bl));
     load_k(st, kb);
     load_v(st, kb);
     page_next[st] = b0 + 4 * NS < nblk ? page_of(b0 + 4 * NS) : 0;
+  };
+  load_first(0);
+  f32x4 x1 = {0.f, 0.f, 0.f, 0.f}, x2 = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (ROTATE) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (u < p.splits) { x1 += f1[u]; x2 += f2[u]; }   // slices are added in order
+    __builtin_amdgcn_sched_barrier(0);
   }
+#pragma unroll
+  for (int st = 1; st < NS; ++st) load_first(st);
+  if constexpr (ROTATE) {
+    __builtin_amdgcn_sched_barrier(0);
+    if (rotates) {
+      bf16x4 lo, hi;   // elements pair .. pair + 3 and half + pair .. half + pair + 3 of the head
+      if (hh <= G) {
+        rotate_pairs(x1, x2, rc, rs, lo, hi);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { lo[e] = (__bf16)x1[e]; hi[e] = (__bf16)x2[e]; }
+      }
+      bf16_t *to = s_qkv + (hh < G ? hh : hh - G + 16) * HD + pair;
+      *(bf16x4 *)to = lo;
+      *(bf16x4 *)(to + HD / 2) = hi;
+      if (hh >= G) {   // the step's own k or v goes to the cache
+        const int tok = (ctx - 1) % p.page_tokens;
+        bf16_t *kb = p.kv + ((int64_t)own_page * p.Hkv + g) * page_elems;
+        if (hh == G) {
+          *(bf16x4 *)(kb + k_elem_offset(tok, pair, HD)) = lo;
+          *(bf16x4 *)(kb + k_elem_offset(tok, HD / 2 + pair, HD)) = hi;
+        } else {
+          bf16_t *vb = kb + (int64_t)p.page_tokens * HD;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            vb[v_elem_offset(tok, pair + e, HD)] = lo[e];
+            vb[v_elem_offset(tok, HD / 2 + pair + e, HD)] = hi[e];
+          }
+        }
+      }
+    }
+    // Only LDS passes between the wavefronts here: a full barrier would also wait for every K/V load in flight.
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    read_q(s_qkv);
+  }
+  // The run that holds the step's own position was loaded before (or while) the position was written: its operands
+  // are patched from LDS.
+  const int blk_own = appends ? nblk - 1 : -1;
+  auto patch_own = [&](int st) {
+    const int u = (ctx - 1) & 31, T = (u >> 2) & 1, R = ((u >> 3) << 2) | (u & 3);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+      if (head == R) {
+        const bf16x8 kn = *(const bf16x8 *)(s_qkv + 16 * HD + j * 32 + qg * 8);
+        if (T == 0) kf[st][0][j] = kn; else kf[st][1][j] = kn;
+      }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const bf16_t vn = s_qkv[17 * HD + i * 16 + head];
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (qg == (u >> 3) && e == (u & 7)) vf[st][i][e] = vn;
+    }
+  };
   // Results of this wavefront's finished subs, folded in order; o is kept in the wavefront's own part of sm_o.
   __shared__ float sm_o[4][16][HD];
   __shared__ float sm_m[4][16], sm_l[4][16];
@@ -224,6 +319,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
     for (int st = 0; st < NS; ++st) {
       const int blk = base + 4 * st;
       if (blk < nblk) {
+        if (ROTATE && blk == blk_own) patch_own(st);
         // scores of the 32 tokens of this run: two 16-token tiles
         f32x4 s4[2];
 #pragma unroll
@@ -637,6 +733,14 @@ bool attention_split(int chunk, int64_t total_tokens, int64_t longest_item, int6
   return chunk > ATTN_SUB && longest_item >= 3 * ATTN_SUB && n_subs * Hkv <= ATTN_SPLIT_PARTS && longest_item * 128 > total_tokens * Hkv;
 }
 
+// Whether a step's attention rotates and appends by itself: while its workgroups run all at once (two per compute
+// unit, three at half the head dimension) it saves the launch (1.5B shape, 64 rows: 26.5 + 5.1 us and a gap -> 27.6; 7B, 19
+// rows: 34.5 + 5.0 -> 36.2), in later rounds every workgroup pays the round trip (7B, 256 rows: 265 + 8.9 -> 289).
+// Slices and rotated quads have to fit the registers and threads of one workgroup.
+bool attention_rotates(int items, int Hq, int Hkv, int hd, int splits) {
+  return items * Hkv <= 768 && splits <= ATTN_ROTATE_SLICES && (Hq / Hkv + 2) * (hd / 8) <= 256;
+}
+
 // ints of the work buffer (which must be 32-byte aligned): a header of 8, one 8-int record per item
 int64_t attention_worklist_ints(int64_t max_items) { return 8 + 8 * max_items; }
 
@@ -650,7 +754,10 @@ template <int HD>
 static void launch_attention_hd(const AttnParams &p, hipStream_t s, int part) {
   if (part != 2) {
     const dim3 grid((unsigned)(p.max_items * p.Hkv));
-    hipLaunchKernelGGL((attn_decode_kernel<HD, PL_ATTN_NS>), grid, dim3(256), 0, s, p);
+    if (p.q)
+      hipLaunchKernelGGL((attn_decode_kernel<HD, PL_ATTN_NS, false>), grid, dim3(256), 0, s, p);
+    else
+      hipLaunchKernelGGL((attn_decode_kernel<HD, PL_ATTN_NS, true>), grid, dim3(256), 0, s, p);
   }
   // items are subs, or there is no list (whose kernel clears the tickets) and a row can span several chunks
   if (part != 1 && (p.item_tokens < p.chunk || (!p.tickets && p.max_chunks > 1)))

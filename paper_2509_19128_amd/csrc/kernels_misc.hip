@@ -168,11 +168,7 @@ __global__ __launch_bounds__(256) void rope_append_kernel(const float *qkv, int 
   bf16x4 lo, hi;   // elements i .. i + 3 and half + i .. half + i + 3 of the head
   if (hh < Hq + Hkv) {
     const f32x4 c = *(const f32x4 *)(cs + (int64_t)row * hd + i), sn = *(const f32x4 *)(cs + (int64_t)row * hd + half + i);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      lo[e] = (__bf16)(x1[e] * c[e] - x2[e] * sn[e]);
-      hi[e] = (__bf16)(x2[e] * c[e] + x1[e] * sn[e]);
-    }
+    rotate_pairs(x1, x2, c, sn, lo, hi);
   } else {
 #pragma unroll
     for (int e = 0; e < 4; ++e) { lo[e] = (__bf16)x1[e]; hi[e] = (__bf16)x2[e]; }

@@ -66,9 +66,23 @@ __host__ __device__ inline int64_t v_elem_offset(int t, int d, int hd) {
 constexpr int ATTN_SUB = 512;            // tokens of a sub of an attention chunk (chunks are powers of two)
 constexpr int ATTN_ML = 32;              // floats of the soft-max statistics of one part: (m, l) of up to 16 heads, one cache line
 constexpr int ATTN_SPLIT_PARTS = 2048;   // most (sub, kv head) pairs of a launch whose items are subs
+// Four rotated pairs (elements i .. i + 3 of the first half with the same of the second), rounded the same way by
+// every kernel that rotates.
+__device__ inline void rotate_pairs(f32x4 x1, f32x4 x2, f32x4 c, f32x4 s, bf16x4 &lo, bf16x4 &hi) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    lo[e] = (__bf16)__builtin_fmaf(x1[e], c[e], -__fmul_rn(x2[e], s[e]));
+    hi[e] = (__bf16)__builtin_fmaf(x2[e], c[e], __fmul_rn(x1[e], s[e]));
+  }
+}
+
+constexpr int ATTN_ROTATE_SLICES = 8;    // most QKV slices the attention kernel adds up itself
 struct AttnParams {
-  const bf16_t *q;          // [n_seq, Hq, hd]
-  const bf16_t *kv;         // page pool of one layer
+  const bf16_t *q;          // [n_seq, Hq, hd], or null: the kernel rotates the QKV product's slices and appends k and v itself
+  const float *qkv;         // [splits, n_seq, (Hq + 2 Hkv) hd] (q null)
+  const float *cs;          // [n_seq, hd] cos | sin of the row's position (q null)
+  int32_t splits;
+  bf16_t *kv;               // page pool of one layer (written only with q null)
   const int32_t *page_table;// [n_slots, pages_per_seq], row = slot_of_row[row] (or row if null)
   const int32_t *ctx_len;   // [n_seq]
   const int32_t *row_slot;  // [n_seq] or null
@@ -85,6 +99,7 @@ struct AttnParams {
   int32_t item_tokens;      // tokens of a work item: chunk, or ATTN_SUB where attention_split says so
 };
 int launch_attention(const AttnParams &p, hipStream_t s, int part = 0);
+bool attention_rotates(int items, int Hq, int Hkv, int hd, int splits);
 int launch_attention_rows(const AttnParams &p, hipStream_t s);
 int attention_rows_per_group(int Hq, int Hkv);
 int64_t attention_worklist_ints(int64_t max_items);

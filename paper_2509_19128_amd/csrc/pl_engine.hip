@@ -481,6 +481,8 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   ap.max_chunks = e->attn_max_chunks; ap.item_tokens = w.attn_split ? pl::ATTN_SUB : e->attn_chunk;
   ap.work = w.attn_work; ap.tickets = w.attn_tickets; ap.first_item = w.attn_first; ap.max_items = w.attn_items;
   if (prefill) ap.groups = w.m_pairs(true);
+  // (the rows of a pass attend to one another: all their keys and values are appended first)
+  const bool rotates = !prefill && pl::attention_rotates(w.attn_items, c.n_q_heads, c.n_kv_heads, c.head_dim, e->ks_qkv.splits);
   pl::StepBegin sb{};
   sb.src = w.meta(prefill);   // a pass's metadata is on the device already, a decode step's is fetched from the host's image
   if (!prefill) { sb.dst = w.meta(true); sb.updates = w.m_pairs(false); }
@@ -494,9 +496,14 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
     if (timed) mark(e, CAT_OTHER);
     rc |= gemm(w.a, lw.w_qkv, w.parts, nullptr, wq, d, 0, e->ks_qkv);
     if (timed) mark(e, CAT_GEMM);
-    rc |= pl::launch_rope_append(w.parts, slices(e->ks_qkv), w.cs, w.m_pos(true), w.m_row_slot(true), w.pt, w.q_rot, kv_layer, n,
-                                 c.n_q_heads, c.n_kv_heads, c.head_dim, e->page_tokens, e->pages_per_seq, s);
-    ap.q = w.q_rot; ap.kv = kv_layer;
+    ap.kv = kv_layer;
+    if (rotates) {
+      ap.qkv = w.parts; ap.cs = w.cs; ap.splits = e->ks_qkv.splits;
+    } else {
+      rc |= pl::launch_rope_append(w.parts, slices(e->ks_qkv), w.cs, w.m_pos(true), w.m_row_slot(true), w.pt, w.q_rot, kv_layer, n,
+                                   c.n_q_heads, c.n_kv_heads, c.head_dim, e->page_tokens, e->pages_per_seq, s);
+      ap.q = w.q_rot;
+    }
     if (prefill && l + 1 == c.n_layers) break;
     if (prefill) {
       rc |= pl::launch_attention_rows(ap, s);
@@ -1459,7 +1466,7 @@ int pl_attention_decode(const void *q, const void *kv_pages, const int32_t *page
   if (page_tokens < 32 || page_tokens % 32 || pages_per_seq < 1 || max_ctx < 1 || max_ctx > (int64_t)pages_per_seq * page_tokens)
     return fail(PL_E_INVAL, "bad page geometry");
   pl::AttnParams p{};
-  p.q = (const bf16_t *)q; p.kv = (const bf16_t *)kv_pages; p.page_table = page_table; p.ctx_len = ctx_len;
+  p.q = (const bf16_t *)q; p.kv = (bf16_t *)kv_pages; p.page_table = page_table; p.ctx_len = ctx_len;   // (with q the pages are only read)
   p.row_slot = nullptr; p.out = (bf16_t *)out;
   p.n_seq = n_seq; p.Hq = n_q_heads; p.Hkv = n_kv_heads; p.hd = hd; p.page_tokens = page_tokens;
   p.pages_per_seq = pages_per_seq;
