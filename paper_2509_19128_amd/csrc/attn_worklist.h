@@ -82,7 +82,7 @@ __device__ inline void build_worklist(int ctx, int slot, const int32_t *page_tab
     }
     put(total + rank, b, n - 1, ctx, slot);
   }
-  for (int i = b; i < n_seq * Hkv; i += 1024) tickets[i] = 0;
+  for (int i = b; tickets && i < n_seq * Hkv; i += 1024) tickets[i] = 0;
   for (int i = total + n_last + b; i < cap; i += 1024) ((int4 *)(work + 8 + 8 * (int64_t)i))[0] = make_int4(0, 0, 0, 0);
 }
 

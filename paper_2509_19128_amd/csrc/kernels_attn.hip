@@ -214,15 +214,17 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) vf[st][i] = __builtin_nontemporal_load((const bf16x8 *)(vb + i * 512));
   };
-  // The first loads carry no condition (a wavefront without a run loads the last one), so that the wait counts that
-  // follow stay exact.  ROTATE: stage 0 is requested right behind the rotation's input, the others when that has
-  // arrived and freed its registers.
+  // The first loads of stage 0 carry no condition (a wavefront without a run loads the last one), so that the wait
+  // counts of the rotation stay exact.  ROTATE: stage 0 is requested right behind the rotation's input, the others
+  // when that has arrived and freed its registers.
   int page_next[NS];   // page of the run stage st takes after the one it holds
   auto load_first = [&](int st) {
     const int b0 = wave + 4 * st, bl = min(b0, nblk - 1);
-    const bf16_t *kb = run_base(bl, page_of(bl));
-    load_k(st, kb);
-    load_v(st, kb);
+    if (st == 0 || b0 < nblk) {
+      const bf16_t *kb = run_base(bl, page_of(bl));
+      load_k(st, kb);
+      load_v(st, kb);
+    }
     page_next[st] = b0 + 4 * NS < nblk ? page_of(b0 + 4 * NS) : 0;
   };
   load_first(0);
@@ -733,6 +735,11 @@ bool attention_split(int chunk, int64_t total_tokens, int64_t longest_item, int6
   return chunk > ATTN_SUB && longest_item >= 3 * ATTN_SUB && n_subs * Hkv <= ATTN_SPLIT_PARTS && longest_item * 128 > total_tokens * Hkv;
 }
 
+// Whether the workgroup that finishes a row last merges its chunks.  One workgroup folds them eight at a time, each a
+// round trip to the shared memory: 118 chunks (5 rows of up to 15000 tokens in 128-token chunks) 41 us against 37 with the
+// merge launch, which has a workgroup per head; up to 17 (1.5B shape, 64 rows) the same or better.
+bool attention_tickets(int max_chunks) { return max_chunks <= 32; }
+
 // Whether a step's attention rotates and appends by itself: while its workgroups run all at once (two per compute
 // unit, three at half the head dimension) it saves the launch (1.5B shape, 64 rows: 26.5 + 5.1 us and a gap -> 27.6; 7B, 19
 // rows: 34.5 + 5.0 -> 36.2), in later rounds every workgroup pays the round trip (7B, 256 rows: 265 + 8.9 -> 289).
@@ -759,8 +766,7 @@ static void launch_attention_hd(const AttnParams &p, hipStream_t s, int part) {
     else
       hipLaunchKernelGGL((attn_decode_kernel<HD, PL_ATTN_NS, true>), grid, dim3(256), 0, s, p);
   }
-  // items are subs, or there is no list (whose kernel clears the tickets) and a row can span several chunks
-  if (part != 1 && (p.item_tokens < p.chunk || (!p.tickets && p.max_chunks > 1)))
+  if (part != 1 && p.merge)
     hipLaunchKernelGGL(attn_merge_kernel<HD>, dim3(p.Hq, p.n_seq), dim3(HD), 0, s, p);
 }
 

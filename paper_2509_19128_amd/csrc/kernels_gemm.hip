@@ -17,12 +17,14 @@ namespace {
 
 constexpr int BK = 64;          // k elements per main-loop step
 constexpr int LDS_ROW = 72;     // padded row length (elements) of the x tile in LDS
-// Cache policy of the W loads: non-temporal (2) where a W tile is read by one wavefront of a workgroup (WM = 1), ordinary
-// where two share it through the caches.  SwiGLU of the 32B shape, 128 rows: 111.8 -> 98.7 us (5.7 TB/s); 7B shape,
-// 19 rows, whole step -4 %; products at 256 rows -1 % (the second row tile's reader still finds it in L2); with
-// WM = 2 tiles (1.5B shape, 64 rows) non-temporal loads cost 3.5 % of the step.
-template <int WM>
-constexpr int W_CACHE = WM == 1 ? 2 : 0;
+// Cache policy of the W loads: non-temporal (2) for weights that are COLD, that is, cannot be in the 256 MB last-level cache
+// from the pass before, in tiles whose W one wavefront reads (WM = 1): they have no second reader, and ordinary loads
+// evict each other from L2 on the way.  SwiGLU of the 32B shape, 128 rows: 111.8 -> 98.7 us (5.7 TB/s); 7B shape, 19 rows,
+// whole step -4 %; products at 256 rows -1 % (the second row tile's reader still finds W in L2).  Where two wavefronts
+// share W through the caches (WM = 2; 1.5B shape, 64 rows) they cost 3.5 % of the step, and a matrix that stays in the
+// last-level cache between calls 5 to 30 % (55 MB, 3 rows: 11 -> 16 us).
+template <int WM, bool COLD>
+constexpr int W_CACHE = WM == 1 && COLD ? 2 : 0;
 
 // Workgroup = 4 wavefronts arranged WM x WN; each owns (AT*32) x (BT*32) outputs.
 // Software pipeline: W fragments live in a 4-deep register ring (loads run three k-steps ahead of
@@ -35,7 +37,7 @@ constexpr int W_CACHE = WM == 1 ? 2 : 0;
 // workgroup; the kernels below are thin wrappers that pick the tile(s) of a workgroup.
 // FOLD: all K slices of `ksteps` k-steps in one go: every slice's sum starts from zero and is added to the
 // running total in slice order, so the one result equals the sum a consumer makes of separate slices bit for bit.
-template <int WM, int WN, int AT, int BT, int MODE, bool FOLD = false>
+template <int WM, int WN, int AT, int BT, int MODE, bool COLD, bool FOLD = false>
 __device__ __forceinline__ void gemm_tile(bf16_t (*xs)[WM * AT * 32 * LDS_ROW], const bf16_t *__restrict__ X,
                                           const bf16_t *__restrict__ W, void *__restrict__ Yv, int M, int N, int K,
                                           int ksteps, int n_tile0, int m0, int split, int n_end, int ldy, int y_col0) {
@@ -83,7 +85,7 @@ __device__ __forceinline__ void gemm_tile(bf16_t (*xs)[WM * AT * 32 * LDS_ROW], 
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         wf[stage][bt][j] = __builtin_bit_cast(
-            bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, w_lane + j * 1024, (int)(w_blk[bt] + (uint32_t)ks * w_plane), W_CACHE<WM>));
+            bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, w_lane + j * 1024, (int)(w_blk[bt] + (uint32_t)ks * w_plane), W_CACHE<WM, COLD>));
   };
   auto load_x = [&](int stage, int ks) {
 #pragma unroll
@@ -248,7 +250,7 @@ __device__ __forceinline__ void gemm_tile(bf16_t (*xs)[WM * AT * 32 * LDS_ROW], 
 // own left to load, issue the first loads of B into the ring slots they free, so B starts with its
 // operands already on the way while A's epilogue runs.  Same k order per output element as gemm_tile.
 // K / BK and B's k-step count are multiples of 4 and at least 4.
-template <int WM, int WN, int AT, int BT>
+template <int WM, int WN, int AT, int BT, bool COLD>
 __device__ __forceinline__ void gemm_tile2(bf16_t (*xs)[WM * AT * 32 * LDS_ROW], const bf16_t *__restrict__ X,
                                            const bf16_t *__restrict__ W, bf16_t *__restrict__ mid, float *__restrict__ ws,
                                            int M, int N, int K, int n_tileA, int m0A, int n_main, int n_tileB, int m0B,
@@ -297,7 +299,7 @@ __device__ __forceinline__ void gemm_tile2(bf16_t (*xs)[WM * AT * 32 * LDS_ROW],
       for (int j = 0; j < 4; ++j)
         wf[stage][bt][j] = __builtin_bit_cast(
             bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
-                        rw, w_lane + j * 1024, (int)((decltype(SEG)::value == 1 ? w_blkA[bt] : w_blkB[bt]) + (uint32_t)ks * w_plane), W_CACHE<WM>));
+                        rw, w_lane + j * 1024, (int)((decltype(SEG)::value == 1 ? w_blkA[bt] : w_blkB[bt]) + (uint32_t)ks * w_plane), W_CACHE<WM, COLD>));
   };
   auto load_x = [&](auto SEG, int stage, int ks) {
 #pragma unroll
@@ -440,7 +442,7 @@ __device__ __forceinline__ void gemm_tile2(bf16_t (*xs)[WM * AT * 32 * LDS_ROW],
   }
 }
 
-template <int WM, int WN, int AT, int BT, int MODE>
+template <int WM, int WN, int AT, int BT, int MODE, bool COLD>
 __global__ __launch_bounds__(256) void gemm_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
                                                    void *__restrict__ Yv, int M, int N, int K, int ksteps,
                                                    int n_base, int n_end, int nrow, int ldy, int y_col0) {
@@ -456,12 +458,12 @@ __global__ __launch_bounds__(256) void gemm_kernel(const bf16_t *__restrict__ X,
     ctile = (blockIdx.x / (8 * nrow)) * 8 + (blockIdx.x & 7);
     if (n_base + ctile * BN >= n_end) return;   // padding of the flat grid (uniform for the workgroup)
   }
-  gemm_tile<WM, WN, AT, BT, MODE>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, blockIdx.y, n_end, ldy, y_col0);
+  gemm_tile<WM, WN, AT, BT, MODE, COLD>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, blockIdx.y, n_end, ldy, y_col0);
 }
 
 // Many rows (prompt passes): flat grid in XCD-local groups of row tiles as above, all K slices of a tile in
 // one workgroup.
-template <int WM, int WN, int AT, int BT, int MODE>
+template <int WM, int WN, int AT, int BT, int MODE, bool COLD>
 __global__ __launch_bounds__(256) void gemm_fold_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
                                                         void *__restrict__ Yv, int M, int N, int K, int ksteps,
                                                         int n_base, int n_end, int nrow) {
@@ -469,7 +471,7 @@ __global__ __launch_bounds__(256) void gemm_fold_kernel(const bf16_t *__restrict
   __shared__ __attribute__((aligned(16))) bf16_t xs[2][BM * LDS_ROW];
   const int rtile = (blockIdx.x >> 3) % nrow, ctile = (blockIdx.x / (8 * nrow)) * 8 + (blockIdx.x & 7);
   if (n_base + ctile * BN >= n_end) return;   // padding of the flat grid (uniform for the workgroup)
-  gemm_tile<WM, WN, AT, BT, MODE, true>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, 0, n_end, N, 0);
+  gemm_tile<WM, WN, AT, BT, MODE, COLD, true>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, 0, n_end, N, 0);
 }
 
 // The SwiGLU product of a 129..256-row batch in ONE launch of one workgroup per compute unit.  Workgroup i
@@ -481,7 +483,7 @@ __global__ __launch_bounds__(256) void gemm_fold_kernel(const bf16_t *__restrict
 // both runs them back to back through gemm_tile2, the slice's first loads issued under the main tile's
 // last k-steps.  Every unit thus works 56 + 12 k-steps at the 7B shape instead of 256 units 56 and then
 // 160 units 56 more on quarter-size tiles.
-template <int WM, int WN, int AT, int BT>
+template <int WM, int WN, int AT, int BT, bool COLD>
 __global__ __launch_bounds__(256) void gemm_gu_fused_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
                                                             bf16_t *__restrict__ mid, float *__restrict__ ws, int M, int N,
                                                             int K, int n_main, int rem_splits, int rem_ksteps) {
@@ -495,18 +497,18 @@ __global__ __launch_bounds__(256) void gemm_gu_fused_kernel(const bf16_t *__rest
   const bool hasB = item < rem_ctiles * nrow;
   const int ctileB = item / nrow, rtileB = item % nrow;
   if (hasA && hasB)   // uniform for the workgroup
-    gemm_tile2<WM, WN, AT, BT>(xs, X, W, mid, ws, M, N, K, ctileA * BN, rtileA * BM, n_main, n_main + ctileB * BN,
+    gemm_tile2<WM, WN, AT, BT, COLD>(xs, X, W, mid, ws, M, N, K, ctileA * BN, rtileA * BM, n_main, n_main + ctileB * BN,
                                rtileB * BM, split, rem_ksteps);
   else if (hasA)
-    gemm_tile<WM, WN, AT, BT, 1>(xs, X, W, mid, M, N, K, K / BK, ctileA * BN, rtileA * BM, 0, n_main, 0, 0);
+    gemm_tile<WM, WN, AT, BT, 1, COLD>(xs, X, W, mid, M, N, K, K / BK, ctileA * BN, rtileA * BM, 0, n_main, 0, 0);
   else if (hasB)
-    gemm_tile<WM, WN, AT, BT, 0>(xs, X, W, ws, M, N, K, rem_ksteps, n_main + ctileB * BN, rtileB * BM, split, N, N - n_main, n_main);
+    gemm_tile<WM, WN, AT, BT, 0, COLD>(xs, X, W, ws, M, N, K, rem_ksteps, n_main + ctileB * BN, rtileB * BM, split, N, N - n_main, n_main);
 }
 
 // The same product for calls of at most one row tile (a decayed batch in an engine sized for more rows): workgroups
 // below n_tiles take the main tiles, the others the K slices of the remainder, in one launch.  The two launches
 // in a row each left part of the chip idle: 7B shape, 19 rows, 43 + 11 us and a gap; joined 50.
-template <int WM, int WN, int AT, int BT>
+template <int WM, int WN, int AT, int BT, bool COLD>
 __global__ __launch_bounds__(256) void gemm_gu_joint_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
                                                             bf16_t *__restrict__ mid, float *__restrict__ ws, int M, int N,
                                                             int K, int n_main, int n_tiles, int rem_splits, int rem_ksteps) {
@@ -514,9 +516,9 @@ __global__ __launch_bounds__(256) void gemm_gu_joint_kernel(const bf16_t *__rest
   __shared__ __attribute__((aligned(16))) bf16_t xs[2][BM * LDS_ROW];
   const int item = (int)blockIdx.x - n_tiles;
   if (item < 0)   // uniform for the workgroup
-    gemm_tile<WM, WN, AT, BT, 1>(xs, X, W, mid, M, N, K, K / BK, (int)blockIdx.x * BN, 0, 0, n_main, 0, 0);
+    gemm_tile<WM, WN, AT, BT, 1, COLD>(xs, X, W, mid, M, N, K, K / BK, (int)blockIdx.x * BN, 0, 0, n_main, 0, 0);
   else
-    gemm_tile<WM, WN, AT, BT, 0>(xs, X, W, ws, M, N, K, rem_ksteps, n_main + item / rem_splits * BN, 0, item % rem_splits, N,
+    gemm_tile<WM, WN, AT, BT, 0, COLD>(xs, X, W, ws, M, N, K, rem_ksteps, n_main + item / rem_splits * BN, 0, item % rem_splits, N,
                                  N - n_main, n_main);
 }
 
@@ -546,9 +548,15 @@ struct Launch {
   const bf16_t *x, *w;
   void *y;
   int M, N, K, mode, splits, n_begin, n_end, ldy, y_col0;
-  bool paired;
+  bool paired, cold;
   hipStream_t s;
 };
+
+// calls f(bool constant), true where the tile shape has a kernel of its own for cold weights
+template <int WM, typename F>
+void with_cold(bool cold, F f) {
+  if (WM == 1 && cold) f(std::bool_constant<WM == 1>{}); else f(std::false_type{});
+}
 
 // Launch over output columns [n_begin, n_end) (multiples of the tile width, except the matrix edge).
 template <int WM, int WN, int AT, int BT>
@@ -564,12 +572,15 @@ int launch_cfg(const Launch &L) {
     grid.z = 1;
   }
   int ksteps = 4 * ((L.K / (4 * BK) + L.splits - 1) / L.splits);
-  if (L.mode == 0)
-    hipLaunchKernelGGL((gemm_kernel<WM, WN, AT, BT, 0>), grid, dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps,
-                       L.n_begin, L.n_end, nrow, L.ldy, L.y_col0);
-  else
-    hipLaunchKernelGGL((gemm_kernel<WM, WN, AT, (BT > 1 ? BT : 2), 1>), grid, dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N,
-                       L.K, ksteps, L.n_begin, L.n_end, nrow, L.ldy, L.y_col0);
+  with_cold<WM>(L.cold, [&](auto COLD) {
+    constexpr bool cold = decltype(COLD)::value;
+    if (L.mode == 0)
+      hipLaunchKernelGGL((gemm_kernel<WM, WN, AT, BT, 0, cold>), grid, dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps,
+                         L.n_begin, L.n_end, nrow, L.ldy, L.y_col0);
+    else
+      hipLaunchKernelGGL((gemm_kernel<WM, WN, AT, (BT > 1 ? BT : 2), 1, cold>), grid, dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N,
+                         L.K, ksteps, L.n_begin, L.n_end, nrow, L.ldy, L.y_col0);
+  });
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }
 
@@ -603,14 +614,16 @@ int launch_fold_cfg(Launch L) {
   if (splits == 1) return launch_cfg<WM, WN, AT, BT>(L);
   const int nrow = (L.M + BM - 1) / BM, grid = ((L.n_end - L.n_begin + BN - 1) / BN + 7) / 8 * 8 * nrow;
   const int ksteps = 4 * ((L.K / (4 * BK) + splits - 1) / splits);
-  if (L.mode == 0)
-    hipLaunchKernelGGL((gemm_fold_kernel<WM, WN, AT, BT, 0>), dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps,
-                       L.n_begin, L.n_end, nrow);
-  else if constexpr (BT == 2 && AT <= 2)
-    hipLaunchKernelGGL((gemm_fold_kernel<WM, WN, AT, BT, 1>), dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps,
-                       L.n_begin, L.n_end, nrow);
-  else
-    return -1;
+  if (L.mode == 1 && (BT != 2 || AT > 2)) return -1;   // (not used: no registers for a second set of accumulators)
+  with_cold<WM>(L.cold, [&](auto COLD) {
+    constexpr bool cold = decltype(COLD)::value;
+    if (L.mode == 0)
+      hipLaunchKernelGGL((gemm_fold_kernel<WM, WN, AT, BT, 0, cold>), dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K,
+                         ksteps, L.n_begin, L.n_end, nrow);
+    else if constexpr (BT == 2 && AT <= 2)
+      hipLaunchKernelGGL((gemm_fold_kernel<WM, WN, AT, BT, 1, cold>), dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K,
+                         ksteps, L.n_begin, L.n_end, nrow);
+  });
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }
 
@@ -635,14 +648,14 @@ int gemm_tile_rows(int cfg) {
 // One launch of one tile configuration over a column range (tuning and tests).  mode 1 with
 // splits > 1 writes fp32 partials to ws and finishes with the SwiGLU reduction.
 int launch_gemm_cfg(int cfg, const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int N, int K, int mode,
-                    int splits, int n_begin, int n_end, bool paired, hipStream_t s) {
+                    int splits, int n_begin, int n_end, bool paired, bool cold, hipStream_t s) {
   if (M < 1 || M > 512 || K % (4 * BK) || N % 32 || !splits_valid(K, splits)) return -1;
   if (mode != 0 && mode != 1) return -1;
   if (mode == 1 && (N % 64 || n_begin % 64 || n_end % 64)) return -1;
   if (n_begin < 0 || n_end > N || n_begin % 32 || n_end % 32) return -1;
   if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
   if (paired && splits != 1) return -1;
-  Launch L{x, w, y, M, N, K, mode, splits, n_begin, n_end, N, 0, paired, s};
+  Launch L{x, w, y, M, N, K, mode, splits, n_begin, n_end, N, 0, paired, cold, s};
   if (mode == 1 && splits > 1) {
     if (!ws) return -1;
     L.mode = 0; L.y = ws; L.ldy = n_end - n_begin; L.y_col0 = n_begin;
@@ -715,7 +728,7 @@ int64_t gemm_workspace_elems(int M_max, int N, const GemmSplit &ks) {
 }
 
 int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int N, int K, int mode,
-                const GemmSplit &ks, hipStream_t s) {
+                const GemmSplit &ks, bool cold, hipStream_t s) {
   if (M < 1 || M > 512 || K % (4 * BK) || N % 32 || !splits_valid(K, ks.splits)) return -1;
   if (mode != 0 && mode != 1) return -1;
   if (mode == 1 && (N % 64 || ks.n_main % 64 || !splits_valid(K, ks.rem_splits))) return -1;
@@ -753,8 +766,10 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
     const int nrow = (M + 127) / 128, rem_ctiles = (N - n_main + 255) / 256;
     const int wgs = std::max(((n_main / 256 + 7) / 8) * 8 * nrow, rem_ctiles * nrow * ks.rem_splits);
     const int rem_ksteps = 4 * ((K / (4 * BK) + ks.rem_splits - 1) / ks.rem_splits);
-    hipLaunchKernelGGL((gemm_gu_fused_kernel<1, 4, 4, 2>), dim3(wgs), dim3(256), 0, s, x, w, (bf16_t *)y, ws, M, N, K, n_main,
-                       ks.rem_splits, rem_ksteps);
+    with_cold<1>(cold, [&](auto COLD) {
+      hipLaunchKernelGGL((gemm_gu_fused_kernel<1, 4, 4, 2, decltype(COLD)::value>), dim3(wgs), dim3(256), 0, s, x, w, (bf16_t *)y, ws, M,
+                         N, K, n_main, ks.rem_splits, rem_ksteps);
+    });
     if (hipGetLastError() != hipSuccess) return -7;
     return swiglu_reduce(ws, ks.rem_splits, M, N - n_main, n_main, (bf16_t *)y, N / 2, s);
   }
@@ -763,19 +778,22 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
     const int bn = cfg == GEMM_64x128 ? 128 : 256, n_tiles = (n_main + bn - 1) / bn;
     const dim3 grid(n_tiles + (N - n_main + bn - 1) / bn * ks.rem_splits);
     const int rem_ksteps = 4 * ((K / (4 * BK) + ks.rem_splits - 1) / ks.rem_splits);
-    if (cfg == GEMM_32x256)
-      hipLaunchKernelGGL((gemm_gu_joint_kernel<1, 4, 1, 2>), grid, dim3(256), 0, s, x, w, (bf16_t *)y, ws, M, N, K, n_main, n_tiles, ks.rem_splits, rem_ksteps);
-    else if (cfg == GEMM_64x128)
-      hipLaunchKernelGGL((gemm_gu_joint_kernel<2, 2, 1, 2>), grid, dim3(256), 0, s, x, w, (bf16_t *)y, ws, M, N, K, n_main, n_tiles, ks.rem_splits, rem_ksteps);
-    else
-      hipLaunchKernelGGL((gemm_gu_joint_kernel<1, 4, 4, 2>), grid, dim3(256), 0, s, x, w, (bf16_t *)y, ws, M, N, K, n_main, n_tiles, ks.rem_splits, rem_ksteps);
+    with_cold<1>(cold, [&](auto COLD) {
+      constexpr bool c = decltype(COLD)::value;
+      auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, x, w, (bf16_t *)y, ws, M, N, K, n_main, n_tiles, ks.rem_splits, rem_ksteps);
+      };
+      if (cfg == GEMM_32x256) launch(gemm_gu_joint_kernel<1, 4, 1, 2, c>);
+      else if (cfg == GEMM_64x128) launch(gemm_gu_joint_kernel<2, 2, 1, 2, false>);
+      else launch(gemm_gu_joint_kernel<1, 4, 4, 2, c>);
+    });
     if (hipGetLastError() != hipSuccess) return -7;
     return swiglu_reduce(ws, ks.rem_splits, M, N - n_main, n_main, (bf16_t *)y, N / 2, s);
   }
-  int rc = launch_gemm_cfg(cfg, x, w, y, ws, M, N, K, mode, ks.splits, 0, n_main, paired, s);
+  int rc = launch_gemm_cfg(cfg, x, w, y, ws, M, N, K, mode, ks.splits, 0, n_main, paired, cold, s);
   if (rc || n_main == N) return rc;
   return launch_gemm_cfg(GEMM_64x128, x, w, y, ws, M, N, K, mode, mode == 1 ? ks.rem_splits : ks.splits, n_main, N,
-                         false, s);
+                         false, cold, s);
 }
 
 // A product of up to GEMM_MAX_ROWS rows with all K slices of an element added up in the workgroup, in slice
@@ -785,14 +803,15 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
 // are saved.  Measured at 1024 rows against four 256-row launches, consumers' reads not counted: QKV / O / gate-up
 // / down of the 1.5B shape 14 / 13 / 73 / 52 against 50 / 43 / 116 / 100 us, of the 7B shape 53 / 37 / 288 / 189
 // against 82 / 71 / 350 / 200 us.
-int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, int K, int mode, const GemmSplit &ks, hipStream_t s) {
+int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, int K, int mode, const GemmSplit &ks, bool cold,
+                       hipStream_t s) {
   if (M < 1 || M > GEMM_MAX_ROWS || K % (4 * BK) || N % 32 || !splits_valid(K, ks.splits)) return -1;
   if (mode != 0 && mode != 1) return -1;
   if (mode == 1 && (N % 64 || ks.n_main % 64 || !splits_valid(K, ks.rem_splits))) return -1;
   if (mode == 0 && ks.n_main != N) return -1;
   if (ks.n_main < 0 || ks.n_main > N) return -1;
   if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
-  Launch L{x, w, y, M, N, K, mode, ks.splits, 0, ks.n_main, N, 0, true, s};
+  Launch L{x, w, y, M, N, K, mode, ks.splits, 0, ks.n_main, N, 0, true, cold, s};
   if (mode == 1) {
     // 7B shape, 1024 rows: 288 us with 128 x 256 tiles, 302 with 256 x 128, 349 with 128 x 128; 1.5B shape (a third of
     // the tiles): 78, 85, 73

@@ -88,7 +88,7 @@ struct AttnParams {
   const int32_t *row_slot;  // [n_seq] or null
   int32_t *work;            // work list built by launch_attention_worklist for these ctx_len, row_slot and page_table;
                             // null: none (row_slot null; max_items = n_seq * max_chunks)
-  int32_t *tickets;         // [n_seq, Hkv], zero between launches (the work-list kernel clears them); null without a list
+  int32_t *tickets;         // [n_seq, Hkv], zero between launches (the work-list kernel clears them), or null: see attention_tickets
   int32_t *first_item;      // [n_seq] list index of a row's first item (item_tokens < chunk)
   const int32_t *groups;    // rows of a pass: {count, -, (first row, rows) ...}, each group consecutive positions of one slot
   int32_t max_items;        // upper bound on the list length, or on the number of groups (sizes the grid)
@@ -96,9 +96,11 @@ struct AttnParams {
   float *part_o;            // [n_seq, Hkv, max_chunks, G, hd]; item_tokens < chunk: [item, Hkv, 4, G, hd]
   float *part_ml;           // [n_seq, Hkv, max_chunks, ATTN_ML]; item_tokens < chunk: [item, Hkv, 4, 16, 2]
   int32_t n_seq, Hq, Hkv, hd, page_tokens, pages_per_seq, chunk, max_chunks;
+  int32_t merge;            // rows span several items and the decode kernel does not merge them: launch the merge kernel
   int32_t item_tokens;      // tokens of a work item: chunk, or ATTN_SUB where attention_split says so
 };
 int launch_attention(const AttnParams &p, hipStream_t s, int part = 0);
+bool attention_tickets(int max_chunks);
 bool attention_rotates(int items, int Hq, int Hkv, int hd, int splits);
 int launch_attention_rows(const AttnParams &p, hipStream_t s);
 int attention_rows_per_group(int Hq, int Hkv);
@@ -120,14 +122,18 @@ enum { GEMM_32x256, GEMM_64x256, GEMM_128x256, GEMM_64x128, GEMM_128x128, GEMM_2
 struct GemmSplit { int splits, n_main, rem_splits; };
 GemmSplit gemm_pick_split(int M_max, int N, int K, int mode);
 int64_t gemm_workspace_elems(int M_max, int N, const GemmSplit &ks);
+// Bytes that are read again and again but do not stay in the 256 MB last-level cache in between (a matrix a little
+// larger than the cache is still mostly there: 271 MB, 76 rows, 45 us against 53 with non-temporal loads).
+inline bool gemm_cold(int64_t bytes) { return bytes > (int64_t)384 << 20; }
+// cold: gemm_cold of all the weights that pass between two uses of this matrix (kernels_gemm.hip: W_CACHE)
 // ws: fp32 workspace of gemm_workspace_elems (mode 1 with split K), else may be null
 int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int N, int K, int mode,
-                const GemmSplit &ks, hipStream_t s);
+                const GemmSplit &ks, bool cold, hipStream_t s);
 constexpr int GEMM_MAX_ROWS = 1024;   // of launch_gemm_folded
-int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, int K, int mode, const GemmSplit &ks,
+int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, int K, int mode, const GemmSplit &ks, bool cold,
                        hipStream_t s);
 int launch_gemm_cfg(int cfg, const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int N, int K, int mode,
-                    int splits, int n_begin, int n_end, bool paired, hipStream_t s);
+                    int splits, int n_begin, int n_end, bool paired, bool cold, hipStream_t s);
 int gemm_tile_rows(int cfg);
 int gemm_pick_splits(int M, int N, int K);
 

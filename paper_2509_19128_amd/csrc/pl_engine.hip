@@ -112,6 +112,7 @@ struct pl_engine {
     int64_t items_cap = 0;   // records the attention work list holds
     int attn_items = 0;   // bound on this pass's attention work items
     bool attn_split = false;   // this step's attention items are single subs
+    bool attn_merge = false;   // rows of this step span several items and take the merge launch
     // the 8-byte ids come first, so every array is aligned for its type whatever rows_cap is
     uint64_t *m_seq_id(bool dev) { return (uint64_t *)(dev ? meta_d : meta_h); }
     int32_t *m_row_slot(bool dev) { return (int32_t *)(m_seq_id(dev) + rows_cap); }
@@ -160,7 +161,7 @@ struct pl_engine {
   // attention kernels; everything that changes from step to step is read from device buffers.
   struct StepGraph {
     int n = 0, buf = 0, items = 0, set = 0;   // set: 0 decode step, 1 cache-only pass
-    bool split = false;
+    bool split = false, merge = false;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     uint64_t last_use = 0;
@@ -469,8 +470,9 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   const bf16_t *lm = base + e->layout.back().offset;
   int rc = 0;
   const bool fold = prefill && n > std::max(c.max_batch, SLICED_ROWS);   // many rows: the products come as one slice each
+  const bool cold = pl::gemm_cold(e->streamed_weight_bytes);   // every product's weights pass by once per step
   auto gemm = [&](const bf16_t *x, const bf16_t *wt, void *y, float *ws, int N, int K, int mode, const pl::GemmSplit &ks) {
-    return fold ? pl::launch_gemm_folded(x, wt, y, n, N, K, mode, ks, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, s);
+    return fold ? pl::launch_gemm_folded(x, wt, y, n, N, K, mode, ks, cold, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, cold, s);
   };
   auto slices = [&](const pl::GemmSplit &ks) { return fold ? 1 : ks.splits; };
   pl::AttnParams ap{};
@@ -479,7 +481,7 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   ap.n_seq = n; ap.Hq = c.n_q_heads; ap.Hkv = c.n_kv_heads; ap.hd = c.head_dim;
   ap.page_tokens = e->page_tokens; ap.pages_per_seq = e->pages_per_seq; ap.chunk = e->attn_chunk;
   ap.max_chunks = e->attn_max_chunks; ap.item_tokens = w.attn_split ? pl::ATTN_SUB : e->attn_chunk;
-  ap.work = w.attn_work; ap.tickets = w.attn_tickets; ap.first_item = w.attn_first; ap.max_items = w.attn_items;
+  ap.work = w.attn_work; ap.tickets = pl::attention_tickets(e->attn_max_chunks) ? w.attn_tickets : nullptr; ap.merge = w.attn_merge; ap.first_item = w.attn_first; ap.max_items = w.attn_items;
   if (prefill) ap.groups = w.m_pairs(true);
   // (the rows of a pass attend to one another: all their keys and values are appended first)
   const bool rotates = !prefill && pl::attention_rotates(w.attn_items, c.n_q_heads, c.n_kv_heads, c.head_dim, e->ks_qkv.splits);
@@ -528,7 +530,7 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   }
   if (prefill) return rc ? fail(PL_E_HIP, "kernel launch failed: %s", hipGetErrorString(hipGetLastError())) : PL_OK;
   mark(e, CAT_OTHER);
-  rc |= pl::launch_gemm(w.a, lm, e->logits, nullptr, n, c.vocab, d, 0, e->ks_lm, s);
+  rc |= pl::launch_gemm(w.a, lm, e->logits, nullptr, n, c.vocab, d, 0, e->ks_lm, cold, s);
   mark(e, CAT_GEMM);
   pl::SampleParams sp{};
   sp.logits = e->logits; sp.n = n; sp.vocab = c.vocab; sp.seq_id = w.m_seq_id(true);
@@ -559,7 +561,7 @@ int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) {
   w.attn_items = (int)std::min<int64_t>((w.attn_items + 63) / 64 * 64, w.items_cap);
   pl_engine::StepGraph *g = nullptr;
   for (auto &x : e->graphs)
-    if (x.n == n && x.buf == e->active_buf && x.items == w.attn_items && x.split == w.attn_split && x.set == set) { g = &x; break; }
+    if (x.n == n && x.buf == e->active_buf && x.items == w.attn_items && x.split == w.attn_split && x.merge == w.attn_merge && x.set == set) { g = &x; break; }
   if (!g) {
     if (e->graphs.size() >= MAX_STEP_GRAPHS) {   // evict the least recently used
       size_t lru = 0;
@@ -569,7 +571,7 @@ int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) {
       e->graphs.erase(e->graphs.begin() + lru);
     }
     pl_engine::StepGraph ng;
-    ng.n = n; ng.buf = e->active_buf; ng.items = w.attn_items; ng.split = w.attn_split; ng.set = set;
+    ng.n = n; ng.buf = e->active_buf; ng.items = w.attn_items; ng.split = w.attn_split; ng.merge = w.attn_merge; ng.set = set;
     HIP_TRY(hipStreamBeginCapture(w.stream, hipStreamCaptureModeThreadLocal));
     const int rc = enqueue_step(e, w, n, prefill);
     const hipError_t ce = hipStreamEndCapture(w.stream, &ng.graph);
@@ -1209,6 +1211,7 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
 
   w.attn_split = pl::attention_split(e->attn_chunk, (int64_t)kv_tokens + r, longest, subs, c.n_kv_heads);
   w.attn_items = w.attn_split ? subs : items;
+  w.attn_merge = w.attn_split || (items > r && !pl::attention_tickets(e->attn_max_chunks));
 
   // 4. run
   if (!e->dry) {
@@ -1447,8 +1450,14 @@ int pl_debug_kv_pool(pl_engine *e, void **device_ptr, int64_t *nbytes) {
 
 // ---- kernel-level entry points ---------------------------------------------------------------------
 
-// Calls with at most this many workgroups need no work list: all of them run at once, or nearly, in any order.
-static bool attention_direct(int32_t n_seq, int32_t n_kv_heads, int64_t max_chunks) { return n_seq * max_chunks * n_kv_heads <= 2048; }
+// Calls that need no work list: all workgroups run at once, or none of them is long enough for the order to matter
+// (the list puts the long ones first).  The list kernel takes 4 us; without a list chunks are
+// merged by a launch of their own, and with many short chunks the empty workgroups between the others cost more (7B
+// shape, 212 rows of up to 491 tokens, 3392 workgroups: 29.4 us with the list, 39.4 without).
+static bool attention_direct(int32_t n_seq, int32_t n_kv_heads, int64_t max_chunks, int32_t chunk, int32_t max_ctx) {
+  const int64_t workgroups = n_seq * max_chunks * n_kv_heads;
+  return workgroups <= 512 || (workgroups <= (max_chunks == 1 ? 4096 : 2048) && std::min(chunk, max_ctx) <= 512);
+}
 
 int64_t pl_attention_workspace_bytes(int32_t n_seq, int32_t n_q_heads, int32_t n_kv_heads, int32_t hd, int32_t max_ctx) {
   if (n_seq < 1 || n_q_heads < 1 || n_kv_heads < 1 || hd < 1 || max_ctx < 1) return 0;
@@ -1477,11 +1486,12 @@ int pl_attention_decode(const void *q, const void *kv_pages, const int32_t *page
   p.part_ml = p.part_o + np * n_q_heads * hd;
   p.max_items = (int32_t)np;
   if (n_seq > 1024) return fail(PL_E_INVAL, "at most 1024 sequences per launch");
-  if (!attention_direct(n_seq, n_kv_heads, p.max_chunks)) {
+  if (!attention_direct(n_seq, n_kv_heads, p.max_chunks, p.chunk, max_ctx)) {
     p.work = (int32_t *)(p.part_ml + np * n_kv_heads * pl::ATTN_ML);
-    p.tickets = p.work + pl::attention_worklist_ints(np);
+    if (pl::attention_tickets(p.max_chunks)) p.tickets = p.work + pl::attention_worklist_ints(np);
     if (pl::launch_attention_worklist(p, p.max_items, (hipStream_t)stream)) return fail(PL_E_HIP, "attention launch failed");
   }
+  p.merge = !p.tickets && p.max_chunks > 1;
   if (pl::launch_attention(p, (hipStream_t)stream)) return fail(PL_E_HIP, "attention launch failed");
   return PL_OK;
 }
@@ -1521,7 +1531,8 @@ int pl_gemm_bf16(const void *x, const void *w, void *y, int32_t M, int32_t N, in
                  void *stream) {
   if (!x || !w || !y) return fail(PL_E_INVAL, "NULL argument");
   if (mode == 1 && splits != 1) return fail(PL_E_INVAL, "the SwiGLU product takes splits = 1");
-  int rc = pl::launch_gemm((const bf16_t *)x, (const bf16_t *)w, y, nullptr, M, N, K, mode, pl::GemmSplit{splits, N, 1}, (hipStream_t)stream);
+  int rc = pl::launch_gemm((const bf16_t *)x, (const bf16_t *)w, y, nullptr, M, N, K, mode, pl::GemmSplit{splits, N, 1}, pl::gemm_cold((int64_t)N * K * 2),
+                           (hipStream_t)stream);
   if (rc == -1) return fail(PL_E_INVAL, "unsupported GEMM shape M=%d N=%d K=%d mode=%d splits=%d", M, N, K, mode, splits);
   if (rc) return fail(PL_E_HIP, "GEMM launch failed");
   return PL_OK;
@@ -1531,7 +1542,7 @@ int pl_debug_gemm_cfg(int32_t cfg, const void *x, const void *w, void *y, void *
                       int32_t mode, int32_t splits, int32_t n_begin, int32_t n_end, int32_t paired, void *stream) {
   if (!x || !w || !y) return fail(PL_E_INVAL, "NULL argument");
   int rc = pl::launch_gemm_cfg(cfg, (const bf16_t *)x, (const bf16_t *)w, y, (float *)ws, M, N, K, mode, splits, n_begin,
-                               n_end, paired != 0, (hipStream_t)stream);
+                               n_end, paired != 0, pl::gemm_cold((int64_t)N * K * 2), (hipStream_t)stream);
   if (rc == -1) return fail(PL_E_INVAL, "unsupported GEMM launch cfg=%d M=%d N=%d K=%d mode=%d splits=%d [%d, %d)", cfg, M, N, K, mode, splits, n_begin, n_end);
   if (rc) return fail(PL_E_HIP, "GEMM launch failed");
   return PL_OK;
@@ -1555,7 +1566,7 @@ int pl_debug_gemm_planned(const void *x, const void *w, void *y, void *ws, int32
     return fail(PL_E_INVAL, "unsupported GEMM shape");
   const pl::GemmSplit ks = pl::gemm_pick_split(M_max, N, K, mode);
   if (!ws && mode == 1 && pl::gemm_workspace_elems(M_max, N, ks) > 0) return fail(PL_E_INVAL, "this plan needs a workspace");
-  int rc = pl::launch_gemm((const bf16_t *)x, (const bf16_t *)w, y, (float *)ws, M, N, K, mode, ks, (hipStream_t)stream);
+  int rc = pl::launch_gemm((const bf16_t *)x, (const bf16_t *)w, y, (float *)ws, M, N, K, mode, ks, pl::gemm_cold((int64_t)N * K * 2), (hipStream_t)stream);
   if (rc == -1) return fail(PL_E_INVAL, "unsupported GEMM shape M=%d N=%d K=%d mode=%d", M, N, K, mode);
   if (rc) return fail(PL_E_HIP, "GEMM launch failed");
   return PL_OK;
@@ -1567,7 +1578,7 @@ int pl_debug_gemm_folded(const void *x, const void *w, void *y, int32_t M_max, i
   if (M_max < 1 || M_max > 512 || M < 1 || M > pl::GEMM_MAX_ROWS || N < 32 || K < 256 || (mode != 0 && mode != 1))
     return fail(PL_E_INVAL, "unsupported GEMM shape");
   int rc = pl::launch_gemm_folded((const bf16_t *)x, (const bf16_t *)w, y, M, N, K, mode, pl::gemm_pick_split(M_max, N, K, mode),
-                                  (hipStream_t)stream);
+                                  pl::gemm_cold((int64_t)N * K * 2), (hipStream_t)stream);
   if (rc == -1) return fail(PL_E_INVAL, "unsupported GEMM shape M=%d N=%d K=%d mode=%d", M, N, K, mode);
   if (rc) return fail(PL_E_HIP, "GEMM launch failed");
   return PL_OK;

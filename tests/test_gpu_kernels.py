@@ -151,6 +151,37 @@ def test_attention_of_a_sequence_does_not_depend_on_its_neighbours():
     assert not np.array_equal(out_a[0], out_b[0])        # the other rows did change
 
 
+@pytest.mark.parametrize("n,Hq,Hkv,hd,page,max_ctx", [
+    (5, 28, 4, 128, 128, 900),       # no list, chunks merged by a launch of their own
+    (300, 40, 8, 128, 32, 300),      # no list, one chunk per row
+    (212, 28, 4, 128, 64, 480),      # list, chunks of 128 merged by the last workgroup
+    (3, 28, 4, 128, 64, 24000)])     # list, more chunks than one workgroup merges
+def test_attention_on_every_route_of_a_launch(n, Hq, Hkv, hd, page, max_ctx):
+    """With and without a work list, chunks merged by the last workgroup of a row or by the merge launch: sampled rows
+    (the longest, one chunk and a little, an empty one) against the oracle, twice over the same workspace (what
+    one call leaves there must not disturb the next)."""
+    rng = np.random.default_rng(n + max_ctx)
+    ctx = rng.integers(1, max_ctx + 1, n).astype(np.int32)
+    ctx[0], ctx[1], ctx[2] = max_ctx, 129, 0
+    rows = [0, 1] + ([n - 1] if n > 3 else [])
+    pool, table, pps, known = _paged_inputs(rng, np.maximum(ctx, 1), Hq, Hkv, hd, page, rows)
+    qs = [synth.bf16_round(rng.standard_normal((n, Hq, hd)).astype(np.float32)) for _ in range(2)]
+    ws = torch.full((pl.pl_attention_workspace_bytes(n, Hq, Hkv, hd, max_ctx) + 64,), 0xA5, device="cuda", dtype=torch.uint8)
+    tb, cl = torch.from_numpy(table).cuda(), torch.from_numpy(ctx).cuda()
+    for q in qs:
+        qd, out = dev_bf16(q), torch.zeros(n, Hq, hd, device="cuda", dtype=torch.bfloat16)
+        pl.pl_attention_decode(qd.data_ptr(), pool.data_ptr(), tb.data_ptr(), cl.data_ptr(), out.data_ptr(), ws.data_ptr() + 16,
+                               n, Hq, Hkv, hd, page, pps, max_ctx, 0)
+        torch.cuda.synchronize()
+        got = to_np(out)
+        assert np.isfinite(got).all() and np.all(got[2] == 0)
+        for b in rows:
+            K, V = known[b]
+            ref = decoder.attend_one(q[b].astype(np.float64), K.astype(np.float64), V.astype(np.float64))
+            ok, err = close(got[b], ref, ATOL, RTOL)
+            assert ok, (b, int(ctx[b]), err)
+
+
 def test_attention_rejects_bad_arguments():
     t = torch.zeros(1 << 16, device="cuda", dtype=torch.bfloat16)
     p = t.data_ptr()
