@@ -576,7 +576,7 @@ def attention_microbench(args):
                       "dtype": "bf16", "data": "synthetic",
                       "config": {"workload": "decode-attention microbenchmark: batch 512, 28 q / 4 kv heads, head_dim 128, "
                                              "contexts lognormal(4096) in [128, 16384], 128-token pages", "mean_context": float(ctx.mean())},
-                      "roofline": {"bound": "hbm", "kernel": "attn_worklist_kernel + attn_decode_kernel + attn_combine_kernel",
+                      "roofline": {"bound": "hbm", "kernel": "attn_worklist_kernel + attn_decode_kernel",
                                    "achieved": nbytes / (ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                    "frac": nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": None, "bytes_per_launch": nbytes},
                       "cpu_baseline": {"value": toks * Hkv * hd * 4 / t_cpu / 1e9, "unit": "GB/s", "cores": 1, "kind": "oracle",
