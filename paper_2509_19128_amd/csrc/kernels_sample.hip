@@ -111,13 +111,19 @@ __device__ inline void finish_row(const SampleParams &p, int row, const Part &v)
 // computes that one exactly, the wavefront's largest exact value becomes the bar, and only entries whose
 // bound reaches the bar (about one in a thousand) are computed as well.  An entry below the bar cannot
 // win or tie: bound >= exact value entry by entry, rounding included (rounding is monotone).
-// 256 x 152064: 55 us (2.8 TB/s) against 82-93 us with every entry's noise evaluated and a branchy online sum;
+// The sum of exponentials does not depend on NT, so a row's log-prob does not depend on how many rows share the
+// call: all exponentials are relative to the slice's maximum, and they are added up as SUM_LANES threads of
+// SUM_LANES / 64 wavefronts would, whatever number of these a thread takes over (1.6 us of the next line's 52).
+// 256 x 152064, whole call: 52 us (3.0 TB/s) against 82-93 us with every entry's noise evaluated and a branchy online sum;
 // 4 x 4096: 5 us against 8.6.  One 64-bit multiply-add per product (v_mad_u64_u32) is slower than the
 // high/low pair (73 against 61 us before the reductions below), four wavefronts per SIMD spill (69), 16 entries
 // per thread cost 63.
+constexpr int SUM_LANES = 1024;
 template <int NT>
 __global__ __launch_bounds__(NT) void sample_slice_kernel(SampleParams p, int nslice) {
   constexpr int Q = SLICE / NT / 4;   // groups of four entries per thread
+  constexpr int V = SUM_LANES / NT;   // lanes of the sum per thread: lane threadIdx.x + v * NT has groups v, v + V, ...
+  constexpr int NW = NT / 64;
   const int row = blockIdx.y, sl = blockIdx.x;
   const float *lg = p.logits + (int64_t)row * p.vocab;
   const float inv_t = p.inv_t[row];
@@ -151,7 +157,12 @@ __global__ __launch_bounds__(NT) void sample_slice_kernel(SampleParams p, int ns
       if (ub > first) { first = ub; fi = i4 * 4 + e; best_bits = rnd[q][e]; best_z = z[q][e]; }
     }
   }
-  float by = -INFINITY, sum = 0.f;
+  __shared__ float s_max[NW], s_besty[NW], s_sum[SUM_LANES / 64];
+  __shared__ int s_besti[NW];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  mx = wave_max(mx);
+  if (lane == 0) s_max[wave] = mx;
+  float by = -INFINITY;
   int bi = 0x7FFFFFFF;
   if (fi >= 0) merge_best(by, bi, __fadd_rn(best_z, gumbel(best_bits)), fi);
   const float bar = wave_max(by);
@@ -165,16 +176,31 @@ __global__ __launch_bounds__(NT) void sample_slice_kernel(SampleParams p, int ns
           merge_best(by, bi, __fadd_rn(z[q][e], gumbel(rnd[q][e])), i4 * 4 + e);
     }
   }
+  const float besty = wave_max(by);
+  const int besti = wave_min(by == besty ? bi : 0x7FFFFFFF);
+  __syncthreads();
+  mx = s_max[0];
 #pragma unroll
-  for (int q = 0; q < Q; ++q)
+  for (int w = 1; w < NW; ++w) mx = fmaxf(mx, s_max[w]);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) sum += __expf(z[q][e] - mx);   // (entries beyond the slice: exp(-inf) = 0; mx = -inf: unused)
-  Part v = merge_wave(Part{mx, sum, by, bi});
-  __shared__ Part sm[NT / 64];
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
+  for (int v = 0; v < V; ++v) {
+    float sum = 0.f;
+#pragma unroll
+    for (int q = v; q < Q; q += V)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum += __expf(z[q][e] - mx);   // (entries beyond the slice: exp(-inf) = 0; mx = -inf: unused)
+    sum = wave_sum(sum);
+    if (lane == 0) s_sum[v * NW + wave] = sum;
+  }
+  if (lane == 0) { s_besty[wave] = besty; s_besti[wave] = besti; }
   __syncthreads();
   if (threadIdx.x >= 64) return;
-  v = merge_wave(threadIdx.x < NT / 64 ? sm[threadIdx.x] : NO_PART);
+  Part v;
+  v.mx = mx;
+  v.sum = wave_sum(lane < SUM_LANES / 64 ? s_sum[lane] : 0.f);
+  by = lane < NW ? s_besty[lane] : -INFINITY;
+  v.besty = wave_max(by);
+  v.besti = wave_min(lane < NW && by == v.besty ? s_besti[lane] : 0x7FFFFFFF);
   if (threadIdx.x != 0) return;
   if (nslice == 1) finish_row(p, row, v);   // the whole vocabulary: nothing to merge
   else ((Part *)p.workspace)[(int64_t)row * nslice + sl] = v;

@@ -440,6 +440,23 @@ def test_sampler_at_slice_and_launch_boundaries_with_masked_entries(n, V):
         assert abs(lp[r] - lp_ref) <= 1e-4 * max(1.0, abs(lp_ref))
 
 
+@pytest.mark.parametrize("few,many,V", [(26, 27, 152064), (511, 512, 4096), (127, 128, 32000), (3, 300, 8200)])
+def test_a_row_is_sampled_alike_whatever_rows_share_the_call(few, many, V):
+    """Both sides of the choice of threads per slice: the same rows' tokens and log-probs are bit-identical."""
+    rng = np.random.default_rng(V + few)
+    logits = (rng.standard_normal((many, V)) * 3).astype(np.float32)
+    logits[0, : V // 2] = -np.inf
+    seq_id = rng.integers(0, 2**63, size=many, dtype=np.uint64)
+    pos = rng.integers(0, 16384, size=many).astype(np.int32)
+    temps = rng.choice([1.0, 0.7, 1.5], many).astype(np.float32)
+    forced = np.full(many, -1, np.int32)
+    forced[::2] = rng.integers(V // 2, V, len(forced[::2]))
+    a = _gpu_sample(logits[:few], seq_id[:few], pos[:few], temps[:few], forced[:few], 77)
+    b = _gpu_sample(logits, seq_id, pos, temps, forced, 77)
+    assert np.array_equal(a[0], b[0][:few])
+    assert np.array_equal(a[1].view(np.uint32), b[1][:few].view(np.uint32))
+
+
 def test_sampler_ties_resolve_to_the_lowest_index_like_the_oracle():
     """Constant logits: the winner is decided by the noise alone, and with 2^23 distinct uniforms over
     152064 entries equal maxima do occur; both sides must pick the lowest index."""
