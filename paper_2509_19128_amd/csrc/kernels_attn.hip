@@ -16,6 +16,8 @@
 #include "attn_worklist.h"
 #include "pl_common.h"
 
+#include <type_traits>
+
 #ifndef PL_ATTN_NS
 #define PL_ATTN_NS 2   // register stages of K/V runs per wavefront
 #endif
@@ -506,7 +508,7 @@ __global__ __launch_bounds__(HD) void attn_merge_kernel(AttnParams p) {
 // are the heads of 16 / G rows, and every K/V operand serves CB such column blocks, where one row per workgroup
 // (as in a decode step) reads the sequence once per row.  Operation by operation the same sums as the decode kernel
 // for every row: runs, subs, wavefronts and chunks in the same order; a run that lies beyond a row's positions
-// leaves its column as it was (weights 0, factor 1).
+// leaves its column as it was (factor 1, product not taken: 0 times an infinity would not be 0).
 // Bound by vector arithmetic (about 100 operations per run and column block), then by L2.  3001-token prompt, 1.5B
 // shape: 960 -> 375 us over the twelve launches of its passes; 512-token prompt, 7B shape: 79 -> 57 us.
 template <int HD, int CB>
@@ -603,7 +605,8 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnParams p) {
         m_all[cb] = Mx;
       }
     };
-    for (int blk = wave; blk < nblk; blk += 4) {
+    // ENDED: rows of the group end before this run and have no part in it, whatever its values are
+    auto take_run = [&](auto ENDED, int blk) {
       asm volatile("" ::: "memory");   // the queries stay in LDS: read anew for every run
       f32x4 s4[CB][2];
 #pragma unroll
@@ -650,7 +653,10 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnParams p) {
           for (int i = 0; i < NV; ++i) o[cb][i] *= alpha;
         }
 #pragma unroll
-        for (int i = 0; i < NV; ++i) o[cb][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i], pf, o[cb][i], 0, 0, 0);
+        for (int i = 0; i < NV; ++i) {
+          const f32x4 r = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i], pf, o[cb][i], 0, 0, 0);
+          if (!decltype(ENDED)::value || t0 + blk * 32 < ctx[cb]) o[cb][i] = r;
+        }
       }
       load_v(nb);
       if ((blk & (SUB_RUNS - 1)) + 4 >= SUB_RUNS && blk + 4 < nblk) {   // end of a sub
@@ -658,7 +664,10 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnParams p) {
         folded = true;
         reset();
       }
-    }
+    };
+    int blk = wave;
+    for (; blk < nblk && t0 + blk * 32 < ctx0; blk += 4) take_run(std::false_type{}, blk);
+    for (; blk < nblk; blk += 4) take_run(std::true_type{}, blk);
     fold_sub();
     if (qg == 0) {
 #pragma unroll

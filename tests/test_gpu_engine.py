@@ -470,6 +470,33 @@ def test_decode_steps_rotate_and_append_like_the_passes(Hq, Hkv, hd, d):
         e.close()
 
 
+@pytest.mark.parametrize("Hq,Hkv,hd,first,bad", [(12, 4, 64, 0, 35), (4, 4, 64, 5, 34), (8, 1, 32, 2, 33), (16, 1, 128, 1, 32), (12, 4, 64, 3, 130)])
+def test_a_non_finite_position_does_not_reach_rows_that_end_before_its_run(Hq, Hkv, hd, first, bad):
+    """Rows of a pass that one attention workgroup takes together, across the end of a 32-token run: a token whose keys
+    and values are not finite changes nothing for the positions before its run (the embedding of token 7 is infinite)."""
+    m = synth.ModelCfg(2, 256, Hq, Hkv, hd, 256, 512)
+    w = synth.make_weights(m, seed=9)
+    w["embed"][7] = np.inf
+    prompt = 8 + np.random.default_rng(bad).integers(0, 500, 300).astype(np.int32)
+    kv = []
+    for token in (9, 7):
+        prompt[bad] = token
+        eng = pl.Engine.from_model(m, max_batch=2, max_context=512, kv_pool_tokens=512, kv_page_tokens=64, seed=3, device=0)
+        eng.load_weights(eng.pack_weights(w, synth.f32_to_bf16_bits))
+        eng.add_sequence(1, prompt, 4)
+        for _ in range(first):
+            eng.decode_step()
+        assert eng.prefill(0) == 299 - first
+        kv.append([eng.debug_read_kv(0, l, 299) for l in range(m.n_layers)])
+        eng.close()
+    run = bad // 32 * 32
+    for l in range(m.n_layers):
+        for part in range(2):
+            assert np.isfinite(kv[0][l][part]).all()
+            assert np.array_equal(kv[0][l][part][:run], kv[1][l][part][:run]), (l, part)
+    assert not np.isfinite(kv[1][1][1][bad:]).any()
+
+
 def test_a_sequence_alone_equals_the_same_among_many(weights):
     """An engine of 512 slots has attention chunks of 2048 tokens here.  A step of few sequences cuts them into
     smaller work items, a step of many does not: the same sequences' logits are bit-identical, at contexts around
