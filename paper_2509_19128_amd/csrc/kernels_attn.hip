@@ -16,6 +16,7 @@
 #include "attn_worklist.h"
 #include "pl_common.h"
 
+#include <algorithm>
 #include <type_traits>
 
 #ifndef PL_ATTN_NS
@@ -795,6 +796,15 @@ int launch_attention(const AttnParams &p, hipStream_t s, int part) {
 // Rows of a group of attn_rows_kernel: CB column blocks of 16 / G rows.
 constexpr int ATTN_ROWS_CB = 2;
 int attention_rows_per_group(int Hq, int Hkv) { return ATTN_ROWS_CB * (16 / (Hq / Hkv)); }
+
+// Most rows of a pass that attend one by one in the decode kernel, which takes the chunks of a row side by side,
+// instead of in groups that walk the whole context (2.2 us per 128 tokens, whatever the number of groups while they all
+// run at once).  One by one the time grows with the bytes of all rows together.  GPU time of a pass of four layers
+// of the 1.5B (256 elements of k per position), 7B (512) and of two of the 32B (1024) shape, one by one against in groups:
+// 4 rows at position 8000 209 / 568, 521 / 646, 261 / 309 us; 192, 96 and 48 rows there 624 / 642, 919 / 856, 403 / 380.  With 64
+// elements of k per position what a workgroup costs decides: 128 rows at 300 and at 8000 208 / 202, 316 / 435; 256 rows
+// 168 / 156, 353 / 390; 512 rows 184 / 152, 525 / 385.
+int attention_apart_rows(int Hkv, int hd) { return std::min(128, 32768 / (Hkv * hd)); }
 
 int launch_attention_rows(const AttnParams &p, hipStream_t s) {
   if (p.n_seq <= 0) return 0;

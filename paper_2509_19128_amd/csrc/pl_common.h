@@ -104,6 +104,7 @@ bool attention_tickets(int max_chunks);
 bool attention_rotates(int items, int Hq, int Hkv, int hd, int splits);
 int launch_attention_rows(const AttnParams &p, hipStream_t s);
 int attention_rows_per_group(int Hq, int Hkv);
+int attention_apart_rows(int Hkv, int hd);
 int64_t attention_worklist_ints(int64_t max_items);
 bool attention_split(int chunk, int64_t total_tokens, int64_t longest_item, int64_t n_subs, int Hkv);
 int launch_attention_worklist(const AttnParams &p, int cap, hipStream_t s);

@@ -113,6 +113,8 @@ struct pl_engine {
     int attn_items = 0;   // bound on this pass's attention work items
     bool attn_split = false;   // this step's attention items are single subs
     bool attn_merge = false;   // rows of this step span several items and take the merge launch
+    int apart_cap = 0;         // rows the list and the partial results of the decode attention are sized for
+    bool attn_apart = false;   // the rows of this pass attend one by one, as a decode step's do
     // the 8-byte ids come first, so every array is aligned for its type whatever rows_cap is
     uint64_t *m_seq_id(bool dev) { return (uint64_t *)(dev ? meta_d : meta_h); }
     int32_t *m_row_slot(bool dev) { return (int32_t *)(m_seq_id(dev) + rows_cap); }
@@ -161,7 +163,7 @@ struct pl_engine {
   // attention kernels; everything that changes from step to step is read from device buffers.
   struct StepGraph {
     int n = 0, buf = 0, items = 0, set = 0;   // set: 0 decode step, 1 cache-only pass
-    bool split = false, merge = false;
+    bool split = false, merge = false, apart = false;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     uint64_t last_use = 0;
@@ -271,20 +273,20 @@ int alloc_work(pl_engine *e, pl_engine::Work &w, int64_t R, int64_t parts_elems,
   if ((rc = dev_alloc(&w.cs, R * c.head_dim))) return rc;
   if ((rc = dev_alloc(&w.ctx_len, R))) return rc;
   if ((rc = dev_alloc(&w.pt, (int64_t)c.max_batch * e->pages_per_seq))) return rc;
-  if (decode) {   // a pass's attention needs no list and no partial results
-    const int64_t split = e->attn_chunk > pl::ATTN_SUB ? pl::ATTN_SPLIT_PARTS : 0;   // (sub, kv head) pairs
-    const int64_t np = std::max<int64_t>(R * c.n_kv_heads * e->attn_max_chunks, 4 * split);
-    const int64_t po = np * e->G * c.head_dim;   // a multiple of a cache line (32 floats)
-    if ((rc = dev_alloc(&w.attn_po, po + np * pl::ATTN_ML))) return rc;
-    w.attn_pml = w.attn_po + po;
-    w.items_cap = std::max<int64_t>(R * e->attn_max_chunks, split);
-    const int64_t work = pl::attention_worklist_ints(w.items_cap);
-    if ((rc = dev_alloc(&w.attn_work, work + R * c.n_kv_heads + R))) return rc;
-    w.attn_tickets = w.attn_work + work;
-    w.attn_first = w.attn_tickets + R * c.n_kv_heads;
-  } else {
-    w.items_cap = R;
-  }
+  // Lists and partial results of the decode attention: for every row of a step, and for the passes of few rows that
+  // take it (the fp32 build has none, the other passes need none).
+  w.apart_cap = decode ? (int)R : e->f32 ? 0 : (int)std::min<int64_t>(R, pl::attention_apart_rows(c.n_kv_heads, c.head_dim));
+  const int64_t split = decode && e->attn_chunk > pl::ATTN_SUB ? pl::ATTN_SPLIT_PARTS : 0;   // (sub, kv head) pairs
+  const int64_t np = std::max<int64_t>((int64_t)w.apart_cap * c.n_kv_heads * e->attn_max_chunks, 4 * split);
+  const int64_t po = np * e->G * c.head_dim;   // a multiple of a cache line (32 floats)
+  if ((rc = dev_alloc(&w.attn_po, po + np * pl::ATTN_ML))) return rc;
+  w.attn_pml = w.attn_po + po;
+  w.items_cap = std::max<int64_t>((int64_t)w.apart_cap * e->attn_max_chunks, split);
+  const int64_t work = pl::attention_worklist_ints(w.items_cap);
+  if ((rc = dev_alloc(&w.attn_work, work + w.apart_cap * (int64_t)(c.n_kv_heads + 1)))) return rc;
+  w.attn_tickets = w.attn_work + work;
+  w.attn_first = w.attn_tickets + w.apart_cap * (int64_t)c.n_kv_heads;
+  if (!decode) w.items_cap = std::max<int64_t>(w.items_cap, R);   // groups of rows are counted there as well
   if (decode) HIP_TRY(hipHostMalloc((void **)&w.meta_h, (size_t)w.image_bytes(), hipHostMallocDefault));
   return PL_OK;
 }
@@ -481,7 +483,8 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   ap.n_seq = n; ap.Hq = c.n_q_heads; ap.Hkv = c.n_kv_heads; ap.hd = c.head_dim;
   ap.page_tokens = e->page_tokens; ap.pages_per_seq = e->pages_per_seq; ap.chunk = e->attn_chunk;
   ap.max_chunks = e->attn_max_chunks; ap.item_tokens = w.attn_split ? pl::ATTN_SUB : e->attn_chunk;
-  ap.work = w.attn_work; ap.tickets = pl::attention_tickets(e->attn_max_chunks) ? w.attn_tickets : nullptr; ap.merge = w.attn_merge; ap.first_item = w.attn_first; ap.max_items = w.attn_items;
+  const bool rows_share = prefill && !w.attn_apart;
+  ap.work = rows_share ? nullptr : w.attn_work; ap.tickets = pl::attention_tickets(e->attn_max_chunks) ? w.attn_tickets : nullptr; ap.merge = w.attn_merge; ap.first_item = w.attn_first; ap.max_items = w.attn_items;
   if (prefill) ap.groups = w.m_pairs(true);
   // (the rows of a pass attend to one another: all their keys and values are appended first)
   const bool rotates = !prefill && pl::attention_rotates(w.attn_items, c.n_q_heads, c.n_kv_heads, c.head_dim, e->ks_qkv.splits);
@@ -507,7 +510,7 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
       ap.q = w.q_rot;
     }
     if (prefill && l + 1 == c.n_layers) break;
-    if (prefill) {
+    if (rows_share) {
       rc |= pl::launch_attention_rows(ap, s);
     } else if (timed && e->profile) {   // the timers bracket the decode kernel alone; the merge kernel counts as "other"
       mark(e, CAT_OTHER, true);
@@ -561,7 +564,7 @@ int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) {
   w.attn_items = (int)std::min<int64_t>((w.attn_items + 63) / 64 * 64, w.items_cap);
   pl_engine::StepGraph *g = nullptr;
   for (auto &x : e->graphs)
-    if (x.n == n && x.buf == e->active_buf && x.items == w.attn_items && x.split == w.attn_split && x.merge == w.attn_merge && x.set == set) { g = &x; break; }
+    if (x.n == n && x.buf == e->active_buf && x.items == w.attn_items && x.split == w.attn_split && x.merge == w.attn_merge && x.apart == w.attn_apart && x.set == set) { g = &x; break; }
   if (!g) {
     if (e->graphs.size() >= MAX_STEP_GRAPHS) {   // evict the least recently used
       size_t lru = 0;
@@ -571,7 +574,7 @@ int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) {
       e->graphs.erase(e->graphs.begin() + lru);
     }
     pl_engine::StepGraph ng;
-    ng.n = n; ng.buf = e->active_buf; ng.items = w.attn_items; ng.split = w.attn_split; ng.merge = w.attn_merge; ng.set = set;
+    ng.n = n; ng.buf = e->active_buf; ng.items = w.attn_items; ng.split = w.attn_split; ng.merge = w.attn_merge; ng.apart = w.attn_apart; ng.set = set;
     HIP_TRY(hipStreamBeginCapture(w.stream, hipStreamCaptureModeThreadLocal));
     const int rc = enqueue_step(e, w, n, prefill);
     const hipError_t ce = hipStreamEndCapture(w.stream, &ng.graph);
@@ -707,7 +710,7 @@ int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::ve
         harvest_passes(e);
       }
       w.meta_h = im.meta_h;
-      int items = 0;
+      int items = 0, chunks = 0;
       const int per_group = pl::attention_rows_per_group(c.n_q_heads, c.n_kv_heads);
       int32_t *row_slot = w.m_row_slot(false), *pos = w.m_pos(false), *inp = w.m_input(false), *frc = w.m_forced(false);
       int32_t *groups = w.m_pairs(false);
@@ -727,9 +730,12 @@ int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::ve
           groups[3 + 2 * items++] = 0;
         }
         ++groups[1 + 2 * items];
+        chunks += (pos[r] + e->attn_chunk) / e->attn_chunk;
       }
       groups[0] = items;
-      w.attn_items = items;
+      w.attn_apart = n <= w.apart_cap;
+      w.attn_items = w.attn_apart ? chunks : items;
+      w.attn_merge = w.attn_apart && chunks > n && !pl::attention_tickets(e->attn_max_chunks);
       hipStream_t s = w.stream;
       // The page table goes up on this stream into this set's own device copy (no device buffer is ever
       // written from two streams); the rows of the slots being read do not change while they are read.

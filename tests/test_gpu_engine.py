@@ -524,6 +524,60 @@ def test_a_sequence_alone_equals_the_same_among_many(weights):
         assert np.array_equal(few[1], many[1]) and np.array_equal(few[2], many[2])
 
 
+def _random_pool(eng):
+    ptr, nbytes = eng.debug_kv_pool()
+    torch.as_tensor(_Device(ptr, nbytes // 2), device="cuda").view(torch.bfloat16).normal_(0, 1, generator=torch.Generator(device="cuda").manual_seed(3))
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("max_batch,max_context,context,rows", [(4, 8192, 5000, 128), (4, 8192, 5000, 129), (4, 4096, 3000, 40),
+                                                                (4, 8192, 0, 100), (512, 4096, 2040, 30), (4, 8192, 7000, 1)])
+def test_passes_of_few_rows_leave_the_cache_of_reading_token_by_token(weights, max_batch, max_context, context, rows):
+    """Rows that attend one by one (up to 128 here) and in groups; their chunks merged by the last workgroup (up to 32 of
+    128 tokens), by a launch of their own, or of 2048 tokens: bit-identical caches and logits to the steps."""
+    master, _ = weights
+    prompt = synth.random_prompts(np.random.default_rng(rows), 1, context + rows + 1, M.vocab)[0]
+    caches, logits = [], []
+    for batched in (True, False):
+        eng = _engine(max_batch, max_context=max_context, kv_pool_tokens=2 * max_context, kv_page_tokens=128)
+        eng.load_weights(eng.pack_weights(master, synth.f32_to_bf16_bits))
+        _random_pool(eng)
+        assert eng.debug_add_sequence_at(7, prompt, len(prompt), 6, 1.0, context, 0, 5) == 0
+        if batched:
+            assert eng.prefill(0) == rows
+        else:
+            for _ in range(rows):
+                eng.decode_step()
+        caches.append(_kv_of(eng, 0, context + rows))
+        eng.decode_step(np.full(max_batch, 3, np.int32))
+        logits.append(eng.debug_get_logits(1))
+        eng.close()
+    for l in range(M.n_layers):
+        for part in range(2):
+            assert np.array_equal(caches[0][l][part], caches[1][l][part]), (l, part)
+    assert np.isfinite(logits[0]).all() and np.array_equal(logits[0], logits[1])
+
+
+def test_a_few_rows_late_in_a_long_prompt_do_not_walk_it_one_chunk_after_the_other(weights):
+    """Four rows at position 12000 take about as long as at position 700 (their chunks run side by side); walked by
+    one workgroup they took four times as long.  Best of several runs, with room for noise."""
+    master, _ = weights
+    eng = _engine(4, max_context=12800, kv_pool_tokens=2 * 12800, kv_page_tokens=128)
+    eng.load_weights(eng.pack_weights(master, synth.f32_to_bf16_bits))
+    best = []
+    for context in (700, 12000):
+        ms = []
+        for i in range(8):
+            slot = eng.debug_add_sequence_at(i, np.full(context + 5, 3, np.int32), context + 5, 4, 1.0, context, 0, 5)
+            before = eng.stats()["prefill_ms"]
+            assert eng.prefill(slot) == 4
+            ms.append(eng.stats()["prefill_ms"] - before)
+            eng.retire_sequence(slot)
+        best.append(min(ms))
+    eng.close()
+    assert best[1] < 2 * best[0], best
+
+
 class _Device:
     """A device buffer that the library owns, for torch.as_tensor."""
 
