@@ -30,6 +30,7 @@ namespace pl {
 namespace {
 
 constexpr int SUB_RUNS = ATTN_SUB / 32;
+typedef __attribute__((address_space(4))) int32_t scalar_i32;   // read by scalar loads
 
 __device__ inline float shfl_xor(float v, int mask) { return __shfl_xor(v, mask, 64); }
 
@@ -137,7 +138,10 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;   // uniform: page ids by scalar loads
   const int head = l & 15, qg = l >> 4;
   const int G = p.Hq / p.Hkv;
-  const int32_t *pt = p.page_table + (int64_t)slot * p.pages_per_seq;
+  // The launch does not write the page table: reads through the constant address space stay scalar loads.  As ordinary
+  // reads behind the stores of k and v (ROTATE) they became vector loads, each of which waited for every K/V load in
+  // flight, from the fifth page of an item on (7B shape, 34 sequences of 6000 tokens: 16 us per launch).
+  const scalar_i32 *pt = (const scalar_i32 *)(p.page_table + (int64_t)slot * p.pages_per_seq);
   const int page_first = t0 / p.page_tokens;   // r1 holds the ids of pages page_first .. page_first + 3
   const float scale = 1.4426950408889634f / sqrtf((float)HD);   // log2(e) / sqrt(hd)
   const int64_t page_elems = (int64_t)2 * p.page_tokens * HD;   // K block + V block of one kv head
