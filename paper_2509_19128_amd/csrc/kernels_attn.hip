@@ -100,7 +100,7 @@ __device__ inline void merge_chunks(const AttnParams &p, int b, int g, int nchun
 // ROTATE: q, k and v of the step come as the QKV product's slices of partial sums; the workgroup adds them up and
 // rotates its group's heads, and the item that holds the step's own position also appends k and v to the cache
 // and patches them into the run it has loaded.  Saves a launch per layer, but the rotation is a dependent round
-// trip ahead of the first scores: worth it while all workgroups run at once (attention_rotates).
+// trip ahead of the first scores: worth it in launches of few workgroups (attention_rotates).
 template <int HD, int NS, bool ROTATE>
 __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
   constexpr int NJ = HD / 32;   // QK MFMAs per 16-token tile
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
   const int G = p.Hq / p.Hkv;
   // The launch does not write the page table: reads through the constant address space stay scalar loads.  As ordinary
   // reads behind the stores of k and v (ROTATE) they became vector loads, each of which waited for every K/V load in
-  // flight, from the fifth page of an item on (7B shape, 34 sequences of 6000 tokens: 16 us per launch).
+  // flight, from the fifth page of an item on (7B shape, 34 sequences of 6000 tokens: 13 us per launch).
   const scalar_i32 *pt = (const scalar_i32 *)(p.page_table + (int64_t)slot * p.pages_per_seq);
   const int page_first = t0 / p.page_tokens;   // r1 holds the ids of pages page_first .. page_first + 3
   const float scale = 1.4426950408889634f / sqrtf((float)HD);   // log2(e) / sqrt(hd)
@@ -754,12 +754,18 @@ bool attention_split(int chunk, int64_t total_tokens, int64_t longest_item, int6
 // merge launch, which has a workgroup per head; up to 17 (1.5B shape, 64 rows) the same or better.
 bool attention_tickets(int max_chunks) { return max_chunks <= 32; }
 
-// Whether a step's attention rotates and appends by itself: while its workgroups run all at once (two per compute
-// unit, three at half the head dimension) it saves the launch (1.5B shape, 64 rows: 26.5 + 5.1 us and a gap -> 27.6; 7B, 19
-// rows: 34.5 + 5.0 -> 36.2), in later rounds every workgroup pays the round trip (7B, 256 rows: 265 + 8.9 -> 289).
+// Whether a step's attention rotates and appends by itself, for `items` work items over `tokens` positions.  It saves the
+// launch (3 us per layer where nothing else changes), but every workgroup begins with a round trip to the slices: in workgroups
+// that start later, and the more the longer the memory system is saturated, that costs more.  Microseconds per layer won by
+// rotating inside (a step's time with it and without):
+//   bytes: 7B shape, 192 workgroups of 6000 tokens +2.5, 256 -1.7; 384 of 3000 +0.1, 416 -1.4; 768 of 1300 +0.6, of 1600 -0.6;
+//     32B shape, 384 of 2000 +1.4, 512 -2.3; head dimension 64, 448 of 6000 +1.2, 512 -1.1: 400 to 600 MB of keys and values.
+//   workgroups: 7B (four slices) 768 of 800 tokens +2.3; 1.5B (six slices), 512-token chunks, 768 +1.3; head dimension 64, 768 of
+//     800 +1.1, 1024 -1.2; 32B (seven slices) 512 of 500 +3.2, 768 -2.9.
 // Slices and rotated quads have to fit the registers and threads of one workgroup.
-bool attention_rotates(int items, int Hq, int Hkv, int hd, int splits) {
-  return items * Hkv <= 768 && splits <= ATTN_ROTATE_SLICES && (Hq / Hkv + 2) * (hd / 8) <= 256;
+bool attention_rotates(int items, int64_t tokens, int Hq, int Hkv, int hd, int splits) {
+  return items * Hkv <= (splits <= 6 ? 768 : 512) && tokens * Hkv * hd * 4 <= (int64_t)448 << 20 && splits <= ATTN_ROTATE_SLICES &&
+         (Hq / Hkv + 2) * (hd / 8) <= 256;
 }
 
 // ints of the work buffer (which must be 32-byte aligned): a header of 8, one 8-int record per item

@@ -101,7 +101,7 @@ struct AttnParams {
 };
 int launch_attention(const AttnParams &p, hipStream_t s, int part = 0);
 bool attention_tickets(int max_chunks);
-bool attention_rotates(int items, int Hq, int Hkv, int hd, int splits);
+bool attention_rotates(int items, int64_t tokens, int Hq, int Hkv, int hd, int splits);
 int launch_attention_rows(const AttnParams &p, hipStream_t s);
 int attention_rows_per_group(int Hq, int Hkv);
 int attention_apart_rows(int Hkv, int hd);

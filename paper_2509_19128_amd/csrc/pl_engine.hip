@@ -113,6 +113,7 @@ struct pl_engine {
     int attn_items = 0;   // bound on this pass's attention work items
     bool attn_split = false;   // this step's attention items are single subs
     bool attn_merge = false;   // rows of this step span several items and take the merge launch
+    bool attn_rotate = false;  // this step's attention rotates and appends by itself
     int apart_cap = 0;         // rows the list and the partial results of the decode attention are sized for
     bool attn_apart = false;   // the rows of this pass attend one by one, as a decode step's do
     // the 8-byte ids come first, so every array is aligned for its type whatever rows_cap is
@@ -163,7 +164,7 @@ struct pl_engine {
   // attention kernels; everything that changes from step to step is read from device buffers.
   struct StepGraph {
     int n = 0, buf = 0, items = 0, set = 0;   // set: 0 decode step, 1 cache-only pass
-    bool split = false, merge = false, apart = false;
+    bool split = false, merge = false, apart = false, rotate = false;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     uint64_t last_use = 0;
@@ -487,7 +488,7 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   ap.work = rows_share ? nullptr : w.attn_work; ap.tickets = pl::attention_tickets(e->attn_max_chunks) ? w.attn_tickets : nullptr; ap.merge = w.attn_merge; ap.first_item = w.attn_first; ap.max_items = w.attn_items;
   if (prefill) ap.groups = w.m_pairs(true);
   // (the rows of a pass attend to one another: all their keys and values are appended first)
-  const bool rotates = !prefill && pl::attention_rotates(w.attn_items, c.n_q_heads, c.n_kv_heads, c.head_dim, e->ks_qkv.splits);
+  const bool rotates = !prefill && w.attn_rotate;
   pl::StepBegin sb{};
   sb.src = w.meta(prefill);   // a pass's metadata is on the device already, a decode step's is fetched from the host's image
   if (!prefill) { sb.dst = w.meta(true); sb.updates = w.m_pairs(false); }
@@ -564,7 +565,8 @@ int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) {
   w.attn_items = (int)std::min<int64_t>((w.attn_items + 63) / 64 * 64, w.items_cap);
   pl_engine::StepGraph *g = nullptr;
   for (auto &x : e->graphs)
-    if (x.n == n && x.buf == e->active_buf && x.items == w.attn_items && x.split == w.attn_split && x.merge == w.attn_merge && x.apart == w.attn_apart && x.set == set) { g = &x; break; }
+    if (x.n == n && x.buf == e->active_buf && x.items == w.attn_items && x.split == w.attn_split && x.merge == w.attn_merge && x.apart == w.attn_apart &&
+        x.rotate == w.attn_rotate && x.set == set) { g = &x; break; }
   if (!g) {
     if (e->graphs.size() >= MAX_STEP_GRAPHS) {   // evict the least recently used
       size_t lru = 0;
@@ -574,7 +576,7 @@ int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) {
       e->graphs.erase(e->graphs.begin() + lru);
     }
     pl_engine::StepGraph ng;
-    ng.n = n; ng.buf = e->active_buf; ng.items = w.attn_items; ng.split = w.attn_split; ng.merge = w.attn_merge; ng.apart = w.attn_apart; ng.set = set;
+    ng.n = n; ng.buf = e->active_buf; ng.items = w.attn_items; ng.split = w.attn_split; ng.merge = w.attn_merge; ng.apart = w.attn_apart; ng.rotate = w.attn_rotate; ng.set = set;
     HIP_TRY(hipStreamBeginCapture(w.stream, hipStreamCaptureModeThreadLocal));
     const int rc = enqueue_step(e, w, n, prefill);
     const hipError_t ce = hipStreamEndCapture(w.stream, &ng.graph);
@@ -1218,6 +1220,8 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
   w.attn_split = pl::attention_split(e->attn_chunk, (int64_t)kv_tokens + r, longest, subs, c.n_kv_heads);
   w.attn_items = w.attn_split ? subs : items;
   w.attn_merge = w.attn_split || (items > r && !pl::attention_tickets(e->attn_max_chunks));
+  // (decided by the step itself, not by a grid bound: replayed and launched one by one it takes the same route)
+  w.attn_rotate = pl::attention_rotates(w.attn_items, (int64_t)kv_tokens + r, c.n_q_heads, c.n_kv_heads, c.head_dim, e->ks_qkv.splits);
 
   // 4. run
   if (!e->dry) {

@@ -1,0 +1,171 @@
+// The engine's host code on a stand-in for the HIP runtime: memory is host memory, streams run in order at once, graphs
+// record and replay, and kernel launches are noted by name.  Of the kernels only what the tests look at happens: the
+// kernel that begins a step applies the page-table changes.  A runtime call can be made to fail, and device memory to be
+// scarce.  Linked with the library's own objects instead of the HIP runtime; built and run by tests/test_host_device.py.
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <map>
+#include <string>
+#include <vector>
+
+#include "../../include/pl.h"
+#include "../../paper_2509_19128_amd/csrc/pl_common.h"
+
+#define CHECK(cond)                                                                                   \
+  do {                                                                                                \
+    if (!(cond)) {                                                                                    \
+      fprintf(stderr, "check failed at line %d: %s (%s)\n", __LINE__, #cond, pl_last_error());        \
+      exit(1);                                                                                        \
+    }                                                                                                 \
+  } while (0)
+
+// ---- the runtime ---------------------------------------------------------------------------------------
+namespace {
+struct Launch {
+  std::string kernel;
+  dim3 grid;
+  pl::StepBegin begin;
+  pl::AttnParams attn;
+};
+std::map<const void *, std::string> names;
+std::map<void *, size_t> device_memory;
+size_t device_used = 0, device_high = 0, device_limit = ~(size_t)0;
+int host_allocations = 0, fail_event_record = 0;   // fail_event_record: the how-manieth hipEventRecord from now fails
+bool capturing = false;
+std::vector<Launch> done, captured;
+dim3 call_grid, call_block;
+
+void run(const Launch &l) {
+  done.push_back(l);
+  if (l.kernel.find("step_begin_kernel") != std::string::npos && l.begin.updates && l.attn.work)
+    for (int i = 0; i < l.begin.updates[0]; ++i) l.begin.page_table[l.begin.updates[2 + 2 * i]] = l.begin.updates[3 + 2 * i];
+}
+}  // namespace
+
+extern "C" {
+void **__hipRegisterFatBinary(const void *) { static void *m; return &m; }
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterFunction(void **, const void *host, char *, const char *name, unsigned, void *, void *, void *, void *, int *) { names[host] = name; }
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, hipStream_t) { call_grid = grid; call_block = block; return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *shared, hipStream_t *s) {
+  *grid = call_grid; *block = call_block; *shared = 0; *s = nullptr;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, hipStream_t) {
+  Launch l{names[f], grid, {}, {}};
+  if (l.kernel.find("step_begin_kernel") != std::string::npos) {
+    l.begin = *(const pl::StepBegin *)args[0];
+    l.attn = *(const pl::AttnParams *)args[1];
+  } else if (l.kernel.find("attn_") != std::string::npos) {
+    l.attn = *(const pl::AttnParams *)args[0];
+  }
+  if (capturing) captured.push_back(l); else run(l);
+  return hipSuccess;
+}
+hipError_t hipMalloc(void **p, size_t n) {
+  *p = nullptr;
+  if (device_used + n > device_limit) return hipErrorOutOfMemory;
+  *p = aligned_alloc(256, (n + 255) / 256 * 256);   // as device allocations are at least
+  memset(*p, 0, n);
+  device_memory[*p] = n;
+  device_used += n;
+  if (device_used > device_high) device_high = device_used;
+  return hipSuccess;
+}
+hipError_t hipFree(void *p) {
+  if (!p) return hipSuccess;
+  CHECK(device_memory.count(p));
+  device_used -= device_memory[p];
+  device_memory.erase(p);
+  free(p);
+  return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = calloc(1, n); ++host_allocations; return hipSuccess; }
+hipError_t hipHostFree(void *p) { free(p); --host_allocations; return hipSuccess; }
+hipError_t hipMemGetInfo(size_t *f, size_t *t) { *f = device_limit - device_used; *t = device_limit; return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { CHECK(!capturing); memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { CHECK(!capturing); memset(d, v, n); return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "made to fail"; }
+hipError_t hipGetSymbolAddress(void **, const void *) { return hipErrorNotFound; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)malloc(1); return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { free((void *)s); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) { free((void *)e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return fail_event_record && --fail_event_record == 0 ? hipErrorUnknown : hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { capturing = true; captured.clear(); return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *g) { capturing = false; *g = (hipGraph_t) new std::vector<Launch>(captured); return hipSuccess; }
+hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t g, hipGraphNode_t *, char *, size_t) {
+  *x = (hipGraphExec_t) new std::vector<Launch>(*(std::vector<Launch> *)g);
+  return hipSuccess;
+}
+hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t) {
+  for (const Launch &l : *(std::vector<Launch> *)x) run(l);
+  return hipSuccess;
+}
+hipError_t hipGraphDestroy(hipGraph_t g) { delete (std::vector<Launch> *)g; return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t x) { delete (std::vector<Launch> *)x; return hipSuccess; }
+}
+
+// ---- the tests -----------------------------------------------------------------------------------------
+namespace {
+pl_model_cfg shape(int kv_heads, int batch, int context, int64_t pool_tokens) {
+  pl_model_cfg c{};
+  c.n_layers = 2; c.d_model = 256; c.n_q_heads = 8; c.n_kv_heads = kv_heads; c.head_dim = 32; c.d_ffn = 256; c.vocab = 512;
+  c.rope_theta = 1e4f; c.rms_eps = 1e-6f; c.max_batch = batch; c.max_context = context; c.kv_pool_tokens = pool_tokens;
+  c.kv_page_tokens = 32; c.n_weight_buffers = 1; c.seed = 7; c.device = 0;
+  return c;
+}
+pl_engine *engine(const pl_model_cfg &c) {
+  pl_engine *e = nullptr;
+  CHECK(pl_create(&c, &e) == PL_OK);
+  std::vector<char> blob(pl_weight_nbytes(e));
+  CHECK(pl_load_weights(e, blob.data(), blob.size()) == PL_OK);
+  return e;
+}
+const Launch &last(const char *kernel) {
+  for (size_t i = done.size(); i-- > 0;)
+    if (done[i].kernel.find(kernel) != std::string::npos) return done[i];
+  CHECK(!"launched");
+  abort();
+}
+
+// A step takes the same attention route whether it is replayed from a graph or launched kernel by kernel.
+void same_route() {
+  for (int n = 60; n <= 128; ++n) {
+    bool rotates[2];
+    for (int graphs = 0; graphs < 2; ++graphs) {
+      pl_engine *e = engine(shape(8, 128, 256, 128 * 256));
+      CHECK(pl_debug_set_graphs(e, graphs) == PL_OK);
+      std::vector<int32_t> prompt(20, 3);
+      for (int i = 0; i < n; ++i) CHECK(pl_add_sequence(e, i, prompt.data(), 20, 60, 1.f, nullptr) == PL_OK);
+      pl_step_out out{};
+      CHECK(pl_decode_step(e, nullptr, &out) == PL_OK);
+      rotates[graphs] = !last("attn_decode_kernel").attn.q;
+      pl_destroy(e);
+    }
+    CHECK(rotates[0] == rotates[1]);
+  }
+}
+}  // namespace
+
+int main(int, char **argv) {
+  const std::string test = argv[1];
+  if (test == "same_route") same_route();
+  else return 2;
+  CHECK(device_memory.empty() && host_allocations == 0);
+  puts("ok");
+  return 0;
+}

@@ -524,6 +524,27 @@ def test_a_sequence_alone_equals_the_same_among_many(weights):
         assert np.array_equal(few[1], many[1]) and np.array_equal(few[2], many[2])
 
 
+def test_sequences_among_more_than_the_attention_rotates_for_equal_the_same_alone(weights):
+    """Steps of few work items add up, rotate and append inside the attention, steps of many (more than 768 workgroups)
+    in a kernel of their own: the same sequences' logits are bit-identical, with items of one page and of many."""
+    master, _ = weights
+    contexts = [2500, 2048, 2049, 31, 32, 513, 1, 640]
+    seen = []
+    for n in (len(contexts), 400):
+        eng = pl.Engine.from_model(M, max_batch=512, max_context=4096, kv_pool_tokens=8 * 4096 + 400 * 256, kv_page_tokens=128, seed=SEED, device=0)
+        eng.load_weights(eng.pack_weights(master, synth.f32_to_bf16_bits))
+        _random_pool(eng)
+        for i in range(n):      # the first ones get the same pages in both engines
+            c = contexts[i] if i < len(contexts) else 100
+            assert eng.debug_add_sequence_at(i, None, 1, 4096, 1.0, c, c, 5 + i % 50) == i
+        for _ in range(3):
+            eng.decode_step(np.full(512, 9, np.int32))
+            seen.append(eng.debug_get_logits(n)[:len(contexts)])
+        eng.close()
+    for few, many in zip(seen[:3], seen[3:]):
+        assert np.isfinite(few).all() and np.array_equal(few, many)
+
+
 def _random_pool(eng):
     ptr, nbytes = eng.debug_kv_pool()
     torch.as_tensor(_Device(ptr, nbytes // 2), device="cuda").view(torch.bfloat16).normal_(0, 1, generator=torch.Generator(device="cuda").manual_seed(3))
