@@ -96,7 +96,8 @@ struct pl_engine {
   char *kv_pool = nullptr;   // bf16 pages in operand order, or fp32 pages of the test build
   std::vector<int32_t> free_pages;
   int32_t *pt_h = nullptr;   // host page table (pinned): the truth; each work set keeps a device copy of its own
-  bool pt_dirty = false;
+  bool pt_dirty = false;     // the decode step's device copy is to be sent anew
+  bool pt_unsent = false;    // pages have been added to the table by a step that has not been launched
   std::vector<Seq> seqs;
   // Activation buffers and per-pass metadata come in two sets, each with its own stream: set 0 is the
   // decode step's, set 1 belongs to the cache-only passes (prompt reading, cache recomputation), so
@@ -1190,6 +1191,7 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
   double kv_tokens = 0;
   int items = 0, subs = 0, longest = 0, n_upd = 0;
   int32_t *upd = w.m_pairs(false);
+  if (e->pt_unsent) e->pt_dirty = true;   // an earlier step ended between taking pages and its launch
   for (int s = 0; s < c.max_batch; ++s) {
     Seq &q = e->seqs[s];
     if (!q.active || q.reading) continue;
@@ -1201,6 +1203,7 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
         e->pt_h[at] = q.pages.back();
         upd[2 + 2 * n_upd] = (int32_t)at;
         upd[3 + 2 * n_upd++] = q.pages.back();
+        e->pt_unsent = true;
       }
     }
     row_slot[r] = s;
@@ -1238,10 +1241,8 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
     HIP_TRY(hipEventRecord(e->ev_a, s));
     e->prof_n = 0;   // a replayed graph records no per-kernel events: nothing of an earlier step may be counted again
     int rc = run_step(e, w, n);
-    if (rc) {
-      e->pt_dirty = true;   // this step's page-table changes may not have been applied
-      return rc;
-    }
+    if (rc) return rc;
+    e->pt_unsent = false;
     HIP_TRY(hipEventRecord(e->ev_b, s));
     const double t_enq = now_ms();
     HIP_TRY(hipStreamSynchronize(s));

@@ -142,6 +142,24 @@ const Launch &last(const char *kernel) {
   abort();
 }
 
+// A step that takes new pages and then ends early must not leave the device's page table without them.
+void early_return() {
+  for (int at = 1; at <= 2; ++at) {   // the first event of the step (before its launch) and the second (behind it)
+    pl_engine *e = engine(shape(2, 2, 128, 512));
+    std::vector<int32_t> prompt(20, 3);
+    for (int i = 0; i < 2; ++i) CHECK(pl_add_sequence(e, i, prompt.data(), 20, 60, 1.f, nullptr) == PL_OK);
+    pl_step_out out{};
+    for (int i = 0; i < 32; ++i) CHECK(pl_decode_step(e, nullptr, &out) == PL_OK);
+    fail_event_record = at;
+    CHECK(pl_decode_step(e, nullptr, &out) == PL_E_HIP);
+    CHECK(pl_decode_step(e, nullptr, &out) == PL_OK);
+    const int32_t *table = last("step_begin_kernel").begin.page_table;   // pages are handed out in ascending order
+    CHECK(table[0] == 0 && table[4] == 1);
+    CHECK(table[1] == 2 && table[5] == 3);
+    pl_destroy(e);
+  }
+}
+
 // A step takes the same attention route whether it is replayed from a graph or launched kernel by kernel.
 void same_route() {
   for (int n = 60; n <= 128; ++n) {
@@ -163,7 +181,8 @@ void same_route() {
 
 int main(int, char **argv) {
   const std::string test = argv[1];
-  if (test == "same_route") same_route();
+  if (test == "early_return") early_return();
+  else if (test == "same_route") same_route();
   else return 2;
   CHECK(device_memory.empty() && host_allocations == 0);
   puts("ok");
