@@ -343,46 +343,43 @@ int alloc_device(pl_engine *e) {
   e->attn_chunk = pl::attention_chunk_tokens(B, c.n_kv_heads, c.max_context);
   e->attn_max_chunks = (c.max_context + e->attn_chunk - 1) / e->attn_chunk;
   if ((rc = alloc_work(e, e->wk[0], e->rows_cap, parts_elems(e->rows_cap), true))) return rc;
-  // The passes' buffers give way where memory is tight: passes of rows_cap rows do the same, more slowly.
-  auto alloc_pass_work = [&](int rows) {
-    hipStream_t s = e->wk[1].stream;
-    free_work(e->wk[1]);
-    (void)hipGetLastError();
-    e->wk[1].stream = s;
-    e->pass_rows = rows;
-    return alloc_work(e, e->wk[1], rows, parts_elems(rows), false);
-  };
-  rc = alloc_pass_work(e->pass_rows);
-  if (rc == PL_E_NOMEM && e->pass_rows > e->rows_cap) rc = alloc_pass_work(e->rows_cap);
-  if (rc) return rc;
-  e->ring.resize(PASS_RING);
-  for (auto &im : e->ring) {
-    HIP_TRY(hipHostMalloc((void **)&im.meta_h, (size_t)e->wk[1].image_bytes(), hipHostMallocDefault));
-    HIP_TRY(hipEventCreate(&im.ev_begin));
-    HIP_TRY(hipEventCreate(&im.ev_end));
-  }
   e->ev_slot.resize(B);
   for (auto &ev : e->ev_slot) HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
   if ((rc = dev_alloc(&e->logits, (int64_t)B * c.vocab))) return rc;
   char *ws = nullptr;
   if ((rc = dev_alloc(&ws, pl::sample_workspace_bytes(B, c.vocab)))) return rc;
   e->samp_ws = ws;
-  // the KV pool comes last: with kv_pool_tokens == 0 it takes what is left of the device memory, minus
-  // a reserve for the caller, up to the most the slots could ever use
-  if (e->n_pages == 0) {
-    size_t free_b = 0, total_b = 0;
-    HIP_TRY(hipMemGetInfo(&free_b, &total_b));
-    const int64_t page_bytes = e->page_stride * e->esz * std::max(c.n_layers, 1);
-    const int64_t avail = (int64_t)free_b - KV_AUTO_RESERVE_BYTES;
-    const int64_t most = (int64_t)B * e->pages_per_seq;
-    e->n_pages = std::min(avail > 0 ? avail / page_bytes : 0, most);
-    if (e->n_pages < 1) return fail(PL_E_NOMEM, "no device memory left for a KV pool (%lld bytes free)", (long long)free_b);
-    set_pool_pages(e, e->n_pages);
+  // The passes' buffers and the KV pool come last.  With kv_pool_tokens == 0 the pool takes what is left of the device
+  // memory, minus a reserve for the caller, up to the most the slots could ever use.  The passes' buffers give way
+  // where memory is tight: passes of rows_cap rows do the same, more slowly.
+  const bool automatic = e->n_pages == 0;
+  for (;;) {
+    hipStream_t s = e->wk[1].stream;
+    free_work(e->wk[1]);
+    e->wk[1].stream = s;
+    rc = alloc_work(e, e->wk[1], e->pass_rows, parts_elems(e->pass_rows), false);
+    if (!rc && automatic) {
+      size_t free_b = 0, total_b = 0;
+      HIP_TRY(hipMemGetInfo(&free_b, &total_b));
+      const int64_t page_bytes = e->page_stride * e->esz * std::max(c.n_layers, 1);
+      const int64_t avail = (int64_t)free_b - KV_AUTO_RESERVE_BYTES;
+      const int64_t most = (int64_t)B * e->pages_per_seq;
+      set_pool_pages(e, std::min(avail > 0 ? avail / page_bytes : 0, most));
+      if (e->n_pages < 1) rc = fail(PL_E_NOMEM, "no device memory left for a KV pool (%lld bytes free)", (long long)free_b);
+    }
+    if (!rc) rc = dev_alloc(&e->kv_pool, e->layer_stride * c.n_layers * e->esz);
+    if (rc != PL_E_NOMEM || e->pass_rows == e->rows_cap) break;
+    (void)hipGetLastError();
+    e->pass_rows = e->rows_cap;
   }
-  const int64_t pool_elems = e->layer_stride * c.n_layers;
-  rc = dev_alloc(&e->kv_pool, pool_elems * e->esz);
-  if (rc == PL_E_NOMEM && e->pass_rows > e->rows_cap && !(rc = alloc_pass_work(e->rows_cap))) rc = dev_alloc(&e->kv_pool, pool_elems * e->esz);
   if (rc) return rc;
+  const int64_t pool_elems = e->layer_stride * c.n_layers;
+  e->ring.resize(PASS_RING);
+  for (auto &im : e->ring) {
+    HIP_TRY(hipHostMalloc((void **)&im.meta_h, (size_t)e->wk[1].image_bytes(), hipHostMallocDefault));
+    HIP_TRY(hipEventCreate(&im.ev_begin));
+    HIP_TRY(hipEventCreate(&im.ev_end));
+  }
   // Every position a kernel may touch must hold a finite value: masked soft-max weights are
   // exactly 0, and 0 * finite stays 0.
   HIP_TRY(hipMemsetAsync(e->kv_pool, 0, (size_t)pool_elems * e->esz, e->s_dec));

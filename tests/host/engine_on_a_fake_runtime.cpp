@@ -177,12 +177,36 @@ void same_route() {
     CHECK(rotates[0] == rotates[1]);
   }
 }
+
+// The buffers of the prompt passes give way where memory is tight, whatever does not fit beside them: an engine whose pool is
+// one page is created down to well below what it takes with room, also where the pool takes what is left (pool_tokens 0).
+void scarce_memory() {
+  pl_model_cfg c = shape(2, 64, 256, 32);
+  c.vocab = 8192;
+  device_high = 0;
+  pl_destroy(engine(c));
+  const size_t needed = device_high, reserve = (size_t)6 << 30, less = (size_t)2 << 20;
+  for (int64_t pool_tokens : {32, 0}) {
+    c.kv_pool_tokens = pool_tokens;
+    for (size_t missing = 0; missing < less; missing += (size_t)64 << 10) {
+      device_limit = needed - missing + (pool_tokens ? 0 : reserve);
+      pl_engine *e = nullptr;
+      CHECK(pl_create(&c, &e) == PL_OK);
+      pl_destroy(e);
+    }
+    device_limit = needed / 2 + (pool_tokens ? 0 : reserve);
+    pl_engine *e = nullptr;
+    CHECK(pl_create(&c, &e) == PL_E_NOMEM && device_memory.empty());
+    device_limit = ~(size_t)0;
+  }
+}
 }  // namespace
 
 int main(int, char **argv) {
   const std::string test = argv[1];
   if (test == "early_return") early_return();
   else if (test == "same_route") same_route();
+  else if (test == "scarce_memory") scarce_memory();
   else return 2;
   CHECK(device_memory.empty() && host_allocations == 0);
   puts("ok");
