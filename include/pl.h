@@ -44,6 +44,7 @@ typedef enum {
 #define PL_SWAP_RECOMPUTE_KV 2u /* or-ed in: at the flip, rebuild every sequence's cache under the new weights */
 #define PL_DEVICE_NONE (-1) /* bookkeeping-only engine: no GPU is touched, no token is computed  */
 #define PL_BF16 0 /* the engine proper: bf16 weights, KV cache and activations, fp32 accumulation   */
+#define PL_GEMM_COLD 16 /* or-ed into the mode of the pl_debug_gemm_* launches: see pl_debug_gemm_cfg */
 #define PL_F32 1  /* test build: everything in fp32 through plain kernels (see pl_model_cfg.dtype) */
 
 typedef struct pl_engine pl_engine;
@@ -278,7 +279,9 @@ int pl_debug_kv_pool(pl_engine *e, void **device_ptr, int64_t *nbytes);
  * wavefronts stacked along the rows.  mode and splits as in pl_gemm_bf16, except that mode 1 accepts
  * splits > 1: the partial sums then go to ws (device fp32 [splits, M, n_end - n_begin]) and a second
  * kernel applies the SwiGLU to their sum.  paired != 0 (splits = 1 only) lays the grid out so that the
- * row tiles of one column tile run on the same XCD at the same time.  PL_E_INVAL (nothing launched)
+ * row tiles of one column tile run on the same XCD at the same time.  mode | PL_GEMM_COLD (here and in the two
+ * launches below) takes the kernels that an engine takes whose weights together do not stay in the last-level cache
+ * between two steps, whatever the size of this matrix; the results are the same bits.  PL_E_INVAL (nothing launched)
  * for shapes the configuration does not cover. */
 int pl_debug_gemm_cfg(int32_t cfg, const void *x, const void *w, void *y, void *ws, int32_t M, int32_t N, int32_t K,
                       int32_t mode, int32_t splits, int32_t n_begin, int32_t n_end, int32_t paired, void *stream);

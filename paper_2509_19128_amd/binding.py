@@ -8,7 +8,7 @@ import numpy as np
 
 __all__ = [
     "PL_OK", "PL_E_INVAL", "PL_E_NOSLOT", "PL_E_NOKV", "PL_E_BUSY", "PL_E_STATE", "PL_E_CTX", "PL_E_HIP",
-    "PL_E_NOMEM", "PL_SWAP_ASYNC", "PL_SWAP_WAIT", "PL_SWAP_RECOMPUTE_KV", "PL_DEVICE_NONE", "PL_BF16", "PL_F32", "PlError", "ModelCfg", "StepOut", "Stats",
+    "PL_E_NOMEM", "PL_SWAP_ASYNC", "PL_SWAP_WAIT", "PL_SWAP_RECOMPUTE_KV", "PL_DEVICE_NONE", "PL_BF16", "PL_F32", "PL_GEMM_COLD", "PlError", "ModelCfg", "StepOut", "Stats",
     "lib", "library_path", "Engine", "operand_order", "pl_attention_decode", "pl_attention_workspace_bytes", "pl_kv_pack_host",
     "pl_gemm_bf16", "pl_debug_gemm_cfg", "pl_debug_gemm_plan", "pl_debug_gemm_planned", "pl_debug_gemm_folded", "pl_sample", "pl_sample_static", "pl_sample_workspace_bytes", "pl_debug_stream_read", "pl_is_ess", "EXPORTS",
 ]
@@ -17,6 +17,7 @@ PL_OK, PL_E_INVAL, PL_E_NOSLOT, PL_E_NOKV, PL_E_BUSY, PL_E_STATE, PL_E_CTX, PL_E
 PL_SWAP_ASYNC, PL_SWAP_WAIT, PL_SWAP_RECOMPUTE_KV = 0, 1, 2
 PL_DEVICE_NONE = -1
 PL_BF16, PL_F32 = 0, 1
+PL_GEMM_COLD = 16
 
 # every symbol include/pl.h declares
 EXPORTS = [

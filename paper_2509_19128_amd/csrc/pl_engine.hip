@@ -1546,11 +1546,19 @@ int pl_gemm_bf16(const void *x, const void *w, void *y, int32_t M, int32_t N, in
   return PL_OK;
 }
 
+// whether a product of the debug launches takes the kernels for cold weights; the flag is taken out of `mode`
+static bool debug_gemm_cold(int32_t *mode, int32_t N, int32_t K) {
+  const bool asked = (*mode & PL_GEMM_COLD) != 0;
+  *mode &= ~PL_GEMM_COLD;
+  return asked || pl::gemm_cold((int64_t)N * K * 2);
+}
+
 int pl_debug_gemm_cfg(int32_t cfg, const void *x, const void *w, void *y, void *ws, int32_t M, int32_t N, int32_t K,
                       int32_t mode, int32_t splits, int32_t n_begin, int32_t n_end, int32_t paired, void *stream) {
   if (!x || !w || !y) return fail(PL_E_INVAL, "NULL argument");
+  const bool cold = debug_gemm_cold(&mode, N, K);
   int rc = pl::launch_gemm_cfg(cfg, (const bf16_t *)x, (const bf16_t *)w, y, (float *)ws, M, N, K, mode, splits, n_begin,
-                               n_end, paired != 0, pl::gemm_cold((int64_t)N * K * 2), (hipStream_t)stream);
+                               n_end, paired != 0, cold, (hipStream_t)stream);
   if (rc == -1) return fail(PL_E_INVAL, "unsupported GEMM launch cfg=%d M=%d N=%d K=%d mode=%d splits=%d [%d, %d)", cfg, M, N, K, mode, splits, n_begin, n_end);
   if (rc) return fail(PL_E_HIP, "GEMM launch failed");
   return PL_OK;
@@ -1570,11 +1578,12 @@ int pl_debug_gemm_plan(int32_t M_max, int32_t N, int32_t K, int32_t mode, int32_
 int pl_debug_gemm_planned(const void *x, const void *w, void *y, void *ws, int32_t M_max, int32_t M, int32_t N, int32_t K,
                           int32_t mode, void *stream) {
   if (!x || !w || !y) return fail(PL_E_INVAL, "NULL argument");
+  const bool cold = debug_gemm_cold(&mode, N, K);
   if (M_max < 1 || M_max > 512 || M < 1 || M > M_max || N < 32 || K < 256 || (mode != 0 && mode != 1))
     return fail(PL_E_INVAL, "unsupported GEMM shape");
   const pl::GemmSplit ks = pl::gemm_pick_split(M_max, N, K, mode);
   if (!ws && mode == 1 && pl::gemm_workspace_elems(M_max, N, ks) > 0) return fail(PL_E_INVAL, "this plan needs a workspace");
-  int rc = pl::launch_gemm((const bf16_t *)x, (const bf16_t *)w, y, (float *)ws, M, N, K, mode, ks, pl::gemm_cold((int64_t)N * K * 2), (hipStream_t)stream);
+  int rc = pl::launch_gemm((const bf16_t *)x, (const bf16_t *)w, y, (float *)ws, M, N, K, mode, ks, cold, (hipStream_t)stream);
   if (rc == -1) return fail(PL_E_INVAL, "unsupported GEMM shape M=%d N=%d K=%d mode=%d", M, N, K, mode);
   if (rc) return fail(PL_E_HIP, "GEMM launch failed");
   return PL_OK;
@@ -1583,10 +1592,11 @@ int pl_debug_gemm_planned(const void *x, const void *w, void *y, void *ws, int32
 int pl_debug_gemm_folded(const void *x, const void *w, void *y, int32_t M_max, int32_t M, int32_t N, int32_t K, int32_t mode,
                          void *stream) {
   if (!x || !w || !y) return fail(PL_E_INVAL, "NULL argument");
+  const bool cold = debug_gemm_cold(&mode, N, K);
   if (M_max < 1 || M_max > 512 || M < 1 || M > pl::GEMM_MAX_ROWS || N < 32 || K < 256 || (mode != 0 && mode != 1))
     return fail(PL_E_INVAL, "unsupported GEMM shape");
-  int rc = pl::launch_gemm_folded((const bf16_t *)x, (const bf16_t *)w, y, M, N, K, mode, pl::gemm_pick_split(M_max, N, K, mode),
-                                  pl::gemm_cold((int64_t)N * K * 2), (hipStream_t)stream);
+  int rc = pl::launch_gemm_folded((const bf16_t *)x, (const bf16_t *)w, y, M, N, K, mode, pl::gemm_pick_split(M_max, N, K, mode), cold,
+                                  (hipStream_t)stream);
   if (rc == -1) return fail(PL_E_INVAL, "unsupported GEMM shape M=%d N=%d K=%d mode=%d", M, N, K, mode);
   if (rc) return fail(PL_E_HIP, "GEMM launch failed");
   return PL_OK;

@@ -375,6 +375,55 @@ def test_products_of_many_rows_equal_the_slices_of_few_added_in_order(M_max, N, 
             pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), M_max, *bad, mode, 0)
 
 
+@pytest.mark.parametrize("cfg", sorted(CFG_TILES))
+def test_every_gemm_tile_configuration_for_cold_weights_gives_the_same_bits(cfg):
+    """Weights that do not stay in the cache between two steps are loaded with another cache policy, by kernels of their
+    own: equal bit for bit to the others, which the test above holds to float64, in both modes, with and without a K split."""
+    rows, _ = CFG_TILES[cfg]
+    M, N, K = min(2 * rows + 7, 300), 5 * 128, 768
+    g = torch.Generator(device="cuda").manual_seed(cfg)
+    x = torch.empty(M, K, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
+    w = torch.empty(N * K, device="cuda", dtype=torch.bfloat16).normal_(0, 0.05, generator=g)
+    ws = torch.empty(3 * M * N, device="cuda", dtype=torch.float32)
+    for mode, splits, nb, ne, paired in [(0, 1, 0, N, False), (0, 3, 128, N - 64, False), (0, 1, 64, N, True), (1, 1, 0, N, False),
+                                         (1, 3, 0, N, False), (1, 2, 128, N - 64, False)]:
+        if mode == 1 and cfg in (6, 7, 8):
+            continue
+        got = []
+        for cold in (0, pl.PL_GEMM_COLD):
+            y = torch.zeros(splits, M, N, device="cuda") if mode == 0 else torch.zeros(M, N // 2, device="cuda", dtype=torch.bfloat16)
+            pl.pl_debug_gemm_cfg(cfg, x.data_ptr(), w.data_ptr(), y.data_ptr(), ws.data_ptr(), M, N, K, mode | cold, splits, nb, ne, paired, 0)
+            torch.cuda.synchronize()
+            got.append(y)
+        assert bool(got[0].abs().sum() > 0) and torch.equal(got[0], got[1]), (mode, splits, nb, ne, paired)
+
+
+@pytest.mark.parametrize("M_max,N,K,mode", [(64, 2048, 1536, 0), (256, 4608, 3584, 0), (256, 3584, 18944, 0), (128, 7168, 5120, 0), (256, 32800, 256, 0),
+                                            (64, 2 * 8960, 256, 1), (128, 2 * 27648, 256, 1), (256, 2 * 18944, 768, 1), (256, 2 * 18976, 768, 1)])
+def test_products_of_an_engine_with_cold_weights_give_the_same_bits(M_max, N, K, mode):
+    """The same for the launches of a step (at every row count that chooses another kernel) and of a pass of many rows."""
+    splits, _, _, ws_elems = pl.pl_debug_gemm_plan(M_max, N, K, mode)
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    x = torch.empty(1024, K, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
+    w = torch.empty(N * K, device="cuda", dtype=torch.bfloat16).normal_(0, 0.05, generator=g)
+    ws = torch.empty(max(ws_elems, 1), device="cuda", dtype=torch.float32)
+
+    def both(M, slices, launch):
+        got = []
+        for cold in (0, pl.PL_GEMM_COLD):
+            y = torch.full((slices, M, N), float("nan"), device="cuda") if mode == 0 else torch.full((M, N // 2), float("nan"), device="cuda", dtype=torch.bfloat16)
+            ws.fill_(float("nan"))
+            launch(y, M, mode | cold)
+            torch.cuda.synchronize()
+            got.append(y)
+        assert bool(got[0].isfinite().all()) and torch.equal(got[0], got[1]), M
+    for M in (1, 20, 33, 64, 65, 128, 129, 200, 256):
+        if M <= M_max:
+            both(M, splits, lambda y, M, md: pl.pl_debug_gemm_planned(x.data_ptr(), w.data_ptr(), y.data_ptr(), ws.data_ptr(), M_max, M, N, K, md, 0))
+    for M in (300, 511, 1024):
+        both(M, 1, lambda y, M, md: pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), M_max, M, N, K, md, 0))
+
+
 def test_gemm_rejects_bad_shapes():
     t = torch.zeros(600 * 512, device="cuda", dtype=torch.bfloat16)
     for args in [(4, 64, 192, 0, 1), (0, 64, 256, 0, 1), (4, 64, 512, 0, 3), (4, 96, 256, 1, 1), (4, 64, 512, 1, 2),
