@@ -752,6 +752,10 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
     else if (M <= 256 && K <= 4096) cfg = ks.splits <= 2 ? GEMM_128x64 : GEMM_128x128;
     else cfg = GEMM_256x128;
   }
+  // A second row tile of a few rows runs through its W ahead of the first one's loads, which then find nothing in L2 if they
+  // are non-temporal: LM head of the 7B / 32B shape 129 rows 287 / 474 us with ordinary, 318 / 550 with non-temporal
+  // loads, 160 rows 295 / 473 and 301 / 502, 192 rows 303 / 457 and 300 / 438; gate/up of the 7B shape, 136 rows 78 and 88.
+  if (paired && M < 192) cold = false;
   int n_main = ks.n_main;
   if (paired && n_main == N) {
     // Wide matrices without a K split: 128 x 256 tiles in XCD-local pairs.  When the tile count is a
