@@ -20,7 +20,8 @@ constexpr int LDS_ROW = 72;     // padded row length (elements) of the x tile in
 // Cache policy of the W loads: non-temporal (2) for weights that are COLD, that is, cannot be in the 256 MB last-level cache
 // from the pass before, in tiles whose W one wavefront reads (WM = 1): they have no second reader, and ordinary loads
 // evict each other from L2 on the way.  SwiGLU of the 32B shape, 128 rows: 111.8 -> 98.7 us (5.7 TB/s); 7B shape, 19 rows,
-// whole step -4 %; products at 256 rows -1 % (the second row tile's reader still finds W in L2).  Where two wavefronts
+// whole step -4 %; products at 256 rows -1 % (the second row tile's reader still finds W in L2; not where that tile
+// or one of more is short: launch_gemm, launch_gemm_folded).  Where two wavefronts
 // share W through the caches (WM = 2; 1.5B shape, 64 rows) they cost 3.5 % of the step, and a matrix that stays in the
 // last-level cache between calls 5 to 30 % (55 MB, 3 rows: 11 -> 16 us).
 template <int WM, bool COLD>
@@ -462,8 +463,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(const bf16_t *__restrict__ X,
 }
 
 // Many rows (prompt passes): flat grid in XCD-local groups of row tiles as above, all K slices of a tile in
-// one workgroup.
-template <int WM, int WN, int AT, int BT, int MODE, bool COLD>
+// one workgroup.  (With 128 x 256 tiles the second set of accumulators spills 66 registers; the shape is still the fastest where
+// launch_gemm_folded takes it: down product of the 32B shape, 1024 rows, 345 us, 480 with the best of the others.)
+template <int WM, int WN, int AT, int BT, int MODE>
 __global__ __launch_bounds__(256) void gemm_fold_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
                                                         void *__restrict__ Yv, int M, int N, int K, int ksteps,
                                                         int n_base, int n_end, int nrow) {
@@ -471,7 +473,7 @@ __global__ __launch_bounds__(256) void gemm_fold_kernel(const bf16_t *__restrict
   __shared__ __attribute__((aligned(16))) bf16_t xs[2][BM * LDS_ROW];
   const int rtile = (blockIdx.x >> 3) % nrow, ctile = (blockIdx.x / (8 * nrow)) * 8 + (blockIdx.x & 7);
   if (n_base + ctile * BN >= n_end) return;   // padding of the flat grid (uniform for the workgroup)
-  gemm_tile<WM, WN, AT, BT, MODE, COLD, true>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, 0, n_end, N, 0);
+  gemm_tile<WM, WN, AT, BT, MODE, false, true>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, 0, n_end, N, 0);
 }
 
 // The SwiGLU product of a 129..256-row batch in ONE launch of one workgroup per compute unit.  Workgroup i
@@ -615,15 +617,12 @@ int launch_fold_cfg(Launch L) {
   const int nrow = (L.M + BM - 1) / BM, grid = ((L.n_end - L.n_begin + BN - 1) / BN + 7) / 8 * 8 * nrow;
   const int ksteps = 4 * ((L.K / (4 * BK) + splits - 1) / splits);
   if (L.mode == 1 && (BT != 2 || AT > 2)) return -1;   // (not used: no registers for a second set of accumulators)
-  with_cold<WM>(L.cold, [&](auto COLD) {
-    constexpr bool cold = decltype(COLD)::value;
-    if (L.mode == 0)
-      hipLaunchKernelGGL((gemm_fold_kernel<WM, WN, AT, BT, 0, cold>), dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K,
-                         ksteps, L.n_begin, L.n_end, nrow);
-    else if constexpr (BT == 2 && AT <= 2)
-      hipLaunchKernelGGL((gemm_fold_kernel<WM, WN, AT, BT, 1, cold>), dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K,
-                         ksteps, L.n_begin, L.n_end, nrow);
-  });
+  if (L.mode == 0)
+    hipLaunchKernelGGL((gemm_fold_kernel<WM, WN, AT, BT, 0>), dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps,
+                       L.n_begin, L.n_end, nrow);
+  else if constexpr (BT == 2 && AT <= 2)
+    hipLaunchKernelGGL((gemm_fold_kernel<WM, WN, AT, BT, 1>), dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps,
+                       L.n_begin, L.n_end, nrow);
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }
 
@@ -815,6 +814,10 @@ int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, 
   if (mode == 0 && ks.n_main != N) return -1;
   if (ks.n_main < 0 || ks.n_main > N) return -1;
   if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
+  // Non-temporal loads of cold weights only for few and full row tiles: gate/up of the 7B / 32B shape, 384 rows 142 / 236 us with
+  // them and 146 / 234 without, 512 rows 148 / 302 and 150 / 302, but 257 rows 129 / 240 and 128 / 217, 576 rows 182 / 371 and
+  // 185 / 356, 769 rows 258 / 492 and 252 / 451; plain products (32B down, 769 rows) 372 and 348.
+  cold = cold && mode == 1 && M <= 512 && (M - 1) % 128 >= 96;
   Launch L{x, w, y, M, N, K, mode, ks.splits, 0, ks.n_main, N, 0, true, cold, s};
   if (mode == 1) {
     // 7B shape, 1024 rows: 288 us with 128 x 256 tiles, 302 with 256 x 128, 349 with 128 x 128; 1.5B shape (a third of
