@@ -86,6 +86,56 @@ def test_weights_at_every_alignment_of_the_arrays_and_of_the_sequences(shift_pi,
         assert np.isclose(sums[2 * s].item(), seg.sum(), rtol=1e-11) and np.isclose(sums[2 * s + 1].item(), (seg * seg).sum(), rtol=1e-11)
 
 
+@pytest.mark.parametrize("with_w", [True, False])
+def test_a_sequences_sums_do_not_depend_on_the_number_of_sequences(with_w):
+    """Both sides of the choice of threads (1536 sequences): weights and sums of the same sequences are bit-identical, at the
+    lengths where the order of their sums changes (1024 tokens) and a round of it ends."""
+    rng = np.random.default_rng(6)
+    lens = [1, 5, 255, 257, 1023, 1024, 1025, 2049, 0, 4096, 4099, 8200, 16384]
+    got = []
+    for n_seq in (len(lens), 1536, 1537, 4000):
+        r = np.random.default_rng(6)
+        pi, mu, off = _case(r, lens + [3] * (n_seq - len(lens)), 1.5)
+        n = int(off[len(lens)])
+        if not got:
+            first = pi[:n].copy(), mu[:n].copy()
+        pi[:n], mu[:n] = first
+        a, b, o = torch.from_numpy(pi).cuda(), torch.from_numpy(mu).cuda(), torch.from_numpy(off.astype(np.int64)).cuda()
+        w = torch.empty(len(pi), device="cuda") if with_w else None
+        sums, ess, tot = (torch.empty(k, device="cuda", dtype=torch.float64) for k in (2 * n_seq, n_seq, 3))
+        pl.pl_is_ess(a.data_ptr(), b.data_ptr(), o.data_ptr(), n_seq, 5.0, w.data_ptr() if with_w else 0, sums.data_ptr(), ess.data_ptr(), tot.data_ptr(), 0)
+        torch.cuda.synchronize()
+        got.append((sums[:2 * len(lens)].cpu().numpy().view(np.int64), ess[:len(lens)].cpu().numpy().view(np.int64), w[:n].cpu().numpy().view(np.int32) if with_w else 0))
+    ref = np.fmin(5.0, np.exp(first[0].astype(np.float64) - first[1]))
+    ends = np.cumsum([0] + lens)
+    for s in range(len(lens)):
+        assert np.isclose(got[0][0].view(np.float64)[2 * s], ref[ends[s]:ends[s + 1]].sum(), rtol=1e-11)
+    for other in got[1:]:
+        assert all(np.array_equal(x, y) for x, y in zip(got[0], other))
+
+
+def test_many_short_sequences_do_not_take_a_workgroup_of_a_long_one_each():
+    """32768 sequences of 16 tokens against 1024 of them, best of several runs: 4 times the time (43 and 10 us), with workgroups
+    of 1024 threads for each of them 15 times."""
+    def best(n_seq):
+        pi, mu, off = _case(np.random.default_rng(1), [16] * n_seq, 1.5)
+        a, b, o = torch.from_numpy(pi).cuda(), torch.from_numpy(mu).cuda(), torch.from_numpy(off.astype(np.int64)).cuda()
+        sums, ess, tot = (torch.empty(k, device="cuda", dtype=torch.float64) for k in (2 * n_seq, n_seq, 3))
+        times = []
+        for _ in range(8):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(20):
+                pl.pl_is_ess(a.data_ptr(), b.data_ptr(), o.data_ptr(), n_seq, 5.0, 0, sums.data_ptr(), ess.data_ptr(), tot.data_ptr(),
+                             torch.cuda.current_stream().cuda_stream)
+            e1.record()
+            torch.cuda.synchronize()
+            times.append(e0.elapsed_time(e1))
+        return min(times)
+    few, many = best(1024), best(32768)
+    assert many < 8 * few, (few, many)
+
+
 def test_on_policy_batch_is_exactly_one_and_weights_are_optional():
     rng = np.random.default_rng(8)
     lp = (-rng.random(5000) * 9).astype(np.float32)
