@@ -28,7 +28,7 @@ __device__ inline int block_scan_1024(int v, int *wsum, int *total) {
   return v + before;
 }
 
-// The list's items are 8-int records from work[8] on: {sequence, chunk, context length, slot, ids of the
+// The list's items are 8-int records: {sequence, chunk, context length, slot, ids of the
 // chunk's first four pages}.  All full chunks come first, then each sequence's last (partial or full) chunk,
 // longest first, so that the workgroups still running when the grid drains are the short ones.  With
 // `contiguous` a sequence's items follow one another instead, from first_item[sequence] on (what the merge
@@ -49,7 +49,7 @@ __device__ inline void build_worklist(int ctx, int slot, const int32_t *page_tab
     if (i >= cap) return;
     const int32_t *pt = page_table + (int64_t)sl * pages_per_seq;
     const int last_page = (cx - 1) / page_tokens, p0 = (int)((int64_t)c * item_tokens / page_tokens);
-    int4 *rec = (int4 *)(work + 8 + 8 * (int64_t)i);
+    int4 *rec = (int4 *)(work + 8 * (int64_t)i);
     rec[0] = make_int4(bb, c, cx, sl);
     rec[1] = make_int4(pt[min(p0, last_page)], pt[min(p0 + 1, last_page)], pt[min(p0 + 2, last_page)], pt[min(p0 + 3, last_page)]);
   };
@@ -83,7 +83,7 @@ __device__ inline void build_worklist(int ctx, int slot, const int32_t *page_tab
     put(total + rank, b, n - 1, ctx, slot);
   }
   for (int i = b; tickets && i < n_seq * Hkv; i += 1024) tickets[i] = 0;
-  for (int i = total + n_last + b; i < cap; i += 1024) ((int4 *)(work + 8 + 8 * (int64_t)i))[0] = make_int4(0, 0, 0, 0);
+  for (int i = total + n_last + b; i < cap; i += 1024) ((int4 *)(work + 8 * (int64_t)i))[0] = make_int4(0, 0, 0, 0);
 }
 
 }  // namespace

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
   int b, c, ctx, slot;
   int4 r1;   // page ids
   if (p.work) {
-    const int4 *rec = (const int4 *)(p.work + 8 + 8 * (int64_t)item);
+    const int4 *rec = (const int4 *)(p.work + 8 * (int64_t)item);
     const int4 r0 = rec[0];
     r1 = rec[1];
     b = r0.x; c = r0.y; ctx = r0.z; slot = r0.w;
@@ -768,8 +768,8 @@ bool attention_rotates(int items, int64_t tokens, int Hq, int Hkv, int hd, int s
          (Hq / Hkv + 2) * (hd / 8) <= 256;
 }
 
-// ints of the work buffer (which must be 32-byte aligned): a header of 8, one 8-int record per item
-int64_t attention_worklist_ints(int64_t max_items) { return 8 + 8 * max_items; }
+// ints of the work buffer (which must be 32-byte aligned): one 8-int record per item
+int64_t attention_worklist_ints(int64_t max_items) { return 8 * max_items; }
 
 int launch_attention_worklist(const AttnParams &p, int cap, hipStream_t s) {
   if (p.n_seq <= 0 || p.n_seq > 1024 || ((uintptr_t)p.work & 31)) return -1;
