@@ -203,10 +203,9 @@ int pl_add_sequence(pl_engine *e, uint64_t seq_id, const int32_t *prompt, int32_
                     int32_t max_new, float temperature, int32_t *out_slot);
 /* Batched prompt reading on refill ("add prompts", Alg. 2): reads the positions of the slot's prompt
  * that have not been read yet, except the last one, in passes of up to 1024 positions
- * through the same kernels as a decode step (rows = consecutive positions of one sequence, causal
- * because row i attends to positions <= its own), under the active weights.  It leaves exactly the
- * keys and values that reading those tokens one per step would leave (up to bf16 rounding of
- * identical arithmetic: same kernels, same per-row operation order) and emits nothing; the next
+ * (rows = consecutive positions of one sequence, causal because row i attends to positions <= its
+ * own), under the active weights.  It leaves exactly the keys and values that reading those tokens one per
+ * step would leave, bit for bit (kernels of many rows keep the order of operations of a row) and emits nothing; the next
  * pl_decode_step reads the last prompt token and produces the first generated token.
  * *out_positions (may be NULL) receives the number of positions read (0 if none were left).
  * Blocks until done (on a slot that pl_prefill_async is already reading: until that reading is done).
