@@ -579,6 +579,30 @@ def test_passes_of_few_rows_leave_the_cache_of_reading_token_by_token(weights, m
     assert np.isfinite(logits[0]).all() and np.array_equal(logits[0], logits[1])
 
 
+@pytest.mark.parametrize("Hq,Hkv,hd,rows", [(16, 1, 128, 60), (12, 4, 64, 128), (28, 4, 128, 64), (28, 4, 128, 65)])
+def test_passes_of_few_rows_at_other_head_dimensions(Hq, Hkv, hd, rows):
+    """The same for every head dimension, and on both sides of the limit at 512 elements of k per position (64 rows)."""
+    m = synth.ModelCfg(2, 256, Hq, Hkv, hd, 256, 512)
+    w = synth.make_weights(m, seed=9)
+    prompt = synth.random_prompts(np.random.default_rng(rows), 1, 700 + rows + 1, m.vocab)[0]
+    kv = []
+    for batched in (True, False):
+        eng = pl.Engine.from_model(m, max_batch=2, max_context=1024, kv_pool_tokens=1024, kv_page_tokens=64, seed=3, device=0)
+        eng.load_weights(eng.pack_weights(w, synth.f32_to_bf16_bits))
+        _random_pool(eng)
+        eng.debug_add_sequence_at(1, prompt, len(prompt), 4, 1.0, 700, 0, 5)
+        if batched:
+            assert eng.prefill(0) == rows
+        else:
+            for _ in range(rows):
+                eng.decode_step()
+        kv.append([eng.debug_read_kv(0, l, 700 + rows) for l in range(m.n_layers)])
+        eng.close()
+    for l in range(m.n_layers):
+        for part in range(2):
+            assert np.isfinite(kv[0][l][part]).all() and np.array_equal(kv[0][l][part], kv[1][l][part]), (l, part)
+
+
 def test_a_few_rows_late_in_a_long_prompt_do_not_walk_it_one_chunk_after_the_other(weights):
     """Four rows at position 12000 take about as long as at position 700 (their chunks run side by side); walked by
     one workgroup they took four times as long.  Best of several runs, with room for noise."""
