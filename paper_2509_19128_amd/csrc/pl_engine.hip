@@ -288,7 +288,6 @@ int alloc_work(pl_engine *e, pl_engine::Work &w, int64_t R, int64_t parts_elems,
   if ((rc = dev_alloc(&w.attn_work, work + w.apart_cap * (int64_t)(c.n_kv_heads + 1)))) return rc;
   w.attn_tickets = w.attn_work + work;
   w.attn_first = w.attn_tickets + w.apart_cap * (int64_t)c.n_kv_heads;
-  if (!decode) w.items_cap = std::max<int64_t>(w.items_cap, R);   // groups of rows are counted there as well
   if (decode) HIP_TRY(hipHostMalloc((void **)&w.meta_h, (size_t)w.image_bytes(), hipHostMallocDefault));
   return PL_OK;
 }
@@ -559,8 +558,9 @@ int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) {
   if (!e->use_graphs || (!prefill && e->profile != 0)) return enqueue_step(e, w, n, prefill);
   const int set = prefill ? 1 : 0;
   // grid bound of the attention kernel in coarse steps, so that few shapes occur; workgroups beyond
-  // the lists' real lengths (which the kernels read from device memory) leave at once
-  w.attn_items = (int)std::min<int64_t>((w.attn_items + 63) / 64 * 64, w.items_cap);
+  // the lists' real lengths (which the kernels read from device memory) leave at once.  Never more than the list holds
+  // (a pass whose rows share what they read has no list, but at most as many groups as rows).
+  w.attn_items = (int)std::min<int64_t>((w.attn_items + 63) / 64 * 64, prefill && !w.attn_apart ? w.rows_cap : w.items_cap);
   pl_engine::StepGraph *g = nullptr;
   for (auto &x : e->graphs)
     if (x.n == n && x.buf == e->active_buf && x.items == w.attn_items && x.split == w.attn_split && x.merge == w.attn_merge && x.apart == w.attn_apart &&

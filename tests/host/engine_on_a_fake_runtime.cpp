@@ -28,6 +28,7 @@ struct Launch {
   dim3 grid;
   pl::StepBegin begin;
   pl::AttnParams attn;
+  int cap;   // records of the work list that the kernel that begins a step writes
 };
 std::map<const void *, std::string> names;
 std::map<void *, size_t> device_memory;
@@ -55,10 +56,11 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *shared, hi
   return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, hipStream_t) {
-  Launch l{names[f], grid, {}, {}};
+  Launch l{names[f], grid, {}, {}, 0};
   if (l.kernel.find("step_begin_kernel") != std::string::npos) {
     l.begin = *(const pl::StepBegin *)args[0];
     l.attn = *(const pl::AttnParams *)args[1];
+    l.cap = *(const int *)args[2];
   } else if (l.kernel.find("attn_") != std::string::npos) {
     l.attn = *(const pl::AttnParams *)args[0];
   }
@@ -178,6 +180,38 @@ void same_route() {
   }
 }
 
+// The records that a step or a pass of few rows may write end where the list ends, whatever a graph rounds its grid up to,
+// and the attention reads no further.
+void list_capacity() {
+  for (int kv_heads : {1, 2, 3, 4, 8})
+    for (int head_dim : {32, 64, 128})
+      for (int context : {128, 256, 1024})
+        for (int graphs = 0; graphs < 2; ++graphs) {
+          pl_model_cfg c = shape(kv_heads, 4, context, 4 * context);
+          c.n_q_heads = kv_heads * 8;
+          c.head_dim = head_dim;
+          pl_engine *e = engine(c);
+          CHECK(pl_debug_set_graphs(e, graphs) == PL_OK);
+          pl_step_out out{};
+          std::vector<int32_t> prompt(context - 8, 3);
+          for (int rows : {1, 2, 7, 31, 32, 33, 63, 64, 65, 85, 100, 119, 128, 129, 200, 247}) {
+            if (rows >= context - 8) break;
+            done.clear();
+            int32_t slot = -1;
+            CHECK(pl_add_sequence(e, 1, prompt.data(), rows + 1, 4, 1.f, &slot) == PL_OK);
+            CHECK(pl_prefill(e, slot, nullptr) == PL_OK && pl_decode_step(e, nullptr, &out) == PL_OK);
+            CHECK(pl_retire_sequence(e, slot) == PL_OK);
+            for (const Launch &l : done) {
+              if (!l.attn.work) continue;
+              const int64_t records = (l.attn.tickets - l.attn.work) / 8;   // the tickets follow the list
+              if (l.kernel.find("step_begin_kernel") != std::string::npos) CHECK(l.cap <= records);
+              if (l.kernel.find("attn_decode_kernel") != std::string::npos) CHECK((int64_t)l.grid.x <= records * l.attn.Hkv);
+            }
+          }
+          pl_destroy(e);
+        }
+}
+
 // The buffers of the prompt passes give way where memory is tight, whatever does not fit beside them: an engine whose pool is
 // one page is created down to well below what it takes with room, also where the pool takes what is left (pool_tokens 0).
 void scarce_memory() {
@@ -206,6 +240,7 @@ int main(int, char **argv) {
   const std::string test = argv[1];
   if (test == "early_return") early_return();
   else if (test == "same_route") same_route();
+  else if (test == "list_capacity") list_capacity();
   else if (test == "scarce_memory") scarce_memory();
   else return 2;
   CHECK(device_memory.empty() && host_allocations == 0);
