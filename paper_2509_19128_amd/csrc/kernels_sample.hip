@@ -16,6 +16,7 @@
 #include "pl_common.h"
 
 #include <mutex>
+#include <type_traits>
 #pragma clang fp contract(off)
 
 namespace pl {
@@ -23,14 +24,22 @@ namespace {
 
 constexpr int SLICE = 8192;   // vocabulary entries per workgroup
 
+// a ^ b ^ c as one instruction
+__device__ inline uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+#else
+  return a ^ b ^ c;
+#endif
+}
 __device__ inline void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                      uint32_t k1, uint32_t out[4]) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     if (r) { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
-    const uint32_t hi0 = __umulhi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
-    const uint32_t hi1 = __umulhi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
-    c0 = hi1 ^ c1 ^ k0; c1 = lo1; c2 = hi0 ^ c3 ^ k1; c3 = lo0;
+    const uint64_t p0 = (uint64_t)c0 * 0xD2511F53u, p1 = (uint64_t)c2 * 0xCD9E8D57u;   // one instruction each
+    const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0, hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
+    c0 = xor3(hi1, c1, k0); c1 = lo1; c2 = xor3(hi0, c3, k1); c3 = lo0;
   }
   out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
@@ -73,15 +82,6 @@ __device__ inline void merge_best(float &by, int &bi, float y, int i) {
   if (y > by || (y == by && i < bi)) { by = y; bi = i; }
 }
 
-// Upper bound of gumbel(bits) from one hardware logarithm.  With t = 1 - u (exact: 2 k' + 1 with k' the
-// complement of k) -log u >= t, so -log(-log u) <= -log t.  The slack covers the rounding of the specified
-// logarithm (2e-6 at the largest value, 16.6) and of the hardware's.
-__device__ inline float gumbel_bound(uint32_t bits) {
-  const float k = (float)((bits >> 9) ^ 0x7FFFFFu);
-  const float t = __fmul_rn(__fadd_rn(__fmul_rn(k, 2.0f), 1.0f), 5.9604644775390625e-08f);
-  return __builtin_amdgcn_logf(t) * -0.693147180559945f + 1.0e-3f;
-}
-
 // All 64 lanes' parts in one, in a fixed order; every lane ends with the result.  A part without a finite or
 // infinite maximum (all entries -inf) contributes nothing to the sum.
 __device__ inline Part merge_wave(const Part &v) {
@@ -104,21 +104,24 @@ __device__ inline void finish_row(const SampleParams &p, int row, const Part &v)
   if (p.last_tok) p.last_tok[p.row_slot[row]] = tok;
 }
 
-// One slice of one row; NT threads keep its logits and random words in registers (SLICE / NT of each).
-// Bound: vector arithmetic, not the 4 bytes per entry.  Philox takes 40 quarter-rate multiplies per four
-// entries; the two specified logarithms of the noise (about 60 operations) are therefore evaluated only
-// where they can matter: each lane first takes the entry with the largest upper bound z + gumbel_bound,
-// computes that one exactly, the wavefront's largest exact value becomes the bar, and only entries whose
-// bound reaches the bar (about one in a thousand) are computed as well.  An entry below the bar cannot
-// win or tie: bound >= exact value entry by entry, rounding included (rounding is monotone).
+// One slice of one row; NT threads keep its entries in registers (SLICE / NT of each).
+// Bound: vector arithmetic, then the 4 bytes per entry.  The two specified logarithms of the noise (about 60 operations)
+// are evaluated only where they can matter.  y = z + g is largest where x / -log u is, with x = e^(z - max), and with
+// t = 1 - u (exact) t <= -log u <= t / (1 - t): so x / t bounds an entry from above, and the slice's best is no less than
+// the largest x / t minus 1, nor than 1 / 16.7 (the entry with x = 1 and the least noise).  x / t is compared by `key`, the difference
+// of the two floats' bits, which is 2^23 log2(x / t) within KEY_ERROR.  Only entries whose key can reach that bar are
+// computed as specified (about one per slice; their random words are drawn again).  KEY_SLACK covers the rounding of x and of y
+// as long as |max| <= BOUND_MAX; slices beyond that, whose maximum is infinite or that hold NaNs compute every entry.
 // The sum of exponentials does not depend on NT, so a row's log-prob does not depend on how many rows share the
 // call: all exponentials are relative to the slice's maximum, and they are added up as SUM_LANES threads of
-// SUM_LANES / 64 wavefronts would, whatever number of these a thread takes over (1.6 us of the next line's 52).
-// 256 x 152064, whole call: 52 us (3.0 TB/s) against 82-93 us with every entry's noise evaluated and a branchy online sum;
-// 4 x 4096: 5 us against 8.6.  One 64-bit multiply-add per product (v_mad_u64_u32) is slower than the
-// high/low pair (73 against 61 us before the reductions below), four wavefronts per SIMD spill (69), 16 entries
-// per thread cost 63.
+// SUM_LANES / 64 wavefronts would, whatever number of these a thread takes over.
+// 256 x 152064, whole call: 38 us (the kernel 34, 4.5 TB/s) against 54 with the bounds by logarithms, the best entry of every lane
+// computed, and two multiplications per product (a product is one instruction now, v_mad_u64_u32, 5.6 cycles where the two
+// took 9.7; fused multiply-adds in double precision, three per product, gave 55 us); 82-93 us with every entry's noise evaluated.
+constexpr float KEY_ERROR = 0.088f, KEY_SLACK = 0.004f;   // of log2: 0.0861 per difference of bits and logarithm
+constexpr int KEY_MOST = 25 << 23;                        // beyond any key of numbers: x <= 1, t >= 2^-24
 constexpr int SUM_LANES = 1024;
+constexpr float BOUND_MAX = 1024.f;
 template <int NT>
 __global__ __launch_bounds__(NT) void sample_slice_kernel(SampleParams p, int nslice) {
   constexpr int Q = SLICE / NT / 4;   // groups of four entries per thread
@@ -132,66 +135,94 @@ __global__ __launch_bounds__(NT) void sample_slice_kernel(SampleParams p, int ns
   const uint32_t k0 = (uint32_t)p.seed, k1 = (uint32_t)(p.seed >> 32);
   const int beg4 = sl * (SLICE / 4) + threadIdx.x, end4 = min(p.vocab, (sl + 1) * SLICE) / 4;   // vocab is a multiple of 4
   float z[Q][4];
-  uint32_t rnd[Q][4];
-  float mx = -INFINITY, first = -INFINITY, second = -INFINITY;   // largest two upper bounds
-  int fi = -1;
+  auto load = [&](auto WHOLE) {   // a whole slice asks for no end
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int i4 = beg4 + q * NT;
+      f32x4 v = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+      if (decltype(WHOLE)::value || i4 < end4) v = __builtin_nontemporal_load((const f32x4 *)(lg + (int64_t)i4 * 4));
+      z[q][0] = v[0]; z[q][1] = v[1]; z[q][2] = v[2]; z[q][3] = v[3];
+    }
+  };
+  if ((sl + 1) * SLICE <= p.vocab) load(std::true_type{}); else load(std::false_type{});
+  int key[Q][4];   // the bits of t, later the keys
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
-    const int i4 = beg4 + q * NT;
-    float4 v = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-    if (i4 < end4) v = *(const float4 *)(lg + (int64_t)i4 * 4);
-    z[q][0] = v.x; z[q][1] = v.y; z[q][2] = v.z; z[q][3] = v.w;
+    uint32_t rnd[4];
+    philox4x32_10((uint32_t)(beg4 + q * NT), pos, (uint32_t)sid, (uint32_t)(sid >> 32), k0, k1, rnd);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)   // t = 1 - (2 k + 1) 2^-24 is exact
+      key[q][e] = __float_as_int(__builtin_fmaf((float)(rnd[e] >> 9), -1.1920928955078125e-07f, 0.999999940395355224609375f));
   }
-  uint32_t best_bits = 0;
-  float best_z = 0.f;
+  float mx = -INFINITY;
 #pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const int i4 = beg4 + q * NT;
-    philox4x32_10((uint32_t)i4, pos, (uint32_t)sid, (uint32_t)(sid >> 32), k0, k1, rnd[q]);
+  for (int q = 0; q < Q; ++q)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       z[q][e] = __fmul_rn(z[q][e], inv_t);
       mx = fmaxf(mx, z[q][e]);
-      const float ub = __fadd_rn(z[q][e], gumbel_bound(rnd[q][e]));
-      second = fmaxf(second, fminf(first, ub));
-      if (ub > first) { first = ub; fi = i4 * 4 + e; best_bits = rnd[q][e]; best_z = z[q][e]; }
     }
-  }
   __shared__ float s_max[NW], s_besty[NW], s_sum[SUM_LANES / 64];
-  __shared__ int s_besti[NW];
+  __shared__ int s_key[NW], s_besti[NW];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   mx = wave_max(mx);
   if (lane == 0) s_max[wave] = mx;
-  float by = -INFINITY;
-  int bi = 0x7FFFFFFF;
-  if (fi >= 0) merge_best(by, bi, __fadd_rn(best_z, gumbel(best_bits)), fi);
-  const float bar = wave_max(by);
-  if (second >= bar) {
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int i4 = beg4 + q * NT;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (i4 < end4 && __fadd_rn(z[q][e], gumbel_bound(rnd[q][e])) >= bar)
-          merge_best(by, bi, __fadd_rn(z[q][e], gumbel(rnd[q][e])), i4 * 4 + e);
-    }
-  }
-  const float besty = wave_max(by);
-  const int besti = wave_min(by == besty ? bi : 0x7FFFFFFF);
   __syncthreads();
   mx = s_max[0];
 #pragma unroll
   for (int w = 1; w < NW; ++w) mx = fmaxf(mx, s_max[w]);
+  int most[Q];   // largest key of a group
 #pragma unroll
   for (int v = 0; v < V; ++v) {
     float sum = 0.f;
 #pragma unroll
-    for (int q = v; q < Q; q += V)
+    for (int q = v; q < Q; q += V) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sum += __expf(z[q][e] - mx);   // (entries beyond the slice: exp(-inf) = 0; mx = -inf: unused)
+      for (int e = 0; e < 4; ++e) {
+        const float x = __expf(z[q][e] - mx);   // (entries beyond the slice: exp(-inf) = 0; mx = -inf: unused)
+        sum += x;
+        key[q][e] = __float_as_int(x) - key[q][e];
+      }
+      most[q] = max(max(key[q][0], key[q][1]), max(key[q][2], key[q][3]));
+    }
     sum = wave_sum(sum);
     if (lane == 0) s_sum[v * NW + wave] = sum;
   }
+  int top = most[0];
+#pragma unroll
+  for (int q = 1; q < Q; ++q) top = max(top, most[q]);
+  const int wave_top = wave_max(top);
+  if (lane == 0) s_key[wave] = wave_top;
+  __syncthreads();
+  int slice_top = s_key[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) slice_top = max(slice_top, s_key[w]);
+  const float least = __builtin_amdgcn_exp2f((float)slice_top * 1.1920928955078125e-07f - KEY_ERROR) - 1.f;   // of the best's x / t
+  const int bar = (int)((__builtin_amdgcn_logf(fmaxf(least, 0.0598f)) - KEY_ERROR - KEY_SLACK) * 8388608.f);
+  uint32_t todo = 0;   // entries (q, e) that any lane of the wavefront has to compute
+  if (wave_top >= bar) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (__builtin_amdgcn_ballot_w64(most[q] >= bar)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (__builtin_amdgcn_ballot_w64(key[q][e] >= bar)) todo |= 1u << (4 * q + e);
+      }
+  }
+  if (!(fabsf(mx) <= BOUND_MAX) || slice_top > KEY_MOST) todo = (uint32_t)((1ull << (4 * Q)) - 1);
+  float by = -INFINITY;
+  int bi = 0x7FFFFFFF;
+  for (; todo; todo &= todo - 1) {
+    const int at = __builtin_ctz(todo), i4 = beg4 + (at >> 2) * NT, e = at & 3;
+    if (i4 >= end4) continue;
+    const float z = __fmul_rn(lg[(int64_t)i4 * 4 + e], inv_t);
+    uint32_t rnd[4];
+    philox4x32_10((uint32_t)i4, pos, (uint32_t)sid, (uint32_t)(sid >> 32), k0, k1, rnd);
+    const uint32_t bits = e == 0 ? rnd[0] : e == 1 ? rnd[1] : e == 2 ? rnd[2] : rnd[3];
+    merge_best(by, bi, __fadd_rn(z, gumbel(bits)), i4 * 4 + e);
+  }
+  const float besty = wave_max(by);
+  const int besti = wave_min(by == besty ? bi : 0x7FFFFFFF);
   if (lane == 0) { s_besty[wave] = besty; s_besti[wave] = besti; }
   __syncthreads();
   if (threadIdx.x >= 64) return;
@@ -267,9 +298,10 @@ int launch_sample(const SampleParams &p, hipStream_t s) {
   if (p.vocab % 4) return -1;
   const int nslice = (p.vocab + SLICE - 1) / SLICE;
   // Few slices leave most of the chip idle whatever the workgroup does: 1024 threads of 8 entries each shorten
-  // the chain of a slice; with two workgroups per compute unit or more, 32 entries per thread share the fixed
-  // work (exact value of the lane's best entry, reductions) among more of them.
-  if ((int64_t)nslice * p.n < 512)
+  // the chain of a slice as long as all workgroups run at once (two per compute unit); beyond that, 32 entries per thread share the
+  // fixed work (reductions, the scan for candidates) among more of them.  1024 and 256 threads, whole call: 512 x 4096 7.7 and 9.0 us,
+  // 128 x 32000 10.5 and 12.7, 26 x 152064 10.1 both, 30 x 152064 11.1 and 10.3, 128 x 152064 26.6 and 21.4.
+  if ((int64_t)nslice * p.n <= 512)
     hipLaunchKernelGGL(sample_slice_kernel<1024>, dim3(nslice, p.n), dim3(1024), 0, s, p, nslice);
   else
     hipLaunchKernelGGL(sample_slice_kernel<256>, dim3(nslice, p.n), dim3(256), 0, s, p, nslice);

@@ -11,44 +11,56 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 namespace pl {
 
-// ---- wavefront reductions: 16 lanes by data-parallel primitives (a few cycles a step instead of an LDS
-// round trip), the four rows of 16 by shuffles; fixed order, every lane ends with the result -------------
+// ---- wavefront reductions: lanes of 16 by data-parallel primitives that the combining instruction reads through, the four
+// rows of 16 by row swaps (a few cycles a step, no LDS round trips); fixed order, every lane ends with the result -------------
+template <typename T>
+__device__ inline uint32_t lane_bits(T v) { return __builtin_bit_cast(uint32_t, v); }
 #ifdef __HIP_DEVICE_COMPILE__
-template <int CTRL>
-__device__ inline int dpp_i(int v) { return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false); }
-template <int CTRL>
-__device__ inline float dpp_f(float v) { return __builtin_bit_cast(float, dpp_i<CTRL>(__builtin_bit_cast(int, v))); }
+template <int CTRL, typename T>
+__device__ inline T dpp(T v) {   // (every lane has a source: the old value and the bounds play no part)
+  return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, (int)lane_bits(v), CTRL, 0xF, 0xF, true));
+}
+// op of a lane's value with that of the lane 16 (32) away
+template <typename T, typename F>
+__device__ inline T with_xor16(T v, F op) {
+  const auto r = __builtin_amdgcn_permlane16_swap(lane_bits(v), lane_bits(v), false, false);
+  const uint32_t a = r[0], b = r[1];
+  return op(__builtin_bit_cast(T, a), __builtin_bit_cast(T, b));
+}
+template <typename T, typename F>
+__device__ inline T with_xor32(T v, F op) {
+  const auto r = __builtin_amdgcn_permlane32_swap(lane_bits(v), lane_bits(v), false, false);
+  const uint32_t a = r[0], b = r[1];
+  return op(__builtin_bit_cast(T, a), __builtin_bit_cast(T, b));
+}
 #else
-template <int CTRL>
-__device__ inline int dpp_i(int v) { return v; }
-template <int CTRL>
-__device__ inline float dpp_f(float v) { return v; }
+template <int CTRL, typename T>
+__device__ inline T dpp(T v) { return v; }
+template <typename T, typename F>
+__device__ inline T with_xor16(T v, F op) { return op(v, v); }
+template <typename T, typename F>
+__device__ inline T with_xor32(T v, F op) { return op(v, v); }
 #endif
 constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
-__device__ inline float wave_sum(float v) {
-  v += dpp_f<DPP_XOR1>(v);
-  v += dpp_f<DPP_XOR2>(v);
-  v += dpp_f<DPP_HALF_MIRROR>(v);
-  v += dpp_f<DPP_MIRROR>(v);
-  v += __shfl_xor(v, 16, 64);
-  return v + __shfl_xor(v, 32, 64);
+struct OpSum { __device__ float operator()(float a, float b) const { return a + b; } };
+struct OpMax {
+  __device__ float operator()(float a, float b) const { return fmaxf(a, b); }
+  __device__ int operator()(int a, int b) const { return max(a, b); }
+};
+struct OpMin { __device__ int operator()(int a, int b) const { return min(a, b); } };
+template <typename T, typename F>
+__device__ inline T wave_reduce(T v, F op) {
+  v = op(v, dpp<DPP_XOR1>(v));
+  v = op(v, dpp<DPP_XOR2>(v));
+  v = op(v, dpp<DPP_HALF_MIRROR>(v));
+  v = op(v, dpp<DPP_MIRROR>(v));
+  v = with_xor16(v, op);
+  return with_xor32(v, op);
 }
-__device__ inline float wave_max(float v) {
-  v = fmaxf(v, dpp_f<DPP_XOR1>(v));
-  v = fmaxf(v, dpp_f<DPP_XOR2>(v));
-  v = fmaxf(v, dpp_f<DPP_HALF_MIRROR>(v));
-  v = fmaxf(v, dpp_f<DPP_MIRROR>(v));
-  v = fmaxf(v, __shfl_xor(v, 16, 64));
-  return fmaxf(v, __shfl_xor(v, 32, 64));
-}
-__device__ inline int wave_min(int v) {
-  v = min(v, dpp_i<DPP_XOR1>(v));
-  v = min(v, dpp_i<DPP_XOR2>(v));
-  v = min(v, dpp_i<DPP_HALF_MIRROR>(v));
-  v = min(v, dpp_i<DPP_MIRROR>(v));
-  v = min(v, __shfl_xor(v, 16, 64));
-  return min(v, __shfl_xor(v, 32, 64));
-}
+__device__ inline float wave_sum(float v) { return wave_reduce(v, OpSum{}); }
+__device__ inline float wave_max(float v) { return wave_reduce(v, OpMax{}); }
+__device__ inline int wave_max(int v) { return wave_reduce(v, OpMax{}); }
+__device__ inline int wave_min(int v) { return wave_reduce(v, OpMin{}); }
 
 // ---- KV page geometry (one layer, one page, one kv head: K block then V block) ---------------
 // Tokens of a page are grouped in runs of 32 (t = 32 r + u).  Both blocks are laid out so that the

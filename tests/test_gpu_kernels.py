@@ -489,6 +489,35 @@ def test_sampler_at_slice_and_launch_boundaries_with_masked_entries(n, V):
         assert abs(lp[r] - lp_ref) <= 1e-4 * max(1.0, abs(lp_ref))
 
 
+@pytest.mark.parametrize("n,V", [(10, 8), (10, 8196), (60, 152064)])
+def test_sampler_where_bounds_say_little_or_nothing(n, V):
+    """Rows in which the bounds on the noise decide little (one dominating logit, two far apart from the rest) and rows
+    beyond their use, where every entry is computed (large magnitudes, infinities, NaNs): the tokens of the definition."""
+    rng = np.random.default_rng(V + 3 * n)
+    logits = (rng.standard_normal((n, V)) * 2).astype(np.float32)
+    at = rng.integers(0, V, n)
+    logits[0, at[0]] = 30.0                     # the others are e^-30 of it
+    logits[1, at[1]] = 300.0                    # e^-300 = 0 in fp32
+    logits[2, at[2]], logits[2, (at[2] + V // 2) % V] = 40.0, 40.5
+    logits[3] += np.float32(1000.0)             # on both sides of the largest magnitude that the bounds are used for
+    logits[4] -= np.float32(1030.0)
+    logits[5] *= np.float32(3000.0)
+    logits[6] = np.float32(65536.0)             # the sum with the noise keeps two binary places
+    logits[7, [at[7], V - 1]] = np.inf
+    logits[8, ::2] = np.nan
+    logits[9] = -np.inf
+    seq_id = rng.integers(0, 2**63, size=n, dtype=np.uint64)
+    pos = rng.integers(0, 16384, size=n).astype(np.int32)
+    tok, lp = _gpu_sample(logits, seq_id, pos, np.ones(n, np.float32), np.full(n, -1, np.int32), 99)
+    for r in range(10):
+        z = np.where(np.isnan(logits[r]), -np.inf, logits[r])     # a NaN is never drawn
+        t_ref = sampler.sample_row(z, 1.0, 99, int(seq_id[r]), int(pos[r]), -1)[0] if r not in (7, 9) else int(np.argmax(z))
+        assert tok[r] == t_ref, (r, tok[r], t_ref)
+        if r < 7:
+            lp_ref = sampler.log_softmax(logits[r])[tok[r]]
+            assert abs(lp[r] - lp_ref) <= 1e-4 * max(1.0, abs(lp_ref))
+
+
 @pytest.mark.parametrize("few,many,V", [(26, 27, 152064), (511, 512, 4096), (127, 128, 32000), (3, 300, 8200)])
 def test_a_row_is_sampled_alike_whatever_rows_share_the_call(few, many, V):
     """Both sides of the choice of threads per slice: the same rows' tokens and log-probs are bit-identical."""
