@@ -32,7 +32,9 @@ namespace {
 constexpr int SUB_RUNS = ATTN_SUB / 32;
 typedef __attribute__((address_space(4))) int32_t scalar_i32;   // read by scalar loads
 
-__device__ inline float shfl_xor(float v, int mask) { return __shfl_xor(v, mask, 64); }
+// of the four lanes that hold a column's tokens
+__device__ inline float column_sum(float v) { return with_xor32(with_xor16(v, OpSum{}), OpSum{}); }
+__device__ inline float column_max(float v) { return with_xor32(with_xor16(v, OpMax{}), OpMax{}); }
 
 // (m, l, o) <- (m, l, o) folded with a later part (mi, li, oi); m is in log2 units.  A part without tokens
 // has mi = -inf and changes nothing; the first part is taken over as it is.
@@ -62,6 +64,25 @@ __device__ inline void fold_part(float &m, float &l, V &o, float mi, float li, V
   o = fold_value(o, e0, oi, e1);
   l = fold_value(l, e0, li, e1);
   m = M;
+}
+
+// One run of scores, 8 per lane: its largest, and its exponentials relative to m with their sum.
+__device__ inline float run_max(const float (&s)[8]) {
+  float v = s[0];
+#pragma unroll
+  for (int e = 1; e < 8; ++e) v = fmaxf(v, s[e]);
+  return column_max(v);
+}
+__device__ inline bf16x8 run_exp(const float (&s)[8], float m, float &sum) {
+  bf16x8 p;
+  sum = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float v = __builtin_amdgcn_exp2f(s[e] - m);
+    sum += v;
+    p[e] = (__bf16)v;
+  }
+  return p;
 }
 
 // Values that another workgroup of the same launch reads: written through to the memory all XCDs share and
@@ -303,8 +324,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
   float m_all = -INFINITY, l_all = 0.f;
   bool folded = false;
   auto fold_sub = [&](bool first) {
-    lsum += shfl_xor(lsum, 16);
-    lsum += shfl_xor(lsum, 32);
+    lsum = column_sum(lsum);
     float *mine = &sm_o[wave][head][qg * 4];
     if (first) {
       if (head < G) {
@@ -345,35 +365,26 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
           load_k(st, nb);
           page_next[st] = nxt + 4 * NS < nblk ? page_of(nxt + 4 * NS) : 0;
         }
-        const int tbase = t0 + blk * 32 + qg * 8;
         float s[8];
-        float mb = -INFINITY;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          float v = s4[e >> 2][e & 3] * scale;
-          v = (tbase + e < t1) ? v : -INFINITY;
-          s[e] = v;
-          mb = fmaxf(mb, v);
+        for (int e = 0; e < 8; ++e) s[e] = s4[e >> 2][e & 3] * scale;
+        if (t0 + blk * 32 + 32 > t1) {   // the item's last run
+          const int left = t1 - (t0 + blk * 32 + qg * 8);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) s[e] = e < left ? s[e] : -INFINITY;
         }
-        mb = fmaxf(mb, shfl_xor(mb, 16));
-        mb = fmaxf(mb, shfl_xor(mb, 32));
-        const float m_new = fmaxf(m, mb);
+        const float m_new = fmaxf(m, run_max(s));
         const float alpha = __builtin_amdgcn_exp2f(m - m_new);
-        float psum = 0.f;
-        bf16x8 pf;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          float pe = __builtin_amdgcn_exp2f(s[e] - m_new);
-          psum += pe;
-          pf[e] = (__bf16)pe;
-        }
+        float psum;
+        const bf16x8 pf = run_exp(s, m_new, psum);
         lsum = __builtin_fmaf(lsum, alpha, psum);
         m = m_new;
+        if (__builtin_amdgcn_ballot_w64(!(alpha == 1.f))) {   // a maximum has moved (a factor of 1 changes nothing)
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-          o[i] *= alpha;
-          o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[st][i], pf, o[i], 0, 0, 0);
+          for (int i = 0; i < NV; ++i) o[i] *= alpha;
         }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[st][i], pf, o[i], 0, 0, 0);
         if (nb) load_v(st, nb);
       }
     }
@@ -389,8 +400,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnParams p) {
   }
 
   if (p.item_tokens < p.chunk && ctx > p.item_tokens) {   // an item is one sub: the wavefronts' results, for the merge kernel
-    lsum += shfl_xor(lsum, 16);
-    lsum += shfl_xor(lsum, 32);
+    lsum = column_sum(lsum);
     const int64_t part = ((int64_t)item * p.Hkv + g) * 4 + wave;
     if (head < G) {
 #pragma unroll
@@ -514,8 +524,9 @@ __global__ __launch_bounds__(HD) void attn_merge_kernel(AttnParams p) {
 // (as in a decode step) reads the sequence once per row.  Operation by operation the same sums as the decode kernel
 // for every row: runs, subs, wavefronts and chunks in the same order; a run that lies beyond a row's positions
 // leaves its column as it was (factor 1, product not taken: 0 times an infinity would not be 0).
-// Bound by vector arithmetic (about 100 operations per run and column block), then by L2.  3001-token prompt, 1.5B
-// shape: 960 -> 375 us over the twelve launches of its passes; 512-token prompt, 7B shape: 79 -> 57 us.
+// Bound by vector arithmetic (about 80 operations per run and column block; positions are masked only in runs that some row
+// does not see whole), then by L2.  3001-token prompt, 1.5B shape, the nine launches of its passes: 346 us, 365 with
+// every run masked, maxima by shuffles through LDS and page ids by vector loads; 960 row by row.
 template <int HD, int CB>
 __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnParams p) {
   constexpr int NJ = HD / 32, NV = HD / 16, COLS = CB * 16, PER = COLS * HD / 1024;
@@ -523,7 +534,8 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnParams p) {
   if (index < 0) return;
   const int row0 = p.groups[2 + 2 * index], nrows = p.groups[3 + 2 * index];
   const int G = p.Hq / p.Hkv, rpb = 16 / G;   // rows of a column block
-  const int32_t *pt = p.page_table + (int64_t)p.row_slot[row0] * p.pages_per_seq;
+  // (constant address space: the loop's stores to LDS would turn the page ids into vector loads that wait for the keys in flight)
+  const scalar_i32 *pt = (const scalar_i32 *)(p.page_table + (int64_t)p.row_slot[row0] * p.pages_per_seq);
   const int ctx0 = p.ctx_len[row0], ctx_max = ctx0 + nrows - 1;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, col = l & 15, qg = l >> 4;
   const float scale = 1.4426950408889634f / sqrtf((float)HD);   // log2(e) / sqrt(hd)
@@ -592,8 +604,7 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnParams p) {
     auto fold_sub = [&]() {
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
-        lsum[cb] += shfl_xor(lsum[cb], 16);
-        lsum[cb] += shfl_xor(lsum[cb], 32);
+        lsum[cb] = column_sum(lsum[cb]);
         float *mine = &sm_o[wave][cb * 16 + col][qg * 4];
         if (!folded) {
 #pragma unroll
@@ -628,29 +639,21 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnParams p) {
       }
       const bf16_t *nb = run_at(blk + 4 < nblk ? t0 + (blk + 4) * 32 : t0 + p.chunk + wave * 32);   // (of the next chunk)
       load_k(nb);
-      const int tbase = t0 + blk * 32 + qg * 8;
+      const bool whole = t0 + blk * 32 + 32 <= ctx0;   // every row sees every position of the run
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
-        float s[8], mb = -INFINITY;
+        float s[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          float v = s4[cb][e >> 2][e & 3] * scale;
-          v = (tbase + e < ctx[cb]) ? v : -INFINITY;
-          s[e] = v;
-          mb = fmaxf(mb, v);
+        for (int e = 0; e < 8; ++e) s[e] = s4[cb][e >> 2][e & 3] * scale;
+        if (!whole) {
+          const int left = ctx[cb] - (t0 + blk * 32 + qg * 8);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) s[e] = e < left ? s[e] : -INFINITY;
         }
-        mb = fmaxf(mb, shfl_xor(mb, 16));
-        mb = fmaxf(mb, shfl_xor(mb, 32));
-        const float m_new = fmaxf(m[cb], mb), m_ref = m_new == -INFINITY ? 0.f : m_new;
+        const float m_new = fmaxf(m[cb], run_max(s)), m_ref = m_new == -INFINITY ? 0.f : m_new;
         const float alpha = __builtin_amdgcn_exp2f(m[cb] - m_ref);
-        float psum = 0.f;
-        bf16x8 pf;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float pe = __builtin_amdgcn_exp2f(s[e] - m_ref);
-          psum += pe;
-          pf[e] = (__bf16)pe;
-        }
+        float psum;
+        const bf16x8 pf = run_exp(s, m_ref, psum);
         lsum[cb] = __builtin_fmaf(lsum[cb], alpha, psum);
         m[cb] = m_new;
         if (__builtin_amdgcn_ballot_w64(!(alpha == 1.f))) {   // a maximum has moved (a factor of 1 changes nothing)
