@@ -3,8 +3,8 @@
 // With M = batch <= 256 rows these products are bound by streaming W once from HBM; W is never
 // reused across workgroups, so it bypasses LDS: every wavefront loads the W rows it owns straight
 // into MFMA B-operand registers.  W is stored in operand order (blocks of 32 rows x 64 k, see
-// pl_weight_layout in pl.h), so each of those loads is one contiguous KiB per wavefront.  The small activation tile x is what all workgroups share; it is staged through LDS
-// (padded rows, conflict-free 16-byte reads) and feeds the A operand.  32x32x16 bf16 MFMAs
+// pl_weight_layout in pl.h), so each of those loads is one contiguous KiB per wavefront.  The small activation tile x is what all
+// workgroups share; it goes to LDS by direct loads and feeds the other operand.  32x32x16 bf16 MFMAs
 // accumulate in fp32.  K can be split across workgroups (partials summed by the consumer in a
 // fixed order) so that narrow outputs still occupy every compute unit.
 #include "pl_common.h"
@@ -16,7 +16,8 @@ namespace pl {
 namespace {
 
 constexpr int BK = 64;          // k elements per main-loop step
-constexpr int LDS_ROW = 72;     // padded row length (elements) of the x tile in LDS
+constexpr int STAGES = 4;       // k-steps held: one is multiplied while three are on their way
+typedef __attribute__((address_space(3))) void lds_void;
 // Cache policy of the W loads: non-temporal (2) for weights that are COLD, that is, cannot be in the 256 MB last-level cache
 // from the pass before, in tiles whose W one wavefront reads (WM = 1): they have no second reader, and ordinary loads
 // evict each other from L2 on the way.  SwiGLU of the 32B shape, 128 rows: 111.8 -> 98.7 us (5.7 TB/s); 7B shape, 19 rows,
@@ -27,154 +28,234 @@ constexpr int LDS_ROW = 72;     // padded row length (elements) of the x tile in
 template <int WM, bool COLD>
 constexpr int W_CACHE = WM == 1 && COLD ? 2 : 0;
 
-// Workgroup = 4 wavefronts arranged WM x WN; each owns (AT*32) x (BT*32) outputs.
-// Software pipeline: W fragments live in a 4-deep register ring (loads run three k-steps ahead of
-// the MFMAs that consume them, which is what hides HBM latency with one wavefront per SIMD); the x
-// tile runs two k-steps ahead through a 2-deep register stage and a double-buffered LDS tile.
-// Within a k-step the x loads are issued before the W loads, so waiting for an x tile (in-order
-// completion) never waits for the younger W loads.
-//
-// gemm_tile computes one tile (column tile at n_tile0, rows from m0, K slice `split`) with the whole
-// workgroup; the kernels below are thin wrappers that pick the tile(s) of a workgroup.
-// FOLD: all K slices of `ksteps` k-steps in one go: every slice's sum starts from zero and is added to the
-// running total in slice order, so the one result equals the sum a consumer makes of separate slices bit for bit.
-template <int WM, int WN, int AT, int BT, int MODE, bool COLD, bool FOLD = false>
-__device__ __forceinline__ void gemm_tile(bf16_t (*xs)[WM * AT * 32 * LDS_ROW], const bf16_t *__restrict__ X,
-                                          const bf16_t *__restrict__ W, void *__restrict__ Yv, int M, int N, int K,
-                                          int ksteps, int n_tile0, int m0, int split, int n_end, int ldy, int y_col0) {
-  constexpr int BM = WM * AT * 32;
-  constexpr int XCH = BM * (BK / 8) / 256;       // 16-byte chunks of the x tile per thread
-  static_assert(WM * WN == 4 && XCH >= 1, "tile");
-  const int tid = threadIdx.x, l = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: keeps W offsets in scalar registers
-  const int wm = wave / WN, wn = wave % WN;
-  const int n0 = n_tile0 + wn * BT * 32;
-  const int kbeg = split * ksteps * BK;
-  const int nks = FOLD ? K / BK : min(ksteps, K / BK - split * ksteps);
-  const int lrow = l & 31, half = l >> 5;
+// A tile of the product: a workgroup of 4 wavefronts arranged WM x WN, each of which owns (AT*32) x (BT*32) outputs.
+// W fragments go from memory to a ring of register stages, x tiles by direct loads to a ring of LDS stages (no registers
+// and no store instructions on the way), both three k-steps ahead of the products that use them; nothing waits for
+// younger loads, as loads complete in order and each wait names the number that may stay in flight.  What bounds a k-step is the
+// larger of its MFMA time and of its bytes at what one compute unit gets from the caches (about 100 KB/us from L2, 45
+// from HBM): cycles per k-step of a lone workgroup with W in L2, and of its MFMAs alone, 256x256 2260 and 2048, 128x256 1100 and 1024,
+// 128x128 790 and 512 (with x through registers, a double-buffered LDS tile and a full wait at each barrier: 128x256 1680).
+// On the full chip with random operands the clock settles so that about 1.5 PFLOP/s are left at the margin (256x256 tiles, 1024 rows:
+// 1.42 us per k-step, 1.01 with operands of zeros).
+// Row r of an LDS stage holds its eight 16-byte chunks at slots chunk ^ (r & 7): a direct load fills a KiB in lane order, 8 whole rows,
+// and the reads of a fragment (one chunk of 32 rows) meet every bank once.
+// The products are taken with W as the first operand: a lane ends with one row and groups of four consecutive columns.
+template <int WM, int WN, int AT, int BT, bool COLD>
+struct Tile {
+  static constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
+  static constexpr int XI = BM / 32, XH = (XI + 1) / 2, WI = BT * 4;   // loads of a wavefront per k-step: x (half of them XH), W
+  static constexpr int STAGE = BM * BK, LDS = STAGES * STAGE;          // elements
+  static_assert(WM * WN == 4 && BT <= 2, "tile");
 
-  // Buffer addressing: one resource per operand, a per-lane byte offset in a VGPR, everything that
-  // is uniform across the wavefront in scalar registers; rows of x at or beyond M read as zeros.
-  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)W, 0, (int)((int64_t)N * K * 2), 0x00020000);
-  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)X, 0, (int)((int64_t)M * K * 2), 0x00020000);
-  // operand-ordered W: block (k-step, n / 32) is 4096 bytes: [j][lane][16 B], lane = half * 32 + row.
+  // where a tile's operands are
+  struct Part {
+    int x_lane[XI];        // per lane: byte offset of its row and chunk (rows beyond M repeat the last one)
+    int x_k;               // byte offset of the first k
+    uint32_t w_blk[BT];    // byte offset of the first W block
+  };
+  // Operand-ordered W: block (k-step, n / 32) is 4096 bytes: [j][lane][16 B], lane = half * 32 + row.
   // Blocks are k-step-major: workgroups walk K in step, so at any moment the whole chip reads one
   // contiguous plane of W and the traffic spreads over every HBM channel (with row-block-major
   // order all streams sit a multiple of 8 blocks apart and camp on a fraction of the channels).
-  const int w_lane = l * 16;
-  const uint32_t w_plane = (uint32_t)(N >> 5) * 4096u;
-  uint32_t w_blk[BT];
-#pragma unroll
-  for (int bt = 0; bt < BT; ++bt)
-    w_blk[bt] = (uint32_t)(split * ksteps) * w_plane + (uint32_t)min((n0 >> 5) + bt, (N >> 5) - 1) * 4096u;
-  // x tile: 16-byte chunk ch = tid + 256 i is row ch / 8, k columns (ch % 8) * 8
-  const int x_lane = ((m0 + (tid >> 3)) * K + kbeg + (tid & 7) * 8) * 2;
-  const int x_lds = (tid >> 3) * LDS_ROW + (tid & 7) * 8;
-
+  __amdgpu_buffer_rsrc_t rw, rx;   // one resource per operand; what is uniform across a wavefront is in scalar registers
+  uint32_t w_plane;
+  int wave, wm, wn, l, lrow, half, a_off[4];
+  bf16_t *xs;
   f32x16 acc[AT][BT];
+  bf16x8 wf[STAGES][BT][4], af[2][AT];
+
+  __device__ __forceinline__ void init(bf16_t *xs_, const bf16_t *X, const bf16_t *W, int M, int N, int K) {
+    xs = xs_;
+    l = threadIdx.x & 63;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    wm = wave / WN; wn = wave % WN;
+    lrow = l & 31; half = l >> 5;
+    w_plane = (uint32_t)(N >> 5) * 4096u;
+    rw = __builtin_amdgcn_make_buffer_rsrc((void *)W, 0, (int)((int64_t)N * K * 2), 0x00020000);
+    rx = __builtin_amdgcn_make_buffer_rsrc((void *)X, 0, (int)((int64_t)M * K * 2), 0x00020000);
 #pragma unroll
-  for (int a = 0; a < AT; ++a)
+    for (int j = 0; j < 4; ++j) a_off[j] = (wm * AT * 32 + lrow) * BK + ((half * 4 + j) ^ (lrow & 7)) * 8;
+  }
+  __device__ __forceinline__ Part part(int n_tile0, int m0, int ks0, int M, int N, int K) const {
+    Part p;
+#pragma unroll
+    for (int i = 0; i < XI; ++i)
+      p.x_lane[i] = (min(m0 + (wave * XI + i) * 8 + (l >> 3), M - 1) * K + ((l & 7) ^ (l >> 3)) * 8) * 2;
+    p.x_k = ks0 * BK * 2;
 #pragma unroll
     for (int b = 0; b < BT; ++b)
+      p.w_blk[b] = (uint32_t)ks0 * w_plane + (uint32_t)min(((n_tile0 + wn * BT * 32) >> 5) + b, (N >> 5) - 1) * 4096u;
+    return p;
+  }
+  __device__ __forceinline__ void zero() {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-
-  bf16x8 wf[4][BT][4], xr[2][XCH];
-  auto load_w = [&](int stage, int ks) {
+    for (int a = 0; a < AT; ++a)
 #pragma unroll
-    for (int bt = 0; bt < BT; ++bt)
+      for (int b = 0; b < BT; ++b)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        wf[stage][bt][j] = __builtin_bit_cast(
-            bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, w_lane + j * 1024, (int)(w_blk[bt] + (uint32_t)ks * w_plane), W_CACHE<WM, COLD>));
-  };
-  auto load_x = [&](int stage, int ks) {
+        for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+  }
+  __device__ __forceinline__ void load_x(const Part &p, int st, int ks, int i0, int i1) {
+#ifdef __HIP_DEVICE_COMPILE__
 #pragma unroll
-    for (int i = 0; i < XCH; ++i)
-      xr[stage][i] = __builtin_bit_cast(
-          bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rx, x_lane, ks * (BK * 2) + i * 64 * K, 0));
-  };
-  auto store_x = [&](int stage, int buf) {
+    for (int i = i0; i < i1; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(xs + st * STAGE + (wave * XI + i) * 512), 16, p.x_lane[i], p.x_k + ks * (BK * 2), 0, 0);
+#endif
+  }
+  __device__ __forceinline__ void load_w(const Part &p, int st, int ks, int b) {
 #pragma unroll
-    for (int i = 0; i < XCH; ++i) *(bf16x8 *)(&xs[buf][x_lds + i * 32 * LDS_ROW]) = xr[stage][i];
-  };
-
-  // nks is a multiple of 4 and at least 4 (the host splits K in units of 4 k-steps)
-  load_x(0, 0);
-  load_w(0, 0);
-  load_x(1, 1);
-  load_w(1, 1);
-  load_w(2, 2);
-  store_x(0, 0);
-  __syncthreads();
-
-  const int a_off = (wm * AT * 32 + lrow) * LDS_ROW + half * 32;
-  // one k-step: u = k-step index mod 4 (compile time), LX/LW/SX say which transfers are still needed
-  // Scheduling-group fences: the loads and LDS stores of a k-step are issued one at a time between
-  // MFMAs instead of in a burst, so the memory pipeline fills while the matrix pipeline stays busy.
-#define PL_SG_MFMA 0x008
-#define PL_SG_VMEM_READ 0x020
-#define PL_SG_DS_WRITE 0x200
-  auto kstep = [&](auto U, auto LX, auto LW, auto SX, int ks) {
-    constexpr int u = decltype(U)::value;
-    // A fragments are read from LDS two 16-wide k-slices ahead of the MFMAs that use them (a
-    // 2-deep register ring); the fences pin that order.
-    bf16x8 af[2][AT];
-    auto read_a = [&](int j) {
+    for (int j = 0; j < 4; ++j)
+      wf[st][b][j] = __builtin_bit_cast(
+          bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, l * 16 + j * 1024, (int)(p.w_blk[b] + (uint32_t)ks * w_plane), W_CACHE<WM, COLD>));
+  }
+  __device__ __forceinline__ void load(const Part &p, int st, int ks) {
+    load_x(p, st, ks, 0, XI);
 #pragma unroll
-      for (int a = 0; a < AT; ++a) af[j & 1][a] = *(const bf16x8 *)(&xs[u & 1][a_off + a * 32 * LDS_ROW + j * 8]);
-    };
-    auto mma = [&](int j) {
+    for (int b = 0; b < BT; ++b) load_w(p, st, ks, b);
+  }
+  __device__ __forceinline__ void read_a(int st, int j) {
 #pragma unroll
-      for (int a = 0; a < AT; ++a)
+    for (int a = 0; a < AT; ++a) af[j & 1][a] = *(const bf16x8 *)(xs + st * STAGE + a_off[j] + a * 32 * BK);
+  }
+  __device__ __forceinline__ void mma(int st, int j) {
 #pragma unroll
-        for (int b = 0; b < BT; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[j & 1][a], wf[u][b][j], acc[a][b], 0, 0, 0);
-    };
-    read_a(0);
-    read_a(1);
+    for (int a = 0; a < AT; ++a)
+#pragma unroll
+      for (int b = 0; b < BT; ++b)
+        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[st][b][j], af[j & 1][a], acc[a][b], 0, 0, 0);
+  }
+  // all but the LEFT youngest loads have arrived, and this wavefront has its operands out of LDS; then the others too
+  template <int LEFT>
+  __device__ __forceinline__ void meet() {
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"i"(LEFT) : "memory");
+    __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (decltype(LX)::value) load_x(u & 1, ks + 2);     // x before W: waiting for x never waits for W
-    mma(0);
-    if constexpr (decltype(LX)::value) {
+#endif
+  }
+  // Issue order of a quarter of a k-step: LDS reads (for the next quarter) and VM loads one by one between the products.
+  template <int VM, bool READS>
+  __device__ __forceinline__ void order() {
+    constexpr int per = VM >= AT ? VM / AT : 1;
 #pragma unroll
-      for (int i = 0; i < XCH; ++i) {
-        __builtin_amdgcn_sched_group_barrier(PL_SG_MFMA, (AT * BT) / XCH > 0 ? (AT * BT) / XCH : 1, 0);
-        __builtin_amdgcn_sched_group_barrier(PL_SG_VMEM_READ, 1, 0);
+    for (int i = 0; i < AT; ++i) {
+      if (READS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, BT, 0);
+      if (VM >= AT || i * VM / AT != (i + 1) * VM / AT) __builtin_amdgcn_sched_group_barrier(0x020, per, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // First three k-steps of a part into stages 0 .. 2, and the first operands out of LDS.
+  __device__ __forceinline__ void begin(const Part &p) {
+#pragma unroll
+    for (int st = 0; st < STAGES - 1; ++st) load(p, st, st);
+    meet<2 * (XI + WI) + WI>();
+    read_a(0, 0);
+  }
+  // One k-step in stage U (k-step index mod 4).  LOAD: k-step ks of part p goes to the stage that the last one freed.
+  // AFTER: k-steps that follow (3: three or more), whose loads stay in flight while the next stage is waited for.
+  // The operands of the last quarter are read before that wait, those of the next k-step's first quarter behind it, so that the matrix
+  // pipeline has a quarter's products to work on meanwhile.
+  template <int U, bool LOAD, int AFTER>
+  __device__ __forceinline__ void kstep(const Part &p, int ks) {
+    constexpr int TO = (U + 3) & 3;
+    read_a(U, 1);
+    if (LOAD) load_x(p, TO, ks, 0, XH);
+    mma(U, 0);
+    order<LOAD ? XH : 0, true>();
+    read_a(U, 2);
+    if (LOAD) load_x(p, TO, ks, XH, XI);
+    mma(U, 1);
+    order<LOAD ? XI - XH : 0, true>();
+    read_a(U, 3);
+    if (LOAD) load_w(p, TO, ks, 0);
+    mma(U, 2);
+    order<LOAD ? 4 : 0, true>();
+    if (AFTER > 0) {
+      meet<AFTER == 1 ? WI : AFTER == 2 ? XI + 2 * WI : 2 * (XI + WI) + 4>();
+      read_a((U + 1) & 3, 0);
+    }
+    if (LOAD && BT > 1) load_w(p, TO, ks, BT - 1);
+    mma(U, 3);
+    if (AFTER > 0) {
+#pragma unroll
+      for (int i = 0; i < AT; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, BT, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        if (LOAD && BT > 1 && (4 >= AT || i * 4 / AT != (i + 1) * 4 / AT)) __builtin_amdgcn_sched_group_barrier(0x020, 4 >= AT ? 4 / AT : 1, 0);
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    read_a(2);
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (decltype(LW)::value) load_w((u + 3) & 3, ks + 3);
-    mma(1);
-    if constexpr (decltype(LW)::value) {
+  }
+  // k-steps ks .. ks + 3 of a part of more than ks + 7, and its last four
+  __device__ __forceinline__ void four(const Part &p, int ks) {
+    kstep<0, true, 3>(p, ks + 3);
+    kstep<1, true, 3>(p, ks + 4);
+    kstep<2, true, 3>(p, ks + 5);
+    kstep<3, true, 3>(p, ks + 6);
+  }
+  __device__ __forceinline__ void last_four(const Part &p, int ks) {
+    kstep<0, true, 3>(p, ks + 3);
+    kstep<1, false, 2>(p, 0);
+    kstep<2, false, 1>(p, 0);
+    kstep<3, false, 0>(p, 0);
+  }
+  // accumulator register i of lane l is column (i / 4) * 8 + (l / 32) * 4 + i % 4, row l % 32
+  // fp32 sums: row stride ldy, columns counted from y_col0, columns below n_end (a multiple of 32)
+  __device__ __forceinline__ void store(float *Y, int n_tile0, int m0, int M, int n_end, int64_t ldy, int y_col0) const {
+    const int n0 = n_tile0 + wn * BT * 32;
 #pragma unroll
-      for (int i = 0; i < BT * 4; ++i) {
-        __builtin_amdgcn_sched_group_barrier(PL_SG_MFMA, (AT * BT) / (BT * 4) > 0 ? (AT * BT) / (BT * 4) : 1, 0);
-        __builtin_amdgcn_sched_group_barrier(PL_SG_VMEM_READ, 1, 0);
+    for (int a = 0; a < AT; ++a) {
+      const int m = m0 + (wm * AT + a) * 32 + lrow;
+      if (m >= M) continue;
+#pragma unroll
+      for (int b = 0; b < BT; ++b) {
+        if (n0 + b * 32 >= n_end) continue;
+        float *y = Y + m * ldy + (n0 + b * 32 + half * 4 - y_col0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          *(f32x4 *)(y + i * 8) = f32x4{acc[a][b][4 * i], acc[a][b][4 * i + 1], acc[a][b][4 * i + 2], acc[a][b][4 * i + 3]};
       }
     }
-    __builtin_amdgcn_sched_barrier(0);
-    read_a(3);
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (decltype(SX)::value) store_x((u + 1) & 1, (u + 1) & 1);
-    mma(2);
-    mma(3);
-    if constexpr (decltype(SX)::value) {
+  }
+  // SwiGLU: the two column tiles of a wavefront are the gate and the up half of a 64-row block
+  __device__ __forceinline__ void store_swiglu(bf16_t *Y, int n_tile0, int m0, int M, int n_end, int N) const {
+    const int n0 = n_tile0 + wn * BT * 32;
+    if (n0 >= n_end) return;
 #pragma unroll
-      for (int i = 0; i < XCH; ++i) {
-        __builtin_amdgcn_sched_group_barrier(PL_SG_MFMA, (2 * AT * BT) / XCH > 0 ? (2 * AT * BT) / XCH : 1, 0);
-        __builtin_amdgcn_sched_group_barrier(PL_SG_DS_WRITE, 1, 0);
+    for (int a = 0; a < AT; ++a) {
+      const int m = m0 + (wm * AT + a) * 32 + lrow;
+      if (m >= M) continue;
+      bf16_t *y = Y + (int64_t)m * (N / 2) + (n0 >> 1) + half * 4;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float gte = acc[a][0][4 * i + e], up = acc[a][BT - 1][4 * i + e];
+          const float sv = gte / (1.f + __expf(-gte));
+          o[e] = (__bf16)(sv * up);
+        }
+        *(bf16x4 *)(y + i * 8) = o;
       }
     }
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();
-  };
-  using I0 = std::integral_constant<int, 0>; using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, 2>; using I3 = std::integral_constant<int, 3>;
-  using Y = std::true_type; using No = std::false_type;
-  int ks = 0;
+  }
+};
+
+// One tile (column tile at n_tile0, rows from m0, K slice `split`) with the whole workgroup; the kernels below are thin
+// wrappers that pick the tile(s) of a workgroup.  K slices are multiples of four k-steps (the host sees to it).
+// FOLD: all K slices of `ksteps` k-steps in one go: every slice's sum starts from zero and is added to the
+// running total in slice order, so the one result equals the sum a consumer makes of separate slices bit for bit.
+template <int WM, int WN, int AT, int BT, int MODE, bool COLD, bool FOLD = false>
+__device__ __forceinline__ void gemm_tile(bf16_t *xs, const bf16_t *__restrict__ X,
+                                          const bf16_t *__restrict__ W, void *__restrict__ Yv, int M, int N, int K,
+                                          int ksteps, int n_tile0, int m0, int split, int n_end, int ldy, int y_col0) {
+  Tile<WM, WN, AT, BT, COLD> t;
+  t.init(xs, X, W, M, N, K);
+  const int nks = FOLD ? K / BK : min(ksteps, K / BK - split * ksteps);
+  const auto p = t.part(n_tile0, m0, split * ksteps, M, N, K);
+  t.zero();
+  t.begin(p);
   f32x16 tot[FOLD ? AT : 1][FOLD ? BT : 1];
   int slice_end = ksteps;
   if constexpr (FOLD) {
@@ -192,255 +273,55 @@ __device__ __forceinline__ void gemm_tile(bf16_t (*xs)[WM * AT * 32 * LDS_ROW], 
 #pragma unroll
         for (int b = 0; b < BT; ++b)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) { tot[a][b][i] += acc[a][b][i]; acc[a][b][i] = 0.f; }
+          for (int i = 0; i < 16; ++i) { tot[a][b][i] += t.acc[a][b][i]; t.acc[a][b][i] = 0.f; }
     }
   };
+  int ks = 0;
   for (; ks < nks - 4; ks += 4) {
     if (FOLD && ks == slice_end) { fold(); slice_end += ksteps; }
-    kstep(I0{}, Y{}, Y{}, Y{}, ks);
-    kstep(I1{}, Y{}, Y{}, Y{}, ks + 1);
-    kstep(I2{}, Y{}, Y{}, Y{}, ks + 2);
-    kstep(I3{}, Y{}, Y{}, Y{}, ks + 3);
+    t.four(p, ks);
   }
   if (FOLD && ks == slice_end) fold();
-  kstep(I0{}, Y{}, Y{}, Y{}, ks);
-  kstep(I1{}, Y{}, No{}, Y{}, ks + 1);
-  kstep(I2{}, No{}, No{}, Y{}, ks + 2);
-  kstep(I3{}, No{}, No{}, No{}, ks + 3);
+  t.last_four(p, ks);
   if constexpr (FOLD) {
 #pragma unroll
     for (int a = 0; a < AT; ++a)
 #pragma unroll
       for (int b = 0; b < BT; ++b)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[a][b][i] += tot[a][b][i];
+        for (int i = 0; i < 16; ++i) t.acc[a][b][i] += tot[a][b][i];
   }
-
-  // epilogue: accumulator register i of lane l is row (i/4)*8 + (l/32)*4 + i%4, column l%32
-#pragma unroll
-  for (int a = 0; a < AT; ++a) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int m = m0 + wm * AT * 32 + a * 32 + (i >> 2) * 8 + half * 4 + (i & 3);
-      if (m >= M) continue;
-      if (MODE == 0) {
-        // partial sums of slice `split`: row stride ldy, columns counted from y_col0
-        float *Y = (float *)Yv + ((int64_t)split * M + m) * ldy - y_col0;
-#pragma unroll
-        for (int b = 0; b < BT; ++b) {
-          int n = n0 + b * 32 + lrow;
-          if (n < n_end) Y[n] = acc[a][b][i];
-        }
-      } else {
-        // SwiGLU: the two column tiles of a wavefront are the gate and the up half of a 64-row block
-        bf16_t *Y = (bf16_t *)Yv + (int64_t)m * (N / 2);
-        int n = n0 + lrow;
-        if (n < n_end) {
-          float gte = acc[a][0][i], up = acc[a][BT - 1][i];
-          float sv = gte / (1.f + __expf(-gte));
-          Y[(n0 >> 1) + lrow] = (__bf16)(sv * up);
-        }
-      }
-    }
-  }
+  if constexpr (MODE == 0) t.store((float *)Yv + (int64_t)split * M * ldy, n_tile0, m0, M, n_end, ldy, y_col0);
+  else t.store_swiglu((bf16_t *)Yv, n_tile0, m0, M, n_end, N);
 }
 
 // Two tiles back to back in one workgroup without draining the pipeline between them: tile A (all of
 // K, SwiGLU epilogue into mid, columns below n_main) and then K slice `split` of tile B (fp32 partial
 // sums into ws, as gemm_tile<MODE 0> writes them).  The last k-steps of A, which have nothing of their
-// own left to load, issue the first loads of B into the ring slots they free, so B starts with its
-// operands already on the way while A's epilogue runs.  Same k order per output element as gemm_tile.
-// K / BK and B's k-step count are multiples of 4 and at least 4.
+// own left to load, issue the first loads of B, so B starts with its operands already on the way while A's epilogue
+// runs.  Same k order per output element as gemm_tile.
 template <int WM, int WN, int AT, int BT, bool COLD>
-__device__ __forceinline__ void gemm_tile2(bf16_t (*xs)[WM * AT * 32 * LDS_ROW], const bf16_t *__restrict__ X,
+__device__ __forceinline__ void gemm_tile2(bf16_t *xs, const bf16_t *__restrict__ X,
                                            const bf16_t *__restrict__ W, bf16_t *__restrict__ mid, float *__restrict__ ws,
                                            int M, int N, int K, int n_tileA, int m0A, int n_main, int n_tileB, int m0B,
                                            int split, int kstepsB) {
-  constexpr int BM = WM * AT * 32;
-  constexpr int XCH = BM * (BK / 8) / 256;
-  static_assert(WM * WN == 4 && XCH >= 1 && BT == 2, "tile");
-  const int tid = threadIdx.x, l = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
-  const int n0A = n_tileA + wn * BT * 32, n0B = n_tileB + wn * BT * 32;
-  const int nksA = K / BK;
-  const int nksB = min(kstepsB, K / BK - split * kstepsB);
-  const int lrow = l & 31, half = l >> 5;
-  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)W, 0, (int)((int64_t)N * K * 2), 0x00020000);
-  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)X, 0, (int)((int64_t)M * K * 2), 0x00020000);
-  const int w_lane = l * 16;
-  const uint32_t w_plane = (uint32_t)(N >> 5) * 4096u;
-  uint32_t w_blkA[BT], w_blkB[BT];
-#pragma unroll
-  for (int bt = 0; bt < BT; ++bt) {
-    w_blkA[bt] = (uint32_t)min((n0A >> 5) + bt, (N >> 5) - 1) * 4096u;
-    w_blkB[bt] = (uint32_t)(split * kstepsB) * w_plane + (uint32_t)min((n0B >> 5) + bt, (N >> 5) - 1) * 4096u;
-  }
-  const int x_laneA = ((m0A + (tid >> 3)) * K + (tid & 7) * 8) * 2;
-  const int x_laneB = ((m0B + (tid >> 3)) * K + split * kstepsB * BK + (tid & 7) * 8) * 2;
-  const int x_lds = (tid >> 3) * LDS_ROW + (tid & 7) * 8;
-
-  f32x16 acc[AT][BT];
-  auto zero_acc = [&]() {
-#pragma unroll
-    for (int a = 0; a < AT; ++a)
-#pragma unroll
-      for (int b = 0; b < BT; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-  };
-  zero_acc();
-
-  bf16x8 wf[4][BT][4], xr[2][XCH];
-  // SEG: 1 = tile A, 2 = tile B
-  auto load_w = [&](auto SEG, int stage, int ks) {
-#pragma unroll
-    for (int bt = 0; bt < BT; ++bt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        wf[stage][bt][j] = __builtin_bit_cast(
-            bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
-                        rw, w_lane + j * 1024, (int)((decltype(SEG)::value == 1 ? w_blkA[bt] : w_blkB[bt]) + (uint32_t)ks * w_plane), W_CACHE<WM, COLD>));
-  };
-  auto load_x = [&](auto SEG, int stage, int ks) {
-#pragma unroll
-    for (int i = 0; i < XCH; ++i)
-      xr[stage][i] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
-                                                    rx, decltype(SEG)::value == 1 ? x_laneA : x_laneB, ks * (BK * 2) + i * 64 * K, 0));
-  };
-  auto store_x = [&](int stage, int buf) {
-#pragma unroll
-    for (int i = 0; i < XCH; ++i) *(bf16x8 *)(&xs[buf][x_lds + i * 32 * LDS_ROW]) = xr[stage][i];
-  };
-  using S0 = std::integral_constant<int, 0>; using S1 = std::integral_constant<int, 1>; using S2 = std::integral_constant<int, 2>;
-  using I0 = std::integral_constant<int, 0>; using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, 2>; using I3 = std::integral_constant<int, 3>;
-  using Y = std::true_type; using No = std::false_type;
-
-  load_x(S1{}, 0, 0);
-  load_w(S1{}, 0, 0);
-  load_x(S1{}, 1, 1);
-  load_w(S1{}, 1, 1);
-  load_w(S1{}, 2, 2);
-  store_x(0, 0);
-  __syncthreads();
-
-  const int a_off = (wm * AT * 32 + lrow) * LDS_ROW + half * 32;
-  // one k-step in ring slot u; LX / LW: segment whose x tile (k-step ksx) / W tiles (k-step ksw) are
-  // loaded meanwhile (S0: none); SX: whether the x tile loaded one step earlier goes to LDS
-  auto kstep = [&](auto U, auto LX, auto LW, auto SX, int ksx, int ksw) {
-    constexpr int u = decltype(U)::value;
-    constexpr bool lx = decltype(LX)::value != 0, lw = decltype(LW)::value != 0;
-    bf16x8 af[2][AT];
-    auto read_a = [&](int j) {
-#pragma unroll
-      for (int a = 0; a < AT; ++a) af[j & 1][a] = *(const bf16x8 *)(&xs[u & 1][a_off + a * 32 * LDS_ROW + j * 8]);
-    };
-    auto mma = [&](int j) {
-#pragma unroll
-      for (int a = 0; a < AT; ++a)
-#pragma unroll
-        for (int b = 0; b < BT; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[j & 1][a], wf[u][b][j], acc[a][b], 0, 0, 0);
-    };
-    read_a(0);
-    read_a(1);
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (lx) load_x(LX, u & 1, ksx);
-    mma(0);
-    if constexpr (lx) {
-#pragma unroll
-      for (int i = 0; i < XCH; ++i) {
-        __builtin_amdgcn_sched_group_barrier(PL_SG_MFMA, (AT * BT) / XCH > 0 ? (AT * BT) / XCH : 1, 0);
-        __builtin_amdgcn_sched_group_barrier(PL_SG_VMEM_READ, 1, 0);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    read_a(2);
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (lw) load_w(LW, (u + 3) & 3, ksw);
-    mma(1);
-    if constexpr (lw) {
-#pragma unroll
-      for (int i = 0; i < BT * 4; ++i) {
-        __builtin_amdgcn_sched_group_barrier(PL_SG_MFMA, (AT * BT) / (BT * 4) > 0 ? (AT * BT) / (BT * 4) : 1, 0);
-        __builtin_amdgcn_sched_group_barrier(PL_SG_VMEM_READ, 1, 0);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    read_a(3);
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (decltype(SX)::value) store_x((u + 1) & 1, (u + 1) & 1);
-    mma(2);
-    mma(3);
-    if constexpr (decltype(SX)::value) {
-#pragma unroll
-      for (int i = 0; i < XCH; ++i) {
-        __builtin_amdgcn_sched_group_barrier(PL_SG_MFMA, (2 * AT * BT) / XCH > 0 ? (2 * AT * BT) / XCH : 1, 0);
-        __builtin_amdgcn_sched_group_barrier(PL_SG_DS_WRITE, 1, 0);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();
-  };
-
-  // tile A; its last three k-steps load the first operands of tile B
+  Tile<WM, WN, AT, BT, COLD> t;
+  t.init(xs, X, W, M, N, K);
+  const int nksA = K / BK, nksB = min(kstepsB, K / BK - split * kstepsB);
+  const auto pa = t.part(n_tileA, m0A, 0, M, N, K), pb = t.part(n_tileB, m0B, split * kstepsB, M, N, K);
+  t.zero();
+  t.begin(pa);
   int ks = 0;
-  for (; ks < nksA - 4; ks += 4) {
-    kstep(I0{}, S1{}, S1{}, Y{}, ks + 2, ks + 3);
-    kstep(I1{}, S1{}, S1{}, Y{}, ks + 3, ks + 4);
-    kstep(I2{}, S1{}, S1{}, Y{}, ks + 4, ks + 5);
-    kstep(I3{}, S1{}, S1{}, Y{}, ks + 5, ks + 6);
-  }
-  kstep(I0{}, S1{}, S1{}, Y{}, ks + 2, ks + 3);
-  kstep(I1{}, S1{}, S2{}, Y{}, ks + 3, 0);
-  kstep(I2{}, S2{}, S2{}, Y{}, 0, 1);
-  kstep(I3{}, S2{}, S2{}, Y{}, 1, 2);
-
-  // epilogue of A (SwiGLU): accumulator register i of lane l is row (i/4)*8 + (l/32)*4 + i%4, column l%32
-#pragma unroll
-  for (int a = 0; a < AT; ++a) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int m = m0A + wm * AT * 32 + a * 32 + (i >> 2) * 8 + half * 4 + (i & 3);
-      if (m >= M) continue;
-      bf16_t *Y_ = mid + (int64_t)m * (N / 2);
-      if (n0A + lrow < n_main) {
-        const float gte = acc[a][0][i], up = acc[a][BT - 1][i];
-        const float sv = gte / (1.f + __expf(-gte));
-        Y_[(n0A >> 1) + lrow] = (__bf16)(sv * up);
-      }
-    }
-  }
-  zero_acc();
-
-  // K slice of tile B: its first two x tiles and three W tiles are already loaded or on the way
-  for (ks = 0; ks < nksB - 4; ks += 4) {
-    kstep(I0{}, S2{}, S2{}, Y{}, ks + 2, ks + 3);
-    kstep(I1{}, S2{}, S2{}, Y{}, ks + 3, ks + 4);
-    kstep(I2{}, S2{}, S2{}, Y{}, ks + 4, ks + 5);
-    kstep(I3{}, S2{}, S2{}, Y{}, ks + 5, ks + 6);
-  }
-  kstep(I0{}, S2{}, S2{}, Y{}, ks + 2, ks + 3);
-  kstep(I1{}, S2{}, S0{}, Y{}, ks + 3, 0);
-  kstep(I2{}, S0{}, S0{}, Y{}, 0, 0);
-  kstep(I3{}, S0{}, S0{}, No{}, 0, 0);
-
-  const int ldy = N - n_main;
-#pragma unroll
-  for (int a = 0; a < AT; ++a) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int m = m0B + wm * AT * 32 + a * 32 + (i >> 2) * 8 + half * 4 + (i & 3);
-      if (m >= M) continue;
-      float *Y_ = ws + ((int64_t)split * M + m) * ldy - n_main;
-#pragma unroll
-      for (int b = 0; b < BT; ++b) {
-        const int n = n0B + b * 32 + lrow;
-        if (n < N) Y_[n] = acc[a][b][i];
-      }
-    }
-  }
+  for (; ks < nksA - 4; ks += 4) t.four(pa, ks);
+  t.template kstep<0, true, 3>(pa, ks + 3);
+  t.template kstep<1, true, 3>(pb, 0);
+  t.template kstep<2, true, 3>(pb, 1);
+  t.template kstep<3, true, 3>(pb, 2);
+  t.store_swiglu(mid, n_tileA, m0A, M, n_main, N);
+  t.zero();
+  for (ks = 0; ks < nksB - 4; ks += 4) t.four(pb, ks);
+  t.last_four(pb, ks);
+  t.store(ws + (int64_t)split * M * (N - n_main), n_tileB, m0B, M, N, N - n_main, n_main);
 }
 
 template <int WM, int WN, int AT, int BT, int MODE, bool COLD>
@@ -448,7 +329,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(const bf16_t *__restrict__ X,
                                                    void *__restrict__ Yv, int M, int N, int K, int ksteps,
                                                    int n_base, int n_end, int nrow, int ldy, int y_col0) {
   constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
-  __shared__ __attribute__((aligned(16))) bf16_t xs[2][BM * LDS_ROW];
+  __shared__ __attribute__((aligned(1024))) bf16_t xs[Tile<WM, WN, AT, BT, false>::LDS];
   // Tile of this workgroup.  nrow = 0: (column tile, row tile) = (blockIdx.x, blockIdx.z).  nrow > 0:
   // a flat grid in which the row tiles of one column tile sit 8 workgroup ids apart, so the hardware's
   // round-robin deal of consecutive ids to the 8 XCDs puts them on the same XCD at the same moment
@@ -470,7 +351,7 @@ __global__ __launch_bounds__(256) void gemm_fold_kernel(const bf16_t *__restrict
                                                         void *__restrict__ Yv, int M, int N, int K, int ksteps,
                                                         int n_base, int n_end, int nrow) {
   constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
-  __shared__ __attribute__((aligned(16))) bf16_t xs[2][BM * LDS_ROW];
+  __shared__ __attribute__((aligned(1024))) bf16_t xs[Tile<WM, WN, AT, BT, false>::LDS];
   const int rtile = (blockIdx.x >> 3) % nrow, ctile = (blockIdx.x / (8 * nrow)) * 8 + (blockIdx.x & 7);
   if (n_base + ctile * BN >= n_end) return;   // padding of the flat grid (uniform for the workgroup)
   gemm_tile<WM, WN, AT, BT, MODE, false, true>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, 0, n_end, N, 0);
@@ -490,7 +371,7 @@ __global__ __launch_bounds__(256) void gemm_gu_fused_kernel(const bf16_t *__rest
                                                             bf16_t *__restrict__ mid, float *__restrict__ ws, int M, int N,
                                                             int K, int n_main, int rem_splits, int rem_ksteps) {
   constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
-  __shared__ __attribute__((aligned(16))) bf16_t xs[2][BM * LDS_ROW];
+  __shared__ __attribute__((aligned(1024))) bf16_t xs[Tile<WM, WN, AT, BT, false>::LDS];
   const int nrow = (M + BM - 1) / BM;
   const int rtileA = (blockIdx.x >> 3) % nrow, ctileA = (blockIdx.x / (8 * nrow)) * 8 + (blockIdx.x & 7);
   const bool hasA = ctileA * BN < n_main;
@@ -514,8 +395,8 @@ template <int WM, int WN, int AT, int BT, bool COLD>
 __global__ __launch_bounds__(256) void gemm_gu_joint_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
                                                             bf16_t *__restrict__ mid, float *__restrict__ ws, int M, int N,
                                                             int K, int n_main, int n_tiles, int rem_splits, int rem_ksteps) {
-  constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
-  __shared__ __attribute__((aligned(16))) bf16_t xs[2][BM * LDS_ROW];
+  constexpr int BN = WN * BT * 32;
+  __shared__ __attribute__((aligned(1024))) bf16_t xs[Tile<WM, WN, AT, BT, false>::LDS];
   const int item = (int)blockIdx.x - n_tiles;
   if (item < 0)   // uniform for the workgroup
     gemm_tile<WM, WN, AT, BT, 1, COLD>(xs, X, W, mid, M, N, K, K / BK, (int)blockIdx.x * BN, 0, 0, n_main, 0, 0);

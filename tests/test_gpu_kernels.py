@@ -424,6 +424,26 @@ def test_products_of_an_engine_with_cold_weights_give_the_same_bits(M_max, N, K,
         both(M, 1, lambda y, M, md: pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), M_max, M, N, K, md, 0))
 
 
+@pytest.mark.parametrize("M,mode", [(1, 0), (37, 0), (200, 0), (200, 1)])
+def test_products_of_operands_at_any_alignment(M, mode):
+    """16-byte accesses, direct loads to LDS among them, on operands that start at any element."""
+    N, K = 640, 512
+    g = torch.Generator(device="cuda").manual_seed(M)
+    x = torch.empty(M * K, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
+    w = torch.empty(N * K, device="cuda", dtype=torch.bfloat16).normal_(0, 0.05, generator=g)
+    n, dtype = (M * N, torch.float32) if mode == 0 else (M * N // 2, torch.bfloat16)
+    want = None
+    for ox, ow, oy in [(0, 0, 0), (1, 0, 0), (2, 0, 0), (0, 1, 0), (0, 6, 0), (0, 0, 1), (3, 5, 2)]:
+        xs, ws, ys = (torch.zeros(k + 8, device="cuda", dtype=t) for k, t in ((M * K, x.dtype), (N * K, w.dtype), (n, dtype)))
+        xs[ox:ox + M * K], ws[ow:ow + N * K] = x, w
+        pl.pl_gemm_bf16(xs[ox:].data_ptr(), ws[ow:].data_ptr(), ys[oy:].data_ptr(), M, N, K, mode, 1, 0)
+        torch.cuda.synchronize()
+        got = ys[oy:oy + n]
+        want = got.clone() if want is None else want
+        assert bool(want.abs().sum() > 0) and torch.equal(got, want), (ox, ow, oy)
+        assert bool((ys[:oy] == 0).all()) and bool((ys[oy + n:] == 0).all())
+
+
 def test_gemm_rejects_bad_shapes():
     t = torch.zeros(600 * 512, device="cuda", dtype=torch.bfloat16)
     for args in [(4, 64, 192, 0, 1), (0, 64, 256, 0, 1), (4, 64, 512, 0, 3), (4, 96, 256, 1, 1), (4, 64, 512, 1, 2),
