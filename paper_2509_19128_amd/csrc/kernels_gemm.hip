@@ -218,25 +218,52 @@ struct Tile {
       }
     }
   }
-  // SwiGLU: the two column tiles of a wavefront are the gate and the up half of a 64-row block
-  __device__ __forceinline__ void store_swiglu(bf16_t *Y, int n_tile0, int m0, int M, int n_end, int N) const {
-    const int n0 = n_tile0 + wn * BT * 32;
+  // SwiGLU of a 64-row block's gate and up halves: the two column tiles of a wavefront, or (BT = 1) the tiles of two
+  // neighbours, which swap half of them through the LDS stages that nothing reads any more and take half of the block each.
+  __device__ __forceinline__ void store_swiglu(bf16_t *Y, int n_tile0, int m0, int M, int n_end, int N) {
+    static_assert(BT == 2 || WM == 1, "pairs");
+    constexpr int NI = BT == 2 ? 4 : 2;   // groups of four columns per lane
+    const int n0 = BT == 2 ? n_tile0 + wn * 64 : n_tile0 + (wn >> 1) * 64, i0 = BT == 2 ? 0 : (wn & 1) * 2;
+    f32x4 *swap = (f32x4 *)xs + l;        // [wavefront][a][2][lane]: two stages at most, and the last k-step reads the fourth
+    if (BT == 1) {
+#pragma unroll
+      for (int a = 0; a < AT; ++a)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {   // an even wavefront (gate) hands on its groups 2 and 3, an odd one (up) 0 and 1
+          f32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = wn & 1 ? acc[a][0][4 * i + e] : acc[a][0][4 * (i + 2) + e];
+          swap[((wn * AT + a) * 2 + i) * 64] = v;
+        }
+      __syncthreads();
+    }
     if (n0 >= n_end) return;
 #pragma unroll
     for (int a = 0; a < AT; ++a) {
       const int m = m0 + (wm * AT + a) * 32 + lrow;
-      if (m >= M) continue;
       bf16_t *y = Y + (int64_t)m * (N / 2) + (n0 >> 1) + half * 4;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < NI; ++i) {
+        f32x4 gte, up;
+        if (BT == 2) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { gte[e] = acc[a][0][4 * i + e]; up[e] = acc[a][BT - 1][4 * i + e]; }
+        } else {
+          const f32x4 other = swap[(((wn ^ 1) * AT + a) * 2 + i) * 64];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float mine = wn & 1 ? acc[a][0][4 * (i + 2) + e] : acc[a][0][4 * i + e];
+            gte[e] = wn & 1 ? other[e] : mine;
+            up[e] = wn & 1 ? mine : other[e];
+          }
+        }
         bf16x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float gte = acc[a][0][4 * i + e], up = acc[a][BT - 1][4 * i + e];
-          const float sv = gte / (1.f + __expf(-gte));
-          o[e] = (__bf16)(sv * up);
+          const float sv = gte[e] / (1.f + __expf(-gte[e]));
+          o[e] = (__bf16)(sv * up[e]);
         }
-        *(bf16x4 *)(y + i * 8) = o;
+        if (m < M) *(bf16x4 *)(y + (i0 + i) * 8) = o;
       }
     }
   }
@@ -305,6 +332,7 @@ __device__ __forceinline__ void gemm_tile2(bf16_t *xs, const bf16_t *__restrict_
                                            const bf16_t *__restrict__ W, bf16_t *__restrict__ mid, float *__restrict__ ws,
                                            int M, int N, int K, int n_tileA, int m0A, int n_main, int n_tileB, int m0B,
                                            int split, int kstepsB) {
+  static_assert(BT == 2, "the stages already hold tile B when A is stored");
   Tile<WM, WN, AT, BT, COLD> t;
   t.init(xs, X, W, M, N, K);
   const int nksA = K / BK, nksB = min(kstepsB, K / BK - split * kstepsB);
@@ -330,17 +358,19 @@ __global__ __launch_bounds__(256) void gemm_kernel(const bf16_t *__restrict__ X,
                                                    int n_base, int n_end, int nrow, int ldy, int y_col0) {
   constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
   __shared__ __attribute__((aligned(1024))) bf16_t xs[Tile<WM, WN, AT, BT, false>::LDS];
-  // Tile of this workgroup.  nrow = 0: (column tile, row tile) = (blockIdx.x, blockIdx.z).  nrow > 0:
-  // a flat grid in which the row tiles of one column tile sit 8 workgroup ids apart, so the hardware's
+  // Tile and K slice of this workgroup.  nrow = 0: (column tile, slice, row tile) = the block index.  nrow > 0:
+  // a flat grid in which the row tiles of one column tile and slice sit 8 workgroup ids apart, so the hardware's
   // round-robin deal of consecutive ids to the 8 XCDs puts them on the same XCD at the same moment
   // and the second reader of a W tile finds it in that XCD's L2.
-  int ctile = blockIdx.x, rtile = blockIdx.z;
+  int ctile = blockIdx.x, split = blockIdx.y, rtile = blockIdx.z;
   if (nrow > 0) {
+    const int item = (blockIdx.x / (8 * nrow)) * 8 + (blockIdx.x & 7), nct = (n_end - n_base + BN - 1) / BN;
     rtile = (blockIdx.x >> 3) % nrow;
-    ctile = (blockIdx.x / (8 * nrow)) * 8 + (blockIdx.x & 7);
-    if (n_base + ctile * BN >= n_end) return;   // padding of the flat grid (uniform for the workgroup)
+    ctile = item % nct;
+    split = item / nct;
+    if (split * ksteps * BK >= K) return;   // padding of the flat grid (uniform for the workgroup)
   }
-  gemm_tile<WM, WN, AT, BT, MODE, COLD>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, blockIdx.y, n_end, ldy, y_col0);
+  gemm_tile<WM, WN, AT, BT, MODE, COLD>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, split, n_end, ldy, y_col0);
 }
 
 // Many rows (prompt passes): flat grid in XCD-local groups of row tiles as above, all K slices of a tile in
@@ -355,6 +385,22 @@ __global__ __launch_bounds__(256) void gemm_fold_kernel(const bf16_t *__restrict
   const int rtile = (blockIdx.x >> 3) % nrow, ctile = (blockIdx.x / (8 * nrow)) * 8 + (blockIdx.x & 7);
   if (n_base + ctile * BN >= n_end) return;   // padding of the flat grid (uniform for the workgroup)
   gemm_tile<WM, WN, AT, BT, MODE, false, true>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, 0, n_end, N, 0);
+}
+
+// SwiGLU product of many rows by 256 x 256 tiles, one per compute unit: workgroups below n_big take the tiles of columns [0, n_cut)
+// (paired on XCDs as above), the others 256 x 64 tiles of the columns behind, which would be a nearly empty last round of big
+// ones, in one slice or (FOLD) in slices of `ksteps` added up.  1.5B shape, 1024 rows (280 big tiles): 66 us, as two rounds of big
+// ones 75, by 128 x 128 tiles 78; 7B shape with its sliced remainder, 1024 rows, 265, by 128 x 256 tiles and two launches 272.
+template <bool FOLD>
+__global__ __launch_bounds__(256) void gemm_wide_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
+                                                        void *__restrict__ Yv, int M, int N, int K, int ksteps, int n_cut, int n_big) {
+  __shared__ __attribute__((aligned(1024))) bf16_t xs[Tile<1, 4, 8, 2, false>::LDS];
+  const bool big = (int)blockIdx.x < n_big;   // uniform for the workgroup
+  const int i = big ? blockIdx.x : blockIdx.x - n_big, nrow = (M + 255) / 256;
+  const int m0 = (i >> 3) % nrow * 256, ctile = (i / (8 * nrow)) * 8 + (i & 7), n0 = big ? ctile * 256 : n_cut + ctile * 64;
+  if (n0 >= (big ? n_cut : N)) return;        // padding of the flat grid
+  if (big) gemm_tile<1, 4, 8, 2, 1, false>(xs, X, W, Yv, M, N, K, K / BK, n0, m0, 0, n_cut, N, 0);
+  else gemm_tile<4, 1, 2, 2, 1, false, FOLD>(xs, X, W, Yv, M, N, K, ksteps, n0, m0, 0, N, N, 0);
 }
 
 // The SwiGLU product of a 129..256-row batch in ONE launch of one workgroup per compute unit.  Workgroup i
@@ -388,8 +434,9 @@ __global__ __launch_bounds__(256) void gemm_gu_fused_kernel(const bf16_t *__rest
     gemm_tile<WM, WN, AT, BT, 0, COLD>(xs, X, W, ws, M, N, K, rem_ksteps, n_main + ctileB * BN, rtileB * BM, split, N, N - n_main, n_main);
 }
 
-// The same product for calls of at most one row tile (a decayed batch in an engine sized for more rows): workgroups
-// below n_tiles take the main tiles, the others the K slices of the remainder, in one launch.  The two launches
+// The same product in calls of at most one row tile: workgroups
+// below n_tiles take the main tiles, the others the K slices of the remainder, in one launch.  Tiles of 128 columns: 7B shape, 19 / 64 / 128
+// rows 45 / 48 / 60 us with the reduction, by 256 (64 rows: 128) columns 49 / 56 / 68.  The two launches
 // in a row each left part of the chip idle: 7B shape, 19 rows, 43 + 11 us and a gap; joined 50.
 template <int WM, int WN, int AT, int BT, bool COLD>
 __global__ __launch_bounds__(256) void gemm_gu_joint_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
@@ -446,13 +493,13 @@ template <int WM, int WN, int AT, int BT>
 int launch_cfg(const Launch &L) {
   constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
   if (L.n_end <= L.n_begin) return 0;
-  if (BT == 1 && L.mode == 1) return -1;   // the SwiGLU epilogue needs a gate and an up tile per wavefront
+  if (BT == 1 && WM > 1 && L.mode == 1) return -1;   // gate and up tiles of a block: in one wavefront or in neighbours
   dim3 grid((L.n_end - L.n_begin + BN - 1) / BN, L.splits, (L.M + BM - 1) / BM);
   int nrow = 0;
-  if (L.paired) {   // flat grid, column tiles padded to a multiple of 8 (see the kernel)
+  if (L.paired) {   // flat grid, column tiles and slices padded to a multiple of 8 (see the kernel)
     nrow = grid.z;
-    grid.x = ((grid.x + 7) / 8) * 8 * nrow;
-    grid.z = 1;
+    grid.x = ((grid.x * L.splits + 7) / 8) * 8 * nrow;
+    grid.y = grid.z = 1;
   }
   int ksteps = 4 * ((L.K / (4 * BK) + L.splits - 1) / L.splits);
   with_cold<WM>(L.cold, [&](auto COLD) {
@@ -461,7 +508,7 @@ int launch_cfg(const Launch &L) {
       hipLaunchKernelGGL((gemm_kernel<WM, WN, AT, BT, 0, cold>), grid, dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps,
                          L.n_begin, L.n_end, nrow, L.ldy, L.y_col0);
     else
-      hipLaunchKernelGGL((gemm_kernel<WM, WN, AT, (BT > 1 ? BT : 2), 1, cold>), grid, dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N,
+      hipLaunchKernelGGL((gemm_kernel<WM, WN, AT, (BT > 1 || WM == 1 ? BT : 2), 1, cold>), grid, dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N,
                          L.K, ksteps, L.n_begin, L.n_end, nrow, L.ldy, L.y_col0);
   });
   return hipGetLastError() == hipSuccess ? 0 : -7;
@@ -480,6 +527,10 @@ int launch_by_id(int cfg, const Launch &L) {
     case GEMM_32x128: return launch_cfg<1, 4, 1, 1>(L);
     case GEMM_128x64P: return launch_cfg<4, 1, 1, 2>(L);
     case GEMM_256x64P: return launch_cfg<4, 1, 2, 2>(L);
+    case GEMM_128x128R: return launch_cfg<1, 4, 4, 1>(L);
+    case GEMM_256x128R: return launch_cfg<1, 4, 8, 1>(L);
+    case GEMM_64x128R: return launch_cfg<1, 4, 2, 1>(L);
+    case GEMM_256x256: return launch_cfg<1, 4, 8, 2>(L);
     default: return -1;
   }
 }
@@ -507,6 +558,18 @@ int launch_fold_cfg(Launch L) {
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }
 
+// SwiGLU product of many rows: columns [0, n_cut) by 256 x 256 tiles, the rest by narrow tiles, its K in rem_splits slices
+int launch_wide(const Launch &L, int n_cut, int rem_splits) {
+  const int nrow = (L.M + 255) / 256;
+  const int big = (n_cut / 256 + 7) / 8 * 8 * nrow, left = ((L.N - n_cut + 63) / 64 + 7) / 8 * 8 * nrow;
+  const int ksteps = 4 * ((L.K / (4 * BK) + rem_splits - 1) / rem_splits);
+  if (rem_splits == 1)
+    hipLaunchKernelGGL((gemm_wide_kernel<false>), dim3(big + left), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps, n_cut, big);
+  else
+    hipLaunchKernelGGL((gemm_wide_kernel<true>), dim3(big + left), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps, n_cut, big);
+  return hipGetLastError() == hipSuccess ? 0 : -7;
+}
+
 bool splits_valid(int K, int splits) {
   const int total = K / (4 * BK);
   return splits >= 1 && splits <= total && (splits - 1) * ((total + splits - 1) / splits) < total;   // no empty slice
@@ -520,9 +583,46 @@ int swiglu_reduce(const float *parts, int splits, int M, int ld, int col0, bf16_
 
 }  // namespace
 
+
+// Microseconds of a product by tiles of one shape, as measured: fixed + out * MB written + k-steps of a workgroup * (base + load *
+// (fraction of the compute units at work) + round * (workgroups on the fullest unit - 1) + more * (average beyond one)).
+// Fits by hand to 10000 launches (the products of the 1.5B, 7B and 32B shapes, 1 to 512 rows, 1 to 9 slices, weights in and out of the
+// last-level cache): the shape with the least is the best measured one within 2.5 % on average (11 % in 95 of 100).
+struct ShapeTime { int cfg, log_rows, log_cols; float fixed, base, load, round, more, out; };
+constexpr ShapeTime SHAPES[] = {
+    {GEMM_32x128, 5, 7, 5.2f, 0.23f, 0.13f, 0.42f, 0.26f, 0.f},   {GEMM_64x128R, 6, 7, 5.3f, 0.24f, 0.20f, 0.53f, 0.30f, 0.05f},
+    {GEMM_64x64, 6, 6, 5.1f, 0.22f, 0.05f, 0.20f, 0.20f, 0.15f},   {GEMM_128x64, 7, 6, 4.9f, 0.26f, 0.12f, 0.28f, 0.25f, 0.13f},
+    {GEMM_128x128R, 7, 7, 5.3f, 0.31f, 0.31f, 0.80f, 0.10f, 0.15f}, {GEMM_128x128, 7, 7, 5.5f, 0.40f, 0.35f, 0.f, 0.60f, 0.15f},
+    {GEMM_32x256, 5, 8, 6.0f, 0.40f, 0.55f, 0.70f, 0.50f, 0.f},   {GEMM_64x256, 6, 8, 6.3f, 0.50f, 0.55f, 0.80f, 0.65f, 0.f},
+    {GEMM_128x256, 7, 8, 6.3f, 0.59f, 0.41f, 1.0f, 0.40f, 0.16f}, {GEMM_256x128R, 8, 7, 5.5f, 0.50f, 0.39f, 0.90f, 0.28f, 0.25f},
+    {GEMM_256x256, 8, 8, 7.7f, 0.84f, 0.62f, 1.45f, 0.50f, 0.23f}};
+
 int gemm_tile_rows(int cfg) {
-  static const int rows[GEMM_N_CFGS] = {32, 64, 128, 64, 128, 256, 64, 128, 32, 128, 256};
-  return cfg >= 0 && cfg < GEMM_N_CFGS ? rows[cfg] : 0;
+  for (const ShapeTime &t : SHAPES)
+    if (t.cfg == cfg) return 1 << t.log_rows;
+  return 0;
+}
+
+// Tile shape of a call.  Shapes whose wavefronts stack rows have no SwiGLU pairs (64 x 64, 128 x 64); 64 x 64 tiles for up to 32 rows
+// pay only where W comes from memory (7B down in one slice, 16 rows: 75 us, by 32 x 128 tiles 95; O from the cache 10.6 and 10.0); 128 x 128
+// tiles in two rows of two are a second choice where two of them share a unit.
+int pick_shape(int M, int N, int K, int mode, int splits, bool cold) {
+  const float ksteps = 4 * ((K / (4 * BK) + splits - 1) / splits), out_mb = 4e-6f * M * N * (mode == 0 ? splits : 0.25f);
+  const float floor_us = 2e-6f / 6.6f * N * K + 3;
+  int best = -1;
+  float best_us = 0;
+  for (const ShapeTime &t : SHAPES) {   // (in a caller's launch path: no divisions)
+    const int rows = 1 << t.log_rows;
+    if ((rows > 64 && rows >= 4 * M) || rows * 5 < M) continue;
+    const int n = ((M + rows - 1) >> t.log_rows) * ((N + (1 << t.log_cols) - 1) >> t.log_cols) * splits;
+    if (t.cfg == GEMM_64x64 && (mode == 1 || (M <= 32 && !cold))) continue;
+    if ((t.cfg == GEMM_128x64 && mode == 1) || (t.cfg == GEMM_128x128 && n > 512)) continue;
+    const float r = n * (1.f / 256);
+    const float us = t.fixed + t.out * out_mb + ksteps * (t.base + t.load * std::min(r, 1.f) + t.round * ((n + 255) / 256 - 1) + t.more * std::max(r - 1, 0.f));
+    const float bound = std::max(us, floor_us + r * 0.128f);
+    if (best < 0 || bound < best_us) { best = t.cfg; best_us = bound; }
+  }
+  return best;
 }
 
 // One launch of one tile configuration over a column range (tuning and tests).  mode 1 with
@@ -534,7 +634,7 @@ int launch_gemm_cfg(int cfg, const bf16_t *x, const bf16_t *w, void *y, float *w
   if (mode == 1 && (N % 64 || n_begin % 64 || n_end % 64)) return -1;
   if (n_begin < 0 || n_end > N || n_begin % 32 || n_end % 32) return -1;
   if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
-  if (paired && splits != 1) return -1;
+  if (paired && splits != 1 && mode == 1) return -1;
   Launch L{x, w, y, M, N, K, mode, splits, n_begin, n_end, N, 0, paired, cold, s};
   if (mode == 1 && splits > 1) {
     if (!ws) return -1;
@@ -614,70 +714,57 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
   if (mode == 1 && (N % 64 || ks.n_main % 64 || !splits_valid(K, ks.rem_splits))) return -1;
   if (mode == 0 && ks.n_main != N) return -1;
   if (ks.n_main < 0 || ks.n_main > N) return -1;
-  // tile shape from the rows of this call
-  int cfg;
-  bool paired = false;
-  if (mode == 1) {
-    if (M <= 32) cfg = GEMM_32x256;
-    else if (M <= 64) cfg = GEMM_64x128;
-    else if (M <= 128) cfg = GEMM_128x256;
-    else if (M <= 256 && N >= 128 * 256) { cfg = GEMM_128x256; paired = ks.splits == 1; }
-    else cfg = GEMM_256x128;
-  } else {
-    if (M <= 32) cfg = N >= 16384 ? GEMM_32x256 : GEMM_32x128;   // all four wavefronts stream their own columns
-    else if (M <= 64 && N < 16384) cfg = GEMM_64x64;
-    else if (M <= 64) cfg = GEMM_64x256;
-    else if (M <= 128) cfg = GEMM_128x256;
-    else if (M <= 256 && ks.splits == 1 && N >= 128 * 256) { cfg = GEMM_128x256; paired = true; }
-    else if (M <= 256 && K <= 4096) cfg = ks.splits <= 2 ? GEMM_128x64 : GEMM_128x128;
-    else cfg = GEMM_256x128;
-  }
-  // A second row tile of a few rows runs through its W ahead of the first one's loads, which then find nothing in L2 if they
-  // are non-temporal: LM head of the 7B / 32B shape 129 rows 287 / 474 us with ordinary, 318 / 550 with non-temporal
-  // loads, 160 rows 295 / 473 and 301 / 502, 192 rows 303 / 457 and 300 / 438; gate/up of the 7B shape, 136 rows 78 and 88.
-  if (paired && M < 192) cold = false;
-  int n_main = ks.n_main;
-  if (paired && n_main == N) {
-    // Wide matrices without a K split: 128 x 256 tiles in XCD-local pairs.  When the tile count is a
-    // little over a multiple of 256 the last round would run on a few units at full length: those
-    // columns go to a second launch of 64 x 128 tiles instead.
-    const int ctiles = (N + 255) / 256, tiles = 2 * ctiles, rem = tiles % 256;
-    if (tiles > 256 && rem > 0 && rem <= 64) n_main = ((tiles - rem) / 2) * 256;
-  }
-  if (mode == 1 && paired && n_main < N && ks.rem_splits > 1 && ks.splits == 1 && ws) {
+  if (mode == 1 && M <= 256 && ks.n_main < N && ks.rem_splits > 1 && ks.splits == 1 && ws) {
     // main tiles and K slices of the remainder in one launch, then the SwiGLU over the slices
     if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
-    const int nrow = (M + 127) / 128, rem_ctiles = (N - n_main + 255) / 256;
-    const int wgs = std::max(((n_main / 256 + 7) / 8) * 8 * nrow, rem_ctiles * nrow * ks.rem_splits);
     const int rem_ksteps = 4 * ((K / (4 * BK) + ks.rem_splits - 1) / ks.rem_splits);
-    with_cold<1>(cold, [&](auto COLD) {
-      hipLaunchKernelGGL((gemm_gu_fused_kernel<1, 4, 4, 2, decltype(COLD)::value>), dim3(wgs), dim3(256), 0, s, x, w, (bf16_t *)y, ws, M,
-                         N, K, n_main, ks.rem_splits, rem_ksteps);
-    });
+    if (M > 128) {   // (256 x 256 tiles beside 256 x 256 slices: 82.7 us, 80.0 so)
+      const int wgs = std::max((ks.n_main / 256 + 7) / 8 * 8 * 2, (N - ks.n_main + 255) / 256 * 2 * ks.rem_splits);
+      with_cold<1>(cold && M >= 192, [&](auto COLD) {
+        hipLaunchKernelGGL((gemm_gu_fused_kernel<1, 4, 4, 2, decltype(COLD)::value>), dim3(wgs), dim3(256), 0, s, x, w, (bf16_t *)y, ws, M,
+                           N, K, ks.n_main, ks.rem_splits, rem_ksteps);
+      });
+    } else {
+      const int n_tiles = (ks.n_main + 127) / 128;
+      const dim3 grid(n_tiles + (N - ks.n_main + 127) / 128 * ks.rem_splits);
+      with_cold<1>(cold, [&](auto COLD) {
+        constexpr bool c = decltype(COLD)::value;
+        auto launch = [&](auto kernel) {
+          hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, x, w, (bf16_t *)y, ws, M, N, K, ks.n_main, n_tiles, ks.rem_splits, rem_ksteps);
+        };
+        if (M <= 32) launch(gemm_gu_joint_kernel<1, 4, 1, 1, c>);
+        else if (M <= 64) launch(gemm_gu_joint_kernel<1, 4, 2, 1, c>);
+        else launch(gemm_gu_joint_kernel<1, 4, 4, 1, c>);
+      });
+    }
     if (hipGetLastError() != hipSuccess) return -7;
-    return swiglu_reduce(ws, ks.rem_splits, M, N - n_main, n_main, (bf16_t *)y, N / 2, s);
+    return swiglu_reduce(ws, ks.rem_splits, M, N - ks.n_main, ks.n_main, (bf16_t *)y, N / 2, s);
   }
-  if (mode == 1 && M <= 128 && n_main < N && ks.rem_splits > 1 && ks.splits == 1 && ws) {
-    if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
-    const int bn = cfg == GEMM_64x128 ? 128 : 256, n_tiles = (n_main + bn - 1) / bn;
-    const dim3 grid(n_tiles + (N - n_main + bn - 1) / bn * ks.rem_splits);
-    const int rem_ksteps = 4 * ((K / (4 * BK) + ks.rem_splits - 1) / ks.rem_splits);
-    with_cold<1>(cold, [&](auto COLD) {
-      constexpr bool c = decltype(COLD)::value;
-      auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, x, w, (bf16_t *)y, ws, M, N, K, n_main, n_tiles, ks.rem_splits, rem_ksteps);
-      };
-      if (cfg == GEMM_32x256) launch(gemm_gu_joint_kernel<1, 4, 1, 2, c>);
-      else if (cfg == GEMM_64x128) launch(gemm_gu_joint_kernel<2, 2, 1, 2, false>);
-      else launch(gemm_gu_joint_kernel<1, 4, 4, 2, c>);
-    });
-    if (hipGetLastError() != hipSuccess) return -7;
-    return swiglu_reduce(ws, ks.rem_splits, M, N - n_main, n_main, (bf16_t *)y, N / 2, s);
-  }
-  int rc = launch_gemm_cfg(cfg, x, w, y, ws, M, N, K, mode, ks.splits, 0, n_main, paired, cold, s);
+  const int cfg = pick_shape(M, ks.n_main, K, mode, ks.splits, cold), n_main = ks.n_main;
+  const bool paired = M > gemm_tile_rows(cfg);
+  // A second row tile of a few rows runs through its W ahead of the first one's loads, which then find nothing in L2 if they
+  // are non-temporal: LM head of the 7B / 32B shape by 128 x 256 tiles, 129 rows 287 / 474 us with ordinary, 318 / 550 with non-temporal
+  // loads, 160 rows 295 / 473 and 301 / 502, 192 rows 303 / 457 and 300 / 438.
+  if (paired && (M - 1) % gemm_tile_rows(cfg) < gemm_tile_rows(cfg) / 2) cold = false;
+  int rc = launch_gemm_cfg(cfg, x, w, y, ws, M, N, K, mode, ks.splits, 0, n_main, paired && (mode == 0 || ks.splits == 1), cold, s);
   if (rc || n_main == N) return rc;
   return launch_gemm_cfg(GEMM_64x128, x, w, y, ws, M, N, K, mode, mode == 1 ? ks.rem_splits : ks.splits, n_main, N,
                          false, cold, s);
+}
+
+// us per k-step of this many 256 x 256 tiles
+static double big_rounds(int64_t tiles) { return tiles / 256 * 1.45 + (tiles % 256 ? 1.05 + tiles % 256 * (0.4 / 256) : 0.0); }
+
+// us per k-step of a folded product by its four tile shapes: the time of the fullest compute unit, 0.26 / 0.38 / 0.50 / 0.80 per
+// resident 64 x 64 / 128 x 64 / 128 x 128 / 128 x 256 tile (fits of a sweep over twelve shapes at the products of the 1.5B, 7B
+// and 32B shapes, 300 to 1024 rows; the choice is the measured best in 29 of 35, within 6 % in the others).  128 x 128 tiles by four
+// wavefronts side by side, which load no W twice: 7B QKV, 511 rows, 33 us, in two rows of two 38; 32B QKV, 400 rows, 42 and 49.
+static int fold_shape(int M, int N, double *us) {
+  auto cost = [&](int bm, int bn, double t) { return (((M + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256 * t; };
+  const double c[4] = {cost(64, 64, 0.26), cost(128, 64, 0.38), cost(128, 128, 0.50), cost(128, 256, 0.80)};
+  const int best = (int)(std::min_element(c, c + 4) - c);
+  if (us) *us = c[best];
+  return best;
 }
 
 // A product of up to GEMM_MAX_ROWS rows with all K slices of an element added up in the workgroup, in slice
@@ -700,25 +787,65 @@ int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, 
   // 185 / 356, 769 rows 258 / 492 and 252 / 451; plain products (32B down, 769 rows) 372 and 348.
   cold = cold && mode == 1 && M <= 512 && (M - 1) % 128 >= 96;
   Launch L{x, w, y, M, N, K, mode, ks.splits, 0, ks.n_main, N, 0, true, cold, s};
-  if (mode == 1) {
-    // 7B shape, 1024 rows: 288 us with 128 x 256 tiles, 302 with 256 x 128, 349 with 128 x 128; 1.5B shape (a third of
-    // the tiles): 78, 85, 73
+  if (mode == 1 && ks.n_main < N) {
+    // 7B shape, main columns and remainder: 128 x 256 tiles and a launch for the remainder 135 us with 511 rows, 195 with 700, 272 with
+    // 1024; 256 x 256 tiles with the remainder in their launch 137, 183, 265.  (Splits of the main columns do not occur.)
+    if (ks.splits == 1 && M > 512) return launch_wide(L, ks.n_main, ks.rem_splits);
     const int rc = ks.splits == 1 && ks.n_main >= 128 * 256 ? launch_fold_cfg<1, 4, 4, 2>(L) : launch_fold_cfg<2, 2, 2, 2>(L);
-    if (rc || ks.n_main == N) return rc;
+    if (rc) return rc;
     L.n_begin = ks.n_main; L.n_end = N; L.splits = ks.rem_splits;
     return launch_fold_cfg<2, 2, 2, 2>(L);
   }
-  // The shape with the least time of its fullest compute unit: a k-step of 64 takes 0.26 / 0.38 / 0.65 / 1.05 us per
-  // resident 64 x 64 / 128 x 64 / 128 x 128 / 128 x 256 tile (fits of a sweep over the products of the 1.5B, 7B
-  // and 32B shapes at 511 and 1024 rows; the choice is the measured best in all 18).
-  auto cost = [&](int bm, int bn, double t) { return (((M + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256 * t; };
-  const double c[4] = {cost(64, 64, 0.26), cost(128, 64, 0.38), cost(128, 128, 0.65), cost(128, 256, 1.05)};
-  switch (std::min_element(c, c + 4) - c) {
+  if (mode == 1) {
+    if (ks.splits > 1) return launch_fold_cfg<2, 2, 2, 2>(L);
+    // The shape with the least time: a round of 256 x 256 tiles takes 1.45 us per k-step (1.05 when few of them run), 256 of the
+    // 128 x 256 tiles of a wide matrix 1.05 and of 128 x 128 tiles 0.62 whether the last round is full or not (an idle unit's power
+    // goes to the others), a round of leftover 256 x 64 tiles 0.75.  Fits of a sweep over the 1.5B, 7B and 32B shapes at 300 to 1024 rows; us
+    // by 128-row tiles, by 256 x 256 and with leftovers: 1.5B 300 rows 34 / 41 / -, 511 49 / 36 / -, 768 61 / 41 / -, 1024 78 / 75 / 66; 7B 300
+    // 100 / 146 / 123, 511 149 / 155 / 136, 768 198 / 176 / 242, 1024 251 / 244 / 265; 32B 300 207 / 232 / 275, 511 279 / 247 / 315, 1024 491 / 468 / 497.
+    const int nrow = (M + 255) / 256, ncol = (N + 255) / 256, cut = ncol * nrow / 256 * 256 / nrow;
+    const int left = (N - cut * 256 + 63) / 64 * nrow;
+    const double t[4] = {big_rounds(nrow * ncol), N >= 128 * 256 ? (M + 127) / 128 * ncol / 256. * 1.05 : 1e9,
+                         (M + 127) / 128 * ((N + 127) / 128) / 256. * 0.62,
+                         cut > 0 ? nrow * ncol / 256 * 1.45 + (left + 255) / 256 * 0.75 : 1e9};
+    switch (std::min_element(t, t + 4) - t) {
+      case 0: L.cold = false; return launch_cfg<1, 4, 8, 2>(L);
+      case 1: return launch_cfg<1, 4, 4, 2>(L);
+      case 2: return launch_cfg<2, 2, 2, 2>(L);
+      default: return launch_wide(L, cut * 256, 1);
+    }
+  }
+  switch (fold_shape(M, N, nullptr)) {
     case 0: return launch_fold_cfg<2, 2, 1, 1>(L);
     case 1: return launch_fold_cfg<2, 2, 2, 1>(L);
-    case 2: return launch_fold_cfg<2, 2, 2, 2>(L);
+    case 2: return launch_fold_cfg<1, 4, 4, 1>(L);
     default: return launch_fold_cfg<1, 4, 4, 2>(L);
   }
+}
+
+// How many slices a pass of M rows leaves a plain product in: 1 (launch_gemm_folded) or all ks.splits, as a step does.  A long K in one
+// workgroup after the other leaves the chip to 128 x 64 tiles, one per compute unit and half its rate; by slices there are enough 256 x 256
+// tiles, for the price of the slices' way to memory and back.  Down products, us folded / in slices (without the consumer's reads, here
+// counted at 4 TB/s): 7B shape 511 rows 118 / 69, 1024 rows 181 / 138; 32B 511 262 / 143, 1024 326 / 273; 1.5B 511 42 / 23, 1024 57 / 41.
+// QKV and O: 7B, 511 rows, 38 / 33 and 25 / 31; 32B, 1024 rows, 77 / 112.
+int gemm_pass_slices(int M, int N, int K, const GemmSplit &ks) {
+  if (ks.splits == 1 || K < 8192) return 1;
+  double fold;
+  fold_shape(M, N, &fold);
+  const int ksteps = 4 * ((K / (4 * BK) + ks.splits - 1) / ks.splits);
+  const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256) * ks.splits;
+  const double sliced = 4 + ksteps * big_rounds(tiles) + (ks.splits - 1) * (4e-6 * M * N / 4);
+  return sliced < K / BK * fold ? ks.splits : 1;
+}
+
+// The product of a pass of more than 256 rows in gemm_pass_slices(...) slices.
+int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, int M, int N, int K, int mode, const GemmSplit &ks, bool cold, hipStream_t s) {
+  if (mode != 0 || gemm_pass_slices(M, N, K, ks) == 1) return launch_gemm_folded(x, w, y, M, N, K, mode, ks, cold, s);
+  if (M < 1 || M > GEMM_MAX_ROWS || K % (4 * BK) || N % 32 || !splits_valid(K, ks.splits) || ks.n_main != N) return -1;
+  if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
+  const Launch L{x, w, y, M, N, K, 0, ks.splits, 0, N, N, 0, true, false, s};
+  // few tiles: 128 x 256 ones (1.5B shape, 511 rows: 32 -> 23 us; 1024 rows 41 -> 44)
+  return (M + 255) / 256 * ((N + 255) / 256) * ks.splits <= 128 ? launch_cfg<1, 4, 4, 2>(L) : launch_cfg<1, 4, 8, 2>(L);
 }
 
 }  // namespace pl

@@ -15,6 +15,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <tuple>
 #include <vector>
 
 namespace {
@@ -299,7 +300,7 @@ void free_work(pl_engine::Work &w) {
   w = pl_engine::Work{};
 }
 
-// Passes of more rows than this add up a product's K slices inside the GEMM (launch_gemm_folded).
+// Passes of more rows than this may add up a product's K slices inside the GEMM (launch_gemm_pass).
 constexpr int SLICED_ROWS = 256;
 constexpr int PASS_RING = 8;   // host metadata images of cache-only passes that may wait on the device at once
 
@@ -335,7 +336,12 @@ int alloc_device(pl_engine *e) {
     const int64_t sliced = std::min<int64_t>(R, std::max(B, SLICED_ROWS));
     const int64_t slices = std::max(std::max(std::max(e->ks_qkv.splits * wq, e->ks_o.splits * d), e->ks_d.splits * d) * sliced,
                                     pl::gemm_workspace_elems((int)sliced, 2 * c.d_ffn, e->ks_gu));
-    return std::max(slices, std::max(wq, d) * R);
+    int64_t pass = std::max(wq, d) * R;   // of passes of more rows, in one slice or all
+    const std::tuple<int64_t, int64_t, pl::GemmSplit> plain[] = {{wq, d, e->ks_qkv}, {d, qd, e->ks_o}, {d, c.d_ffn, e->ks_d}};
+    for (const auto &[N, K, ks] : plain)
+      for (int64_t r = SLICED_ROWS + 1; r <= R; ++r)
+        pass = std::max(pass, pl::gemm_pass_slices((int)r, (int)N, (int)K, ks) * N * r);
+    return std::max(slices, pass);
   };
   // the chunk length is fixed by max_batch alone, so a sequence's attention result never depends on
   // how many rows a pass holds
@@ -472,9 +478,9 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   const bool fold = prefill && n > std::max(c.max_batch, SLICED_ROWS);   // many rows: the products come as one slice each
   const bool cold = pl::gemm_cold(e->streamed_weight_bytes);   // every product's weights pass by once per step
   auto gemm = [&](const bf16_t *x, const bf16_t *wt, void *y, float *ws, int N, int K, int mode, const pl::GemmSplit &ks) {
-    return fold ? pl::launch_gemm_folded(x, wt, y, n, N, K, mode, ks, cold, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, cold, s);
+    return fold ? pl::launch_gemm_pass(x, wt, y, n, N, K, mode, ks, cold, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, cold, s);
   };
-  auto slices = [&](const pl::GemmSplit &ks) { return fold ? 1 : ks.splits; };
+  auto slices = [&](const pl::GemmSplit &ks, int N, int K) { return fold ? pl::gemm_pass_slices(n, N, K, ks) : ks.splits; };
   pl::AttnParams ap{};
   ap.page_table = w.pt; ap.ctx_len = w.ctx_len; ap.row_slot = w.m_row_slot(true);
   ap.out = w.attn_out; ap.part_o = w.attn_po; ap.part_ml = w.attn_pml;
@@ -503,7 +509,7 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
     if (rotates) {
       ap.qkv = w.parts; ap.cs = w.cs; ap.splits = e->ks_qkv.splits;
     } else {
-      rc |= pl::launch_rope_append(w.parts, slices(e->ks_qkv), w.cs, w.m_pos(true), w.m_row_slot(true), w.pt, w.q_rot, kv_layer, n,
+      rc |= pl::launch_rope_append(w.parts, slices(e->ks_qkv, wq, d), w.cs, w.m_pos(true), w.m_row_slot(true), w.pt, w.q_rot, kv_layer, n,
                                    c.n_q_heads, c.n_kv_heads, c.head_dim, e->page_tokens, e->pages_per_seq, s);
       ap.q = w.q_rot;
     }
@@ -521,13 +527,13 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
     }
     rc |= gemm(w.attn_out, lw.w_o, w.parts, nullptr, d, qd, 0, e->ks_o);
     if (timed) mark(e, CAT_GEMM);
-    rc |= pl::launch_resid_rmsnorm(w.h, w.parts, slices(e->ks_o), lw.g2, w.a, n, d, c.rms_eps, s);
+    rc |= pl::launch_resid_rmsnorm(w.h, w.parts, slices(e->ks_o, d, qd), lw.g2, w.a, n, d, c.rms_eps, s);
     if (timed) mark(e, CAT_OTHER);
     rc |= gemm(w.a, lw.w_gu, w.mid, w.parts, 2 * c.d_ffn, d, 1, e->ks_gu);
     rc |= gemm(w.mid, lw.w_d, w.parts, nullptr, d, c.d_ffn, 0, e->ks_d);
     if (timed) mark(e, CAT_GEMM);
     const bf16_t *g_next = (l + 1 < c.n_layers) ? layer_weights(e, l + 1).g1 : gf;
-    rc |= pl::launch_resid_rmsnorm(w.h, w.parts, slices(e->ks_d), g_next, w.a, n, d, c.rms_eps, s);
+    rc |= pl::launch_resid_rmsnorm(w.h, w.parts, slices(e->ks_d, d, c.d_ffn), g_next, w.a, n, d, c.rms_eps, s);
   }
   if (prefill) return rc ? fail(PL_E_HIP, "kernel launch failed: %s", hipGetErrorString(hipGetLastError())) : PL_OK;
   mark(e, CAT_OTHER);
@@ -1557,6 +1563,8 @@ int pl_debug_gemm_cfg(int32_t cfg, const void *x, const void *w, void *y, void *
                       int32_t mode, int32_t splits, int32_t n_begin, int32_t n_end, int32_t paired, void *stream) {
   if (!x || !w || !y) return fail(PL_E_INVAL, "NULL argument");
   const bool cold = debug_gemm_cold(&mode, N, K);
+  if (cfg >= pl::GEMM_N_CFGS || (cfg == pl::GEMM_32x128 && mode == 1 && splits == 1) || (paired && splits != 1))
+    return fail(PL_E_INVAL, "unsupported GEMM launch cfg=%d mode=%d splits=%d", cfg, mode, splits);
   int rc = pl::launch_gemm_cfg(cfg, (const bf16_t *)x, (const bf16_t *)w, y, (float *)ws, M, N, K, mode, splits, n_begin,
                                n_end, paired != 0, cold, (hipStream_t)stream);
   if (rc == -1) return fail(PL_E_INVAL, "unsupported GEMM launch cfg=%d M=%d N=%d K=%d mode=%d splits=%d [%d, %d)", cfg, M, N, K, mode, splits, n_begin, n_end);

@@ -439,6 +439,32 @@ def test_prompt_passes_of_many_rows_leave_the_cache_of_reading_token_by_token(we
         e.close()
 
 
+@pytest.mark.parametrize("d,n_prompt", [(256, 290), (1024, 390), (1024, 520)])
+def test_passes_whose_long_product_stays_in_slices_leave_the_cache_of_reading_token_by_token(d, n_prompt):
+    """A down projection of long K leaves a pass of more than 256 rows in all its K slices, by 128 x 256 tiles (few of them) or
+    256 x 256: bit-identical caches and logits to the prompt read one token per step."""
+    m = synth.ModelCfg(2, d, 8, 2, 32, 9216, 512)
+    eng = [pl.Engine.from_model(m, max_batch=2, max_context=576, kv_pool_tokens=1152, kv_page_tokens=64, seed=3, device=0) for _ in range(2)]
+    blob = eng[0].pack_weights(synth.make_weights(m, seed=11), synth.f32_to_bf16_bits)
+    prompt = synth.random_prompts(np.random.default_rng(d), 1, n_prompt, m.vocab)[0]
+    for e in eng:
+        e.load_weights(blob)
+        e.add_sequence(5, prompt, 4)
+    assert eng[0].prefill(0) == n_prompt - 1
+    for _ in range(n_prompt - 1):
+        eng[1].decode_step()
+    kv = [[e.debug_read_kv(0, l, n_prompt - 1) for l in range(m.n_layers)] for e in eng]
+    for l in range(m.n_layers):
+        for part in range(2):
+            assert np.array_equal(kv[0][l][part], kv[1][l][part]), (l, part)
+    for e in eng:
+        e.decode_step(np.array([5, 5], np.int32))
+    logits = [e.debug_get_logits(1) for e in eng]
+    assert np.isfinite(logits[0]).all() and np.array_equal(logits[0], logits[1])
+    for e in eng:
+        e.close()
+
+
 @pytest.mark.parametrize("Hq,Hkv,hd,d", [(16, 1, 128, 256), (4, 4, 64, 256), (8, 1, 32, 256), (12, 2, 64, 2560)])
 def test_decode_steps_rotate_and_append_like_the_passes(Hq, Hkv, hd, d):
     """A decode step's attention adds up the QKV slices, rotates and appends by itself, a pass in a kernel of its

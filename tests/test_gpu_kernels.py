@@ -235,6 +235,28 @@ def test_gemm_swiglu_epilogue(M, F, K):
     assert ok, err
 
 
+@pytest.mark.parametrize("F,K", [(352, 512), (96, 1024), (8960, 256)])
+def test_swiglu_of_every_row_count_gives_the_same_rows(F, K):
+    """Row counts on both sides of every tile height, a last tile of one gate/up pair and of two: shapes whose wavefronts hold both
+    halves of a pair and shapes whose neighbours swap them, against fp64 and bit for bit against one another."""
+    g = torch.Generator(device="cuda").manual_seed(F)
+    x = torch.empty(512, K, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
+    w = synth.bf16_round(np.random.default_rng(F).standard_normal((2 * F, K), dtype=np.float32) * 0.05)
+    wd = dev_bf16(pl.operand_order(w))
+    p = to_np(x).astype(np.float64) @ w.astype(np.float64).T
+    gate, up = (p.reshape(512, F // 32, 2, 32)[:, :, i].reshape(512, F) for i in (0, 1))
+    want, widest = decoder.silu(gate) * up, None
+    for M in (512, 511, 385, 257, 256, 160, 129, 128, 97, 65, 64, 33, 32, 9, 1):
+        y = torch.full((M + 1, F), float("nan"), device="cuda", dtype=torch.bfloat16)
+        pl.pl_gemm_bf16(x.data_ptr(), wd.data_ptr(), y.data_ptr(), M, 2 * F, K, 1, 1, 0)
+        torch.cuda.synchronize()
+        if widest is None:
+            widest = y.clone()
+            ok, err = close(to_np(y[:M]), want, 2e-3, RTOL)
+            assert ok, err
+        assert torch.equal(y[:M], widest[:M]) and bool(y[M].isnan().all()), M
+
+
 CFG_TILES = {0: (32, 256), 1: (64, 256), 2: (128, 256), 3: (64, 128), 4: (128, 128), 5: (256, 128), 6: (64, 64),
              7: (128, 64), 8: (32, 128), 9: (128, 64), 10: (256, 64)}
 
