@@ -203,7 +203,7 @@ int pl_swap_poll(pl_engine *e, int32_t *staged_ready, uint32_t *active_version);
 int pl_add_sequence(pl_engine *e, uint64_t seq_id, const int32_t *prompt, int32_t n_prompt,
                     int32_t max_new, float temperature, int32_t *out_slot);
 /* Batched prompt reading on refill ("add prompts", Alg. 2): reads the positions of the slot's prompt
- * that have not been read yet, except the last one, in passes of up to 1024 positions
+ * that have not been read yet, except the last one, in passes of up to 4096 positions
  * (rows = consecutive positions of one sequence, causal because row i attends to positions <= its
  * own), under the active weights.  It leaves exactly the keys and values that reading those tokens one per
  * step would leave, bit for bit (kernels of many rows keep the order of operations of a row) and emits nothing; the next

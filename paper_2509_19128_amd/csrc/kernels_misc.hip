@@ -34,8 +34,10 @@ __device__ inline void rope_angle(float *cs, int pos, int i, int hd, float theta
 // own ahead of this one), cos/sin of its position, h = E[token], a = rmsnorm(h) * g.
 // As separate launches: metadata copy 4 us, tables 4, work list 13, embedding 13 (7B shape, 256 rows), each with its
 // launch gap; now 14 us.
-__global__ __launch_bounds__(1024) void step_begin_kernel(StepBegin q, AttnParams p, int cap) {
+template <int NT>
+__global__ __launch_bounds__(NT) void step_begin_kernel(StepBegin q, AttnParams p, int cap) {
   if (blockIdx.x == 0) {
+    if constexpr (NT < 1024) return;   // a pass
     const int n_upd = q.updates ? q.updates[0] : 0;
     if (!p.work) return;   // a pass
     for (int i = threadIdx.x; i < n_upd; i += 1024) q.page_table[q.updates[2 + 2 * i]] = q.updates[3 + 2 * i];
@@ -48,10 +50,10 @@ __global__ __launch_bounds__(1024) void step_begin_kernel(StepBegin q, AttnParam
   }
   const int row = blockIdx.x - 1, pos = q.src.pos[row], d8 = q.d >> 3;
   const int tok = min(max(q.src.input_tok[row], 0), q.vocab - 1);
-  const bool mine = (int)threadIdx.x < d8;   // d <= 8192: one piece of eight elements per thread
+  const bool mine = (int)threadIdx.x < d8;   // d <= 8 NT: one piece of eight elements per thread
   bf16x8 e = {};
   if (mine) e = ((const bf16x8 *)(q.embed + (int64_t)tok * q.d))[threadIdx.x];
-  const int i = 1023 - (int)threadIdx.x;   // the last wavefronts, which have least of the row, take the angles
+  const int i = NT - 1 - (int)threadIdx.x;   // the last wavefronts, which have least of the row, take the angles
   if (i < p.hd / 2) rope_angle(q.cs + (int64_t)row * p.hd, pos, i, p.hd, q.theta);
   if (threadIdx.x == 0) {
     q.ctx_len[row] = pos + 1;
@@ -66,7 +68,7 @@ __global__ __launch_bounds__(1024) void step_begin_kernel(StepBegin q, AttnParam
   float v[8], ss = 0.f;
 #pragma unroll
   for (int k = 0; k < 8; ++k) { v[k] = (float)e[k]; ss += v[k] * v[k]; }
-  ss = block_sum<16>(ss);
+  ss = block_sum<NT / 64>(ss);
   if (!mine) return;
   const float r = 1.0f / sqrtf(ss / (float)q.d + q.eps);
   const bf16x8 g = ((const bf16x8 *)q.g)[threadIdx.x];
@@ -238,20 +240,25 @@ static inline int ok() { return hipGetLastError() == hipSuccess ? 0 : -7; }
 
 int launch_step_begin(const StepBegin &q, const AttnParams &p, int cap, hipStream_t s) {
   if (p.n_seq <= 0) return 0;
-  if (p.n_seq > 1024 || q.d > 8192 || ((uintptr_t)p.work & 31)) return -1;
-  hipLaunchKernelGGL(step_begin_kernel, dim3(p.n_seq + 1), dim3(1024), 0, s, q, p, cap);
+  if ((p.work && p.n_seq > 1024) || q.d > 8192 || ((uintptr_t)p.work & 31)) return -1;
+  // the work list needs 1024 threads; the rows of a pass no more than they have pieces (1536 wide: 1000 rows 11 us by 1024 threads, 3000 rows 14 by 256)
+  auto launch = [&](auto kernel, int nt) { hipLaunchKernelGGL(kernel, dim3(p.n_seq + 1), dim3(nt), 0, s, q, p, cap); };
+  if (p.work || q.d > 4096) launch(step_begin_kernel<1024>, 1024);
+  else if (q.d > 2048) launch(step_begin_kernel<512>, 512);
+  else launch(step_begin_kernel<256>, 256);
   return ok();
 }
 
 int launch_resid_rmsnorm(float *h, const float *parts, int splits, const bf16_t *g, bf16_t *a, int n, int d,
                          float eps, hipStream_t s) {
   if (n <= 0) return 0;
-  // rows of up to 4096 floats: 1024 threads, one 16-byte piece each (all loads of a row in flight at
-  // once); wider rows: 1024 threads x 2 pieces (d <= 8192)
-  if (d <= 4096)
-    hipLaunchKernelGGL((resid_rmsnorm_kernel<1024, 1>), dim3(n), dim3(1024), 0, s, h, parts, splits, g, a, n, d, eps);
-  else
-    hipLaunchKernelGGL((resid_rmsnorm_kernel<1024, 2>), dim3(n), dim3(1024), 0, s, h, parts, splits, g, a, n, d, eps);
+  // as many threads as a row has 16-byte pieces, so that all loads of a row are in flight at once and as many rows as fit a
+  // compute unit (rows of 1536 floats, 1000 of them: 13 us by workgroups of 1024 threads; 3000 of them 12 by 512); 4096 to 8192 floats two pieces each
+  auto launch = [&](auto kernel, int nt) { hipLaunchKernelGGL(kernel, dim3(n), dim3(nt), 0, s, h, parts, splits, g, a, n, d, eps); };
+  if (d <= 1024) launch(resid_rmsnorm_kernel<256, 1>, 256);
+  else if (d <= 2048) launch(resid_rmsnorm_kernel<512, 1>, 512);
+  else if (d <= 4096) launch(resid_rmsnorm_kernel<1024, 1>, 1024);
+  else launch(resid_rmsnorm_kernel<1024, 2>, 1024);
   return ok();
 }
 

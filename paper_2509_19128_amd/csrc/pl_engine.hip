@@ -106,6 +106,7 @@ struct pl_engine {
   struct Work {
     hipStream_t stream = nullptr;
     int rows_cap = 0;
+    int pitch = 0;   // rows from one metadata array to the next: rows_cap, or for a pass its own rows (so that its image is short)
     char *meta_h = nullptr, *meta_d = nullptr;   // per-pass metadata: host (pinned) and device images, same layout
     float *h = nullptr, *parts = nullptr, *cs = nullptr, *attn_po = nullptr, *attn_pml = nullptr;
     bf16_t *a = nullptr, *q_rot = nullptr, *attn_out = nullptr, *mid = nullptr;
@@ -118,18 +119,17 @@ struct pl_engine {
     bool attn_rotate = false;  // this step's attention rotates and appends by itself
     int apart_cap = 0;         // rows the list and the partial results of the decode attention are sized for
     bool attn_apart = false;   // the rows of this pass attend one by one, as a decode step's do
-    // the 8-byte ids come first, so every array is aligned for its type whatever rows_cap is
+    // the 8-byte ids come first, so every array is aligned for its type whatever the pitch is
     uint64_t *m_seq_id(bool dev) { return (uint64_t *)(dev ? meta_d : meta_h); }
-    int32_t *m_row_slot(bool dev) { return (int32_t *)(m_seq_id(dev) + rows_cap); }
-    int32_t *m_pos(bool dev) { return m_row_slot(dev) + rows_cap; }
-    int32_t *m_input(bool dev) { return m_pos(dev) + rows_cap; }
-    int32_t *m_forced(bool dev) { return m_input(dev) + rows_cap; }
-    float *m_inv_t(bool dev) { return (float *)(m_forced(dev) + rows_cap); }
+    int32_t *m_row_slot(bool dev) { return (int32_t *)(m_seq_id(dev) + pitch); }
+    int32_t *m_pos(bool dev) { return m_row_slot(dev) + pitch; }
+    int32_t *m_input(bool dev) { return m_pos(dev) + pitch; }
+    int32_t *m_forced(bool dev) { return m_input(dev) + pitch; }
+    float *m_inv_t(bool dev) { return (float *)(m_forced(dev) + pitch); }
     // behind the rows, {count, -, pairs}: a decode step's page-table changes (element, page id; fetched from the host
     // image), a pass's groups of rows (first row, rows)
-    int32_t *m_pairs(bool dev) { return (int32_t *)(m_inv_t(dev) + rows_cap); }
-    int64_t meta_bytes() const { return (int64_t)rows_cap * (4 * 5 + 8); }
-    int64_t image_bytes() const { return meta_bytes() + ((int64_t)rows_cap * 2 + 2) * 4; }
+    int32_t *m_pairs(bool dev) { return (int32_t *)(m_inv_t(dev) + pitch); }
+    static int64_t image_bytes(int64_t rows) { return rows * (4 * 5 + 8) + (rows * 2 + 2) * 4; }
     pl::StepMeta meta(bool dev) {
       return pl::StepMeta{m_row_slot(dev), m_pos(dev), m_input(dev), m_forced(dev), m_inv_t(dev), m_seq_id(dev)};
     }
@@ -145,6 +145,7 @@ struct pl_engine {
     double *ms_into = nullptr;
   };
   std::vector<PassImage> ring;
+  char *ring_h = nullptr;   // the images' pinned memory
   size_t ring_next = 0;
   std::vector<hipEvent_t> ev_slot;   // per slot: end of its background prompt reading
   hipEvent_t ev_pre_last = nullptr;  // end of the last cache-only pass enqueued
@@ -265,8 +266,8 @@ int alloc_work(pl_engine *e, pl_engine::Work &w, int64_t R, int64_t parts_elems,
   const int64_t d = c.d_model, qd = (int64_t)c.n_q_heads * c.head_dim;
   const int64_t wide = e->esz / 2;   // the activation buffers are declared bf16; the fp32 build needs twice the bytes
   int rc;
-  w.rows_cap = (int)R;
-  if ((rc = dev_alloc(&w.meta_d, w.image_bytes()))) return rc;
+  w.rows_cap = w.pitch = (int)R;
+  if ((rc = dev_alloc(&w.meta_d, w.image_bytes(R)))) return rc;
   if ((rc = dev_alloc(&w.h, R * d))) return rc;
   if ((rc = dev_alloc(&w.a, R * d * wide))) return rc;
   if ((rc = dev_alloc(&w.parts, parts_elems))) return rc;
@@ -289,7 +290,7 @@ int alloc_work(pl_engine *e, pl_engine::Work &w, int64_t R, int64_t parts_elems,
   if ((rc = dev_alloc(&w.attn_work, work + w.apart_cap * (int64_t)(c.n_kv_heads + 1)))) return rc;
   w.attn_tickets = w.attn_work + work;
   w.attn_first = w.attn_tickets + w.apart_cap * (int64_t)c.n_kv_heads;
-  if (decode) HIP_TRY(hipHostMalloc((void **)&w.meta_h, (size_t)w.image_bytes(), hipHostMallocDefault));
+  if (decode) HIP_TRY(hipHostMalloc((void **)&w.meta_h, (size_t)w.image_bytes(R), hipHostMallocDefault));
   return PL_OK;
 }
 
@@ -339,8 +340,8 @@ int alloc_device(pl_engine *e) {
     int64_t pass = std::max(wq, d) * R;   // of passes of more rows, in one slice or all
     const std::tuple<int64_t, int64_t, pl::GemmSplit> plain[] = {{wq, d, e->ks_qkv}, {d, qd, e->ks_o}, {d, c.d_ffn, e->ks_d}};
     for (const auto &[N, K, ks] : plain)
-      for (int64_t r = SLICED_ROWS + 1; r <= R; ++r)
-        pass = std::max(pass, pl::gemm_pass_slices((int)r, (int)N, (int)K, ks) * N * r);
+      for (int64_t r = SLICED_ROWS + 1; r <= R; r += 64)   // (among the row counts of a row of tiles, the least is most in favour of slices)
+        pass = std::max(pass, pl::gemm_pass_slices((int)r, (int)N, (int)K, ks) * N * std::min(r + 63, R));
     return std::max(slices, pass);
   };
   // the chunk length is fixed by max_batch alone, so a sequence's attention result never depends on
@@ -356,32 +357,41 @@ int alloc_device(pl_engine *e) {
   e->samp_ws = ws;
   // The passes' buffers and the KV pool come last.  With kv_pool_tokens == 0 the pool takes what is left of the device
   // memory, minus a reserve for the caller, up to the most the slots could ever use.  The passes' buffers give way
-  // where memory is tight: passes of rows_cap rows do the same, more slowly.
+  // where memory is tight, half their rows at a time: passes of rows_cap rows do the same, more slowly.
   const bool automatic = e->n_pages == 0;
   for (;;) {
     hipStream_t s = e->wk[1].stream;
     free_work(e->wk[1]);
     e->wk[1].stream = s;
+    size_t before_b = 0, total_b = 0;
+    if (automatic) HIP_TRY(hipMemGetInfo(&before_b, &total_b));
     rc = alloc_work(e, e->wk[1], e->pass_rows, parts_elems(e->pass_rows), false);
     if (!rc && automatic) {
-      size_t free_b = 0, total_b = 0;
+      size_t free_b = 0;
       HIP_TRY(hipMemGetInfo(&free_b, &total_b));
       const int64_t page_bytes = e->page_stride * e->esz * std::max(c.n_layers, 1);
       const int64_t avail = (int64_t)free_b - KV_AUTO_RESERVE_BYTES;
       const int64_t most = (int64_t)B * e->pages_per_seq;
       set_pool_pages(e, std::min(avail > 0 ? avail / page_bytes : 0, most));
+      // (rows beyond 1024 only where they cost the pool no more than a 64th)
+      if (e->n_pages < most && e->pass_rows > std::max(1024, e->rows_cap) && (int64_t)(before_b - free_b) > avail / 64) {
+        e->pass_rows = std::max(std::max(e->pass_rows / 2, 1024), e->rows_cap);
+        continue;
+      }
       if (e->n_pages < 1) rc = fail(PL_E_NOMEM, "no device memory left for a KV pool (%lld bytes free)", (long long)free_b);
     }
     if (!rc) rc = dev_alloc(&e->kv_pool, e->layer_stride * c.n_layers * e->esz);
     if (rc != PL_E_NOMEM || e->pass_rows == e->rows_cap) break;
     (void)hipGetLastError();
-    e->pass_rows = e->rows_cap;
+    e->pass_rows = std::max(e->pass_rows / 2, e->rows_cap);
   }
   if (rc) return rc;
   const int64_t pool_elems = e->layer_stride * c.n_layers;
   e->ring.resize(PASS_RING);
+  const int64_t image = (pl_engine::Work::image_bytes(e->pass_rows) + 63) / 64 * 64;
+  HIP_TRY(hipHostMalloc((void **)&e->ring_h, (size_t)(image * PASS_RING), hipHostMallocDefault));
   for (auto &im : e->ring) {
-    HIP_TRY(hipHostMalloc((void **)&im.meta_h, (size_t)e->wk[1].image_bytes(), hipHostMallocDefault));
+    im.meta_h = e->ring_h + (&im - e->ring.data()) * image;
     HIP_TRY(hipEventCreate(&im.ev_begin));
     HIP_TRY(hipEventCreate(&im.ev_end));
   }
@@ -716,6 +726,7 @@ int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::ve
         harvest_passes(e);
       }
       w.meta_h = im.meta_h;
+      w.pitch = std::min((n + 63) / 64 * 64, w.rows_cap);   // (a function of n, as graphs hold the arrays' addresses)
       int items = 0, chunks = 0;
       const int per_group = pl::attention_rows_per_group(c.n_q_heads, c.n_kv_heads);
       int32_t *row_slot = w.m_row_slot(false), *pos = w.m_pos(false), *inp = w.m_input(false), *frc = w.m_forced(false);
@@ -748,7 +759,7 @@ int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::ve
       // The dirty flag stays: the decode stream sends the table to its own copy.
       if (r0 == 0)
         HIP_TRY(hipMemcpyAsync(w.pt, e->pt_h, (size_t)c.max_batch * e->pages_per_seq * 4, hipMemcpyHostToDevice, s));
-      HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)w.image_bytes(), hipMemcpyHostToDevice, s));
+      HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)w.image_bytes(w.pitch), hipMemcpyHostToDevice, s));
       HIP_TRY(hipEventRecord(im.ev_begin, s));
       int rc = run_step(e, w, n, true);
       if (rc) return rc;
@@ -827,12 +838,14 @@ int pl_create(const pl_model_cfg *cfg, pl_engine **out) {
   e->seqs.resize(cfg->max_batch);
   set_pool_pages(e, n_pages);
   e->rows_cap = std::max(cfg->max_batch, 256);
-  // no more than all slots can hold; the fp32 test build keeps whole products: fewer rows
-  e->pass_rows = e->f32 ? e->rows_cap : (int)std::min<int64_t>(std::max<int64_t>((int64_t)cfg->max_batch * cfg->max_context, e->rows_cap), pl::GEMM_MAX_ROWS);
-  e->wk[0].rows_cap = e->rows_cap;
-  e->wk[1].rows_cap = e->pass_rows;
+  // a whole prompt of the longest, or 1024 rows (a recomputation's pass holds several sequences), and no more than all slots
+  // can hold; the fp32 test build keeps whole products: fewer rows
+  const int64_t all = (int64_t)cfg->max_batch * cfg->max_context, longest = std::min<int64_t>(std::max(cfg->max_context, 1024), pl::GEMM_MAX_ROWS);
+  e->pass_rows = e->f32 ? e->rows_cap : (int)std::max<int64_t>(std::min(all, longest), e->rows_cap);
+  e->wk[0].rows_cap = e->wk[0].pitch = e->rows_cap;
+  e->wk[1].rows_cap = e->wk[1].pitch = e->pass_rows;
   if (e->dry) {
-    e->wk[0].meta_h = (char *)calloc(1, (size_t)e->wk[0].image_bytes());
+    e->wk[0].meta_h = (char *)calloc(1, (size_t)pl_engine::Work::image_bytes(e->rows_cap));
     if (!e->wk[0].meta_h) { delete e; return fail(PL_E_NOMEM, "out of host memory"); }
   } else {
     if (cfg->device < 0) { delete e; return fail(PL_E_INVAL, "bad device"); }
@@ -855,7 +868,7 @@ void pl_destroy(pl_engine *e) {
     void *dev[] = {e->wbuf[0], e->wbuf[1], e->kv_pool, e->logits, e->samp_ws};
     for (void *p : dev)
       if (p) (void)hipFree(p);
-    void *hst[] = {e->pt_h, e->wk[0].meta_h, e->tok_h, e->lp_h};
+    void *hst[] = {e->pt_h, e->wk[0].meta_h, e->tok_h, e->lp_h, e->ring_h};
     for (void *p : hst)
       if (p) (void)hipHostFree(p);
     for (auto &g : e->graphs) drop_graph(g);
@@ -863,7 +876,6 @@ void pl_destroy(pl_engine *e) {
     free_work(e->wk[0]);
     free_work(e->wk[1]);
     for (auto &im : e->ring) {
-      if (im.meta_h) (void)hipHostFree(im.meta_h);
       if (im.ev_begin) (void)hipEventDestroy(im.ev_begin);
       if (im.ev_end) (void)hipEventDestroy(im.ev_end);
     }
@@ -1240,7 +1252,7 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
       e->pt_dirty = false;
     }
     upd[0] = n_upd;
-    if (e->f32) HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)w.meta_bytes(), hipMemcpyHostToDevice, s));
+    if (e->f32) HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)w.image_bytes(w.pitch), hipMemcpyHostToDevice, s));
     HIP_TRY(hipEventRecord(e->ev_a, s));
     e->prof_n = 0;   // a replayed graph records no per-kernel events: nothing of an earlier step may be counted again
     int rc = run_step(e, w, n);
@@ -1601,7 +1613,7 @@ int pl_debug_gemm_folded(const void *x, const void *w, void *y, int32_t M_max, i
                          void *stream) {
   if (!x || !w || !y) return fail(PL_E_INVAL, "NULL argument");
   const bool cold = debug_gemm_cold(&mode, N, K);
-  if (M_max < 1 || M_max > 512 || M < 1 || M > pl::GEMM_MAX_ROWS || N < 32 || K < 256 || (mode != 0 && mode != 1))
+  if (M_max < 1 || M_max > 512 || M < 1 || M > 1024 || N < 32 || K < 256 || (mode != 0 && mode != 1))
     return fail(PL_E_INVAL, "unsupported GEMM shape");
   int rc = pl::launch_gemm_folded((const bf16_t *)x, (const bf16_t *)w, y, M, N, K, mode, pl::gemm_pick_split(M_max, N, K, mode), cold,
                                   (hipStream_t)stream);

@@ -439,6 +439,33 @@ def test_prompt_passes_of_many_rows_leave_the_cache_of_reading_token_by_token(we
         e.close()
 
 
+@pytest.mark.parametrize("d,f,n_prompt", [(256, 512, 1901), (768, 9216, 4098), (2304, 512, 4500)])
+def test_passes_of_more_than_1024_rows_leave_the_cache_of_reading_token_by_token(d, f, n_prompt):
+    """Bit-identical caches and logits, at widths on both sides of what a row's kernels choose their threads by and with a long product
+    that stays in slices.  4098 and 4500: a full pass of 4096 rows and one of a single row, and one with a longer remainder."""
+    m = synth.ModelCfg(2, d, 8, 2, 32, f, 512)
+    eng = [pl.Engine.from_model(m, max_batch=2, max_context=4608, kv_pool_tokens=4608, kv_page_tokens=64, seed=3, device=0) for _ in range(2)]
+    blob = eng[0].pack_weights(synth.make_weights(m, seed=11), synth.f32_to_bf16_bits)
+    prompt = synth.random_prompts(np.random.default_rng(d), 1, n_prompt, m.vocab)[0]
+    for e in eng:
+        e.load_weights(blob)
+    assert eng[0].add_sequence(5, prompt, 4) == 0 and eng[0].prefill(0) == n_prompt - 1
+    assert eng[0].stats()["prefill_passes"] == -(-(n_prompt - 1) // 4096)
+    assert eng[1].add_sequence(5, prompt, 4) == 0
+    for _ in range(n_prompt - 1):
+        eng[1].decode_step()
+    kv = [[e.debug_read_kv(0, l, n_prompt - 1) for l in range(m.n_layers)] for e in eng]
+    for l in range(m.n_layers):
+        for part in range(2):
+            assert np.array_equal(kv[0][l][part], kv[1][l][part]), (l, part)
+    for e in eng:
+        e.decode_step(np.array([5, 5], np.int32))
+    logits = [e.debug_get_logits(1) for e in eng]
+    assert np.isfinite(logits[0]).all() and np.array_equal(logits[0], logits[1])
+    for e in eng:
+        e.close()
+
+
 @pytest.mark.parametrize("d,n_prompt", [(256, 290), (1024, 390), (1024, 520)])
 def test_passes_whose_long_product_stays_in_slices_leave_the_cache_of_reading_token_by_token(d, n_prompt):
     """A down projection of long K leaves a pass of more than 256 rows in all its K slices, by 128 x 256 tiles (few of them) or
