@@ -133,6 +133,12 @@ struct Tile {
     __builtin_amdgcn_sched_barrier(0);
 #endif
   }
+  // no load is on its way to LDS any more
+  __device__ __forceinline__ void drain() {
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
+  }
   // Issue order of a quarter of a k-step: LDS reads (for the next quarter) and VM loads one by one between the products.
   template <int VM, bool READS>
   __device__ __forceinline__ void order() {
@@ -201,20 +207,62 @@ struct Tile {
     kstep<3, false, 0>(p, 0);
   }
   // accumulator register i of lane l is column (i / 4) * 8 + (l / 32) * 4 + i % 4, row l % 32
-  // fp32 sums: row stride ldy, columns counted from y_col0, columns below n_end (a multiple of 32)
+  // a 32 x 32 block so that the four lanes of a quad hold 64 bytes of a row: v[t] is row (l % 32 & ~3) + t, columns l / 32 * 16 + l % 4 * 4 on
+  static __device__ __forceinline__ void by_rows(f32x4 (&v)[4], const f32x16 &c) {
+#ifdef __HIP_DEVICE_COMPILE__
+    const int odd = threadIdx.x & 1, high = threadIdx.x >> 1 & 1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+      auto halves = [&](float x, float y, uint32_t &a, uint32_t &b) {   // lanes 32 .. 63 of x against 0 .. 31 of y
+        const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false));
+        a = r[0]; b = r[1];
+      };
+      uint32_t q[4];   // 16 columns of a row, in groups of four
+      halves(c[e], c[8 + e], q[0], q[1]);
+      halves(c[4 + e], c[12 + e], q[2], q[3]);
+      // each lane reads its neighbour's registers before it chooses (a choice between reads would be a branch that leaves the neighbour out)
+      uint32_t x[4], y[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q[k ^ 1], 0xB1, 0xf, 0xf, true);   // quad_perm 1 0 3 2
+#pragma unroll
+      for (int k = 0; k < 4; ++k) y[k] = odd != (k & 1) ? x[k] : q[k];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)y[k ^ 2], 0x4E, 0xf, 0xf, true);   // quad_perm 2 3 0 1
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k][e] = __uint_as_float(high != (k >> 1) ? x[k] : y[k]);
+    }
+#endif
+  }
+  // fp32 sums: row stride ldy, columns counted from y_col0, columns below n_end (a multiple of 32).
+  // Stores of 64 bytes of a row instead of 32 (a lane's own columns): LM head of the 7B shape, 256 rows, 322 -> 306 us, 7B QKV 22.6 -> 20.9,
+  // 32B QKV, 128 rows, 22.3 -> 21.4.  Up to 64 rows the exchange costs more than it saves (1.5B QKV, 64 rows, 4.8 -> 5.0; a step of the tiny
+  // shape 3 %).
   __device__ __forceinline__ void store(float *Y, int n_tile0, int m0, int M, int n_end, int64_t ldy, int y_col0) const {
     const int n0 = n_tile0 + wn * BT * 32;
 #pragma unroll
     for (int a = 0; a < AT; ++a) {
-      const int m = m0 + (wm * AT + a) * 32 + lrow;
+      const int m = m0 + (wm * AT + a) * 32;
       if (m >= M) continue;
 #pragma unroll
       for (int b = 0; b < BT; ++b) {
         if (n0 + b * 32 >= n_end) continue;
-        float *y = Y + m * ldy + (n0 + b * 32 + half * 4 - y_col0);
+        if (M <= 64) {
+          float *y = Y + (m + lrow) * ldy + (n0 + b * 32 + half * 4 - y_col0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          *(f32x4 *)(y + i * 8) = f32x4{acc[a][b][4 * i], acc[a][b][4 * i + 1], acc[a][b][4 * i + 2], acc[a][b][4 * i + 3]};
+          for (int i = 0; i < 4; ++i)
+            if (m + lrow < M) *(f32x4 *)(y + i * 8) = f32x4{acc[a][b][4 * i], acc[a][b][4 * i + 1], acc[a][b][4 * i + 2], acc[a][b][4 * i + 3]};
+          continue;
+        }
+        f32x4 v[4];
+        by_rows(v, acc[a][b]);
+        float *y = Y + (m + (lrow & ~3)) * ldy + (n0 + b * 32 + half * 16 + (lrow & 3) * 4 - y_col0);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          if (m + (lrow & ~3) + t < M) *(f32x4 *)(y + t * ldy) = v[t];
+#ifdef __HIP_DEVICE_COMPILE__
+        __builtin_amdgcn_sched_barrier(0);   // (one block's registers at a time)
+#endif
       }
     }
   }
@@ -387,20 +435,67 @@ __global__ __launch_bounds__(256) void gemm_fold_kernel(const bf16_t *__restrict
   gemm_tile<WM, WN, AT, BT, MODE, false, true>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, 0, n_end, N, 0);
 }
 
-// SwiGLU product of many rows by 256 x 256 tiles, one per compute unit: workgroups below n_big take the tiles of columns [0, n_cut)
-// (paired on XCDs as above), the others 256 x 64 tiles of the columns behind, which would be a nearly empty last round of big
-// ones, in one slice or (FOLD) in slices of `ksteps` added up.  1.5B shape, 1024 rows (280 big tiles): 66 us, as two rounds of big
-// ones 75, by 128 x 128 tiles 78; 7B shape with its sliced remainder, 1024 rows, 265, by 128 x 256 tiles and two launches 272.
-template <bool FOLD>
-__global__ __launch_bounds__(256) void gemm_wide_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
-                                                        void *__restrict__ Yv, int M, int N, int K, int ksteps, int n_cut, int n_big) {
-  __shared__ __attribute__((aligned(1024))) bf16_t xs[Tile<1, 4, 8, 2, false>::LDS];
-  const bool big = (int)blockIdx.x < n_big;   // uniform for the workgroup
-  const int i = big ? blockIdx.x : blockIdx.x - n_big, nrow = (M + 255) / 256;
-  const int m0 = (i >> 3) % nrow * 256, ctile = (i / (8 * nrow)) * 8 + (i & 7), n0 = big ? ctile * 256 : n_cut + ctile * 64;
-  if (n0 >= (big ? n_cut : N)) return;        // padding of the flat grid
-  if (big) gemm_tile<1, 4, 8, 2, 1, false>(xs, X, W, Yv, M, N, K, K / BK, n0, m0, 0, n_cut, N, 0);
-  else gemm_tile<4, 1, 2, 2, 1, false, FOLD>(xs, X, W, Yv, M, N, K, ksteps, n0, m0, 0, N, N, 0);
+// Products of more 256 x 256 tiles than compute units: a workgroup of each takes tiles one after the other and loads the first
+// k-steps of the next one under the last products of the tile at hand (as gemm_tile2), so that the pipeline fills once and not
+// once per round (one tile fills a compute unit: no other workgroup could work meanwhile).  Tiles below n_big are those of columns
+// [0, n_cut), all K slices (mode 0); the columns behind, which would be a nearly empty last round, go in narrower tiles: LEFT 0
+// 256 x 128 (sliced alike), 2 256 x 64 with the K of a tile in slices of `ksteps` added up (SwiGLU; the big tiles are whole).
+// One launch of a workgroup per tile and this kernel: gate/up of the 1.5B shape, 3000 rows (840 tiles), 166 and 154 us, its down product
+// (648) 112 and 104; LM head of the 7B shape, 256 rows (594), 337 and 322, 129 rows 303 and 279; 7B down as one slice, 512 rows, 171 and 146.
+template <int MODE, bool COLD, int LEFT>
+__global__ __launch_bounds__(256) void gemm_rounds_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
+                                                          void *__restrict__ Yv, int M, int N, int K, int ksteps, int n_cut, int n_big, int n_left) {
+  using Big = Tile<1, 4, 8, 2, COLD>;
+  __shared__ __attribute__((aligned(1024))) bf16_t xs[Big::LDS];
+  static_assert(LEFT == 0 || (LEFT == 2 && MODE == 1), "leftover tiles");
+  constexpr int LN = LEFT == 0 ? 128 : 64;
+  const int nrow = (M + 255) / 256, per = MODE == 0 ? ksteps : K / BK;
+  struct At { int m0, n0, split; };
+  // tile `i` of column tiles `width` wide from `n_begin`: row tiles of a column tile and slice 8 apart, padded as everywhere
+  auto at = [&](int i, int n_begin, int n_end, int width) {
+    const int item = (i / (8 * nrow)) * 8 + (i & 7), nct = (n_end - n_begin + width - 1) / width;
+    return At{(i >> 3) % nrow * 256, n_begin + item % nct * width, item / nct};
+  };
+  const int slices = MODE == 0 ? (K / BK + per - 1) / per : 1;
+  auto next = [&](int i) {   // the first tile from i on that is none of the grid's padding
+    while (i < n_big && at(i, 0, n_cut, 256).split >= slices) i += gridDim.x;
+    return i;
+  };
+  int i = next(blockIdx.x);
+  if (i < n_big) {   // (all of this is uniform for the workgroup)
+    Big t;
+    t.init(xs, X, W, M, N, K);
+    At c = at(i, 0, n_cut, 256);
+    auto p = t.part(c.n0, c.m0, c.split * per, M, N, K);
+    t.zero();
+    t.begin(p);
+    for (;;) {
+      const int nks = min(per, K / BK - c.split * per), n = next(i + gridDim.x);
+      const At d = n < n_big ? at(n, 0, n_cut, 256) : c;   // behind the last tile: its own first k-steps again, which nothing reads
+      int ks = 0;
+      for (; ks < nks - 4; ks += 4) t.four(p, ks);
+      t.template kstep<0, true, 3>(p, ks + 3);
+      p = t.part(d.n0, d.m0, d.split * per, M, N, K);
+      t.template kstep<1, true, 3>(p, 0);
+      t.template kstep<2, true, 3>(p, 1);
+      t.template kstep<3, true, 3>(p, 2);
+      if constexpr (MODE == 0) t.store((float *)Yv + (int64_t)c.split * M * N, c.n0, c.m0, M, n_cut, N, 0);
+      else t.store_swiglu((bf16_t *)Yv, c.n0, c.m0, M, n_cut, N);
+      if (n >= n_big) break;
+      t.zero();
+      c = d;
+      i = n;
+    }
+    t.drain();
+    __syncthreads();
+  }
+  for (int j = blockIdx.x; j < n_left; j += gridDim.x) {
+    const At c = at(j, n_cut, N, LN);
+    if (c.split >= slices) continue;
+    if constexpr (LEFT == 0) gemm_tile<1, 4, 8, 1, MODE, COLD>(xs, X, W, Yv, M, N, K, per, c.n0, c.m0, c.split, N, N, 0);
+    else gemm_tile<4, 1, 2, 2, MODE, false, true>(xs, X, W, Yv, M, N, K, ksteps, c.n0, c.m0, 0, N, N, 0);
+    __syncthreads();   // (the next tile's first stages, and the halves that neighbours swap, share the LDS)
+  }
 }
 
 // The SwiGLU product of a 129..256-row batch in ONE launch of one workgroup per compute unit.  Workgroup i
@@ -558,15 +653,21 @@ int launch_fold_cfg(Launch L) {
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }
 
-// SwiGLU product of many rows: columns [0, n_cut) by 256 x 256 tiles, the rest by narrow tiles, its K in rem_splits slices
-int launch_wide(const Launch &L, int n_cut, int rem_splits) {
-  const int nrow = (L.M + 255) / 256;
-  const int big = (n_cut / 256 + 7) / 8 * 8 * nrow, left = ((L.N - n_cut + 63) / 64 + 7) / 8 * 8 * nrow;
-  const int ksteps = 4 * ((L.K / (4 * BK) + rem_splits - 1) / rem_splits);
-  if (rem_splits == 1)
-    hipLaunchKernelGGL((gemm_wide_kernel<false>), dim3(big + left), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps, n_cut, big);
-  else
-    hipLaunchKernelGGL((gemm_wide_kernel<true>), dim3(big + left), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps, n_cut, big);
+// Columns [0, n_cut) by 256 x 256 tiles, a workgroup per compute unit, the rest by narrower tiles (LEFT of gemm_rounds_kernel) in the
+// same launch; rem_splits: the slices that LEFT 2 adds up.
+template <int LEFT>
+int launch_rounds(const Launch &L, int n_cut, int rem_splits = 1) {
+  const int nrow = (L.M + 255) / 256, ln = LEFT == 0 ? 128 : 64, splits = L.mode == 0 ? L.splits : 1;
+  const int big = ((n_cut + 255) / 256 * splits + 7) / 8 * 8 * nrow, left = ((L.N - n_cut + ln - 1) / ln * splits + 7) / 8 * 8 * nrow;
+  const int slices = L.mode == 0 ? L.splits : rem_splits, ksteps = 4 * ((L.K / (4 * BK) + slices - 1) / slices);
+  with_cold<1>(L.cold, [&](auto COLD) {
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(256), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps, n_cut, big, n_cut < L.N ? left : 0);
+    };
+    constexpr bool cold = decltype(COLD)::value;
+    if (L.mode == 1) launch(gemm_rounds_kernel<1, cold, LEFT>);
+    else if constexpr (LEFT == 0) launch(gemm_rounds_kernel<0, cold, 0>);
+  });
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }
 
@@ -603,6 +704,21 @@ int gemm_tile_rows(int cfg) {
   return 0;
 }
 
+// us per k-step of this many 256 x 256 tiles
+float big_rounds(int64_t tiles) { return tiles / 256 * 1.45f + (tiles % 256 ? 1.05f + tiles % 256 * (0.4f / 256) : 0.f); }
+
+// Columns that launch_rounds<0> gives to 256 x 256 tiles: all, or full rounds of them where what is left fits one round of 256 x 128 tiles
+// (0.89 us per k-step when they fill the chip, 0.5 when few) in less time; *us: per k-step.
+int rounds_cut(int M, int N, int splits, float *us) {
+  const int per = (M + 255) / 256 * splits, ncol = (N + 255) / 256, cut = ncol * per / 256 * 256 / per, left = (N - cut * 256 + 127) / 128 * per;
+  *us = big_rounds((int64_t)ncol * per);
+  if (cut == 0 || cut == ncol || left > 256) return N;
+  const float with = big_rounds((int64_t)cut * per / 256 * 256) + (cut * per % 256 ? 1.45f : 0.f) + 0.5f + left * (0.39f / 256);
+  if (with >= *us) return N;
+  *us = with;
+  return cut * 256;
+}
+
 // Tile shape of a call.  Shapes whose wavefronts stack rows have no SwiGLU pairs (64 x 64, 128 x 64); 64 x 64 tiles for up to 32 rows
 // pay only where W comes from memory (7B down in one slice, 16 rows: 75 us, by 32 x 128 tiles 95; O from the cache 10.6 and 10.0); 128 x 128
 // tiles in two rows of two are a second choice where two of them share a unit.
@@ -618,7 +734,11 @@ int pick_shape(int M, int N, int K, int mode, int splits, bool cold) {
     if (t.cfg == GEMM_64x64 && (mode == 1 || (M <= 32 && !cold))) continue;
     if ((t.cfg == GEMM_128x64 && mode == 1) || (t.cfg == GEMM_128x128 && n > 512)) continue;
     const float r = n * (1.f / 256);
-    const float us = t.fixed + t.out * out_mb + ksteps * (t.base + t.load * std::min(r, 1.f) + t.round * ((n + 255) / 256 - 1) + t.more * std::max(r - 1, 0.f));
+    float us = t.fixed + t.out * out_mb + ksteps * (t.base + t.load * std::min(r, 1.f) + t.round * ((n + 255) / 256 - 1) + t.more * std::max(r - 1, 0.f));
+    if (t.cfg == GEMM_256x256 && n > 256) {
+      rounds_cut(M, N, splits, &us);
+      us = t.fixed + ksteps * us;   // (what earlier rounds write goes out under later ones)
+    }
     const float bound = std::max(us, floor_us + r * 0.128f);
     if (best < 0 || bound < best_us) { best = t.cfg; best_us = bound; }
   }
@@ -746,14 +866,16 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
   // are non-temporal: LM head of the 7B / 32B shape by 128 x 256 tiles, 129 rows 287 / 474 us with ordinary, 318 / 550 with non-temporal
   // loads, 160 rows 295 / 473 and 301 / 502, 192 rows 303 / 457 and 300 / 438.
   if (paired && (M - 1) % gemm_tile_rows(cfg) < gemm_tile_rows(cfg) / 2) cold = false;
+  if (cfg == GEMM_256x256 && n_main == N && (mode == 0 || ks.splits == 1) && (M + 255) / 256 * ((N + 255) / 256) * ks.splits > 256 &&
+      (int64_t)N * K * 2 < GEMM_MAX_OPERAND_BYTES) {
+    float us;
+    return launch_rounds<0>(Launch{x, w, y, M, N, K, mode, ks.splits, 0, N, N, 0, true, cold, s}, rounds_cut(M, N, ks.splits, &us));
+  }
   int rc = launch_gemm_cfg(cfg, x, w, y, ws, M, N, K, mode, ks.splits, 0, n_main, paired && (mode == 0 || ks.splits == 1), cold, s);
   if (rc || n_main == N) return rc;
   return launch_gemm_cfg(GEMM_64x128, x, w, y, ws, M, N, K, mode, mode == 1 ? ks.rem_splits : ks.splits, n_main, N,
                          false, cold, s);
 }
-
-// us per k-step of this many 256 x 256 tiles
-static double big_rounds(int64_t tiles) { return tiles / 256 * 1.45 + (tiles % 256 ? 1.05 + tiles % 256 * (0.4 / 256) : 0.0); }
 
 // us per k-step of a folded product by its four tile shapes: the time of the fullest compute unit, 0.26 / 0.38 / 0.50 / 0.80 per
 // resident 64 x 64 / 128 x 64 / 128 x 128 / 128 x 256 tile (fits of a sweep over twelve shapes at the products of the 1.5B, 7B
@@ -790,7 +912,7 @@ int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, 
   if (mode == 1 && ks.n_main < N) {
     // 7B shape, main columns and remainder: 128 x 256 tiles and a launch for the remainder 135 us with 511 rows, 195 with 700, 272 with
     // 1024; 256 x 256 tiles with the remainder in their launch 137, 183, 265.  (Splits of the main columns do not occur.)
-    if (ks.splits == 1 && M > 512) return launch_wide(L, ks.n_main, ks.rem_splits);
+    if (ks.splits == 1 && M > 512) return launch_rounds<2>(L, ks.n_main, ks.rem_splits);
     const int rc = ks.splits == 1 && ks.n_main >= 128 * 256 ? launch_fold_cfg<1, 4, 4, 2>(L) : launch_fold_cfg<2, 2, 2, 2>(L);
     if (rc) return rc;
     L.n_begin = ks.n_main; L.n_end = N; L.splits = ks.rem_splits;
@@ -803,16 +925,14 @@ int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, 
     // goes to the others), a round of leftover 256 x 64 tiles 0.75.  Fits of a sweep over the 1.5B, 7B and 32B shapes at 300 to 1024 rows; us
     // by 128-row tiles, by 256 x 256 and with leftovers: 1.5B 300 rows 34 / 41 / -, 511 49 / 36 / -, 768 61 / 41 / -, 1024 78 / 75 / 66; 7B 300
     // 100 / 146 / 123, 511 149 / 155 / 136, 768 198 / 176 / 242, 1024 251 / 244 / 265; 32B 300 207 / 232 / 275, 511 279 / 247 / 315, 1024 491 / 468 / 497.
-    const int nrow = (M + 255) / 256, ncol = (N + 255) / 256, cut = ncol * nrow / 256 * 256 / nrow;
-    const int left = (N - cut * 256 + 63) / 64 * nrow;
-    const double t[4] = {big_rounds(nrow * ncol), N >= 128 * 256 ? (M + 127) / 128 * ncol / 256. * 1.05 : 1e9,
-                         (M + 127) / 128 * ((N + 127) / 128) / 256. * 0.62,
-                         cut > 0 ? nrow * ncol / 256 * 1.45 + (left + 255) / 256 * 0.75 : 1e9};
-    switch (std::min_element(t, t + 4) - t) {
-      case 0: L.cold = false; return launch_cfg<1, 4, 8, 2>(L);
+    const int ncol = (N + 255) / 256;
+    float big;
+    const int cut = rounds_cut(M, N, 1, &big);
+    const float t[3] = {big, N >= 128 * 256 ? (M + 127) / 128 * ncol / 256.f * 1.05f : 1e9f, (M + 127) / 128 * ((N + 127) / 128) / 256.f * 0.62f};
+    switch (std::min_element(t, t + 3) - t) {
+      case 0: L.cold = false; return launch_rounds<0>(L, cut);
       case 1: return launch_cfg<1, 4, 4, 2>(L);
-      case 2: return launch_cfg<2, 2, 2, 2>(L);
-      default: return launch_wide(L, cut * 256, 1);
+      default: return launch_cfg<2, 2, 2, 2>(L);
     }
   }
   switch (fold_shape(M, N, nullptr)) {
@@ -844,8 +964,9 @@ int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, int M, int N, in
   if (M < 1 || M > GEMM_MAX_ROWS || K % (4 * BK) || N % 32 || !splits_valid(K, ks.splits) || ks.n_main != N) return -1;
   if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
   const Launch L{x, w, y, M, N, K, 0, ks.splits, 0, N, N, 0, true, false, s};
+  float us;
   // few tiles: 128 x 256 ones (1.5B shape, 511 rows: 32 -> 23 us; 1024 rows 41 -> 44)
-  return (M + 255) / 256 * ((N + 255) / 256) * ks.splits <= 128 ? launch_cfg<1, 4, 4, 2>(L) : launch_cfg<1, 4, 8, 2>(L);
+  return (M + 255) / 256 * ((N + 255) / 256) * ks.splits <= 128 ? launch_cfg<1, 4, 4, 2>(L) : launch_rounds<0>(L, rounds_cut(M, N, ks.splits, &us));
 }
 
 }  // namespace pl

@@ -446,6 +446,31 @@ def test_products_of_an_engine_with_cold_weights_give_the_same_bits(M_max, N, K,
         both(M, 1, lambda y, M, md: pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), M_max, M, N, K, md, 0))
 
 
+@pytest.mark.parametrize("M,N,K,mode,splits", [(130, 66048, 256, 0, 1), (200, 78112, 512, 0, 1), (256, 65600, 768, 1, 1), (256, 131136, 256, 1, 1),
+                                              (300, 33792, 256, 0, 1), (512, 36896, 1280, 0, 2), (511, 33856, 512, 1, 1), (129, 152064, 256, 0, 1)])
+def test_products_of_more_tiles_than_compute_units(M, N, K, mode, splits):
+    """A workgroup takes 256 x 256 tiles one after the other, whatever is left behind full rounds by narrower ones: with and without
+    leftover columns, short last column tiles and rows, K of four k-steps (the ring never runs within a tile) and slices.  Against the
+    float64 product (sums of K products of N(0, 1) and N(0, 0.05): the bound of the tests above), and nothing written beyond the rows."""
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    x = torch.empty(M, K, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
+    w = torch.empty(N, K, device="cuda", dtype=torch.bfloat16).normal_(0, 0.05, generator=g)
+    packed = w.view(N // 32, 32, K // 64, 2, 4, 8).permute(2, 0, 4, 3, 1, 5).contiguous()   # [k-step][row block][j][half][row][8]
+    shape = (splits, M, N) if mode == 0 else (1, M, N // 2)
+    y = torch.full((shape[0] * M + 1, shape[2]), float("nan"), device="cuda", dtype=torch.float32 if mode == 0 else torch.bfloat16)
+    pl.pl_gemm_bf16(x.data_ptr(), packed.data_ptr(), y.data_ptr(), M, N, K, mode, splits, 0)
+    torch.cuda.synchronize()
+    assert bool(y[-1].isnan().all())
+    got = y[:-1].view(shape).double().sum(0)
+    ref = x.double() @ w.double().T
+    if mode == 1:
+        r = ref.view(M, N // 64, 2, 32)
+        ref = (torch.nn.functional.silu(r[:, :, 0]) * r[:, :, 1]).reshape(M, N // 2)
+        assert bool((got - ref).abs().le(2 ** -8 * ref.abs() + 1e-3).all())   # rounded to bf16; sums of up to 768 products, both factors
+    else:
+        assert bool((got - ref).abs().le(1e-4 * np.sqrt(K) * 0.05 + 1e-4 * ref.abs()).all())
+
+
 @pytest.mark.parametrize("M,mode", [(1, 0), (37, 0), (200, 0), (200, 1)])
 def test_products_of_operands_at_any_alignment(M, mode):
     """16-byte accesses, direct loads to LDS among them, on operands that start at any element."""
