@@ -520,7 +520,7 @@ __global__ __launch_bounds__(HD) void attn_merge_kernel(AttnParams p) {
 
 // Attention of the rows of a cache-only pass: consecutive positions of one sequence, each over the positions up to its
 // own.  One workgroup per (group of rows, kv head) walks all keys of the group's longest row; the columns of an MFMA
-// are the heads of 16 / G rows, and every K/V operand serves CB such column blocks, where one row per workgroup
+// are the heads of 16 CB / G rows, and every K/V operand serves CB blocks of 16 columns, where one row per workgroup
 // (as in a decode step) reads the sequence once per row.  Operation by operation the same sums as the decode kernel
 // for every row: runs, subs, wavefronts and chunks in the same order; a run that lies beyond a row's positions
 // leaves its column as it was (factor 1, product not taken: 0 times an infinity would not be 0).
@@ -533,7 +533,7 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnParams p) {
   const int g = blockIdx.x % p.Hkv, n_groups = p.groups[0], index = n_groups - 1 - (int)(blockIdx.x / p.Hkv);   // longest rows first
   if (index < 0) return;
   const int row0 = p.groups[2 + 2 * index], nrows = p.groups[3 + 2 * index];
-  const int G = p.Hq / p.Hkv, rpb = 16 / G;   // rows of a column block
+  const int G = p.Hq / p.Hkv;   // column c of all CB blocks: head c % G of row c / G
   // (constant address space: the loop's stores to LDS would turn the page ids into vector loads that wait for the keys in flight)
   const scalar_i32 *pt = (const scalar_i32 *)(p.page_table + (int64_t)p.row_slot[row0] * p.pages_per_seq);
   const int ctx0 = p.ctx_len[row0], ctx_max = ctx0 + nrows - 1;
@@ -544,15 +544,15 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnParams p) {
   // queries in operand order: element (column block, slice j, lane); in LDS, as the registers are taken by the results
   __shared__ __attribute__((aligned(16))) bf16x8 sq[CB * NJ * 64];
   for (int i = threadIdx.x; i < CB * NJ * 64; i += 256) {
-    const int ln = i & 63, j = i / 64 % NJ, cb = i / (64 * NJ), c = ln & 15, r = cb * rpb + c / G;
+    const int ln = i & 63, j = i / 64 % NJ, c = i / (64 * NJ) * 16 + (ln & 15), r = c / G;
     bf16x8 v = {};
-    if (c / G < rpb && r < nrows) v = *(const bf16x8 *)(p.q + ((int64_t)(row0 + r) * p.Hq + g * G + c % G) * HD + j * 32 + (ln >> 4) * 8);
+    if (r < nrows) v = *(const bf16x8 *)(p.q + ((int64_t)(row0 + r) * p.Hq + g * G + c % G) * HD + j * 32 + (ln >> 4) * 8);
     sq[i] = v;
   }
   __shared__ int s_ctx[COLS];   // context of a column; columns without a row see no position
   if (threadIdx.x < COLS) {
-    const int in = threadIdx.x % 16 / G, r = threadIdx.x / 16 * rpb + in;
-    s_ctx[threadIdx.x] = in < rpb && r < nrows ? ctx0 + r : 0;
+    const int r = threadIdx.x / G;
+    s_ctx[threadIdx.x] = r < nrows ? ctx0 + r : 0;
   }
 
   __shared__ __attribute__((aligned(16))) float sm_o[4][COLS][HD];
@@ -718,8 +718,8 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnParams p) {
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int at = threadIdx.x + 256 * k, cc = at / (HD / 4), d = at % (HD / 4) * 4;
-    const int in = cc % 16 / G, r = cc / 16 * rpb + in, h = cc % 16 % G;
-    if (in >= rpb || r >= nrows) continue;
+    const int r = cc / G, h = cc % G;
+    if (r >= nrows) continue;
     bf16x4 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = (__bf16)(run_o[k][e] / run_l[cc]);
@@ -806,9 +806,10 @@ int launch_attention(const AttnParams &p, hipStream_t s, int part) {
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }
 
-// Rows of a group of attn_rows_kernel: CB column blocks of 16 / G rows.
+// Rows of a group of attn_rows_kernel: as many as have their G heads in the columns of CB blocks (six heads: five rows in 32 columns,
+// where whole rows per block would be four).
 constexpr int ATTN_ROWS_CB = 2;
-int attention_rows_per_group(int Hq, int Hkv) { return ATTN_ROWS_CB * (16 / (Hq / Hkv)); }
+int attention_rows_per_group(int Hq, int Hkv) { return ATTN_ROWS_CB * 16 / (Hq / Hkv); }
 
 // Most rows of a pass that attend one by one in the decode kernel, which takes the chunks of a row side by side,
 // instead of in groups that walk the whole context (2.2 us per 128 tokens, whatever the number of groups while they all
