@@ -338,6 +338,7 @@ int alloc_device(pl_engine *e) {
     const int64_t slices = std::max(std::max(std::max(e->ks_qkv.splits * wq, e->ks_o.splits * d), e->ks_d.splits * d) * sliced,
                                     pl::gemm_workspace_elems((int)sliced, 2 * c.d_ffn, e->ks_gu));
     int64_t pass = std::max(wq, d) * R;   // of passes of more rows, in one slice or all
+    pass = std::max(pass, pl::gemm_workspace_elems((int)std::min<int64_t>(R, 512), 2 * c.d_ffn, e->ks_gu));
     const std::tuple<int64_t, int64_t, pl::GemmSplit> plain[] = {{wq, d, e->ks_qkv}, {d, qd, e->ks_o}, {d, c.d_ffn, e->ks_d}};
     for (const auto &[N, K, ks] : plain)
       for (int64_t r = SLICED_ROWS + 1; r <= R; r += 64)   // (among the row counts of a row of tiles, the least is most in favour of slices)
@@ -488,7 +489,7 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   const bool fold = prefill && n > std::max(c.max_batch, SLICED_ROWS);   // many rows: the products come as one slice each
   const bool cold = pl::gemm_cold(e->streamed_weight_bytes);   // every product's weights pass by once per step
   auto gemm = [&](const bf16_t *x, const bf16_t *wt, void *y, float *ws, int N, int K, int mode, const pl::GemmSplit &ks) {
-    return fold ? pl::launch_gemm_pass(x, wt, y, n, N, K, mode, ks, cold, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, cold, s);
+    return fold ? pl::launch_gemm_pass(x, wt, y, ws, n, N, K, mode, ks, cold, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, cold, s);
   };
   auto slices = [&](const pl::GemmSplit &ks, int N, int K) { return fold ? pl::gemm_pass_slices(n, N, K, ks) : ks.splits; };
   pl::AttnParams ap{};

@@ -492,6 +492,29 @@ def test_passes_whose_long_product_stays_in_slices_leave_the_cache_of_reading_to
         e.close()
 
 
+@pytest.mark.parametrize("n_prompt", [258, 390, 513, 514])
+def test_passes_with_a_sliced_gate_up_remainder_leave_the_cache_of_reading_token_by_token(n_prompt):
+    """Engines of 129 to 256 slots slice the leftover columns of a wide gate/up product; passes of 257 to 512 rows run the slices behind
+    256 x 256 main tiles, longer ones add them up in a workgroup: bit-identical caches."""
+    m = synth.ModelCfg(2, 1024, 8, 2, 32, 18944, 512)
+    assert pl.pl_debug_gemm_plan(130, 2 * 18944, 1024, 1)[2] > 1
+    eng = [pl.Engine.from_model(m, max_batch=130, max_context=576, kv_pool_tokens=1152, kv_page_tokens=64, seed=3, device=0) for _ in range(2)]
+    blob = eng[0].pack_weights(synth.make_weights(m, seed=11), synth.f32_to_bf16_bits)
+    prompt = synth.random_prompts(np.random.default_rng(n_prompt), 1, n_prompt, m.vocab)[0]
+    for e in eng:
+        e.load_weights(blob)
+        e.add_sequence(5, prompt, 4)
+    assert eng[0].prefill(0) == n_prompt - 1
+    for _ in range(n_prompt - 1):
+        eng[1].decode_step()
+    kv = [[e.debug_read_kv(0, l, n_prompt - 1) for l in range(m.n_layers)] for e in eng]
+    for l in range(m.n_layers):
+        for part in range(2):
+            assert np.array_equal(kv[0][l][part], kv[1][l][part]), (l, part)
+    for e in eng:
+        e.close()
+
+
 @pytest.mark.parametrize("Hq,Hkv,hd,d", [(16, 1, 128, 256), (4, 4, 64, 256), (8, 1, 32, 256), (12, 2, 64, 2560)])
 def test_decode_steps_rotate_and_append_like_the_passes(Hq, Hkv, hd, d):
     """A decode step's attention adds up the QKV slices, rotates and appends by itself, a pass in a kernel of its
