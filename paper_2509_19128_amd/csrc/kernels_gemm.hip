@@ -877,14 +877,20 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
                          false, cold, s);
 }
 
-// us per k-step of a folded product by its four tile shapes: the time of the fullest compute unit, 0.26 / 0.38 / 0.50 / 0.80 per
-// resident 64 x 64 / 128 x 64 / 128 x 128 / 128 x 256 tile (fits of a sweep over twelve shapes at the products of the 1.5B, 7B
-// and 32B shapes, 300 to 1024 rows; the choice is the measured best in 29 of 35, within 6 % in the others).  128 x 128 tiles by four
-// wavefronts side by side, which load no W twice: 7B QKV, 511 rows, 33 us, in two rows of two 38; 32B QKV, 400 rows, 42 and 49.
-static int fold_shape(int M, int N, double *us) {
-  auto cost = [&](int bm, int bn, double t) { return (((M + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256 * t; };
-  const double c[4] = {cost(64, 64, 0.26), cost(128, 64, 0.38), cost(128, 128, 0.50), cost(128, 256, 0.80)};
-  const int best = (int)(std::min_element(c, c + 4) - c);
+// us per k-step of a folded product by its six tile shapes: the time of the fullest compute unit, 0.26 / 0.38 / 0.42 / 0.50 / 0.72 per
+// resident 64 x 64 / 128 x 64 / 96 x 128 / 128 x 128 / 192 x 128 tile (128 x 128 a quarter more where most units hold two, or x is far), 128 x 256 tiles by how
+// many run (fits of sweeps at the products of the 1.5B, 7B and 32B shapes, 300 to 4000 rows).  96 and 192 x 128 only while x stays near the
+// L2s: with 8960-long rows, 2000 of them, a k-step of 96 x 128 tiles takes 0.65.  128-wide tiles by four wavefronts side by side, which load
+// no W twice.  7B QKV, 511 rows, by 128 x 128 tiles 33 us, by 96 x 128 27; 1.5B QKV, 3000 rows, by 128 x 256 33, by 192 x 128 29; 7B QKV, 1400
+// rows, by 128 x 256 tiles 91, by 128 x 128 60.
+static int fold_shape(int M, int N, int K, double *us) {
+  auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  auto cost = [&](int bm, int bn, double t) { return (tiles(bm, bn) + 255) / 256 * t; };
+  const int square = tiles(128, 128), wide = tiles(128, 256);
+  const bool near = (int64_t)M * K <= 5 << 20;
+  const double c[6] = {cost(64, 64, 0.26), cost(128, 64, 0.38), near ? cost(96, 128, 0.42) : 1e9, cost(128, 128, square > 420 || (!near && square > 256) ? 0.625 : 0.50),
+                       near ? cost(192, 128, 0.72) : 1e9, wide <= 256 ? 0.45 + wide * (0.75 / 256) : cost(128, 256, 1.2)};
+  const int best = (int)(std::min_element(c, c + 6) - c);
   if (us) *us = c[best];
   return best;
 }
@@ -935,10 +941,12 @@ int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, 
       default: return launch_cfg<2, 2, 2, 2>(L);
     }
   }
-  switch (fold_shape(M, N, nullptr)) {
+  switch (fold_shape(M, N, K, nullptr)) {
     case 0: return launch_fold_cfg<2, 2, 1, 1>(L);
     case 1: return launch_fold_cfg<2, 2, 2, 1>(L);
-    case 2: return launch_fold_cfg<1, 4, 4, 1>(L);
+    case 2: return launch_fold_cfg<1, 4, 3, 1>(L);
+    case 3: return launch_fold_cfg<1, 4, 4, 1>(L);
+    case 4: return launch_fold_cfg<1, 4, 6, 1>(L);
     default: return launch_fold_cfg<1, 4, 4, 2>(L);
   }
 }
@@ -951,7 +959,7 @@ int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, 
 int gemm_pass_slices(int M, int N, int K, const GemmSplit &ks) {
   if (ks.splits == 1 || K < 8192) return 1;
   double fold;
-  fold_shape(M, N, &fold);
+  fold_shape(M, N, K, &fold);
   const int ksteps = 4 * ((K / (4 * BK) + ks.splits - 1) / ks.splits);
   const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256) * ks.splits;
   const double sliced = 4 + ksteps * big_rounds(tiles) + (ks.splits - 1) * (4e-6 * M * N / 4);
