@@ -422,8 +422,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(const bf16_t *__restrict__ X,
 }
 
 // Many rows (prompt passes): flat grid in XCD-local groups of row tiles as above, all K slices of a tile in
-// one workgroup.  (With 128 x 256 tiles the second set of accumulators spills 66 registers; the shape is still the fastest where
-// launch_gemm_folded takes it: down product of the 32B shape, 1024 rows, 345 us, 480 with the best of the others.)
+// one workgroup.  (128 x 256 tiles: the second set of accumulators leaves no register free and each fold moves 256; still the fastest where
+// launch_gemm_folded takes it: down product of the 32B shape, 1024 rows, 345 us, 480 with the best of 64- and 128-wide tiles.)
 template <int WM, int WN, int AT, int BT, int MODE>
 __global__ __launch_bounds__(256) void gemm_fold_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
                                                         void *__restrict__ Yv, int M, int N, int K, int ksteps,
@@ -658,6 +658,7 @@ int launch_fold_cfg(Launch L) {
 template <int LEFT>
 int launch_rounds(const Launch &L, int n_cut, int rem_splits = 1) {
   const int nrow = (L.M + 255) / 256, ln = LEFT == 0 ? 128 : 64, splits = L.mode == 0 ? L.splits : 1;
+  if (LEFT == 0 && n_cut >= L.N && (L.N + 255) / 256 * splits * nrow <= 256) return launch_cfg<1, 4, 8, 2>(L);   // a tile each
   const int big = ((n_cut + 255) / 256 * splits + 7) / 8 * 8 * nrow, left = ((L.N - n_cut + ln - 1) / ln * splits + 7) / 8 * 8 * nrow;
   const int slices = L.mode == 0 ? L.splits : rem_splits, ksteps = 4 * ((L.K / (4 * BK) + slices - 1) / slices);
   with_cold<1>(L.cold, [&](auto COLD) {
@@ -928,8 +929,8 @@ int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, 
     if (ks.splits > 1) return launch_fold_cfg<2, 2, 2, 2>(L);
     // The shape with the least time: a round of 256 x 256 tiles takes 1.45 us per k-step (1.05 when few of them run), 256 of the
     // 128 x 256 tiles of a wide matrix 1.05 and of 128 x 128 tiles 0.62 whether the last round is full or not (an idle unit's power
-    // goes to the others), a round of leftover 256 x 64 tiles 0.75.  Fits of a sweep over the 1.5B, 7B and 32B shapes at 300 to 1024 rows; us
-    // by 128-row tiles, by 256 x 256 and with leftovers: 1.5B 300 rows 34 / 41 / -, 511 49 / 36 / -, 768 61 / 41 / -, 1024 78 / 75 / 66; 7B 300
+    // goes to the others).  Fits of a sweep over the 1.5B, 7B and 32B shapes at 300 to 1024 rows; us by 128-row tiles, by launches of
+    // 256 x 256 and with leftover 256 x 64 tiles (gemm_rounds_kernel takes 7 % less than the launches, its leftovers are 256 x 128): 1.5B 300 rows 34 / 41 / -, 511 49 / 36 / -, 768 61 / 41 / -, 1024 78 / 75 / 66; 7B 300
     // 100 / 146 / 123, 511 149 / 155 / 136, 768 198 / 176 / 242, 1024 251 / 244 / 265; 32B 300 207 / 232 / 275, 511 279 / 247 / 315, 1024 491 / 468 / 497.
     const int ncol = (N + 255) / 256;
     float big;
