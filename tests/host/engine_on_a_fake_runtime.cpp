@@ -234,6 +234,31 @@ void scarce_memory() {
     device_limit = ~(size_t)0;
   }
 }
+
+// Rows of a pass: a whole prompt of up to 4096, half of that where the buffers do not fit or would take pages from a pool that takes what
+// is left; the metadata of a pass lies as close as its rows allow.
+void pass_rows() {
+  const size_t reserve = (size_t)6 << 30, mib = (size_t)1 << 20;
+  pl_model_cfg c = shape(2, 2, 4096, 8192);
+  device_high = 0;
+  pl_destroy(engine(c));
+  const size_t needed = device_high;
+  for (int what = 0; what < 3; ++what) {   // room; a byte too little; a pool that would be half of what its slots can use
+    c.kv_pool_tokens = what == 2 ? 0 : 8192;
+    device_limit = what == 0 ? needed : what == 1 ? needed - 1 : reserve + needed - 2 * mib;
+    pl_engine *e = engine(c);
+    std::vector<int32_t> prompt(4001, 3);
+    int32_t slot = -1, read = 0;
+    CHECK(pl_add_sequence(e, 1, prompt.data(), 4001, 4, 1.f, &slot) == PL_OK && pl_prefill(e, slot, &read) == PL_OK && read == 4000);
+    pl_stats st{};
+    CHECK(pl_get_stats(e, &st) == PL_OK && st.prefill_passes == (what == 0 ? 1u : 2u) && st.kv_pages_total == 256);
+    const Launch &l = last("step_begin_kernel");
+    const int rows = what == 0 ? 4000 : 4000 - 2048;
+    CHECK(l.begin.src.row_slot - (const int32_t *)l.begin.src.seq_id == 2 * ((rows + 63) / 64 * 64));   // (ids of eight bytes)
+    pl_destroy(e);
+    device_limit = ~(size_t)0;
+  }
+}
 }  // namespace
 
 int main(int, char **argv) {
@@ -242,6 +267,7 @@ int main(int, char **argv) {
   else if (test == "same_route") same_route();
   else if (test == "list_capacity") list_capacity();
   else if (test == "scarce_memory") scarce_memory();
+  else if (test == "pass_rows") pass_rows();
   else return 2;
   CHECK(device_memory.empty() && host_allocations == 0);
   puts("ok");
