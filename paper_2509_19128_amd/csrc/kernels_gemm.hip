@@ -967,15 +967,24 @@ int gemm_pass_slices(int M, int N, int K, const GemmSplit &ks) {
   return sliced < K / BK * fold ? ks.splits : 1;
 }
 
+// fp32 elements of a plain product of a pass of up to R rows.  Slices come and go with the row count (fold_shape steps at the rows of six
+// tile shapes and where x no longer stays near), so every row count is asked, from the most down to the first that keeps them.
+int64_t gemm_pass_elems(int R, int N, int K, const GemmSplit &ks) {
+  int r = R;
+  while (r > 0 && gemm_pass_slices(r, N, K, ks) == 1) --r;
+  return std::max((int64_t)R, (int64_t)r * ks.splits) * N;
+}
+
 // The product of a pass of more than 256 rows in gemm_pass_slices(...) slices.
 // 257 to 512 rows of a wide SwiGLU product with a sliced remainder: two row tiles of 256 x 256 main tiles with the remainder's slices behind
 // them, as steps of 129 to 256 rows run, given a workspace for the slices (gemm_workspace_elems).
 // Where the K of a remainder's tile is added up in a workgroup (launch_gemm_folded), it is one long tile more: 7B shape, four layers, a prompt
 // of 260 / 300 / 385 / 450 / 512 tokens 1408 / 1432 / 1513 / 1560 / 1618 us, so 1372 / 1389 / 1450 / 1523 / 1570.  Non-temporal loads change nothing.
-int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int N, int K, int mode, const GemmSplit &ks, bool cold,
-                     hipStream_t s) {
+int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, float *ws, int64_t room, int M, int N, int K, int mode, const GemmSplit &ks,
+                     bool cold, hipStream_t s) {
   if (ws && mode == 1 && M > 256 && M <= 512 && ks.splits == 1 && ks.rem_splits > 1 && ks.n_main < N) {
     if (K % (4 * BK) || N % 64 || ks.n_main < 0 || ks.n_main % 256 || !splits_valid(K, ks.rem_splits)) return -1;
+    if (gemm_workspace_elems(M, N, ks) > room) return -1;
     if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
     const int rem_ksteps = 4 * ((K / (4 * BK) + ks.rem_splits - 1) / ks.rem_splits);
     const int wgs = std::max((ks.n_main / 256 + 7) / 8 * 8 * 2, (N - ks.n_main + 255) / 256 * 2 * ks.rem_splits);
@@ -984,7 +993,9 @@ int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M
     if (hipGetLastError() != hipSuccess) return -7;
     return swiglu_reduce(ws, ks.rem_splits, M, N - ks.n_main, ks.n_main, (bf16_t *)y, N / 2, s);
   }
-  if (mode != 0 || gemm_pass_slices(M, N, K, ks) == 1) return launch_gemm_folded(x, w, y, M, N, K, mode, ks, cold, s);
+  const int slices = mode == 0 ? gemm_pass_slices(M, N, K, ks) : 1;
+  if (mode == 0 && (int64_t)slices * M * N > room) return -1;
+  if (slices == 1) return launch_gemm_folded(x, w, y, M, N, K, mode, ks, cold, s);
   if (M < 1 || M > GEMM_MAX_ROWS || K % (4 * BK) || N % 32 || !splits_valid(K, ks.splits) || ks.n_main != N) return -1;
   if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
   const Launch L{x, w, y, M, N, K, 0, ks.splits, 0, N, N, 0, true, false, s};

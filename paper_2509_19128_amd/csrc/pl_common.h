@@ -149,8 +149,10 @@ constexpr int GEMM_MAX_ROWS = 4096;
 int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, int K, int mode, const GemmSplit &ks, bool cold,
                        hipStream_t s);
 int gemm_pass_slices(int M, int N, int K, const GemmSplit &ks);
-int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int N, int K, int mode, const GemmSplit &ks, bool cold,
-                     hipStream_t s);
+int64_t gemm_pass_elems(int R, int N, int K, const GemmSplit &ks);
+// room: fp32 elements of what takes partial sums (mode 0: y, mode 1: ws); -1 where the call would need more
+int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, float *ws, int64_t room, int M, int N, int K, int mode, const GemmSplit &ks,
+                     bool cold, hipStream_t s);
 int launch_gemm_cfg(int cfg, const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int N, int K, int mode,
                     int splits, int n_begin, int n_end, bool paired, bool cold, hipStream_t s);
 int gemm_pick_splits(int M, int N, int K);

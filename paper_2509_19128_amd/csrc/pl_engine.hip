@@ -15,7 +15,6 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
-#include <tuple>
 #include <vector>
 
 namespace {
@@ -109,6 +108,7 @@ struct pl_engine {
     int pitch = 0;   // rows from one metadata array to the next: rows_cap, or for a pass its own rows (so that its image is short)
     char *meta_h = nullptr, *meta_d = nullptr;   // per-pass metadata: host (pinned) and device images, same layout
     float *h = nullptr, *parts = nullptr, *cs = nullptr, *attn_po = nullptr, *attn_pml = nullptr;
+    int64_t parts_elems = 0;   // that `parts` holds
     bf16_t *a = nullptr, *q_rot = nullptr, *attn_out = nullptr, *mid = nullptr;
     int32_t *ctx_len = nullptr, *attn_work = nullptr, *attn_tickets = nullptr, *attn_first = nullptr;
     int32_t *pt = nullptr;   // device copy of the page table, written on this set's stream only
@@ -270,7 +270,7 @@ int alloc_work(pl_engine *e, pl_engine::Work &w, int64_t R, int64_t parts_elems,
   if ((rc = dev_alloc(&w.meta_d, w.image_bytes(R)))) return rc;
   if ((rc = dev_alloc(&w.h, R * d))) return rc;
   if ((rc = dev_alloc(&w.a, R * d * wide))) return rc;
-  if ((rc = dev_alloc(&w.parts, parts_elems))) return rc;
+  if ((rc = dev_alloc(&w.parts, w.parts_elems = parts_elems))) return rc;
   if ((rc = dev_alloc(&w.q_rot, R * qd * wide))) return rc;
   if ((rc = dev_alloc(&w.attn_out, R * qd * wide))) return rc;
   if ((rc = dev_alloc(&w.mid, R * c.d_ffn * wide))) return rc;
@@ -331,19 +331,15 @@ int alloc_device(pl_engine *e) {
   e->ks_gu = pl::gemm_pick_split(B, 2 * c.d_ffn, (int)d, 1);
   e->ks_d = pl::gemm_pick_split(B, (int)d, c.d_ffn, 0);
   e->ks_lm = pl::GemmSplit{1, c.vocab, 1};
-  // fp32 partial sums of a work set: K slices for passes of up to SLICED_ROWS rows, one folded slice beyond
+  // fp32 partial sums of a work set: all K slices for calls of up to max(max_batch, SLICED_ROWS) rows, one or all (launch_gemm_pass) beyond
   auto parts_elems = [&](int64_t R) {
     if (e->f32) return R * std::max(wq, 2 * (int64_t)c.d_ffn);   // the fp32 build keeps whole products there
     const int64_t sliced = std::min<int64_t>(R, std::max(B, SLICED_ROWS));
     const int64_t slices = std::max(std::max(std::max(e->ks_qkv.splits * wq, e->ks_o.splits * d), e->ks_d.splits * d) * sliced,
                                     pl::gemm_workspace_elems((int)sliced, 2 * c.d_ffn, e->ks_gu));
-    int64_t pass = std::max(wq, d) * R;   // of passes of more rows, in one slice or all
-    pass = std::max(pass, pl::gemm_workspace_elems((int)std::min<int64_t>(R, 512), 2 * c.d_ffn, e->ks_gu));
-    const std::tuple<int64_t, int64_t, pl::GemmSplit> plain[] = {{wq, d, e->ks_qkv}, {d, qd, e->ks_o}, {d, c.d_ffn, e->ks_d}};
-    for (const auto &[N, K, ks] : plain)
-      for (int64_t r = SLICED_ROWS + 1; r <= R; r += 64)   // (among the row counts of a row of tiles, the least is most in favour of slices)
-        pass = std::max(pass, pl::gemm_pass_slices((int)r, (int)N, (int)K, ks) * N * std::min(r + 63, R));
-    return std::max(slices, pass);
+    return std::max({slices, pl::gemm_workspace_elems((int)std::min<int64_t>(R, 512), 2 * c.d_ffn, e->ks_gu),
+                     pl::gemm_pass_elems((int)R, (int)wq, (int)d, e->ks_qkv), pl::gemm_pass_elems((int)R, (int)d, (int)qd, e->ks_o),
+                     pl::gemm_pass_elems((int)R, (int)d, c.d_ffn, e->ks_d)});
   };
   // the chunk length is fixed by max_batch alone, so a sequence's attention result never depends on
   // how many rows a pass holds
@@ -486,10 +482,10 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   const bf16_t *gf = base + e->layout[e->layout.size() - 2].offset;
   const bf16_t *lm = base + e->layout.back().offset;
   int rc = 0;
-  const bool fold = prefill && n > std::max(c.max_batch, SLICED_ROWS);   // many rows: the products come as one slice each
+  const bool fold = prefill && n > std::max(c.max_batch, SLICED_ROWS);   // many rows: a product comes in one slice or in all
   const bool cold = pl::gemm_cold(e->streamed_weight_bytes);   // every product's weights pass by once per step
   auto gemm = [&](const bf16_t *x, const bf16_t *wt, void *y, float *ws, int N, int K, int mode, const pl::GemmSplit &ks) {
-    return fold ? pl::launch_gemm_pass(x, wt, y, ws, n, N, K, mode, ks, cold, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, cold, s);
+    return fold ? pl::launch_gemm_pass(x, wt, y, ws, w.parts_elems, n, N, K, mode, ks, cold, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, cold, s);
   };
   auto slices = [&](const pl::GemmSplit &ks, int N, int K) { return fold ? pl::gemm_pass_slices(n, N, K, ks) : ks.splits; };
   pl::AttnParams ap{};

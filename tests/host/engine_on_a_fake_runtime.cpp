@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <sys/mman.h>
 
 #include <map>
 #include <string>
@@ -34,9 +35,51 @@ std::map<const void *, std::string> names;
 std::map<void *, size_t> device_memory;
 size_t device_used = 0, device_high = 0, device_limit = ~(size_t)0;
 int host_allocations = 0, fail_event_record = 0;   // fail_event_record: the how-manieth hipEventRecord from now fails
-bool capturing = false;
+bool capturing = false, copying = true;   // copying: copies and fills happen
 std::vector<Launch> done, captured;
 dim3 call_grid, call_block;
+int products = 0;   // launches whose buffers were looked at
+
+// The buffers of a product and of the kernels that take its slices lie in one allocation each.
+void buffers_fit(const std::string &kernel, void **args) {
+  auto number = [&](int i) { return (int64_t) * (const int *)args[i]; };
+  auto fits = [&](int i, int64_t bytes) {
+    const char *p = *(const char *const *)args[i];
+    auto in = device_memory.upper_bound((void *)p);
+    CHECK(in != device_memory.begin());
+    --in;
+    const int64_t room = (const char *)in->first + in->second - p;
+    if (bytes <= room) return;
+    fprintf(stderr, "%s: %lld bytes into %lld\n", kernel.c_str(), (long long)bytes, (long long)room);
+    CHECK(!"a buffer holds what a kernel reads or writes");
+  };
+  std::vector<int> t;   // numbers among the template's arguments
+  const size_t at = kernel.find("_kernelI");
+  for (size_t i = at; at != std::string::npos && kernel[i] && kernel.compare(i, 2, "EE"); ++i)
+    if (kernel[i] == 'L') t.push_back(atoi(kernel.c_str() + i + 2));
+  auto is = [&](const char *name) { return kernel.find(name) != std::string::npos; };
+  if (is("gemm_gu_")) {   // x, w, mid, slices, M, N, K, n_main, ...
+    const int64_t M = number(4), N = number(5), K = number(6), rem = N - number(7), slices = number(is("joint") ? 9 : 8);
+    fits(0, 2 * M * K); fits(1, 2 * N * K); fits(2, M * N); fits(3, 4 * slices * M * rem);
+  } else if (is("gemm_")) {   // x, w, y, M, N, K, ksteps, ...
+    const int64_t M = number(3), N = number(4), K = number(5), per = number(6) * 64;
+    const bool fold = is("fold"), plain = is("gemm_kernel");
+    const int64_t slices = fold ? 1 : (K + per - 1) / per, ld = plain ? number(10) : N;
+    fits(0, 2 * M * K); fits(1, 2 * N * K);
+    fits(2, t[is("rounds") ? 0 : 4] == 1 ? M * N : 4 * slices * M * ld);
+  } else if (is("swiglu_reduce")) {
+    fits(0, 4 * number(1) * number(2) * number(3));
+  } else if (is("resid_rmsnorm")) {
+    const int64_t row = number(5) * number(6);
+    fits(0, 4 * row); fits(1, 4 * number(2) * row); fits(4, 2 * row);
+  } else if (is("rope_append")) {
+    const int64_t n = number(8), hd = number(11);
+    fits(0, 4 * number(1) * n * (number(9) + 2 * number(10)) * hd); fits(6, 2 * n * number(9) * hd);
+  } else {
+    return;
+  }
+  ++products;
+}
 
 void run(const Launch &l) {
   done.push_back(l);
@@ -57,6 +100,7 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *shared, hi
 }
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, hipStream_t) {
   Launch l{names[f], grid, {}, {}, 0};
+  buffers_fit(l.kernel, args);
   if (l.kernel.find("step_begin_kernel") != std::string::npos) {
     l.begin = *(const pl::StepBegin *)args[0];
     l.attn = *(const pl::AttnParams *)args[1];
@@ -70,8 +114,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, 
 hipError_t hipMalloc(void **p, size_t n) {
   *p = nullptr;
   if (device_used + n > device_limit) return hipErrorOutOfMemory;
-  *p = aligned_alloc(256, (n + 255) / 256 * 256);   // as device allocations are at least
-  memset(*p, 0, n);
+  *p = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);   // pages that nothing touches take no memory
   device_memory[*p] = n;
   device_used += n;
   if (device_used > device_high) device_high = device_used;
@@ -81,16 +124,16 @@ hipError_t hipFree(void *p) {
   if (!p) return hipSuccess;
   CHECK(device_memory.count(p));
   device_used -= device_memory[p];
+  munmap(p, device_memory[p]);
   device_memory.erase(p);
-  free(p);
   return hipSuccess;
 }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = calloc(1, n); ++host_allocations; return hipSuccess; }
 hipError_t hipHostFree(void *p) { free(p); --host_allocations; return hipSuccess; }
 hipError_t hipMemGetInfo(size_t *f, size_t *t) { *f = device_limit - device_used; *t = device_limit; return hipSuccess; }
-hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
-hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { CHECK(!capturing); memcpy(d, s, n); return hipSuccess; }
-hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { CHECK(!capturing); memset(d, v, n); return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { if (copying) memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { CHECK(!capturing); if (copying) memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { CHECK(!capturing); if (copying) memset(d, v, n); return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -259,6 +302,51 @@ void pass_rows() {
     device_limit = ~(size_t)0;
   }
 }
+
+// Every launch of a pass, whatever its row count, finds its operands and its slices in the buffers (the runtime above looks): shapes whose
+// long product comes in slices from a row count on that is no multiple of a tile's rows, for engines of few and many slots, and the
+// shapes of common decoders; with room, and with the rows that are left where memory is tight.
+void pass_buffers() {
+  struct { int d, q, kv, f, batch, context; } shapes[] = {{3584, 28, 4, 9728, 96, 1024}, {3584, 28, 4, 9728, 128, 1024}, {3584, 28, 4, 9728, 1, 640},
+    {3328, 26, 2, 8448, 1, 640}, {1536, 12, 2, 8960, 64, 4224}, {3584, 28, 4, 18944, 256, 2100}, {5120, 40, 8, 27648, 128, 1300}, {1024, 8, 2, 8192, 130, 700},
+    {2048, 16, 8, 10240, 16, 1500}, {4096, 32, 8, 14336, 200, 1100}, {8192, 64, 8, 28672, 512, 900}};
+  for (const auto &m : shapes)
+    for (int tight = 0; tight < 2; ++tight) {
+      pl_model_cfg c = shape(m.kv, m.batch, m.context, m.context + 31);
+      c.d_model = m.d; c.n_q_heads = m.q; c.head_dim = 128; c.d_ffn = m.f;
+      copying = false;   // (weights of gigabytes)
+      if (tight) device_limit = device_high - 1;
+      device_high = 0;
+      pl_engine *e = nullptr;
+      CHECK(pl_create(&c, &e) == PL_OK);
+      const int64_t bytes = pl_weight_nbytes(e);
+      void *blob = mmap(nullptr, bytes, PROT_READ, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+      CHECK(pl_load_weights(e, blob, bytes) == PL_OK && pl_debug_set_graphs(e, 0) == PL_OK);
+      munmap(blob, bytes);
+      copying = true;
+      std::vector<int32_t> prompt(m.context, 3);
+      for (int rows = 2; rows < m.context; ++rows) {
+        done.clear();
+        int32_t slot = -1, read = 0;
+        CHECK(pl_add_sequence(e, 1, prompt.data(), rows + 1, 1, 1.f, &slot) == PL_OK);
+        CHECK(pl_prefill(e, slot, &read) == PL_OK && read == rows);
+        CHECK(pl_retire_sequence(e, slot) == PL_OK);
+      }
+      pl_destroy(e);
+      device_limit = ~(size_t)0;
+    }
+  CHECK(products > 100000);
+
+  // and a call whose slices do not fit is refused
+  const pl::GemmSplit down = pl::gemm_pick_split(96, 3584, 9728, 0), gu = pl::gemm_pick_split(256, 37888, 3584, 1);
+  CHECK(pl::gemm_pass_slices(557, 3584, 9728, down) == down.splits && down.splits > 1 && gu.rem_splits > 1);
+  float *ws = (float *)&done;   // (not null)
+  done.clear();
+  CHECK(pl::launch_gemm_pass(nullptr, nullptr, ws, nullptr, (int64_t)down.splits * 557 * 3584 - 1, 557, 3584, 9728, 0, down, false, nullptr) == -1);
+  CHECK(pl::launch_gemm_pass(nullptr, nullptr, nullptr, ws, pl::gemm_workspace_elems(300, 37888, gu) - 1, 300, 37888, 3584, 1, gu, false, nullptr) == -1);
+  CHECK(pl::launch_gemm_pass(nullptr, nullptr, ws, nullptr, 2000 * 1536 - 1, 2000, 1536, 1536, 0, pl::GemmSplit{1, 1536, 1}, false, nullptr) == -1);
+  CHECK(done.empty());
+}
 }  // namespace
 
 int main(int, char **argv) {
@@ -268,6 +356,7 @@ int main(int, char **argv) {
   else if (test == "list_capacity") list_capacity();
   else if (test == "scarce_memory") scarce_memory();
   else if (test == "pass_rows") pass_rows();
+  else if (test == "pass_buffers") pass_buffers();
   else return 2;
   CHECK(device_memory.empty() && host_allocations == 0);
   puts("ok");
