@@ -835,9 +835,9 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
   if (mode == 1 && (N % 64 || ks.n_main % 64 || !splits_valid(K, ks.rem_splits))) return -1;
   if (mode == 0 && ks.n_main != N) return -1;
   if (ks.n_main < 0 || ks.n_main > N) return -1;
+  if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
   if (mode == 1 && M <= 256 && ks.n_main < N && ks.rem_splits > 1 && ks.splits == 1 && ws) {
     // main tiles and K slices of the remainder in one launch, then the SwiGLU over the slices
-    if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
     const int rem_ksteps = 4 * ((K / (4 * BK) + ks.rem_splits - 1) / ks.rem_splits);
     if (M > 128) {   // (256 x 256 tiles beside 256 x 256 slices: 82.7 us, 80.0 so)
       const int wgs = std::max((ks.n_main / 256 + 7) / 8 * 8 * 2, (N - ks.n_main + 255) / 256 * 2 * ks.rem_splits);
@@ -867,8 +867,7 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
   // are non-temporal: LM head of the 7B / 32B shape by 128 x 256 tiles, 129 rows 287 / 474 us with ordinary, 318 / 550 with non-temporal
   // loads, 160 rows 295 / 473 and 301 / 502, 192 rows 303 / 457 and 300 / 438.
   if (paired && (M - 1) % gemm_tile_rows(cfg) < gemm_tile_rows(cfg) / 2) cold = false;
-  if (cfg == GEMM_256x256 && n_main == N && (mode == 0 || ks.splits == 1) && (M + 255) / 256 * ((N + 255) / 256) * ks.splits > 256 &&
-      (int64_t)N * K * 2 < GEMM_MAX_OPERAND_BYTES) {
+  if (cfg == GEMM_256x256 && n_main == N && (mode == 0 || ks.splits == 1) && (M + 255) / 256 * ((N + 255) / 256) * ks.splits > 256) {
     float us;
     return launch_rounds<0>(Launch{x, w, y, M, N, K, mode, ks.splits, 0, N, N, 0, true, cold, s}, rounds_cut(M, N, ks.splits, &us));
   }

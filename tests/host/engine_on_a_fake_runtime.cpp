@@ -347,6 +347,25 @@ void pass_buffers() {
   CHECK(pl::launch_gemm_pass(nullptr, nullptr, ws, nullptr, 2000 * 1536 - 1, 2000, 1536, 1536, 0, pl::GemmSplit{1, 1536, 1}, false, nullptr) == -1);
   CHECK(done.empty());
 }
+
+// Operands of 2 GiB are refused whichever kernel the sizes call for: offsets into them have 31 bits.
+void operand_limits() {
+  const int K = 1 << 21;
+  float nothing = 0;
+  for (int rows : {512, 600, 1024, 4096}) {
+    for (int N : {64, 256, 480})
+      for (int splits : {1, 2, 64, 65, 128, 129, 256, 400, 8192})
+        for (int mode : {0, 1}) {
+          done.clear();
+          if (mode == 0 || splits == 1) CHECK(pl_gemm_bf16(&nothing, &nothing, &nothing, rows, N, K, mode, splits, nullptr) == PL_E_INVAL);
+          const pl::GemmSplit ks{splits, N, 1};
+          CHECK(pl::launch_gemm(nullptr, nullptr, nullptr, &nothing, rows, N, K, mode, ks, false, nullptr) == -1);
+          CHECK(pl::launch_gemm_folded(nullptr, nullptr, nullptr, rows, N, K, mode, ks, false, nullptr) == -1);
+          CHECK(pl::launch_gemm_pass(nullptr, nullptr, nullptr, &nothing, (int64_t)1 << 40, rows, N, K, mode, ks, false, nullptr) == -1);
+          CHECK(done.empty());
+        }
+  }
+}
 }  // namespace
 
 int main(int, char **argv) {
@@ -357,6 +376,7 @@ int main(int, char **argv) {
   else if (test == "scarce_memory") scarce_memory();
   else if (test == "pass_rows") pass_rows();
   else if (test == "pass_buffers") pass_buffers();
+  else if (test == "operand_limits") operand_limits();
   else return 2;
   CHECK(device_memory.empty() && host_allocations == 0);
   puts("ok");
