@@ -836,9 +836,10 @@ int pl_create(const pl_model_cfg *cfg, pl_engine **out) {
   set_pool_pages(e, n_pages);
   e->rows_cap = std::max(cfg->max_batch, 256);
   // a whole prompt of the longest, or 1024 rows (a recomputation's pass holds several sequences), and no more than all slots
-  // can hold; the fp32 test build keeps whole products: fewer rows
+  // can hold or a product's x of that many rows may take; the fp32 test build keeps whole products: fewer rows
   const int64_t all = (int64_t)cfg->max_batch * cfg->max_context, longest = std::min<int64_t>(std::max(cfg->max_context, 1024), pl::GEMM_MAX_ROWS);
-  e->pass_rows = e->f32 ? e->rows_cap : (int)std::max<int64_t>(std::min(all, longest), e->rows_cap);
+  const int64_t widest = std::max({cfg->d_model, cfg->n_q_heads * cfg->head_dim, cfg->d_ffn}), held = (pl::GEMM_MAX_OPERAND_BYTES - 1) / (2 * widest);
+  e->pass_rows = e->f32 ? e->rows_cap : (int)std::max<int64_t>(std::min({all, longest, held}), e->rows_cap);
   e->wk[0].rows_cap = e->wk[0].pitch = e->rows_cap;
   e->wk[1].rows_cap = e->wk[1].pitch = e->pass_rows;
   if (e->dry) {

@@ -365,6 +365,23 @@ void operand_limits() {
           CHECK(done.empty());
         }
   }
+  // and an engine whose rows are long enough to come near that reads its prompts in passes of fewer rows
+  for (int f : {262144, 524288, 1048576}) {
+    pl_model_cfg c = shape(2, 2, 4096, 8192);
+    c.d_ffn = f;
+    copying = false;
+    pl_engine *e = nullptr;
+    CHECK(pl_create(&c, &e) == PL_OK);
+    const int64_t bytes = pl_weight_nbytes(e);
+    void *blob = mmap(nullptr, bytes, PROT_READ, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    CHECK(pl_load_weights(e, blob, bytes) == PL_OK);
+    munmap(blob, bytes);
+    copying = true;
+    std::vector<int32_t> prompt(4096, 3);
+    int32_t slot = -1, read = 0;
+    CHECK(pl_add_sequence(e, 1, prompt.data(), 4096, 1, 1.f, &slot) == PL_OK && pl_prefill(e, slot, &read) == PL_OK && read == 4095);
+    pl_destroy(e);
+  }
 }
 }  // namespace
 
