@@ -20,7 +20,7 @@
 #include <type_traits>
 
 #ifndef PL_ATTN_NS
-#define PL_ATTN_NS 2   // register stages of K/V runs per wavefront
+#define PL_ATTN_NS 2   // register stages of K/V runs per wavefront where the kernel does not rotate
 #endif
 #ifndef PL_ATTN_CHUNK
 #define PL_ATTN_CHUNK 8192   // largest number of tokens one workgroup handles
@@ -124,9 +124,9 @@ __device__ inline void merge_chunks(const AttnParams &p, int b, int g, int nchun
 // trip ahead of the first scores: worth it in launches of few workgroups (attention_rotates).  Those launches do better with three
 // workgroups per compute unit of one register stage than with two of two (7B shape, 19 rows: a step 2450 -> 2425 us, others the same; the large
 // launches lose by it: 512 ragged sequences 680 -> 690).
-template <int HD, int STAGES, bool ROTATE>
+template <int HD, int NS, bool ROTATE>
 __global__ __launch_bounds__(256, ROTATE ? 3 : 2) void attn_decode_kernel(AttnParams p) {
-  constexpr int NS = ROTATE ? STAGES / 2 : STAGES;   // (see above)
+  static_assert(NS >= 1 && SUB_RUNS % (4 * NS) == 0, "a sub is whole rounds of the stages");
   constexpr int NJ = HD / 32;   // QK MFMAs per 16-token tile
   constexpr int NV = HD / 16;   // PV MFMAs per 32-token run
   // Work items come from a compact list built on the device for this step: every launched workgroup
@@ -791,7 +791,7 @@ static void launch_attention_hd(const AttnParams &p, hipStream_t s, int part) {
     if (p.q)
       hipLaunchKernelGGL((attn_decode_kernel<HD, PL_ATTN_NS, false>), grid, dim3(256), 0, s, p);
     else
-      hipLaunchKernelGGL((attn_decode_kernel<HD, PL_ATTN_NS, true>), grid, dim3(256), 0, s, p);
+      hipLaunchKernelGGL((attn_decode_kernel<HD, 1, true>), grid, dim3(256), 0, s, p);
   }
   if (part != 1 && p.merge)
     hipLaunchKernelGGL(attn_merge_kernel<HD>, dim3(p.Hq, p.n_seq), dim3(HD), 0, s, p);

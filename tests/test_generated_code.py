@@ -22,7 +22,7 @@ def attention(tmp_path_factory):
 def test_decode_attention_reads_page_ids_by_scalar_loads(attention, hd, rotate):
     """In the loop over a sequence's runs a page id that comes by a vector load waits for all K/V loads in flight: no
     block of the kernel may load one value by vector and hand it to the scalar unit."""
-    body = re.search(r"^(_ZN\S*attn_decode_kernelILi%dELi2ELb%dE\S*):(.*?)\.Lfunc_end" % (hd, rotate), attention, re.S | re.M).group(2)
+    body = re.search(r"^(_ZN\S*attn_decode_kernelILi%dELi%dELb%dE\S*):(.*?)\.Lfunc_end" % (hd, 1 if rotate else 2, rotate), attention, re.S | re.M).group(2)
     assert "mfma" in body
     for block in re.split(r"^\.LBB\S+:", body, flags=re.M):
         loaded = set(re.findall(r"global_load_dword (v\d+),", block))
