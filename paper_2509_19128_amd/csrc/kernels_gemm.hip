@@ -424,15 +424,14 @@ __global__ __launch_bounds__(256) void gemm_kernel(const bf16_t *__restrict__ X,
 // Many rows (prompt passes): flat grid in XCD-local groups of row tiles as above, all K slices of a tile in
 // one workgroup.  (128 x 256 tiles: the second set of accumulators leaves no register free and each fold moves 256; still the fastest where
 // launch_gemm_folded takes it: down product of the 32B shape, 1024 rows, 345 us, 480 with the best of 64- and 128-wide tiles.)
-template <int WM, int WN, int AT, int BT, int MODE>
+template <int WM, int WN, int AT, int BT>
 __global__ __launch_bounds__(256) void gemm_fold_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
-                                                        void *__restrict__ Yv, int M, int N, int K, int ksteps,
-                                                        int n_base, int n_end, int nrow) {
+                                                        void *__restrict__ Yv, int M, int N, int K, int ksteps, int nrow) {
   constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
   __shared__ __attribute__((aligned(1024))) bf16_t xs[Tile<WM, WN, AT, BT, false>::LDS];
   const int rtile = (blockIdx.x >> 3) % nrow, ctile = (blockIdx.x / (8 * nrow)) * 8 + (blockIdx.x & 7);
-  if (n_base + ctile * BN >= n_end) return;   // padding of the flat grid (uniform for the workgroup)
-  gemm_tile<WM, WN, AT, BT, MODE, false, true>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, 0, n_end, N, 0);
+  if (ctile * BN >= N) return;   // padding of the flat grid (uniform for the workgroup)
+  gemm_tile<WM, WN, AT, BT, 0, false, true>(xs, X, W, Yv, M, N, K, ksteps, ctile * BN, rtile * BM, 0, N, N, 0);
 }
 
 // Products of more 256 x 256 tiles than compute units: a workgroup of each takes tiles one after the other and loads the first
@@ -630,26 +629,18 @@ int launch_by_id(int cfg, const Launch &L) {
   }
 }
 
-// Columns [n_begin, n_end) of a product of many rows, K in `splits` slices added up in the workgroup (one slice:
+// A plain product of many rows, K in `splits` slices added up in the workgroup (one slice:
 // the plain kernel, which needs no second set of accumulators).
 template <int WM, int WN, int AT, int BT>
 int launch_fold_cfg(Launch L) {
   constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
-  if (BT == 1 && L.mode == 1) return -1;
-  if (L.n_end <= L.n_begin) return 0;
   const int splits = L.splits;
   L.splits = 1;
   L.paired = true;
   if (splits == 1) return launch_cfg<WM, WN, AT, BT>(L);
-  const int nrow = (L.M + BM - 1) / BM, grid = ((L.n_end - L.n_begin + BN - 1) / BN + 7) / 8 * 8 * nrow;
+  const int nrow = (L.M + BM - 1) / BM, grid = ((L.N + BN - 1) / BN + 7) / 8 * 8 * nrow;
   const int ksteps = 4 * ((L.K / (4 * BK) + splits - 1) / splits);
-  if (L.mode == 1 && (BT != 2 || AT > 2)) return -1;   // (not used: no registers for a second set of accumulators)
-  if (L.mode == 0)
-    hipLaunchKernelGGL((gemm_fold_kernel<WM, WN, AT, BT, 0>), dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps,
-                       L.n_begin, L.n_end, nrow);
-  else if constexpr (BT == 2 && AT <= 2)
-    hipLaunchKernelGGL((gemm_fold_kernel<WM, WN, AT, BT, 1>), dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps,
-                       L.n_begin, L.n_end, nrow);
+  hipLaunchKernelGGL((gemm_fold_kernel<WM, WN, AT, BT>), dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps, nrow);
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }
 
@@ -661,11 +652,11 @@ int launch_rounds(const Launch &L, int n_cut, int rem_splits = 1) {
   if (LEFT == 0 && n_cut >= L.N && (L.N + 255) / 256 * splits * nrow <= 256) return launch_cfg<1, 4, 8, 2>(L);   // a tile each
   const int big = ((n_cut + 255) / 256 * splits + 7) / 8 * 8 * nrow, left = ((L.N - n_cut + ln - 1) / ln * splits + 7) / 8 * 8 * nrow;
   const int slices = L.mode == 0 ? L.splits : rem_splits, ksteps = 4 * ((L.K / (4 * BK) + slices - 1) / slices);
-  with_cold<1>(L.cold, [&](auto COLD) {
+  with_cold<1>(L.cold && LEFT == 0, [&](auto COLD) {
     auto launch = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(256), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps, n_cut, big, n_cut < L.N ? left : 0);
     };
-    constexpr bool cold = decltype(COLD)::value;
+    constexpr bool cold = LEFT == 0 && decltype(COLD)::value;
     if (L.mode == 1) launch(gemm_rounds_kernel<1, cold, LEFT>);
     else if constexpr (LEFT == 0) launch(gemm_rounds_kernel<0, cold, 0>);
   });
@@ -861,20 +852,18 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
     if (hipGetLastError() != hipSuccess) return -7;
     return swiglu_reduce(ws, ks.rem_splits, M, N - ks.n_main, ks.n_main, (bf16_t *)y, N / 2, s);
   }
-  const int cfg = pick_shape(M, ks.n_main, K, mode, ks.splits, cold), n_main = ks.n_main;
+  if (ks.n_main != N) return -1;
+  const int cfg = pick_shape(M, N, K, mode, ks.splits, cold);
   const bool paired = M > gemm_tile_rows(cfg);
   // A second row tile of a few rows runs through its W ahead of the first one's loads, which then find nothing in L2 if they
   // are non-temporal: LM head of the 7B / 32B shape by 128 x 256 tiles, 129 rows 287 / 474 us with ordinary, 318 / 550 with non-temporal
   // loads, 160 rows 295 / 473 and 301 / 502, 192 rows 303 / 457 and 300 / 438.
   if (paired && (M - 1) % gemm_tile_rows(cfg) < gemm_tile_rows(cfg) / 2) cold = false;
-  if (cfg == GEMM_256x256 && n_main == N && (mode == 0 || ks.splits == 1) && (M + 255) / 256 * ((N + 255) / 256) * ks.splits > 256) {
+  if (cfg == GEMM_256x256 && (mode == 0 || ks.splits == 1) && (M + 255) / 256 * ((N + 255) / 256) * ks.splits > 256) {
     float us;
     return launch_rounds<0>(Launch{x, w, y, M, N, K, mode, ks.splits, 0, N, N, 0, true, cold, s}, rounds_cut(M, N, ks.splits, &us));
   }
-  int rc = launch_gemm_cfg(cfg, x, w, y, ws, M, N, K, mode, ks.splits, 0, n_main, paired && (mode == 0 || ks.splits == 1), cold, s);
-  if (rc || n_main == N) return rc;
-  return launch_gemm_cfg(GEMM_64x128, x, w, y, ws, M, N, K, mode, mode == 1 ? ks.rem_splits : ks.splits, n_main, N,
-                         false, cold, s);
+  return launch_gemm_cfg(cfg, x, w, y, ws, M, N, K, mode, ks.splits, 0, N, paired && (mode == 0 || ks.splits == 1), cold, s);
 }
 
 // us per k-step of a folded product by its six tile shapes: the time of the fullest compute unit, 0.26 / 0.38 / 0.42 / 0.50 / 0.72 per
@@ -915,17 +904,11 @@ int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, 
   // 185 / 356, 769 rows 258 / 492 and 252 / 451; plain products (32B down, 769 rows) 372 and 348.
   cold = cold && mode == 1 && M <= 512 && (M - 1) % 128 >= 96;
   Launch L{x, w, y, M, N, K, mode, ks.splits, 0, ks.n_main, N, 0, true, cold, s};
-  if (mode == 1 && ks.n_main < N) {
-    // 7B shape, main columns and remainder: 128 x 256 tiles and a launch for the remainder 135 us with 511 rows, 195 with 700, 272 with
-    // 1024; 256 x 256 tiles with the remainder in their launch 137, 183, 265.  (Splits of the main columns do not occur.)
-    if (ks.splits == 1 && M > 512) return launch_rounds<2>(L, ks.n_main, ks.rem_splits);
-    const int rc = ks.splits == 1 && ks.n_main >= 128 * 256 ? launch_fold_cfg<1, 4, 4, 2>(L) : launch_fold_cfg<2, 2, 2, 2>(L);
-    if (rc) return rc;
-    L.n_begin = ks.n_main; L.n_end = N; L.splits = ks.rem_splits;
-    return launch_fold_cfg<2, 2, 2, 2>(L);
-  }
   if (mode == 1) {
-    if (ks.splits > 1) return launch_fold_cfg<2, 2, 2, 2>(L);
+    if (ks.splits > 1) return -1;   // (gemm_pick_split leaves the main columns whole)
+    // 7B shape, main columns and remainder: 128 x 256 tiles and a launch for the remainder 195 us with 700 rows, 272 with 1024; 256 x 256
+    // tiles with the remainder in their launch 183 and 265.
+    if (ks.n_main < N) return launch_rounds<2>(L, ks.n_main, ks.rem_splits);
     // The shape with the least time: a round of 256 x 256 tiles takes 1.45 us per k-step (1.05 when few of them run), 256 of the
     // 128 x 256 tiles of a wide matrix 1.05 and of 128 x 128 tiles 0.62 whether the last round is full or not (an idle unit's power
     // goes to the others).  Fits of a sweep over the 1.5B, 7B and 32B shapes at 300 to 1024 rows; us by 128-row tiles, by launches of

@@ -66,7 +66,7 @@ void buffers_fit(const std::string &kernel, void **args) {
     const bool fold = is("fold"), plain = is("gemm_kernel");
     const int64_t slices = fold ? 1 : (K + per - 1) / per, ld = plain ? number(10) : N;
     fits(0, 2 * M * K); fits(1, 2 * N * K);
-    fits(2, t[is("rounds") ? 0 : 4] == 1 ? M * N : 4 * slices * M * ld);
+    fits(2, !fold && t[is("rounds") ? 0 : 4] == 1 ? M * N : 4 * slices * M * ld);
   } else if (is("swiglu_reduce")) {
     fits(0, 4 * number(1) * number(2) * number(3));
   } else if (is("resid_rmsnorm")) {
