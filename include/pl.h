@@ -275,11 +275,12 @@ int pl_debug_kv_pool(pl_engine *e, void **device_ptr, int64_t *nbytes);
 
 /* One launch of one tile configuration of the GEMM kernel over output columns [n_begin, n_end) (tuning
  * and tests).  cfg: 0 32x256, 1 64x256, 2 128x256, 3 64x128, 4 128x128, 5 256x128, 6 64x64, 7 128x64,
- * 8 32x128 (rows x columns of a workgroup's tile; 6-8 mode 0 only), 9 128x64 and 10 256x64 with the
- * wavefronts stacked along the rows.  mode and splits as in pl_gemm_bf16, except that mode 1 accepts
+ * 8 32x128 (rows x columns of a workgroup's tile; 6 and 7 in mode 1 only with splits > 1), 9 128x64 and 10 256x64 with
+ * the wavefronts stacked along the rows, 11 64x128, 12 128x128 and 13 256x128 with the wavefronts side by side along the
+ * columns, 14 256x256.  mode and splits as in pl_gemm_bf16, except that mode 1 accepts
  * splits > 1: the partial sums then go to ws (device fp32 [splits, M, n_end - n_begin]) and a second
- * kernel applies the SwiGLU to their sum.  paired != 0 (splits = 1 only) lays the grid out so that the
- * row tiles of one column tile run on the same XCD at the same time.  mode | PL_GEMM_COLD (here and in the two
+ * kernel applies the SwiGLU to their sum.  paired != 0 (mode 1: splits = 1 only) lays the grid out so that
+ * the row tiles of one column tile and slice run on the same XCD at the same time.  mode | PL_GEMM_COLD (here and in the two
  * launches below) takes the kernels that an engine takes whose weights together do not stay in the last-level cache
  * between two steps, whatever the size of this matrix; the results are the same bits.  PL_E_INVAL (nothing launched)
  * for shapes the configuration does not cover. */
@@ -299,7 +300,7 @@ int pl_debug_gemm_plan(int32_t M_max, int32_t N, int32_t K, int32_t mode, int32_
 int pl_debug_gemm_planned(const void *x, const void *w, void *y, void *ws, int32_t M_max, int32_t M, int32_t N, int32_t K,
                           int32_t mode, void *stream);
 
-/* The product of up to 1024 rows as the prompt passes of such an engine launch it when they hold more than
+/* The product of up to 4096 rows as the prompt passes of such an engine launch it when they hold more than
  * 256 rows: the K slices of an output element are added up, in slice order, by the workgroup that owns it.
  * y is one slice (mode 0: device fp32 [M, N]; mode 1: device bf16 [M, N / 2]), bit-identical to adding
  * pl_debug_gemm_planned's slices in order (mode 1: to its result).  PL_E_INVAL (nothing launched) for

@@ -128,8 +128,7 @@ constexpr int64_t GEMM_MAX_OPERAND_BYTES = (int64_t)1 << 31;
 // tile configurations of the GEMM kernel: rows x columns of a workgroup's tile ("P": the four wavefronts
 // stacked along the rows, each holding a gate and an up tile; "R": side by side along the columns)
 enum { GEMM_32x256, GEMM_64x256, GEMM_128x256, GEMM_64x128, GEMM_128x128, GEMM_256x128, GEMM_64x64, GEMM_128x64,
-       GEMM_32x128, GEMM_128x64P, GEMM_256x64P, GEMM_N_CFGS, GEMM_64x128R, GEMM_128x128R,
-       GEMM_256x128R, GEMM_256x256 };
+       GEMM_32x128, GEMM_128x64P, GEMM_256x64P, GEMM_64x128R, GEMM_128x128R, GEMM_256x128R, GEMM_256x256 };
 // How K is split: columns [0, n_main) in `splits` slices, columns [n_main, N) in `rem_splits` (mode 1
 // only; mode 0 has n_main = N).  Chosen once per product from the largest row count (gemm_pick_split),
 // so that every call adds up an output element in the same order whatever its row count.

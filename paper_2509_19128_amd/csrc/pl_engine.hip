@@ -1573,8 +1573,6 @@ int pl_debug_gemm_cfg(int32_t cfg, const void *x, const void *w, void *y, void *
                       int32_t mode, int32_t splits, int32_t n_begin, int32_t n_end, int32_t paired, void *stream) {
   if (!x || !w || !y) return fail(PL_E_INVAL, "NULL argument");
   const bool cold = debug_gemm_cold(&mode, N, K);
-  if (cfg >= pl::GEMM_N_CFGS || (cfg == pl::GEMM_32x128 && mode == 1 && splits == 1) || (paired && splits != 1))
-    return fail(PL_E_INVAL, "unsupported GEMM launch cfg=%d mode=%d splits=%d", cfg, mode, splits);
   int rc = pl::launch_gemm_cfg(cfg, (const bf16_t *)x, (const bf16_t *)w, y, (float *)ws, M, N, K, mode, splits, n_begin,
                                n_end, paired != 0, cold, (hipStream_t)stream);
   if (rc == -1) return fail(PL_E_INVAL, "unsupported GEMM launch cfg=%d M=%d N=%d K=%d mode=%d splits=%d [%d, %d)", cfg, M, N, K, mode, splits, n_begin, n_end);
@@ -1611,7 +1609,7 @@ int pl_debug_gemm_folded(const void *x, const void *w, void *y, int32_t M_max, i
                          void *stream) {
   if (!x || !w || !y) return fail(PL_E_INVAL, "NULL argument");
   const bool cold = debug_gemm_cold(&mode, N, K);
-  if (M_max < 1 || M_max > 512 || M < 1 || M > 1024 || N < 32 || K < 256 || (mode != 0 && mode != 1))
+  if (M_max < 1 || M_max > 512 || M < 1 || M > pl::GEMM_MAX_ROWS || N < 32 || K < 256 || (mode != 0 && mode != 1))
     return fail(PL_E_INVAL, "unsupported GEMM shape");
   int rc = pl::launch_gemm_folded((const bf16_t *)x, (const bf16_t *)w, y, M, N, K, mode, pl::gemm_pick_split(M_max, N, K, mode), cold,
                                   (hipStream_t)stream);

@@ -258,7 +258,7 @@ def test_swiglu_of_every_row_count_gives_the_same_rows(F, K):
 
 
 CFG_TILES = {0: (32, 256), 1: (64, 256), 2: (128, 256), 3: (64, 128), 4: (128, 128), 5: (256, 128), 6: (64, 64),
-             7: (128, 64), 8: (32, 128), 9: (128, 64), 10: (256, 64)}
+             7: (128, 64), 8: (32, 128), 9: (128, 64), 10: (256, 64), 11: (64, 128), 12: (128, 128), 13: (256, 128), 14: (256, 256)}
 
 
 @pytest.mark.parametrize("cfg", sorted(CFG_TILES))
@@ -273,7 +273,7 @@ def test_every_gemm_tile_configuration_against_fp64(cfg):
     w = synth.bf16_round(rng.standard_normal((N, K), dtype=np.float32) * 0.05)
     xd, wd = dev_bf16(x), dev_bf16(pl.operand_order(w))
     ref = x.astype(np.float64) @ w.astype(np.float64).T
-    for splits, nb, ne, paired in [(1, 0, N, False), (3, 128, N - 64, False), (1, 64, N, True)]:
+    for splits, nb, ne, paired in [(1, 0, N, False), (3, 128, N - 64, False), (1, 64, N, True), (3, 64, N - 32, True)]:
         y = torch.full((splits, M, N), float("nan"), device="cuda", dtype=torch.float32)
         pl.pl_debug_gemm_cfg(cfg, xd.data_ptr(), wd.data_ptr(), y.data_ptr(), 0, M, N, K, 0, splits, nb, ne, paired, 0)
         torch.cuda.synchronize()
@@ -281,7 +281,7 @@ def test_every_gemm_tile_configuration_against_fp64(cfg):
         assert np.isnan(got[:, :, :nb]).all() and np.isnan(got[:, :, ne:]).all()       # nothing outside the range
         tol = 1e-4 * (np.sqrt(K) * 0.05 + np.abs(ref[:, nb:ne]))
         assert (np.abs(got[:, :, nb:ne].astype(np.float64).sum(0) - ref[:, nb:ne]) <= tol).all(), (splits, nb, ne)
-    if cfg in (6, 7, 8):                              # one 32-column tile per wavefront: no gate/up pair
+    if cfg in (6, 7):                                 # wavefronts of one column tile in two rows: no gate/up pair
         with pytest.raises(pl.PlError):
             pl.pl_debug_gemm_cfg(cfg, xd.data_ptr(), wd.data_ptr(), xd.data_ptr(), 0, M, N, K, 1, 1, 0, N, False, 0)
         return
@@ -289,7 +289,9 @@ def test_every_gemm_tile_configuration_against_fp64(cfg):
     gate = ref.reshape(M, N // 64, 2, 32)[:, :, 0].reshape(M, F)
     up = ref.reshape(M, N // 64, 2, 32)[:, :, 1].reshape(M, F)
     want = gate / (1.0 + np.exp(-gate)) * up
-    for splits, nb, ne in [(1, 0, N), (3, 0, N), (2, 128, N - 64)]:
+    with pytest.raises(pl.PlError):
+        pl.pl_debug_gemm_cfg(cfg, xd.data_ptr(), wd.data_ptr(), xd.data_ptr(), wd.data_ptr(), M, N, K, 1, 2, 0, N, True, 0)
+    for splits, nb, ne in [(1, 0, N), (3, 0, N), (2, 128, N - 64), (1, 64, N - 64)]:
         mid = torch.full((M, F), float("nan"), device="cuda", dtype=torch.bfloat16)
         ws = torch.empty(splits * M * (ne - nb), device="cuda", dtype=torch.float32)
         pl.pl_debug_gemm_cfg(cfg, xd.data_ptr(), wd.data_ptr(), mid.data_ptr(), ws.data_ptr(), M, N, K, 1, splits, nb, ne, False, 0)
@@ -371,12 +373,13 @@ def test_products_of_many_rows_equal_the_slices_of_few_added_in_order(M_max, N, 
     the choice of a tile shape ends.  (Row counts and shapes between them reach every tile shape of the choice.)"""
     splits, n_main, _, ws_elems = pl.pl_debug_gemm_plan(M_max, N, K, mode)
     g = torch.Generator(device="cuda").manual_seed(N + K)
-    x = torch.empty(1024, K, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
+    rows_most = 4096
+    x = torch.empty(rows_most, K, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
     w = torch.empty(N * K, device="cuda", dtype=torch.bfloat16).normal_(0, 0.05, generator=g)
-    want = torch.empty(1024, N if mode == 0 else N // 2, device="cuda", dtype=torch.float32)
+    want = torch.empty(rows_most, N if mode == 0 else N // 2, device="cuda", dtype=torch.float32)
     ws = torch.empty(max(ws_elems, 1), device="cuda", dtype=torch.float32)
-    for r in range(0, 1024, M_max):
-        rows = min(M_max, 1024 - r)
+    for r in range(0, rows_most, M_max):
+        rows = min(M_max, rows_most - r)
         y = torch.empty(splits, rows, N, device="cuda") if mode == 0 else torch.empty(rows, N // 2, device="cuda", dtype=torch.bfloat16)
         pl.pl_debug_gemm_planned(x[r:].data_ptr(), w.data_ptr(), y.data_ptr(), ws.data_ptr(), M_max, rows, N, K, mode, 0)
         if mode == 0:
@@ -386,13 +389,13 @@ def test_products_of_many_rows_equal_the_slices_of_few_added_in_order(M_max, N, 
         else:
             want[r:r + rows] = y.float()
         torch.cuda.synchronize()
-    for M in (257, 300, 384, 511, 512, 513, 1023, 1024):
+    for M in (257, 300, 384, 511, 512, 513, 1023, 1024, 1025, 1537, 2000, 3001, 4095, 4096):
         y = torch.full((M + 1, want.shape[1]), float("nan"), device="cuda", dtype=torch.float32 if mode == 0 else torch.bfloat16)
         pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), M_max, M, N, K, mode, 0)
         torch.cuda.synchronize()
         assert torch.equal(y[:M].float(), want[:M]), M
         assert bool(y[M].isnan().all()), M             # nothing written beyond the rows
-    for bad in [(1025, N, K), (0, N, K), (300, N, K + 64), (300, N + 16, K)]:
+    for bad in [(rows_most + 1, N, K), (0, N, K), (300, N, K + 64), (300, N + 16, K)]:
         with pytest.raises(pl.PlError):
             pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), M_max, *bad, mode, 0)
 
@@ -407,9 +410,9 @@ def test_every_gemm_tile_configuration_for_cold_weights_gives_the_same_bits(cfg)
     x = torch.empty(M, K, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
     w = torch.empty(N * K, device="cuda", dtype=torch.bfloat16).normal_(0, 0.05, generator=g)
     ws = torch.empty(3 * M * N, device="cuda", dtype=torch.float32)
-    for mode, splits, nb, ne, paired in [(0, 1, 0, N, False), (0, 3, 128, N - 64, False), (0, 1, 64, N, True), (1, 1, 0, N, False),
+    for mode, splits, nb, ne, paired in [(0, 1, 0, N, False), (0, 3, 128, N - 64, False), (0, 1, 64, N, True), (0, 3, 64, N - 32, True), (1, 1, 0, N, False),
                                          (1, 3, 0, N, False), (1, 2, 128, N - 64, False)]:
-        if mode == 1 and cfg in (6, 7, 8):
+        if mode == 1 and cfg in (6, 7):
             continue
         got = []
         for cold in (0, pl.PL_GEMM_COLD):
