@@ -536,7 +536,7 @@ def test_sampler_tokens_bit_exact_and_logprobs_close(n, V):
         assert abs(lp[r] - lp_ref) <= 1e-4 * max(1.0, abs(lp_ref))
 
 
-@pytest.mark.parametrize("n,V", [(1, 4), (2, 8188), (2, 8192), (3, 8196), (26, 152064), (27, 152064), (512, 4096)])
+@pytest.mark.parametrize("n,V", [(1, 4), (2, 8188), (2, 8192), (3, 8196), (26, 152064), (27, 152064), (512, 4096), (513, 4096)])
 def test_sampler_at_slice_and_launch_boundaries_with_masked_entries(n, V):
     """One slice and a little more or less, both sides of the choice of threads per slice (512 workgroups), and rows
     with masked entries: -inf, the lowest float, a whole masked slice, equal logits."""
@@ -588,7 +588,7 @@ def test_sampler_where_bounds_say_little_or_nothing(n, V):
             assert abs(lp[r] - lp_ref) <= 1e-4 * max(1.0, abs(lp_ref))
 
 
-@pytest.mark.parametrize("few,many,V", [(26, 27, 152064), (511, 512, 4096), (127, 128, 32000), (3, 300, 8200)])
+@pytest.mark.parametrize("few,many,V", [(26, 27, 152064), (512, 513, 4096), (128, 129, 32000), (3, 300, 8200)])
 def test_a_row_is_sampled_alike_whatever_rows_share_the_call(few, many, V):
     """Both sides of the choice of threads per slice: the same rows' tokens and log-probs are bit-identical."""
     rng = np.random.default_rng(V + few)
