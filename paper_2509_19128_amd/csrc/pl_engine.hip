@@ -303,7 +303,14 @@ void free_work(pl_engine::Work &w) {
 
 // Passes of more rows than this may add up a product's K slices inside the GEMM (launch_gemm_pass).
 constexpr int SLICED_ROWS = 256;
-constexpr int PASS_RING = 8;   // host metadata images of cache-only passes that may wait on the device at once
+// Most rows of a pass that reads a prompt beside decode steps.  The tiles of more rows fill the compute units for long, and a step
+// waits for each of its kernels' turns.  A step's 99th percentile, and the time until the prompt is read, beside 3000 tokens in passes of
+// 4096 / 1024 / 896 / 768 / 640 / 512 rows: 1.5B shape, 60 sequences (2.3 ms alone) 7.6 / 4.6 / 4.4 / 4.0 / 3.8 / 3.3 and 17 / 24 / 29 / 26 / 30 /
+// 34 ms; 7B shape, 200 sequences (12 alone) 35 / 25 / 22 / 22 / 20 / 20 and 79 / 98 / 112 / 98 / 125 / 128.  768 is where steps are as fast as
+// beside 1024 rows of plain 128-row tiles (4.2 and 21.5, 29 and 124).
+constexpr int BACKGROUND_ROWS = 768;
+// Host metadata images of cache-only passes that may wait on the device at once: background reading of 18432 tokens returns at once.
+constexpr int PASS_RING = 24;
 
 int alloc_device(pl_engine *e) {
   const pl_model_cfg &c = e->cfg;
@@ -702,13 +709,12 @@ int drain_passes(pl_engine *e) {
 }
 
 // Cache-only passes: rows (slot, position, token) go through the decode kernels in prefill mode, in
-// groups of up to pass_rows, on the second work set's stream; the rows of one slot must come in position
+// groups of up to rows_max (no more than pass_rows), on the second work set's stream; the rows of one slot must come in position
 // order, because a row attends to the keys and values that earlier rows of its slot (in this or an
 // earlier group) leave.  Returns once everything is enqueued; the caller waits (or records an event).
 int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::vector<int32_t> &positions,
-                  const std::vector<int32_t> &tokens, double *ms_total, uint64_t *passes) {
+                  const std::vector<int32_t> &tokens, int rows_max, double *ms_total, uint64_t *passes) {
   const pl_model_cfg &c = e->cfg;
-  const int rows_max = e->pass_rows;
   pl_engine::Work &w = e->wk[1];
   if (!e->dry) HIP_TRY(hipSetDevice(c.device));
   const size_t total = slots.size();
@@ -790,7 +796,7 @@ int recompute_all_kv(pl_engine *e) {
       tokens.push_back(q.hist[p]);
     }
   }
-  rc = run_kv_passes(e, slots, positions, tokens, &e->st.recompute_ms, &e->st.recompute_passes);
+  rc = run_kv_passes(e, slots, positions, tokens, e->pass_rows, &e->st.recompute_ms, &e->st.recompute_passes);
   if (rc) return rc;
   if ((rc = drain_passes(e))) return rc;
   e->st.recompute_positions += slots.size();
@@ -1315,7 +1321,7 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
 
 // Enqueue the reading of a slot's prompt (all positions not read yet, except the last) on the
 // cache-only stream; the slot is marked as reading and its event recorded.
-static int start_prefill(pl_engine *e, int32_t slot, int32_t *out_positions) {
+static int start_prefill(pl_engine *e, int32_t slot, int rows_max, int32_t *out_positions) {
   if (out_positions) *out_positions = 0;
   if (!e->loaded) return fail(PL_E_STATE, "no weights loaded");
   const pl_model_cfg &c = e->cfg;
@@ -1328,7 +1334,7 @@ static int start_prefill(pl_engine *e, int32_t slot, int32_t *out_positions) {
   if ((int64_t)q.pages.size() * e->page_tokens < last) return fail(PL_E_STATE, "slot %d has no pages for its prompt", slot);
   std::vector<int32_t> slots(last - first, slot), positions, tokens;
   for (int p = first; p < last; ++p) { positions.push_back(p); tokens.push_back(q.prompt[p]); }
-  int rc = run_kv_passes(e, slots, positions, tokens, &e->st.prefill_ms, &e->st.prefill_passes);
+  int rc = run_kv_passes(e, slots, positions, tokens, rows_max, &e->st.prefill_ms, &e->st.prefill_passes);
   if (rc) return rc;
   if (!e->dry) HIP_TRY(hipEventRecord(e->ev_slot[slot], e->wk[1].stream));
   e->st.prefill_positions += last - first;
@@ -1344,7 +1350,7 @@ int pl_prefill(pl_engine *e, int32_t slot, int32_t *out_positions) {
   // a slot whose prompt is already being read in the background: nothing is left to read, wait for it
   const bool already = slot >= 0 && slot < e->cfg.max_batch && e->seqs[slot].active && e->seqs[slot].reading;
   if (already && out_positions) *out_positions = 0;
-  int rc = already ? PL_OK : start_prefill(e, slot, out_positions);
+  int rc = already ? PL_OK : start_prefill(e, slot, e->pass_rows, out_positions);
   if (rc) return rc;
   Seq &q = e->seqs[slot];
   if (q.reading) {
@@ -1360,7 +1366,7 @@ int pl_prefill(pl_engine *e, int32_t slot, int32_t *out_positions) {
 
 int pl_prefill_async(pl_engine *e, int32_t slot, int32_t *out_positions) {
   if (!e) return fail(PL_E_INVAL, "NULL argument");
-  return start_prefill(e, slot, out_positions);
+  return start_prefill(e, slot, std::min(e->pass_rows, BACKGROUND_ROWS), out_positions);
 }
 
 int pl_get_stats(pl_engine *e, pl_stats *out) {

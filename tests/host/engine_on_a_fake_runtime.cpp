@@ -298,6 +298,10 @@ void pass_rows() {
     const Launch &l = last("step_begin_kernel");
     const int rows = what == 0 ? 4000 : 4000 - 2048;
     CHECK(l.begin.src.row_slot - (const int32_t *)l.begin.src.seq_id == 2 * ((rows + 63) / 64 * 64));   // (ids of eight bytes)
+    // beside decode steps, whose kernels would wait for a long pass's, no more than 768 rows
+    CHECK(pl_add_sequence(e, 2, prompt.data(), 4001, 4, 1.f, &slot) == PL_OK && pl_prefill_async(e, slot, &read) == PL_OK && read == 4000);
+    const uint64_t before = st.prefill_passes;
+    CHECK(pl_get_stats(e, &st) == PL_OK && st.prefill_passes - before == 6 && last("step_begin_kernel").attn.n_seq == 4000 - 5 * 768);
     pl_destroy(e);
     device_limit = ~(size_t)0;
   }

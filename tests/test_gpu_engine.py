@@ -466,6 +466,27 @@ def test_passes_of_more_than_1024_rows_leave_the_cache_of_reading_token_by_token
         e.close()
 
 
+@pytest.mark.parametrize("n_prompt,passes", [(769, 1), (770, 2), (2001, 3)])
+def test_passes_beside_steps_leave_the_cache_of_the_blocking_ones(n_prompt, passes):
+    """Background reading takes fewer rows a pass than pl_prefill: bit-identical caches on both sides of its limit."""
+    m = synth.ModelCfg(2, 768, 8, 2, 32, 9216, 512)
+    eng = [pl.Engine.from_model(m, max_batch=2, max_context=2048, kv_pool_tokens=2048, kv_page_tokens=64, seed=3, device=0) for _ in range(2)]
+    blob = eng[0].pack_weights(synth.make_weights(m, seed=11), synth.f32_to_bf16_bits)
+    prompt = synth.random_prompts(np.random.default_rng(n_prompt), 1, n_prompt, m.vocab)[0]
+    for e, read in zip(eng, ("prefill", "prefill_async")):
+        e.load_weights(blob)
+        assert e.add_sequence(5, prompt, 4) == 0 and getattr(e, read)(0) == n_prompt - 1
+        e.decode_step(np.array([5, 5], np.int32))
+    assert [e.stats()["prefill_passes"] for e in eng] == [1, passes]
+    kv = [[e.debug_read_kv(0, l, n_prompt) for l in range(m.n_layers)] for e in eng]
+    for l in range(m.n_layers):
+        for part in range(2):
+            assert np.array_equal(kv[0][l][part], kv[1][l][part]), (l, part)
+    assert np.array_equal(*(e.debug_get_logits(1) for e in eng))
+    for e in eng:
+        e.close()
+
+
 @pytest.mark.parametrize("d,n_prompt", [(256, 290), (1024, 390), (1024, 520)])
 def test_passes_whose_long_product_stays_in_slices_leave_the_cache_of_reading_token_by_token(d, n_prompt):
     """A down projection of long K leaves a pass of more than 256 rows in all its K slices, by 128 x 256 tiles (few of them) or
