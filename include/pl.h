@@ -213,7 +213,7 @@ int pl_add_sequence(pl_engine *e, uint64_t seq_id, const int32_t *prompt, int32_
  * PL_E_STATE if the slot is idle or before pl_load_weights. */
 int pl_prefill(pl_engine *e, int32_t slot, int32_t *out_positions);
 /* The same reading, in the background: passes of up to 768 positions are enqueued on a stream of their own and the call
- * returns at once (with 24 passes under way it waits for the oldest), so decode steps of the other slots go on meanwhile (the passes are GEMM-bound, the
+ * returns at once (with more than about 32000 positions under way it waits for the oldest), so decode steps of the other slots go on meanwhile (the passes are GEMM-bound, the
  * decode step mostly waits for K/V bytes; the two overlap on the GPU).  Until its passes have finished
  * the slot takes no part in decode steps: pl_decode_step leaves it out (its entry is simply missing
  * from that step's output) and includes it from the first step that finds the reading complete; a

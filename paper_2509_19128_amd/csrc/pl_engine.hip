@@ -136,16 +136,18 @@ struct pl_engine {
   };
   Work wk[2];
   // Host images of the cache-only passes in flight: a pass's image must stay intact until its copy to
-  // the device has run, so the passes take images from a ring; each entry carries the events that
-  // time its pass.
+  // the device has run, so the passes take images one behind the other from a ring of pinned memory; each entry carries the
+  // events that time its pass.
   struct PassImage {
     char *meta_h = nullptr;
+    int64_t bytes = 0;
     hipEvent_t ev_begin = nullptr, ev_end = nullptr;
     bool pending = false;
     double *ms_into = nullptr;
   };
-  std::vector<PassImage> ring;
-  char *ring_h = nullptr;   // the images' pinned memory
+  std::vector<PassImage> ring;   // in the order of their passes from ring_next on
+  char *ring_h = nullptr;        // the images' pinned memory: ring_bytes, the next image at ring_at if it fits behind
+  int64_t ring_bytes = 0, ring_at = 0;
   size_t ring_next = 0;
   std::vector<hipEvent_t> ev_slot;   // per slot: end of its background prompt reading
   hipEvent_t ev_pre_last = nullptr;  // end of the last cache-only pass enqueued
@@ -309,8 +311,9 @@ constexpr int SLICED_ROWS = 256;
 // 34 ms; 7B shape, 200 sequences (12 alone) 35 / 25 / 22 / 22 / 20 / 20 and 79 / 98 / 112 / 98 / 125 / 128.  768 is where steps are as fast as
 // beside 1024 rows of plain 128-row tiles (4.2 and 21.5, 29 and 124).
 constexpr int BACKGROUND_ROWS = 768;
-// Host metadata images of cache-only passes that may wait on the device at once: background reading of 18432 tokens returns at once.
-constexpr int PASS_RING = 24;
+// Cache-only passes that may wait on the device at once: as many as their host images fit the memory of PASS_RING images of the longest
+// pass (background reading of 32000 tokens returns at once), and no more than PASS_RING_MOST.
+constexpr int PASS_RING = 8, PASS_RING_MOST = 48;
 
 int alloc_device(pl_engine *e) {
   const pl_model_cfg &c = e->cfg;
@@ -392,10 +395,9 @@ int alloc_device(pl_engine *e) {
   if (rc) return rc;
   const int64_t pool_elems = e->layer_stride * c.n_layers;
   e->ring.resize(PASS_RING);
-  const int64_t image = (pl_engine::Work::image_bytes(e->pass_rows) + 63) / 64 * 64;
-  HIP_TRY(hipHostMalloc((void **)&e->ring_h, (size_t)(image * PASS_RING), hipHostMallocDefault));
+  e->ring_bytes = (pl_engine::Work::image_bytes(e->pass_rows) + 63) / 64 * 64 * PASS_RING;
+  HIP_TRY(hipHostMalloc((void **)&e->ring_h, (size_t)e->ring_bytes, hipHostMallocDefault));
   for (auto &im : e->ring) {
-    im.meta_h = e->ring_h + (&im - e->ring.data()) * image;
     HIP_TRY(hipEventCreate(&im.ev_begin));
     HIP_TRY(hipEventCreate(&im.ev_end));
   }
@@ -692,6 +694,39 @@ void harvest_passes(pl_engine *e) {
   (void)hipGetLastError();
 }
 
+// The entry of the next cache-only pass, with room for an image of `bytes`.  Waits for the passes whose images lie there, and, with
+// PASS_RING_MOST on their way, for the oldest; *out is good until the next call.
+int take_image(pl_engine *e, int64_t bytes, pl_engine::PassImage **out) {
+  bytes = (bytes + 63) / 64 * 64;
+  if (e->ring[e->ring_next].pending) harvest_passes(e);
+  if (e->ring[e->ring_next].pending && e->ring.size() < PASS_RING_MOST) {
+    pl_engine::PassImage im;
+    HIP_TRY(hipEventCreate(&im.ev_begin));
+    const hipError_t err = hipEventCreate(&im.ev_end);
+    if (err != hipSuccess) {
+      (void)hipEventDestroy(im.ev_begin);
+      HIP_TRY(err);
+    }
+    e->ring.insert(e->ring.begin() + e->ring_next, im);
+  }
+  pl_engine::PassImage &im = e->ring[e->ring_next];
+  if (e->ring_at + bytes > e->ring_bytes) e->ring_at = 0;
+  char *at = e->ring_h + e->ring_at;
+  bool waited = false;
+  for (auto &x : e->ring) {
+    if (!x.pending || (&x != &im && (x.meta_h >= at + bytes || at >= x.meta_h + x.bytes))) continue;
+    HIP_TRY(hipEventSynchronize(x.ev_end));
+    waited = true;
+  }
+  if (waited) harvest_passes(e);
+  im.meta_h = at;
+  im.bytes = bytes;
+  e->ring_at += bytes;
+  e->ring_next = (e->ring_next + 1) % e->ring.size();
+  *out = &im;
+  return PL_OK;
+}
+
 // Wait for every cache-only pass enqueued so far; slots whose prompts were being read join the batch.
 int drain_passes(pl_engine *e) {
   if (e->dry) {
@@ -721,15 +756,12 @@ int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::ve
   for (size_t r0 = 0; r0 < total; r0 += rows_max) {
     const int n = (int)std::min<size_t>(rows_max, total - r0);
     if (!e->dry) {
-      // next host image of the ring; if its previous pass has not run yet, wait for it
-      pl_engine::PassImage &im = e->ring[e->ring_next];
-      e->ring_next = (e->ring_next + 1) % e->ring.size();
-      if (im.pending) {
-        HIP_TRY(hipEventSynchronize(im.ev_end));
-        harvest_passes(e);
-      }
-      w.meta_h = im.meta_h;
       w.pitch = std::min((n + 63) / 64 * 64, w.rows_cap);   // (a function of n, as graphs hold the arrays' addresses)
+      pl_engine::PassImage *image = nullptr;
+      const int taken = take_image(e, w.image_bytes(w.pitch), &image);
+      if (taken) return taken;
+      pl_engine::PassImage &im = *image;
+      w.meta_h = im.meta_h;
       int items = 0, chunks = 0;
       const int per_group = pl::attention_rows_per_group(c.n_q_heads, c.n_kv_heads);
       int32_t *row_slot = w.m_row_slot(false), *pos = w.m_pos(false), *inp = w.m_input(false), *frc = w.m_forced(false);

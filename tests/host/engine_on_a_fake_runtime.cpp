@@ -40,6 +40,23 @@ std::vector<Launch> done, captured;
 dim3 call_grid, call_block;
 int products = 0;   // launches whose buffers were looked at
 
+// A device that is behind: nothing enqueued has run until an event behind it (or its stream) is waited for, so the host memory that
+// copies read must stay as it is.
+struct Copy { const char *from; size_t bytes; int at; };
+std::vector<Copy> on_their_way;
+std::map<hipEvent_t, int> recorded;
+bool behind = false;
+int enqueued = 0, finished = 0, waits = 0;
+size_t table_bytes = 0;   // copies of the page table, whose rows in use stay the same, are not looked at
+
+void finish(int upto) {
+  if (upto > finished) finished = upto;
+  size_t k = 0;
+  for (const Copy &c : on_their_way)
+    if (c.at > finished) on_their_way[k++] = c;
+  on_their_way.resize(k);
+}
+
 // The buffers of a product and of the kernels that take its slices lie in one allocation each.
 void buffers_fit(const std::string &kernel, void **args) {
   auto number = [&](int i) { return (int64_t) * (const int *)args[i]; };
@@ -132,7 +149,15 @@ hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = calloc(1, n); ++ho
 hipError_t hipHostFree(void *p) { free(p); --host_allocations; return hipSuccess; }
 hipError_t hipMemGetInfo(size_t *f, size_t *t) { *f = device_limit - device_used; *t = device_limit; return hipSuccess; }
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { if (copying) memcpy(d, s, n); return hipSuccess; }
-hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { CHECK(!capturing); if (copying) memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) {
+  CHECK(!capturing);
+  if (copying) memcpy(d, s, n);
+  if (behind && n != table_bytes) {
+    for (const Copy &c : on_their_way) CHECK((const char *)s + n <= c.from || c.from + c.bytes <= (const char *)s);
+    on_their_way.push_back(Copy{(const char *)s, n, ++enqueued});
+  }
+  return hipSuccess;
+}
 hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { CHECK(!capturing); if (copying) memset(d, v, n); return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
@@ -141,14 +166,17 @@ const char *hipGetErrorString(hipError_t) { return "made to fail"; }
 hipError_t hipGetSymbolAddress(void **, const void *) { return hipErrorNotFound; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)malloc(1); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { free((void *)s); return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { finish(enqueued); return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
-hipError_t hipEventDestroy(hipEvent_t e) { free((void *)e); return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return fail_event_record && --fail_event_record == 0 ? hipErrorUnknown : hipSuccess; }
-hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { recorded.erase(e); free((void *)e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
+  recorded[e] = enqueued;
+  return fail_event_record && --fail_event_record == 0 ? hipErrorUnknown : hipSuccess;
+}
+hipError_t hipEventQuery(hipEvent_t e) { return behind && recorded[e] > finished ? hipErrorNotReady : hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t e) { finish(recorded[e]); ++waits; return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { capturing = true; captured.clear(); return hipSuccess; }
 hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *g) { capturing = false; *g = (hipGraph_t) new std::vector<Launch>(captured); return hipSuccess; }
@@ -352,6 +380,36 @@ void pass_buffers() {
   CHECK(done.empty());
 }
 
+// Background reading does not wait for the device while the host images of its passes fit the pinned memory, and no image is overwritten
+// before its copy has run, whatever passes (long, short, of one prompt or of many) come one behind the other.
+void pass_images() {
+  for (int graphs = 0; graphs < 2; ++graphs) {
+    pl_model_cfg c = shape(2, 128, 31744, 128 * 256 + 4 * 31744);
+    pl_engine *e = engine(c);
+    CHECK(pl_debug_set_graphs(e, graphs) == PL_OK);
+    table_bytes = (size_t)c.max_batch * ((c.max_context + c.kv_page_tokens - 1) / c.kv_page_tokens) * 4;
+    std::vector<int32_t> prompt(c.max_context, 3);
+    behind = true;
+    waits = 0;
+    int32_t slot = -1, blocking = -1;
+    CHECK(pl_add_sequence(e, 1, prompt.data(), 30001, 4, 1.f, &slot) == PL_OK && pl_prefill_async(e, slot, nullptr) == PL_OK && waits == 0);
+    CHECK(pl_add_sequence(e, 2, prompt.data(), 31001, 4, 1.f, &slot) == PL_OK && pl_prefill_async(e, slot, nullptr) == PL_OK && waits > 0);
+    for (int i = 0; i < 100; ++i) {
+      CHECK(pl_add_sequence(e, 10 + i, prompt.data(), 2 + i * 2, 4, 1.f, &slot) == PL_OK && pl_prefill_async(e, slot, nullptr) == PL_OK);
+      if (i % 40 == 20) CHECK(pl_add_sequence(e, 200 + i, prompt.data(), 9001, 4, 1.f, &blocking) == PL_OK && pl_prefill(e, blocking, nullptr) == PL_OK);
+    }
+    pl_step_out out{};
+    CHECK(pl_decode_step(e, nullptr, &out) == PL_OK && out.n > 0);
+    for (int i = 0; i < 30; ++i) {   // nothing on its way, then a little: no wait
+      CHECK(pl_retire_sequence(e, slot) == PL_OK && (waits = 0) == 0);
+      CHECK(pl_add_sequence(e, 300 + i, prompt.data(), 1000, 4, 1.f, &slot) == PL_OK && pl_prefill_async(e, slot, nullptr) == PL_OK && waits == 0);
+    }
+    pl_destroy(e);
+    behind = false;
+    on_their_way.clear();
+  }
+}
+
 // Operands of 2 GiB are refused whichever kernel the sizes call for: offsets into them have 31 bits.
 void operand_limits() {
   const int K = 1 << 21;
@@ -397,6 +455,7 @@ int main(int, char **argv) {
   else if (test == "scarce_memory") scarce_memory();
   else if (test == "pass_rows") pass_rows();
   else if (test == "pass_buffers") pass_buffers();
+  else if (test == "pass_images") pass_images();
   else if (test == "operand_limits") operand_limits();
   else return 2;
   CHECK(device_memory.empty() && host_allocations == 0);
