@@ -6,7 +6,7 @@
 // wavefront fetches one contiguous KiB that is already in MFMA operand order (the page layout is
 // chosen for that), the query heads that share a kv head ride along as the 16 columns of one
 // 16x16x32 MFMA so each K/V byte is read once for the whole group, and soft-max statistics are
-// reduced with cross-lane shuffles.  Work is split over (sequence, kv head, item of tokens).
+// reduced by row swaps between lanes.  Work is split over (sequence, kv head, item of tokens).
 //
 // The order of a result's additions is fixed by the chunk length alone, whatever is launched: a chunk is
 // cut into subs of ATTN_SUB tokens; wavefront w takes the 32-token runs w, w + 4, ... of a sub with an
@@ -527,9 +527,10 @@ __global__ __launch_bounds__(HD) void attn_merge_kernel(AttnParams p) {
 // (as in a decode step) reads the sequence once per row.  Operation by operation the same sums as the decode kernel
 // for every row: runs, subs, wavefronts and chunks in the same order; a run that lies beyond a row's positions
 // leaves its column as it was (factor 1, product not taken: 0 times an infinity would not be 0).
-// Bound by vector arithmetic (about 80 operations per run and column block; positions are masked only in runs that some row
-// does not see whole), then by L2.  3001-token prompt, 1.5B shape, the nine launches of its passes: 346 us, 365 with
-// every run masked, maxima by shuffles through LDS and page ids by vector loads; 960 row by row.
+// Bound by vector arithmetic (about 80 instructions per run and column block, 32 more where a maximum moves; positions are masked only
+// in runs that some row does not see whole), then by L2.  3000 rows of the 1.5B shape in one launch: 65 us, 84 with results at a
+// stride of HD in LDS, 100 with whole rows per column block too.  As nine launches of 1000 rows before those two: 346 us, 365 with every run
+// masked, maxima by shuffles through LDS and page ids by vector loads; 960 row by row.
 template <int HD, int CB>
 __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnParams p) {
   constexpr int NJ = HD / 32, NV = HD / 16, COLS = CB * 16, PER = COLS * HD / 1024;

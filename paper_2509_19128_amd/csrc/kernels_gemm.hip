@@ -2,7 +2,7 @@
 //
 // With M = batch <= 256 rows these products are bound by streaming W once from HBM; W is never
 // reused across workgroups, so it bypasses LDS: every wavefront loads the W rows it owns straight
-// into MFMA B-operand registers.  W is stored in operand order (blocks of 32 rows x 64 k, see
+// into the registers of the MFMA's first operand.  W is stored in operand order (blocks of 32 rows x 64 k, see
 // pl_weight_layout in pl.h), so each of those loads is one contiguous KiB per wavefront.  The small activation tile x is what all
 // workgroups share; it goes to LDS by direct loads and feeds the other operand.  32x32x16 bf16 MFMAs
 // accumulate in fp32.  K can be split across workgroups (partials summed by the consumer in a

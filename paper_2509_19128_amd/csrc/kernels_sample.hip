@@ -115,7 +115,7 @@ __device__ inline void finish_row(const SampleParams &p, int row, const Part &v)
 // The sum of exponentials does not depend on NT, so a row's log-prob does not depend on how many rows share the
 // call: all exponentials are relative to the slice's maximum, and they are added up as SUM_LANES threads of
 // SUM_LANES / 64 wavefronts would, whatever number of these a thread takes over.
-// 256 x 152064, whole call: 38 us (the kernel 34, 4.5 TB/s) against 54 with the bounds by logarithms, the best entry of every lane
+// 256 x 152064, whole call, the merge launch included: 35 us (4.4 TB/s) against 54 with the bounds by logarithms, the best entry of every lane
 // computed, and two multiplications per product (a product is one instruction now, v_mad_u64_u32, 5.6 cycles where the two
 // took 9.7; fused multiply-adds in double precision, three per product, gave 55 us); 82-93 us with every entry's noise evaluated.
 constexpr float KEY_ERROR = 0.088f, KEY_SLACK = 0.004f;   // of log2: 0.0861 per difference of bits and logarithm
