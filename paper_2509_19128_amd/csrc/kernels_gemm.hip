@@ -307,10 +307,7 @@ struct Tile {
         }
         bf16x4 o;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float sv = gte[e] / (1.f + __expf(-gte[e]));
-          o[e] = (__bf16)(sv * up[e]);
-        }
+        for (int e = 0; e < 4; ++e) o[e] = swiglu(gte[e], up[e]);
         if (m < M) *(bf16x4 *)(y + (i0 + i) * 8) = o;
       }
     }
@@ -564,7 +561,7 @@ __global__ __launch_bounds__(256) void swiglu_reduce_kernel(const float *__restr
   }
   bf16x4 o;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) o[i] = (__bf16)(g[i] / (1.f + __expf(-g[i])) * u[i]);
+  for (int i = 0; i < 4; ++i) o[i] = swiglu(g[i], u[i]);
   *(bf16x4 *)(mid + (int64_t)m * F + (col0 >> 1) + j) = o;
 }
 

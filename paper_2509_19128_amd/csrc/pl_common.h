@@ -62,6 +62,17 @@ __device__ inline float wave_max(float v) { return wave_reduce(v, OpMax{}); }
 __device__ inline int wave_max(int v) { return wave_reduce(v, OpMax{}); }
 __device__ inline int wave_min(int v) { return wave_reduce(v, OpMin{}); }
 
+// SwiGLU of a gate and an up value, one rounding rule for every kernel that has both.  A reciprocal instead of a division: the division's
+// dozen instructions and its switches of the denormal mode were all that a wavefront did between its last product and its stores
+// (errors of a few 2^-24 where the result is rounded to 2^-9).
+__device__ inline __bf16 swiglu(float g, float u) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return (__bf16)(g * __builtin_amdgcn_rcpf(1.f + __expf(-g)) * u);
+#else
+  return (__bf16)0.f;
+#endif
+}
+
 // ---- KV page geometry (one layer, one page, one kv head: K block then V block) ---------------
 // Tokens of a page are grouped in runs of 32 (t = 32 r + u).  Both blocks are laid out so that the
 // 64 lanes of a wavefront read one MFMA operand with a single fully contiguous 1 KiB load.
