@@ -546,19 +546,15 @@ __global__ __launch_bounds__(256) void gemm_gu_joint_kernel(const bf16_t *__rest
 // SwiGLU over K-split partial sums: parts [splits][M][ld] holds columns [col0, col0 + ld) of the
 // interleaved gate/up product (blocks of 64 columns: 32 gate, then the 32 matching up columns);
 // mid[m][(col0 + c) / 2 ...] = silu(sum_s gate) * (sum_s up), slices added in order.
+// Four outputs of a row per thread.
+template <int SL>
 __global__ __launch_bounds__(256) void swiglu_reduce_kernel(const float *__restrict__ parts, int splits, int M, int ld,
                                                             int col0, bf16_t *__restrict__ mid, int F) {
-  const int quads = ld >> 3;   // four outputs per thread (ld is a multiple of 64)
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (int64_t)M * quads) return;
-  const int m = (int)(idx / quads), j = (int)(idx % quads) * 4;
-  const int c = (j >> 5) * 64 + (j & 31);
-  f32x4 g = {0.f, 0.f, 0.f, 0.f}, u = {0.f, 0.f, 0.f, 0.f};
-  for (int sl = 0; sl < splits; ++sl) {
-    const float *row = parts + ((int64_t)sl * M + m) * ld;
-    g += *(const f32x4 *)(row + c);
-    u += *(const f32x4 *)(row + c + 32);
-  }
+  const int j = (blockIdx.x * blockDim.x + threadIdx.x) * 4, m = blockIdx.y;   // (ld is a multiple of 64)
+  if (j >= ld / 2) return;
+  const f32x4 *row = (const f32x4 *)(parts + (int64_t)m * ld + (j >> 5) * 64 + (j & 31));
+  const int64_t stride = (int64_t)M * (ld / 4);
+  const f32x4 g = sum_slices<SL>(row, splits, stride), u = sum_slices<SL>(row + 8, splits, stride);
   bf16x4 o;
 #pragma unroll
   for (int i = 0; i < 4; ++i) o[i] = swiglu(g[i], u[i]);
@@ -666,8 +662,10 @@ bool splits_valid(int K, int splits) {
 }
 
 int swiglu_reduce(const float *parts, int splits, int M, int ld, int col0, bf16_t *mid, int F, hipStream_t s) {
-  const int64_t total = (int64_t)M * (ld / 8);
-  hipLaunchKernelGGL(swiglu_reduce_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, parts, splits, M, ld, col0, mid, F);
+  const int quads = ld / 8, blocks = (quads + 255) / 256, nt = ((quads + blocks - 1) / blocks + 63) / 64 * 64;
+  with_slices(splits, [&](auto SL) {
+    hipLaunchKernelGGL(swiglu_reduce_kernel<decltype(SL)::value>, dim3(blocks, M), dim3(nt), 0, s, parts, splits, M, ld, col0, mid, F);
+  });
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }
 

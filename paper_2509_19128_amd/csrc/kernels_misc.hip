@@ -83,48 +83,45 @@ __global__ __launch_bounds__(NT) void step_begin_kernel(StepBegin q, AttnParams 
 
 // h[row] += sum_s parts[s][row]; a[row] = rmsnorm(h[row]) * g.  The slices are added up in slice order, their
 // sum to h (a product that comes as one slice, added up the same way before, gives the same bits).
-// One workgroup of NT threads per row, NV 16-byte pieces per thread (NT * NV * 4 >= d); the row stays in
-// registers between the two passes.
-template <int NT, int NV>
-__global__ __launch_bounds__(NT) void resid_rmsnorm_kernel(float *h, const float *parts, int splits,
-                                                           const bf16_t *g, bf16_t *a, int n, int d, float eps) {
-  const int row = blockIdx.x, d4 = d >> 2;
-  float4 *h4 = (float4 *)(h + (int64_t)row * d);
-  float4 v[NV];
+// One workgroup per row, NV 16-byte pieces per thread, as many threads as that takes; the row stays in registers between the two passes.
+// Bound by its own chain (a kernel of a graph that does nothing takes 1.7 us): loads, a sum over the row, stores, and by the instructions
+// on the way, so every number of slices has a kernel without branches, the sum goes through lanes, the root is one instruction.  Rows
+// of 3584 floats, nine slices: 1 row 3.7 -> 2.7 us, 64 rows 4.1 -> 3.0, 256 rows 6.7 -> 5.5; of 1536, six slices, 64 rows 2.7 -> 2.0.
+template <int SL, int NV>
+__global__ __launch_bounds__(NV == 1 ? 512 : 1024) void resid_rmsnorm_kernel(float *h, const float *parts, int splits, const bf16_t *g,
+                                                                            bf16_t *a, int n, int d, float inv_d, float eps, int waves) {
+  const int row = blockIdx.x, d4 = d >> 2, threads = waves * 64;
+  f32x4 *h4 = (f32x4 *)(h + (int64_t)row * d);
+  const f32x4 *p4 = (const f32x4 *)(parts + (int64_t)row * d);
+  f32x4 v[NV];
+  bf16x4 gg[NV];
   float ss = 0.f;
 #pragma unroll
   for (int it = 0; it < NV; ++it) {
-    const int idx = threadIdx.x + it * NT;
-    if (idx < d4) {
-      float4 x = h4[idx], y = make_float4(0.f, 0.f, 0.f, 0.f);
-      // loads of up to 8 slices are issued together, the adds stay in slice order
-      for (int s0 = 0; s0 < splits; s0 += 8) {
-        float4 p[8];
+    const int idx = threadIdx.x + it * threads;
+    if (it == 0 || idx < d4) {   // (NV = 1: a thread per piece)
+      v[it] = h4[idx];
+      gg[it] = ((const bf16x4 *)g)[idx];
+      v[it] += sum_slices<SL>(p4 + idx, splits, (int64_t)n * d4);
+      h4[idx] = v[it];
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (s0 + u < splits) p[u] = ((const float4 *)(parts + ((int64_t)(s0 + u) * n + row) * d))[idx];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (s0 + u < splits) { y.x += p[u].x; y.y += p[u].y; y.z += p[u].z; y.w += p[u].w; }
-      }
-      x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
-      h4[idx] = x;
-      v[it] = x;
-      ss += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+      for (int e = 0; e < 4; ++e) ss += v[it][e] * v[it][e];
     }
   }
-  ss = block_sum<NT / 64>(ss);
-  const float r = 1.0f / sqrtf(ss / (float)d + eps);
+  __shared__ float red[16];
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  ss = wave_sum(lane < waves ? red[lane] : 0.f);
+  const float r = __builtin_amdgcn_rsqf(ss * inv_d + eps);
 #pragma unroll
   for (int it = 0; it < NV; ++it) {
-    const int idx = threadIdx.x + it * NT;
-    if (idx < d4) {
-      const bf16x4 gg = ((const bf16x4 *)g)[idx];
+    const int idx = threadIdx.x + it * threads;
+    if (it == 0 || idx < d4) {
       bf16x4 o;
-      o[0] = (__bf16)(v[it].x * r * (float)gg[0]);
-      o[1] = (__bf16)(v[it].y * r * (float)gg[1]);
-      o[2] = (__bf16)(v[it].z * r * (float)gg[2]);
-      o[3] = (__bf16)(v[it].w * r * (float)gg[3]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = (__bf16)(v[it][e] * r * (float)gg[it][e]);
       ((bf16x4 *)(a + (int64_t)row * d))[idx] = o;
     }
   }
@@ -141,35 +138,54 @@ __global__ void rope_tables_kernel(const int32_t *pos, float *cs, int32_t *ctx_l
 }
 
 // qkv (fp32, split-K partials) -> rotated q (bf16), rotated k and v into the row's cache page.
-// One thread per four consecutive rotated pairs (i .. i + 3 with their partners half + i ..), 16-byte
-// loads; a workgroup of 256 threads covers 1024 consecutive pairs of one row, i.e. several heads of q|k|v.
+// One thread per four consecutive rotated pairs (i .. i + 3 with their partners half + i ..) of a row, 16-byte
+// loads.  The page is looked up by scalar loads while the vectors are on their way.
+// BLOCKS (a pass): v goes eight rows at a time where they are eight consecutive positions from a multiple of eight on, whose elements
+// of one dimension are 16 bytes of the V block: grid rows n .. n + groups - 1, a thread per four dimensions of the eight.
+// 1.5B shape, 3000 rows 13.4 us with 2-byte stores of v.
+template <int SL, bool BLOCKS>
 __global__ __launch_bounds__(256) void rope_append_kernel(const float *qkv, int splits, const float *cs, const int32_t *pos,
                                                           const int32_t *row_slot, const int32_t *page_table, bf16_t *q_out,
                                                           bf16_t *kv_layer, int n, int Hq, int Hkv, int hd, int page_tokens,
                                                           int pages_per_seq) {
-  const int half = hd / 2, quads = half / 4;
-  const int quad = blockIdx.x * 256 + threadIdx.x;
-  if (quad >= (Hq + 2 * Hkv) * quads) return;
-  const int row = blockIdx.y, hh = quad / quads, i = (quad % quads) * 4;
-  const int width = (Hq + 2 * Hkv) * hd;
-  f32x4 x1 = {0.f, 0.f, 0.f, 0.f}, x2 = {0.f, 0.f, 0.f, 0.f};
-  // loads of up to 8 slices are issued together, the adds stay in slice order
-  for (int s0 = 0; s0 < splits; s0 += 8) {
-    f32x4 p1[8], p2[8];
+  const int half = hd / 2, quads = half / 4, width = (Hq + 2 * Hkv) * hd;
+  const int64_t page_elems = (int64_t)2 * page_tokens * hd, stride = (int64_t)n * (width / 4);
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  int row = blockIdx.y;
+  bool v_alone = true;   // this row's v goes by itself
+  if constexpr (BLOCKS) {
+    const bool group = row >= n;
+    const int r0 = group ? (row - n) * 8 : row & ~7;
+    bool eight = r0 + 8 <= n && pos[r0] % 8 == 0;
+    if (eight)
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (s0 + u < splits) {
-        const float *src = qkv + ((int64_t)(s0 + u) * n + row) * width + hh * hd;
-        p1[u] = *(const f32x4 *)(src + i);
-        p2[u] = *(const f32x4 *)(src + half + i);
+      for (int r = 1; r < 8; ++r) eight &= pos[r0 + r] == pos[r0] + r && row_slot[r0 + r] == row_slot[r0];
+    v_alone = !eight;
+    if (group) {
+      if (!eight || idx >= Hkv * hd / 4) return;
+      const int p = pos[r0], page = page_table[(int64_t)row_slot[r0] * pages_per_seq + p / page_tokens], hv = idx / (hd / 4), dim = idx % (hd / 4) * 4;
+      const f32x4 *src = (const f32x4 *)(qkv + (int64_t)r0 * width + (Hq + Hkv + hv) * hd + dim);
+      bf16x8 o[4];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        const f32x4 x = sum_slices<SL>(src + r * (width / 4), splits, stride);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e][r] = (__bf16)x[e];
       }
+      bf16_t *vb = kv_layer + ((int64_t)page * Hkv + hv) * page_elems + (int64_t)page_tokens * hd + v_elem_offset(p % page_tokens, dim, hd);
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (s0 + u < splits) { x1 += p1[u]; x2 += p2[u]; }
+      for (int e = 0; e < 4; ++e) *(bf16x8 *)(vb + e * 8) = o[e];
+      return;
+    }
   }
+  if (idx >= (Hq + (v_alone ? 2 : 1) * Hkv) * quads) return;
+  const int hh = idx / quads, i = (idx % quads) * 4;
+  const int p = pos[row], page = page_table[(int64_t)row_slot[row] * pages_per_seq + p / page_tokens], t = p % page_tokens;
+  const f32x4 *src = (const f32x4 *)(qkv + (int64_t)row * width + hh * hd + i);
+  const f32x4 c = *(const f32x4 *)(cs + (int64_t)row * hd + i), sn = *(const f32x4 *)(cs + (int64_t)row * hd + half + i);
+  const f32x4 x1 = sum_slices<SL>(src, splits, stride), x2 = sum_slices<SL>(src + half / 4, splits, stride);
   bf16x4 lo, hi;   // elements i .. i + 3 and half + i .. half + i + 3 of the head
   if (hh < Hq + Hkv) {
-    const f32x4 c = *(const f32x4 *)(cs + (int64_t)row * hd + i), sn = *(const f32x4 *)(cs + (int64_t)row * hd + half + i);
     rotate_pairs(x1, x2, c, sn, lo, hi);
   } else {
 #pragma unroll
@@ -181,10 +197,6 @@ __global__ __launch_bounds__(256) void rope_append_kernel(const float *qkv, int 
     *(bf16x4 *)(q + half + i) = hi;
     return;
   }
-  const int p = pos[row];
-  const int page = page_table[(int64_t)row_slot[row] * pages_per_seq + p / page_tokens];
-  const int t = p % page_tokens;
-  const int64_t page_elems = (int64_t)2 * page_tokens * hd;
   if (hh < Hq + Hkv) {
     // four consecutive dims of a token (i is a multiple of 4) are contiguous in the K block
     bf16_t *kb = kv_layer + ((int64_t)page * Hkv + (hh - Hq)) * page_elems;
@@ -252,13 +264,16 @@ int launch_step_begin(const StepBegin &q, const AttnParams &p, int cap, hipStrea
 int launch_resid_rmsnorm(float *h, const float *parts, int splits, const bf16_t *g, bf16_t *a, int n, int d,
                          float eps, hipStream_t s) {
   if (n <= 0) return 0;
-  // as many threads as a row has 16-byte pieces, so that all loads of a row are in flight at once and as many rows as fit a
-  // compute unit (rows of 1536 floats, 1000 of them: 13 us by workgroups of 1024 threads; 3000 of them 12 by 512); 4096 to 8192 floats two pieces each
-  auto launch = [&](auto kernel, int nt) { hipLaunchKernelGGL(kernel, dim3(n), dim3(nt), 0, s, h, parts, splits, g, a, n, d, eps); };
-  if (d <= 1024) launch(resid_rmsnorm_kernel<256, 1>, 256);
-  else if (d <= 2048) launch(resid_rmsnorm_kernel<512, 1>, 512);
-  else if (d <= 4096) launch(resid_rmsnorm_kernel<1024, 1>, 1024);
-  else launch(resid_rmsnorm_kernel<1024, 2>, 1024);
+  if (d % 256 || d > 8192 || splits < 1) return -1;
+  // a piece per thread up to rows of 2048 floats, two beyond (3584 floats, nine slices, 256 rows: 5.6 us by 896 threads, 5.5 by 448)
+  const int nv = d <= 2048 ? 1 : 2, waves = (d / 4 / nv + 63) / 64;
+  with_slices(splits, [&](auto SL) {
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(n), dim3(waves * 64), 0, s, h, parts, splits, g, a, n, d, 1.f / (float)d, eps, waves);
+    };
+    if (nv == 1) launch(resid_rmsnorm_kernel<decltype(SL)::value, 1>);
+    else launch(resid_rmsnorm_kernel<decltype(SL)::value, 2>);
+  });
   return ok();
 }
 
@@ -273,10 +288,17 @@ int launch_rope_tables(const int32_t *pos, float *cs, int32_t *ctx_len, int n, i
 
 int launch_rope_append(const float *qkv, int splits, const float *cs, const int32_t *pos,
                        const int32_t *row_slot, const int32_t *page_table, bf16_t *q_out, bf16_t *kv_layer,
-                       int n, int Hq, int Hkv, int hd, int page_tokens, int pages_per_seq, hipStream_t s) {
+                       int n, int Hq, int Hkv, int hd, int page_tokens, int pages_per_seq, bool pass, hipStream_t s) {
   if (n <= 0) return 0;
-  hipLaunchKernelGGL(rope_append_kernel, dim3(((Hq + 2 * Hkv) * (hd / 8) + 255) / 256, n), dim3(256), 0, s, qkv, splits, cs, pos, row_slot,
-                     page_table, q_out, kv_layer, n, Hq, Hkv, hd, page_tokens, pages_per_seq);
+  const int threads = (Hq + 2 * Hkv) * (hd / 8), blocks = (threads + 255) / 256, nt = ((threads + blocks - 1) / blocks + 63) / 64 * 64;
+  with_slices(splits, [&](auto SL) {
+    auto launch = [&](auto kernel, int rows) {
+      hipLaunchKernelGGL(kernel, dim3(blocks, rows), dim3(nt), 0, s, qkv, splits, cs, pos, row_slot, page_table, q_out, kv_layer, n, Hq, Hkv, hd,
+                         page_tokens, pages_per_seq);
+    };
+    if (pass) launch(rope_append_kernel<decltype(SL)::value, true>, n + n / 8);
+    else launch(rope_append_kernel<decltype(SL)::value, false>, n);
+  });
   return ok();
 }
 

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 typedef __bf16 bf16_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
@@ -61,6 +63,39 @@ __device__ inline float wave_sum(float v) { return wave_reduce(v, OpSum{}); }
 __device__ inline float wave_max(float v) { return wave_reduce(v, OpMax{}); }
 __device__ inline int wave_max(int v) { return wave_reduce(v, OpMax{}); }
 __device__ inline int wave_min(int v) { return wave_reduce(v, OpMin{}); }
+
+// Sum of `splits` partial sums, `stride` vectors apart, in slice order.  SL > 0: exactly that many, all loads issued together and no branch between
+// them; SL = 0: any number, eight loads at a time.
+template <int SL>
+__device__ __forceinline__ f32x4 sum_slices(const f32x4 *p, int splits, int64_t stride) {
+  f32x4 y = {0.f, 0.f, 0.f, 0.f};   // (from zero, as a folded product: slices of -0 add up to 0)
+  if constexpr (SL > 0) {
+    f32x4 v[SL];
+#pragma unroll
+    for (int u = 0; u < SL; ++u) v[u] = p[u * stride];
+#pragma unroll
+    for (int u = 0; u < SL; ++u) y += v[u];
+  } else {
+    for (int s0 = 0; s0 < splits; s0 += 8) {
+      f32x4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (s0 + u < splits) v[u] = p[(s0 + u) * stride];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (s0 + u < splits) y += v[u];
+    }
+  }
+  return y;
+}
+constexpr int SLICES_MOST = 12;   // slices that have a kernel of their own
+// calls f(integral constant): the number of slices, or 0 beyond SLICES_MOST
+template <int SL = 1, typename F>
+void with_slices(int splits, F f) {
+  if constexpr (SL > SLICES_MOST) f(std::integral_constant<int, 0>{});
+  else if (splits == SL) f(std::integral_constant<int, SL>{});
+  else with_slices<SL + 1>(splits, f);
+}
 
 // SwiGLU of a gate and an up value, one rounding rule for every kernel that has both.  A reciprocal instead of a division: the division's
 // dozen instructions and its switches of the denormal mode were all that a wavefront did between its last product and its stores
@@ -203,7 +238,7 @@ int launch_rope_tables(const int32_t *pos, float *cs, int32_t *ctx_len, int n, i
                        hipStream_t s);
 int launch_rope_append(const float *qkv, int splits, const float *cs, const int32_t *pos,
                        const int32_t *row_slot, const int32_t *page_table, bf16_t *q_out, bf16_t *kv_layer,
-                       int n, int Hq, int Hkv, int hd, int page_tokens, int pages_per_seq, hipStream_t s);
+                       int n, int Hq, int Hkv, int hd, int page_tokens, int pages_per_seq, bool pass, hipStream_t s);
 // fp32 test build (kernels_f32.hip)
 int f32_launch_norm(const float *embed, const int32_t *input_tok, int vocab, const float *y, const float *g, float *h,
                     float *a, int n, int d, float eps, hipStream_t s);

@@ -526,7 +526,7 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
       ap.qkv = w.parts; ap.cs = w.cs; ap.splits = e->ks_qkv.splits;
     } else {
       rc |= pl::launch_rope_append(w.parts, slices(e->ks_qkv, wq, d), w.cs, w.m_pos(true), w.m_row_slot(true), w.pt, w.q_rot, kv_layer, n,
-                                   c.n_q_heads, c.n_kv_heads, c.head_dim, e->page_tokens, e->pages_per_seq, s);
+                                   c.n_q_heads, c.n_kv_heads, c.head_dim, e->page_tokens, e->pages_per_seq, prefill, s);
       ap.q = w.q_rot;
     }
     if (prefill && l + 1 == c.n_layers) break;

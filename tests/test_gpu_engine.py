@@ -727,6 +727,29 @@ class _Device:
         self.__cuda_array_interface__ = dict(shape=(n,), typestr="<i2", data=(ptr, False), version=2)
 
 
+@pytest.mark.parametrize("first,n_prompt", [(0, 8), (0, 9), (0, 18), (1, 30), (8, 25), (13, 126)])
+def test_values_of_a_pass_are_appended_alike_whatever_position_it_begins_at(weights, first, n_prompt):
+    """Eight consecutive positions from a multiple of eight on are appended together, others one by one: a prompt of which `first` tokens
+    were read step by step leaves the cache of one read so to its end, bit for bit."""
+    master, _ = weights
+    prompt = synth.random_prompts(np.random.default_rng(n_prompt), 1, n_prompt, M.vocab)[0]
+    engines = [_engine(), _engine()]
+    for e in engines:
+        e.load_weights(e.pack_weights(master, synth.f32_to_bf16_bits))
+        assert e.add_sequence(3, prompt, 2) == 0
+        for _ in range(first):
+            e.decode_step()
+    assert engines[0].prefill(0) == n_prompt - 1 - first
+    for _ in range(n_prompt - 1 - first):
+        engines[1].decode_step()
+    caches = [_kv_of(e, 0, n_prompt - 1) for e in engines]
+    for l in range(M.n_layers):
+        for part in range(2):
+            assert np.array_equal(caches[0][l][part], caches[1][l][part]), (l, part)
+    for e in engines:
+        e.close()
+
+
 def test_batched_prefill_under_the_weights_active_at_admission_then_a_swap(weights):
     """A sequence admitted after an update reads its prompt under the new weights, while its
     neighbour keeps the cache computed under the old ones (Sec. 5.1)."""
