@@ -86,6 +86,27 @@ def test_weights_at_every_alignment_of_the_arrays_and_of_the_sequences(shift_pi,
         assert np.isclose(sums[2 * s].item(), seg.sum(), rtol=1e-11) and np.isclose(sums[2 * s + 1].item(), (seg * seg).sum(), rtol=1e-11)
 
 
+def test_a_weight_is_the_exponential_to_the_last_bits():
+    """Sequences of one token and a cap beyond every number: their sums are the exponentials themselves.  The kernel's may be off by 1.1 units in the
+    last place (half of one from its table, half from its last addition), numpy's by less than one; subnormal results by one unit of
+    their own more."""
+    rng = np.random.default_rng(8)
+    pi = np.concatenate([rng.uniform(-745, 709, 6000), rng.normal(0, 1, 6000), rng.normal(0, 1e-3, 2000), [0.0, -0.0, 709.78, 710.0, -745.1, -746.5, 1e30,
+                         -1e30, np.inf, -np.inf]]).astype(np.float32)
+    n = len(pi)
+    a, b, o = torch.from_numpy(pi).cuda(), torch.zeros(n, device="cuda"), torch.arange(n + 1, device="cuda")
+    sums, ess, tot = (torch.empty(k, device="cuda", dtype=torch.float64) for k in (2 * n, n, 3))
+    pl.pl_is_ess(a.data_ptr(), b.data_ptr(), o.data_ptr(), n, np.inf, 0, sums.data_ptr(), ess.data_ptr(), tot.data_ptr(), 0)
+    got = sums.cpu().numpy()[::2]
+    with np.errstate(over="ignore"):
+        ref = np.exp(pi.astype(np.float64))
+    fin = np.isfinite(ref)
+    assert np.array_equal(got[~fin], ref[~fin])
+    off = np.abs(got[fin] - ref[fin]) / np.spacing(ref[fin])
+    print("most units in the last place:", off.max())
+    assert off.max() <= 2 + (ref[fin][off.argmax()] < 2.3e-308)
+
+
 @pytest.mark.parametrize("with_w", [True, False])
 def test_a_sequences_sums_do_not_depend_on_the_number_of_sequences(with_w):
     """Both sides of the choice of threads (1536 sequences): weights and sums of the same sequences are bit-identical, at the
