@@ -85,36 +85,64 @@ __device__ inline bf16x8 run_exp(const float (&s)[8], float m, float &sum) {
   return p;
 }
 
-// Values that another workgroup of the same launch reads: written through to the memory all XCDs share and
-// read from there (agent scope), so that no L2 has to be written back or invalidated.
-__device__ inline void store_shared(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline float load_shared(const float *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// A result from its sums.  (A division would be a dozen instructions and two switches of the denormal mode for a value that is rounded to 2^-9.)
+__device__ inline bf16x4 finish(f32x4 o, float l) {
+  bf16x4 r = {};
+#ifdef __HIP_DEVICE_COMPILE__
+  const float f = __builtin_amdgcn_rcpf(l);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) r[e] = (__bf16)(o[e] * f);
+#endif
+  return r;
 }
 
-// The chunks of one (sequence, kv head), written by store_shared, folded in order into the output row.  256 threads.
+// Values that another workgroup of the same launch reads: written through to the memory all XCDs share and
+// read from there (agent scope), so that no L2 has to be written back or invalidated.
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+#ifdef __HIP_DEVICE_COMPILE__
+constexpr int AGENT_SCOPE = 16;   // of a buffer instruction
+struct Shared {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ Shared(const float *p, int64_t n) : r(__builtin_amdgcn_make_buffer_rsrc((void *)p, 0, (int)(n * 4), 0x00020000)) {}
+  __device__ void store4(int at, f32x4 v) const { __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, at * 4, 0, AGENT_SCOPE); }
+  __device__ void store2(int at, float2 v) const { __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, at * 4, 0, AGENT_SCOPE); }
+  __device__ f32x4 load4(int at) const { return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, at * 4, 0, AGENT_SCOPE)); }
+  __device__ float2 load2(int at) const { return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, at * 4, 0, AGENT_SCOPE)); }
+};
+#else
+struct Shared {
+  __device__ Shared(const float *, int64_t) {}
+  __device__ void store4(int, f32x4) const {}
+  __device__ void store2(int, float2) const {}
+  __device__ f32x4 load4(int) const { return {}; }
+  __device__ float2 load2(int) const { return {}; }
+};
+#endif
+
+// The chunks of one (sequence, kv head), written through, folded in order into the output row: four elements of a head per thread,
+// the loads of eight chunks together.  256 threads.
 template <int HD>
-__device__ inline void merge_chunks(const AttnParams &p, int b, int g, int nchunk) {
+__device__ inline void merge_chunks(const AttnParams &p, const Shared &po, const Shared &pml, int b, int g, int nchunk) {
   const int G = p.Hq / p.Hkv;
-  const int64_t base = ((int64_t)b * p.Hkv + g) * p.max_chunks;
-  for (int idx = threadIdx.x; idx < G * HD; idx += 256) {
-    const int h = idx / HD, d = idx % HD;
-    const float *ml = p.part_ml + base * ATTN_ML + h * 2, *po = p.part_o + base * G * HD + idx;
-    float M = -INFINITY, L = 0.f, O = 0.f;
-    for (int c0 = 0; c0 < nchunk; c0 += 8) {   // the loads of eight chunks are issued together
-      float m8[8], l8[8], o8[8];
+  for (int i = threadIdx.x; i < G * (HD / 4); i += 256) {
+    const int h = i / (HD / 4);
+    float M = -INFINITY, L = 0.f;
+    f32x4 O = {0.f, 0.f, 0.f, 0.f};
+    for (int c0 = 0; c0 < nchunk; c0 += 8) {
+      float2 ml[8];
+      f32x4 o[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         const int c = min(c0 + u, nchunk - 1);
-        m8[u] = load_shared(ml + (int64_t)c * ATTN_ML);
-        l8[u] = load_shared(ml + (int64_t)c * ATTN_ML + 1);
-        o8[u] = load_shared(po + (int64_t)c * G * HD);
+        ml[u] = pml.load2(c * ATTN_ML + h * 2);
+        o[u] = po.load4(c * G * HD + i * 4);
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (c0 + u < nchunk) fold_part(M, L, O, m8[u], l8[u], o8[u]);
+        if (c0 + u < nchunk) fold_part(M, L, O, ml[u].x, ml[u].y, o[u]);
     }
-    p.out[((int64_t)b * p.Hq + g * G + h) * HD + d] = (__bf16)(O / L);
+    *(bf16x4 *)(p.out + ((int64_t)b * p.Hq + g * G) * HD + i * 4) = finish(O, L);
   }
 }
 
@@ -124,7 +152,7 @@ __device__ inline void merge_chunks(const AttnParams &p, int b, int g, int nchun
 // trip ahead of the first scores: worth it in launches of few workgroups (attention_rotates).  Those launches do better with three
 // workgroups per compute unit of one register stage than with two of two (7B shape, 19 rows: a step 2450 -> 2425 us, others the same; the large
 // launches lose by it: 512 ragged sequences 680 -> 690).
-template <int HD, int NS, bool ROTATE>
+template <int HD, int NS, bool ROTATE, int SP>   // SP: slices of the product (ROTATE)
 __global__ __launch_bounds__(256, ROTATE ? 3 : 2) void attn_decode_kernel(AttnParams p) {
   static_assert(NS >= 1 && SUB_RUNS % (4 * NS) == 0, "a sub is whole rounds of the stages");
   constexpr int NJ = HD / 32;   // QK MFMAs per 16-token tile
@@ -176,18 +204,17 @@ __global__ __launch_bounds__(256, ROTATE ? 3 : 2) void attn_decode_kernel(AttnPa
   constexpr int QUADS = HD / 8;
   const int n_rot = ROTATE ? (G + (appends ? 2 : 0)) * QUADS : 0, hh = threadIdx.x / QUADS, pair = threadIdx.x % QUADS * 4;
   const bool rotates = (int)threadIdx.x < n_rot;
-  f32x4 f1[8], f2[8], rc = {}, rs = {};
+  f32x4 f1[SP], f2[SP], rc = {}, rs = {};
   int own_page = 0;
   if (ROTATE && rotates) {
     // everything the rotation reads is requested before the first K/V loads: loads return in order
     const int width = (p.Hq + 2 * p.Hkv) * HD;
     const float *src = p.qkv + (int64_t)b * width + (hh < G ? g * G + hh : hh == G ? p.Hq + g : p.Hq + p.Hkv + g) * HD + pair;
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (u < p.splits) {
-        f1[u] = *(const f32x4 *)(src + (int64_t)u * p.n_seq * width);
-        f2[u] = *(const f32x4 *)(src + (int64_t)u * p.n_seq * width + HD / 2);
-      }
+    for (int u = 0; u < SP; ++u) {
+      f1[u] = *(const f32x4 *)(src + (int64_t)u * p.n_seq * width);
+      f2[u] = *(const f32x4 *)(src + (int64_t)u * p.n_seq * width + HD / 2);
+    }
     rc = *(const f32x4 *)(p.cs + (int64_t)b * HD + pair);
     rs = *(const f32x4 *)(p.cs + (int64_t)b * HD + HD / 2 + pair);
     if (appends) own_page = pt[(ctx - 1) / p.page_tokens];
@@ -263,8 +290,7 @@ __global__ __launch_bounds__(256, ROTATE ? 3 : 2) void attn_decode_kernel(AttnPa
   if constexpr (ROTATE) {
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (u < p.splits) { x1 += f1[u]; x2 += f2[u]; }   // slices are added in order
+    for (int u = 0; u < SP; ++u) { x1 += f1[u]; x2 += f2[u]; }   // slices are added in order
     __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
@@ -417,28 +443,34 @@ __global__ __launch_bounds__(256, ROTATE ? 3 : 2) void attn_decode_kernel(AttnPa
   __syncthreads();
   // merge the four wavefronts of the workgroup
   const int nchunk = (ctx + p.chunk - 1) / p.chunk;
-  const int64_t pidx = ((int64_t)b * p.Hkv + g) * p.max_chunks + c;
-  for (int idx = threadIdx.x; idx < G * HD; idx += 256) {
-    int h = idx / HD, d = idx % HD;
-    float M = fmaxf(fmaxf(sm_m[0][h], sm_m[1][h]), fmaxf(sm_m[2][h], sm_m[3][h]));
-    float L = 0.f, O = 0.f;
+  // (1.5B shape, 64 rows: the last workgroup ended 6.6 us behind the last run, merging an element at a time in three rounds of loads; four elements per
+  // thread, and no division: 32.5 -> 29.9 us for the launch)
+  auto merged = [&](auto put) {   // four elements of a head per thread
+    for (int i = threadIdx.x; i < G * (HD / 4); i += 256) {
+      const int h = i / (HD / 4), d = i % (HD / 4) * 4;
+      const float M = fmaxf(fmaxf(sm_m[0][h], sm_m[1][h]), fmaxf(sm_m[2][h], sm_m[3][h]));
+      float L = 0.f;
+      f32x4 O = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      float f = __builtin_amdgcn_exp2f(sm_m[w][h] - M);
-      L = __builtin_fmaf(sm_l[w][h], f, L);
-      O = __builtin_fmaf(sm_o[w][h][d], f, O);
-    }
-    if (nchunk == 1) {
-      p.out[((int64_t)b * p.Hq + g * G + h) * HD + d] = (__bf16)(O / L);
-    } else {
-      store_shared(p.part_o + pidx * G * HD + idx, O);
-      if (d == 0) {
-        store_shared(p.part_ml + pidx * ATTN_ML + h * 2, M);
-        store_shared(p.part_ml + pidx * ATTN_ML + h * 2 + 1, L);
+      for (int w = 0; w < 4; ++w) {
+        const float f = __builtin_amdgcn_exp2f(sm_m[w][h] - M);
+        L = __builtin_fmaf(sm_l[w][h], f, L);
+        O = fma4(*(const f32x4 *)&sm_o[w][h][d], f, O);
       }
+      put(i, h, d, M, L, O);
     }
+  };
+  if (nchunk == 1) {
+    merged([&](int i, int, int, float, float L, f32x4 O) { *(bf16x4 *)(p.out + ((int64_t)b * p.Hq + g * G) * HD + i * 4) = finish(O, L); });
+    return;
   }
-  if (nchunk == 1 || !p.tickets) return;
+  const int64_t row_parts = ((int64_t)b * p.Hkv + g) * p.max_chunks;
+  const Shared po(p.part_o + row_parts * G * HD, (int64_t)p.max_chunks * G * HD), pml(p.part_ml + row_parts * ATTN_ML, (int64_t)p.max_chunks * ATTN_ML);
+  merged([&](int i, int h, int d, float M, float L, f32x4 O) {
+    po.store4(c * G * HD + i * 4, O);
+    if (d == 0) pml.store2(c * ATTN_ML + h * 2, make_float2(M, L));
+  });
+  if (!p.tickets) return;
   // The workgroup that finishes a (sequence, kv head) last folds its chunks: no merge launch (a 5 us kernel and
   // a launch gap per layer).  Every store above has reached the shared memory (the wait) before the
   // ticket is taken; partial results of different workgroups share no cache line (128 bytes), so the last one
@@ -454,71 +486,84 @@ __global__ __launch_bounds__(256, ROTATE ? 3 : 2) void attn_decode_kernel(AttnPa
     if (before == nchunk - 1) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
   }
   __syncthreads();
-  if (s_last) merge_chunks<HD>(p, b, g, nchunk);
+  if (s_last) merge_chunks<HD>(p, po, pml, b, g, nchunk);
 }
 
-// Merge of rows that span several items, where the decode kernel does not do it itself: one workgroup of HD
-// threads per (row, query head), four output elements each; thread group w folds wavefront w's subs, thread
-// group 0 whole chunks.  Latency bound (a few KiB per thread group): the loads of 16 parts are issued together.
-template <int HD>
-__global__ __launch_bounds__(HD) void attn_merge_kernel(AttnParams p) {
+// Merge of rows that span several items, where the decode kernel does not do it itself: one workgroup per (row, query head), four output
+// elements per thread.  Latency bound (a few KiB per thread group): the loads of 16 parts are issued together, no branch between them (19
+// rows of 7300 tokens, 7B shape, 8.0 -> 6.6 us).
+// SUBS: items are subs.  Two chunks at a time, HD threads for each; thread group w of a chunk folds wavefront w's subs, then the four
+// wavefronts are merged as the decode kernel does it and the chunks folded in order.
+template <int HD, bool SUBS>
+__global__ __launch_bounds__(SUBS ? 2 * HD : 64) void attn_merge_kernel(AttnParams p) {
   constexpr int QUADS = HD / 4;
-  const int b = blockIdx.y, hq = blockIdx.x, w = threadIdx.x / QUADS, d = threadIdx.x % QUADS * 4;
+  const int b = blockIdx.y, hq = blockIdx.x, at = threadIdx.x % HD, w = at / QUADS, d = at % QUADS * 4;
   const int G = p.Hq / p.Hkv, g = hq / G, h = hq % G;
-  const bool subs = p.item_tokens < p.chunk;
-  const int ctx = p.ctx_len[b], first = subs ? p.first_item[b] : 0;   // (list index of the row's first item)
+  const int ctx = p.ctx_len[b], first = SUBS ? p.first_item[b] : 0;   // (list index of the row's first item)
   if (ctx <= p.item_tokens) return;   // the decode kernel wrote the row
   const int nchunk = (ctx + p.chunk - 1) / p.chunk;
-  __shared__ f32x4 so[4][QUADS];
-  __shared__ float sml[4][2];
   float M = -INFINITY, L = 0.f;
   f32x4 O = {0.f, 0.f, 0.f, 0.f};
   // fold of n parts, part i at index at(i)
-  auto fold_parts = [&](float &m, float &l, f32x4 &o, int n, int ml_floats, auto at) {
+  auto fold_parts = [&](float &m, float &l, f32x4 &o, int n, int ml_floats, auto index) {
     for (int j0 = 0; j0 < n; j0 += 16) {
       float2 ml[16];
       f32x4 o16[16];
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
-        const int64_t part = at(min(j0 + u, n - 1));
+        const int64_t part = index(min(j0 + u, n - 1));
         ml[u] = *(const float2 *)(p.part_ml + part * ml_floats + h * 2);
         o16[u] = *(const f32x4 *)(p.part_o + (part * G + h) * HD + d);
       }
 #pragma unroll
-      for (int u = 0; u < 16; ++u)
-        if (j0 + u < n) fold_part(m, l, o, ml[u].x, ml[u].y, o16[u]);
+      for (int u = 0; u < 16; ++u) {   // (selects, not branches: parts beyond the last change nothing)
+        float m1 = m, l1 = l;
+        f32x4 o1 = o;
+        fold_part(m1, l1, o1, ml[u].x, ml[u].y, o16[u]);
+        const bool in = j0 + u < n;
+        m = in ? m1 : m;
+        l = in ? l1 : l;
+        o = in ? o1 : o;
+      }
     }
   };
-  if (!subs) {
+  if constexpr (!SUBS) {
+    if ((int)threadIdx.x >= QUADS) return;
     const int64_t base = ((int64_t)b * p.Hkv + g) * p.max_chunks;
-    if (w == 0) fold_parts(M, L, O, nchunk, ATTN_ML, [&](int c) { return base + c; });
-  }
-  for (int c = 0; subs && c < nchunk; ++c) {
-    const int per = p.chunk / p.item_tokens, n = min(per, (ctx - c * p.chunk + p.item_tokens - 1) / p.item_tokens);
-    float mw = -INFINITY, lw = 0.f;
-    f32x4 ow = {0.f, 0.f, 0.f, 0.f};
-    fold_parts(mw, lw, ow, n, 32, [&](int j) { return ((int64_t)(first + c * per + j) * p.Hkv + g) * 4 + w; });
-    __syncthreads();
-    so[w][threadIdx.x % QUADS] = ow;
-    if (d == 0) { sml[w][0] = mw; sml[w][1] = lw; }
-    __syncthreads();
-    // the merge of the four wavefronts as the decode kernel does it
-    const float Mc = fmaxf(fmaxf(sml[0][0], sml[1][0]), fmaxf(sml[2][0], sml[3][0]));
-    float Lc = 0.f;
-    f32x4 Oc = {0.f, 0.f, 0.f, 0.f};
+    fold_parts(M, L, O, nchunk, ATTN_ML, [&](int c) { return base + c; });
+  } else {
+    __shared__ f32x4 so[2][4][QUADS];
+    __shared__ float sml[2][4][2];
+    const int half = threadIdx.x / HD, per = p.chunk / p.item_tokens;
+    for (int c0 = 0; c0 < nchunk; c0 += 2) {
+      const int c = c0 + half;
+      float mw = -INFINITY, lw = 0.f;
+      f32x4 ow = {0.f, 0.f, 0.f, 0.f};
+      if (c < nchunk)
+        fold_parts(mw, lw, ow, min(per, (ctx - c * p.chunk + p.item_tokens - 1) / p.item_tokens), 32,
+                   [&](int j) { return ((int64_t)(first + c * per + j) * p.Hkv + g) * 4 + w; });
+      __syncthreads();
+      so[half][w][at % QUADS] = ow;
+      if (d == 0) { sml[half][w][0] = mw; sml[half][w][1] = lw; }
+      __syncthreads();
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const float f = __builtin_amdgcn_exp2f(sml[v][0] - Mc);
-      Lc = __builtin_fmaf(sml[v][1], f, Lc);
-      Oc = fma4(so[v][threadIdx.x % QUADS], f, Oc);
+      for (int k = 0; k < 2; ++k) {
+        if (c0 + k >= nchunk) continue;
+        const float Mc = fmaxf(fmaxf(sml[k][0][0], sml[k][1][0]), fmaxf(sml[k][2][0], sml[k][3][0]));
+        float Lc = 0.f;
+        f32x4 Oc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float f = __builtin_amdgcn_exp2f(sml[k][v][0] - Mc);
+          Lc = __builtin_fmaf(sml[k][v][1], f, Lc);
+          Oc = fma4(so[k][v][at % QUADS], f, Oc);
+        }
+        fold_part(M, L, O, Mc, Lc, Oc);
+      }
     }
-    fold_part(M, L, O, Mc, Lc, Oc);
+    if ((int)threadIdx.x >= QUADS) return;
   }
-  if (w != 0) return;
-  bf16x4 out;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) out[e] = (__bf16)(O[e] / L);
-  *(bf16x4 *)(p.out + ((int64_t)b * p.Hq + hq) * HD + d) = out;
+  *(bf16x4 *)(p.out + ((int64_t)b * p.Hq + hq) * HD + d) = finish(O, L);
 }
 
 // Attention of the rows of a cache-only pass: consecutive positions of one sequence, each over the positions up to its
@@ -725,10 +770,7 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnParams p) {
     const int at = threadIdx.x + 256 * k, cc = at / (HD / 4), d = at % (HD / 4) * 4;
     const int r = cc / G, h = cc % G;
     if (r >= nrows) continue;
-    bf16x4 o;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = (__bf16)(run_o[k][e] / run_l[cc]);
-    *(bf16x4 *)(p.out + ((int64_t)(row0 + r) * p.Hq + g * G + h) * HD + d) = o;
+    *(bf16x4 *)(p.out + ((int64_t)(row0 + r) * p.Hq + g * G + h) * HD + d) = finish(run_o[k], run_l[cc]);
   }
 }
 
@@ -751,7 +793,7 @@ int attention_chunk_tokens(int n_seq, int Hkv, int max_ctx) {
 
 // A step in which one item would outlast the rest: an item is then one sub.  A compute unit alone streams about
 // 1/128 of what the chip does, so a launch lasts at least longest_item x 128 of total bytes; cutting pays from
-// about three subs on (the merge launch takes 5 us, a sub 5).  7B shape, 19 sequences of 7000 tokens in an engine of
+// about three subs on (the merge launch takes 5 to 7 us, a sub 5).  7B shape, 19 sequences of 7000 tokens in an engine of
 // 256 slots (8192-token chunks): 82 + 5 (merge) -> 34 + 8 us per layer.  The result's bits do not depend on the choice.
 bool attention_split(int chunk, int64_t total_tokens, int64_t longest_item, int64_t n_subs, int Hkv) {
   return chunk > ATTN_SUB && longest_item >= 3 * ATTN_SUB && n_subs * Hkv <= ATTN_SPLIT_PARTS && longest_item * 128 > total_tokens * Hkv;
@@ -790,12 +832,16 @@ static void launch_attention_hd(const AttnParams &p, hipStream_t s, int part) {
   if (part != 2) {
     const dim3 grid((unsigned)(p.max_items * p.Hkv));
     if (p.q)
-      hipLaunchKernelGGL((attn_decode_kernel<HD, PL_ATTN_NS, false>), grid, dim3(256), 0, s, p);
+      hipLaunchKernelGGL((attn_decode_kernel<HD, PL_ATTN_NS, false, 1>), grid, dim3(256), 0, s, p);
     else
-      hipLaunchKernelGGL((attn_decode_kernel<HD, 1, true>), grid, dim3(256), 0, s, p);
+      with_slices<1, ATTN_ROTATE_SLICES>(p.splits, [&](auto SP) {
+        if constexpr (decltype(SP)::value > 0) hipLaunchKernelGGL((attn_decode_kernel<HD, 1, true, decltype(SP)::value>), grid, dim3(256), 0, s, p);
+      });
   }
-  if (part != 1 && p.merge)
-    hipLaunchKernelGGL(attn_merge_kernel<HD>, dim3(p.Hq, p.n_seq), dim3(HD), 0, s, p);
+  if (part != 1 && p.merge) {
+    if (p.item_tokens < p.chunk) hipLaunchKernelGGL((attn_merge_kernel<HD, true>), dim3(p.Hq, p.n_seq), dim3(2 * HD), 0, s, p);
+    else hipLaunchKernelGGL((attn_merge_kernel<HD, false>), dim3(p.Hq, p.n_seq), dim3(64), 0, s, p);
+  }
 }
 
 // part: 0 = the decode kernel and, where it does not merge the items of a row itself, the merge kernel; 1 = the

@@ -89,12 +89,12 @@ __device__ __forceinline__ f32x4 sum_slices(const f32x4 *p, int splits, int64_t 
   return y;
 }
 constexpr int SLICES_MOST = 12;   // slices that have a kernel of their own
-// calls f(integral constant): the number of slices, or 0 beyond SLICES_MOST
-template <int SL = 1, typename F>
+// calls f(integral constant): the number of slices, or 0 beyond MOST
+template <int SL = 1, int MOST = SLICES_MOST, typename F>
 void with_slices(int splits, F f) {
-  if constexpr (SL > SLICES_MOST) f(std::integral_constant<int, 0>{});
+  if constexpr (SL > MOST) f(std::integral_constant<int, 0>{});
   else if (splits == SL) f(std::integral_constant<int, SL>{});
-  else with_slices<SL + 1>(splits, f);
+  else with_slices<SL + 1, MOST>(splits, f);
 }
 
 // SwiGLU of a gate and an up value, one rounding rule for every kernel that has both.  A reciprocal instead of a division: the division's
