@@ -30,6 +30,7 @@ namespace pl {
 namespace {
 
 constexpr int SUB_RUNS = ATTN_SUB / 32;
+static_assert(PL_ATTN_CHUNK <= 1 << 20, "a work list's keys");
 typedef __attribute__((address_space(4))) int32_t scalar_i32;   // read by scalar loads
 
 // of the four lanes that hold a column's tokens
@@ -776,7 +777,7 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnParams p) {
 
 __global__ __launch_bounds__(1024) void attn_worklist_kernel(AttnParams p, int cap) {
   const int b = threadIdx.x;
-  build_worklist(b < p.n_seq ? p.ctx_len[b] : 0, b < p.n_seq ? (p.row_slot ? p.row_slot[b] : b) : 0, p.page_table, p.work, p.tickets,
+  build_worklist<1024>(b < p.n_seq ? p.ctx_len[b] : 0, b < p.n_seq ? (p.row_slot ? p.row_slot[b] : b) : 0, p.page_table, p.work, p.tickets,
                  p.first_item, p.n_seq, p.Hkv, p.item_tokens, p.page_tokens, p.pages_per_seq, cap, p.item_tokens < p.chunk);
 }
 

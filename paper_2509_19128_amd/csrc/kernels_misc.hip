@@ -6,79 +6,113 @@
 namespace pl {
 namespace {
 
-template <int NW>
-__device__ inline float block_sum(float v) {
-  __shared__ float red[NW];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  __syncthreads();
+constexpr int BEGIN_LIST = 512;   // most sequences of a step (threads of the workgroup that builds its list)
+
+
+// Sum over a workgroup of `waves` (at most 16) wavefronts, in a fixed order.
+__device__ inline float block_sum(float v, int waves) {
+  __shared__ float red[16];
+  v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  float t = 0.f;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) t += red[w];
-  return t;
+  const int lane = threadIdx.x & 63;
+  return wave_sum(lane < waves ? red[lane] : 0.f);
 }
 
-// cos/sin of pos * theta^(-2i/hd), evaluated in double so long positions lose nothing
-__device__ inline void rope_angle(float *cs, int pos, int i, int hd, float theta) {
-  const double inv_freq = pow((double)theta, -2.0 * (double)i / (double)hd);
-  const double ang = (double)pos * inv_freq;
-  cs[i] = (float)cos(ang);
-  cs[hd / 2 + i] = (float)sin(ang);
+// theta^(-2i/hd), and cos/sin of pos times that: in double so that long positions lose nothing
+__device__ inline double rope_freq(int i, int hd, float theta) { return pow((double)theta, -2.0 * (double)i / (double)hd); }
+__device__ inline void rope_angle(float *cs, int pos, int i, int hd, double freq) {
+  double sn, c;
+  sincos((double)pos * freq, &sn, &c);
+  cs[i] = (float)c;
+  cs[hd / 2 + i] = (float)sn;
 }
+__global__ void rope_freqs_kernel(double *freqs, int hd, float theta) { freqs[threadIdx.x] = rope_freq(threadIdx.x, hd, theta); }
 
 // The beginning of a step or pass, one launch: everything the layers need that depends on the metadata alone.
 // Workgroup 0 applies a decode step's page-table changes and builds the attention work list; workgroup r + 1 brings
 // row r: its metadata (read from the host's pinned image in a decode step, where a copy would be a launch of its
 // own ahead of this one), cos/sin of its position, h = E[token], a = rmsnorm(h) * g.
-// As separate launches: metadata copy 4 us, tables 4, work list 13, embedding 13 (7B shape, 256 rows), each with its
-// launch gap; now 14 us.
-template <int NT>
+// Bound by latency: one round trip to the host's memory (all of what a thread wants from there at once), one to the table or the row, the row's sum.
+// Decode steps, the frequencies' powers taken anew, scans through LDS and 1024 threads: 4 rows of the tiny shape 6.3 us, 64 of the 1.5B shape 7.6, 256 of the
+// 7B shape 13.1; now 4.1, 5.2 and 7.4.
+template <int NT, int NV>   // NV: pieces of eight elements per thread
 __global__ __launch_bounds__(NT) void step_begin_kernel(StepBegin q, AttnParams p, int cap) {
   if (blockIdx.x == 0) {
-    if constexpr (NT < 1024) return;   // a pass
-    const int n_upd = q.updates ? q.updates[0] : 0;
-    if (!p.work) return;   // a pass
-    for (int i = threadIdx.x; i < n_upd; i += 1024) q.page_table[q.updates[2 + 2 * i]] = q.updates[3 + 2 * i];
+    if (NT < BEGIN_LIST || !p.work) return;   // a pass
+    const int b = min((int)threadIdx.x, p.n_seq - 1);   // (no branch between the loads)
+    int n_upd = 0, at = 0, page = 0;
+    const int pos = q.src.pos[b], slot = q.src.row_slot[b];
+    if (q.updates) {   // one per sequence at most
+      at = q.updates[2 + 2 * b];
+      page = q.updates[3 + 2 * b];
+      n_upd = q.updates[0];
+    }
+    const bool has = (int)threadIdx.x < p.n_seq;
+    const int ctx = has ? pos + 1 : 0;
+    if ((int)threadIdx.x < n_upd) q.page_table[at] = page;
     __syncthreads();   // the list is built from the table
-    const int b = threadIdx.x;
-    const bool has = b < p.n_seq;
-    build_worklist(has ? q.src.pos[b] + 1 : 0, has ? q.src.row_slot[b] : 0, q.page_table, p.work, p.tickets, p.first_item, p.n_seq, p.Hkv,
-                   p.item_tokens, p.page_tokens, p.pages_per_seq, cap, p.item_tokens < p.chunk);
+    build_worklist<NT>(ctx, has ? slot : 0, q.page_table, p.work, p.tickets, p.first_item, p.n_seq, p.Hkv, p.item_tokens, p.page_tokens, p.pages_per_seq, cap,
+                       p.item_tokens < p.chunk);
     return;
   }
-  const int row = blockIdx.x - 1, pos = q.src.pos[row], d8 = q.d >> 3;
-  const int tok = min(max(q.src.input_tok[row], 0), q.vocab - 1);
-  const bool mine = (int)threadIdx.x < d8;   // d <= 8 NT: one piece of eight elements per thread
-  bf16x8 e = {};
-  if (mine) e = ((const bf16x8 *)(q.embed + (int64_t)tok * q.d))[threadIdx.x];
+  const int row = blockIdx.x - 1, d8 = q.d >> 3;
+  int pos = q.src.pos[row], tok = q.src.input_tok[row], slot = q.src.row_slot[row], forced = q.src.forced[row];
+  float inv_t = q.src.inv_t[row];
+  uint64_t seq_id = q.src.seq_id[row];
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+s"(pos), "+s"(tok), "+s"(slot), "+s"(forced), "+s"(inv_t), "+s"(seq_id));   // one round trip for all of them
+#endif
+  tok = min(max(tok, 0), q.vocab - 1);
   const int i = NT - 1 - (int)threadIdx.x;   // the last wavefronts, which have least of the row, take the angles
-  if (i < p.hd / 2) rope_angle(q.cs + (int64_t)row * p.hd, pos, i, p.hd, q.theta);
+  const double freq = i < p.hd / 2 ? q.freqs[i] : 0.0;
+  bf16x8 e[NV], g[NV];
+  bool mine[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int at = threadIdx.x + k * NT;
+    mine[k] = at < d8;
+    e[k] = g[k] = bf16x8{};
+    if (mine[k]) {
+      e[k] = ((const bf16x8 *)(q.embed + (int64_t)tok * q.d))[at];
+      g[k] = ((const bf16x8 *)q.g)[at];
+    }
+  }
+  if (i < p.hd / 2) rope_angle(q.cs + (int64_t)row * p.hd, pos, i, p.hd, freq);
   if (threadIdx.x == 0) {
     q.ctx_len[row] = pos + 1;
     if (q.dst.pos) {
-      q.dst.row_slot[row] = q.src.row_slot[row];
+      q.dst.row_slot[row] = slot;
       q.dst.pos[row] = pos;
-      q.dst.forced[row] = q.src.forced[row];
-      q.dst.inv_t[row] = q.src.inv_t[row];
-      q.dst.seq_id[row] = q.src.seq_id[row];
+      q.dst.forced[row] = forced;
+      q.dst.inv_t[row] = inv_t;
+      q.dst.seq_id[row] = seq_id;
     }
   }
-  float v[8], ss = 0.f;
+  float ss = 0.f;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) { v[k] = (float)e[k]; ss += v[k] * v[k]; }
-  ss = block_sum<NT / 64>(ss);
-  if (!mine) return;
-  const float r = 1.0f / sqrtf(ss / (float)q.d + q.eps);
-  const bf16x8 g = ((const bf16x8 *)q.g)[threadIdx.x];
-  bf16x8 o;
+  for (int k = 0; k < NV; ++k)
 #pragma unroll
-  for (int k = 0; k < 8; ++k) o[k] = (__bf16)(v[k] * r * (float)g[k]);
-  f32x4 *h = (f32x4 *)(q.h + (int64_t)row * q.d) + 2 * threadIdx.x;
-  h[0] = f32x4{v[0], v[1], v[2], v[3]};
-  h[1] = f32x4{v[4], v[5], v[6], v[7]};
-  ((bf16x8 *)(q.a + (int64_t)row * q.d))[threadIdx.x] = o;
+    for (int j = 0; j < 8; ++j) ss += (float)e[k][j] * (float)e[k][j];
+  ss = block_sum(ss, NT / 64);
+  const float r = __builtin_amdgcn_rsqf(ss * q.inv_d + q.eps);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int at = threadIdx.x + k * NT;
+    if (!mine[k]) continue;
+    bf16x8 o;
+    f32x4 h0, h1;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float v = (float)e[k][j];
+      o[j] = (__bf16)(v * r * (float)g[k][j]);
+      if (j < 4) h0[j] = v; else h1[j - 4] = v;
+    }
+    f32x4 *h = (f32x4 *)(q.h + (int64_t)row * q.d) + 2 * at;
+    h[0] = h0;
+    h[1] = h1;
+    ((bf16x8 *)(q.a + (int64_t)row * q.d))[at] = o;
+  }
 }
 
 // h[row] += sum_s parts[s][row]; a[row] = rmsnorm(h[row]) * g.  The slices are added up in slice order, their
@@ -108,12 +142,7 @@ __global__ __launch_bounds__(NV == 1 ? 512 : 1024) void resid_rmsnorm_kernel(flo
       for (int e = 0; e < 4; ++e) ss += v[it][e] * v[it][e];
     }
   }
-  __shared__ float red[16];
-  ss = wave_sum(ss);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  const int lane = threadIdx.x & 63;
-  ss = wave_sum(lane < waves ? red[lane] : 0.f);
+  ss = block_sum(ss, waves);
   const float r = __builtin_amdgcn_rsqf(ss * inv_d + eps);
 #pragma unroll
   for (int it = 0; it < NV; ++it) {
@@ -133,7 +162,7 @@ __global__ void rope_tables_kernel(const int32_t *pos, float *cs, int32_t *ctx_l
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n * half) return;
   const int row = idx / half, i = idx % half;
-  rope_angle(cs + (int64_t)row * hd, pos[row], i, hd, theta);
+  rope_angle(cs + (int64_t)row * hd, pos[row], i, hd, rope_freq(i, hd, theta));
   if (i == 0) ctx_len[row] = pos[row] + 1;
 }
 
@@ -252,12 +281,17 @@ static inline int ok() { return hipGetLastError() == hipSuccess ? 0 : -7; }
 
 int launch_step_begin(const StepBegin &q, const AttnParams &p, int cap, hipStream_t s) {
   if (p.n_seq <= 0) return 0;
-  if ((p.work && p.n_seq > 1024) || q.d > 8192 || ((uintptr_t)p.work & 31)) return -1;
-  // the work list needs 1024 threads; the rows of a pass no more than they have pieces (1536 wide: 1000 rows 11 us by 1024 threads, 3000 rows 14 by 256)
+  if ((p.work && p.n_seq > BEGIN_LIST) || q.d > 8192 || ((uintptr_t)p.work & 31)) return -1;
+  // the work list's threads; the rows of a pass no more than they have pieces (1536 wide: 1000 rows 11 us by 1024 threads, 3000 rows 14 by 256)
   auto launch = [&](auto kernel, int nt) { hipLaunchKernelGGL(kernel, dim3(p.n_seq + 1), dim3(nt), 0, s, q, p, cap); };
-  if (p.work || q.d > 4096) launch(step_begin_kernel<1024>, 1024);
-  else if (q.d > 2048) launch(step_begin_kernel<512>, 512);
-  else launch(step_begin_kernel<256>, 256);
+  if (q.d > 4096) launch(step_begin_kernel<512, 2>, 512);
+  else if (p.work || q.d > 2048) launch(step_begin_kernel<512, 1>, 512);
+  else launch(step_begin_kernel<256, 1>, 256);
+  return ok();
+}
+
+int launch_rope_freqs(double *freqs, int hd, float theta, hipStream_t s) {
+  hipLaunchKernelGGL(rope_freqs_kernel, dim3(1), dim3(hd / 2), 0, s, freqs, hd, theta);
   return ok();
 }
 

@@ -228,9 +228,11 @@ struct StepBegin {
   float *h, *cs;
   bf16_t *a;
   int32_t *ctx_len;
+  const double *freqs;      // [hd / 2] rotary frequencies (launch_rope_freqs)
   int32_t d, vocab;
-  float eps, theta;
+  float inv_d, eps;         // inv_d: 1 / d
 };
+int launch_rope_freqs(double *freqs, int hd, float theta, hipStream_t s);
 int launch_step_begin(const StepBegin &q, const AttnParams &p, int cap, hipStream_t s);
 int launch_resid_rmsnorm(float *h, const float *parts, int splits, const bf16_t *g, bf16_t *a, int n,
                          int d, float eps, hipStream_t s);

@@ -156,6 +156,7 @@ struct pl_engine {
   // (what a copy into the buffer, or a fill of it, has to wait for)
   hipEvent_t ev_pre_buf[2] = {nullptr, nullptr};
   bool pre_buf_pending[2] = {false, false};
+  double *freqs = nullptr;   // rotary frequencies
   float *logits = nullptr;
   void *samp_ws = nullptr;
   int32_t *tok_h = nullptr;   // pinned: the sampler writes the step's tokens and log-probs there itself
@@ -358,6 +359,8 @@ int alloc_device(pl_engine *e) {
   if ((rc = alloc_work(e, e->wk[0], e->rows_cap, parts_elems(e->rows_cap), true))) return rc;
   e->ev_slot.resize(B);
   for (auto &ev : e->ev_slot) HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+  if ((rc = dev_alloc(&e->freqs, c.head_dim / 2))) return rc;
+  if (pl::launch_rope_freqs(e->freqs, c.head_dim, c.rope_theta, e->s_dec)) return fail(PL_E_HIP, "kernel launch failed");
   if ((rc = dev_alloc(&e->logits, (int64_t)B * c.vocab))) return rc;
   char *ws = nullptr;
   if ((rc = dev_alloc(&ws, pl::sample_workspace_bytes(B, c.vocab)))) return rc;
@@ -513,7 +516,7 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   if (!prefill) { sb.dst = w.meta(true); sb.updates = w.m_pairs(false); }
   sb.page_table = w.pt; sb.embed = embed; sb.g = c.n_layers ? layer_weights(e, 0).g1 : gf;
   sb.h = w.h; sb.cs = w.cs; sb.a = w.a; sb.ctx_len = w.ctx_len;
-  sb.d = d; sb.vocab = c.vocab; sb.eps = c.rms_eps; sb.theta = c.rope_theta;
+  sb.freqs = e->freqs; sb.d = d; sb.vocab = c.vocab; sb.inv_d = 1.f / (float)d; sb.eps = c.rms_eps;
   rc |= pl::launch_step_begin(sb, ap, w.attn_items, s);
   for (int l = 0; l < c.n_layers && !rc; ++l) {
     const LayerW lw = layer_weights(e, l);
@@ -901,7 +904,7 @@ void pl_destroy(pl_engine *e) {
     if (e->s_dec) (void)hipStreamSynchronize(e->s_dec);
     if (e->s_copy) (void)hipStreamSynchronize(e->s_copy);
     if (e->wk[1].stream) (void)hipStreamSynchronize(e->wk[1].stream);
-    void *dev[] = {e->wbuf[0], e->wbuf[1], e->kv_pool, e->logits, e->samp_ws};
+    void *dev[] = {e->wbuf[0], e->wbuf[1], e->kv_pool, e->freqs, e->logits, e->samp_ws};
     for (void *p : dev)
       if (p) (void)hipFree(p);
     void *hst[] = {e->pt_h, e->wk[0].meta_h, e->tok_h, e->lp_h, e->ring_h};
