@@ -39,6 +39,7 @@ __global__ void rope_freqs_kernel(double *freqs, int hd, float theta) { freqs[th
 template <int NT, int NV>   // NV: pieces of eight elements per thread
 __global__ __launch_bounds__(NT) void step_begin_kernel(StepBegin q, AttnParams p, int cap) {
   if (blockIdx.x == 0) {
+    if (q.time && threadIdx.x == 0) __hip_atomic_store(q.time, (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (NT < BEGIN_LIST || !p.work) return;   // a pass
     const int b = min((int)threadIdx.x, p.n_seq - 1);   // (no branch between the loads)
     int n_upd = 0, at = 0, page = 0;

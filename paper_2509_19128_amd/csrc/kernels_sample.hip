@@ -99,8 +99,14 @@ __device__ inline void finish_row(const SampleParams &p, int row, const Part &v)
   if (tok < 0) tok = v.besti;
   tok = min(max(tok, 0), p.vocab - 1);
   const float z = __fmul_rn(p.logits[(int64_t)row * p.vocab + tok], p.inv_t[row]);
-  p.token[row] = tok;
-  p.logprob[row] = (z - v.mx) - logf(v.sum);
+  const float lp = (z - v.mx) - logf(v.sum);
+  if (p.results) {   // the host is waiting for these words
+    __hip_atomic_store(&p.results[row].time, (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&p.results[row].token_logprob, (uint64_t)__float_as_uint(lp) << 32 | (uint32_t)tok, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  } else {
+    p.token[row] = tok;
+    p.logprob[row] = lp;
+  }
   if (p.last_tok) p.last_tok[p.row_slot[row]] = tok;
 }
 

@@ -202,11 +202,16 @@ int launch_gemm_cfg(int cfg, const bf16_t *x, const bf16_t *w, void *y, float *w
                     int splits, int n_begin, int n_end, bool paired, bool cold, hipStream_t s);
 int gemm_pick_splits(int M, int N, int K);
 
+// A row's result as the host polls for it in pinned memory: both words differ from RESULT_PENDING once they have arrived.
+struct StepResult { uint64_t token_logprob, time; };   // token | log-prob's bits << 32; wall clock
+constexpr uint64_t RESULT_PENDING = ~(uint64_t)0;
+constexpr double WALL_CLOCK_MS = 1e-5;   // of a tick of the constant clock (100 MHz)
 struct SampleParams {
   const float *logits; int32_t n, vocab;
   const uint64_t *seq_id; const int32_t *position; const float *inv_t; const int32_t *forced;
   uint64_t seed; int32_t *token; float *logprob; void *workspace;
   int32_t *last_tok; const int32_t *row_slot;   // optional: last_tok[row_slot[row]] = token
+  StepResult *results;      // optional, instead of token and logprob
 };
 int64_t sample_workspace_bytes(int n, int vocab);
 int launch_sample(const SampleParams &p, hipStream_t s);
@@ -231,6 +236,7 @@ struct StepBegin {
   const double *freqs;      // [hd / 2] rotary frequencies (launch_rope_freqs)
   int32_t d, vocab;
   float inv_d, eps;         // inv_d: 1 / d
+  uint64_t *time;           // null, or where the wall clock goes when the step begins (host)
 };
 int launch_rope_freqs(double *freqs, int hd, float theta, hipStream_t s);
 int launch_step_begin(const StepBegin &q, const AttnParams &p, int cap, hipStream_t s);
