@@ -29,17 +29,27 @@ __device__ inline void rope_angle(float *cs, int pos, int i, int hd, double freq
 }
 __global__ void rope_freqs_kernel(double *freqs, int hd, float theta) { freqs[threadIdx.x] = rope_freq(threadIdx.x, hd, theta); }
 
+__device__ inline uint64_t pass_word(uint64_t mark) { return mark << PASS_CLOCK_BITS | ((uint64_t)wall_clock64() & PASS_CLOCK); }
+// The end of a pass: its mark goes to the host, who may be waiting for it.
+__global__ void pass_end_kernel(const uint64_t *mark_at, uint64_t *word) {
+  __hip_atomic_store(word, pass_word(*mark_at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The beginning of a step or pass, one launch: everything the layers need that depends on the metadata alone.
-// Workgroup 0 applies a decode step's page-table changes and builds the attention work list; workgroup r + 1 brings
-// row r: its metadata (read from the host's pinned image in a decode step, where a copy would be a launch of its
-// own ahead of this one), cos/sin of its position, h = E[token], a = rmsnorm(h) * g.
+// Workgroup 0 applies a decode step's page-table changes (a pass's: brings its slot's pages and its groups of rows) and builds the attention work
+// list; workgroup r + 1 brings row r: its metadata (read from the host's pinned image in a decode step and in a pass that its caller waits for,
+// where a copy would be a launch of its own ahead of this one), cos/sin of its position, h = E[token], a = rmsnorm(h) * g.
 // Bound by latency: one round trip to the host's memory (all of what a thread wants from there at once), one to the table or the row, the row's sum.
 // Decode steps, the frequencies' powers taken anew, scans through LDS and 1024 threads: 4 rows of the tiny shape 6.3 us, 64 of the 1.5B shape 7.6, 256 of the
 // 7B shape 13.1; now 4.1, 5.2 and 7.4.
 template <int NT, int NV>   // NV: pieces of eight elements per thread
 __global__ __launch_bounds__(NT) void step_begin_kernel(StepBegin q, AttnParams p, int cap) {
   if (blockIdx.x == 0) {
-    if (q.time && threadIdx.x == 0) __hip_atomic_store(q.time, (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (q.time && threadIdx.x == 0)
+      __hip_atomic_store(q.time, q.mark_at ? pass_word(q.mark) : (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (q.mark_at && threadIdx.x == 0) *q.mark_at = q.mark;
+    for (int i = threadIdx.x; i < q.n_pairs; i += NT) q.pairs_dst[i] = q.pairs_src[i];
+    for (int i = threadIdx.x; i < q.n_table; i += NT) q.table_dst[i] = q.table_src[i];
     if (NT < BEGIN_LIST || !p.work) return;   // a pass
     const int b = min((int)threadIdx.x, p.n_seq - 1);   // (no branch between the loads)
     int n_upd = 0, at = 0, page = 0;
@@ -288,6 +298,11 @@ int launch_step_begin(const StepBegin &q, const AttnParams &p, int cap, hipStrea
   if (q.d > 4096) launch(step_begin_kernel<512, 2>, 512);
   else if (p.work || q.d > 2048) launch(step_begin_kernel<512, 1>, 512);
   else launch(step_begin_kernel<256, 1>, 256);
+  return ok();
+}
+
+int launch_pass_end(const uint64_t *mark_at, uint64_t *word, hipStream_t s) {
+  hipLaunchKernelGGL(pass_end_kernel, dim3(1), dim3(1), 0, s, mark_at, word);
   return ok();
 }
 

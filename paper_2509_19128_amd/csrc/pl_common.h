@@ -237,7 +237,16 @@ struct StepBegin {
   int32_t d, vocab;
   float inv_d, eps;         // inv_d: 1 / d
   uint64_t *time;           // null, or where the wall clock goes when the step begins (host)
+  // A pass that fetches everything itself: rows of pairs and of the page table as the host has them, and a mark that launch_pass_end hands on.
+  const int32_t *pairs_src, *table_src;   // null: they are on the device already
+  int32_t *pairs_dst, *table_dst;
+  int32_t n_pairs, n_table;
+  uint64_t mark, *mark_at;                // mark_at: device
 };
+// Words of a pass in the host's memory: its mark's low bits above the wall clock's.
+constexpr int PASS_CLOCK_BITS = 40;
+constexpr uint64_t PASS_CLOCK = ((uint64_t)1 << PASS_CLOCK_BITS) - 1;
+int launch_pass_end(const uint64_t *mark_at, uint64_t *word, hipStream_t s);
 int launch_rope_freqs(double *freqs, int hd, float theta, hipStream_t s);
 int launch_step_begin(const StepBegin &q, const AttnParams &p, int cap, hipStream_t s);
 int launch_resid_rmsnorm(float *h, const float *parts, int splits, const bf16_t *g, bf16_t *a, int n,

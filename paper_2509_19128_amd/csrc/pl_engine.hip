@@ -14,6 +14,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -163,8 +164,14 @@ struct pl_engine {
   double *freqs = nullptr;   // rotary frequencies
   float *logits = nullptr;
   void *samp_ws = nullptr;
-  // pinned: the sampler writes the step's tokens and log-probs there itself, and when they were ready; behind the rows, when the step began
+  // pinned: the sampler writes the step's tokens and log-probs there itself, and when they were ready; behind the rows, when the step began, and
+  // the words of the last pass (its end and its beginning)
   pl::StepResult *res_h = nullptr;
+  uint64_t *pass_mark_d = nullptr;   // mark of the pass that runs
+  uint64_t pass_mark = 0;            // of the last one enqueued
+  bool poll = true;                  // such words arrive
+  uint64_t &pass_end_word() { return res_h[cfg.max_batch].token_logprob; }
+  uint64_t &pass_begin_word() { return res_h[cfg.max_batch + 1].time; }
   int32_t *tok_h = nullptr;   // the fp32 test build's
   float *lp_h = nullptr;
   int attn_chunk = 1024, attn_max_chunks = 1;
@@ -366,6 +373,7 @@ int alloc_device(pl_engine *e) {
   e->ev_slot.resize(B);
   for (auto &ev : e->ev_slot) HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
   if ((rc = dev_alloc(&e->freqs, c.head_dim / 2))) return rc;
+  if ((rc = dev_alloc(&e->pass_mark_d, 1))) return rc;
   if (pl::launch_rope_freqs(e->freqs, c.head_dim, c.rope_theta, e->s_dec)) return fail(PL_E_HIP, "kernel launch failed");
   if ((rc = dev_alloc(&e->logits, (int64_t)B * c.vocab))) return rc;
   char *ws = nullptr;
@@ -414,7 +422,8 @@ int alloc_device(pl_engine *e) {
   // exactly 0, and 0 * finite stays 0.
   HIP_TRY(hipMemsetAsync(e->kv_pool, 0, (size_t)pool_elems * e->esz, e->s_dec));
   HIP_TRY(hipHostMalloc((void **)&e->pt_h, (size_t)B * e->pages_per_seq * 4, hipHostMallocDefault));
-  HIP_TRY(hipHostMalloc((void **)&e->res_h, (size_t)(B + 1) * sizeof(pl::StepResult), hipHostMallocDefault));
+  HIP_TRY(hipHostMalloc((void **)&e->res_h, (size_t)(B + 2) * sizeof(pl::StepResult), hipHostMallocDefault));
+  memset((void *)e->res_h, 0, (size_t)(B + 2) * sizeof(pl::StepResult));
   HIP_TRY(hipHostMalloc((void **)&e->tok_h, (size_t)B * 4, hipHostMallocDefault));
   HIP_TRY(hipHostMalloc((void **)&e->lp_h, (size_t)B * 4, hipHostMallocDefault));
   memset(e->pt_h, 0, (size_t)B * e->pages_per_seq * 4);
@@ -487,7 +496,46 @@ int enqueue_step_f32(pl_engine *e, pl_engine::Work &w, int n, bool prefill) {
   return rc ? fail(PL_E_HIP, "kernel launch failed: %s", hipGetErrorString(hipGetLastError())) : PL_OK;
 }
 
-// prefill: cache-only pass; only the keys and values the rows leave in the cache are wanted, so the
+pl::AttnParams attention_params(pl_engine *e, pl_engine::Work &w, int n, bool prefill) {
+  const pl_model_cfg &c = e->cfg;
+  pl::AttnParams ap{};
+  ap.page_table = w.pt; ap.ctx_len = w.ctx_len; ap.row_slot = w.m_row_slot(true);
+  ap.out = w.attn_out; ap.part_o = w.attn_po; ap.part_ml = w.attn_pml;
+  ap.n_seq = n; ap.Hq = c.n_q_heads; ap.Hkv = c.n_kv_heads; ap.hd = c.head_dim;
+  ap.page_tokens = e->page_tokens; ap.pages_per_seq = e->pages_per_seq; ap.chunk = e->attn_chunk;
+  ap.max_chunks = e->attn_max_chunks; ap.item_tokens = w.attn_split ? pl::ATTN_SUB : e->attn_chunk;
+  const bool rows_share = prefill && !w.attn_apart;
+  ap.work = rows_share ? nullptr : w.attn_work; ap.tickets = pl::attention_tickets(e->attn_max_chunks) ? w.attn_tickets : nullptr;
+  ap.merge = w.attn_merge; ap.first_item = w.attn_first; ap.max_items = w.attn_items;
+  if (prefill) ap.groups = w.m_pairs(true);
+  return ap;
+}
+
+// The kernel that begins a step or pass.  slot >= 0: a pass over rows of this slot alone fetches its metadata and the slot's pages from the host's memory by
+// itself; other passes find theirs on the device.
+int enqueue_begin(pl_engine *e, pl_engine::Work &w, int n, bool prefill, int slot = -1) {
+  const pl_model_cfg &c = e->cfg;
+  const bf16_t *base = (const bf16_t *)e->wbuf[e->active_buf];
+  pl::StepBegin sb{};
+  sb.src = w.meta(prefill && slot < 0);   // a decode step's metadata is fetched from the host's image
+  if (!prefill) { sb.dst = w.meta(true); sb.updates = w.m_pairs(false); sb.time = &e->res_h[c.max_batch].time; }
+  sb.page_table = w.pt; sb.embed = base + e->layout.front().offset;
+  sb.g = c.n_layers ? layer_weights(e, 0).g1 : base + e->layout[e->layout.size() - 2].offset;
+  sb.h = w.h; sb.cs = w.cs; sb.a = w.a; sb.ctx_len = w.ctx_len;
+  sb.freqs = e->freqs; sb.d = c.d_model; sb.vocab = c.vocab; sb.inv_d = 1.f / (float)c.d_model; sb.eps = c.rms_eps;
+  if (prefill) { sb.mark = ++e->pass_mark; sb.mark_at = e->pass_mark_d; }
+  if (slot >= 0) {
+    sb.dst = w.meta(true);
+    sb.time = &e->pass_begin_word();
+    sb.pairs_src = w.m_pairs(false); sb.pairs_dst = w.m_pairs(true);
+    sb.n_pairs = w.attn_apart ? 0 : 2 + 2 * sb.pairs_src[0];
+    sb.table_src = e->pt_h + (int64_t)slot * e->pages_per_seq; sb.table_dst = w.pt + (int64_t)slot * e->pages_per_seq;
+    sb.n_table = e->pages_per_seq;
+  }
+  return pl::launch_step_begin(sb, attention_params(e, w, n, prefill), w.attn_items, w.stream);
+}
+
+// prefill: cache-only pass (behind its beginning, which is launched by itself); only the keys and values the rows leave in the cache are wanted, so the
 // last layer stops after its append and there is no LM head or sampler.  Runs on the work set's stream.
 int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) {
   const pl_model_cfg &c = e->cfg;
@@ -497,7 +545,6 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   if (timed) { e->prof_n = 0; mark(e, CAT_OTHER); }
   const bf16_t *base = (const bf16_t *)e->wbuf[e->active_buf];
   const int d = c.d_model, qd = c.n_q_heads * c.head_dim, kvd = c.n_kv_heads * c.head_dim, wq = qd + 2 * kvd;
-  const bf16_t *embed = base + e->layout.front().offset;
   const bf16_t *gf = base + e->layout[e->layout.size() - 2].offset;
   const bf16_t *lm = base + e->layout.back().offset;
   int rc = 0;
@@ -507,24 +554,11 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
     return fold ? pl::launch_gemm_pass(x, wt, y, ws, w.parts_elems, n, N, K, mode, ks, cold, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, cold, s);
   };
   auto slices = [&](const pl::GemmSplit &ks, int N, int K) { return fold ? pl::gemm_pass_slices(n, N, K, ks) : ks.splits; };
-  pl::AttnParams ap{};
-  ap.page_table = w.pt; ap.ctx_len = w.ctx_len; ap.row_slot = w.m_row_slot(true);
-  ap.out = w.attn_out; ap.part_o = w.attn_po; ap.part_ml = w.attn_pml;
-  ap.n_seq = n; ap.Hq = c.n_q_heads; ap.Hkv = c.n_kv_heads; ap.hd = c.head_dim;
-  ap.page_tokens = e->page_tokens; ap.pages_per_seq = e->pages_per_seq; ap.chunk = e->attn_chunk;
-  ap.max_chunks = e->attn_max_chunks; ap.item_tokens = w.attn_split ? pl::ATTN_SUB : e->attn_chunk;
+  pl::AttnParams ap = attention_params(e, w, n, prefill);
   const bool rows_share = prefill && !w.attn_apart;
-  ap.work = rows_share ? nullptr : w.attn_work; ap.tickets = pl::attention_tickets(e->attn_max_chunks) ? w.attn_tickets : nullptr; ap.merge = w.attn_merge; ap.first_item = w.attn_first; ap.max_items = w.attn_items;
-  if (prefill) ap.groups = w.m_pairs(true);
   // (the rows of a pass attend to one another: all their keys and values are appended first)
   const bool rotates = !prefill && w.attn_rotate;
-  pl::StepBegin sb{};
-  sb.src = w.meta(prefill);   // a pass's metadata is on the device already, a decode step's is fetched from the host's image
-  if (!prefill) { sb.dst = w.meta(true); sb.updates = w.m_pairs(false); sb.time = &e->res_h[c.max_batch].time; }
-  sb.page_table = w.pt; sb.embed = embed; sb.g = c.n_layers ? layer_weights(e, 0).g1 : gf;
-  sb.h = w.h; sb.cs = w.cs; sb.a = w.a; sb.ctx_len = w.ctx_len;
-  sb.freqs = e->freqs; sb.d = d; sb.vocab = c.vocab; sb.inv_d = 1.f / (float)d; sb.eps = c.rms_eps;
-  rc |= pl::launch_step_begin(sb, ap, w.attn_items, s);
+  if (!prefill) rc |= enqueue_begin(e, w, n, false);
   for (int l = 0; l < c.n_layers && !rc; ++l) {
     const LayerW lw = layer_weights(e, l);
     bf16_t *kv_layer = (bf16_t *)e->kv_pool + (int64_t)l * e->layer_stride;
@@ -561,6 +595,7 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
     const bf16_t *g_next = (l + 1 < c.n_layers) ? layer_weights(e, l + 1).g1 : gf;
     rc |= pl::launch_resid_rmsnorm(w.h, w.parts, slices(e->ks_d, d, c.d_ffn), g_next, w.a, n, d, c.rms_eps, s);
   }
+  if (prefill) rc |= pl::launch_pass_end(e->pass_mark_d, &e->pass_end_word(), s);
   if (prefill) return rc ? fail(PL_E_HIP, "kernel launch failed: %s", hipGetErrorString(hipGetLastError())) : PL_OK;
   mark(e, CAT_OTHER);
   rc |= pl::launch_gemm(w.a, lm, e->logits, nullptr, n, c.vocab, d, 0, e->ks_lm, cold, s);
@@ -586,13 +621,16 @@ void drop_graph(pl_engine::StepGraph &g) {
 // Run the kernels of a decode step (or of a cache-only pass) for n rows on the work set's stream: as
 // the replay of a captured graph when one may be used (no per-kernel timers on the decode step), launch
 // by launch otherwise.
-int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) {
-  if (!e->use_graphs || (!prefill && e->profile != 0)) return enqueue_step(e, w, n, prefill);
+int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false, int slot = -1) {
+  const bool replay = e->use_graphs && (prefill || e->profile == 0);
   const int set = prefill ? 1 : 0;
   // grid bound of the attention kernel in coarse steps, so that few shapes occur; workgroups beyond
   // the lists' real lengths (which the kernels read from device memory) leave at once.  Never more than the list holds
   // (a pass whose rows share what they read has no list, but at most as many groups as rows).
-  w.attn_items = (int)std::min<int64_t>((w.attn_items + 63) / 64 * 64, prefill && !w.attn_apart ? w.rows_cap : w.items_cap);
+  if (replay) w.attn_items = (int)std::min<int64_t>((w.attn_items + 63) / 64 * 64, prefill && !w.attn_apart ? w.rows_cap : w.items_cap);
+  // (a pass begins outside its graph: what it reads is somewhere else each time, and the device starts on it while the rest is enqueued)
+  if (prefill && !e->f32 && enqueue_begin(e, w, n, true, slot)) return fail(PL_E_HIP, "kernel launch failed: %s", hipGetErrorString(hipGetLastError()));
+  if (!replay) return enqueue_step(e, w, n, prefill);
   pl_engine::StepGraph *g = nullptr;
   for (auto &x : e->graphs)
     if (x.n == n && x.buf == e->active_buf && x.items == w.attn_items && x.split == w.attn_split && x.merge == w.attn_merge && x.apart == w.attn_apart &&
@@ -629,27 +667,42 @@ int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) {
   return PL_OK;
 }
 
-// Waits until a step's n results are in the host's memory.  Polling for the words that the kernels write is 13 us faster than events around the step and
+// Waits until words that kernels write are in the host's memory (a step's n results).  Polling for the words that the kernels write is 13 us faster than events around the step and
 // hipStreamSynchronize (17 kernels of a graph: 49.6 -> 36.4 us; tiny shape, a step 76 -> 55).  Steps of more than POLL_MS wait for the stream, which is
 // also how an error of the device ends the wait; and one step in SYNC_STEPS is taken with events as before, as the runtime gives back what a
 // launch took only at a synchronisation.
 constexpr double POLL_MS = 4;
 constexpr uint64_t SYNC_STEPS = 32;
-int wait_results(pl_engine *e, int n) {
-  auto here = [](const pl::StepResult &x) {
-    return __atomic_load_n(&x.token_logprob, __ATOMIC_ACQUIRE) != pl::RESULT_PENDING && __atomic_load_n(&x.time, __ATOMIC_ACQUIRE) != pl::RESULT_PENDING;
-  };
+template <typename F>   // arrived(): everything waited for is there
+int wait_words(pl_engine *e, hipStream_t s, bool synchronise, F arrived) {
   const double limit = now_ms() + POLL_MS;
-  int r = 0;
-  for (unsigned spins = 1; r < n; ++spins) {
-    if (here(e->res_h[r])) { ++r; continue; }
+  for (unsigned spins = 1; e->poll && !synchronise && !arrived(); ++spins) {
 #if defined(__x86_64__)
     __builtin_ia32_pause();
 #endif
     if (spins % 256 == 0 && now_ms() > limit) break;
   }
-  if (r == n && __atomic_load_n(&e->res_h[e->cfg.max_batch].time, __ATOMIC_ACQUIRE) != pl::RESULT_PENDING) return PL_OK;
-  HIP_TRY(hipStreamSynchronize(e->s_dec));
+  if (e->poll && !synchronise && arrived()) return PL_OK;
+  HIP_TRY(hipStreamSynchronize(s));
+  e->poll = arrived();   // (words that do not come are not waited for again)
+  return PL_OK;
+}
+int wait_results(pl_engine *e, int n) {
+  int r = 0;
+  return wait_words(e, e->s_dec, false, [&] {
+    for (; r < n; ++r)
+      if (__atomic_load_n(&e->res_h[r].token_logprob, __ATOMIC_ACQUIRE) == pl::RESULT_PENDING || __atomic_load_n(&e->res_h[r].time, __ATOMIC_ACQUIRE) == pl::RESULT_PENDING)
+        return false;
+    return __atomic_load_n(&e->res_h[e->cfg.max_batch].time, __ATOMIC_ACQUIRE) != pl::RESULT_PENDING;
+  });
+}
+// Waits for the pass enqueued last, by its mark.  What was enqueued before it on its stream has ended too.
+int wait_pass(pl_engine *e, double *ms) {
+  auto in = [&](const uint64_t &word) { return __atomic_load_n(&word, __ATOMIC_ACQUIRE) >> pl::PASS_CLOCK_BITS == (e->pass_mark & (~(uint64_t)0 >> pl::PASS_CLOCK_BITS)); };
+  auto both = [&] { return in(e->pass_end_word()) && in(e->pass_begin_word()); };
+  const int rc = wait_words(e, e->wk[1].stream, e->pass_mark % SYNC_STEPS == 0, both);
+  if (rc) return rc;
+  if (both()) *ms += (double)((e->pass_end_word() - e->pass_begin_word()) & pl::PASS_CLOCK) * pl::WALL_CLOCK_MS;
   return PL_OK;
 }
 
@@ -780,9 +833,10 @@ int drain_passes(pl_engine *e) {
 // Cache-only passes: rows (slot, position, token) go through the decode kernels in prefill mode, in
 // groups of up to rows_max (no more than pass_rows), on the second work set's stream; the rows of one slot must come in position
 // order, because a row attends to the keys and values that earlier rows of its slot (in this or an
-// earlier group) leave.  Returns once everything is enqueued; the caller waits (or records an event).
+// earlier group) leave.  Returns once everything is enqueued; the caller waits (or records an event).  wait: the rows are of one slot and
+// fit one pass, and have been read when the call returns.
 int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::vector<int32_t> &positions,
-                  const std::vector<int32_t> &tokens, int rows_max, double *ms_total, uint64_t *passes) {
+                  const std::vector<int32_t> &tokens, int rows_max, double *ms_total, uint64_t *passes, bool wait = false) {
   const pl_model_cfg &c = e->cfg;
   pl_engine::Work &w = e->wk[1];
   if (!e->dry) HIP_TRY(hipSetDevice(c.device));
@@ -823,6 +877,13 @@ int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::ve
       w.attn_items = w.attn_apart ? chunks : items;
       w.attn_merge = w.attn_apart && chunks > n && !pl::attention_tickets(e->attn_max_chunks);
       hipStream_t s = w.stream;
+      if (wait) {   // one pass over one slot's rows: no copies ahead of it, no events around it
+        int rc = run_step(e, w, n, true, slots[0]);
+        if (!rc) rc = wait_pass(e, ms_total);
+        if (rc) return rc;
+        ++*passes;
+        return PL_OK;
+      }
       // The page table goes up on this stream into this set's own device copy (no device buffer is ever
       // written from two streams); the rows of the slots being read do not change while they are read.
       // The dirty flag stays: the decode stream sends the table to its own copy.
@@ -935,7 +996,7 @@ void pl_destroy(pl_engine *e) {
     if (e->s_dec) (void)hipStreamSynchronize(e->s_dec);
     if (e->s_copy) (void)hipStreamSynchronize(e->s_copy);
     if (e->wk[1].stream) (void)hipStreamSynchronize(e->wk[1].stream);
-    void *dev[] = {e->wbuf[0], e->wbuf[1], e->kv_pool, e->freqs, e->logits, e->samp_ws};
+    void *dev[] = {e->wbuf[0], e->wbuf[1], e->kv_pool, e->freqs, e->pass_mark_d, e->logits, e->samp_ws};
     for (void *p : dev)
       if (p) (void)hipFree(p);
     void *hst[] = {e->pt_h, e->wk[0].meta_h, e->res_h, e->tok_h, e->lp_h, e->ring_h};
@@ -1408,7 +1469,7 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
 
 // Enqueue the reading of a slot's prompt (all positions not read yet, except the last) on the
 // cache-only stream; the slot is marked as reading and its event recorded.
-static int start_prefill(pl_engine *e, int32_t slot, int rows_max, int32_t *out_positions) {
+static int start_prefill(pl_engine *e, int32_t slot, int rows_max, bool wait, int32_t *out_positions) {
   if (out_positions) *out_positions = 0;
   if (!e->loaded) return fail(PL_E_STATE, "no weights loaded");
   const pl_model_cfg &c = e->cfg;
@@ -1419,15 +1480,16 @@ static int start_prefill(pl_engine *e, int32_t slot, int rows_max, int32_t *out_
   if (first >= last) return PL_OK;
   if ((int)q.prompt.size() < q.n_prompt) return fail(PL_E_STATE, "slot %d holds no prompt", slot);
   if ((int64_t)q.pages.size() * e->page_tokens < last) return fail(PL_E_STATE, "slot %d has no pages for its prompt", slot);
-  std::vector<int32_t> slots(last - first, slot), positions, tokens;
-  for (int p = first; p < last; ++p) { positions.push_back(p); tokens.push_back(q.prompt[p]); }
-  int rc = run_kv_passes(e, slots, positions, tokens, rows_max, &e->st.prefill_ms, &e->st.prefill_passes);
+  wait &= !e->dry && !e->f32 && last - first <= rows_max;
+  std::vector<int32_t> slots(last - first, slot), positions(last - first), tokens(q.prompt.begin() + first, q.prompt.begin() + last);
+  std::iota(positions.begin(), positions.end(), first);
+  int rc = run_kv_passes(e, slots, positions, tokens, rows_max, &e->st.prefill_ms, &e->st.prefill_passes, wait);
   if (rc) return rc;
-  if (!e->dry) HIP_TRY(hipEventRecord(e->ev_slot[slot], e->wk[1].stream));
+  if (!e->dry && !wait) HIP_TRY(hipEventRecord(e->ev_slot[slot], e->wk[1].stream));
   e->st.prefill_positions += last - first;
   if (q.hist_known) q.hist.insert(q.hist.end(), tokens.begin(), tokens.end());
   q.pos = last;
-  q.reading = true;
+  q.reading = !wait;
   if (out_positions) *out_positions = last - first;
   return PL_OK;
 }
@@ -1437,7 +1499,7 @@ int pl_prefill(pl_engine *e, int32_t slot, int32_t *out_positions) {
   // a slot whose prompt is already being read in the background: nothing is left to read, wait for it
   const bool already = slot >= 0 && slot < e->cfg.max_batch && e->seqs[slot].active && e->seqs[slot].reading;
   if (already && out_positions) *out_positions = 0;
-  int rc = already ? PL_OK : start_prefill(e, slot, e->pass_rows, out_positions);
+  int rc = already ? PL_OK : start_prefill(e, slot, e->pass_rows, true, out_positions);
   if (rc) return rc;
   Seq &q = e->seqs[slot];
   if (q.reading) {
@@ -1453,7 +1515,7 @@ int pl_prefill(pl_engine *e, int32_t slot, int32_t *out_positions) {
 
 int pl_prefill_async(pl_engine *e, int32_t slot, int32_t *out_positions) {
   if (!e) return fail(PL_E_INVAL, "NULL argument");
-  return start_prefill(e, slot, std::min(e->pass_rows, BACKGROUND_ROWS), out_positions);
+  return start_prefill(e, slot, std::min(e->pass_rows, BACKGROUND_ROWS), false, out_positions);
 }
 
 int pl_get_stats(pl_engine *e, pl_stats *out) {
