@@ -491,11 +491,11 @@ __global__ __launch_bounds__(256, ROTATE ? 3 : 2) void attn_decode_kernel(AttnPa
 }
 
 // Merge of rows that span several items, where the decode kernel does not do it itself: one workgroup per (row, query head), four output
-// elements per thread.  Latency bound (a few KiB per thread group): the loads of 16 parts are issued together, no branch between them (19
+// elements per thread.  Latency bound (a few KiB per thread group): the loads of PARTS parts are issued together, no branch between them (19
 // rows of 7300 tokens, 7B shape, 8.0 -> 6.6 us).
 // SUBS: items are subs.  Two chunks at a time, HD threads for each; thread group w of a chunk folds wavefront w's subs, then the four
 // wavefronts are merged as the decode kernel does it and the chunks folded in order.
-template <int HD, bool SUBS>
+template <int HD, bool SUBS, int PARTS>
 __global__ __launch_bounds__(SUBS ? 2 * HD : 64) void attn_merge_kernel(AttnParams p) {
   constexpr int QUADS = HD / 4;
   const int b = blockIdx.y, hq = blockIdx.x, at = threadIdx.x % HD, w = at / QUADS, d = at % QUADS * 4;
@@ -507,20 +507,20 @@ __global__ __launch_bounds__(SUBS ? 2 * HD : 64) void attn_merge_kernel(AttnPara
   f32x4 O = {0.f, 0.f, 0.f, 0.f};
   // fold of n parts, part i at index at(i)
   auto fold_parts = [&](float &m, float &l, f32x4 &o, int n, int ml_floats, auto index) {
-    for (int j0 = 0; j0 < n; j0 += 16) {
-      float2 ml[16];
-      f32x4 o16[16];
+    for (int j0 = 0; j0 < n; j0 += PARTS) {
+      float2 ml[PARTS];
+      f32x4 op[PARTS];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
+      for (int u = 0; u < PARTS; ++u) {
         const int64_t part = index(min(j0 + u, n - 1));
         ml[u] = *(const float2 *)(p.part_ml + part * ml_floats + h * 2);
-        o16[u] = *(const f32x4 *)(p.part_o + (part * G + h) * HD + d);
+        op[u] = *(const f32x4 *)(p.part_o + (part * G + h) * HD + d);
       }
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {   // (selects, not branches: parts beyond the last change nothing)
-        float m1 = m, l1 = l;
+      for (int u = 0; u < PARTS; ++u) {
+        float m1 = m, l1 = l;   // (selects, not branches: parts beyond the last change nothing)
         f32x4 o1 = o;
-        fold_part(m1, l1, o1, ml[u].x, ml[u].y, o16[u]);
+        fold_part(m1, l1, o1, ml[u].x, ml[u].y, op[u]);
         const bool in = j0 + u < n;
         m = in ? m1 : m;
         l = in ? l1 : l;
@@ -840,8 +840,11 @@ static void launch_attention_hd(const AttnParams &p, hipStream_t s, int part) {
       });
   }
   if (part != 1 && p.merge) {
-    if (p.item_tokens < p.chunk) hipLaunchKernelGGL((attn_merge_kernel<HD, true>), dim3(p.Hq, p.n_seq), dim3(2 * HD), 0, s, p);
-    else hipLaunchKernelGGL((attn_merge_kernel<HD, false>), dim3(p.Hq, p.n_seq), dim3(64), 0, s, p);
+    // (whole chunks: 101 sequences of at most two, head dimension 32, 2.7 us a call by 16 parts at a time, 2.5 by four; three of up to 128 5.4 by 16, 6.4
+    // by 16 with a branch for each)
+    if (p.item_tokens < p.chunk) hipLaunchKernelGGL((attn_merge_kernel<HD, true, 16>), dim3(p.Hq, p.n_seq), dim3(2 * HD), 0, s, p);
+    else if (p.max_chunks <= 4) hipLaunchKernelGGL((attn_merge_kernel<HD, false, 4>), dim3(p.Hq, p.n_seq), dim3(64), 0, s, p);
+    else hipLaunchKernelGGL((attn_merge_kernel<HD, false, 16>), dim3(p.Hq, p.n_seq), dim3(64), 0, s, p);
   }
 }
 
