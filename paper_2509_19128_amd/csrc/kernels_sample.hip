@@ -94,11 +94,9 @@ __device__ inline Part merge_wave(const Part &v) {
 }
 constexpr Part NO_PART = {-INFINITY, 0.f, -INFINITY, 0x7FFFFFFF};
 
-__device__ inline void finish_row(const SampleParams &p, int row, const Part &v) {
-  int tok = p.forced ? p.forced[row] : -1;
-  if (tok < 0) tok = v.besti;
-  tok = min(max(tok, 0), p.vocab - 1);
-  const float z = __fmul_rn(p.logits[(int64_t)row * p.vocab + tok], p.inv_t[row]);
+__device__ inline void finish_row(const SampleParams &p, int row, const Part &v, int forced, float inv_t) {
+  const int tok = min(max(forced < 0 ? v.besti : forced, 0), p.vocab - 1);
+  const float z = __fmul_rn(p.logits[(int64_t)row * p.vocab + tok], inv_t);
   const float lp = (z - v.mx) - logf(v.sum);
   if (p.results) {   // the host is waiting for these words
     __hip_atomic_store(&p.results[row].time, (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -128,9 +126,8 @@ constexpr float KEY_ERROR = 0.088f, KEY_SLACK = 0.004f;   // of log2: 0.0861 per
 constexpr int KEY_MOST = 25 << 23;                        // beyond any key of numbers: x <= 1, t >= 2^-24
 constexpr int SUM_LANES = 1024;
 constexpr float BOUND_MAX = 1024.f;
-template <int NT>
+template <int NT, bool ONE, int Q = SLICE / NT / 4>   // ONE: a row is one slice; Q: groups of four entries per thread (half of them: a row of half a slice)
 __global__ __launch_bounds__(NT) void sample_slice_kernel(SampleParams p, int nslice) {
-  constexpr int Q = SLICE / NT / 4;   // groups of four entries per thread
   constexpr int V = SUM_LANES / NT;   // lanes of the sum per thread: lane threadIdx.x + v * NT has groups v, v + V, ...
   constexpr int NW = NT / 64;
   const int row = blockIdx.y, sl = blockIdx.x;
@@ -139,6 +136,7 @@ __global__ __launch_bounds__(NT) void sample_slice_kernel(SampleParams p, int ns
   const uint64_t sid = p.seq_id[row];
   const uint32_t pos = (uint32_t)p.position[row];
   const uint32_t k0 = (uint32_t)p.seed, k1 = (uint32_t)(p.seed >> 32);
+  const int forced = ONE && p.forced ? p.forced[row] : -1;
   const int beg4 = sl * (SLICE / 4) + threadIdx.x, end4 = min(p.vocab, (sl + 1) * SLICE) / 4;   // vocab is a multiple of 4
   float z[Q][4];
   auto load = [&](auto WHOLE) {   // a whole slice asks for no end
@@ -150,7 +148,7 @@ __global__ __launch_bounds__(NT) void sample_slice_kernel(SampleParams p, int ns
       z[q][0] = v[0]; z[q][1] = v[1]; z[q][2] = v[2]; z[q][3] = v[3];
     }
   };
-  if ((sl + 1) * SLICE <= p.vocab) load(std::true_type{}); else load(std::false_type{});
+  if ((Q * NT * 4 == SLICE ? (sl + 1) * SLICE : Q * NT * 4) <= p.vocab) load(std::true_type{}); else load(std::false_type{});
   int key[Q][4];   // the bits of t, later the keys
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
@@ -239,7 +237,7 @@ __global__ __launch_bounds__(NT) void sample_slice_kernel(SampleParams p, int ns
   v.besty = wave_max(by);
   v.besti = wave_min(lane < NW && by == v.besty ? s_besti[lane] : 0x7FFFFFFF);
   if (threadIdx.x != 0) return;
-  if (nslice == 1) finish_row(p, row, v);   // the whole vocabulary: nothing to merge
+  if constexpr (ONE) finish_row(p, row, v, forced, inv_t);   // the whole vocabulary: nothing to merge
   else ((Part *)p.workspace)[(int64_t)row * nslice + sl] = v;
 }
 
@@ -248,6 +246,8 @@ __global__ __launch_bounds__(NT) void sample_slice_kernel(SampleParams p, int ns
 __global__ __launch_bounds__(64) void sample_merge_kernel(SampleParams p, int nslice) {
   const int row = blockIdx.x;
   const Part *pp = (const Part *)p.workspace + (int64_t)row * nslice;
+  const int forced = p.forced ? p.forced[row] : -1;
+  const float inv_t = p.inv_t[row];
   Part v = NO_PART;
   for (int s = threadIdx.x; s < nslice; s += 64) {
     const Part w = pp[s];
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(64) void sample_merge_kernel(SampleParams p, int ns
     merge_best(v.besty, v.besti, w.besty, w.besti);
   }
   v = merge_wave(v);
-  if (threadIdx.x == 0) finish_row(p, row, v);
+  if (threadIdx.x == 0) finish_row(p, row, v, forced, inv_t);
 }
 
 }  // namespace
@@ -307,10 +307,17 @@ int launch_sample(const SampleParams &p, hipStream_t s) {
   // the chain of a slice as long as all workgroups run at once (two per compute unit); beyond that, 32 entries per thread share the
   // fixed work (reductions, the scan for candidates) among more of them.  1024 and 256 threads, whole call: 512 x 4096 7.7 and 9.0 us,
   // 128 x 32000 10.5 and 12.7, 26 x 152064 10.1 both, 30 x 152064 11.1 and 10.3, 128 x 152064 26.6 and 21.4.
-  if ((int64_t)nslice * p.n <= 512)
-    hipLaunchKernelGGL(sample_slice_kernel<1024>, dim3(nslice, p.n), dim3(1024), 0, s, p, nslice);
-  else
-    hipLaunchKernelGGL(sample_slice_kernel<256>, dim3(nslice, p.n), dim3(256), 0, s, p, nslice);
+  // A vocabulary of half a slice or less: no thread takes a group that has no entries, and a row of one slice
+  // has its forced token before the draw (1 x 4096 4.2 -> 3.6 us, 64 x 4096 4.8 -> 4.2; the missing zeros of a sum change nothing).
+  auto launch = [&](auto kernel, int nt) { hipLaunchKernelGGL(kernel, dim3(nslice, p.n), dim3(nt), 0, s, p, nslice); };
+  const bool few = (int64_t)nslice * p.n <= 512;
+  if (p.vocab <= SLICE / 2) {
+    if (few) launch(sample_slice_kernel<1024, true, 1>, 1024); else launch(sample_slice_kernel<256, true, 4>, 256);
+  } else if (nslice == 1) {
+    if (few) launch(sample_slice_kernel<1024, true>, 1024); else launch(sample_slice_kernel<256, true>, 256);
+  } else {
+    if (few) launch(sample_slice_kernel<1024, false>, 1024); else launch(sample_slice_kernel<256, false>, 256);
+  }
   if (nslice > 1) hipLaunchKernelGGL(sample_merge_kernel, dim3(p.n), dim3(64), 0, s, p, nslice);
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }

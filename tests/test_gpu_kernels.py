@@ -559,6 +559,31 @@ def test_sampler_at_slice_and_launch_boundaries_with_masked_entries(n, V):
         assert abs(lp[r] - lp_ref) <= 1e-4 * max(1.0, abs(lp_ref))
 
 
+@pytest.mark.parametrize("n", [3, 513])
+@pytest.mark.parametrize("V", [4, 4092, 4096, 4100])
+def test_sampler_around_half_a_slice(n, V):
+    """Vocabularies of half a slice and a little more or less, on both sides of the choice of threads: the definition's
+    tokens, with the last entries drawn and forced and with masked rows; a vocabulary that ends in masked entries
+    gives the same bits as one without them."""
+    rng = np.random.default_rng(V + n)
+    logits = (rng.standard_normal((n, V)) * 3).astype(np.float32)
+    logits[0, -1] = 40.0
+    logits[1, : V - 2] = -np.inf
+    seq_id = rng.integers(0, 2**63, size=n, dtype=np.uint64)
+    pos = rng.integers(0, 16384, size=n).astype(np.int32)
+    temps = rng.choice([1.0, 0.7, 1.5], n).astype(np.float32)
+    forced = np.full(n, -1, np.int32)
+    forced[2] = V - 1
+    tok, lp = _gpu_sample(logits, seq_id, pos, temps, forced, 5)
+    for r in list(range(3)) + [n - 1]:
+        t_ref, lp_ref = sampler.sample_row(logits[r], float(temps[r]), 5, int(seq_id[r]), int(pos[r]), int(forced[r]))
+        assert tok[r] == t_ref, (r, tok[r], t_ref)
+        assert abs(lp[r] - lp_ref) <= 1e-4 * max(1.0, abs(lp_ref))
+    masked = np.concatenate([logits, np.full((n, 8192 - V), -np.inf, np.float32)], 1)
+    tok2, lp2 = _gpu_sample(masked, seq_id, pos, temps, forced, 5)
+    assert np.array_equal(tok, tok2) and np.array_equal(lp.view(np.uint32), lp2.view(np.uint32))
+
+
 @pytest.mark.parametrize("n,V", [(10, 8), (10, 8196), (60, 152064)])
 def test_sampler_where_bounds_say_little_or_nothing(n, V):
     """Rows in which the bounds on the noise decide little (one dominating logit, two far apart from the rest) and rows
