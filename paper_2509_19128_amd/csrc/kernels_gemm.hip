@@ -418,17 +418,23 @@ __global__ __launch_bounds__(256) void gemm_kernel(const bf16_t *__restrict__ X,
   gemm_tile<WM, WN, AT, BT, MODE, COLD>(xs, X, W, Yv, M, N, K, ksteps, n_base + ctile * BN, rtile * BM, split, n_end, ldy, y_col0);
 }
 
-// Many rows (prompt passes): flat grid in XCD-local groups of row tiles as above, all K slices of a tile in
-// one workgroup.  (128 x 256 tiles: the second set of accumulators leaves no register free and each fold moves 256; still the fastest where
-// launch_gemm_folded takes it: down product of the 32B shape, 1024 rows, 345 us, 480 with the best of 64- and 128-wide tiles.)
-template <int WM, int WN, int AT, int BT>
+// Many rows (prompt passes): all K slices of a tile in one workgroup (FOLD; one slice: the plain sum).
+// A flat grid of which the hardware deals consecutive ids to the 8 XCDs in turn: XCD i takes the i-th eighth of the tiles, so that all units
+// have the same number whatever the shape (groups of 8 column tiles gave 12 of them as 2 and 1 per XCD), column tile by column tile or, ROWS,
+// row tile by row tile: the order in which an eighth shares more of its operands.  us, groups of 8 column tiles -> so, same tiles: 1.5B O, 3000 rows,
+// 160 x 128 33.7 -> 19.8, 1.5B down, 3000 rows, 140 -> 88, 2000 rows, 96 x 128 94 -> 57; 7B QKV, 1024 rows, 160 x 128 56 -> 36; 3000 rows, 128 x 256 128 -> 101.
+// (128 x 256 tiles: the second set of accumulators leaves no register free and each fold moves 256; still the fastest where
+// launch_gemm_folded takes it: down product of the 32B shape, 1536 rows, 375 us, 418 with the best of the 128-wide tiles.)
+template <int WM, int WN, int AT, int BT, bool FOLD>
 __global__ __launch_bounds__(256) void gemm_fold_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
-                                                        void *__restrict__ Yv, int M, int N, int K, int ksteps, int nrow) {
+                                                        void *__restrict__ Yv, int M, int N, int K, int ksteps, int nrow, bool rows) {
   constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
   __shared__ __attribute__((aligned(1024))) bf16_t xs[Tile<WM, WN, AT, BT, false>::LDS];
-  const int rtile = (blockIdx.x >> 3) % nrow, ctile = (blockIdx.x / (8 * nrow)) * 8 + (blockIdx.x & 7);
-  if (ctile * BN >= N) return;   // padding of the flat grid (uniform for the workgroup)
-  gemm_tile<WM, WN, AT, BT, 0, false, true>(xs, X, W, Yv, M, N, K, ksteps, ctile * BN, rtile * BM, 0, N, N, 0);
+  const int ncol = (N + BN - 1) / BN, tiles = nrow * ncol, xcd = blockIdx.x & 7;
+  const int t = xcd * (tiles >> 3) + min(xcd, tiles & 7) + (blockIdx.x >> 3);
+  const int slow = t / (rows ? ncol : nrow), fast = t - slow * (rows ? ncol : nrow);
+  const int rtile = rows ? slow : fast, ctile = rows ? fast : slow;
+  gemm_tile<WM, WN, AT, BT, 0, false, FOLD>(xs, X, W, Yv, M, N, K, ksteps, ctile * BN, rtile * BM, 0, N, N, 0);
 }
 
 // Products of more 256 x 256 tiles than compute units: a workgroup of each takes tiles one after the other and loads the first
@@ -622,18 +628,19 @@ int launch_by_id(int cfg, const Launch &L) {
   }
 }
 
-// A plain product of many rows, K in `splits` slices added up in the workgroup (one slice:
-// the plain kernel, which needs no second set of accumulators).
+// A plain product of many rows, K in `splits` slices added up in the workgroup (one slice: no second set of accumulators).  An eighth of the tiles
+// reads all rows and an eighth of the columns or the other way round; the line between the orders lies where both take the same time (128 x 256 tiles, column /
+// row order: 7B O, 2000 / 3000 / 4096 rows 47.8 / 85.8 / 103.9 and 48.8 / 87.9 / 101.2 us; 32B QKV, 3000 rows, 216 and 239; 1.5B O, 3000 rows, 96 x 128, 23.1 and 20.5).
 template <int WM, int WN, int AT, int BT>
-int launch_fold_cfg(Launch L) {
+int launch_fold_cfg(const Launch &L) {
   constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
-  const int splits = L.splits;
-  L.splits = 1;
-  L.paired = true;
-  if (splits == 1) return launch_cfg<WM, WN, AT, BT>(L);
-  const int nrow = (L.M + BM - 1) / BM, grid = ((L.N + BN - 1) / BN + 7) / 8 * 8 * nrow;
-  const int ksteps = 4 * ((L.K / (4 * BK) + splits - 1) / splits);
-  hipLaunchKernelGGL((gemm_fold_kernel<WM, WN, AT, BT>), dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps, nrow);
+  const int nrow = (L.M + BM - 1) / BM, grid = (L.N + BN - 1) / BN * nrow;
+  const int ksteps = 4 * ((L.K / (4 * BK) + L.splits - 1) / L.splits);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps, nrow, (int64_t)L.M * 5 >= (int64_t)L.N * 4);
+  };
+  if (L.splits == 1) launch(gemm_fold_kernel<WM, WN, AT, BT, false>);
+  else launch(gemm_fold_kernel<WM, WN, AT, BT, true>);
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }
 
@@ -861,21 +868,25 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
   return launch_gemm_cfg(cfg, x, w, y, ws, M, N, K, mode, ks.splits, 0, N, paired && (mode == 0 || ks.splits == 1), cold, s);
 }
 
-// us per k-step of a folded product by its six tile shapes: the time of the fullest compute unit, 0.26 / 0.38 / 0.42 / 0.50 / 0.72 per
-// resident 64 x 64 / 128 x 64 / 96 x 128 / 128 x 128 / 192 x 128 tile (128 x 128 a quarter more where most units hold two, or x is far), 128 x 256 tiles by how
-// many run (fits of sweeps at the products of the 1.5B, 7B and 32B shapes, 300 to 4000 rows).  96 and 192 x 128 only while x stays near the
-// L2s: with 8960-long rows, 2000 of them, a k-step of 96 x 128 tiles takes 0.65.  128-wide tiles by four wavefronts side by side, which load
-// no W twice.  7B QKV, 511 rows, by 128 x 128 tiles 33 us, by 96 x 128 27; 1.5B QKV, 3000 rows, by 128 x 256 33, by 192 x 128 29; 7B QKV, 1400
-// rows, by 128 x 256 tiles 91, by 128 x 128 60.
-static int fold_shape(int M, int N, int K, double *us) {
-  auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  auto cost = [&](int bm, int bn, double t) { return (tiles(bm, bn) + 255) / 256 * t; };
-  const int square = tiles(128, 128), wide = tiles(128, 256);
-  const bool near = (int64_t)M * K <= 5 << 20;
-  const double c[6] = {cost(64, 64, 0.26), cost(128, 64, 0.38), near ? cost(96, 128, 0.42) : 1e9, cost(128, 128, square > 420 || (!near && square > 256) ? 0.625 : 0.50),
-                       near ? cost(192, 128, 0.72) : 1e9, wide <= 256 ? 0.45 + wide * (0.75 / 256) : cost(128, 256, 1.2)};
-  const int best = (int)(std::min_element(c, c + 6) - c);
-  if (us) *us = c[best];
+// Microseconds of a folded product by tiles of one shape: fixed + k-steps * (base + load * (fraction of the compute units at work) + round * (tiles of
+// the fullest unit - 1) + more * (average beyond one)).  Fits to 1264 launches (the products of the 1.5B, 7B and 32B shapes, 260 to 4096 rows): the shape with the
+// least takes 0.3 % more than the best measured one on average, 1.4 % in 95 of 100.  128-wide tiles by four wavefronts side by side, which load no W twice.
+// Before tiles were dealt evenly and with six shapes, us: 1.5B O, 3000 rows, 24.8, now 20; 7B QKV, 511 / 1024 / 3000 rows 24 / 42 / 126, now 23 / 36 / 101; 7B O, 511
+// / 3000 rows 21 / 93, now 18 / 82; 32B QKV, 4096 rows, 382, now 301 (all of the sweep 11 % less on average).
+struct FoldTime { int rows, cols; float fixed, base, load, round, more; };
+constexpr FoldTime FOLDS[] = {{64, 64, 2.7f, 0.180f, 0.063f, 0.146f, 0.114f},  {64, 128, 3.0f, 0.230f, 0.107f, 0.167f, 0.183f},
+                              {96, 128, 4.1f, 0.290f, 0.110f, 0.203f, 0.279f}, {128, 128, 5.8f, 0.308f, 0.172f, 0.295f, 0.323f},
+                              {160, 128, 6.7f, 0.361f, 0.188f, 0.353f, 0.361f}, {192, 128, 8.1f, 0.406f, 0.224f, 0.443f, 0.374f},
+                              {128, 256, 8.8f, 0.522f, 0.271f, 0.511f, 0.473f}};
+static int fold_shape(int M, int N, int K, float *us) {
+  int best = 0;
+  for (int i = 0; i < (int)(sizeof(FOLDS) / sizeof(FOLDS[0])); ++i) {
+    const FoldTime &f = FOLDS[i];
+    const int n = (M + f.rows - 1) / f.rows * ((N + f.cols - 1) / f.cols);
+    const float r = n * (1.f / 256);
+    const float t = f.fixed + K / BK * (f.base + f.load * std::min(r, 1.f) + f.round * ((n + 255) / 256 - 1) + f.more * std::max(r - 1, 0.f));
+    if (i == 0 || t < *us) { best = i; *us = t; }
+  }
   return best;
 }
 
@@ -919,33 +930,35 @@ int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, 
       default: return launch_cfg<2, 2, 2, 2>(L);
     }
   }
-  switch (fold_shape(M, N, K, nullptr)) {
+  float us;
+  switch (fold_shape(M, N, K, &us)) {
     case 0: return launch_fold_cfg<2, 2, 1, 1>(L);
-    case 1: return launch_fold_cfg<2, 2, 2, 1>(L);
+    case 1: return launch_fold_cfg<1, 4, 2, 1>(L);
     case 2: return launch_fold_cfg<1, 4, 3, 1>(L);
     case 3: return launch_fold_cfg<1, 4, 4, 1>(L);
-    case 4: return launch_fold_cfg<1, 4, 6, 1>(L);
+    case 4: return launch_fold_cfg<1, 4, 5, 1>(L);
+    case 5: return launch_fold_cfg<1, 4, 6, 1>(L);
     default: return launch_fold_cfg<1, 4, 4, 2>(L);
   }
 }
 
 // How many slices a pass of M rows leaves a plain product in: 1 (launch_gemm_folded) or all ks.splits, as a step does.  A long K in one
-// workgroup after the other leaves the chip to 128 x 64 tiles, one per compute unit and half its rate; by slices there are enough 256 x 256
-// tiles, for the price of the slices' way to memory and back.  Down products, us folded / in slices (without the consumer's reads, here
-// counted at 4 TB/s): 7B shape 511 rows 118 / 69, 1024 rows 181 / 138; 32B 511 262 / 143, 1024 326 / 273; 1.5B 511 42 / 23, 1024 57 / 41.
-// QKV and O: 7B, 511 rows, 38 / 33 and 25 / 31; 32B, 1024 rows, 77 / 112.
+// workgroup after the other leaves the chip to small tiles, at half the rate; by slices there are enough 256 x 256
+// tiles, for the price of the slices' way to memory (0.24 us per MB) and back (0.14).  Down products, us folded / in slices with the consumer's reads:
+// 1.5B shape 511 rows 35 / 26, 1024 42 / 44, 2000 56 / 84, 3000 76 / 118; 7B 511 115 / 87, 900 124 / 144, 2000 241 / 282; 32B 511 173 / 165, 1024 312 / 297,
+// 1536 375 / 442.  QKV and O: 7B, 511 rows, 38 / 33 and 25 / 31; 32B, 1024 rows, 77 / 112.
 int gemm_pass_slices(int M, int N, int K, const GemmSplit &ks) {
   if (ks.splits == 1 || K < 8192) return 1;
-  double fold;
+  float fold;
   fold_shape(M, N, K, &fold);
   const int ksteps = 4 * ((K / (4 * BK) + ks.splits - 1) / ks.splits);
   const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256) * ks.splits;
-  const double sliced = 4 + ksteps * big_rounds(tiles) + (ks.splits - 1) * (4e-6 * M * N / 4);
-  return sliced < K / BK * fold ? ks.splits : 1;
+  const float sliced = ksteps * big_rounds(tiles) + 4e-6f * M * N * (0.24f * ks.splits + 0.14f * (ks.splits - 1));
+  return sliced < fold ? ks.splits : 1;
 }
 
-// fp32 elements of a plain product of a pass of up to R rows.  Slices come and go with the row count (fold_shape steps at the rows of six
-// tile shapes and where x no longer stays near), so every row count is asked, from the most down to the first that keeps them.
+// fp32 elements of a plain product of a pass of up to R rows.  Slices come and go with the row count (fold_shape steps at the rows of its
+// tile shapes), so every row count is asked, from the most down to the first that keeps them.
 int64_t gemm_pass_elems(int R, int N, int K, const GemmSplit &ks) {
   int r = R;
   while (r > 0 && gemm_pass_slices(r, N, K, ks) == 1) --r;

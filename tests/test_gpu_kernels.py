@@ -400,6 +400,32 @@ def test_products_of_many_rows_equal_the_slices_of_few_added_in_order(M_max, N, 
             pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), M_max, *bad, mode, 0)
 
 
+@pytest.mark.parametrize("N,K", [(32, 512), (96, 1536), (352, 768), (1312, 1536), (2080, 256)])
+def test_every_tile_of_a_folded_product_is_dealt_to_one_workgroup(N, K):
+    """Fewer tiles than XCDs, counts that eight does not divide, and both orders of the deal (by rows where 5 M >= 4 N): every element once,
+    bit-equal to the slices of a narrow pass added in order."""
+    splits = pl.pl_debug_gemm_plan(64, N, K, 0)[0]
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    x = torch.empty(2050, K, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
+    w = torch.empty(N * K, device="cuda", dtype=torch.bfloat16).normal_(0, 0.05, generator=g)
+    want = torch.empty(2050, N, device="cuda")
+    ws = torch.empty(1, device="cuda")
+    for r in range(0, 2050, 64):
+        rows = min(64, 2050 - r)
+        y = torch.empty(splits, rows, N, device="cuda")
+        pl.pl_debug_gemm_planned(x[r:].data_ptr(), w.data_ptr(), y.data_ptr(), ws.data_ptr(), 64, rows, N, K, 0, 0)
+        for s in range(1, splits):
+            y[0] += y[s]
+        want[r:r + rows] = y[0]
+        torch.cuda.synchronize()
+    for M in (1, 31, 65, 259, 4 * N // 5, 4 * N // 5 + 1, 2050):
+        y = torch.full((M + 1, N), float("nan"), device="cuda")
+        pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), 64, M, N, K, 0, 0)
+        torch.cuda.synchronize()
+        assert torch.equal(y[:M], want[:M]), M
+        assert bool(y[M].isnan().all()), M
+
+
 @pytest.mark.parametrize("cfg", sorted(CFG_TILES))
 def test_every_gemm_tile_configuration_for_cold_weights_gives_the_same_bits(cfg):
     """Weights that do not stay in the cache between two steps are loaded with another cache policy, by kernels of their
