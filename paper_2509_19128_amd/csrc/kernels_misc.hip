@@ -42,7 +42,9 @@ __global__ void pass_end_kernel(const uint64_t *mark_at, uint64_t *word) {
 // Bound by latency: one round trip to the host's memory (all of what a thread wants from there at once), one to the table or the row, the row's sum.
 // Decode steps, the frequencies' powers taken anew, scans through LDS and 1024 threads: 4 rows of the tiny shape 6.3 us, 64 of the 1.5B shape 7.6, 256 of the
 // 7B shape 13.1; now 4.1, 5.2 and 7.4.
-template <int NT, int NV>   // NV: pieces of eight elements per thread
+// ONE: a pass over one slot's rows, whose metadata is the token alone: six reads per row over the bus held 3000 rows of the 1.5B shape up
+// for 33 us, one leaves 14.5 (512 rows of the 7B shape 11.3 -> 10.0).
+template <int NT, int NV, bool ONE>   // NV: pieces of eight elements per thread
 __global__ __launch_bounds__(NT) void step_begin_kernel(StepBegin q, AttnParams p, int cap) {
   if (blockIdx.x == 0) {
     if (q.time && threadIdx.x == 0)
@@ -68,12 +70,19 @@ __global__ __launch_bounds__(NT) void step_begin_kernel(StepBegin q, AttnParams 
     return;
   }
   const int row = blockIdx.x - 1, d8 = q.d >> 3;
-  int pos = q.src.pos[row], tok = q.src.input_tok[row], slot = q.src.row_slot[row], forced = q.src.forced[row];
-  float inv_t = q.src.inv_t[row];
-  uint64_t seq_id = q.src.seq_id[row];
+  int tok = q.src.input_tok[row], pos = q.first_pos + row, slot = q.one_slot, forced = -1;
+  float inv_t = 0.f;
+  uint64_t seq_id = 0;
+  if constexpr (!ONE) {
+    pos = q.src.pos[row];
+    slot = q.src.row_slot[row];
+    forced = q.src.forced[row];
+    inv_t = q.src.inv_t[row];
+    seq_id = q.src.seq_id[row];
 #ifdef __HIP_DEVICE_COMPILE__
-  asm volatile("" : "+s"(pos), "+s"(tok), "+s"(slot), "+s"(forced), "+s"(inv_t), "+s"(seq_id));   // one round trip for all of them
+    asm volatile("" : "+s"(pos), "+s"(tok), "+s"(slot), "+s"(forced), "+s"(inv_t), "+s"(seq_id));   // one round trip for all of them
 #endif
+  }
   tok = min(max(tok, 0), q.vocab - 1);
   const int i = NT - 1 - (int)threadIdx.x;   // the last wavefronts, which have least of the row, take the angles
   const double freq = i < p.hd / 2 ? q.freqs[i] : 0.0;
@@ -95,9 +104,11 @@ __global__ __launch_bounds__(NT) void step_begin_kernel(StepBegin q, AttnParams 
     if (q.dst.pos) {
       q.dst.row_slot[row] = slot;
       q.dst.pos[row] = pos;
-      q.dst.forced[row] = forced;
-      q.dst.inv_t[row] = inv_t;
-      q.dst.seq_id[row] = seq_id;
+      if constexpr (!ONE) {   // (nothing of a pass is sampled)
+        q.dst.forced[row] = forced;
+        q.dst.inv_t[row] = inv_t;
+        q.dst.seq_id[row] = seq_id;
+      }
     }
   }
   float ss = 0.f;
@@ -295,9 +306,13 @@ int launch_step_begin(const StepBegin &q, const AttnParams &p, int cap, hipStrea
   if ((p.work && p.n_seq > BEGIN_LIST) || q.d > 8192 || ((uintptr_t)p.work & 31)) return -1;
   // the work list's threads; the rows of a pass no more than they have pieces (1536 wide: 1000 rows 11 us by 1024 threads, 3000 rows 14 by 256)
   auto launch = [&](auto kernel, int nt) { hipLaunchKernelGGL(kernel, dim3(p.n_seq + 1), dim3(nt), 0, s, q, p, cap); };
-  if (q.d > 4096) launch(step_begin_kernel<512, 2>, 512);
-  else if (p.work || q.d > 2048) launch(step_begin_kernel<512, 1>, 512);
-  else launch(step_begin_kernel<256, 1>, 256);
+  auto shape = [&](auto ONE) {
+    constexpr bool one = decltype(ONE)::value;
+    if (q.d > 4096) launch(step_begin_kernel<512, 2, one>, 512);
+    else if (p.work || q.d > 2048) launch(step_begin_kernel<512, 1, one>, 512);
+    else launch(step_begin_kernel<256, 1, one>, 256);
+  };
+  if (q.pairs_src) shape(std::true_type{}); else shape(std::false_type{});
   return ok();
 }
 

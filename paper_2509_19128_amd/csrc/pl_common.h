@@ -242,6 +242,7 @@ struct StepBegin {
   int32_t *pairs_dst, *table_dst;
   int32_t n_pairs, n_table;
   uint64_t mark, *mark_at;                // mark_at: device
+  int32_t one_slot, first_pos;            // with pairs_src: the rows are this slot's, at consecutive positions from first_pos on
 };
 // Words of a pass in the host's memory: its mark's low bits above the wall clock's.
 constexpr int PASS_CLOCK_BITS = 40;

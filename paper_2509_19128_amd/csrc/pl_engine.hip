@@ -526,6 +526,8 @@ int enqueue_begin(pl_engine *e, pl_engine::Work &w, int n, bool prefill, int slo
   if (prefill) { sb.mark = ++e->pass_mark; sb.mark_at = e->pass_mark_d; }
   if (slot >= 0) {
     sb.dst = w.meta(true);
+    sb.one_slot = slot;
+    sb.first_pos = w.m_pos(false)[0];
     sb.time = &e->pass_begin_word();
     sb.pairs_src = w.m_pairs(false); sb.pairs_dst = w.m_pairs(true);
     sb.n_pairs = w.attn_apart ? 0 : 2 + 2 * sb.pairs_src[0];
