@@ -715,7 +715,9 @@ int rounds_cut(int M, int N, int splits, float *us) {
 
 // Tile shape of a call.  Shapes whose wavefronts stack rows have no SwiGLU pairs (64 x 64, 128 x 64); 64 x 64 tiles for up to 32 rows
 // pay only where W comes from memory (7B down in one slice, 16 rows: 75 us, by 32 x 128 tiles 95; O from the cache 10.6 and 10.0); 128 x 128
-// tiles in two rows of two are a second choice where two of them share a unit.
+// tiles in two rows of two are a second choice where two of them share a unit.  256 x 256 tiles in rounds only from 129 rows on: half of a tile's
+// products would be of rows that are not there (LM head of the 7B / 32B / 1.5B shape, 128 rows, 256 / 348 / 125 us, by 128 x 256 226 / 304 / 116; 96 rows 246 / 361 / 116
+// and 213 / 291 / 110; 160 rows 261 / 360 / 129 and 291 / 402 / 145).
 int pick_shape(int M, int N, int K, int mode, int splits, bool cold) {
   const float ksteps = 4 * ((K / (4 * BK) + splits - 1) / splits), out_mb = 4e-6f * M * N * (mode == 0 ? splits : 0.25f);
   const float floor_us = 2e-6f / 6.6f * N * K + 3;
@@ -726,7 +728,7 @@ int pick_shape(int M, int N, int K, int mode, int splits, bool cold) {
     if ((rows > 64 && rows >= 4 * M) || rows * 5 < M) continue;
     const int n = ((M + rows - 1) >> t.log_rows) * ((N + (1 << t.log_cols) - 1) >> t.log_cols) * splits;
     if (t.cfg == GEMM_64x64 && (mode == 1 || (M <= 32 && !cold))) continue;
-    if ((t.cfg == GEMM_128x64 && mode == 1) || (t.cfg == GEMM_128x128 && n > 512)) continue;
+    if ((t.cfg == GEMM_128x64 && mode == 1) || (t.cfg == GEMM_128x128 && n > 512) || (t.cfg == GEMM_256x256 && n > 256 && M <= 128)) continue;
     const float r = n * (1.f / 256);
     float us = t.fixed + t.out * out_mb + ksteps * (t.base + t.load * std::min(r, 1.f) + t.round * ((n + 255) / 256 - 1) + t.more * std::max(r - 1, 0.f));
     if (t.cfg == GEMM_256x256 && n > 256) {

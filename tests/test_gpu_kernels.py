@@ -400,6 +400,27 @@ def test_products_of_many_rows_equal_the_slices_of_few_added_in_order(M_max, N, 
             pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), M_max, *bad, mode, 0)
 
 
+def test_rows_of_a_wide_product_do_not_depend_on_the_row_count():
+    """A product of more 256-wide column tiles than compute units at the row counts where its tiles change: close to fp64, and the same rows
+    whatever their number."""
+    N, K = 257 * 256 + 32, 256
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.empty(160, K, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
+    w = torch.empty(N, K, device="cuda", dtype=torch.bfloat16).normal_(0, 0.05, generator=g)
+    packed = w.view(N // 32, 32, K // 64, 2, 4, 8).permute(2, 0, 4, 3, 1, 5).contiguous()   # [k-step][row block][j][half][row][8]
+    ref = x.double() @ w.double().T
+    widest = None
+    for M in (160, 129, 128, 127, 96, 65, 64):
+        y = torch.full((M + 1, N), float("nan"), device="cuda")
+        pl.pl_gemm_bf16(x.data_ptr(), packed.data_ptr(), y.data_ptr(), M, N, K, 0, 1, 0)
+        torch.cuda.synchronize()
+        assert bool(y[M].isnan().all()), M
+        if widest is None:
+            widest = y[:M].clone()
+            assert float((widest.double() - ref).abs().max()) <= K * 2.0 ** -24 * float((x.double().abs() @ w.double().abs().T).max())   # fp32 sums of K products
+        assert torch.equal(y[:M], widest[:M]), M
+
+
 @pytest.mark.parametrize("N,K", [(32, 512), (96, 1536), (352, 768), (1312, 1536), (2080, 256)])
 def test_every_tile_of_a_folded_product_is_dealt_to_one_workgroup(N, K):
     """Fewer tiles than XCDs, counts that eight does not divide, and both orders of the deal (by rows where 5 M >= 4 N): every element once,
