@@ -425,32 +425,44 @@ __global__ __launch_bounds__(256) void gemm_kernel(const bf16_t *__restrict__ X,
 // 160 x 128 33.7 -> 19.8, 1.5B down, 3000 rows, 140 -> 88, 2000 rows, 96 x 128 94 -> 57; 7B QKV, 1024 rows, 160 x 128 56 -> 36; 3000 rows, 128 x 256 128 -> 101.
 // (128 x 256 tiles: the second set of accumulators leaves no register free and each fold moves 256; still the fastest where
 // launch_gemm_folded takes it: down product of the 32B shape, 1536 rows, 375 us, 418 with the best of the 128-wide tiles.)
+__device__ __forceinline__ void deal(int nrow, int ncol, bool rows, int &rtile, int &ctile) {
+  const int tiles = nrow * ncol, xcd = blockIdx.x & 7;
+  const int t = xcd * (tiles >> 3) + min(xcd, tiles & 7) + (blockIdx.x >> 3);
+  const int slow = t / (rows ? ncol : nrow), fast = t - slow * (rows ? ncol : nrow);
+  rtile = rows ? slow : fast;
+  ctile = rows ? fast : slow;
+}
 template <int WM, int WN, int AT, int BT, bool FOLD>
 __global__ __launch_bounds__(256) void gemm_fold_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
                                                         void *__restrict__ Yv, int M, int N, int K, int ksteps, int nrow, bool rows) {
   constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
   __shared__ __attribute__((aligned(1024))) bf16_t xs[Tile<WM, WN, AT, BT, false>::LDS];
-  const int ncol = (N + BN - 1) / BN, tiles = nrow * ncol, xcd = blockIdx.x & 7;
-  const int t = xcd * (tiles >> 3) + min(xcd, tiles & 7) + (blockIdx.x >> 3);
-  const int slow = t / (rows ? ncol : nrow), fast = t - slow * (rows ? ncol : nrow);
-  const int rtile = rows ? slow : fast, ctile = rows ? fast : slow;
+  int rtile, ctile;
+  deal(nrow, (N + BN - 1) / BN, rows, rtile, ctile);
   gemm_tile<WM, WN, AT, BT, 0, false, FOLD>(xs, X, W, Yv, M, N, K, ksteps, ctile * BN, rtile * BM, 0, N, N, 0);
+}
+// The SwiGLU product (MODE 1) of a pass over columns [n_begin, n_end), dealt like that; FOLD: columns whose K is in slices elsewhere.
+template <int WM, int WN, int AT, int BT, int MODE, bool FOLD>
+__global__ __launch_bounds__(256) void gemm_pass_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W, void *__restrict__ Yv,
+                                                        int M, int N, int K, int ksteps, int nrow, bool rows, int n_begin, int n_end) {
+  constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
+  __shared__ __attribute__((aligned(1024))) bf16_t xs[Tile<WM, WN, AT, BT, false>::LDS];
+  int rtile, ctile;
+  deal(nrow, (n_end - n_begin + BN - 1) / BN, rows, rtile, ctile);
+  gemm_tile<WM, WN, AT, BT, MODE, false, FOLD>(xs, X, W, Yv, M, N, K, ksteps, n_begin + ctile * BN, rtile * BM, 0, n_end, N, 0);
 }
 
 // Products of more 256 x 256 tiles than compute units: a workgroup of each takes tiles one after the other and loads the first
 // k-steps of the next one under the last products of the tile at hand (as gemm_tile2), so that the pipeline fills once and not
 // once per round (one tile fills a compute unit: no other workgroup could work meanwhile).  Tiles below n_big are those of columns
-// [0, n_cut), all K slices (mode 0); the columns behind, which would be a nearly empty last round, go in narrower tiles: LEFT 0
-// 256 x 128 (sliced alike), 2 256 x 64 with the K of a tile in slices of `ksteps` added up (SwiGLU; the big tiles are whole).
+// [0, n_cut), all K slices (mode 0); the columns behind, which would be a nearly empty last round, go in 256 x 128 tiles.
 // One launch of a workgroup per tile and this kernel: gate/up of the 1.5B shape, 3000 rows (840 tiles), 166 and 154 us, its down product
 // (648) 112 and 104; LM head of the 7B shape, 256 rows (594), 337 and 322, 129 rows 303 and 279; 7B down as one slice, 512 rows, 171 and 146.
-template <int MODE, bool COLD, int LEFT>
+template <int MODE, bool COLD>
 __global__ __launch_bounds__(256) void gemm_rounds_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
                                                           void *__restrict__ Yv, int M, int N, int K, int ksteps, int n_cut, int n_big, int n_left) {
   using Big = Tile<1, 4, 8, 2, COLD>;
   __shared__ __attribute__((aligned(1024))) bf16_t xs[Big::LDS];
-  static_assert(LEFT == 0 || (LEFT == 2 && MODE == 1), "leftover tiles");
-  constexpr int LN = LEFT == 0 ? 128 : 64;
   const int nrow = (M + 255) / 256, per = MODE == 0 ? ksteps : K / BK;
   struct At { int m0, n0, split; };
   // tile `i` of column tiles `width` wide from `n_begin`: row tiles of a column tile and slice 8 apart, padded as everywhere
@@ -492,10 +504,9 @@ __global__ __launch_bounds__(256) void gemm_rounds_kernel(const bf16_t *__restri
     __syncthreads();
   }
   for (int j = blockIdx.x; j < n_left; j += gridDim.x) {
-    const At c = at(j, n_cut, N, LN);
+    const At c = at(j, n_cut, N, 128);
     if (c.split >= slices) continue;
-    if constexpr (LEFT == 0) gemm_tile<1, 4, 8, 1, MODE, COLD>(xs, X, W, Yv, M, N, K, per, c.n0, c.m0, c.split, N, N, 0);
-    else gemm_tile<4, 1, 2, 2, MODE, false, true>(xs, X, W, Yv, M, N, K, ksteps, c.n0, c.m0, 0, N, N, 0);
+    gemm_tile<1, 4, 8, 1, MODE, COLD>(xs, X, W, Yv, M, N, K, per, c.n0, c.m0, c.split, N, N, 0);
     __syncthreads();   // (the next tile's first stages, and the halves that neighbours swap, share the LDS)
   }
 }
@@ -644,21 +655,27 @@ int launch_fold_cfg(const Launch &L) {
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }
 
-// Columns [0, n_cut) by 256 x 256 tiles, a workgroup per compute unit, the rest by narrower tiles (LEFT of gemm_rounds_kernel) in the
-// same launch; rem_splits: the slices that LEFT 2 adds up.
-template <int LEFT>
-int launch_rounds(const Launch &L, int n_cut, int rem_splits = 1) {
-  const int nrow = (L.M + 255) / 256, ln = LEFT == 0 ? 128 : 64, splits = L.mode == 0 ? L.splits : 1;
-  if (LEFT == 0 && n_cut >= L.N && (L.N + 255) / 256 * splits * nrow <= 256) return launch_cfg<1, 4, 8, 2>(L);   // a tile each
-  const int big = ((n_cut + 255) / 256 * splits + 7) / 8 * 8 * nrow, left = ((L.N - n_cut + ln - 1) / ln * splits + 7) / 8 * 8 * nrow;
-  const int slices = L.mode == 0 ? L.splits : rem_splits, ksteps = 4 * ((L.K / (4 * BK) + slices - 1) / slices);
-  with_cold<1>(L.cold && LEFT == 0, [&](auto COLD) {
+template <int AT, int BT, bool FOLD>
+int launch_pass_cfg(const Launch &L, int slices) {
+  constexpr int BM = AT * 32, BN = BT * 128;
+  const int nrow = (L.M + BM - 1) / BM, cols = L.n_end - L.n_begin, ksteps = 4 * ((L.K / (4 * BK) + slices - 1) / slices);
+  hipLaunchKernelGGL((gemm_pass_kernel<1, 4, AT, BT, 1, FOLD>), dim3(nrow * ((cols + BN - 1) / BN)), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K,
+                     ksteps, nrow, (int64_t)L.M * 5 >= (int64_t)cols * 4, L.n_begin, L.n_end);
+  return hipGetLastError() == hipSuccess ? 0 : -7;
+}
+
+// Columns [0, n_cut) by 256 x 256 tiles, a workgroup per compute unit, the rest by 256 x 128 tiles in the same launch.
+int launch_rounds(const Launch &L, int n_cut) {
+  const int nrow = (L.M + 255) / 256, splits = L.mode == 0 ? L.splits : 1;
+  if (n_cut >= L.N && (L.N + 255) / 256 * splits * nrow <= 256) return launch_cfg<1, 4, 8, 2>(L);   // a tile each
+  const int big = ((n_cut + 255) / 256 * splits + 7) / 8 * 8 * nrow, left = ((L.N - n_cut + 127) / 128 * splits + 7) / 8 * 8 * nrow;
+  const int ksteps = 4 * ((L.K / (4 * BK) + splits - 1) / splits);
+  with_cold<1>(L.cold, [&](auto COLD) {
     auto launch = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(256), dim3(256), 0, L.s, L.x, L.w, L.y, L.M, L.N, L.K, ksteps, n_cut, big, n_cut < L.N ? left : 0);
     };
-    constexpr bool cold = LEFT == 0 && decltype(COLD)::value;
-    if (L.mode == 1) launch(gemm_rounds_kernel<1, cold, LEFT>);
-    else if constexpr (LEFT == 0) launch(gemm_rounds_kernel<0, cold, 0>);
+    constexpr bool cold = decltype(COLD)::value;
+    if (L.mode == 1) launch(gemm_rounds_kernel<1, cold>); else launch(gemm_rounds_kernel<0, cold>);
   });
   return hipGetLastError() == hipSuccess ? 0 : -7;
 }
@@ -701,7 +718,7 @@ int gemm_tile_rows(int cfg) {
 // us per k-step of this many 256 x 256 tiles
 float big_rounds(int64_t tiles) { return tiles / 256 * 1.45f + (tiles % 256 ? 1.05f + tiles % 256 * (0.4f / 256) : 0.f); }
 
-// Columns that launch_rounds<0> gives to 256 x 256 tiles: all, or full rounds of them where what is left fits one round of 256 x 128 tiles
+// Columns that launch_rounds gives to 256 x 256 tiles: all, or full rounds of them where what is left fits one round of 256 x 128 tiles
 // (0.89 us per k-step when they fill the chip, 0.5 when few) in less time; *us: per k-step.
 int rounds_cut(int M, int N, int splits, float *us) {
   const int per = (M + 255) / 256 * splits, ncol = (N + 255) / 256, cut = ncol * per / 256 * 256 / per, left = (N - cut * 256 + 127) / 128 * per;
@@ -865,7 +882,7 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
   if (paired && (M - 1) % gemm_tile_rows(cfg) < gemm_tile_rows(cfg) / 2) cold = false;
   if (cfg == GEMM_256x256 && (mode == 0 || ks.splits == 1) && (M + 255) / 256 * ((N + 255) / 256) * ks.splits > 256) {
     float us;
-    return launch_rounds<0>(Launch{x, w, y, M, N, K, mode, ks.splits, 0, N, N, 0, true, cold, s}, rounds_cut(M, N, ks.splits, &us));
+    return launch_rounds(Launch{x, w, y, M, N, K, mode, ks.splits, 0, N, N, 0, true, cold, s}, rounds_cut(M, N, ks.splits, &us));
   }
   return launch_gemm_cfg(cfg, x, w, y, ws, M, N, K, mode, ks.splits, 0, N, paired && (mode == 0 || ks.splits == 1), cold, s);
 }
@@ -880,17 +897,26 @@ constexpr FoldTime FOLDS[] = {{64, 64, 2.7f, 0.180f, 0.063f, 0.146f, 0.114f},  {
                               {96, 128, 4.1f, 0.290f, 0.110f, 0.203f, 0.279f}, {128, 128, 5.8f, 0.308f, 0.172f, 0.295f, 0.323f},
                               {160, 128, 6.7f, 0.361f, 0.188f, 0.353f, 0.361f}, {192, 128, 8.1f, 0.406f, 0.224f, 0.443f, 0.374f},
                               {128, 256, 8.8f, 0.522f, 0.271f, 0.511f, 0.473f}};
-static int fold_shape(int M, int N, int K, float *us) {
-  int best = 0;
-  for (int i = 0; i < (int)(sizeof(FOLDS) / sizeof(FOLDS[0])); ++i) {
-    const FoldTime &f = FOLDS[i];
+static int least(const FoldTime *f0, int from, int to, int M, int N, int K, float *us) {
+  int best = from;
+  for (int i = from; i < to; ++i) {
+    const FoldTime &f = f0[i];
     const int n = (M + f.rows - 1) / f.rows * ((N + f.cols - 1) / f.cols);
     const float r = n * (1.f / 256);
     const float t = f.fixed + K / BK * (f.base + f.load * std::min(r, 1.f) + f.round * ((n + 255) / 256 - 1) + f.more * std::max(r - 1, 0.f));
-    if (i == 0 || t < *us) { best = i; *us = t; }
+    if (i == from || t < *us) { best = i; *us = t; }
   }
   return best;
 }
+static int fold_shape(int M, int N, int K, float *us) { return least(FOLDS, 0, 7, M, N, K, us); }
+
+// The same of a pass's SwiGLU product: fits to 512 launches (1.5B, 7B and 32B shapes, 260 to 4096 rows); the shape with the least takes 0.2 % more than
+// the best measured one on average.  Against 128 x 256 and 128 x 128 tiles in groups of eight column tiles or rounds of 256 x 256, us: 1.5B 300 / 511 / 640 / 1024 / 1300 rows
+// 33 / 41 / 44 / 72 / 84, now 25 / 33 / 38 / 57 / 68, 3000 rows 159 -> 155; 7B 511 / 640 / 1300 143 / 175 / 328, now 132 / 154 / 298; 32B 260 / 640 / 1300 214 / 366 / 726,
+// now 161 / 315 / 567.
+constexpr FoldTime PASSES[] = {{128, 256, 11.3f, 0.f, 0.769f, 0.546f, 0.347f},   {160, 256, 12.9f, 0.354f, 0.447f, 0.767f, 0.270f},
+                               {192, 256, 15.8f, 0.294f, 0.610f, 0.917f, 0.293f}, {224, 256, 18.7f, 0.110f, 0.912f, 0.933f, 0.481f},
+                               {256, 256, 23.6f, 0.028f, 1.126f, 1.124f, 0.491f}};
 
 // A product of up to GEMM_MAX_ROWS rows with all K slices of an element added up in the workgroup, in slice
 // order: y is ONE slice (mode 0: [M][N]; mode 1: the SwiGLU result), equal bit for bit to what a consumer of
@@ -899,7 +925,7 @@ static int fold_shape(int M, int N, int K, float *us) {
 // are saved.  Measured at 1024 rows against four 256-row launches, consumers' reads not counted: QKV / O / gate-up
 // / down of the 1.5B shape 14 / 13 / 73 / 52 against 50 / 43 / 116 / 100 us, of the 7B shape 53 / 37 / 288 / 189
 // against 82 / 71 / 350 / 200 us.
-int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, int K, int mode, const GemmSplit &ks, bool cold,
+int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, int K, int mode, const GemmSplit &ks, bool /*cold*/,
                        hipStream_t s) {
   if (M < 1 || M > GEMM_MAX_ROWS || K % (4 * BK) || N % 32 || !splits_valid(K, ks.splits)) return -1;
   if (mode != 0 && mode != 1) return -1;
@@ -907,32 +933,40 @@ int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, 
   if (mode == 0 && ks.n_main != N) return -1;
   if (ks.n_main < 0 || ks.n_main > N) return -1;
   if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
-  // Non-temporal loads of cold weights only for few and full row tiles: gate/up of the 7B / 32B shape, 384 rows 142 / 236 us with
-  // them and 146 / 234 without, 512 rows 148 / 302 and 150 / 302, but 257 rows 129 / 240 and 128 / 217, 576 rows 182 / 371 and
-  // 185 / 356, 769 rows 258 / 492 and 252 / 451; plain products (32B down, 769 rows) 372 and 348.
-  cold = cold && mode == 1 && M <= 512 && (M - 1) % 128 >= 96;
-  Launch L{x, w, y, M, N, K, mode, ks.splits, 0, ks.n_main, N, 0, true, cold, s};
+  Launch L{x, w, y, M, N, K, mode, ks.splits, 0, ks.n_main, N, 0, true, false, s};
+  float us;
   if (mode == 1) {
     if (ks.splits > 1) return -1;   // (gemm_pick_split leaves the main columns whole)
-    // 7B shape, main columns and remainder: 128 x 256 tiles and a launch for the remainder 195 us with 700 rows, 272 with 1024; 256 x 256
-    // tiles with the remainder in their launch 183 and 265.
-    if (ks.n_main < N) return launch_rounds<2>(L, ks.n_main, ks.rem_splits);
-    // The shape with the least time: a round of 256 x 256 tiles takes 1.45 us per k-step (1.05 when few of them run), 256 of the
-    // 128 x 256 tiles of a wide matrix 1.05 and of 128 x 128 tiles 0.62 whether the last round is full or not (an idle unit's power
-    // goes to the others).  Fits of a sweep over the 1.5B, 7B and 32B shapes at 300 to 1024 rows; us by 128-row tiles, by launches of
-    // 256 x 256 and with leftover 256 x 64 tiles (gemm_rounds_kernel takes 7 % less than the launches, its leftovers are 256 x 128): 1.5B 300 rows 34 / 41 / -, 511 49 / 36 / -, 768 61 / 41 / -, 1024 78 / 75 / 66; 7B 300
-    // 100 / 146 / 123, 511 149 / 155 / 136, 768 198 / 176 / 242, 1024 251 / 244 / 265; 32B 300 207 / 232 / 275, 511 279 / 247 / 315, 1024 491 / 468 / 497.
-    const int ncol = (N + 255) / 256;
-    float big;
-    const int cut = rounds_cut(M, N, 1, &big);
-    const float t[3] = {big, N >= 128 * 256 ? (M + 127) / 128 * ncol / 256.f * 1.05f : 1e9f, (M + 127) / 128 * ((N + 127) / 128) / 256.f * 0.62f};
-    switch (std::min_element(t, t + 3) - t) {
-      case 0: L.cold = false; return launch_rounds<0>(L, cut);
-      case 1: return launch_cfg<1, 4, 4, 2>(L);
-      default: return launch_cfg<2, 2, 2, 2>(L);
+    auto narrow = [&](int n_begin, int n_end, int slices, auto FOLD) {   // by 128-wide tiles
+      constexpr bool fold = decltype(FOLD)::value;
+      L.n_begin = n_begin;
+      L.n_end = n_end;
+      switch (least(FOLDS, 1, 6, M, n_end - n_begin, K, &us)) {
+        case 1: return launch_pass_cfg<2, 1, fold>(L, slices);
+        case 2: return launch_pass_cfg<3, 1, fold>(L, slices);
+        case 3: return launch_pass_cfg<4, 1, fold>(L, slices);
+        case 4: return launch_pass_cfg<5, 1, fold>(L, slices);
+        default: return launch_pass_cfg<6, 1, fold>(L, slices);
+      }
+    };
+    int rc = 0;
+    // Few tiles leave the chip idle: 2048 x 256, 260 / 2000 rows, by 128 x 256 tiles 7.8 / 9.0 us, by 64 x 128 5.1 / 7.1; 5632 x 1024, 384 / 640 rows, 14.8 / 16.0, by 96 and 128 x 128 9.6 / 11.7,
+    // 1024 rows (176 tiles) 17.3, by 128-wide ones 16.9.
+    if ((M + 127) / 128 * ((ks.n_main + 255) / 256) <= 128) {
+      if (ks.n_main > 0) rc = narrow(0, ks.n_main, 1, std::false_type{});
+    } else {
+      switch (least(PASSES, 0, 5, M, ks.n_main, K, &us)) {
+        case 0: rc = launch_pass_cfg<4, 2, false>(L, 1); break;
+        case 1: rc = launch_pass_cfg<5, 2, false>(L, 1); break;
+        case 2: rc = launch_pass_cfg<6, 2, false>(L, 1); break;
+        case 3: rc = launch_pass_cfg<7, 2, false>(L, 1); break;
+        default: rc = ks.n_main < N ? launch_pass_cfg<8, 2, false>(L, 1) : launch_rounds(L, rounds_cut(M, N, 1, &us));
+      }
     }
+    // A remainder's columns, whose K a step adds up in slices, behind the main ones (7B shape, 640 / 1024 / 2000 rows, as leftovers of rounds of 256 x 256 tiles
+    // 204 / 271 / 488 us, so 160 / 237 / 457).
+    return rc || ks.n_main == N ? rc : narrow(ks.n_main, N, ks.rem_splits, std::true_type{});
   }
-  float us;
   switch (fold_shape(M, N, K, &us)) {
     case 0: return launch_fold_cfg<2, 2, 1, 1>(L);
     case 1: return launch_fold_cfg<1, 4, 2, 1>(L);
@@ -1008,7 +1042,7 @@ int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, float *ws, int64
   const Launch L{x, w, y, M, N, K, 0, ks.splits, 0, N, N, 0, true, false, s};
   float us;
   // few tiles: 128 x 256 ones (1.5B shape, 511 rows: 32 -> 23 us; 1024 rows 41 -> 44)
-  return (M + 255) / 256 * ((N + 255) / 256) * ks.splits <= 128 ? launch_cfg<1, 4, 4, 2>(L) : launch_rounds<0>(L, rounds_cut(M, N, ks.splits, &us));
+  return (M + 255) / 256 * ((N + 255) / 256) * ks.splits <= 128 ? launch_cfg<1, 4, 4, 2>(L) : launch_rounds(L, rounds_cut(M, N, ks.splits, &us));
 }
 
 }  // namespace pl

@@ -400,6 +400,24 @@ def test_products_of_many_rows_equal_the_slices_of_few_added_in_order(M_max, N, 
             pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), M_max, *bad, mode, 0)
 
 
+@pytest.mark.parametrize("N,K", [(17920, 1536), (4160, 2048), (5632, 512)])
+def test_swiglu_products_of_passes_give_the_rows_of_steps(N, K):
+    """Every tile shape of a pass's SwiGLU product (few tiles: 128 wide; 128 to 256 x 256), full and ragged: the rows that calls of 64 give, to the last bit."""
+    g = torch.Generator(device="cuda").manual_seed(N)
+    x = torch.empty(4096, K, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
+    w = torch.empty(N * K, device="cuda", dtype=torch.bfloat16).normal_(0, 0.05, generator=g)
+    want, ws = torch.empty(4096, N // 2, device="cuda", dtype=torch.bfloat16), torch.empty(1, device="cuda")
+    for r in range(0, 4096, 64):
+        pl.pl_debug_gemm_planned(x[r:].data_ptr(), w.data_ptr(), want[r:].data_ptr(), ws.data_ptr(), 64, 64, N, K, 1, 0)
+    torch.cuda.synchronize()
+    for M in (1, 257, 384, 511, 640, 673, 900, 1025, 1281, 1537, 2017, 3001, 4096):
+        y = torch.full((M + 1, N // 2), float("nan"), device="cuda", dtype=torch.bfloat16)
+        pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), 64, M, N, K, 1, 0)
+        torch.cuda.synchronize()
+        assert torch.equal(y[:M], want[:M]), M
+        assert bool(y[M].isnan().all()), M
+
+
 def test_rows_of_a_wide_product_do_not_depend_on_the_row_count():
     """A product of more 256-wide column tiles than compute units at the row counts where its tiles change: close to fp64, and the same rows
     whatever their number."""
