@@ -367,36 +367,6 @@ __device__ __forceinline__ void gemm_tile(bf16_t *xs, const bf16_t *__restrict__
   else t.store_swiglu((bf16_t *)Yv, n_tile0, m0, M, n_end, N);
 }
 
-// Two tiles back to back in one workgroup without draining the pipeline between them: tile A (all of
-// K, SwiGLU epilogue into mid, columns below n_main) and then K slice `split` of tile B (fp32 partial
-// sums into ws, as gemm_tile<MODE 0> writes them).  The last k-steps of A, which have nothing of their
-// own left to load, issue the first loads of B, so B starts with its operands already on the way while A's epilogue
-// runs.  Same k order per output element as gemm_tile.
-template <int WM, int WN, int AT, int BT, bool COLD>
-__device__ __forceinline__ void gemm_tile2(bf16_t *xs, const bf16_t *__restrict__ X,
-                                           const bf16_t *__restrict__ W, bf16_t *__restrict__ mid, float *__restrict__ ws,
-                                           int M, int N, int K, int n_tileA, int m0A, int n_main, int n_tileB, int m0B,
-                                           int split, int kstepsB) {
-  static_assert(BT == 2, "the stages already hold tile B when A is stored");
-  Tile<WM, WN, AT, BT, COLD> t;
-  t.init(xs, X, W, M, N, K);
-  const int nksA = K / BK, nksB = min(kstepsB, K / BK - split * kstepsB);
-  const auto pa = t.part(n_tileA, m0A, 0, M, N, K), pb = t.part(n_tileB, m0B, split * kstepsB, M, N, K);
-  t.zero();
-  t.begin(pa);
-  int ks = 0;
-  for (; ks < nksA - 4; ks += 4) t.four(pa, ks);
-  t.template kstep<0, true, 3>(pa, ks + 3);
-  t.template kstep<1, true, 3>(pb, 0);
-  t.template kstep<2, true, 3>(pb, 1);
-  t.template kstep<3, true, 3>(pb, 2);
-  t.store_swiglu(mid, n_tileA, m0A, M, n_main, N);
-  t.zero();
-  for (ks = 0; ks < nksB - 4; ks += 4) t.four(pb, ks);
-  t.last_four(pb, ks);
-  t.store(ws + (int64_t)split * M * (N - n_main), n_tileB, m0B, M, N, N - n_main, n_main);
-}
-
 template <int WM, int WN, int AT, int BT, int MODE, bool COLD>
 __global__ __launch_bounds__(256) void gemm_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
                                                    void *__restrict__ Yv, int M, int N, int K, int ksteps,
@@ -453,7 +423,7 @@ __global__ __launch_bounds__(256) void gemm_pass_kernel(const bf16_t *__restrict
 }
 
 // Products of more 256 x 256 tiles than compute units: a workgroup of each takes tiles one after the other and loads the first
-// k-steps of the next one under the last products of the tile at hand (as gemm_tile2), so that the pipeline fills once and not
+// k-steps of the next one under the last products of the tile at hand, so that the pipeline fills once and not
 // once per round (one tile fills a compute unit: no other workgroup could work meanwhile).  Tiles below n_big are those of columns
 // [0, n_cut), all K slices (mode 0); the columns behind, which would be a nearly empty last round, go in 256 x 128 tiles.
 // One launch of a workgroup per tile and this kernel: gate/up of the 1.5B shape, 3000 rows (840 tiles), 166 and 154 us, its down product
@@ -511,35 +481,26 @@ __global__ __launch_bounds__(256) void gemm_rounds_kernel(const bf16_t *__restri
   }
 }
 
-// The SwiGLU product of a 129..256-row batch in ONE launch of one workgroup per compute unit.  Workgroup i
-// computes main tile i (128 x 256, row tiles paired on an XCD as above) with the SwiGLU epilogue.  The
-// columns left over beyond the last full round of tiles, [n_main, N), are cut into 128 x 256 tiles and
-// those along K into `rem_splits` slices; workgroup i also takes slice i % rem_splits of tile
-// i / rem_splits and writes its fp32 partial sums to ws, as a launch of the plain kernel with that K
-// split would (same slices, same k order); swiglu_reduce_kernel finishes them.  A workgroup that has
-// both runs them back to back through gemm_tile2, the slice's first loads issued under the main tile's
-// last k-steps.  Every unit thus works 56 + 12 k-steps at the 7B shape instead of 256 units 56 and then
-// 160 units 56 more on quarter-size tiles.
-template <int WM, int WN, int AT, int BT, bool COLD>
-__global__ __launch_bounds__(256) void gemm_gu_fused_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
-                                                            bf16_t *__restrict__ mid, float *__restrict__ ws, int M, int N,
-                                                            int K, int n_main, int rem_splits, int rem_ksteps) {
+// The SwiGLU product of a 129..256-row batch in one launch.  Main tiles (128 x 256, row tiles paired on an XCD as above) fill the chip once; the columns left
+// over beyond them, [n_main, N), whose K is added up in slices by batches of fewer rows, are 64 x 128 tiles with the slices added up in the workgroup, ahead of the main
+// tiles: a unit that has one takes its main tile when it is done, and nothing is written and read again.  Bound by what a compute unit gets from the caches (48 KB per k-step at
+// 45 KB/us) in both.  7B shape, 256 / 129 rows: 80 / 81 us; the K slices of the remainder behind the main tiles, written as partial sums for a launch that adds them up, 85 / 85.
+template <int WM, int WN, int AT, int BT, int MODE, bool COLD>
+__global__ __launch_bounds__(256) void gemm_ahead_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W, void *__restrict__ mid, int M, int N,
+                                                         int K, int ksteps, int n_main, int n_ahead) {
   constexpr int BM = WM * AT * 32, BN = WN * BT * 32;
   __shared__ __attribute__((aligned(1024))) bf16_t xs[Tile<WM, WN, AT, BT, false>::LDS];
-  const int nrow = (M + BM - 1) / BM;
-  const int rtileA = (blockIdx.x >> 3) % nrow, ctileA = (blockIdx.x / (8 * nrow)) * 8 + (blockIdx.x & 7);
-  const bool hasA = ctileA * BN < n_main;
-  const int item = blockIdx.x / rem_splits, split = blockIdx.x % rem_splits;
-  const int rem_ctiles = (N - n_main + BN - 1) / BN;
-  const bool hasB = item < rem_ctiles * nrow;
-  const int ctileB = item / nrow, rtileB = item % nrow;
-  if (hasA && hasB)   // uniform for the workgroup
-    gemm_tile2<WM, WN, AT, BT, COLD>(xs, X, W, mid, ws, M, N, K, ctileA * BN, rtileA * BM, n_main, n_main + ctileB * BN,
-                               rtileB * BM, split, rem_ksteps);
-  else if (hasA)
-    gemm_tile<WM, WN, AT, BT, 1, COLD>(xs, X, W, mid, M, N, K, K / BK, ctileA * BN, rtileA * BM, 0, n_main, 0, 0);
-  else if (hasB)
-    gemm_tile<WM, WN, AT, BT, 0, COLD>(xs, X, W, ws, M, N, K, rem_ksteps, n_main + ctileB * BN, rtileB * BM, split, N, N - n_main, n_main);
+  if ((int)blockIdx.x < n_ahead) {   // uniform for the workgroup
+    const int nr = (M + 63) / 64, nc = (N - n_main + 127) / 128, tiles = nr * nc;
+    if ((int)(blockIdx.x >> 3) >= (tiles >> 3) + ((int)(blockIdx.x & 7) < (tiles & 7) ? 1 : 0)) return;   // padding of the grid
+    int rtile, ctile;
+    deal(nr, nc, false, rtile, ctile);
+    gemm_tile<1, 4, 2, 1, MODE, false, true>(xs, X, W, mid, M, N, K, ksteps, n_main + ctile * 128, rtile * 64, 0, N, N, 0);
+    return;
+  }
+  const int nrow = (M + BM - 1) / BM, i = blockIdx.x - n_ahead;
+  const int rtile = (i >> 3) % nrow, ctile = (i / (8 * nrow)) * 8 + (i & 7);
+  if (ctile * BN < n_main) gemm_tile<WM, WN, AT, BT, MODE, COLD>(xs, X, W, mid, M, N, K, K / BK, ctile * BN, rtile * BM, 0, n_main, N, 0);
 }
 
 // The same product in calls of at most one row tile: workgroups
@@ -808,7 +769,7 @@ int gemm_pick_splits(int M, int N, int K) {
 // count exceeds 1 the partial sums go through the workspace and the SwiGLU is applied by a reduction.
 // Launched on their own, no SwiGLU product gained from a K split in the sweeps (64 x 128 tiles fill the
 // chip for narrow batches).  The one split chosen is the column remainder of a wide product at 129..256
-// rows, whose slices ride in the launch of the main tiles (gemm_gu_fused_kernel): 1.2 % of the 7B step.
+// rows, whose slices ride in the launch of the main tiles (gemm_gu_joint_kernel; 129 to 256 rows add them up in the workgroup, gemm_ahead_kernel).
 GemmSplit gemm_pick_split(int M_max, int N, int K, int mode) {
   GemmSplit ks{1, N, 1};
   if (mode == 0) {
@@ -817,7 +778,7 @@ GemmSplit gemm_pick_split(int M_max, int N, int K, int mode) {
   }
   if (M_max > 128 && M_max <= 256 && N >= 128 * 256) {
     // 128 x 256 tiles, two row tiles: what is left over a multiple of 256 tiles is split along K so that
-    // every compute unit gets one slice on top of its main tile (gemm_gu_fused_kernel)
+    // every compute unit gets one slice on top of its main tile
     const int ctiles = (N + 255) / 256, tiles = 2 * ctiles, rem = tiles % 256;
     if (tiles > 256 && rem > 0 && rem <= 96) {
       int best = 1;
@@ -851,12 +812,13 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
   if (mode == 1 && M <= 256 && ks.n_main < N && ks.rem_splits > 1 && ks.splits == 1 && ws) {
     // main tiles and K slices of the remainder in one launch, then the SwiGLU over the slices
     const int rem_ksteps = 4 * ((K / (4 * BK) + ks.rem_splits - 1) / ks.rem_splits);
-    if (M > 128) {   // (256 x 256 tiles beside 256 x 256 slices: 82.7 us, 80.0 so)
-      const int wgs = std::max((ks.n_main / 256 + 7) / 8 * 8 * 2, (N - ks.n_main + 255) / 256 * 2 * ks.rem_splits);
+    if (M > 128) {
+      const int ahead = ((M + 63) / 64 * ((N - ks.n_main + 127) / 128) + 7) / 8 * 8, nrow = (M + 127) / 128;
       with_cold<1>(cold && M >= 192, [&](auto COLD) {
-        hipLaunchKernelGGL((gemm_gu_fused_kernel<1, 4, 4, 2, decltype(COLD)::value>), dim3(wgs), dim3(256), 0, s, x, w, (bf16_t *)y, ws, M,
-                           N, K, ks.n_main, ks.rem_splits, rem_ksteps);
+        hipLaunchKernelGGL((gemm_ahead_kernel<1, 4, 4, 2, 1, decltype(COLD)::value>), dim3(ahead + ((ks.n_main + 255) / 256 + 7) / 8 * 8 * nrow), dim3(256), 0, s, x,
+                           w, y, M, N, K, rem_ksteps, ks.n_main, ahead);
       });
+      return hipGetLastError() == hipSuccess ? 0 : -7;
     } else {
       const int n_tiles = (ks.n_main + 127) / 128;
       const dim3 grid(n_tiles + (N - ks.n_main + 127) / 128 * ks.rem_splits);
@@ -1017,23 +979,13 @@ int64_t gemm_pass_elems(int R, int N, int K, const GemmSplit &ks) {
 }
 
 // The product of a pass of more than 256 rows in gemm_pass_slices(...) slices.
-// 257 to 512 rows of a wide SwiGLU product with a sliced remainder: two row tiles of 256 x 256 main tiles with the remainder's slices behind
-// them, as steps of 129 to 256 rows run, given a workspace for the slices (gemm_workspace_elems).
-// Where the K of a remainder's tile is added up in a workgroup (launch_gemm_folded), it is one long tile more: 7B shape, four layers, a prompt
-// of 260 / 300 / 385 / 450 / 512 tokens 1408 / 1432 / 1513 / 1560 / 1618 us, so 1372 / 1389 / 1450 / 1523 / 1570.  Non-temporal loads change nothing.
+// ws: room for the slices of a SwiGLU product's remainder as steps write them; a call whose room is too small is refused, though passes add them up in the workgroup (7B shape,
+// 257 / 384 / 511 rows, by slices behind 256 x 256 tiles 138 / 125 / 135 us, so 88 / 99 / 126).
 int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, float *ws, int64_t room, int M, int N, int K, int mode, const GemmSplit &ks,
                      bool cold, hipStream_t s) {
-  if (ws && mode == 1 && M > 256 && M <= 512 && ks.splits == 1 && ks.rem_splits > 1 && ks.n_main < N) {
-    if (K % (4 * BK) || N % 64 || ks.n_main < 0 || ks.n_main % 256 || !splits_valid(K, ks.rem_splits)) return -1;
-    if (gemm_workspace_elems(M, N, ks) > room) return -1;
-    if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
-    const int rem_ksteps = 4 * ((K / (4 * BK) + ks.rem_splits - 1) / ks.rem_splits);
-    const int wgs = std::max((ks.n_main / 256 + 7) / 8 * 8 * 2, (N - ks.n_main + 255) / 256 * 2 * ks.rem_splits);
-    hipLaunchKernelGGL((gemm_gu_fused_kernel<1, 4, 8, 2, false>), dim3(wgs), dim3(256), 0, s, x, w, (bf16_t *)y, ws, M, N, K, ks.n_main,
-                       ks.rem_splits, rem_ksteps);
-    if (hipGetLastError() != hipSuccess) return -7;
-    return swiglu_reduce(ws, ks.rem_splits, M, N - ks.n_main, ks.n_main, (bf16_t *)y, N / 2, s);
-  }
+  if (ws && mode == 1 && M > 256 && M <= 512 && ks.splits == 1 && ks.rem_splits > 1 && ks.n_main < N &&
+      (ks.n_main % 256 || gemm_workspace_elems(M, N, ks) > room))
+    return -1;
   const int slices = mode == 0 ? gemm_pass_slices(M, N, K, ks) : 1;
   if (mode == 0 && (int64_t)slices * M * N > room) return -1;
   if (slices == 1) return launch_gemm_folded(x, w, y, M, N, K, mode, ks, cold, s);
