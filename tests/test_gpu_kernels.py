@@ -280,6 +280,29 @@ def test_every_gemm_tile_configuration_against_fp64(cfg):
         got = to_np(y)
         assert np.isnan(got[:, :, :nb]).all() and np.isnan(got[:, :, ne:]).all()       # nothing outside the range
         tol = 1e-4 * (np.sqrt(K) * 0.05 + np.abs(ref[:, nb:ne]))
+@pytest.mark.parametrize("splits", [1, 2])
+def test_swiglu_of_a_saturated_gate_is_the_quotient(splits):
+    """Gates down to where 1 + e^-g is near the largest float (its reciprocal is subnormal), up values that bring the results back among
+    ordinary numbers: within a rounding to bf16 (2^-8) and the exponential's error (2^-24 of an exponent of up to 128, 2^-17) of the definition, by the
+    epilogue and by the reduction over K slices."""
+    F, K = 320, 512
+    coarse, fine = np.linspace(0, -87, F // 32)[:, None].round(), -np.arange(32, dtype=np.float32)[None] / 20
+    w = np.zeros((F // 32, 2, 32, K), np.float32)
+    w[:, 0, :, 0], w[:, 0, :, K // 2] = coarse, synth.bf16_round(np.broadcast_to(fine, (F // 32, 32)).astype(np.float32))
+    up = 2.0 ** np.clip(np.round(-coarse / np.log(2)) - 1, 0, 125)
+    w[:, 1, :, 0] = up
+    gate = (w[:, 0, :, 0].astype(np.float64) + w[:, 0, :, K // 2]).reshape(F)
+    x = np.zeros((1, K), np.float32)
+    x[0, 0] = x[0, K // 2] = 1
+    xd, wd = dev_bf16(x), dev_bf16(pl.operand_order(w.reshape(2 * F, K)))
+    y, ws = torch.full((1, F), float("nan"), device="cuda", dtype=torch.bfloat16), torch.empty(splits * 2 * F, device="cuda")
+    pl.pl_debug_gemm_cfg(8, xd.data_ptr(), wd.data_ptr(), y.data_ptr(), ws.data_ptr(), 1, 2 * F, K, 1, splits, 0, 2 * F, False, 0)
+    torch.cuda.synchronize()
+    assert gate.min() < -88.5
+    want = gate / (1 + np.exp(-gate)) * np.broadcast_to(up, (F // 32, 32)).reshape(F)
+    assert (np.abs(to_np(y)[0] - want) <= (2.0 ** -8 + 2.0 ** -16) * np.abs(want)).all()
+
+
         assert (np.abs(got[:, :, nb:ne].astype(np.float64).sum(0) - ref[:, nb:ne]) <= tol).all(), (splits, nb, ne)
     if cfg in (6, 7):                                 # wavefronts of one column tile in two rows: no gate/up pair
         with pytest.raises(pl.PlError):
