@@ -182,6 +182,29 @@ def test_attention_on_every_route_of_a_launch(n, Hq, Hkv, hd, page, max_ctx):
             assert ok, (b, int(ctx[b]), err)
 
 
+@pytest.mark.parametrize("n,Hq,Hkv,hd,page,max_ctx", [
+    (300, 40, 8, 128, 32, 300),      # one chunk per row
+    (5, 28, 4, 128, 128, 900),       # chunks merged by a launch of their own
+    (212, 28, 4, 128, 64, 480),      # chunks merged by the last workgroup
+    (3, 28, 4, 64, 64, 24000), (17, 8, 2, 32, 32, 2000)])
+def test_attention_divides_by_the_sum_of_the_weights(n, Hq, Hkv, hd, page, max_ctx):
+    """q = 0 makes every weight 1, so sums over an even number of tokens whose values alternate are exact and their means lie half-way between two bf16
+    values (1 + 2^-8 and 1 + 3 2^-8): rounded once, to even, whatever the number of tokens."""
+    pages = -(-max_ctx // page)
+    V = np.empty((pages * page, Hkv, hd), np.float32)
+    V[0::2, :, 0::2], V[1::2, :, 0::2] = 1, 1 + 2.0 ** -7
+    V[0::2, :, 1::2], V[1::2, :, 1::2] = 1 + 2.0 ** -7, 1 + 2.0 ** -6
+    img = np.zeros(pages * Hkv * 2 * page * hd, np.uint16)
+    pl.pl_kv_pack_host(img, np.arange(pages, dtype=np.int32), np.zeros_like(V), V, 0, Hkv, hd, page)
+    pool = torch.from_numpy(img.view(np.int16)).cuda()
+    table = np.broadcast_to(np.arange(pages, dtype=np.int32), (n, pages)).copy()
+    for seed in range(5):
+        ctx = (2 * np.random.default_rng(seed).integers(1, max_ctx // 2 + 1, n)).astype(np.int32)
+        ctx[0] = max_ctx - 2 * seed
+        got = _run_attention(np.zeros((n, Hq, hd), np.float32), pool, table, ctx, Hq, Hkv, hd, page, pages, max_ctx)
+        assert (got[:, :, 0::2] == 1).all() and (got[:, :, 1::2] == 1 + 2.0 ** -6).all(), seed
+
+
 def test_attention_rejects_bad_arguments():
     t = torch.zeros(1 << 16, device="cuda", dtype=torch.bfloat16)
     p = t.data_ptr()
