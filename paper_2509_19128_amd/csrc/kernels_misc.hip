@@ -9,14 +9,31 @@ namespace {
 constexpr int BEGIN_LIST = 512;   // most sequences of a step (threads of the workgroup that builds its list)
 
 
-// Sum over a workgroup of `waves` (at most 16) wavefronts, in a fixed order.
-__device__ inline float block_sum(float v, int waves) {
-  __shared__ float red[16];
-  v = wave_sum(v);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+// Root mean square of a row, inverted.  A row's squares are added up in an order that its length decides: in every group of 64 values (one per lane) lanes
+// 32, 16, ... 1 apart, then the groups in order.  v: the lane's values of N groups, number n * waves + its wavefront; at most G.
+// (The root and the divisions in full: the instruction for an inverted root and a product with 1 / d, each up to an ulp off, are 0.1 to 0.2 us less: 7B shape, 256 rows,
+// four and nine slices 5.3 and 7.7 us under a trace, so 5.6 and 7.8.)
+template <int G, int N>
+__device__ inline float inverse_rms(const float (&v)[N], int waves, int d, float eps) {
+  __shared__ __attribute__((aligned(16))) float red[G];
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    float s = with_xor16(with_xor32(v[n], OpSum{}), OpSum{});
+    s += dpp<DPP_ROR8>(s);
+    s += dpp<DPP_ROR4>(s);   // (what is 8 apart is the same by now)
+    s += dpp<DPP_XOR2>(s);
+    s += dpp<DPP_XOR1>(s);
+    if ((threadIdx.x & 63) == 0) red[n * waves + (threadIdx.x >> 6)] = s;
+  }
   __syncthreads();
-  const int lane = threadIdx.x & 63;
-  return wave_sum(lane < waves ? red[lane] : 0.f);
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < G; i += 4) {
+    const f32x4 r = *(const f32x4 *)&red[i];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ss += i + e < N * waves ? r[e] : 0.f;
+  }
+  return 1.0f / sqrtf(ss / (float)d + eps);
 }
 
 // theta^(-2i/hd), and cos/sin of pos times that: in double so that long positions lose nothing
@@ -111,13 +128,12 @@ __global__ __launch_bounds__(NT) void step_begin_kernel(StepBegin q, AttnParams 
       }
     }
   }
-  float ss = 0.f;
+  float ss[NV] = {};
 #pragma unroll
   for (int k = 0; k < NV; ++k)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) ss += (float)e[k][j] * (float)e[k][j];
-  ss = block_sum(ss, NT / 64);
-  const float r = __builtin_amdgcn_rsqf(ss * q.inv_d + q.eps);
+    for (int j = 0; j < 8; ++j) ss[k] += (float)e[k][j] * (float)e[k][j];
+  const float r = inverse_rms<NV * NT / 64>(ss, NT / 64, q.d, q.eps);
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int at = threadIdx.x + k * NT;
@@ -141,17 +157,18 @@ __global__ __launch_bounds__(NT) void step_begin_kernel(StepBegin q, AttnParams 
 // sum to h (a product that comes as one slice, added up the same way before, gives the same bits).
 // One workgroup per row, NV 16-byte pieces per thread, as many threads as that takes; the row stays in registers between the two passes.
 // Bound by its own chain (a kernel of a graph that does nothing takes 1.7 us): loads, a sum over the row, stores, and by the instructions
-// on the way, so every number of slices has a kernel without branches, the sum goes through lanes, the root is one instruction.  Rows
+// on the way, so every number of slices has a kernel without branches and the sum goes through lanes.  Rows
 // of 3584 floats, nine slices: 1 row 3.7 -> 2.7 us, 64 rows 4.1 -> 3.0, 256 rows 6.7 -> 5.5; of 1536, six slices, 64 rows 2.7 -> 2.0.
-template <int SL, int NV>
-__global__ __launch_bounds__(NV == 1 ? 512 : 1024) void resid_rmsnorm_kernel(float *h, const float *parts, int splits, const bf16_t *g,
-                                                                            bf16_t *a, int n, int d, float inv_d, float eps, int waves) {
+// JOIN: a thread's two pieces count as one of a group's 64 values.
+template <int SL, int NV, bool JOIN>
+__global__ __launch_bounds__(JOIN ? 1024 : 512) void resid_rmsnorm_kernel(float *h, const float *parts, int splits, const bf16_t *g, bf16_t *a, int n,
+                                                                         int d, float eps, int waves) {
   const int row = blockIdx.x, d4 = d >> 2, threads = waves * 64;
   f32x4 *h4 = (f32x4 *)(h + (int64_t)row * d);
   const f32x4 *p4 = (const f32x4 *)(parts + (int64_t)row * d);
   f32x4 v[NV];
   bf16x4 gg[NV];
-  float ss = 0.f;
+  float ss[JOIN ? 1 : NV] = {};
 #pragma unroll
   for (int it = 0; it < NV; ++it) {
     const int idx = threadIdx.x + it * threads;
@@ -160,12 +177,13 @@ __global__ __launch_bounds__(NV == 1 ? 512 : 1024) void resid_rmsnorm_kernel(flo
       gg[it] = ((const bf16x4 *)g)[idx];
       v[it] += sum_slices<SL>(p4 + idx, splits, (int64_t)n * d4);
       h4[idx] = v[it];
+      float sq = v[it][0] * v[it][0];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) ss += v[it][e] * v[it][e];
+      for (int e = 1; e < 4; ++e) sq = __builtin_fmaf(v[it][e], v[it][e], sq);
+      ss[JOIN ? 0 : it] += sq;
     }
   }
-  ss = block_sum(ss, waves);
-  const float r = __builtin_amdgcn_rsqf(ss * inv_d + eps);
+  const float r = inverse_rms<NV == 1 ? 8 : 16>(ss, waves, d, eps);
 #pragma unroll
   for (int it = 0; it < NV; ++it) {
     const int idx = threadIdx.x + it * threads;
@@ -331,13 +349,13 @@ int launch_resid_rmsnorm(float *h, const float *parts, int splits, const bf16_t 
   if (n <= 0) return 0;
   if (d % 256 || d > 8192 || splits < 1) return -1;
   // a piece per thread up to rows of 2048 floats, two beyond (3584 floats, nine slices, 256 rows: 5.6 us by 896 threads, 5.5 by 448)
-  const int nv = d <= 2048 ? 1 : 2, waves = (d / 4 / nv + 63) / 64;
+  const int nv = d <= 2048 ? 1 : 2, waves = d > 4096 ? 16 : (d / 4 / nv + 63) / 64;
   with_slices(splits, [&](auto SL) {
-    auto launch = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3(n), dim3(waves * 64), 0, s, h, parts, splits, g, a, n, d, 1.f / (float)d, eps, waves);
-    };
-    if (nv == 1) launch(resid_rmsnorm_kernel<decltype(SL)::value, 1>);
-    else launch(resid_rmsnorm_kernel<decltype(SL)::value, 2>);
+    constexpr int sl = decltype(SL)::value;
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(n), dim3(waves * 64), 0, s, h, parts, splits, g, a, n, d, eps, waves); };
+    if (nv == 1) launch(resid_rmsnorm_kernel<sl, 1, false>);
+    else if (d <= 4096) launch(resid_rmsnorm_kernel<sl, 2, false>);
+    else launch(resid_rmsnorm_kernel<sl, 2, true>);
   });
   return ok();
 }

@@ -43,7 +43,7 @@ __device__ inline T with_xor16(T v, F op) { return op(v, v); }
 template <typename T, typename F>
 __device__ inline T with_xor32(T v, F op) { return op(v, v); }
 #endif
-constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140, DPP_ROR4 = 0x124, DPP_ROR8 = 0x128;
 struct OpSum { __device__ float operator()(float a, float b) const { return a + b; } };
 struct OpMax {
   __device__ float operator()(float a, float b) const { return fmaxf(a, b); }
@@ -101,7 +101,7 @@ void with_slices(int splits, F f) {
 // (tiny shape, one row, 4.0 -> 3.6 us), but is up to an ulp off, and zero where the divisor is beyond 2^126 (gates below -87.3).
 __device__ inline __bf16 swiglu(float g, float u) {
 #ifdef __HIP_DEVICE_COMPILE__
-  return (__bf16)(g * __builtin_amdgcn_rcpf(1.f + __expf(-g)) * u);
+  return (__bf16)(g / (1.f + __expf(-g)) * u);
 #else
   return (__bf16)0.f;
 #endif
@@ -234,7 +234,7 @@ struct StepBegin {
   int32_t *ctx_len;
   const double *freqs;      // [hd / 2] rotary frequencies (launch_rope_freqs)
   int32_t d, vocab;
-  float inv_d, eps;         // inv_d: 1 / d
+  float eps;
   uint64_t *time;           // null, or where the wall clock goes when the step begins (host)
   // A pass that fetches everything itself: rows of pairs and of the page table as the host has them, and a mark that launch_pass_end hands on.
   const int32_t *pairs_src, *table_src;   // null: they are on the device already

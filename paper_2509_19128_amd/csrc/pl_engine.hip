@@ -522,7 +522,7 @@ int enqueue_begin(pl_engine *e, pl_engine::Work &w, int n, bool prefill, int slo
   sb.page_table = w.pt; sb.embed = base + e->layout.front().offset;
   sb.g = c.n_layers ? layer_weights(e, 0).g1 : base + e->layout[e->layout.size() - 2].offset;
   sb.h = w.h; sb.cs = w.cs; sb.a = w.a; sb.ctx_len = w.ctx_len;
-  sb.freqs = e->freqs; sb.d = c.d_model; sb.vocab = c.vocab; sb.inv_d = 1.f / (float)c.d_model; sb.eps = c.rms_eps;
+  sb.freqs = e->freqs; sb.d = c.d_model; sb.vocab = c.vocab; sb.eps = c.rms_eps;
   if (prefill) { sb.mark = ++e->pass_mark; sb.mark_at = e->pass_mark_d; }
   if (slot >= 0) {
     sb.dst = w.meta(true);

@@ -750,6 +750,37 @@ def test_values_of_a_pass_are_appended_alike_whatever_position_it_begins_at(weig
         e.close()
 
 
+@pytest.mark.parametrize("d", [256, 1536, 2304, 3584, 5120])
+def test_norms_are_rounded_as_ieee_roots_and_divisions_are(d):
+    """Rows of small integers, whose squares add up exactly in any order: the first norm (seen in the cache's values: unit rows in W_v) and the last
+    one (seen in the logits: unit rows in the LM head, products of zero on the way) are numpy's float32 root and divisions, rounded to bf16, bit for
+    bit.  An ulp in the root's inverse moves one in 2^16 results: 1.8 million of d = 1536."""
+    rng = np.random.default_rng(d)
+    m = synth.ModelCfg(1, d, 8, 4, 128, 256, d)
+    w = {k: np.zeros(v, np.float32) for k, v in synth.weight_shapes(m).items()}
+    w["embed"] = (rng.integers(-31, 32, (d, d)) * 2.0 ** rng.integers(-12, 13, (d, 1))).astype(np.float32)
+    g1, gf = (synth.bf16_round(rng.uniform(0.5, 2, d).astype(np.float32)) for _ in range(2))
+    w["l0.g1"], w["l0.g2"], w["gf"] = g1, np.ones(d, np.float32), gf
+    w["l0.wv"][:, :] = np.eye(d, dtype=np.float32)[d - min(d, 512):][np.arange(512) % min(d, 512)]
+    w["lm_head"] = np.eye(d, dtype=np.float32)
+    eng = pl.Engine.from_model(m, max_batch=256, max_context=32, kv_pool_tokens=256 * 32, kv_page_tokens=32, n_weight_buffers=1, seed=1, device=0)
+    eng.load_weights(eng.pack_weights(w, synth.f32_to_bf16_bits))
+    x = w["embed"]
+    inv = np.float32(1) / np.sqrt((x.astype(np.float64) ** 2).sum(1).astype(np.float32) / np.float32(d) + np.float32(m.rms_eps))
+    assert inv.dtype == np.float32
+    first, last = (synth.bf16_round(x * inv[:, None] * g) for g in (g1, gf))
+    for t0 in range(0, min(d, 1280), 256):
+        for r in range(256):
+            assert eng.add_sequence(r, [t0 + r], 1) == r
+        eng.decode_step()
+        assert np.array_equal(eng.debug_get_logits(256), last[t0:t0 + 256])
+        for r in range(256):
+            v = eng.debug_read_kv(r, 0, 1)[1][0].reshape(512)
+            assert np.array_equal(v, first[t0 + r][d - min(d, 512):][np.arange(512) % min(d, 512)]), r
+            eng.retire_sequence(r)
+    eng.close()
+
+
 def test_batched_prefill_under_the_weights_active_at_admission_then_a_swap(weights):
     """A sequence admitted after an update reads its prompt under the new weights, while its
     neighbour keeps the cache computed under the old ones (Sec. 5.1)."""
