@@ -28,8 +28,9 @@ __device__ inline double wave_sum(double v) {
 }
 
 // e^x: 2^(j / 64) from a table, 2^i by the exponent, and e^r - 1 by its power series to r^5 with the next term spread over the even ones
-// (Chebyshev's r^6 on |r| <= ln 2 / 128), which leaves 2^-59.6.  18 fp64 operations where the library's exp has 28: a compute unit with more than its share of tokens
-// is busy with them (1024 sequences 14.4 -> 13.1 us).  At most 1.1 units in the last place: half of one each from the table and the last addition.
+// (Chebyshev's r^6 on |r| <= ln 2 / 128), which leaves 2^-59.6.  19 fp64 operations where the library's exp has 28: a compute unit with more than its share of tokens
+// is busy with them (1024 sequences 14.4 -> 13.6 us).  At most 0.53 units in the last place: half of one from the last addition, 0.01 from the series,
+// 0.02 from what is added to the table's value (with the table rounded to one number, an operation and 0.5 us less, it was 1.0).
 __device__ const double EXP2_64[64] = {
     0x1.0000000000000p+0, 0x1.02c9a3e778061p+0, 0x1.059b0d3158574p+0, 0x1.0874518759bc8p+0,
     0x1.0b5586cf9890fp+0, 0x1.0e3ec32d3d1a2p+0, 0x1.11301d0125b51p+0, 0x1.1429aaea92de0p+0,
@@ -48,20 +49,38 @@ __device__ const double EXP2_64[64] = {
     0x1.d5818dcfba487p+0, 0x1.da9e603db3285p+0, 0x1.dfc97337b9b5fp+0, 0x1.e502ee78b3ff6p+0,
     0x1.ea4afa2a490dap+0, 0x1.efa1bee615a27p+0, 0x1.f50765b6e4540p+0, 0x1.fa7c1819e90d8p+0,
 };
-__device__ inline double exp_table(double x, const double *t) {
+__device__ const double EXP2_64_REST[64] = {   // what the values above lack
+    0x0.0p+0, -0x1.19083535b085dp-56, 0x1.d73e2a475b465p-55, 0x1.186be4bb284ffp-57,
+    0x1.8a62e4adc610bp-54, 0x1.03a1727c57b53p-59, -0x1.6c51039449b3ap-54, -0x1.32fbf9af1369ep-54,
+    -0x1.19041b9d78a76p-55, 0x1.e5b4c7b4968e4p-55, 0x1.e016e00a2643cp-54, 0x1.dc775814a8495p-55,
+    0x1.9b07eb6c70573p-54, 0x1.2bd339940e9d9p-55, 0x1.612e8afad1255p-55, 0x1.0024754db41d5p-54,
+    0x1.6f46ad23182e4p-55, 0x1.32721843659a6p-54, -0x1.63aeabf42eae2p-54, -0x1.5e436d661f5e3p-56,
+    0x1.ada0911f09ebcp-55, -0x1.ef3691c309278p-58, 0x1.89b7a04ef80d0p-59, 0x1.3c1a3b69062f0p-56,
+    0x1.d4397afec42e2p-56, -0x1.4b309d25957e3p-54, -0x1.07abe1db13cadp-55, 0x1.9bb2c011d93adp-54,
+    0x1.6324c054647adp-54, 0x1.ba6f93080e65ep-54, -0x1.383c17e40b497p-54, -0x1.bb60987591c34p-54,
+    -0x1.bdd3413b26456p-54, -0x1.bbe3a683c88abp-57, -0x1.16e4786887a99p-55, -0x1.0245957316dd3p-54,
+    -0x1.41577ee04992fp-55, 0x1.05d02ba15797ep-56, -0x1.d4c1dd41532d8p-54, -0x1.fc6f89bd4f6bap-54,
+    0x1.6e9f156864b27p-54, 0x1.5cc13a2e3976cp-55, -0x1.75fc781b57ebcp-57, -0x1.d185b7c1b85d1p-54,
+    0x1.c7c46b071f2bep-56, -0x1.359495d1cd533p-54, -0x1.d2f6edb8d41e1p-54, 0x1.0fac90ef7fd31p-54,
+    0x1.7a1cd345dcc81p-54, -0x1.2805e3084d708p-57, -0x1.5584f7e54ac3bp-56, 0x1.23dd07a2d9e84p-55,
+    0x1.11065895048ddp-55, 0x1.2884dff483cadp-54, 0x1.503cbd1e949dbp-56, -0x1.cbc3743797a9cp-54,
+    0x1.2ed02d75b3707p-55, 0x1.c2300696db532p-54, -0x1.1a5cd4f184b5cp-54, 0x1.39e8980a9cc8fp-55,
+    -0x1.e9c23179c2893p-54, 0x1.dc7f486a4b6b0p-54, 0x1.9d3e12dd8a18bp-54, 0x1.74853f3a5931ep-55,
+};
+__device__ inline double exp_table(double x, const double *t) {   // t: EXP2_64, then EXP2_64_REST
   x = fmax(fmin(x, 710.0), -746.0);   // infinity and zero beyond; a NaN goes with infinity, as fmin(c, NaN) is c
   const double shifted = __builtin_fma(x, 0x1.71547652b82fep+6, 0x1.8p52), k = shifted - 0x1.8p52;   // k = rint(64 x / ln 2), also in the low bits
   const int n = (int)(uint32_t)__builtin_bit_cast(uint64_t, shifted);
   const double r = __builtin_fma(-k, 0x1.473de6af278edp-40, __builtin_fma(-k, 0x1.62e42fef00000p-7, x));
   const double q = __builtin_fma(__builtin_fma(__builtin_fma(r, 1.0 / 120, 0x1.55557621dbbb3p-5), r, 1.0 / 6), r, 0x1.fffffffffd0bap-2);
   const double p = __builtin_fma(r * r, q, r), e = t[n & 63];
-  return __builtin_ldexp(__builtin_fma(e, p, e), n >> 6);
+  return __builtin_ldexp(e + __builtin_fma(e, p, t[64 + (n & 63)]), n >> 6);
 }
 
 // One workgroup per sequence: tokens [offsets[s], offsets[s + 1]).  A thread takes four tokens with 16-byte accesses wherever the
 // three arrays are aligned alike (the tokens before the first aligned one and after the last go one by one), the loads of its next four under the
 // exponentials of those at hand.  Bound by the compute unit that gets the most tokens (its fp64 exponentials and what it can read): 1024 sequences
-// (4096 tokens on average, 16384 at most) 13.1 us, 9.5 if all were as long as the average; their tokens without sequences 9.4 with the library's
+// (4096 tokens on average, 16384 at most) 13.6 us, 9.5 if all were as long as the average; their tokens without sequences 9.4 with the library's
 // exp.  With that exp 14.4; and with a question per quad whether weights are wanted 15.1; with 1024 threads 15.4; and with no load under way
 // meanwhile 16.5.  Sequences ranked by length, so that long and short ones share a unit: finding the rank takes what the balance gains.
 // A sequence's sums are added up in an order that its own length decides, not the number of sequences in the call: one of more than
@@ -81,8 +100,11 @@ __global__ __launch_bounds__(NT) void is_seq_kernel(const float *__restrict__ lp
                                                     float *__restrict__ w_out, double *__restrict__ seq_sums,
                                                     double *__restrict__ ess_seq) {
   constexpr int V = IS_LANES / NT, NW = IS_LANES / 64;   // lanes of a thread: threadIdx.x + v * NT
-  __shared__ double red[2 * NW], exp2_64[64];
-  if (threadIdx.x < 64) exp2_64[threadIdx.x] = EXP2_64[threadIdx.x];
+  __shared__ double red[2 * NW], exp2_64[128];
+  if (threadIdx.x < 64) {
+    exp2_64[threadIdx.x] = EXP2_64[threadIdx.x];
+    exp2_64[64 + threadIdx.x] = EXP2_64_REST[threadIdx.x];
+  }
   const int s = blockIdx.x;
   const int64_t a = offsets[s], b = offsets[s + 1];
   double s1[V] = {}, s2[V] = {};

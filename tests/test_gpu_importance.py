@@ -107,6 +107,25 @@ def test_a_weight_is_the_exponential_to_the_last_bits():
     assert off.max() <= 2 + (ref[fin][off.argmax()] < 2.3e-308)
 
 
+def test_a_weight_is_as_near_to_the_exponential_as_the_last_addition_allows():
+    """Against 64-bit mantissas, over ordinary results: half a unit in the last place from the rounding of the last addition, 0.03 from what it adds."""
+    rng = np.random.default_rng(9)
+    x = np.concatenate([rng.uniform(-700, 700, 200000), rng.normal(0, 1, 200000), rng.normal(0, 1e-2, 100000), np.arange(-64, 65) * np.log(2) / 64,
+                        (np.arange(-64, 65) + 0.5) * np.log(2) / 64])
+    pi = x.astype(np.float32)
+    mu = (pi.astype(np.float64) - x).astype(np.float32)   # (the kernel's argument is a difference of two floats)
+    n = len(pi)
+    a, b, o = torch.from_numpy(pi).cuda(), torch.from_numpy(mu).cuda(), torch.arange(n + 1, device="cuda")
+    sums, ess, tot = (torch.empty(k, device="cuda", dtype=torch.float64) for k in (2 * n, n, 3))
+    pl.pl_is_ess(a.data_ptr(), b.data_ptr(), o.data_ptr(), n, np.inf, 0, sums.data_ptr(), ess.data_ptr(), tot.data_ptr(), 0)
+    assert np.finfo(np.longdouble).nmant >= 63
+    ref = np.exp(pi.astype(np.longdouble) - mu.astype(np.longdouble))
+    got = sums.cpu().numpy()[::2]
+    off = np.abs(got - ref) / np.spacing(ref.astype(np.float64))
+    print("most units in the last place:", off.max())
+    assert off.max() <= 0.53
+
+
 @pytest.mark.parametrize("with_w", [True, False])
 def test_a_sequences_sums_do_not_depend_on_the_number_of_sequences(with_w):
     """Both sides of the choice of threads (1536 sequences): weights and sums of the same sequences are bit-identical, at the
