@@ -280,29 +280,6 @@ def test_swiglu_of_every_row_count_gives_the_same_rows(F, K):
         assert torch.equal(y[:M], widest[:M]) and bool(y[M].isnan().all()), M
 
 
-CFG_TILES = {0: (32, 256), 1: (64, 256), 2: (128, 256), 3: (64, 128), 4: (128, 128), 5: (256, 128), 6: (64, 64),
-             7: (128, 64), 8: (32, 128), 9: (128, 64), 10: (256, 64), 11: (64, 128), 12: (128, 128), 13: (256, 128), 14: (256, 256)}
-
-
-@pytest.mark.parametrize("cfg", sorted(CFG_TILES))
-def test_every_gemm_tile_configuration_against_fp64(cfg):
-    """Each tile configuration of the kernel on shapes with several row tiles, a ragged last row tile,
-    a column range that starts and ends inside the matrix, with and without a K split; the SwiGLU
-    product also with its K split (partials + reduction)."""
-    rows, cols = CFG_TILES[cfg]
-    rng = np.random.default_rng(100 + cfg)
-    M, N, K = min(2 * rows + 7, 300), 5 * 128, 768
-    x = synth.bf16_round(rng.standard_normal((M, K), dtype=np.float32))
-    w = synth.bf16_round(rng.standard_normal((N, K), dtype=np.float32) * 0.05)
-    xd, wd = dev_bf16(x), dev_bf16(pl.operand_order(w))
-    ref = x.astype(np.float64) @ w.astype(np.float64).T
-    for splits, nb, ne, paired in [(1, 0, N, False), (3, 128, N - 64, False), (1, 64, N, True), (3, 64, N - 32, True)]:
-        y = torch.full((splits, M, N), float("nan"), device="cuda", dtype=torch.float32)
-        pl.pl_debug_gemm_cfg(cfg, xd.data_ptr(), wd.data_ptr(), y.data_ptr(), 0, M, N, K, 0, splits, nb, ne, paired, 0)
-        torch.cuda.synchronize()
-        got = to_np(y)
-        assert np.isnan(got[:, :, :nb]).all() and np.isnan(got[:, :, ne:]).all()       # nothing outside the range
-        tol = 1e-4 * (np.sqrt(K) * 0.05 + np.abs(ref[:, nb:ne]))
 @pytest.mark.parametrize("splits", [1, 2])
 def test_swiglu_of_a_saturated_gate_is_the_quotient(splits):
     """Gates down to where 1 + e^-g is near the largest float (its reciprocal is subnormal), up values that bring the results back among
@@ -326,6 +303,29 @@ def test_swiglu_of_a_saturated_gate_is_the_quotient(splits):
     assert (np.abs(to_np(y)[0] - want) <= (2.0 ** -8 + 2.0 ** -16) * np.abs(want)).all()
 
 
+CFG_TILES = {0: (32, 256), 1: (64, 256), 2: (128, 256), 3: (64, 128), 4: (128, 128), 5: (256, 128), 6: (64, 64),
+             7: (128, 64), 8: (32, 128), 9: (128, 64), 10: (256, 64), 11: (64, 128), 12: (128, 128), 13: (256, 128), 14: (256, 256)}
+
+
+@pytest.mark.parametrize("cfg", sorted(CFG_TILES))
+def test_every_gemm_tile_configuration_against_fp64(cfg):
+    """Each tile configuration of the kernel on shapes with several row tiles, a ragged last row tile,
+    a column range that starts and ends inside the matrix, with and without a K split; the SwiGLU
+    product also with its K split (partials + reduction)."""
+    rows, cols = CFG_TILES[cfg]
+    rng = np.random.default_rng(100 + cfg)
+    M, N, K = min(2 * rows + 7, 300), 5 * 128, 768
+    x = synth.bf16_round(rng.standard_normal((M, K), dtype=np.float32))
+    w = synth.bf16_round(rng.standard_normal((N, K), dtype=np.float32) * 0.05)
+    xd, wd = dev_bf16(x), dev_bf16(pl.operand_order(w))
+    ref = x.astype(np.float64) @ w.astype(np.float64).T
+    for splits, nb, ne, paired in [(1, 0, N, False), (3, 128, N - 64, False), (1, 64, N, True), (3, 64, N - 32, True)]:
+        y = torch.full((splits, M, N), float("nan"), device="cuda", dtype=torch.float32)
+        pl.pl_debug_gemm_cfg(cfg, xd.data_ptr(), wd.data_ptr(), y.data_ptr(), 0, M, N, K, 0, splits, nb, ne, paired, 0)
+        torch.cuda.synchronize()
+        got = to_np(y)
+        assert np.isnan(got[:, :, :nb]).all() and np.isnan(got[:, :, ne:]).all()       # nothing outside the range
+        tol = 1e-4 * (np.sqrt(K) * 0.05 + np.abs(ref[:, nb:ne]))
         assert (np.abs(got[:, :, nb:ne].astype(np.float64).sum(0) - ref[:, nb:ne]) <= tol).all(), (splits, nb, ne)
     if cfg in (6, 7):                                 # wavefronts of one column tile in two rows: no gate/up pair
         with pytest.raises(pl.PlError):
