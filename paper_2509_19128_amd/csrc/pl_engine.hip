@@ -169,7 +169,7 @@ struct pl_engine {
   pl::StepResult *res_h = nullptr;
   uint64_t *pass_mark_d = nullptr;   // mark of the pass that runs
   uint64_t pass_mark = 0;            // of the last one enqueued
-  bool poll = true;                  // such words arrive
+  bool pass_words = true;            // a pass's words arrive
   uint64_t &pass_end_word() { return res_h[cfg.max_batch].token_logprob; }
   uint64_t &pass_begin_word() { return res_h[cfg.max_batch + 1].time; }
   int32_t *tok_h = nullptr;   // the fp32 test build's
@@ -675,36 +675,41 @@ int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false, int 
 // launch took only at a synchronisation.
 constexpr double POLL_MS = 4;
 constexpr uint64_t SYNC_STEPS = 32;
-template <typename F>   // arrived(): everything waited for is there
-int wait_words(pl_engine *e, hipStream_t s, bool synchronise, F arrived) {
+template <typename F>   // arrived(): everything waited for is there; it may still be missing where the stream was waited for
+int wait_words(hipStream_t s, bool poll, F arrived) {
   const double limit = now_ms() + POLL_MS;
-  for (unsigned spins = 1; e->poll && !synchronise && !arrived(); ++spins) {
+  for (unsigned spins = 1; poll; ++spins) {
+    if (arrived()) return PL_OK;
 #if defined(__x86_64__)
     __builtin_ia32_pause();
 #endif
-    if (spins % 256 == 0 && now_ms() > limit) break;
+    poll = spins % 256 || now_ms() <= limit;
   }
-  if (e->poll && !synchronise && arrived()) return PL_OK;
   HIP_TRY(hipStreamSynchronize(s));
-  e->poll = arrived();   // (words that do not come are not waited for again)
   return PL_OK;
 }
-int wait_results(pl_engine *e, int n) {
+// Waits for the results of a step of n rows, which are nowhere but in these words.
+int wait_results(pl_engine *e, int n, bool poll) {
   int r = 0;
-  return wait_words(e, e->s_dec, false, [&] {
+  auto arrived = [&] {
     for (; r < n; ++r)
       if (__atomic_load_n(&e->res_h[r].token_logprob, __ATOMIC_ACQUIRE) == pl::RESULT_PENDING || __atomic_load_n(&e->res_h[r].time, __ATOMIC_ACQUIRE) == pl::RESULT_PENDING)
         return false;
     return __atomic_load_n(&e->res_h[e->cfg.max_batch].time, __ATOMIC_ACQUIRE) != pl::RESULT_PENDING;
-  });
+  };
+  const int rc = wait_words(e->s_dec, poll, arrived);
+  if (rc || arrived()) return rc;
+  return fail(PL_E_HIP, "the step ended, but the results of row %d of %d did not arrive", std::min(r, n - 1), n);
 }
-// Waits for the pass enqueued last, by its mark.  What was enqueued before it on its stream has ended too.
+// Waits for the pass enqueued last, by its mark.  What was enqueued before it on its stream has ended too.  The words carry its time
+// alone: if they do not come, the next pass is waited for without them.
 int wait_pass(pl_engine *e, double *ms) {
   auto in = [&](const uint64_t &word) { return __atomic_load_n(&word, __ATOMIC_ACQUIRE) >> pl::PASS_CLOCK_BITS == (e->pass_mark & (~(uint64_t)0 >> pl::PASS_CLOCK_BITS)); };
   auto both = [&] { return in(e->pass_end_word()) && in(e->pass_begin_word()); };
-  const int rc = wait_words(e, e->wk[1].stream, e->pass_mark % SYNC_STEPS == 0, both);
+  const int rc = wait_words(e->wk[1].stream, e->pass_words && e->pass_mark % SYNC_STEPS, both);
   if (rc) return rc;
-  if (both()) *ms += (double)((e->pass_end_word() - e->pass_begin_word()) & pl::PASS_CLOCK) * pl::WALL_CLOCK_MS;
+  e->pass_words = both();
+  if (e->pass_words) *ms += (double)((e->pass_end_word() - e->pass_begin_word()) & pl::PASS_CLOCK) * pl::WALL_CLOCK_MS;
   return PL_OK;
 }
 
@@ -1395,11 +1400,8 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
     e->pt_unsent = false;
     if (!polled) HIP_TRY(hipEventRecord(e->ev_b, s));
     const double t_enq = now_ms();
-    if (polled) {
-      if ((rc = wait_results(e, n))) return rc;
-    } else {
-      HIP_TRY(hipStreamSynchronize(s));
-    }
+    if (e->f32) HIP_TRY(hipStreamSynchronize(s));
+    else if ((rc = wait_results(e, n, polled))) return rc;
     e->st.host_enqueue_ms += t_enq - t_enter;
     e->st.host_wait_ms += now_ms() - t_enq;
     if (polled) {

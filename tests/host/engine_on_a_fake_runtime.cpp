@@ -1,7 +1,7 @@
 // The engine's host code on a stand-in for the HIP runtime: memory is host memory, streams run in order at once, graphs
 // record and replay, and kernel launches are noted by name.  Of the kernels only what the tests look at happens: the
-// kernel that begins a step applies the page-table changes.  A runtime call can be made to fail, and device memory to be
-// scarce.  Linked with the library's own objects instead of the HIP runtime; built and run by tests/test_host_device.py.
+// kernel that begins a step applies the page-table changes, and the words that the host waits for are written.  A runtime call can be made to
+// fail, device memory to be scarce, and the words to be missing.  Linked with the library's own objects instead of the HIP runtime; built and run by tests/test_host_device.py.
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -30,6 +30,9 @@ struct Launch {
   pl::StepBegin begin;
   pl::AttnParams attn;
   int cap;   // records of the work list that the kernel that begins a step writes
+  pl::SampleParams sample;
+  const uint64_t *mark_at;   // of the kernel that ends a pass
+  uint64_t *end_word;
 };
 std::map<const void *, std::string> names;
 std::map<void *, size_t> device_memory;
@@ -39,6 +42,8 @@ bool capturing = false, copying = true;   // copying: copies and fills happen
 std::vector<Launch> done, captured;
 dim3 call_grid, call_block;
 int products = 0;   // launches whose buffers were looked at
+uint64_t device_clock = 0, step_ticks = 0;   // step_ticks: what passes from the beginning of a step or pass to its end
+bool words_come = true;                      // the kernels' words reach the host
 
 // A device that is behind: nothing enqueued has run until an event behind it (or its stream) is waited for, so the host memory that
 // copies read must stay as it is.
@@ -102,6 +107,18 @@ void run(const Launch &l) {
   done.push_back(l);
   if (l.kernel.find("step_begin_kernel") != std::string::npos && l.begin.updates && l.attn.work)
     for (int i = 0; i < l.begin.updates[0]; ++i) l.begin.page_table[l.begin.updates[2 + 2 * i]] = l.begin.updates[3 + 2 * i];
+  auto word = [](uint64_t *at, uint64_t value) { if (words_come) *at = value; };
+  auto pass_word = [](uint64_t mark) { return mark << pl::PASS_CLOCK_BITS | (device_clock & pl::PASS_CLOCK); };
+  if (l.kernel.find("step_begin_kernel") != std::string::npos) {
+    if (l.begin.time) word(l.begin.time, l.begin.mark_at ? pass_word(l.begin.mark) : device_clock);
+    if (l.begin.mark_at) *l.begin.mark_at = l.begin.mark;
+    device_clock += step_ticks;
+  }
+  if (l.end_word) word(l.end_word, pass_word(*l.mark_at));
+  for (int r = 0; l.sample.results && r < l.sample.n; ++r) {
+    word(&l.sample.results[r].time, device_clock);
+    word(&l.sample.results[r].token_logprob, 5);
+  }
 }
 }  // namespace
 
@@ -116,7 +133,7 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *shared, hi
   return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, hipStream_t) {
-  Launch l{names[f], grid, {}, {}, 0};
+  Launch l{names[f], grid, {}, {}, 0, {}, nullptr, nullptr};
   buffers_fit(l.kernel, args);
   if (l.kernel.find("step_begin_kernel") != std::string::npos) {
     l.begin = *(const pl::StepBegin *)args[0];
@@ -124,6 +141,11 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, 
     l.cap = *(const int *)args[2];
   } else if (l.kernel.find("attn_") != std::string::npos) {
     l.attn = *(const pl::AttnParams *)args[0];
+  } else if (l.kernel.find("sample_") != std::string::npos) {
+    l.sample = *(const pl::SampleParams *)args[0];
+  } else if (l.kernel.find("pass_end_kernel") != std::string::npos) {
+    l.mark_at = *(const uint64_t *const *)args[0];
+    l.end_word = *(uint64_t *const *)args[1];
   }
   if (capturing) captured.push_back(l); else run(l);
   return hipSuccess;
@@ -231,6 +253,31 @@ void early_return() {
     CHECK(table[1] == 2 && table[5] == 3);
     pl_destroy(e);
   }
+}
+
+// A step whose results do not come is an error, however its end was waited for, and leaves its sequences as they were; a pass
+// whose words do not come (they carry its time alone) has read its prompt all the same.
+void missing_words() {
+  pl_engine *e = engine(shape(2, 2, 256, 512));
+  std::vector<int32_t> prompt(20, 3);
+  int32_t slot = -1, read = 0, token = -1, position = -1;
+  CHECK(pl_add_sequence(e, 1, prompt.data(), 20, 200, 1.f, &slot) == PL_OK);
+  words_come = false;
+  CHECK(pl_prefill(e, slot, &read) == PL_OK && read == 19);
+  pl_step_out out{};
+  out.token = &token;
+  out.position = &position;
+  for (int i = 0; i < 70; ++i) {
+    const bool profiled = i % 5 == 3;
+    CHECK(pl_debug_set_profile(e, profiled ? 2 : 0) == PL_OK);
+    pl_stats before{}, after{};
+    words_come = false;
+    CHECK(pl_get_stats(e, &before) == PL_OK && pl_decode_step(e, nullptr, &out) == PL_E_HIP && pl_get_stats(e, &after) == PL_OK);
+    CHECK(after.steps == before.steps && after.tokens_emitted == before.tokens_emitted && before.steps == (uint64_t)i);
+    words_come = true;
+    CHECK(pl_decode_step(e, nullptr, &out) == PL_OK && out.n == 1 && token == 5 && position == 19 + i);
+  }
+  pl_destroy(e);
 }
 
 // A step takes the same attention route whether it is replayed from a graph or launched kernel by kernel.
@@ -450,6 +497,7 @@ void operand_limits() {
 int main(int, char **argv) {
   const std::string test = argv[1];
   if (test == "early_return") early_return();
+  else if (test == "missing_words") missing_words();
   else if (test == "same_route") same_route();
   else if (test == "list_capacity") list_capacity();
   else if (test == "scarce_memory") scarce_memory();
