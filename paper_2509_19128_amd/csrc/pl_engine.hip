@@ -169,6 +169,7 @@ struct pl_engine {
   pl::StepResult *res_h = nullptr;
   uint64_t *pass_mark_d = nullptr;   // mark of the pass that runs
   uint64_t pass_mark = 0;            // of the last one enqueued
+  uint64_t pass_synced = 0;          // of the last one whose end a synchronisation of the stream brought
   bool pass_words = true;            // a pass's words arrive
   uint64_t &pass_end_word() { return res_h[cfg.max_batch].token_logprob; }
   uint64_t &pass_begin_word() { return res_h[cfg.max_batch + 1].time; }
@@ -671,8 +672,8 @@ int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false, int 
 
 // Waits until words that kernels write are in the host's memory (a step's n results).  Polling for the words that the kernels write is 13 us faster than events around the step and
 // hipStreamSynchronize (17 kernels of a graph: 49.6 -> 36.4 us; tiny shape, a step 76 -> 55).  Steps of more than POLL_MS wait for the stream, which is
-// also how an error of the device ends the wait; and one step in SYNC_STEPS is taken with events as before, as the runtime gives back what a
-// launch took only at a synchronisation.
+// also how an error of the device ends the wait; and of SYNC_STEPS steps (passes of either kind) one is waited for by a synchronisation, as the runtime
+// gives back what a launch took only there.
 constexpr double POLL_MS = 4;
 constexpr uint64_t SYNC_STEPS = 32;
 template <typename F>   // arrived(): everything waited for is there; it may still be missing where the stream was waited for
@@ -706,8 +707,10 @@ int wait_results(pl_engine *e, int n, bool poll) {
 int wait_pass(pl_engine *e, double *ms) {
   auto in = [&](const uint64_t &word) { return __atomic_load_n(&word, __ATOMIC_ACQUIRE) >> pl::PASS_CLOCK_BITS == (e->pass_mark & (~(uint64_t)0 >> pl::PASS_CLOCK_BITS)); };
   auto both = [&] { return in(e->pass_end_word()) && in(e->pass_begin_word()); };
-  const int rc = wait_words(e->wk[1].stream, e->pass_words && e->pass_mark % SYNC_STEPS, both);
+  const bool poll = e->pass_words && e->pass_mark - e->pass_synced < SYNC_STEPS;
+  const int rc = wait_words(e->wk[1].stream, poll, both);
   if (rc) return rc;
+  if (!poll) e->pass_synced = e->pass_mark;
   e->pass_words = both();
   if (e->pass_words) *ms += (double)((e->pass_end_word() - e->pass_begin_word()) & pl::PASS_CLOCK) * pl::WALL_CLOCK_MS;
   return PL_OK;

@@ -51,7 +51,7 @@ struct Copy { const char *from; size_t bytes; int at; };
 std::vector<Copy> on_their_way;
 std::map<hipEvent_t, int> recorded;
 bool behind = false;
-int enqueued = 0, finished = 0, waits = 0;
+int enqueued = 0, finished = 0, waits = 0, synchronised = 0;
 size_t table_bytes = 0;   // copies of the page table, whose rows in use stay the same, are not looked at
 
 void finish(int upto) {
@@ -188,7 +188,7 @@ const char *hipGetErrorString(hipError_t) { return "made to fail"; }
 hipError_t hipGetSymbolAddress(void **, const void *) { return hipErrorNotFound; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)malloc(1); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { free((void *)s); return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { finish(enqueued); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { finish(enqueued); ++synchronised; return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
@@ -278,6 +278,30 @@ void missing_words() {
     CHECK(pl_decode_step(e, nullptr, &out) == PL_OK && out.n == 1 && token == 5 && position == 19 + i);
   }
   pl_destroy(e);
+}
+
+// Passes that a caller waits for end by a synchronisation of their stream every so often, however many background passes lie between them.
+void passes_synchronise() {
+  for (int background = 0; background <= 40; ++background) {
+    pl_engine *e = engine(shape(2, 2, 128, 256));
+    std::vector<int32_t> prompt(20, 3);
+    int32_t slot = -1;
+    auto read = [&](bool wait) {
+      CHECK(pl_add_sequence(e, 1, prompt.data(), 20, 4, 1.f, &slot) == PL_OK);
+      CHECK((wait ? pl_prefill(e, slot, nullptr) : pl_prefill_async(e, slot, nullptr)) == PL_OK && pl_retire_sequence(e, slot) == PL_OK);
+    };
+    synchronised = 0;
+    int passes = 0, most = 0;   // most: passes from one synchronisation to the next that a pass in between could have brought
+    for (int i = 0, before = 0; i < 100; ++i) {
+      for (int b = 0; b < background; ++b) read(false);
+      read(true);
+      passes += background + 1;
+      if (synchronised != before) { before = synchronised; passes = 0; }
+      most = passes > most ? passes : most;
+    }
+    CHECK(most < 32);
+    pl_destroy(e);
+  }
 }
 
 // A step takes the same attention route whether it is replayed from a graph or launched kernel by kernel.
@@ -498,6 +522,7 @@ int main(int, char **argv) {
   const std::string test = argv[1];
   if (test == "early_return") early_return();
   else if (test == "missing_words") missing_words();
+  else if (test == "passes_synchronise") passes_synchronise();
   else if (test == "same_route") same_route();
   else if (test == "list_capacity") list_capacity();
   else if (test == "scarce_memory") scarce_memory();
