@@ -171,6 +171,8 @@ struct pl_engine {
   uint64_t pass_mark = 0;            // of the last one enqueued
   uint64_t pass_synced = 0;          // of the last one whose end a synchronisation of the stream brought
   bool pass_words = true;            // a pass's words arrive
+  double last_step_ms = 0, last_pass_ms = 0;   // what the last step, and the last pass that was waited for, took
+  int last_pass_rows = 0;
   uint64_t &pass_end_word() { return res_h[cfg.max_batch].token_logprob; }
   uint64_t &pass_begin_word() { return res_h[cfg.max_batch + 1].time; }
   int32_t *tok_h = nullptr;   // the fp32 test build's
@@ -671,8 +673,8 @@ int run_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false, int 
 }
 
 // Waits until words that kernels write are in the host's memory (a step's n results).  Polling for the words that the kernels write is 13 us faster than events around the step and
-// hipStreamSynchronize (17 kernels of a graph: 49.6 -> 36.4 us; tiny shape, a step 76 -> 55).  Steps of more than POLL_MS wait for the stream, which is
-// also how an error of the device ends the wait; and of SYNC_STEPS steps (passes of either kind) one is waited for by a synchronisation, as the runtime
+// hipStreamSynchronize (17 kernels of a graph: 49.6 -> 36.4 us; tiny shape, a step 76 -> 55).  After POLL_MS the stream is waited for, which is
+// also how an error of the device ends the wait, and from the outset where the last step took so long (a pass: one of as many rows): the caller's core is then free. Of SYNC_STEPS steps (passes of either kind) one is waited for by a synchronisation, as the runtime
 // gives back what a launch took only there.
 constexpr double POLL_MS = 4;
 constexpr uint64_t SYNC_STEPS = 32;
@@ -704,15 +706,20 @@ int wait_results(pl_engine *e, int n, bool poll) {
 }
 // Waits for the pass enqueued last, by its mark.  What was enqueued before it on its stream has ended too.  The words carry its time
 // alone: if they do not come, the next pass is waited for without them.
-int wait_pass(pl_engine *e, double *ms) {
+int wait_pass(pl_engine *e, int rows, double *ms) {
   auto in = [&](const uint64_t &word) { return __atomic_load_n(&word, __ATOMIC_ACQUIRE) >> pl::PASS_CLOCK_BITS == (e->pass_mark & (~(uint64_t)0 >> pl::PASS_CLOCK_BITS)); };
   auto both = [&] { return in(e->pass_end_word()) && in(e->pass_begin_word()); };
-  const bool poll = e->pass_words && e->pass_mark - e->pass_synced < SYNC_STEPS;
+  const double like_last = rows < e->last_pass_rows ? e->last_pass_ms * rows / e->last_pass_rows : e->last_pass_ms;
+  const bool poll = e->pass_words && e->pass_mark - e->pass_synced < SYNC_STEPS && like_last <= POLL_MS;
   const int rc = wait_words(e->wk[1].stream, poll, both);
   if (rc) return rc;
   if (!poll) e->pass_synced = e->pass_mark;
   e->pass_words = both();
-  if (e->pass_words) *ms += (double)((e->pass_end_word() - e->pass_begin_word()) & pl::PASS_CLOCK) * pl::WALL_CLOCK_MS;
+  if (e->pass_words) {
+    e->last_pass_ms = (double)((e->pass_end_word() - e->pass_begin_word()) & pl::PASS_CLOCK) * pl::WALL_CLOCK_MS;
+    e->last_pass_rows = rows;
+    *ms += e->last_pass_ms;
+  }
   return PL_OK;
 }
 
@@ -889,7 +896,7 @@ int run_kv_passes(pl_engine *e, const std::vector<int32_t> &slots, const std::ve
       hipStream_t s = w.stream;
       if (wait) {   // one pass over one slot's rows: no copies ahead of it, no events around it
         int rc = run_step(e, w, n, true, slots[0]);
-        if (!rc) rc = wait_pass(e, ms_total);
+        if (!rc) rc = wait_pass(e, n, ms_total);
         if (rc) return rc;
         ++*passes;
         return PL_OK;
@@ -1391,29 +1398,30 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
     upd[0] = n_upd;
     if (e->f32) HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)w.image_bytes(w.pitch), hipMemcpyHostToDevice, s));
     // the step's own words tell when it began and ended, except where events are wanted anyway
-    const bool polled = !e->f32 && !e->profile && !timed_stall && e->st.steps % SYNC_STEPS;
+    const bool events = e->f32 || e->profile || timed_stall || e->st.steps % SYNC_STEPS == 0;
     if (!e->f32) {
       for (int i = 0; i < n; ++i) e->res_h[i] = pl::StepResult{pl::RESULT_PENDING, pl::RESULT_PENDING};
       e->res_h[c.max_batch].time = pl::RESULT_PENDING;
     }
-    if (!polled) HIP_TRY(hipEventRecord(e->ev_a, s));
+    if (events) HIP_TRY(hipEventRecord(e->ev_a, s));
     e->prof_n = 0;   // a replayed graph records no per-kernel events: nothing of an earlier step may be counted again
     int rc = run_step(e, w, n);
     if (rc) return rc;
     e->pt_unsent = false;
-    if (!polled) HIP_TRY(hipEventRecord(e->ev_b, s));
+    if (events) HIP_TRY(hipEventRecord(e->ev_b, s));
     const double t_enq = now_ms();
     if (e->f32) HIP_TRY(hipStreamSynchronize(s));
-    else if ((rc = wait_results(e, n, polled))) return rc;
+    else if ((rc = wait_results(e, n, !events && e->last_step_ms <= POLL_MS))) return rc;
     e->st.host_enqueue_ms += t_enq - t_enter;
     e->st.host_wait_ms += now_ms() - t_enq;
-    if (polled) {
+    if (events) {
+      HIP_TRY(hipEventElapsedTime(&out->step_ms, e->ev_a, e->ev_b));
+    } else {
       uint64_t end = 0;
       for (int i = 0; i < n; ++i) end = std::max(end, e->res_h[i].time);
       out->step_ms = (float)((double)(end - e->res_h[c.max_batch].time) * pl::WALL_CLOCK_MS);
-    } else {
-      HIP_TRY(hipEventElapsedTime(&out->step_ms, e->ev_a, e->ev_b));
     }
+    e->last_step_ms = out->step_ms;
     for (size_t i = 1; i < e->prof_n; ++i) {
       float ms = 0.f;
       if (hipEventElapsedTime(&ms, e->prof_ev[i - 1], e->prof_ev[i]) != hipSuccess) continue;

@@ -7,6 +7,8 @@
 #include <string.h>
 #include <sys/mman.h>
 
+#include <chrono>
+#include <functional>
 #include <map>
 #include <string>
 #include <vector>
@@ -44,6 +46,8 @@ dim3 call_grid, call_block;
 int products = 0;   // launches whose buffers were looked at
 uint64_t device_clock = 0, step_ticks = 0;   // step_ticks: what passes from the beginning of a step or pass to its end
 bool words_come = true;                      // the kernels' words reach the host
+bool words_late = false;                     // and do so when somebody synchronises
+std::vector<std::function<void()>> late;
 
 // A device that is behind: nothing enqueued has run until an event behind it (or its stream) is waited for, so the host memory that
 // copies read must stay as it is.
@@ -107,7 +111,10 @@ void run(const Launch &l) {
   done.push_back(l);
   if (l.kernel.find("step_begin_kernel") != std::string::npos && l.begin.updates && l.attn.work)
     for (int i = 0; i < l.begin.updates[0]; ++i) l.begin.page_table[l.begin.updates[2 + 2 * i]] = l.begin.updates[3 + 2 * i];
-  auto word = [](uint64_t *at, uint64_t value) { if (words_come) *at = value; };
+  auto word = [](uint64_t *at, uint64_t value) {
+    if (words_come && words_late) late.push_back([=] { *at = value; });
+    else if (words_come) *at = value;
+  };
   auto pass_word = [](uint64_t mark) { return mark << pl::PASS_CLOCK_BITS | (device_clock & pl::PASS_CLOCK); };
   if (l.kernel.find("step_begin_kernel") != std::string::npos) {
     if (l.begin.time) word(l.begin.time, l.begin.mark_at ? pass_word(l.begin.mark) : device_clock);
@@ -188,7 +195,13 @@ const char *hipGetErrorString(hipError_t) { return "made to fail"; }
 hipError_t hipGetSymbolAddress(void **, const void *) { return hipErrorNotFound; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)malloc(1); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { free((void *)s); return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { finish(enqueued); ++synchronised; return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) {
+  finish(enqueued);
+  ++synchronised;
+  for (auto &w : late) w();
+  late.clear();
+  return hipSuccess;
+}
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
@@ -302,6 +315,39 @@ void passes_synchronise() {
     CHECK(most < 32);
     pl_destroy(e);
   }
+}
+
+// Steps and passes like one that took longer than polling lasts are not polled for: the caller's core is free meanwhile.
+void long_waits() {
+  pl_engine *e = engine(shape(2, 4, 1024, 4096));
+  std::vector<int32_t> prompt(901, 3);
+  int32_t slot = -1;
+  auto host_ms = [](auto f) {
+    const auto t0 = std::chrono::steady_clock::now();
+    f();
+    return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
+  };
+  auto pass = [&](int rows) {
+    CHECK(pl_add_sequence(e, 1, prompt.data(), rows + 1, 4, 1.f, &slot) == PL_OK && pl_prefill(e, slot, nullptr) == PL_OK && pl_retire_sequence(e, slot) == PL_OK);
+  };
+  pl_step_out out{};
+  words_late = true;
+  step_ticks = 1000000;   // 10 ms
+  pass(500);
+  CHECK(host_ms([&] { for (int i = 0; i < 30; ++i) pass(500 + i); }) < 60);
+  CHECK(pl_add_sequence(e, 2, prompt.data(), 20, 900, 1.f, &slot) == PL_OK && pl_decode_step(e, nullptr, &out) == PL_OK && pl_decode_step(e, nullptr, &out) == PL_OK);
+  CHECK(out.step_ms == 10.f);
+  CHECK(host_ms([&] { for (int i = 0; i < 28; ++i) CHECK(pl_decode_step(e, nullptr, &out) == PL_OK); }) < 60);
+  // but shorter ones are, also shorter passes than the long one, and no synchronisation ends them
+  words_late = false;
+  step_ticks = 1000;
+  synchronised = 0;
+  CHECK(pl_decode_step(e, nullptr, &out) == PL_OK && out.step_ms < 1 && synchronised == 1);
+  for (int i = 0; i < 50; ++i) CHECK(pl_decode_step(e, nullptr, &out) == PL_OK);
+  pass(100);
+  for (int i = 0; i < 20; ++i) pass(900);
+  CHECK(synchronised <= 1 + 2 + 1);
+  pl_destroy(e);
 }
 
 // A step takes the same attention route whether it is replayed from a graph or launched kernel by kernel.
@@ -523,6 +569,7 @@ int main(int, char **argv) {
   if (test == "early_return") early_return();
   else if (test == "missing_words") missing_words();
   else if (test == "passes_synchronise") passes_synchronise();
+  else if (test == "long_waits") long_waits();
   else if (test == "same_route") same_route();
   else if (test == "list_capacity") list_capacity();
   else if (test == "scarce_memory") scarce_memory();
