@@ -204,7 +204,6 @@ int gemm_pick_splits(int M, int N, int K);
 // A row's result as the host polls for it in pinned memory: both words differ from RESULT_PENDING once they have arrived.
 struct StepResult { uint64_t token_logprob, time; };   // token | log-prob's bits << 32; wall clock
 constexpr uint64_t RESULT_PENDING = ~(uint64_t)0;
-constexpr double WALL_CLOCK_MS = 1e-5;   // of a tick of the constant clock (100 MHz)
 struct SampleParams {
   const float *logits; int32_t n, vocab;
   const uint64_t *seq_id; const int32_t *position; const float *inv_t; const int32_t *forced;

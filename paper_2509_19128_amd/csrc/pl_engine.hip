@@ -171,6 +171,7 @@ struct pl_engine {
   uint64_t pass_mark = 0;            // of the last one enqueued
   uint64_t pass_synced = 0;          // of the last one whose end a synchronisation of the stream brought
   bool pass_words = true;            // a pass's words arrive
+  double tick_ms = 0;                // of the clock in these words
   double last_step_ms = 0, last_pass_ms = 0;   // what the last step, and the last pass that was waited for, took
   int last_pass_rows = 0;
   uint64_t &pass_end_word() { return res_h[cfg.max_batch].token_logprob; }
@@ -335,6 +336,10 @@ constexpr int PASS_RING = 8, PASS_RING_MOST = 48;
 int alloc_device(pl_engine *e) {
   const pl_model_cfg &c = e->cfg;
   HIP_TRY(hipSetDevice(c.device));
+  int khz = 0;
+  HIP_TRY(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, c.device));
+  if (khz <= 0) return fail(PL_E_HIP, "the device does not say how fast its wall clock runs");
+  e->tick_ms = 1.0 / khz;
   HIP_TRY(hipStreamCreateWithFlags(&e->s_dec, hipStreamNonBlocking));
   HIP_TRY(hipStreamCreateWithFlags(&e->s_copy, hipStreamNonBlocking));
   HIP_TRY(hipStreamCreateWithFlags(&e->wk[1].stream, hipStreamNonBlocking));
@@ -716,7 +721,7 @@ int wait_pass(pl_engine *e, int rows, double *ms) {
   if (!poll) e->pass_synced = e->pass_mark;
   e->pass_words = both();
   if (e->pass_words) {
-    e->last_pass_ms = (double)((e->pass_end_word() - e->pass_begin_word()) & pl::PASS_CLOCK) * pl::WALL_CLOCK_MS;
+    e->last_pass_ms = (double)((e->pass_end_word() - e->pass_begin_word()) & pl::PASS_CLOCK) * e->tick_ms;
     e->last_pass_rows = rows;
     *ms += e->last_pass_ms;
   }
@@ -1397,8 +1402,8 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
     }
     upd[0] = n_upd;
     if (e->f32) HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)w.image_bytes(w.pitch), hipMemcpyHostToDevice, s));
-    // the step's own words tell when it began and ended, except where events are wanted anyway
-    const bool events = e->f32 || e->profile || timed_stall || e->st.steps % SYNC_STEPS == 0;
+    // the step's own words tell when it began and ended; events around it where there are no words or the time between kernels is wanted anyway, or its stall
+    const bool words = !e->f32 && !e->profile, events = !words || timed_stall || e->st.steps % SYNC_STEPS == 0;
     if (!e->f32) {
       for (int i = 0; i < n; ++i) e->res_h[i] = pl::StepResult{pl::RESULT_PENDING, pl::RESULT_PENDING};
       e->res_h[c.max_batch].time = pl::RESULT_PENDING;
@@ -1414,12 +1419,12 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
     else if ((rc = wait_results(e, n, !events && e->last_step_ms <= POLL_MS))) return rc;
     e->st.host_enqueue_ms += t_enq - t_enter;
     e->st.host_wait_ms += now_ms() - t_enq;
-    if (events) {
-      HIP_TRY(hipEventElapsedTime(&out->step_ms, e->ev_a, e->ev_b));
-    } else {
+    if (words) {
       uint64_t end = 0;
       for (int i = 0; i < n; ++i) end = std::max(end, e->res_h[i].time);
-      out->step_ms = (float)((double)(end - e->res_h[c.max_batch].time) * pl::WALL_CLOCK_MS);
+      out->step_ms = (float)((double)(end - e->res_h[c.max_batch].time) * e->tick_ms);
+    } else {
+      HIP_TRY(hipEventElapsedTime(&out->step_ms, e->ev_a, e->ev_b));
     }
     e->last_step_ms = out->step_ms;
     for (size_t i = 1; i < e->prof_n; ++i) {

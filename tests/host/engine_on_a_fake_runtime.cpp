@@ -44,6 +44,7 @@ bool capturing = false, copying = true;   // copying: copies and fills happen
 std::vector<Launch> done, captured;
 dim3 call_grid, call_block;
 int products = 0;   // launches whose buffers were looked at
+int clock_khz = 100000;
 uint64_t device_clock = 0, step_ticks = 0;   // step_ticks: what passes from the beginning of a step or pass to its end
 bool words_come = true;                      // the kernels' words reach the host
 bool words_late = false;                     // and do so when somebody synchronises
@@ -190,6 +191,7 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipSt
 hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { CHECK(!capturing); if (copying) memset(d, v, n); return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t a, int) { CHECK(a == hipDeviceAttributeWallClockRate); *v = clock_khz; return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "made to fail"; }
 hipError_t hipGetSymbolAddress(void **, const void *) { return hipErrorNotFound; }
@@ -348,6 +350,26 @@ void long_waits() {
   for (int i = 0; i < 20; ++i) pass(900);
   CHECK(synchronised <= 1 + 2 + 1);
   pl_destroy(e);
+}
+
+// One measure of a step's GPU time, whatever its end was waited for by: from its first kernel to its last result, by the device's own clock.  (The
+// stand-in's events measure nothing.)
+void step_time() {
+  clock_khz = 25000;
+  pl_engine *e = engine(shape(2, 2, 256, 512));
+  step_ticks = 50000;
+  std::vector<int32_t> prompt(20, 3);
+  CHECK(pl_add_sequence(e, 1, prompt.data(), 20, 200, 1.f, nullptr) == PL_OK && pl_prefill(e, 0, nullptr) == PL_OK);
+  pl_step_out out{};
+  for (int i = 0; i < 100; ++i) CHECK(pl_decode_step(e, nullptr, &out) == PL_OK && out.step_ms == 2.f);
+  pl_stats st{};
+  CHECK(pl_get_stats(e, &st) == PL_OK && st.gpu_ms_total == 200. && st.prefill_ms == 2.);
+  CHECK(pl_debug_set_profile(e, 2) == PL_OK && pl_decode_step(e, nullptr, &out) == PL_OK && out.step_ms == 0.f);   // (events: profiled)
+  pl_destroy(e);
+  clock_khz = 0;
+  pl_engine *none = nullptr;
+  const pl_model_cfg c = shape(2, 2, 256, 512);
+  CHECK(pl_create(&c, &none) == PL_E_HIP);
 }
 
 // A step takes the same attention route whether it is replayed from a graph or launched kernel by kernel.
@@ -570,6 +592,7 @@ int main(int, char **argv) {
   else if (test == "missing_words") missing_words();
   else if (test == "passes_synchronise") passes_synchronise();
   else if (test == "long_waits") long_waits();
+  else if (test == "step_time") step_time();
   else if (test == "same_route") same_route();
   else if (test == "list_capacity") list_capacity();
   else if (test == "scarce_memory") scarce_memory();
