@@ -1552,6 +1552,7 @@ int pl_debug_get_logits(pl_engine *e, float *out, int64_t out_elems) {
   if (e->dry) return fail(PL_E_STATE, "bookkeeping-only engine computes no logits");
   if (out_elems < (int64_t)e->last_n * e->cfg.vocab) return fail(PL_E_INVAL, "output buffer too small");
   HIP_TRY(hipSetDevice(e->cfg.device));
+  HIP_TRY(hipStreamSynchronize(e->s_dec));   // (the copy's stream waits for no other, and a step may have been polled for)
   HIP_TRY(hipMemcpy(out, e->logits, (size_t)e->last_n * e->cfg.vocab * 4, hipMemcpyDeviceToHost));
   return PL_OK;
 }

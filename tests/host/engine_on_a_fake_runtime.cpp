@@ -56,7 +56,7 @@ struct Copy { const char *from; size_t bytes; int at; };
 std::vector<Copy> on_their_way;
 std::map<hipEvent_t, int> recorded;
 bool behind = false;
-int enqueued = 0, finished = 0, waits = 0, synchronised = 0;
+int enqueued = 0, finished = 0, waits = 0, synchronised = 0, copied_behind = 0;   // copied_behind: synchronisations before the last hipMemcpy
 size_t table_bytes = 0;   // copies of the page table, whose rows in use stay the same, are not looked at
 
 void finish(int upto) {
@@ -178,7 +178,11 @@ hipError_t hipFree(void *p) {
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = calloc(1, n); ++host_allocations; return hipSuccess; }
 hipError_t hipHostFree(void *p) { free(p); --host_allocations; return hipSuccess; }
 hipError_t hipMemGetInfo(size_t *f, size_t *t) { *f = device_limit - device_used; *t = device_limit; return hipSuccess; }
-hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { if (copying) memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) {
+  copied_behind = synchronised;
+  if (copying) memcpy(d, s, n);
+  return hipSuccess;
+}
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) {
   CHECK(!capturing);
   if (copying) memcpy(d, s, n);
@@ -370,6 +374,21 @@ void step_time() {
   pl_engine *none = nullptr;
   const pl_model_cfg c = shape(2, 2, 256, 512);
   CHECK(pl_create(&c, &none) == PL_E_HIP);
+}
+
+// Logits are copied by a stream that waits for no other: behind a synchronisation of theirs, which a step that was polled for has not had.
+void logits_behind_their_stream() {
+  pl_engine *e = engine(shape(2, 2, 256, 512));
+  std::vector<int32_t> prompt(2, 3);
+  std::vector<float> logits(2 * 512);
+  CHECK(pl_add_sequence(e, 1, prompt.data(), 2, 200, 1.f, nullptr) == PL_OK);
+  pl_step_out out{};
+  for (int i = 0; i < 40; ++i) {
+    CHECK(pl_decode_step(e, nullptr, &out) == PL_OK);
+    const int before = synchronised;
+    CHECK(pl_debug_get_logits(e, logits.data(), 2 * 512) == PL_OK && copied_behind > before);
+  }
+  pl_destroy(e);
 }
 
 // A step takes the same attention route whether it is replayed from a graph or launched kernel by kernel.
@@ -593,6 +612,7 @@ int main(int, char **argv) {
   else if (test == "passes_synchronise") passes_synchronise();
   else if (test == "long_waits") long_waits();
   else if (test == "step_time") step_time();
+  else if (test == "logits_behind_their_stream") logits_behind_their_stream();
   else if (test == "same_route") same_route();
   else if (test == "list_capacity") list_capacity();
   else if (test == "scarce_memory") scarce_memory();
