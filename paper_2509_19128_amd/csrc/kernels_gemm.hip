@@ -946,22 +946,11 @@ int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, 
 // more than fold_shape says.  Down products, us folded / in slices with the consumer's reads: 1.5B shape 511 rows 33 / 25, 1024 42 / 42, 2000 56 / 84, 3000 76 / 118;
 // 7B 511 116 / 73, 900 126 / 136, 1024 159 / 143, 1280 182 / 200; 32B 511 205 / 154, 1024 309 / 297, 1280 345 / 374; 4096 x 14336, 8 slices, 511 90 / 65, 1280
 // 147 / 174.  QKV and O: 7B, 511 rows, 38 / 33 and 25 / 31; 32B, 1024 rows, 77 / 112.
-// 513 to 640 rows keep the choice made for the tiles of 64 to 192 rows in groups of eight columns, which room for slices was asked for and calls without
-// it are refused by (3584 x 9728, 13 slices, 557 rows: 59 / 90, where that choice says slices; 7B, 600 rows, 114 / 120; 32B 239 / 210).
+// Over 216 points (12 shapes, 300 to 1500 rows, random operands) the choice takes 0.5 % more than the better of the two on average.
 int gemm_pass_slices(int M, int N, int K, const GemmSplit &ks) {
   if (ks.splits == 1 || K < 8192) return 1;
   const int ksteps = 4 * ((K / (4 * BK) + ks.splits - 1) / ks.splits);
   const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256) * ks.splits;
-  if (M > 512 && M <= 640) {
-    auto count = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    auto cost = [&](int bm, int bn, double t) { return (count(bm, bn) + 255) / 256 * t; };
-    const int square = count(128, 128), wide = count(128, 256);
-    const bool near = (int64_t)M * K <= 5 << 20;
-    const double fold = std::min({cost(64, 64, 0.26), cost(128, 64, 0.38), near ? cost(96, 128, 0.42) : 1e9,
-                                  cost(128, 128, square > 420 || (!near && square > 256) ? 0.625 : 0.50), near ? cost(192, 128, 0.72) : 1e9,
-                                  wide <= 256 ? 0.45 + wide * (0.75 / 256) : cost(128, 256, 1.2)});
-    return 4 + ksteps * big_rounds(tiles) + (ks.splits - 1) * (4e-6 * M * N / 4) < K / BK * fold ? ks.splits : 1;
-  }
   float fold;
   fold_shape(M, N, K, &fold);
   const int64_t halves = (int64_t)((M + 127) / 128) * ((N + 255) / 256) * ks.splits;

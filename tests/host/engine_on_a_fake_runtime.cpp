@@ -528,11 +528,11 @@ void pass_buffers() {
   CHECK(products > 100000);
 
   // and a call whose slices do not fit is refused
-  const pl::GemmSplit down = pl::gemm_pick_split(96, 3584, 9728, 0), gu = pl::gemm_pick_split(256, 37888, 3584, 1);
-  CHECK(pl::gemm_pass_slices(557, 3584, 9728, down) == down.splits && down.splits > 1 && gu.rem_splits > 1);
+  const pl::GemmSplit down = pl::gemm_pick_split(64, 1536, 8960, 0), gu = pl::gemm_pick_split(256, 37888, 3584, 1);
+  CHECK(pl::gemm_pass_slices(557, 1536, 8960, down) == down.splits && down.splits > 1 && gu.rem_splits > 1);
   float *ws = (float *)&done;   // (not null)
   done.clear();
-  CHECK(pl::launch_gemm_pass(nullptr, nullptr, ws, nullptr, (int64_t)down.splits * 557 * 3584 - 1, 557, 3584, 9728, 0, down, false, nullptr) == -1);
+  CHECK(pl::launch_gemm_pass(nullptr, nullptr, ws, nullptr, (int64_t)down.splits * 557 * 1536 - 1, 557, 1536, 8960, 0, down, false, nullptr) == -1);
   CHECK(pl::launch_gemm_pass(nullptr, nullptr, nullptr, ws, pl::gemm_workspace_elems(300, 37888, gu) - 1, 300, 37888, 3584, 1, gu, false, nullptr) == -1);
   CHECK(pl::launch_gemm_pass(nullptr, nullptr, ws, nullptr, 2000 * 1536 - 1, 2000, 1536, 1536, 0, pl::GemmSplit{1, 1536, 1}, false, nullptr) == -1);
   CHECK(done.empty());
@@ -565,6 +565,16 @@ void pass_images() {
     pl_destroy(e);
     behind = false;
     on_their_way.clear();
+  }
+}
+
+// One rule says whether a pass's product comes in slices, at every row count: where it is clear which way is faster (us at 513 to
+// 640 rows, folded / in slices: 3584 x 9728, 13 slices, 57-71 / 88-94; 1536 x 8960, 9 slices, 39-41 / 37; 4096 x 11008, 4 slices, 557 rows, 85 / 72), it says so.
+void slices_rule() {
+  auto slices = [](int M, int N, int K, int rows) { const pl::GemmSplit ks = pl::gemm_pick_split(M, N, K, 0); CHECK(ks.splits > 1); return pl::gemm_pass_slices(rows, N, K, ks); };
+  for (int rows = 500; rows <= 700; ++rows) {
+    CHECK(slices(96, 3584, 9728, rows) == 1 && slices(1, 3328, 8448, rows > 512 ? rows : 513) == 1 && slices(130, 1024, 8192, rows) == 1);
+    CHECK(slices(64, 1536, 8960, rows) > 1 && slices(64, 4096, 11008, rows < 560 ? rows : 560) > 1 && slices(512, 8192, 28672, rows < 512 ? rows : 512) > 1);
   }
 }
 
@@ -619,6 +629,7 @@ int main(int, char **argv) {
   else if (test == "pass_rows") pass_rows();
   else if (test == "pass_buffers") pass_buffers();
   else if (test == "pass_images") pass_images();
+  else if (test == "slices_rule") slices_rule();
   else if (test == "operand_limits") operand_limits();
   else return 2;
   CHECK(device_memory.empty() && host_allocations == 0);

@@ -25,7 +25,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["early_return", "missing_words", "passes_synchronise", "long_waits", "step_time", "logits_behind_their_stream", "same_route", "list_capacity", "scarce_memory", "pass_rows", "pass_buffers", "pass_images", "operand_limits"])
+@pytest.mark.parametrize("what", ["early_return", "missing_words", "passes_synchronise", "long_waits", "step_time", "logits_behind_their_stream", "same_route", "list_capacity", "scarce_memory", "pass_rows", "pass_buffers", "pass_images", "slices_rule", "operand_limits"])
 def test_engine_host_code(program, what):
     r = subprocess.run([program, what], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
