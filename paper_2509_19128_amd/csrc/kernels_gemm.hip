@@ -809,8 +809,8 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
   if (mode == 0 && ks.n_main != N) return -1;
   if (ks.n_main < 0 || ks.n_main > N) return -1;
   if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
-  if (mode == 1 && M <= 256 && ks.n_main < N && ks.rem_splits > 1 && ks.splits == 1 && ws) {
-    // main tiles and K slices of the remainder in one launch, then the SwiGLU over the slices
+  if (mode == 1 && M <= 256 && ks.n_main < N && ks.rem_splits > 1 && ks.splits == 1 && (ws || M > 128)) {
+    // main tiles and K slices of the remainder in one launch; up to 128 rows the SwiGLU over the slices follows
     const int rem_ksteps = 4 * ((K / (4 * BK) + ks.rem_splits - 1) / ks.rem_splits);
     if (M > 128) {
       const int ahead = ((M + 63) / 64 * ((N - ks.n_main + 127) / 128) + 7) / 8 * 8, nrow = (M + 127) / 128;
@@ -968,13 +968,9 @@ int64_t gemm_pass_elems(int R, int N, int K, const GemmSplit &ks) {
 }
 
 // The product of a pass of more than 256 rows in gemm_pass_slices(...) slices.
-// ws: room for the slices of a SwiGLU product's remainder as steps write them; a call whose room is too small is refused, though passes add them up in the workgroup (7B shape,
-// 257 / 384 / 511 rows, by slices behind 256 x 256 tiles 138 / 125 / 135 us, so 88 / 99 / 126).
-int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, float *ws, int64_t room, int M, int N, int K, int mode, const GemmSplit &ks,
+// Those of a SwiGLU product's remainder are added up in the workgroup (7B shape, 257 / 384 / 511 rows, by slices behind 256 x 256 tiles 138 / 125 / 135 us, so 88 / 99 / 126).
+int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, int64_t room, int M, int N, int K, int mode, const GemmSplit &ks,
                      bool cold, hipStream_t s) {
-  if (ws && mode == 1 && M > 256 && M <= 512 && ks.splits == 1 && ks.rem_splits > 1 && ks.n_main < N &&
-      (ks.n_main % 256 || gemm_workspace_elems(M, N, ks) > room))
-    return -1;
   const int slices = mode == 0 ? gemm_pass_slices(M, N, K, ks) : 1;
   if (mode == 0 && (int64_t)slices * M * N > room) return -1;
   if (slices == 1) return launch_gemm_folded(x, w, y, M, N, K, mode, ks, cold, s);

@@ -184,7 +184,7 @@ int64_t gemm_workspace_elems(int M_max, int N, const GemmSplit &ks);
 // larger than the cache is still mostly there: 271 MB, 76 rows, 45 us against 53 with non-temporal loads).
 inline bool gemm_cold(int64_t bytes) { return bytes > (int64_t)384 << 20; }
 // cold: gemm_cold of all the weights that pass between two uses of this matrix (kernels_gemm.hip: W_CACHE)
-// ws: fp32 workspace of gemm_workspace_elems (mode 1 with split K), else may be null
+// ws: fp32 workspace of gemm_workspace_elems (mode 1 with split K, up to 128 rows), else may be null
 int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int N, int K, int mode,
                 const GemmSplit &ks, bool cold, hipStream_t s);
 // Rows of launch_gemm_folded and of a pass.  A prompt in one pass instead of several has its tiles in few full rounds and its short
@@ -194,8 +194,8 @@ int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, 
                        hipStream_t s);
 int gemm_pass_slices(int M, int N, int K, const GemmSplit &ks);
 int64_t gemm_pass_elems(int R, int N, int K, const GemmSplit &ks);
-// room: fp32 elements of what takes partial sums (mode 0: y, mode 1: ws); -1 where the call would need more
-int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, float *ws, int64_t room, int M, int N, int K, int mode, const GemmSplit &ks,
+// room: fp32 elements that y holds (mode 0); -1 where the call would need more
+int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, int64_t room, int M, int N, int K, int mode, const GemmSplit &ks,
                      bool cold, hipStream_t s);
 int launch_gemm_cfg(int cfg, const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int N, int K, int mode,
                     int splits, int n_begin, int n_end, bool paired, bool cold, hipStream_t s);

@@ -368,9 +368,8 @@ int alloc_device(pl_engine *e) {
     if (e->f32) return R * std::max(wq, 2 * (int64_t)c.d_ffn);   // the fp32 build keeps whole products there
     const int64_t sliced = std::min<int64_t>(R, std::max(B, SLICED_ROWS));
     const int64_t slices = std::max(std::max(std::max(e->ks_qkv.splits * wq, e->ks_o.splits * d), e->ks_d.splits * d) * sliced,
-                                    pl::gemm_workspace_elems((int)sliced, 2 * c.d_ffn, e->ks_gu));
-    return std::max({slices, pl::gemm_workspace_elems((int)std::min<int64_t>(R, 512), 2 * c.d_ffn, e->ks_gu),
-                     pl::gemm_pass_elems((int)R, (int)wq, (int)d, e->ks_qkv), pl::gemm_pass_elems((int)R, (int)d, (int)qd, e->ks_o),
+                                    pl::gemm_workspace_elems((int)std::min<int64_t>(R, 128), 2 * c.d_ffn, e->ks_gu));   // (calls of more rows write no slices of w_gu)
+    return std::max({slices, pl::gemm_pass_elems((int)R, (int)wq, (int)d, e->ks_qkv), pl::gemm_pass_elems((int)R, (int)d, (int)qd, e->ks_o),
                      pl::gemm_pass_elems((int)R, (int)d, c.d_ffn, e->ks_d)});
   };
   // the chunk length is fixed by max_batch alone, so a sequence's attention result never depends on
@@ -561,7 +560,7 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   const bool fold = prefill && n > std::max(c.max_batch, SLICED_ROWS);   // many rows: a product comes in one slice or in all
   const bool cold = pl::gemm_cold(e->streamed_weight_bytes);   // every product's weights pass by once per step
   auto gemm = [&](const bf16_t *x, const bf16_t *wt, void *y, float *ws, int N, int K, int mode, const pl::GemmSplit &ks) {
-    return fold ? pl::launch_gemm_pass(x, wt, y, ws, w.parts_elems, n, N, K, mode, ks, cold, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, cold, s);
+    return fold ? pl::launch_gemm_pass(x, wt, y, w.parts_elems, n, N, K, mode, ks, cold, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, cold, s);
   };
   auto slices = [&](const pl::GemmSplit &ks, int N, int K) { return fold ? pl::gemm_pass_slices(n, N, K, ks) : ks.splits; };
   pl::AttnParams ap = attention_params(e, w, n, prefill);

@@ -532,10 +532,20 @@ void pass_buffers() {
   CHECK(pl::gemm_pass_slices(557, 1536, 8960, down) == down.splits && down.splits > 1 && gu.rem_splits > 1);
   float *ws = (float *)&done;   // (not null)
   done.clear();
-  CHECK(pl::launch_gemm_pass(nullptr, nullptr, ws, nullptr, (int64_t)down.splits * 557 * 1536 - 1, 557, 1536, 8960, 0, down, false, nullptr) == -1);
-  CHECK(pl::launch_gemm_pass(nullptr, nullptr, nullptr, ws, pl::gemm_workspace_elems(300, 37888, gu) - 1, 300, 37888, 3584, 1, gu, false, nullptr) == -1);
-  CHECK(pl::launch_gemm_pass(nullptr, nullptr, ws, nullptr, 2000 * 1536 - 1, 2000, 1536, 1536, 0, pl::GemmSplit{1, 1536, 1}, false, nullptr) == -1);
+  CHECK(pl::launch_gemm_pass(nullptr, nullptr, ws, (int64_t)down.splits * 557 * 1536 - 1, 557, 1536, 8960, 0, down, false, nullptr) == -1);
+  CHECK(pl::launch_gemm_pass(nullptr, nullptr, ws, 2000 * 1536 - 1, 2000, 1536, 1536, 0, pl::GemmSplit{1, 1536, 1}, false, nullptr) == -1);
   CHECK(done.empty());
+
+  // A SwiGLU product with a remainder takes slices of it only where it writes them, at up to 128 rows: more rows are launched without room for any, fewer are not.
+  void *x = nullptr, *w = nullptr, *y = nullptr;
+  CHECK(hipMalloc(&x, 2 * 512 * 3584) == hipSuccess && hipMalloc(&w, 2ll * 37888 * 3584) == hipSuccess && hipMalloc(&y, 512ll * 37888) == hipSuccess);
+  auto bf16 = [](void *p) { return (const bf16_t *)p; };
+  for (int rows : {129, 200, 256}) CHECK(pl::launch_gemm(bf16(x), bf16(w), y, nullptr, rows, 37888, 3584, 1, gu, false, nullptr) == 0);
+  for (int rows : {257, 300, 512}) CHECK(pl::launch_gemm_pass(bf16(x), bf16(w), y, 0, rows, 37888, 3584, 1, gu, false, nullptr) == 0);
+  CHECK(done.size() >= 6);
+  done.clear();
+  CHECK(pl::launch_gemm(bf16(x), bf16(w), y, nullptr, 128, 37888, 3584, 1, gu, false, nullptr) == -1 && done.empty());
+  for (void *p : {x, w, y}) CHECK(hipFree(p) == hipSuccess);
 }
 
 // Background reading does not wait for the device while the host images of its passes fit the pinned memory, and no image is overwritten
@@ -591,7 +601,7 @@ void operand_limits() {
           const pl::GemmSplit ks{splits, N, 1};
           CHECK(pl::launch_gemm(nullptr, nullptr, nullptr, &nothing, rows, N, K, mode, ks, false, nullptr) == -1);
           CHECK(pl::launch_gemm_folded(nullptr, nullptr, nullptr, rows, N, K, mode, ks, false, nullptr) == -1);
-          CHECK(pl::launch_gemm_pass(nullptr, nullptr, nullptr, &nothing, (int64_t)1 << 40, rows, N, K, mode, ks, false, nullptr) == -1);
+          CHECK(pl::launch_gemm_pass(nullptr, nullptr, nullptr, (int64_t)1 << 40, rows, N, K, mode, ks, false, nullptr) == -1);
           CHECK(done.empty());
         }
   }
