@@ -283,7 +283,7 @@ int pl_debug_kv_pool(pl_engine *e, void **device_ptr, int64_t *nbytes);
  * kernel applies the SwiGLU to their sum.  paired != 0 (mode 1: splits = 1 only) lays the grid out so that
  * the row tiles of one column tile and slice run on the same XCD at the same time.  mode | PL_GEMM_COLD (here and in the two
  * launches below) takes the kernels that an engine takes whose weights together do not stay in the last-level cache
- * between two steps, whatever the size of this matrix; the results are the same bits.  PL_E_INVAL (nothing launched)
+ * between two steps, whatever the size of this matrix (pl_debug_gemm_folded: the same kernels); the results are the same bits.  PL_E_INVAL (nothing launched)
  * for shapes the configuration does not cover. */
 int pl_debug_gemm_cfg(int32_t cfg, const void *x, const void *w, void *y, void *ws, int32_t M, int32_t N, int32_t K,
                       int32_t mode, int32_t splits, int32_t n_begin, int32_t n_end, int32_t paired, void *stream);

@@ -887,8 +887,7 @@ constexpr FoldTime PASSES[] = {{128, 256, 11.3f, 0.f, 0.769f, 0.546f, 0.347f},  
 // are saved.  Measured at 1024 rows against four 256-row launches, consumers' reads not counted: QKV / O / gate-up
 // / down of the 1.5B shape 14 / 13 / 73 / 52 against 50 / 43 / 116 / 100 us, of the 7B shape 53 / 37 / 288 / 189
 // against 82 / 71 / 350 / 200 us.
-int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, int K, int mode, const GemmSplit &ks, bool /*cold*/,
-                       hipStream_t s) {
+int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, int K, int mode, const GemmSplit &ks, hipStream_t s) {
   if (M < 1 || M > GEMM_MAX_ROWS || K % (4 * BK) || N % 32 || !splits_valid(K, ks.splits)) return -1;
   if (mode != 0 && mode != 1) return -1;
   if (mode == 1 && (N % 64 || ks.n_main % 64 || !splits_valid(K, ks.rem_splits))) return -1;
@@ -970,10 +969,10 @@ int64_t gemm_pass_elems(int R, int N, int K, const GemmSplit &ks) {
 // The product of a pass of more than 256 rows in gemm_pass_slices(...) slices.
 // Those of a SwiGLU product's remainder are added up in the workgroup (7B shape, 257 / 384 / 511 rows, by slices behind 256 x 256 tiles 138 / 125 / 135 us, so 88 / 99 / 126).
 int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, int64_t room, int M, int N, int K, int mode, const GemmSplit &ks,
-                     bool cold, hipStream_t s) {
+                     hipStream_t s) {
   const int slices = mode == 0 ? gemm_pass_slices(M, N, K, ks) : 1;
   if (mode == 0 && (int64_t)slices * M * N > room) return -1;
-  if (slices == 1) return launch_gemm_folded(x, w, y, M, N, K, mode, ks, cold, s);
+  if (slices == 1) return launch_gemm_folded(x, w, y, M, N, K, mode, ks, s);
   if (M < 1 || M > GEMM_MAX_ROWS || K % (4 * BK) || N % 32 || !splits_valid(K, ks.splits) || ks.n_main != N) return -1;
   if ((int64_t)N * K * 2 >= GEMM_MAX_OPERAND_BYTES || (int64_t)M * K * 2 >= GEMM_MAX_OPERAND_BYTES) return -1;
   const Launch L{x, w, y, M, N, K, 0, ks.splits, 0, N, N, 0, true, false, s};

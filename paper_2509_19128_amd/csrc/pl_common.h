@@ -190,13 +190,12 @@ int launch_gemm(const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int
 // Rows of launch_gemm_folded and of a pass.  A prompt in one pass instead of several has its tiles in few full rounds and its short
 // kernels' fixed time once: 3000 rows of a layer of the 1.5B shape 530 us in three passes of 1000, 475 in one.
 constexpr int GEMM_MAX_ROWS = 4096;
-int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, int K, int mode, const GemmSplit &ks, bool cold,
-                       hipStream_t s);
+int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, int K, int mode, const GemmSplit &ks, hipStream_t s);
 int gemm_pass_slices(int M, int N, int K, const GemmSplit &ks);
 int64_t gemm_pass_elems(int R, int N, int K, const GemmSplit &ks);
 // room: fp32 elements that y holds (mode 0); -1 where the call would need more
 int launch_gemm_pass(const bf16_t *x, const bf16_t *w, void *y, int64_t room, int M, int N, int K, int mode, const GemmSplit &ks,
-                     bool cold, hipStream_t s);
+                     hipStream_t s);
 int launch_gemm_cfg(int cfg, const bf16_t *x, const bf16_t *w, void *y, float *ws, int M, int N, int K, int mode,
                     int splits, int n_begin, int n_end, bool paired, bool cold, hipStream_t s);
 int gemm_pick_splits(int M, int N, int K);

@@ -560,7 +560,7 @@ int enqueue_step(pl_engine *e, pl_engine::Work &w, int n, bool prefill = false) 
   const bool fold = prefill && n > std::max(c.max_batch, SLICED_ROWS);   // many rows: a product comes in one slice or in all
   const bool cold = pl::gemm_cold(e->streamed_weight_bytes);   // every product's weights pass by once per step
   auto gemm = [&](const bf16_t *x, const bf16_t *wt, void *y, float *ws, int N, int K, int mode, const pl::GemmSplit &ks) {
-    return fold ? pl::launch_gemm_pass(x, wt, y, w.parts_elems, n, N, K, mode, ks, cold, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, cold, s);
+    return fold ? pl::launch_gemm_pass(x, wt, y, w.parts_elems, n, N, K, mode, ks, s) : pl::launch_gemm(x, wt, y, ws, n, N, K, mode, ks, cold, s);
   };
   auto slices = [&](const pl::GemmSplit &ks, int N, int K) { return fold ? pl::gemm_pass_slices(n, N, K, ks) : ks.splits; };
   pl::AttnParams ap = attention_params(e, w, n, prefill);
@@ -1783,10 +1783,10 @@ int pl_debug_gemm_planned(const void *x, const void *w, void *y, void *ws, int32
 int pl_debug_gemm_folded(const void *x, const void *w, void *y, int32_t M_max, int32_t M, int32_t N, int32_t K, int32_t mode,
                          void *stream) {
   if (!x || !w || !y) return fail(PL_E_INVAL, "NULL argument");
-  const bool cold = debug_gemm_cold(&mode, N, K);
+  (void)debug_gemm_cold(&mode, N, K);   // (passes have no kernels of their own for cold weights)
   if (M_max < 1 || M_max > 512 || M < 1 || M > pl::GEMM_MAX_ROWS || N < 32 || K < 256 || (mode != 0 && mode != 1))
     return fail(PL_E_INVAL, "unsupported GEMM shape");
-  int rc = pl::launch_gemm_folded((const bf16_t *)x, (const bf16_t *)w, y, M, N, K, mode, pl::gemm_pick_split(M_max, N, K, mode), cold,
+  int rc = pl::launch_gemm_folded((const bf16_t *)x, (const bf16_t *)w, y, M, N, K, mode, pl::gemm_pick_split(M_max, N, K, mode),
                                   (hipStream_t)stream);
   if (rc == -1) return fail(PL_E_INVAL, "unsupported GEMM shape M=%d N=%d K=%d mode=%d", M, N, K, mode);
   if (rc) return fail(PL_E_HIP, "GEMM launch failed");

@@ -532,8 +532,8 @@ void pass_buffers() {
   CHECK(pl::gemm_pass_slices(557, 1536, 8960, down) == down.splits && down.splits > 1 && gu.rem_splits > 1);
   float *ws = (float *)&done;   // (not null)
   done.clear();
-  CHECK(pl::launch_gemm_pass(nullptr, nullptr, ws, (int64_t)down.splits * 557 * 1536 - 1, 557, 1536, 8960, 0, down, false, nullptr) == -1);
-  CHECK(pl::launch_gemm_pass(nullptr, nullptr, ws, 2000 * 1536 - 1, 2000, 1536, 1536, 0, pl::GemmSplit{1, 1536, 1}, false, nullptr) == -1);
+  CHECK(pl::launch_gemm_pass(nullptr, nullptr, ws, (int64_t)down.splits * 557 * 1536 - 1, 557, 1536, 8960, 0, down, nullptr) == -1);
+  CHECK(pl::launch_gemm_pass(nullptr, nullptr, ws, 2000 * 1536 - 1, 2000, 1536, 1536, 0, pl::GemmSplit{1, 1536, 1}, nullptr) == -1);
   CHECK(done.empty());
 
   // A SwiGLU product with a remainder takes slices of it only where it writes them, at up to 128 rows: more rows are launched without room for any, fewer are not.
@@ -541,7 +541,7 @@ void pass_buffers() {
   CHECK(hipMalloc(&x, 2 * 512 * 3584) == hipSuccess && hipMalloc(&w, 2ll * 37888 * 3584) == hipSuccess && hipMalloc(&y, 512ll * 37888) == hipSuccess);
   auto bf16 = [](void *p) { return (const bf16_t *)p; };
   for (int rows : {129, 200, 256}) CHECK(pl::launch_gemm(bf16(x), bf16(w), y, nullptr, rows, 37888, 3584, 1, gu, false, nullptr) == 0);
-  for (int rows : {257, 300, 512}) CHECK(pl::launch_gemm_pass(bf16(x), bf16(w), y, 0, rows, 37888, 3584, 1, gu, false, nullptr) == 0);
+  for (int rows : {257, 300, 512}) CHECK(pl::launch_gemm_pass(bf16(x), bf16(w), y, 0, rows, 37888, 3584, 1, gu, nullptr) == 0);
   CHECK(done.size() >= 6);
   done.clear();
   CHECK(pl::launch_gemm(bf16(x), bf16(w), y, nullptr, 128, 37888, 3584, 1, gu, false, nullptr) == -1 && done.empty());
@@ -600,8 +600,8 @@ void operand_limits() {
           if (mode == 0 || splits == 1) CHECK(pl_gemm_bf16(&nothing, &nothing, &nothing, rows, N, K, mode, splits, nullptr) == PL_E_INVAL);
           const pl::GemmSplit ks{splits, N, 1};
           CHECK(pl::launch_gemm(nullptr, nullptr, nullptr, &nothing, rows, N, K, mode, ks, false, nullptr) == -1);
-          CHECK(pl::launch_gemm_folded(nullptr, nullptr, nullptr, rows, N, K, mode, ks, false, nullptr) == -1);
-          CHECK(pl::launch_gemm_pass(nullptr, nullptr, nullptr, (int64_t)1 << 40, rows, N, K, mode, ks, false, nullptr) == -1);
+          CHECK(pl::launch_gemm_folded(nullptr, nullptr, nullptr, rows, N, K, mode, ks, nullptr) == -1);
+          CHECK(pl::launch_gemm_pass(nullptr, nullptr, nullptr, (int64_t)1 << 40, rows, N, K, mode, ks, nullptr) == -1);
           CHECK(done.empty());
         }
   }

@@ -537,7 +537,8 @@ def test_every_gemm_tile_configuration_for_cold_weights_gives_the_same_bits(cfg)
 @pytest.mark.parametrize("M_max,N,K,mode", [(64, 2048, 1536, 0), (256, 4608, 3584, 0), (256, 3584, 18944, 0), (128, 7168, 5120, 0), (256, 32800, 256, 0),
                                             (64, 2 * 8960, 256, 1), (128, 2 * 27648, 256, 1), (256, 2 * 18944, 768, 1), (256, 2 * 18976, 768, 1)])
 def test_products_of_an_engine_with_cold_weights_give_the_same_bits(M_max, N, K, mode):
-    """The same for the launches of a step (at every row count that chooses another kernel) and of a pass of many rows."""
+    """The same for the launches of a step (at every row count that chooses another kernel); and a pass of many rows, which loads cold weights like
+    others, gives the planned slices added in order."""
     splits, _, _, ws_elems = pl.pl_debug_gemm_plan(M_max, N, K, mode)
     g = torch.Generator(device="cuda").manual_seed(N + K)
     x = torch.empty(1024, K, device="cuda", dtype=torch.bfloat16).normal_(generator=g)
@@ -556,8 +557,20 @@ def test_products_of_an_engine_with_cold_weights_give_the_same_bits(M_max, N, K,
     for M in (1, 20, 33, 64, 65, 128, 129, 200, 256):
         if M <= M_max:
             both(M, splits, lambda y, M, md: pl.pl_debug_gemm_planned(x.data_ptr(), w.data_ptr(), y.data_ptr(), ws.data_ptr(), M_max, M, N, K, md, 0))
+    want = torch.empty(1024, N, device="cuda") if mode == 0 else torch.empty(1024, N // 2, device="cuda", dtype=torch.bfloat16)
+    for r in range(0, 1024, M_max):
+        y = torch.empty(splits, M_max, N, device="cuda") if mode == 0 else want[r:]
+        pl.pl_debug_gemm_planned(x[r:].data_ptr(), w.data_ptr(), y.data_ptr(), ws.data_ptr(), M_max, M_max, N, K, mode | pl.PL_GEMM_COLD, 0)
+        if mode == 0:
+            want[r:r + M_max] = 0
+            for s in range(splits):
+                want[r:r + M_max] += y[s]
+        torch.cuda.synchronize()
     for M in (300, 511, 1024):
-        both(M, 1, lambda y, M, md: pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), M_max, M, N, K, md, 0))
+        y = torch.full_like(want[:M], float("nan"))
+        pl.pl_debug_gemm_folded(x.data_ptr(), w.data_ptr(), y.data_ptr(), M_max, M, N, K, mode | pl.PL_GEMM_COLD, 0)
+        torch.cuda.synchronize()
+        assert torch.equal(y, want[:M]), M
 
 
 @pytest.mark.parametrize("M,N,K,mode,splits", [(130, 66048, 256, 0, 1), (200, 78112, 512, 0, 1), (256, 65600, 768, 1, 1), (256, 131136, 256, 1, 1),
