@@ -412,7 +412,8 @@ def test_plain_products_of_an_engine_are_the_same_for_every_row_count(M_max, N, 
 
 
 @pytest.mark.parametrize("M_max,N,K,mode", [(64, 2048, 1536, 0), (64, 1536, 8960, 0), (256, 4608, 3584, 0), (128, 7168, 5120, 0),
-                                            (2, 96, 256, 0), (64, 2 * 8960, 256, 1), (256, 2 * 18944, 768, 1), (256, 2 * 18976, 768, 1)])
+                                            (2, 96, 256, 0), (64, 2 * 8960, 256, 1), (256, 2 * 18944, 768, 1), (256, 2 * 18976, 768, 1),
+                                            (256, 2 * 18944, 3584, 1)])   # (256 x 256 tiles of the main columns at 511, 1024, 2000 and 4096 rows)
 def test_products_of_many_rows_equal_the_slices_of_few_added_in_order(M_max, N, K, mode):
     """The products of a prompt pass of more than 256 rows add up the K slices in the workgroup: bit-equal to the
     slices a narrow pass of the same engine gives its consumer, added in slice order, at the row counts where a tile or
