@@ -777,8 +777,7 @@ def main():
         "host_ms_per_step": {"enqueue": d["host_enqueue_ms"] / max(d["steps"], 1), "wait_for_gpu": d["host_wait_ms"] / max(d["steps"], 1),
                              "outside_the_engine": (1e3 * wall - d["host_enqueue_ms"] - d["host_wait_ms"]) / max(d["steps"], 1),
                              "gpu_mean": d["gpu_ms_total"] / max(d["steps"], 1)},
-        # by the device's clock, from a step's first kernel to its last result: a few microseconds less per step than events around its launch
-        # (as profiled steps are measured)
+        # by the device's clock, from a step's first kernel to its last result: without the beginning and end of its launch, a few microseconds
         "gpu_ms_per_step_median": med, "gpu_ms_per_step_p99": float(np.percentile(sm, 99)),
         "step_hbm": {"algorithmic_bytes_per_step": d["algorithmic_bytes"] / max(d["steps"], 1),
                      "achieved_GBs": d["algorithmic_bytes"] / max(d["gpu_ms_total"], 1e-9) / 1e6,

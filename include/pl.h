@@ -92,8 +92,8 @@ typedef struct {
   int32_t *position;        /* out: position of the token that was consumed (0-based) */
   uint8_t *emitted;         /* out: 1 if `token` is a generated token, 0 while the prompt is read */
   uint8_t *finished;        /* out: 1 if this was the sequence's last token (max_new reached) */
-  float step_ms;            /* out: GPU time of the step, by the device's clock from its first kernel's beginning to its last result; steps of the
-                               fp32 test build and profiled steps (pl_debug_set_profile): between events around their launches */
+  float step_ms;            /* out: GPU time of the step, by the device's clock from its first kernel's beginning to its last result (fp32 test
+                               build: between events around its launches) */
   float swap_stall_ms;      /* out: time this step spent waiting for a staged weight copy */
 } pl_step_out;
 

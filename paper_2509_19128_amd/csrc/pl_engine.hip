@@ -1401,8 +1401,8 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
     }
     upd[0] = n_upd;
     if (e->f32) HIP_TRY(hipMemcpyAsync(w.meta_d, w.meta_h, (size_t)w.image_bytes(w.pitch), hipMemcpyHostToDevice, s));
-    // the step's own words tell when it began and ended; events around it where there are no words or the time between kernels is wanted anyway, or its stall
-    const bool words = !e->f32 && !e->profile, events = !words || timed_stall || e->st.steps % SYNC_STEPS == 0;
+    // the step's own words tell when it began and ended (the fp32 test build has none: events)
+    const bool events = e->f32 || e->profile || timed_stall || e->st.steps % SYNC_STEPS == 0;
     if (!e->f32) {
       for (int i = 0; i < n; ++i) e->res_h[i] = pl::StepResult{pl::RESULT_PENDING, pl::RESULT_PENDING};
       e->res_h[c.max_batch].time = pl::RESULT_PENDING;
@@ -1418,12 +1418,12 @@ int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out) {
     else if ((rc = wait_results(e, n, !events && e->last_step_ms <= POLL_MS))) return rc;
     e->st.host_enqueue_ms += t_enq - t_enter;
     e->st.host_wait_ms += now_ms() - t_enq;
-    if (words) {
+    if (e->f32) {
+      HIP_TRY(hipEventElapsedTime(&out->step_ms, e->ev_a, e->ev_b));
+    } else {
       uint64_t end = 0;
       for (int i = 0; i < n; ++i) end = std::max(end, e->res_h[i].time);
       out->step_ms = (float)((double)(end - e->res_h[c.max_batch].time) * e->tick_ms);
-    } else {
-      HIP_TRY(hipEventElapsedTime(&out->step_ms, e->ev_a, e->ev_b));
     }
     e->last_step_ms = out->step_ms;
     for (size_t i = 1; i < e->prof_n; ++i) {

@@ -365,10 +365,9 @@ void step_time() {
   std::vector<int32_t> prompt(20, 3);
   CHECK(pl_add_sequence(e, 1, prompt.data(), 20, 200, 1.f, nullptr) == PL_OK && pl_prefill(e, 0, nullptr) == PL_OK);
   pl_step_out out{};
-  for (int i = 0; i < 100; ++i) CHECK(pl_decode_step(e, nullptr, &out) == PL_OK && out.step_ms == 2.f);
+  for (int i = 0; i < 100; ++i) CHECK(pl_debug_set_profile(e, i % 7 == 6 ? 1 + i % 2 : 0) == PL_OK && pl_decode_step(e, nullptr, &out) == PL_OK && out.step_ms == 2.f);
   pl_stats st{};
   CHECK(pl_get_stats(e, &st) == PL_OK && st.gpu_ms_total == 200. && st.prefill_ms == 2.);
-  CHECK(pl_debug_set_profile(e, 2) == PL_OK && pl_decode_step(e, nullptr, &out) == PL_OK && out.step_ms == 0.f);   // (events: profiled)
   pl_destroy(e);
   clock_khz = 0;
   pl_engine *none = nullptr;
