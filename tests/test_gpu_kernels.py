@@ -189,11 +189,13 @@ def test_attention_on_every_route_of_a_launch(n, Hq, Hkv, hd, page, max_ctx):
     (3, 28, 4, 64, 64, 24000), (17, 8, 2, 32, 32, 2000)])
 def test_attention_divides_by_the_sum_of_the_weights(n, Hq, Hkv, hd, page, max_ctx):
     """q = 0 makes every weight 1, so sums over an even number of tokens whose values alternate are exact and their means lie half-way between two bf16
-    values (1 + 2^-8 and 1 + 3 2^-8): rounded once, to even, whatever the number of tokens."""
+    values (1 + 2^-8 and 1 + 3 2^-8): rounded once, to even, whatever the number of tokens; and what is
+    infinite or not a number stays so."""
     pages = -(-max_ctx // page)
     V = np.empty((pages * page, Hkv, hd), np.float32)
     V[0::2, :, 0::2], V[1::2, :, 0::2] = 1, 1 + 2.0 ** -7
     V[0::2, :, 1::2], V[1::2, :, 1::2] = 1 + 2.0 ** -7, 1 + 2.0 ** -6
+    V[0, :, 0], V[1, :, 1], V[0, :, 2], V[1, :, 2], V[0, :, 3] = np.inf, -np.inf, np.inf, -np.inf, np.nan
     img = np.zeros(pages * Hkv * 2 * page * hd, np.uint16)
     pl.pl_kv_pack_host(img, np.arange(pages, dtype=np.int32), np.zeros_like(V), V, 0, Hkv, hd, page)
     pool = torch.from_numpy(img.view(np.int16)).cuda()
@@ -202,7 +204,8 @@ def test_attention_divides_by_the_sum_of_the_weights(n, Hq, Hkv, hd, page, max_c
         ctx = (2 * np.random.default_rng(seed).integers(1, max_ctx // 2 + 1, n)).astype(np.int32)
         ctx[0] = max_ctx - 2 * seed
         got = _run_attention(np.zeros((n, Hq, hd), np.float32), pool, table, ctx, Hq, Hkv, hd, page, pages, max_ctx)
-        assert (got[:, :, 0::2] == 1).all() and (got[:, :, 1::2] == 1 + 2.0 ** -6).all(), seed
+        assert (got[:, :, 4::2] == 1).all() and (got[:, :, 5::2] == 1 + 2.0 ** -6).all(), seed
+        assert (got[:, :, 0] == np.inf).all() and (got[:, :, 1] == -np.inf).all() and np.isnan(got[:, :, 2:4]).all(), seed
 
 
 def test_attention_rejects_bad_arguments():
