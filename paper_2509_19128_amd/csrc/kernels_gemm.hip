@@ -942,9 +942,9 @@ int launch_gemm_folded(const bf16_t *x, const bf16_t *w, void *y, int M, int N, 
 // How many slices a pass of M rows leaves a plain product in: 1 (launch_gemm_folded) or all ks.splits, as a step does.  A long K in one
 // workgroup after the other leaves the chip to small tiles, at half the rate; by slices there are enough 256 x 256
 // tiles (few: 128 x 256), for the price of the slices' way to memory (0.24 us per MB) and back (0.14).  Folded weights that are far (48 MB on) take an eighth
-// more than fold_shape says.  Down products, us folded / in slices with the consumer's reads: 1.5B shape 511 rows 33 / 25, 1024 42 / 42, 2000 56 / 84, 3000 76 / 118;
-// 7B 511 116 / 73, 900 126 / 136, 1024 159 / 143, 1280 182 / 200; 32B 511 205 / 154, 1024 309 / 297, 1280 345 / 374; 4096 x 14336, 8 slices, 511 90 / 65, 1280
-// 147 / 174.  QKV and O: 7B, 511 rows, 38 / 33 and 25 / 31; 32B, 1024 rows, 77 / 112.
+// more than fold_shape says.  Down products with the residual + RMSNorm behind them, random operands, us folded / in slices: 1.5B shape 511 rows 41 / 28, 1024 54 / 46,
+// 1200 56 / 65, 2000 74 / 91, 3000 96 / 133; 7B 511 118 / 76, 900 130 / 139, 1024 165 / 145, 1200 163 / 199, 3000 446 / 463; 32B 511 208 / 145, 1024 320 / 296, 1200
+// 344 / 372, 1500 373 / 455; 4096 x 14336, 8 slices, 511 94 / 69, 1200 136 / 173.  QKV and O: 7B, 511 rows, 38 / 33 and 25 / 31; 32B, 1024 rows, 77 / 112.
 // Over 216 points (12 shapes, 300 to 1500 rows, random operands) the choice takes 0.5 % more than the better of the two on average.
 int gemm_pass_slices(int M, int N, int K, const GemmSplit &ks) {
   if (ks.splits == 1 || K < 8192) return 1;

@@ -11,8 +11,8 @@ constexpr int BEGIN_LIST = 512;   // most sequences of a step (threads of the wo
 
 // Root mean square of a row, inverted.  A row's squares are added up in an order that its length decides: in every group of 64 values (one per lane) lanes
 // 32, 16, ... 1 apart, then the groups in order.  v: the lane's values of N groups, number n * waves + its wavefront; at most G.
-// (The root and the divisions in full: the instruction for an inverted root and a product with 1 / d, each up to an ulp off, are 0.1 to 0.2 us less: 7B shape, 256 rows,
-// four and nine slices 5.3 and 7.7 us under a trace, so 5.6 and 7.8.)
+// (The root and the divisions in full: the instruction for an inverted root and a product with 1 / d, each up to an ulp off, take 0.15 us less at rows of
+// 1536 values and 0.27 at 3584.)
 template <int G, int N>
 __device__ inline float inverse_rms(const float (&v)[N], int waves, int d, float eps) {
   __shared__ __attribute__((aligned(16))) float red[G];
@@ -58,7 +58,7 @@ __global__ void pass_end_kernel(const uint64_t *mark_at, uint64_t *word) {
 // where a copy would be a launch of its own ahead of this one), cos/sin of its position, h = E[token], a = rmsnorm(h) * g.
 // Bound by latency: one round trip to the host's memory (all of what a thread wants from there at once), one to the table or the row, the row's sum.
 // Decode steps, the frequencies' powers taken anew, scans through LDS and 1024 threads: 4 rows of the tiny shape 6.3 us, 64 of the 1.5B shape 7.6, 256 of the
-// 7B shape 13.1; now 4.1, 5.2 and 7.4.
+// 7B shape 13.1; 4.1, 5.2 and 7.4 with an approximate root, which is 0.1 to 0.5 us less than the full one (under a trace 4.8, 7.0 and 11.9, now 4.8, 7.2 and 12.4).
 // ONE: a pass over one slot's rows, whose metadata is the token alone: six reads per row over the bus held 3000 rows of the 1.5B shape up
 // for 33 us, one leaves 14.5 (512 rows of the 7B shape 11.3 -> 10.0).
 template <int NT, int NV, bool ONE>   // NV: pieces of eight elements per thread
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(NT) void step_begin_kernel(StepBegin q, AttnParams 
 // One workgroup per row, NV 16-byte pieces per thread, as many threads as that takes; the row stays in registers between the two passes.
 // Bound by its own chain (a kernel of a graph that does nothing takes 1.7 us): loads, a sum over the row, stores, and by the instructions
 // on the way, so every number of slices has a kernel without branches and the sum goes through lanes.  Rows
-// of 3584 floats, nine slices: 1 row 3.7 -> 2.7 us, 64 rows 4.1 -> 3.0, 256 rows 6.7 -> 5.5; of 1536, six slices, 64 rows 2.7 -> 2.0.
+// of 3584 floats, nine slices: 1 row 3.7 -> 3.0 us, 64 rows 4.1 -> 3.3, 256 rows 6.7 -> 5.8; of 1536, six slices, 64 rows 2.7 -> 2.2.
 // JOIN: a thread's two pieces count as one of a group's 64 values.
 template <int SL, int NV, bool JOIN>
 __global__ __launch_bounds__(JOIN ? 1024 : 512) void resid_rmsnorm_kernel(float *h, const float *parts, int splits, const bf16_t *g, bf16_t *a, int n,
@@ -348,7 +348,7 @@ int launch_resid_rmsnorm(float *h, const float *parts, int splits, const bf16_t 
                          float eps, hipStream_t s) {
   if (n <= 0) return 0;
   if (d % 256 || d > 8192 || splits < 1) return -1;
-  // a piece per thread up to rows of 2048 floats, two beyond (3584 floats, nine slices, 256 rows: 5.6 us by 896 threads, 5.5 by 448)
+  // a piece per thread up to rows of 2048 floats, two beyond, 1024 apart from 4096 on, where they join (the order in which squares are added up depends on it) (3584 floats, nine slices, 256 rows: 5.6 us by 896 threads, 5.5 by 448)
   const int nv = d <= 2048 ? 1 : 2, waves = d > 4096 ? 16 : (d / 4 / nv + 63) / 64;
   with_slices(splits, [&](auto SL) {
     constexpr int sl = decltype(SL)::value;
