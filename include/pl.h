@@ -234,7 +234,8 @@ int32_t pl_num_active(const pl_engine *e);
  * it is what the next step consumes); -1 samples.  Blocks until the step's outputs are in `out`.
  * Sampling is Gumbel-max over logits / T with Philox4x32-10 noise keyed by (seed; seq_id,
  * position, vocabulary index), so a sequence's draws do not depend on its slot or neighbours.
- * PL_E_NOKV if a sequence needs a new page and none is free (nothing is executed). */
+ * PL_E_NOKV if a sequence needs a new page and none is free (nothing is executed); PL_E_HIP also if the
+ * device finished the step but its results did not arrive (no sequence has moved on: the step can be taken again). */
 int pl_decode_step(pl_engine *e, const int32_t *forced, pl_step_out *out);
 
 int pl_get_stats(pl_engine *e, pl_stats *out);
